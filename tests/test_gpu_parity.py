@@ -92,6 +92,27 @@ def test_warp_probs_against_oracle(V):
         assert np.abs(got.sum(axis=1) - 1).max() < 1e-5
 
 
+@pytest.mark.parametrize("k", [2, 127, 128, 129, 255, 512, 513, 1024])
+def test_top_k_cut_at_the_edges_of_the_candidate_set(k):
+    """k on both sides of the sizes at which the search for the cut stops, with ties that are longer than any candidate
+    set, peaked rows and rows of few distinct values."""
+    import paper_2505_15380_amd as ssd
+    from oracle.warp import warp_probs
+    V = 6564
+    rng = np.random.default_rng(k)
+    z = rng.standard_normal((7, V)).astype(np.float32)
+    z[1] = np.round(z[1])                                    # a dozen distinct values
+    z[2, 200:1500] = z[2].max() + 1.0                        # 1300 entries tie at the maximum
+    z[3, 200:1500] = np.sort(z[3])[-20]                      # ... and just below it
+    z[4, 77] = 40.0
+    z[5] = -np.abs(z[5])
+    z[6] = np.where(rng.random(V) < 0.5, 0.0, -0.0).astype(np.float32) + np.float32(1e-30) * z[6]
+    got = ssd.ssd_warp_probs(torch.from_numpy(z).cuda(), ssd.sample_config(top_k=k)).cpu().numpy()
+    ref = warp_probs(z.astype(np.float64), 1.0, k, False)
+    assert ((got > 0) == (ref > 0)).all()
+    assert np.abs(got - ref).max() < 1e-6
+
+
 # ------------------------------------------------------------------------------ the whole verify step
 @pytest.mark.parametrize("beta", [0.0, 0.4])
 def test_tiny_fp32_verify_parity(beta):
