@@ -196,21 +196,71 @@ __device__ __forceinline__ void st_split_value(bf16_t* base, int KT, int row, in
 
 __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-// Make `seq` own the blocks that cover `tokens` positions (one thread).
-__device__ inline void kv_reserve(const KvView& kv, int seq, int tokens) {
-  const int need = ceil_div(tokens, kv.bt);
-  int own = kv.owned[seq];
-  int top = kv.ctl[0];
-  while (own < need) {
-    if (top <= 0 || own >= kv.mbps) { kv.ctl[1] = 1; break; }
-    kv.table[seq * kv.mbps + own] = kv.free_stack[--top];
-    ++own;
+// Exclusive prefix sum of one int per thread over a workgroup of up to 1024 threads; w16: 16 entries of LDS.  Callers that
+// use it twice put a barrier in between.
+__device__ __forceinline__ int block_excl_scan(int v, int* w16, int* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  int inc = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(inc, o, WAVE);
+    if (lane >= o) inc += t;
   }
-  kv.owned[seq] = own;
-  kv.ctl[0] = top;
+  if (lane == 63) w16[wave] = inc;
+  __syncthreads();
+  int base = 0, tot = 0;
+  for (int i = 0; i < nw; ++i) {
+    if (i < wave) base += w16[i];
+    tot += w16[i];
+  }
+  *total = tot;
+  return base + inc - v;
 }
 
-// Truncate `seq` to new_len positions, returning whole blocks past it, highest table index first (one thread).
+// The block bookkeeping of many sequences at once, one thread per sequence (whole workgroup calls; `in`: the thread has a
+// sequence).  Sequences take from and give back to the free stack in ascending order of their thread, exactly as a serial
+// walk over them would: a prefix sum of what the earlier ones take (give) says where on the stack a thread's blocks are.
+// (One thread walking 64 sequences costs a chain of dependent memory round trips per sequence: 50 us and more.)
+//
+// kv_reserve_all: make `seq` own the blocks that cover `tokens` positions.
+__device__ inline void kv_reserve_all(const KvView& kv, bool in, int seq, int tokens, int* w16) {
+  const int own = in ? kv.owned[seq] : 0;
+  const int top = kv.ctl[0];
+  const int need = in ? max(0, ceil_div(tokens, kv.bt) - own) : 0;
+  const int want = min(need, max(0, kv.mbps - own));
+  int total;
+  const int before = block_excl_scan(want, w16, &total);
+  const int take = max(0, min(want, top - before));
+  if (take < need) kv.ctl[1] = KV_ERR_POOL;
+  for (int t = 0; t < take; ++t) kv.table[seq * kv.mbps + own + t] = kv.free_stack[top - before - 1 - t];
+  if (take > 0) kv.owned[seq] = own + take;
+  __syncthreads();                                         // every thread has read the stack's height
+  if (threadIdx.x == 0) kv.ctl[0] = max(0, top - total);
+  __syncthreads();
+}
+
+// kv_truncate_all: truncate `seq` to new_len positions, returning whole blocks past it, highest table index first.
+__device__ inline void kv_truncate_all(const KvView& kv, bool in, int seq, int new_len, int* w16) {
+  const int own = in ? kv.owned[seq] : 0;
+  const int top = kv.ctl[0];
+  const int give = in ? max(0, own - ceil_div(new_len, kv.bt)) : 0;
+  int total;
+  const int before = block_excl_scan(give, w16, &total);
+  for (int t = 0; t < give; ++t) {
+    int32_t* slot = kv.table + seq * kv.mbps + own - 1 - t;
+    kv.free_stack[top + before + t] = *slot;
+    *slot = -1;
+  }
+  if (in) {
+    if (give > 0) kv.owned[seq] = own - give;
+    kv.len[seq] = new_len;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) kv.ctl[0] = top + total;
+  __syncthreads();
+}
+
+// Truncate one sequence (one thread).
 __device__ inline void kv_truncate(const KvView& kv, int seq, int new_len) {
   const int keep = ceil_div(new_len, kv.bt);
   int own = kv.owned[seq];
@@ -229,9 +279,12 @@ __device__ inline void kv_publish_flags(const KvView& kv) {
   kv.mirror[2 * kv.max_seqs] = kv.ctl[1];
   kv.mirror[2 * kv.max_seqs + 1] = (int32_t)*kv.err;
 }
-__device__ inline void kv_publish(const KvView& kv, int seq) {
+__device__ inline void kv_publish_seq(const KvView& kv, int seq) {
   kv.mirror[2 * seq] = kv.len[seq];
   kv.mirror[2 * seq + 1] = kv.n_pend[seq];
+}
+__device__ inline void kv_publish(const KvView& kv, int seq) {
+  kv_publish_seq(kv, seq);
   kv_publish_flags(kv);
 }
 // After a forward: the next launch on this cache gets the next number (one thread, the kernel that follows the forward).

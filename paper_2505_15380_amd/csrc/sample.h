@@ -38,11 +38,13 @@ __global__ void __launch_bounds__(BLOCK) k_embed(EmbedArgs e) {
   if (threadIdx.x == 0) { e.rows.pos[m] = pos; e.rows.active[m] = active; }
   const typename WT::T* src = (const typename WT::T*)e.embed + (size_t)tok * e.d;
   for (int i = threadIdx.x; i < e.d; i += BLOCK) e.h[(size_t)m * e.d + i] = WT::ld(src + i);
-  if (m == 0 && threadIdx.x == 0) {
-    for (int b = 0; b < e.n_seqs; ++b) {
-      const int s = e.rows.seq0 + b;
+  if (m == 0) {
+    __shared__ int w16[16];
+    for (int b0 = 0; b0 < e.n_seqs; b0 += BLOCK) {
+      const bool in = b0 + (int)threadIdx.x < e.n_seqs;
+      const int s = e.rows.seq0 + (in ? b0 + (int)threadIdx.x : 0);
       const int o = e.pcap ? e.pcap - e.kv.n_pend[s] : 0;
-      kv_reserve(e.kv, s, e.kv.len[s] + e.rows.R - o);
+      kv_reserve_all(e.kv, in, s, e.kv.len[s] + e.rows.R - o, w16);
     }
   }
 }
@@ -513,25 +515,32 @@ __device__ __forceinline__ void accept_seq(const AcceptArgs a, const int b, cons
     sh_last = (arrived == a.B - 1);
   }
   __syncthreads();
-  if (!sh_last || tid != 0) return;
+  if (!sh_last) return;                                    // (the whole workgroup)
   __threadfence();
-  *a.ticket = 0;
-  if (a.bump_launch) kv_bump_launch(a.kv);
-  if (a.bump_step && a.step_dev) {
-    const uint64_t nx = step - a.step + 1;
-    ((int32_t*)a.step_dev)[0] = (int32_t)(uint32_t)nx;
-    ((int32_t*)a.step_dev)[1] = (int32_t)(uint32_t)(nx >> 32);
+  const bool failed = *a.kv.err != 0;                      // the forward did not finish: commit nothing
+  if (tid == 0) {
+    *a.ticket = 0;
+    if (a.bump_launch) kv_bump_launch(a.kv);
+    if (a.bump_step && a.step_dev) {
+      const uint64_t nx = step - a.step + 1;
+      ((int32_t*)a.step_dev)[0] = (int32_t)(uint32_t)nx;
+      ((int32_t*)a.step_dev)[1] = (int32_t)(uint32_t)(nx >> 32);
+    }
+    if (failed) kv_publish_flags(a.kv);
   }
-  if (*a.kv.err) { kv_publish_flags(a.kv); return; }        // the forward did not finish: commit nothing
-  for (int s = 0; s < a.B; ++s) {
-    const int sq = a.seq0 + s;
-    const int nn = a.n_acc ? ((volatile int32_t*)a.n_acc)[s] : 0;
-    const int tok = ((volatile int32_t*)a.next_tok)[(size_t)s * a.tok_stride];
-    kv_truncate(a.kv, sq, a.kv.len[sq] + a.kv.n_pend[sq] + nn);
+  if (failed) return;
+  __shared__ int c16[16];
+  const bool in = tid < a.B;                               // one thread per sequence (at most MAX_ROWS = SBLOCK of them)
+  const int sq = a.seq0 + (in ? tid : 0);
+  const int nn = in && a.n_acc ? ((volatile int32_t*)a.n_acc)[tid] : 0;
+  const int tok = in ? ((volatile int32_t*)a.next_tok)[(size_t)tid * a.tok_stride] : 0;
+  kv_truncate_all(a.kv, in, sq, a.kv.len[sq] + a.kv.n_pend[sq] + nn, c16);
+  if (in) {
     a.kv.pend[sq * 2] = tok;
     a.kv.n_pend[sq] = 1;
-    kv_publish(a.kv, sq);
+    kv_publish_seq(a.kv, sq);
   }
+  if (tid == 0) kv_publish_flags(a.kv);
 }
 
 template <int SP>
@@ -571,29 +580,30 @@ __global__ void k_kv_set(KvView kv, int seq, int new_len, int add_len, int set_p
   kv_publish(kv, seq);
 }
 
-// Draft cache after a verification of K drafts (see ssd_kv_follow).
+// Draft cache after a verification of K drafts (see ssd_kv_follow): one workgroup, one thread per sequence.
 __global__ void k_kv_follow(KvView kv, int n_seqs, int K, const int32_t* n_acc, const int32_t* next_tok,
                             const int32_t* x, int32_t* step_dev) {
-  if (threadIdx.x || blockIdx.x) return;
-  if (step_dev) {                                          // last kernel of a captured cycle: the next replay is the next step
+  __shared__ int w16[16];
+  const int s = threadIdx.x;
+  if (step_dev && s == 0) {                                // last kernel of a captured cycle: the next replay is the next step
     const uint64_t nx = ((uint64_t)(uint32_t)step_dev[0] | ((uint64_t)(uint32_t)step_dev[1] << 32)) + 1;
     step_dev[0] = (int32_t)(uint32_t)nx;
     step_dev[1] = (int32_t)(uint32_t)(nx >> 32);
   }
-  if (*kv.err) { kv_publish_flags(kv); return; }
-  for (int s = 0; s < n_seqs; ++s) {
-    const int n = n_acc[s];
-    if (n < K) {
-      kv_truncate(kv, s, kv.len[s] - (K - 1 - n));
-      kv.pend[s * 2] = next_tok[s];
-      kv.n_pend[s] = 1;
-    } else {
-      kv.pend[s * 2] = x[s * K + K - 1];
-      kv.pend[s * 2 + 1] = next_tok[s];
-      kv.n_pend[s] = 2;
-    }
-    kv_publish(kv, s);
+  if (*kv.err) {
+    if (s == 0) kv_publish_flags(kv);
+    return;
   }
+  const bool in = s < n_seqs;
+  const int n = in ? n_acc[s] : 0, len = in ? kv.len[s] : 0;
+  kv_truncate_all(kv, in, s, n < K ? len - (K - 1 - n) : len, w16);
+  if (in) {
+    kv.pend[s * 2] = n < K ? next_tok[s] : x[s * K + K - 1];
+    if (n >= K) kv.pend[s * 2 + 1] = next_tok[s];
+    kv.n_pend[s] = n < K ? 1 : 2;
+    kv_publish_seq(kv, s);
+  }
+  if (s == 0) kv_publish_flags(kv);
 }
 
 __global__ void k_kv_init(KvView kv) {

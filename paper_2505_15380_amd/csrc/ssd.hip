@@ -1213,7 +1213,7 @@ extern "C" int ssd_kv_follow(ssd_kv* kv_d, int n_seqs, int K, const int32_t* dev
     const int rc = kv_check_flags(kv_d);
     if (rc) return rc;
   }
-  hipLaunchKernelGGL(k_kv_follow, dim3(1), dim3(1), 0, (hipStream_t)stream, kv_d->v, n_seqs, K, dev_n_accepted,
+  hipLaunchKernelGGL(k_kv_follow, dim3(1), dim3(cdiv(n_seqs, 64) * 64), 0, (hipStream_t)stream, kv_d->v, n_seqs, K, dev_n_accepted,
                      dev_next_token, dev_draft_tokens, (int32_t*)nullptr);
   LAUNCH_CHECK();
   for (int s = 0; s < n_seqs; ++s) kv_d->npend_ub[s] = 2;       // the length can only have shrunk
@@ -1386,7 +1386,7 @@ static int cycle_capture(ssd_cycle* c, hipStream_t st) {
   if (!rc) rc = step(c->target, c->kv, c->n_seqs, K, c->x, c->pd, &c->cfg, 0, 0, c->n_acc, c->next, 1, nullptr, 0, false,
                      nullptr, st, step_dev, false, true);
   if (!rc) {
-    hipLaunchKernelGGL(k_kv_follow, dim3(1), dim3(1), 0, st, c->kv_d->v, c->n_seqs, K, c->n_acc, c->next, c->x,
+    hipLaunchKernelGGL(k_kv_follow, dim3(1), dim3(cdiv(c->n_seqs, 64) * 64), 0, st, c->kv_d->v, c->n_seqs, K, c->n_acc, c->next, c->x,
                        c->kv->v.ctl + 4);
     if (hipGetLastError() != hipSuccess) rc = fail(SSD_EHIP, "k_kv_follow launch failed");
   }

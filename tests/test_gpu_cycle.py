@@ -499,3 +499,62 @@ def test_verify_of_many_sequences_against_the_oracle(B):
             pair.check_state(b, 2e-2, layers=[shape["n_layers"] - 1])
         pair.check_free_stack()
     assert 0 < worst < 2e-2 and len(set(ns)) > 2
+
+
+def test_bookkeeping_of_more_sequences_than_threads_of_a_small_workgroup():
+    """300 sequences of all lengths around block edges: lengths, block tables and the free stack after a verification and
+    after the draft caches have followed, against the serial allocator model."""
+    from oracle.kv_alloc import PagedAllocator
+    import paper_2505_15380_amd as ssd
+    import synth_inputs as si
+    shape = si.model_shape("mini_bf16")
+    B, K, V = 300, 2, shape["vocab"]
+    model = ssd.Model(shape, ssd.upload_weights(shape, si.make_weights(shape, 150)), 64)
+    rng = np.random.default_rng(5)
+    lens = [1 + b % 35 for b in range(B)]
+    kvs = {cap: ssd.KVCache(model, B, 3, 3 * B, 16, 4, cap) for cap in (1, 2)}
+    allocs = {cap: PagedAllocator(3 * B, 16, B, 4) for cap in (1, 2)}
+    for cap in (1, 2):
+        for b in range(B):
+            ssd.ssd_prefill(model, kvs[cap], b, torch.from_numpy(rng.integers(0, V, lens[b] + 1).astype(np.int32)).cuda())
+            for i in range(0, lens[b], 3):
+                r = min(3, lens[b] - i)
+                allocs[cap].reserve(b, r)
+                allocs[cap].set_length(b, allocs[cap].length[b] + r)
+
+    def check(cap):
+        kv, al = kvs[cap], allocs[cap]
+        free, err = kv.free_stack()
+        assert err == 0 and free == al.free
+        for b in range(0, B, 7):
+            st = kv.state(b)
+            assert st["len"] == al.length[b] and st["table"] == al.table[b][:al.owned[b]]
+
+    check(1)
+    cfg = ssd.sample_config(beta=0.3, seed=3)
+    x = torch.zeros((B, K), dtype=torch.int32, device="cuda")
+    pd = torch.zeros((B, K, V), dtype=torch.float32, device="cuda")
+    for step in range(2):
+        for i in range(K):
+            ssd.ssd_draft_step(model, kvs[2], B, cfg, step, i, x[:, i], K, pd[:, i], K * V)
+        rows = [kvs[2].state(b)["len"] - allocs[2].length[b] for b in range(B)]        # K, or K + 1 after a fully accepted cycle
+        for b in range(B):
+            allocs[2].reserve(b, rows[b] - (K - 1))
+        for b in range(B):
+            allocs[2].set_length(b, allocs[2].length[b] + rows[b] - (K - 1))
+        for b in range(B):
+            allocs[2].reserve(b, K - 1)
+        for b in range(B):
+            allocs[2].set_length(b, allocs[2].length[b] + K - 1)
+        out = ssd.ssd_verify(model, kvs[1], B, x, pd, K, cfg, step)
+        n = out["n_accepted"].cpu().numpy()
+        for b in range(B):
+            allocs[1].reserve(b, K + 1)
+        for b in range(B):
+            allocs[1].set_length(b, allocs[1].length[b] + 1 + int(n[b]))
+        check(1)
+        ssd.ssd_kv_follow(kvs[2], B, K, out["n_accepted"], out["next_token"], x)
+        for b in range(B):
+            if n[b] < K:
+                allocs[2].set_length(b, allocs[2].length[b] - (K - 1 - int(n[b])))
+        check(2)
