@@ -194,6 +194,18 @@ __device__ __forceinline__ void st_split_value(bf16_t* base, int KT, int row, in
   base[i + 512] = f_to_bf16(x - __uint_as_float(h));
 }
 
+// Four consecutive values of a split row: the hi halves and the lo halves as 8 bytes each.
+__device__ __forceinline__ uint2 hi_pairs(const f32x4 v) {             // upper 16 bits of four floats
+  const uint32_t a = __float_as_uint(v[0]), b = __float_as_uint(v[1]), c = __float_as_uint(v[2]), d = __float_as_uint(v[3]);
+  return make_uint2((a >> 16) | (b & 0xFFFF0000u), (c >> 16) | (d & 0xFFFF0000u));
+}
+__device__ __forceinline__ uint2 lo_pairs(const f32x4 v) {             // bf16 of what the upper halves leave over
+  float r[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = v[i] - __uint_as_float(__float_as_uint(v[i]) & 0xFFFF0000u);
+  return make_uint2(f2_to_bf16x2(r[0], r[1]), f2_to_bf16x2(r[2], r[3]));
+}
+
 __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Exclusive prefix sum of one int per thread over a workgroup of up to 1024 threads; w16: 16 entries of LDS.  Callers that

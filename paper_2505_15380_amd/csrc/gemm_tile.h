@@ -1,0 +1,317 @@
+// GEMMs of the decoder for more than 16 rows, Y[M,N] = X[M,Kd] . W[N,Kd]^T on MFMA 16x16x32 bf16 tiles, on operands that
+// are already in fragment order: weights as packed tiles (gemm.h), activations as split rows (common.h: hi and lo bf16
+// halves, 1 KB per fragment).  The weight fragment is the matrix core's first operand, so that an accumulator register
+// group holds four consecutive output features of one row: lane l has row l % 16, features 4 (l / 16) .. + 3 of a tile.
+#pragma once
+#include "gemm.h"
+
+namespace ssd {
+
+// How the output is cut up: blocks of row tiles x blocks of column tiles (x k-slices where the output is k-split
+// partials).  Consecutive workgroup indices go to the eight XCDs in turn; each XCD takes a contiguous run of the order
+// (slice, column block, row block), so that its L2 holds one k range of the activations and each weight is fetched by
+// one XCD.
+struct TilePlan {
+  int n_colb, n_rowb, n_slices, slice_kt;     // slice_kt: k-tiles per workgroup
+  int per_xcd;                                // ceil(workgroups / 8)
+};
+__device__ __forceinline__ bool tile_block(const TilePlan& p, int& colb, int& rowb, int& slice) {
+  const int o = (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3);
+  const int per_slice = p.n_colb * p.n_rowb;
+  slice = o / per_slice;
+  const int rem = o - slice * per_slice;
+  colb = rem / p.n_rowb;
+  rowb = rem - colb * p.n_rowb;
+  return slice < p.n_slices && (int)(blockIdx.x >> 3) < p.per_xcd;
+}
+
+// Column tile of slot j of column group cb (a group has TN slots).  SwiGLU: the first half of the slots from the gate matrix,
+// the second half the same tiles of the up matrix.  QKV: slots j and j + TN/2 hold dims d and d + head_dim/2 of a head, the
+// pairs that the rotary embedding turns.
+template <int EPI, int TN>
+__device__ __forceinline__ int slot_tile(int cb, int j, int hd) {
+  if (EPI == EPI_PARTIAL) return cb * TN + j;
+  const int p = cb * (TN / 2) + (j % (TN / 2));
+  if (EPI == EPI_SWIGLU) return p;
+  const int per_head = hd >> 5;
+  const int head = p / per_head, i = p - head * per_head;
+  return head * (hd >> 4) + i + (j >= TN / 2 ? per_head : 0);
+}
+
+// What the QKV epilogue needs of a row, requested ahead of the contraction.
+struct RowDest {
+  int pos, blk;          // blk < 0: the row's key and value are not stored
+};
+__device__ __forceinline__ RowDest row_dest(const GemmArgs& g, int row) {
+  RowDest d{0, -1};
+  if (row < g.M) {
+    d.pos = g.rows.pos[row];
+    if (g.rows.active[row]) d.blk = g.kv.table[(g.rows.seq0 + row / g.rows.R) * g.kv.mbps + d.pos / g.kv.bt];
+  }
+  return d;
+}
+
+// Epilogue of four consecutive features of one row: tile slot j < TN/2 (v0) and its partner j + TN/2 (v1); for partial
+// outputs two independent tiles.  `col` = 4 (lane / 16).
+template <int EPI>
+__device__ __forceinline__ void tile_epilogue(const GemmArgs& g, int t0, int t1, int slice, int row, int col, f32x4 v0, f32x4 v1,
+                                              const RowDest rd) {
+  const int ntiles = (g.N + 15) >> 4;
+  if (row >= g.M || t0 >= ntiles) return;
+  if (EPI == EPI_PARTIAL) {
+    float* o = g.out + (size_t)slice * g.out_split_stride + (size_t)row * g.ldo;
+    const int n0 = t0 * 16 + col, n1 = t1 * 16 + col;
+    if ((g.N & 3) == 0) {
+      if (n0 < g.N) *(f32x4*)(o + n0) = v0;
+      if (n1 < g.N) *(f32x4*)(o + n1) = v1;
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (n0 + r < g.N) o[n0 + r] = v0[r];
+        if (n1 + r < g.N) o[n1 + r] = v1[r];
+      }
+    }
+  } else if (EPI == EPI_SWIGLU) {
+    f32x4 y;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = v0[r] / (1.0f + expf(-v0[r])) * v1[r];
+    bf16_t* o = (bf16_t*)g.act + split_index(row, t0 * 16 + col, g.act_split_kt);
+    *(uint2*)o = hi_pairs(y);
+    *(uint2*)(o + 512) = lo_pairs(y);
+  } else {
+    const int hd = g.kv.hd, half = hd >> 1, nq = g.nq, nkv = g.kv.nkv;
+    const int n0 = t0 * 16 + col, head = n0 / hd, d = n0 - head * hd;
+    if (g.bias) {
+      const f32x4 b0 = *(const f32x4*)(g.bias + n0), b1 = *(const f32x4*)(g.bias + n0 + half);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) { v0[r] += b0[r]; v1[r] += b1[r]; }
+    }
+    if (head < nq + nkv) {
+      const f32x4* cs = (const f32x4*)(g.rope + (size_t)rd.pos * half + d);
+      const f32x4 c0 = cs[0], c1 = cs[1];
+      const float c[4] = {c0[0], c0[2], c1[0], c1[2]}, s[4] = {c0[1], c0[3], c1[1], c1[3]};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float r0 = v0[r] * c[r] - v1[r] * s[r], r1 = v1[r] * c[r] + v0[r] * s[r];
+        v0[r] = r0; v1[r] = r1;
+      }
+    }
+    if (head < nq) {
+      float* qo = g.q + (size_t)row * nq * hd + head * hd + d;
+      *(f32x4*)qo = v0;
+      *(f32x4*)(qo + half) = v1;
+    } else if (rd.blk >= 0) {
+      const int which = head < nq + nkv ? 0 : 1, kvh = head - nq - which * nkv;
+      bf16_t* base = (bf16_t*)g.kv.pool + kv_offset(g.kv, g.layer, which, rd.blk, kvh, 0);
+      const int tok = rd.pos % g.kv.bt;
+      if (which == 0) {
+        *(uint2*)(base + tok * hd + d) = make_uint2(f2_to_bf16x2(v0[0], v0[1]), f2_to_bf16x2(v0[2], v0[3]));
+        *(uint2*)(base + tok * hd + d + half) = make_uint2(f2_to_bf16x2(v1[0], v1[1]), f2_to_bf16x2(v1[2], v1[3]));
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          base[(d + r) * g.kv.bt + tok] = f_to_bf16(v0[r]);
+          base[(d + r + half) * g.kv.bt + tok] = f_to_bf16(v1[r]);
+        }
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------ large tiles
+// A workgroup of W waves owns W * TM row tiles x TN column-tile slots over a k range; wave w owns row tiles w TM .. and
+// all the column tiles.  It loads its own activation fragments into registers, UA k-tiles ahead; the weight fragments
+// that all waves need go from memory to LDS with direct loads (16 bytes per lane, a fragment per instruction, no
+// registers), NBUF - 1 k-tiles ahead.  One barrier per k-tile: it is passed when every wave's share of k-tile k has
+// arrived and every wave has read k-tile k - 1, whose buffer the next request then overwrites.
+template <int EPI, int TM, int TN, int W, int NBUF, int UA, int MINB>
+__global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan p) {
+  constexpr int LW = (TN + W - 1) / W;                     // weight fragments a wave requests per k-tile
+  static_assert(UA >= NBUF - 1, "the first waits rely on it");
+  __shared__ u32x4 stage[NBUF][TN][64];
+  int colb, rowb, slice;
+  if (!tile_block(p, colb, rowb, slice)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int KT = g.K >> 5, ntiles = (g.N + 15) >> 4, last_mt = (g.M - 1) >> 4;
+  const int kb = slice * p.slice_kt, nk = min(KT, kb + p.slice_kt) - kb;
+  const int hd = g.kv.hd;
+  const char* ws[LW];
+  int wdst[LW];
+#pragma unroll
+  for (int q = 0; q < LW; ++q) {                           // (the last ones repeat an earlier slot where TN is not a multiple of W)
+    const int j = (q * W + wave) % TN;
+    const int t = slot_tile<EPI, TN>(colb, j, hd);
+    const void* w = (EPI == EPI_SWIGLU && j >= TN / 2) ? g.W1 : g.W0;
+    ws[q] = (const char*)w + ((size_t)(t < ntiles ? t : 0) * KT + kb) * 1024 + lane * 16;
+    wdst[q] = j;
+  }
+  auto request_w = [&](int k, int buf) {
+#pragma unroll
+    for (int q = 0; q < LW; ++q)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ws[q] + (size_t)k * 1024),
+                                       (__attribute__((address_space(3))) void*)&stage[buf][wdst[q]][0], 16, 0, 0);
+  };
+  const u32x4* ap[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) ap[i] = (const u32x4*)g.A + ((size_t)min((rowb * W + wave) * TM + i, last_mt) * KT + kb) * 128 + lane;
+  u32x4 a[UA][TM][2];
+  auto request_a = [&](int u, int k) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      a[u][i][0] = ap[i][(size_t)k * 128];
+      a[u][i][1] = ap[i][(size_t)k * 128 + 64];
+    }
+  };
+  RowDest rd[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) rd[i] = EPI == EPI_QKV ? row_dest(g, ((rowb * W + wave) * TM + i) * 16 + (lane & 15)) : RowDest{0, -1};
+#pragma unroll
+  for (int b = 0; b < NBUF - 1; ++b) request_w(min(b, nk - 1), b);
+#pragma unroll
+  for (int u = 0; u < UA; ++u) request_a(u, min(u, nk - 1));
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
+  int buf = 0, nbuf = NBUF - 1;                            // buffer of k-tile k, buffer of k-tile k + NBUF - 1
+  auto one = [&](int u, int k) {
+    // k-tile k's weights have arrived when at most this wave's later requests are outstanding
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NBUF - 2) * LW + (NBUF - 1) * 2 * TM) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    request_w(min(k + NBUF - 1, nk - 1), nbuf);
+    u32x4 w[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) w[j] = stage[buf][j][lane];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const bf16x8 hi = __builtin_bit_cast(bf16x8, a[u][i][0]), lo = __builtin_bit_cast(bf16x8, a[u][i][1]);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j]), lo, acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j]), hi, acc[i][j], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    request_a(u, min(k + UA, nk - 1));
+    __builtin_amdgcn_sched_barrier(0);
+    buf = buf + 1 == NBUF ? 0 : buf + 1;
+    nbuf = nbuf + 1 == NBUF ? 0 : nbuf + 1;
+  };
+  const int kfull = (nk / UA) * UA;
+  for (int k0 = 0; k0 < kfull; k0 += UA) {
+#pragma unroll
+    for (int u = 0; u < UA; ++u) one(u, k0 + u);
+  }
+#pragma unroll
+  for (int u = 0; u < UA - 1; ++u)
+    if (kfull + u < nk) one(u, kfull + u);                 // (uniform over the workgroup)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the requests past the end
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int row = ((rowb * W + wave) * TM + i) * 16 + (lane & 15);
+#pragma unroll
+    for (int j = 0; j < TN / 2; ++j)
+      tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), slot_tile<EPI, TN>(colb, j + TN / 2, hd), slice, row, 4 * (lane >> 4), acc[i][j],
+                         acc[i][j + TN / 2], rd[i]);
+    if (TN % 2)
+      tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, TN - 1, hd), 0x7FFFFF, slice, row, 4 * (lane >> 4), acc[i][TN - 1], acc[i][TN - 1], rd[i]);
+  }
+}
+
+// ------------------------------------------------------------------------------------------ few rows
+// A workgroup of W waves owns TM row tiles x TN column-tile slots over a k range; its waves take the k-tiles in turn
+// (wave w: k-tiles w, w + W, ..) straight from memory into registers, U of them in flight, and meet once in LDS.  No
+// barrier before that.  Order of an element's sum: a wave's k-tiles ascending, lo before hi, then the waves ascending.
+template <int EPI, int TM, int TN, int W, int U>
+__global__ void __launch_bounds__(W * 64, 1) k_gemm_kwave(GemmArgs g, TilePlan p) {
+  constexpr int RPR = (128 / (W * TN)) < 1 ? 1 : (128 / (W * TN)) > TM ? TM : 128 / (W * TN);     // row tiles per round of the reduction
+  __shared__ f32x4 red[W][RPR * TN][64];
+  int colb, rowb, slice;
+  if (!tile_block(p, colb, rowb, slice)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int KT = g.K >> 5, ntiles = (g.N + 15) >> 4, last_mt = (g.M - 1) >> 4;
+  const int kb = slice * p.slice_kt, ke = min(KT, kb + p.slice_kt);
+  const int hd = g.kv.hd, nw = (ke - kb - wave + W - 1) / W;                                       // k-tiles of this wave
+  const u32x4 *ap[TM], *wp[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) ap[i] = (const u32x4*)g.A + (size_t)min(rowb * TM + i, last_mt) * KT * 128 + lane;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int t = slot_tile<EPI, TN>(colb, j, hd);
+    wp[j] = (const u32x4*)((EPI == EPI_SWIGLU && j >= TN / 2) ? g.W1 : g.W0) + (size_t)(t < ntiles ? t : 0) * KT * 64 + lane;
+  }
+  u32x4 w[U][TN], a[U][TM][2];
+  auto request = [&](int u, int i) {                       // slot u <- the wave's i-th k-tile
+    const int kt = min(kb + wave + i * W, KT - 1);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) w[u][j] = __builtin_nontemporal_load(wp[j] + (size_t)kt * 64);
+#pragma unroll
+    for (int m = 0; m < TM; ++m) {
+      a[u][m][0] = ap[m][(size_t)kt * 128];
+      a[u][m][1] = ap[m][(size_t)kt * 128 + 64];
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (u < nw) request(u, u);
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
+  auto contract = [&](int u) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const bf16x8 hi = __builtin_bit_cast(bf16x8, a[u][i][0]), lo = __builtin_bit_cast(bf16x8, a[u][i][1]);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[u][j]), lo, acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[u][j]), hi, acc[i][j], 0, 0, 0);
+    }
+  };
+  const int kfull = (nw / U) * U;
+  for (int k0 = 0; k0 < kfull; k0 += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      contract(u);
+      __builtin_amdgcn_sched_barrier(0);
+      if (k0 + u + U < nw) request(u, k0 + u + U);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < U - 1; ++u)
+    if (kfull + u < nw) contract(u);
+  // the waves' tiles meet in LDS, RPR row tiles at a time; unit (row tile, slot pair) u is summed and written by wave u mod W
+  constexpr int PAIRS = (TN + 1) / 2;
+#pragma unroll
+  for (int i0 = 0; i0 < TM; i0 += RPR) {
+    RowDest rd[(RPR * PAIRS + W - 1) / W];
+#pragma unroll
+    for (int q = 0; q < (RPR * PAIRS + W - 1) / W; ++q) {
+      const int u = q * W + wave;
+      rd[q] = EPI == EPI_QKV ? row_dest(g, (rowb * TM + i0 + u / PAIRS) * 16 + (lane & 15)) : RowDest{0, -1};
+    }
+    if (i0) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < RPR; ++i)
+      if (i0 + i < TM)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) red[wave][i * TN + j][lane] = acc[i0 + i][j];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < (RPR * PAIRS + W - 1) / W; ++q) {
+      const int u = q * W + wave, i = u / PAIRS, j = u - i * PAIRS, j1 = min(j + TN / 2 + TN % 2, TN - 1);
+      if (i < RPR && i0 + i < TM) {
+        f32x4 v0 = red[0][i * TN + j][lane], v1 = red[0][i * TN + j1][lane];
+#pragma unroll
+        for (int x = 1; x < W; ++x) { v0 += red[x][i * TN + j][lane]; v1 += red[x][i * TN + j1][lane]; }
+        tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), j1 == j ? 0x7FFFFF : slot_tile<EPI, TN>(colb, j1, hd), slice,
+                           (rowb * TM + i0 + i) * 16 + (lane & 15), 4 * (lane >> 4), v0, v1, rd[q]);
+      }
+    }
+  }
+}
+
+}  // namespace ssd

@@ -49,73 +49,52 @@ __global__ void __launch_bounds__(BLOCK) k_embed(EmbedArgs e) {
   }
 }
 
-// h[m] += sum of the k-split partials of the previous GEMM (ascending split order); xn[m] = RMSNorm(h[m]) * gain.
-template <typename AT>
-__global__ void __launch_bounds__(BLOCK) k_add_norm(float* h, const float* part, int n_part, size_t part_stride,
-                                                    const float* gain, float eps, void* xn, int d) {
-  __shared__ float s4[4];
-  const int m = blockIdx.x;
+// h[m] += sum of the k-split partials of the previous GEMM (ascending split order); xn[m] = RMSNorm(h[m]) * gain, as fp32 rows
+// or as split rows (common.h) for the matrix-core GEMMs.  One workgroup per row, four consecutive columns per thread; a
+// row of up to 4 * blockDim columns stays in registers between the two passes.  The partials of a thread are requested
+// eight at a time: their loads, not their sum, are what the kernel waits for (one at a time, 8 partials of 1024 rows of
+// 896 took 9.0 us).
+template <bool SPLIT>
+__global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, int n_part, size_t part_stride, const float* gain,
+                                                   float eps, void* xn, int d) {
+  __shared__ float s16[16];
+  const int m = blockIdx.x, KT = d >> 5;
   float* hr = h + (size_t)m * d;
+  f32x4 v0 = {0, 0, 0, 0};
   float ss = 0.f;
-  for (int i = threadIdx.x; i < d; i += BLOCK) {
-    float v = hr[i];
+  for (int i = threadIdx.x * 4; i < d; i += blockDim.x * 4) {
+    f32x4 v = *(const f32x4*)(hr + i);
     const float* pp = part + (size_t)m * d + i;
-    for (int s0 = 0; s0 < n_part; s0 += 4) {              // four loads in flight; the sum stays in ascending split order
-      float x[4];
+    for (int s0 = 0; s0 < n_part; s0 += 8) {
+      f32x4 x[8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) x[u] = s0 + u < n_part ? pp[(size_t)(s0 + u) * part_stride] : 0.f;
+      for (int u = 0; u < 8; ++u) x[u] = s0 + u < n_part ? *(const f32x4*)(pp + (size_t)(s0 + u) * part_stride) : f32x4{0, 0, 0, 0};
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < 8; ++u)
         if (s0 + u < n_part) v += x[u];
     }
-    hr[i] = v;
-    ss = fmaf(v, v, ss);
+    if (n_part) *(f32x4*)(hr + i) = v;
+    if (i == (int)threadIdx.x * 4) v0 = v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) ss = fmaf(v[r], v[r], ss);
   }
-  const float tot = block_sum(ss, s4);
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) s16[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  float tot = 0.f;
+  for (int w = 0; w < (int)blockDim.x >> 6; ++w) tot += s16[w];
   const float inv = 1.0f / sqrtf(tot / (float)d + eps);
-  typename AT::T* xr = (typename AT::T*)xn + (size_t)m * d;
-  for (int i = threadIdx.x; i < d; i += BLOCK) AT::st(xr + i, hr[i] * inv * gain[i]);
-}
-
-// The same for the kernels that serve many rows: the normalised row goes out as split rows (see common.h), eight
-// consecutive columns per thread (d <= 4096).
-__global__ void __launch_bounds__(BLOCK) k_add_norm_split(float* h, const float* part, int n_part, size_t part_stride,
-                                                          const float* gain, float eps, bf16_t* xs, int d) {
-  __shared__ float s4[4];
-  const int m = blockIdx.x, KT = d >> 5, nslot = d >> 3;
-  float* hr = h + (size_t)m * d;
-  float v[2][8];
-  float ss = 0.f;
+  for (int i = threadIdx.x * 4; i < d; i += blockDim.x * 4) {
+    f32x4 v = i == (int)threadIdx.x * 4 ? v0 : *(const f32x4*)(hr + i);
+    const f32x4 gn = *(const f32x4*)(gain + i);
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int sl = threadIdx.x + q * BLOCK;
-    if (sl < nslot) {
-      const float4 x0 = *(const float4*)(hr + sl * 8), x1 = *(const float4*)(hr + sl * 8 + 4);
-      v[q][0] = x0.x; v[q][1] = x0.y; v[q][2] = x0.z; v[q][3] = x0.w; v[q][4] = x1.x; v[q][5] = x1.y; v[q][6] = x1.z; v[q][7] = x1.w;
-      const float* pp = part + (size_t)m * d + sl * 8;
-      for (int s0 = 0; s0 < n_part; ++s0) {                 // ascending split order, as k_add_norm
-        const float4 p0 = *(const float4*)(pp + (size_t)s0 * part_stride), p1 = *(const float4*)(pp + (size_t)s0 * part_stride + 4);
-        v[q][0] += p0.x; v[q][1] += p0.y; v[q][2] += p0.z; v[q][3] += p0.w; v[q][4] += p1.x; v[q][5] += p1.y; v[q][6] += p1.z; v[q][7] += p1.w;
-      }
-      *(float4*)(hr + sl * 8) = make_float4(v[q][0], v[q][1], v[q][2], v[q][3]);
-      *(float4*)(hr + sl * 8 + 4) = make_float4(v[q][4], v[q][5], v[q][6], v[q][7]);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) ss = fmaf(v[q][i], v[q][i], ss);
-    }
-  }
-  const float tot = block_sum(ss, s4);
-  const float inv = 1.0f / sqrtf(tot / (float)d + eps);
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int sl = threadIdx.x + q * BLOCK;
-    if (sl < nslot) {
-      uint32_t y[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) y[i] = __float_as_uint(v[q][i] * inv * gain[sl * 8 + i]);
-      const SplitA sp = split_bf16(u32x4{y[0], y[1], y[2], y[3]}, u32x4{y[4], y[5], y[6], y[7]});
-      u32x4* o = (u32x4*)(xs + split_index(m, sl * 8, KT));
-      o[0] = __builtin_bit_cast(u32x4, sp.hi);
-      o[64] = __builtin_bit_cast(u32x4, sp.lo);            // 512 bf16 further
+    for (int r = 0; r < 4; ++r) v[r] = v[r] * inv * gn[r];
+    if (SPLIT) {
+      bf16_t* o = (bf16_t*)xn + split_index(m, i, KT);
+      *(uint2*)o = hi_pairs(v);
+      *(uint2*)(o + 512) = lo_pairs(v);
+    } else {
+      *(f32x4*)((float*)xn + (size_t)m * d + i) = v;
     }
   }
 }

@@ -17,7 +17,7 @@
 #include "attention.h"
 #include "common.h"
 #include "gemm.h"
-#include "gemm_rows.h"
+#include "gemm_tile.h"
 #include "persistent.h"
 #include "dataflow.h"
 #include "sample.h"
@@ -313,7 +313,6 @@ struct ssd_kv {
   bool dataflow = false;
   bool attn_whole = false;   // barrier-free kernel: attention of short prefixes without parts.  Default: caches with two
                              // pending slots (draft caches: one-row steps gain 10 %); SSD_ATTN_WHOLE=0 never, 1 every cache
-  bool gemm_wide = true;     // per-operator path, many rows: the LDS-shared GEMM kernel (SSD_GEMM=narrow: the generic one)
   bool attn_mfma = true;     // per-operator path: matrix-core attention where it applies (SSD_ATTN=valu: the scalar kernel)
   int32_t* ticket_alt = nullptr;   // ssd_verify_noalloc: the commit's arrival counter in the library's static scratch
   bool capturing = false;          // a cycle is being captured on this cache: no synchronisation, no fallback kernels
@@ -478,8 +477,6 @@ extern "C" int ssd_kv_create(const ssd_model* m, int max_seqs, int max_rows, int
     env = getenv("SSD_DF_FLIGHT");
     kv->df_sb = env ? atoi(env) : 0;
     if (kv->df_sb != 2 && kv->df_sb != 4 && kv->df_sb != 10 && kv->df_sb != 12) kv->df_sb = 0;
-    env = getenv("SSD_GEMM");
-    kv->gemm_wide = !(env && strcmp(env, "narrow") == 0);
   }
   if (e != hipSuccess) { (void)hipHostFree(kv->mirror_host); delete kv; return fail(SSD_EHIP, "k_kv_init: %s", hipGetErrorString(e)); }
   *out = kv;
@@ -563,128 +560,117 @@ static int kv_check_room(ssd_kv* kv, int seq0, int B, int R, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------------------------------------ forward
-template <typename DT, int EPI>
-static int launch_gemm(const ssd_model* m, GemmArgs g, int items, hipStream_t st) {
-  if (m->c.dtype == SSD_DTYPE_BF16) {
-    const int MT = cdiv(g.M, 16);
-    if (MT <= 1) hipLaunchKernelGGL((k_gemm_bf16<1, EPI, BF16>), dim3(items), dim3(BLOCK), 0, st, g);
-    else if (MT <= 2) hipLaunchKernelGGL((k_gemm_bf16<2, EPI, BF16>), dim3(items), dim3(BLOCK), 0, st, g);
-    else hipLaunchKernelGGL((k_gemm_bf16<2, EPI, BF16>), dim3(items, cdiv(MT, 2)), dim3(BLOCK), 0, st, g);
-  } else {
-    hipLaunchKernelGGL((k_gemm_f32<EPI, F32>), dim3(items), dim3(BLOCK), 0, st, g);
-  }
-  LAUNCH_CHECK();
-  return SSD_OK;
-}
-
-// Launch shape of k_gemm_wide (see gemm.h) for M rows: fewest row groups of at most 4 tiles, the largest staged chunk
-// that fits the LDS budget, and for k-split outputs one slice per chunk up to the partial buffer's capacity.
-struct WidePlan {
-  int mtw, grid, waves;
-  size_t lds;
-  WideArgs wa;
-};
-static WidePlan plan_wide(int M, int N, int K, bool partial, int mtw_forced, int max_slices) {
-  WidePlan p;
-  const int MT = cdiv(M, 16), KT = K / 32;
-  p.waves = WIDE_WAVES;
-  int n_rowg = cdiv(MT, 4);
-  p.mtw = cdiv(MT, n_rowg);
-  if (mtw_forced >= 1 && mtw_forced <= WIDE_MAX_MTW) p.mtw = mtw_forced;
-  if (p.mtw == 5) p.mtw = 6;                              // instantiated: 1, 2, 3, 4, 6, 8
-  if (p.mtw == 7) p.mtw = 8;
-  n_rowg = cdiv(MT, p.mtw);
-  const int lds_budget = WIDE_LDS_BYTES;
-  const int kc_slice = (lds_budget / 2048 / p.mtw) & ~3;                 // k-tiles per slice of a k-split output
-  const int kc_max = (WIDE_SG * p.waves / p.mtw) & ~3;                   // k-tiles per staged chunk (two buffers of it)
-  const int n_pairs = partial ? cdiv(cdiv(N, 16), 2) : cdiv(N, 16);
-  p.wa.n_colg = cdiv(n_pairs, p.waves);
-  p.wa.n_rowg = n_rowg;
-  p.wa.n_slices = partial ? std::min(max_slices, std::max(1, cdiv(KT, kc_slice))) : 1;
-  p.wa.slice_kt = (cdiv(KT, p.wa.n_slices) + 3) & ~3;
-  p.wa.n_slices = cdiv(KT, p.wa.slice_kt);
-  p.wa.KC = std::min(kc_max, p.wa.slice_kt);
-  p.grid = 8 * cdiv(p.wa.n_colg, 8) * n_rowg * p.wa.n_slices;          // see the kernel's index map
-  p.lds = (size_t)2 * p.mtw * p.wa.KC * 2048;
-  return p;
-}
-
-template <int EPI>
-static int launch_wide(const GemmArgs& g, const WidePlan& p, hipStream_t st) {
-  static const hipError_t lds_ok = [] {                   // more than 64 KB of dynamic LDS is opt-in, once per process
-    const void* fns[] = {(const void*)k_gemm_wide<1, EPI, 8, 1>, (const void*)k_gemm_wide<2, EPI, 8, 1>,
-                         (const void*)k_gemm_wide<3, EPI, 8, 1>, (const void*)k_gemm_wide<4, EPI, 8, 1>,
-                         (const void*)k_gemm_wide<6, EPI, 8, 1>, (const void*)k_gemm_wide<8, EPI, 8, 1>};
-    for (const void* f : fns) {
-      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, WIDE_LDS_BYTES);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }();
-  if (lds_ok != hipSuccess) return fail(SSD_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(lds_ok));
-  const dim3 grid(p.grid), block(p.waves * 64);
-  switch (p.mtw) {
-    case 1: hipLaunchKernelGGL((k_gemm_wide<1, EPI, 8, 1>), grid, block, p.lds, st, g, p.wa); break;
-    case 2: hipLaunchKernelGGL((k_gemm_wide<2, EPI, 8, 1>), grid, block, p.lds, st, g, p.wa); break;
-    case 3: hipLaunchKernelGGL((k_gemm_wide<3, EPI, 8, 1>), grid, block, p.lds, st, g, p.wa); break;
-    case 4: hipLaunchKernelGGL((k_gemm_wide<4, EPI, 8, 1>), grid, block, p.lds, st, g, p.wa); break;
-    case 6: hipLaunchKernelGGL((k_gemm_wide<6, EPI, 8, 1>), grid, block, p.lds, st, g, p.wa); break;
-    case 8: hipLaunchKernelGGL((k_gemm_wide<8, EPI, 8, 1>), grid, block, p.lds, st, g, p.wa); break;
-    default: return fail(SSD_EINVAL, "no wide GEMM for %d row tiles per workgroup", p.mtw);
-  }
-  LAUNCH_CHECK();
-  return SSD_OK;
-}
-
-// Launch of k_gemm_rows (gemm_rows.h), from 256 rows on.  The tile a workgroup owns is chosen for the fewest bytes per
-// workgroup at a workgroup per CU or fewer: 8 waves take 64, 128 or 256 rows (by the launch's rows) x 12 weight tiles
-// of gate and up or 8 of a k-split output; the QKV projection, whose epilogue wants a whole head in one wave, 4 waves
-// x 64 or 128 rows x one head.  k-split outputs get 8 slices, one per XCD (16 where that still leaves few workgroups).
-// Returns the number of slices (> 0).
-template <int EPI>
-static int launch_rows(const GemmArgs& g, int cus, int hd, bool partial, int max_slices, hipStream_t st) {
-  const int KT = g.K / 32, MT = cdiv(g.M, 16);
-  const int n_wt = EPI == EPI_SWIGLU ? 2 * cdiv(g.N, 16) : cdiv(g.N, 16);     // weight tiles in all (gate and up both count)
-  RowsPlan p;
-  auto slices = [&](int n_wg) {                            // a multiple of 8 slices (one XCD each), about a workgroup per CU
-    int ns = 1;
-    if (partial && KT >= 16 && max_slices >= 8) ns = (n_wg * 12 <= cus && KT >= 64 && max_slices >= 16) ? 16 : 8;
-    p.slice_kt = cdiv(KT, ns);
-    p.n_slices = cdiv(KT, p.slice_kt);
-  };
-  if constexpr (EPI == EPI_QKV) {
-    const int tm = MT >= 48 ? 2 : 1;                       // 64 rows x one head per workgroup, 128 rows from 768 rows on
-    p.n_rowb = cdiv(MT, 4 * tm);
-    p.n_colb = cdiv(n_wt, hd / 16);
-    slices(1);
-    const dim3 grid(8 * cdiv(p.n_colb, 8) * p.n_rowb), block(256);
-    if (hd == 64 && tm == 1) hipLaunchKernelGGL((k_gemm_rows<EPI, 1, 4, 4, 1, 6, 1>), grid, block, 0, st, g, p);
-    else if (hd == 64) hipLaunchKernelGGL((k_gemm_rows<EPI, 2, 4, 4, 1, 6, 1>), grid, block, 0, st, g, p);
-    else if (hd == 128 && tm == 1) hipLaunchKernelGGL((k_gemm_rows<EPI, 1, 8, 4, 1, 6, 1>), grid, block, 0, st, g, p);
-    else if (hd == 128) hipLaunchKernelGGL((k_gemm_rows<EPI, 2, 8, 4, 1, 4, 1>), grid, block, 0, st, g, p);
-    else return fail(SSD_ENOSUP, "no many-row QKV kernel for head_dim %d", hd);
-  } else {
-    constexpr int TN = EPI == EPI_SWIGLU ? 6 : 4;
-    // rows per workgroup: 64 below 384 rows, 128 up to 767, 256 from there on (the tile grows with the rows as long as
-    // about 200 workgroups remain: a workgroup's bytes per output fall, the number of busy CUs does not)
-    const int tm = MT >= 48 ? 4 : MT >= 24 ? 2 : 1;
-    p.n_rowb = cdiv(MT, 4 * tm);
-    p.n_colb = cdiv(n_wt, 2 * TN);
-    slices(p.n_colb * p.n_rowb);
-    const dim3 grid(p.n_slices > 1 ? 8 * cdiv(p.n_slices, 8) * p.n_colb * p.n_rowb : 8 * cdiv(p.n_colb, 8) * p.n_rowb), block(512);
-    if (tm == 4) hipLaunchKernelGGL((k_gemm_rows<EPI, 4, TN, 4, 2, 2, 1>), grid, block, 0, st, g, p);
-    else if (tm == 2) hipLaunchKernelGGL((k_gemm_rows<EPI, 2, TN, 4, 2, 6, 1>), grid, block, 0, st, g, p);
-    else hipLaunchKernelGGL((k_gemm_rows<EPI, 1, TN, 4, 2, 6, 1>), grid, block, 0, st, g, p);
-  }
-  LAUNCH_CHECK();
-  return p.n_slices;
-}
-
-static int pick_splits(int K, int npairs) {
+static int pick_splits(int K, int npairs) {                // k-splits of the fp32 GEMM
   const int KT = K / 32;
   int gs = std::max(1, 256 / std::max(1, npairs));
   gs = std::min(gs, std::max(1, KT / 8));
   return std::min(gs, MAX_SPLITS);
+}
+
+template <int EPI>
+static int launch_gemm_f32(const GemmArgs& g, int items, hipStream_t st) {
+  hipLaunchKernelGGL((k_gemm_f32<EPI, F32>), dim3(items), dim3(BLOCK), 0, st, g);
+  LAUNCH_CHECK();
+  return SSD_OK;
+}
+
+// Launch of a bf16 GEMM (gemm_tile.h): picks the kernel, the tile and the k-slices from the sizes alone.  Returns the
+// number of k-slices (1 unless `max_slices` allows more: outputs that are k-split partials).
+//   - Few rows (up to 64; for the QKV projection, whose k range cannot be split over workgroups, up to 512): k_gemm_kwave
+//     with the smallest tile that leaves no more workgroups than compute units.  What bounds it is how long a workgroup's
+//     operand stream takes, so the work is spread as far as one round of workgroups allows; k-split outputs get 8 slices
+//     (4 where k is short) while that round lasts.
+//   - Else k_gemm_tile at the tile and slices of the least estimated time.  The estimate was fitted to measurements of
+//     both model shapes at 72 to 1024 rows: a workgroup's k-tile costs 16.6 cycles per 16x16 tile of its output (twice
+//     what the matrix cores alone would take) or 24 cycles per KB that it loads, whichever is more, workgroups of a
+//     compute unit share it, and one alone cannot hide 160 cycles of latency per k-tile; partial outputs cost their
+//     write and their read at 5 TB/s.  It is within 10 % of the best measured tile at every size that was measured.
+//     Tiles that leave a compute unit one workgroup of four waves keep eight k-tiles in flight instead of four (weights
+//     that come from HBM take more than a microsecond: 97 rows of gate / up 13.1 -> 12.1 us).
+template <int EPI>
+static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t st) {
+  const int KT = g.K / 32, MT = cdiv(g.M, 16);
+  const int n_wt = EPI == EPI_SWIGLU ? 2 * cdiv(g.N, 16) : cdiv(g.N, 16);     // weight tiles (gate and up both count)
+  auto plan = [&](int rows, int cols, int slices) {        // rows, cols: tiles of a workgroup
+    TilePlan p;
+    p.n_colb = cdiv(n_wt, cols);
+    p.n_rowb = cdiv(MT, rows);
+    p.slice_kt = cdiv(KT, slices);
+    p.n_slices = cdiv(KT, p.slice_kt);
+    p.per_xcd = cdiv(p.n_colb * p.n_rowb * p.n_slices, 8);
+    return p;
+  };
+  auto wgs = [](const TilePlan& p) { return p.n_colb * p.n_rowb * p.n_slices; };
+#define KWAVE(TM, TN, U)                                                                             \
+  if (tm == TM && tn == TN) hipLaunchKernelGGL((k_gemm_kwave<EPI, TM, TN, 8, U>), dim3(8 * p.per_xcd), dim3(512), 0, st, g, p)
+  if (MT <= 4 || (EPI == EPI_QKV && MT <= 32)) {
+    static const int shapes[][2] = {{1, 2}, {2, 2}, {1, 4}, {3, 2}, {1, 6}, {2, 4}, {2, 6}, {3, 4}, {4, 4}, {3, 6}, {4, 6}};   // by area
+    int tm = 0, tn = 0;
+    TilePlan p{};
+    auto usable = [&](const int* c) {
+      return c[0] <= MT && (EPI == EPI_SWIGLU ? c[0] < 4 || c[1] == 6 : c[1] <= 4);
+    };
+    for (int ns = max_slices >= 8 && KT >= 64 ? 8 : max_slices >= 4 && KT >= 16 ? 4 : 1; ns >= 1 && !tm; ns /= 2)
+      for (const auto& c : shapes) {
+        if (!usable(c)) continue;
+        const TilePlan q = plan(c[0], c[1], ns);
+        if (wgs(q) <= cus) { tm = c[0]; tn = c[1]; p = q; break; }
+      }
+    if (!tm)                                               // more than one round whatever the tile: the largest usable one
+      for (const auto& c : shapes)
+        if (usable(c)) { tm = c[0]; tn = c[1]; p = plan(tm, tn, 1); }
+    KWAVE(1, 2, 4);
+    else KWAVE(2, 2, 4);
+    else KWAVE(1, 4, 4);
+    else KWAVE(3, 2, 4);
+    else KWAVE(2, 4, 2);
+    else KWAVE(3, 4, 2);
+    else if constexpr (EPI == EPI_SWIGLU) { KWAVE(1, 6, 4); else KWAVE(2, 6, 2); else KWAVE(3, 6, 1); else KWAVE(4, 6, 1); }
+    else { KWAVE(4, 4, 2); }
+    LAUNCH_CHECK();
+    return p.n_slices;
+  }
+#undef KWAVE
+  struct Shape { int tm, tn, w; };
+  static const Shape shapes[] = {{1, 4, 4}, {1, 6, 4}, {1, 8, 4}, {1, 10, 4}, {1, 7, 4}, {1, 8, 8}, {1, 7, 8}, {1, 10, 8}, {2, 12, 4}, {2, 8, 8}};
+  int best = -1;
+  double best_us = 0;
+  TilePlan p{};
+  for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
+    const Shape& c = shapes[i];
+    const bool ok = EPI == EPI_PARTIAL ? c.tn == 4 || c.tn == 7 || c.tn == 8 : EPI == EPI_SWIGLU ? c.tn != 7 && !(c.tm == 2 && c.tn == 8) : c.tn == 4;
+    if (!ok) continue;
+    for (int ns = 1; ns <= std::min(8, max_slices) && (ns == 1 || KT / ns >= 7); ns *= 2) {
+      const TilePlan q = plan(c.tm * c.w, c.tn, ns);
+      const int rounds = cdiv(wgs(q), cus);
+      const double cyc = std::max(16.6 * c.tm * c.w * c.tn, 24.0 * (2 * c.tm * c.w + c.tn));
+      const double us = q.slice_kt * (rounds * cyc + (rounds == 1 ? 160.0 : 0.0)) / 2400.0 +
+                        (max_slices > 1 ? (double)q.n_slices * g.M * g.N * 8.0 / 5e6 : 0.0);
+      if (best < 0 || us < best_us * (c.tm * c.w * c.tn > shapes[best].tm * shapes[best].w * shapes[best].tn ? 1.001 : 0.999)) {
+        best = i; best_us = us; p = q;
+      }
+    }
+  }
+  const Shape c = shapes[best];
+  const bool deep = c.tm == 1 && c.w == 4 && wgs(p) <= cus;
+#define TILE(TM, TN, W)                                                                                         \
+  if (!deep && c.tm == TM && c.tn == TN && c.w == W)                                                             \
+  hipLaunchKernelGGL((k_gemm_tile<EPI, TM, TN, W, 4, 4, TM == 2 && W == 8 ? 1 : 2>), dim3(8 * p.per_xcd), dim3(W * 64), 0, st, g, p)
+#define TILE_DEEP(TN)                                                                                           \
+  if (deep && c.tn == TN) hipLaunchKernelGGL((k_gemm_tile<EPI, 1, TN, 4, 8, 8, 1>), dim3(8 * p.per_xcd), dim3(256), 0, st, g, p)
+  TILE(1, 4, 4);
+  else TILE_DEEP(4);
+  else if constexpr (EPI == EPI_SWIGLU) {
+    TILE(1, 6, 4); else TILE(1, 8, 4); else TILE(1, 10, 4); else TILE(1, 8, 8); else TILE(1, 10, 8); else TILE(2, 12, 4);
+    else TILE_DEEP(6); else TILE_DEEP(8); else TILE_DEEP(10);
+  } else if constexpr (EPI == EPI_PARTIAL) {
+    TILE(1, 7, 4); else TILE(1, 8, 4); else TILE(1, 7, 8); else TILE(1, 8, 8); else TILE(2, 8, 8);
+    else TILE_DEEP(7); else TILE_DEEP(8);
+  }
+#undef TILE
+#undef TILE_DEEP
+  LAUNCH_CHECK();
+  return p.n_slices;
 }
 
 template <typename DT, int HD>
@@ -852,32 +838,11 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
   memset(&g0, 0, sizeof g0);
   g0.M = M; g0.kv = kv->v; g0.rows = rows; g0.nq = nq; g0.rope = m->rope;
   const size_t part_stride = (size_t)M * d;
-  // k-splits fill the machine: about two workgroups per CU over (column pairs x row groups x splits), at least 8
-  // k-tiles per workgroup
-  const int row_groups = m->c.dtype == SSD_DTYPE_BF16 && M > 32 ? cdiv(cdiv(M, 16), 2) : 1;
+  constexpr bool bf16 = std::is_same<DT, BF16>::value;     // bf16: GEMM operands are kept as split rows (common.h)
   const int npairs_d = cdiv(cdiv(d, 16), 2);
-  auto splits_for = [&](int Kd) {
-    if (row_groups == 1) return pick_splits(Kd, npairs_d);
-    const int want = std::max(1, 2 * kv->cus / (npairs_d * row_groups));
-    return std::max(1, std::min(std::min(want, (Kd / 32) / 8), (int)MAX_SPLITS));
-  };
-  const int gs_o = splits_for(nqd);
-  const bool wide = m->c.dtype == SSD_DTYPE_BF16 && M > 32 && kv->gemm_wide;
-  // down projection: slices of the long k range per workgroup, if that still gives half the CUs a workgroup
-  // (measured: 18.7 vs 44.6 us per launch on the 1.5B shape at 72 rows, 168 workgroups; 18.7 vs 17.5 us on the 0.5B
-  // shape at 112 rows, where it has 80)
-  const WidePlan down_plan = plan_wide(M, d, c.d_ffn, true, 0, MAX_SPLITS);
-  const bool wide_down = wide &&
-                         2 * down_plan.wa.n_colg * down_plan.wa.n_rowg * down_plan.wa.n_slices >= kv->cus;
-  const int gs_d = wide_down ? down_plan.wa.n_slices : splits_for(c.d_ffn);
-  // from 256 rows on (prefill chunks): the kernels whose waves each own row tiles x weight tiles (gemm_rows.h); every GEMM
-  // operand (normalised rows, attention output, SwiGLU output) is then kept as split rows
-  const bool rowsk = wide && M >= 256 && d <= 4096 && (hd == 64 || hd == 128);
   auto add_norm = [&](int n_part_, const float* gain) -> int {
-    if (rowsk) hipLaunchKernelGGL(k_add_norm_split, dim3(M), dim3(BLOCK), 0, st, kv->h, kv->part, n_part_, part_stride, gain,
-                                  c.rms_eps, (bf16_t*)kv->xn, d);
-    else hipLaunchKernelGGL((k_add_norm<F32>), dim3(M), dim3(BLOCK), 0, st, kv->h, kv->part, n_part_, part_stride, gain,
-                            c.rms_eps, kv->xn, d);
+    const dim3 block(std::min(1024, cdiv(d / 4, WAVE) * WAVE));
+    hipLaunchKernelGGL((k_add_norm<bf16>), dim3(M), block, 0, st, kv->h, kv->part, n_part_, part_stride, gain, c.rms_eps, kv->xn, d);
     LAUNCH_CHECK();
     return SSD_OK;
   };
@@ -891,15 +856,15 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     g.bias = L.bqkv; g.q = kv->q; g.layer = l;
     {
       ProfScope ps(PROF_QKV, st);
-      if (rowsk) rc = std::min(0, launch_rows<EPI_QKV>(g, kv->cus, hd, false, 1, st));
-      else rc = launch_gemm<DT, EPI_QKV>(m, g, (nq + 2 * nkv) * (hd / 32), st);
+      if constexpr (bf16) rc = std::min(0, launch_gemm<EPI_QKV>(g, kv->cus, 1, st));
+      else rc = launch_gemm_f32<EPI_QKV>(g, (nq + 2 * nkv) * (hd / 32), st);
     }
     if (rc) return rc;
 
     AttnArgs a;
     a.q = kv->q; a.kv = kv->v; a.rows = rows; a.layer = l; a.nq = nq; a.scale = 1.0f / sqrtf((float)hd);
     a.o_part = kv->o_part; a.ml_part = kv->ml_part; a.NC = kv->NC; a.out = kv->attn;
-    a.split_kt = rowsk ? nqd / 32 : 0;
+    a.split_kt = bf16 ? nqd / 32 : 0;
     {
       ProfScope ps(PROF_ATTN, st);
       if (hd == 32) rc = launch_attn<DT, 32>(a, nchunks, nkv, B, M, kv->attn_mfma, st);
@@ -909,43 +874,34 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     if (rc) return rc;
 
     g = g0;                                                // output projection -> k-split partials
-    g.A = kv->attn; g.lda = nqd; g.W0 = L.wo; g.W1 = L.wo; g.N = d; g.K = nqd; g.gs = gs_o;
+    g.A = kv->attn; g.lda = nqd; g.W0 = L.wo; g.W1 = L.wo; g.N = d; g.K = nqd;
     g.out = kv->part; g.out_split_stride = part_stride; g.ldo = d;
-    int np_o = gs_o;
     {
       ProfScope ps(PROF_O, st);
-      if (rowsk) { np_o = launch_rows<EPI_PARTIAL>(g, kv->cus, hd, true, MAX_SPLITS, st); rc = std::min(0, np_o); }
-      else rc = launch_gemm<DT, EPI_PARTIAL>(m, g, cdiv(cdiv(d, 16), 2) * gs_o, st);
+      if constexpr (bf16) { n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, MAX_SPLITS, st); rc = std::min(0, n_part); }
+      else { g.gs = n_part = pick_splits(nqd, npairs_d); rc = launch_gemm_f32<EPI_PARTIAL>(g, npairs_d * n_part, st); }
     }
     if (rc) return rc;
 
-    if ((rc = add_norm(np_o, L.ln2))) return rc;
+    if ((rc = add_norm(n_part, L.ln2))) return rc;
 
     g = g0;                                                // gate / up + SwiGLU
     g.A = kv->xn; g.lda = d; g.W0 = L.wgate; g.W1 = L.wup; g.N = c.d_ffn; g.K = d; g.gs = 1; g.act = kv->act;
-    g.act_split_kt = rowsk ? c.d_ffn / 32 : 0;
+    g.act_split_kt = bf16 ? c.d_ffn / 32 : 0;
     {
       ProfScope ps(PROF_GATEUP, st);
-      if (rowsk) {
-        rc = std::min(0, launch_rows<EPI_SWIGLU>(g, kv->cus, hd, false, 1, st));
-      } else if (wide) {                                          // many rows: activations shared through LDS (see gemm.h)
-        // two row tiles per workgroup: measured best on both shapes (more workgroups beat fewer weight re-reads)
-        rc = launch_wide<EPI_SWIGLU>(g, plan_wide(M, c.d_ffn, d, false, 2, 1), st);
-      } else {
-        rc = launch_gemm<DT, EPI_SWIGLU>(m, g, cdiv(c.d_ffn, 16), st);
-      }
+      if constexpr (bf16) rc = std::min(0, launch_gemm<EPI_SWIGLU>(g, kv->cus, 1, st));
+      else rc = launch_gemm_f32<EPI_SWIGLU>(g, cdiv(c.d_ffn, 16), st);
     }
     if (rc) return rc;
 
     g = g0;                                                // down projection -> k-split partials
-    g.A = kv->act; g.lda = c.d_ffn; g.W0 = L.wdown; g.W1 = L.wdown; g.N = d; g.K = c.d_ffn; g.gs = gs_d;
+    g.A = kv->act; g.lda = c.d_ffn; g.W0 = L.wdown; g.W1 = L.wdown; g.N = d; g.K = c.d_ffn;
     g.out = kv->part; g.out_split_stride = part_stride; g.ldo = d;
-    n_part = gs_d;
     {
       ProfScope ps(PROF_DOWN, st);
-      if (rowsk) { n_part = launch_rows<EPI_PARTIAL>(g, kv->cus, hd, true, MAX_SPLITS, st); rc = std::min(0, n_part); }
-      else if (wide_down) rc = launch_wide<EPI_PARTIAL>(g, down_plan, st);
-      else rc = launch_gemm<DT, EPI_PARTIAL>(m, g, cdiv(cdiv(d, 16), 2) * gs_d, st);
+      if constexpr (bf16) { n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, MAX_SPLITS, st); rc = std::min(0, n_part); }
+      else { g.gs = n_part = pick_splits(c.d_ffn, npairs_d); rc = launch_gemm_f32<EPI_PARTIAL>(g, npairs_d * n_part, st); }
     }
     if (rc) return rc;
   }
@@ -955,8 +911,8 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
   g.A = kv->xn; g.lda = d; g.W0 = m->head; g.W1 = m->head; g.N = c.vocab; g.K = d; g.gs = 1;
   g.out = kv->logits; g.out_split_stride = 0; g.ldo = c.vocab;
   ProfScope ps(PROF_HEAD, st);
-  if (rowsk) return std::min(0, launch_rows<EPI_PARTIAL>(g, kv->cus, hd, false, 1, st));
-  return launch_gemm<DT, EPI_PARTIAL>(m, g, cdiv(cdiv(c.vocab, 16), 2), st);
+  if constexpr (bf16) return std::min(0, launch_gemm<EPI_PARTIAL>(g, kv->cus, 1, st));
+  else return launch_gemm_f32<EPI_PARTIAL>(g, cdiv(cdiv(c.vocab, 16), 2), st);
 }
 
 static int forward_any(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int pcap, const int32_t* dev_tokens,
