@@ -22,7 +22,7 @@ struct AttnArgs {
   int NC;               // chunk capacity of the partial buffers
   void* out;            // [M][nq*hd] (combine)
   int split_kt;         // > 0: `out` is written as split rows (common.h) with this many k-tiles per row (nq*hd / 32)
-  int nparts, tiles_per_wg;   // k_attn_part_mfma: grid.x = nparts x groups of tiles_per_wg row tiles (a multiple of 4)
+  int nparts, part_keys;      // k_attn_mfma: grid.x = nparts x groups of row tiles; keys per part (a multiple of 64)
 };
 
 template <int HD, typename KVT>
@@ -133,235 +133,262 @@ __global__ void __launch_bounds__(WAVE) k_attn_combine(AttnArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------ matrix-core variant
-// The same operation for bf16 caches with 16-token blocks and head_dim 64 or 128, for launches with many rows
-// (batched verification).  Work item = (part of 256 key positions, kv head, sequence).  The query rows that share
-// the keys - R rows of the sequence x the G query heads of the group - form tiles of 16; wave w of the workgroup
-// takes tiles w, w+4, .. and walks the part's four 64-key chunks in ascending order with a running (max, sum,
-// weighted values) per row, so no partial ever crosses waves.  Keys and values are read once, as MFMA operand
-// fragments straight from the cache (a K fragment is 8 consecutive dims of one cached key row, a V fragment 8
-// consecutive tokens of one dim of the token-minor value layout): wave w loads the fragments of chunk w and parks
-// them in LDS in fragment order, so the whole part is in flight at once and every wave then reads any chunk with
-// conflict-free 16-byte LDS reads.  S = Q K^T with the queries as hi + lo bf16, a masked softmax in the base-2
-// domain, O = P V with P split the same way.  The result is one partial per (row, head, part);
-// k_attn_combine_parts merges the parts in ascending order.  Parts and chunks are cut at absolute positions, so a
-// row's bits do not depend on which other rows share the launch.
-constexpr int ATT_PART_KEYS = 256;
+// The same operation for bf16 caches with 16-token blocks and head_dim 64 or 128.  The query rows that share keys - R rows
+// of a sequence x the G query heads of a group - form tiles of 16.  A workgroup takes WQ = 4 tiles and a part of the keys
+// (`part_keys`, cut at absolute positions); its 8 waves are 4 tiles x WK = 2 key groups, and key group k walks the part's
+// 64-key chunks k, k + WK, .. with a running (max, sum, weighted values) per row.  The key groups meet once in LDS.  Where
+// one part covers all keys the row is finished here; else its partial goes to memory and k_attn_combine_parts merges
+// the parts in ascending order.
+//
+// S is computed transposed, S^T = K Q^T, and so is O^T = V^T P^T: a lane then holds scores and outputs of ONE query row
+// (lane % 16), so the row maximum needs two cross-lane steps instead of sixteen, and P goes from the accumulators
+// into the second product without leaving the registers: accumulator (tile h, register r) of lane group g is row
+// 4 g + r of the key tile, and the keys are assigned to the rows of the two key tiles of a 32-key pair such that this is
+// key 8 g + 4 h + r - the eight keys whose values lane group g holds in a value fragment.  The row sum is P times a matrix
+// of ones.
+// Keys and values go from the paged cache to LDS with direct loads, a chunk ahead.  What bounds a long prefix is issue: the
+// 16x16x32 matrix instructions (36 per wave and chunk, 16 cycles each) leave the vector unit (130 instructions and 16
+// exponentials) no slots, so the two add up; with few keys per workgroup it is the chain of dependent latencies.
+// 1024 rows of the 0.5B shape at 512 / 3072 cached positions: 20.9 / 46.6 us (with the parts, their merge and the sixteen-step
+// reductions of the kernel before it: 56 us on average over a prefill of 4096); 16 x 7 rows at about 2200: 10 + 3.6 us (15.6 + 4.7).
+constexpr int ATT_WAVES = 8, ATT_TILES = 4;              // waves and row tiles of a workgroup
 
-template <int HD>
-struct KVFrag {
-  u32x4 kf[4][HD / 32], vf[2][HD / 16];
-};
-
-// Fragments of keys [kbase, kbase + 64) of (seq, kvh); masked keys may read any valid block.
-template <int HD>
-__device__ __forceinline__ void attn_load_chunk(const AttnArgs& a, const bf16_t* kp, const bf16_t* vp, int seq, int kvh,
-                                                int kbase, int pos_max, int g, int c16, KVFrag<HD>& f) {
-  const int nkv = a.kv.nkv;
-  int blk[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int bi = (kbase >> 4) + t;
-    const int b = (bi < a.kv.mbps && bi * 16 <= pos_max) ? a.kv.table[seq * a.kv.mbps + bi] : -1;
-    blk[t] = b < 0 ? 0 : b;
-    const bf16_t* kr = kp + ((size_t)(blk[t] * nkv + kvh) * 16 + c16) * HD + g * 8;
-#pragma unroll
-    for (int ks = 0; ks < HD / 32; ++ks) f.kf[t][ks] = *(const u32x4*)(kr + 32 * ks);
-  }
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const int b0 = blk[2 * ks], b1 = blk[2 * ks + 1];
-    const int vblk = (g >> 1) ? b1 : b0;                              // keys 32ks + 8g.. live in block 2ks + g/2
-    const bf16_t* vr = vp + ((size_t)(vblk * nkv + kvh) * HD + c16) * 16 + (g & 1) * 8;
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) f.vf[ks][dt] = *(const u32x4*)(vr + dt * 256);
-  }
+__device__ __forceinline__ float max_over_groups(float v) {  // over the four lanes l, l ^ 16, l ^ 32, l ^ 48
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
 }
-
 template <int HD>
-__global__ void __launch_bounds__(BLOCK) k_attn_part_mfma(AttnArgs a) {
-  constexpr int KS = HD / 32, DT = HD / 16, NF = 4 * KS + 2 * DT;     // fragments of a chunk: 16 (HD 64) or 32 (HD 128)
-  // A wave's P tile, 16 rows x 64 keys: row r keeps key column c at c ^ 4 (r & 7), so that the 16-byte reads of eight
-  // consecutive rows fall into distinct banks (unswizzled they all hit the same four)
-  __shared__ __attribute__((aligned(16))) float Pw[4][16 * 64];
-  __shared__ u32x4 KV[4][NF][64];                        // the part's fragments, [chunk][fragment][lane]
+__global__ void __launch_bounds__(ATT_WAVES * 64, 2) k_attn_mfma(AttnArgs a) {
+  constexpr int WQ = ATT_TILES, WK = ATT_WAVES / WQ, KS = HD / 32, DT = HD / 16;
+  constexpr int NB = 2, NL = NB * KS;                      // blocks, and direct loads, of a wave and chunk
+  static_assert(WQ == 4, "two waves of a key group load its keys, two its values");
+  extern __shared__ u32x4 kvs[];                           // [key group][keys, values][buffer][block][KS][64]
   const int part = blockIdx.x % a.nparts, tgroup = blockIdx.x / a.nparts, kvh = blockIdx.y, brel = blockIdx.z;
   const int seq = a.rows.seq0 + brel;
-  const int R = a.rows.R, nkv = a.kv.nkv, G = a.nq / nkv, RG = R * G;
-  const int m_first = brel * R;
-  const int ntiles = (RG + 15) >> 4;
-  const int rt_begin = tgroup * a.tiles_per_wg, rt_end = min(ntiles, rt_begin + a.tiles_per_wg);
-  // rows are in ascending position order: the last row of this workgroup's tiles sees the most keys
-  const int pos_max = a.rows.pos[m_first + (min(16 * rt_end, RG) - 1) / G];
-  const int pbase = part * ATT_PART_KEYS;
-  if (pbase > pos_max) return;                           // no row of these tiles reaches the part
-  const int tid = threadIdx.x, lane = tid & 63, uw = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int R = a.rows.R, nkv = a.kv.nkv, G = a.nq / nkv, RG = R * G, m_first = brel * R;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wq = wave % WQ, kg = wave / WQ;
   const int g = lane >> 4, c16 = lane & 15;
-  const int nch = min(4, ((pos_max - pbase) >> 6) + 1);  // chunks of the part that some row reaches
-  // wave w brings chunk w into LDS: every fragment load of the part is in flight at once
-  if (uw < nch) {
-    const size_t plane = (size_t)a.kv.n_blocks * nkv * 16 * HD;
-    const bf16_t* kp = (const bf16_t*)a.kv.pool + (size_t)(2 * a.layer) * plane;
-    KVFrag<HD> f;
-    attn_load_chunk<HD>(a, kp, kp + plane, seq, kvh, pbase + 64 * uw, pos_max, g, c16, f);
+  const int r0 = 16 * (tgroup * WQ + wq);                  // first of this wave's query rows
+  // (constant address space: what the whole wave needs is read with scalar loads, which do not queue behind the loads in flight)
+  typedef const __attribute__((address_space(4))) int32_t* const_i32;
+  const const_i32 row_pos = (const_i32)(uintptr_t)(a.rows.pos + m_first);
+  const const_i32 table = (const_i32)(uintptr_t)(a.kv.table + (size_t)seq * a.kv.mbps);
+  // rows ascend in position: what the workgroup's last row, and this wave's first and last, reach
+  const int wg_reach = row_pos[(min(16 * WQ * (tgroup + 1), RG) - 1) / G];
+  const int pbase = part * a.part_keys;
+  if (pbase > wg_reach) return;                            // (the whole workgroup)
+  const bool has_rows = r0 < RG;
+  const int pos_lo = has_rows ? row_pos[r0 / G] : 0;
+  const int reach = has_rows ? row_pos[(min(r0 + 16, RG) - 1) / G] : -1;
+  const int nch = min(a.part_keys >> 6, ((wg_reach - pbase) >> 6) + 1);           // chunks of the part that some row reaches
+  const int nit = (nch + WK - 1) / WK;
+
+  // Direct loads: each brings 1 KB of consecutive memory of one block (sixteen lanes that touch sixteen rows would load at a
+  // quarter of the rate).  Keys are parked row by row with the 16-byte units of row t of a block permuted by XOR with
+  // (t & 3) + 4 (t / 8), so that the rows of a key tile read their units from distinct banks; values as they are, dim by dim.
+  const bool values = wq >= 2;
+  const size_t block_elems = (size_t)nkv * 16 * HD, plane = (size_t)a.kv.n_blocks * block_elems;
+  const bf16_t* pool = (const bf16_t*)a.kv.pool + (size_t)(2 * a.layer + (values ? 1 : 0)) * plane + (size_t)kvh * 16 * HD;
+  int voff[KS];
+  {
+    constexpr int UPR = 4 * KS;                            // 16-byte units of a cached row
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      const int t = (64 / UPR) * i + lane / UPR, unit = (lane % UPR) ^ ((t & 3) | ((t >> 1) & 4));
+      voff[i] = values ? i * 512 + lane * 8 : t * HD + unit * 8;
+          }
+  }
+  const int last_bi = min(a.kv.mbps - 1, wg_reach >> 4);
+  int blk[NB];                                             // block ids of what this wave requests next
+  auto look_up = [&](int it) {                             // ... which is its share of this key group's chunk of iteration `it`
+    const int bi = (pbase >> 4) + 4 * (it * WK + kg) + 2 * (wq & 1);
+#pragma unroll
+    for (int t = 0; t < NB; ++t) blk[t] = table[min(bi + t, last_bi)];
+  };
+  u32x4* my = kvs + (size_t)kg * (4 * 4 * KS * 64);
+  auto request = [&](int it) {
+    u32x4* dst = my + ((values ? 2 : 0) + (it & 1)) * (4 * KS * 64) + 2 * (wq & 1) * (KS * 64);
+#pragma unroll
+    for (int t = 0; t < NB; ++t)
+#pragma unroll
+      for (int i = 0; i < KS; ++i)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(pool + (size_t)max(blk[t], 0) * block_elems + voff[i]),      // (masked keys may read any block)
+                                         (__attribute__((address_space(3))) void*)(dst + (t * KS + i) * 64), 16, 0, 0);
+  };
+  look_up(0);
+  request(0);
+  look_up(min(1, nit - 1));
+
+  // query row c16 of the tile, scaled into the base-2 domain and split
+  const int qr = r0 + c16;
+  const bool qok = qr < RG;
+  const int j = qok ? qr / G : 0, gq = qok ? qr - j * G : 0;
+  const int m = m_first + j, hq = kvh * G + gq;
+  const int pos = qok ? a.rows.pos[m] : -1;
+  SplitA qf[KS];
+  {
+    const float scale2 = a.scale * 1.4426950408889634f;
+    const f32x4* qp = (const f32x4*)(a.q + ((size_t)m * a.nq + hq) * HD + g * 8);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      qf[ks] = split_bf16(__builtin_bit_cast(u32x4, qp[8 * ks] * scale2), __builtin_bit_cast(u32x4, qp[8 * ks + 1] * scale2));
+  }
+  // running state of a row: mrow, and o and l (all four registers of l hold the row's sum: P times a matrix of ones)
+  float mrow = 0.f;
+  bool first = true;                                       // the wave's first chunk sets the maximum, whatever its sign
+  f32x4 o[DT], l = {0, 0, 0, 0};
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0, 0, 0, 0};
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u});
+  for (int it = 0; it < nit; ++it) {
+    // the chunk has arrived, and every wave of the group has read the one whose buffer the next request overwrites
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (it + 1 < nit) { request(it + 1); look_up(min(it + 2, nit - 1)); }
+    const int kbase = pbase + 64 * (it * WK + kg);
+    if (kbase > reach) continue;                           // (uniform over the wave; always so for a wave without rows)
+    // Scores minus the running maximum (the accumulators start at -mrow).  Element (tile t, register r): key
+    // kbase + 32 (t / 2) + 8 g + 4 (t % 2) + r of row c16.  Independent chains of matrix-core instructions side by side.
+    const u32x4* kk = my + (it & 1) * (4 * KS * 64) + (8 * (c16 >> 2) + (c16 & 3)) * (4 * KS);       // row 8 (c16 / 4) + c16 % 4 of a pair
+    const u32x4* vv = my + (2 + (it & 1)) * (4 * KS * 64) + (g >> 1) * (KS * 64) + 2 * c16 + (g & 1);
+    bf16x8 kf[4][KS];
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) KV[uw][t * KS + ks][lane] = f.kf[t][ks];
+      for (int ks = 0; ks < KS; ++ks) kf[t][ks] = __builtin_bit_cast(bf16x8, kk[(t >> 1) * (2 * KS * 64) + (t & 1) * (16 * KS) + ((4 * ks + g) ^ (c16 & 7))]);
+    f32x4 s[4];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
+    for (int t = 0; t < 4; ++t) s[t] = f32x4{-mrow, -mrow, -mrow, -mrow};
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) KV[uw][4 * KS + ks * DT + dt][lane] = f.vf[ks][dt];
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], qf[ks].lo, s[t], 0, 0, 0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], qf[ks].hi, s[t], 0, 0, 0);
+    if (kbase + 63 > pos_lo) {
+      const int left = pos - kbase - 8 * g;
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (32 * (t >> 1) + 4 * (t & 1) + r > left) s[t][r] = -INFINITY;
+    }
+    float mx = s[0][0];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[t][r]);
+    mx = max_over_groups(mx);
+    if (first || __any(mx > 0.f)) {                        // a new maximum: what is there shrinks
+      const float up = first ? (mx == -INFINITY ? 0.f : mx) : fmaxf(mx, 0.f), alpha = first ? 0.f : __builtin_amdgcn_exp2f(-up);
+      first = false;
+      mrow += up;
+      l *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt] *= alpha;
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[t][r] -= up;
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s[t][r] = __builtin_amdgcn_exp2f(s[t][r]);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const SplitA pf = split_bf16(__builtin_bit_cast(u32x4, s[2 * p]), __builtin_bit_cast(u32x4, s[2 * p + 1]));
+      bf16x8 vf[DT];
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) vf[dt] = __builtin_bit_cast(bf16x8, vv[p * (2 * KS * 64) + dt * 32]);
+      l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf.lo, l, 0, 0, 0);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pf.lo, o[dt], 0, 0, 0);
+      l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf.hi, l, 0, 0, 0);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pf.hi, o[dt], 0, 0, 0);
+    }
   }
-  const float scale2 = a.scale * 1.4426950408889634f;
-  float* P = Pw[uw];
-  // Q fragments of the wave's first tile travel while the keys do
-  auto load_q = [&](int rt, u32x4 (&x)[KS][2]) {
-    const int qr = 16 * rt + c16;                        // A-operand row c16 = (row j of the sequence, query head gq)
-    const bool qok = qr < RG;
-    const int j = qok ? qr / G : 0, gq = qok ? qr - j * G : 0;
-    const u32x4* qp = (const u32x4*)(a.q + ((size_t)(m_first + j) * a.nq + kvh * G + gq) * HD + g * 8);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      x[ks][0] = u32x4{0u, 0u, 0u, 0u};
-      x[ks][1] = x[ks][0];
-      if (qok) { x[ks][0] = qp[8 * ks]; x[ks][1] = qp[8 * ks + 1]; }
-    }
-  };
-  auto load_pos = [&](int rt, int (&pos)[4]) {           // of accumulator rows 4g + r; -1: not a row
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int qr = 16 * rt + 4 * g + r;
-      pos[r] = qr < RG ? a.rows.pos[m_first + qr / G] : -1;
-    }
-  };
-  // position of the last row of tile rt (rows ascend in position: what the tile reaches)
-  auto tile_reach = [&](int rt) { return a.rows.pos[m_first + (min(16 * rt + 16, RG) - 1) / G]; };
-  u32x4 qraw[KS][2], qnext[KS][2];
-  int pos[4], pnext[4], reach = -1, reach_next = -1;
-  if (rt_begin + uw < rt_end) { load_q(rt_begin + uw, qraw); load_pos(rt_begin + uw, pos); reach = tile_reach(rt_begin + uw); }
+  if (l[0] == 0.f) mrow = -1e30f;                          // no key of the row in this key group
+  // key groups 1 .. WK-1 hand their state over, group 0 adds them in ascending order
   __syncthreads();
-  for (int rt = rt_begin + uw; rt < rt_end; rt += 4) {
-    if (rt != rt_begin + uw) {
+  f32x4* xch = (f32x4*)kvs;                                // [key group - 1][wq][DT + 1][64]
+  constexpr int XT = (DT + 1) * 64;
+  if (kg > 0) {
+    f32x4* x = xch + (size_t)((kg - 1) * WQ + wq) * XT + lane;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) { qraw[ks][0] = qnext[ks][0]; qraw[ks][1] = qnext[ks][1]; }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) pos[r] = pnext[r];
-      reach = reach_next;
-    }
-    // the wave's next tile travels while this one is worked on
-    if (rt + 4 < rt_end) { load_q(rt + 4, qnext); load_pos(rt + 4, pnext); reach_next = tile_reach(rt + 4); }
-    __builtin_amdgcn_sched_barrier(0);
-    // causal skip: a tile whose last row does not reach the part has nothing here
-    if (reach < pbase) continue;
-    SplitA qf[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = split_bf16(qraw[ks][0], qraw[ks][1]);
-    float mrow[4], lrow[4];
-    f32x4 oacc[DT];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) { mrow[r] = -INFINITY; lrow[r] = 0.f; }
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) oacc[dt] = f32x4{0, 0, 0, 0};
-    for (int c = 0; c < nch; ++c) {
-      const int kbase = pbase + 64 * c;
-      f32x4 s[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        bf16x8 kf[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) kf[ks] = __builtin_bit_cast(bf16x8, KV[c][t * KS + ks][lane]);
-        f32x4 z = f32x4{0, 0, 0, 0};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[ks].lo, kf[ks], z, 0, 0, 0);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[ks].hi, kf[ks], z, 0, 0, 0);
-        s[t] = z;
-      }
-      // element (reg r, tile t) = (tile row 4g + r, key kbase + 16t + c16)
-      float alpha[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float mx = -INFINITY;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const bool ok = kbase + 16 * t + c16 <= pos[r];
-          s[t][r] = ok ? s[t][r] * scale2 : -INFINITY;
-          mx = fmaxf(mx, s[t][r]);
-        }
-        const float mnew = fmaxf(mrow[r], row16_max(mx));
-        alpha[r] = (mrow[r] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mrow[r] - mnew);
-        float sum = 0.f;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const float p = (s[t][r] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(s[t][r] - mnew);
-          P[(4 * g + r) * 64 + ((16 * t + c16) ^ (((4 * g + r) & 7) << 2))] = p;
-          sum += p;
-        }
-        mrow[r] = mnew;
-        lrow[r] = fmaf(lrow[r], alpha[r], row16_sum(sum));
-      }
-      __builtin_amdgcn_wave_barrier();
-      // O = alpha O + P V: P fragment row c16, keys 32ks + 8g..; V fragment dim 16dt + c16, same keys
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) oacc[dt][r] *= alpha[r];
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const int pc = ks * 32 + g * 8, sw = (c16 & 7) << 2;
-        const SplitA pf = split_bf16(*(const u32x4*)(P + c16 * 64 + (pc ^ sw)), *(const u32x4*)(P + c16 * 64 + ((pc + 4) ^ sw)));
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          const bf16x8 vv = __builtin_bit_cast(bf16x8, KV[c][4 * KS + ks * DT + dt][lane]);
-          oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf.lo, vv, oacc[dt], 0, 0, 0);
-          oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf.hi, vv, oacc[dt], 0, 0, 0);
-        }
-      }
-      __builtin_amdgcn_wave_barrier();                   // P is rewritten by the next chunk
-    }
-    // the part's partial of every row that reaches the part (the combine reads no others)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int qr = 16 * rt + 4 * g + r;
-      if (pbase <= pos[r]) {
-        const int j = qr / G, gq = qr - j * G;
-        const size_t pidx = ((size_t)(m_first + j) * a.nq + kvh * G + gq) * a.NC + part;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) a.o_part[pidx * HD + 16 * dt + c16] = oacc[dt][r];
-        if (c16 == 0) { a.ml_part[pidx * 2] = mrow[r]; a.ml_part[pidx * 2 + 1] = lrow[r]; }
-      }
-    }
+    for (int dt = 0; dt < DT; ++dt) x[dt * 64] = o[dt];
+    x[DT * 64] = f32x4{mrow, l[0], 0.f, 0.f};
   }
-}
-
-// One wave per (row, query head): merge the row's part partials (base-2 maxima) in ascending part order.
-template <int HD, typename AT>
-__global__ void __launch_bounds__(WAVE) k_attn_combine_parts(AttnArgs a) {
-  const int m = blockIdx.x / a.nq, hq = blockIdx.x - m * a.nq;
-  const int lane = threadIdx.x;
-  const int np = a.rows.pos[m] / ATT_PART_KEYS + 1;
-  const size_t base = ((size_t)m * a.nq + hq) * a.NC;
-  float mx = -INFINITY;
-  for (int p = 0; p < np; ++p) mx = fmaxf(mx, a.ml_part[(base + p) * 2]);
-  float l = 0.f, o[HD / 64];
+  __syncthreads();
+  if (kg > 0 || !qok) return;
+  float lr = l[0];
 #pragma unroll
-  for (int i = 0; i < HD / 64; ++i) o[i] = 0.f;
-#pragma unroll 4
-  for (int p = 0; p < np; ++p) {
-    const float mc = a.ml_part[(base + p) * 2];
-    const float w = (mc == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mc - mx);
-    l = fmaf(a.ml_part[(base + p) * 2 + 1], w, l);
+  for (int k = 1; k < WK; ++k) {
+    const f32x4* x = xch + (size_t)((k - 1) * WQ + wq) * XT + lane;
+    const f32x4 ml = x[DT * 64];
+    const float mnew = fmaxf(mrow, ml[0]), wa = __builtin_amdgcn_exp2f(mrow - mnew), wb = __builtin_amdgcn_exp2f(ml[0] - mnew);
+    mrow = mnew;
+    lr = lr * wa + ml[1] * wb;
 #pragma unroll
-    for (int i = 0; i < HD / 64; ++i) o[i] = fmaf(a.o_part[(base + p) * HD + lane + i * WAVE], w, o[i]);
+    for (int dt = 0; dt < DT; ++dt) o[dt] = o[dt] * wa + x[dt * 64] * wb;
   }
-  if (a.split_kt > 0) {
+  if (pbase > pos) return;                                 // the row does not reach the part (the merge reads no such partial)
+  if (a.nparts == 1) {                                     // dims 16 dt + 4 g .. + 3 of the finished row
 #pragma unroll
-    for (int i = 0; i < HD / 64; ++i) st_split_value((bf16_t*)a.out, a.split_kt, m, hq * HD + lane + i * WAVE, o[i] / l);
+    for (int dt = 0; dt < DT; ++dt) {
+      const f32x4 y = o[dt] / lr;
+      bf16_t* out = (bf16_t*)a.out + split_index(m, hq * HD + 16 * dt + 4 * g, a.split_kt);
+      *(uint2*)out = hi_pairs(y);
+      *(uint2*)(out + 512) = lo_pairs(y);
+    }
     return;
   }
-  typename AT::T* out = (typename AT::T*)a.out + (size_t)m * a.nq * HD + hq * HD;
+  const size_t pidx = ((size_t)m * a.nq + hq) * a.NC + part;
 #pragma unroll
-  for (int i = 0; i < HD / 64; ++i) AT::st(out + lane + i * WAVE, o[i] / l);
+  for (int dt = 0; dt < DT; ++dt) *(f32x4*)(a.o_part + pidx * HD + 16 * dt + 4 * g) = o[dt];
+  if (g == 0) { a.ml_part[pidx * 2] = mrow; a.ml_part[pidx * 2 + 1] = lr; }
+}
+
+// Merges a row's part partials (base-2 maxima) in ascending part order: HD / 4 lanes per (row, query head), four dims each.
+template <int HD>
+__global__ void __launch_bounds__(BLOCK) k_attn_combine_parts(AttnArgs a) {
+  constexpr int L = HD / 4;
+  const int rh = blockIdx.x * (BLOCK / L) + threadIdx.x / L, d = (threadIdx.x % L) * 4;
+  if (rh >= a.rows.M * a.nq) return;
+  const int m = rh / a.nq, hq = rh - m * a.nq;
+  const int np = a.rows.pos[m] / a.part_keys + 1;
+  const size_t base = (size_t)rh * a.NC;
+  float mx = -INFINITY, l = 0.f;
+  f32x4 o = {0, 0, 0, 0};
+  for (int p0 = 0; p0 < np; p0 += 4) {                     // four parts' loads in flight
+    float2 ml[4];
+    f32x4 x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int p = min(p0 + u, np - 1);
+      ml[u] = *(const float2*)(a.ml_part + (base + p) * 2);
+      x[u] = *(const f32x4*)(a.o_part + (base + p) * HD + d);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (p0 + u < np) {
+        const float mnew = fmaxf(mx, ml[u].x), wa = __builtin_amdgcn_exp2f(mx - mnew), wb = __builtin_amdgcn_exp2f(ml[u].x - mnew);
+        mx = mnew;
+        l = l * wa + ml[u].y * wb;
+        o = o * wa + x[u] * wb;
+      }
+  }
+  const f32x4 y = o / l;
+  bf16_t* out = (bf16_t*)a.out + split_index(m, hq * HD + d, a.split_kt);
+  *(uint2*)out = hi_pairs(y);
+  *(uint2*)(out + 512) = lo_pairs(y);
 }
 
 }  // namespace ssd

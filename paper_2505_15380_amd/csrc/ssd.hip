@@ -673,23 +673,33 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
   return p.n_slices;
 }
 
+// Matrix-core attention: parts so that a launch has about a workgroup per CU and a key group at least one chunk; one part,
+// and no merge kernel, where the tiles alone fill half the device or the keys are few.
+template <int HD>
+static int launch_attn_mfma(AttnArgs a, int nchunks, int nkv, int B, int M, int cus, hipStream_t st) {
+  constexpr int wk = ATT_WAVES / ATT_TILES;
+  const int n_tg = cdiv(cdiv(a.rows.R * (a.nq / nkv), 16), ATT_TILES);
+  const int want = std::min(std::max(1, cus / (n_tg * nkv * B)), cdiv(nchunks, wk));
+  const int part_chunks = cdiv(cdiv(nchunks, want), wk) * wk;
+  a.part_keys = part_chunks * 64;
+  a.nparts = cdiv(nchunks, part_chunks);
+  constexpr int LDS = wk * 2 * 2 * HD * 128;              // two buffers of 64 keys and 64 values per key group
+  static const hipError_t lds_ok =                        // more than 64 KB of dynamic LDS is opt-in, once per process
+      hipFuncSetAttribute((const void*)k_attn_mfma<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  if (lds_ok != hipSuccess) return fail(SSD_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(lds_ok));
+  hipLaunchKernelGGL((k_attn_mfma<HD>), dim3(a.nparts * n_tg, nkv, B), dim3(ATT_WAVES * 64), LDS, st, a);
+  LAUNCH_CHECK();
+  if (a.nparts > 1) {
+    hipLaunchKernelGGL((k_attn_combine_parts<HD>), dim3(cdiv(M * a.nq, BLOCK / (HD / 4))), dim3(BLOCK), 0, st, a);
+    LAUNCH_CHECK();
+  }
+  return SSD_OK;
+}
+
 template <typename DT, int HD>
-static int launch_attn(AttnArgs a, int nchunks, int nkv, int B, int M, bool mfma, hipStream_t st) {
+static int launch_attn(AttnArgs a, int nchunks, int nkv, int B, int M, bool mfma, int cus, hipStream_t st) {
   if constexpr (std::is_same<DT, BF16>::value && (HD == 64 || HD == 128)) {
-    if (mfma && a.kv.bt == 16) {                          // keys and values as matrix-core fragments, 256-key parts
-      const int nparts = cdiv(nchunks * ATT_CHUNK, ATT_PART_KEYS);
-      // many query rows per sequence (prefill chunks): groups of row tiles get workgroups of their own
-      const int ntiles = cdiv(a.rows.R * (a.nq / nkv), 16);
-      // (about two workgroups per CU: a group that stages a part's keys for more row tiles re-reads them less)
-      const int groups = std::max(1, std::min(cdiv(ntiles, 4), cdiv(512, nparts * nkv * B)));
-      a.nparts = nparts;
-      a.tiles_per_wg = (cdiv(ntiles, groups) + 3) & ~3;
-      hipLaunchKernelGGL((k_attn_part_mfma<HD>), dim3(nparts * cdiv(ntiles, a.tiles_per_wg), nkv, B), dim3(BLOCK), 0, st, a);
-      LAUNCH_CHECK();
-      hipLaunchKernelGGL((k_attn_combine_parts<HD, F32>), dim3(M * a.nq), dim3(WAVE), 0, st, a);
-      LAUNCH_CHECK();
-      return SSD_OK;
-    }
+    if (mfma && a.kv.bt == 16) return launch_attn_mfma<HD>(a, nchunks, nkv, B, M, cus, st);
   }
   hipLaunchKernelGGL((k_attn_chunk<HD, DT>), dim3(nchunks, nkv, B), dim3(BLOCK), 0, st, a);
   LAUNCH_CHECK();
@@ -867,9 +877,9 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     a.split_kt = bf16 ? nqd / 32 : 0;
     {
       ProfScope ps(PROF_ATTN, st);
-      if (hd == 32) rc = launch_attn<DT, 32>(a, nchunks, nkv, B, M, kv->attn_mfma, st);
-      else if (hd == 64) rc = launch_attn<DT, 64>(a, nchunks, nkv, B, M, kv->attn_mfma, st);
-      else rc = launch_attn<DT, 128>(a, nchunks, nkv, B, M, kv->attn_mfma, st);
+      if (hd == 32) rc = launch_attn<DT, 32>(a, nchunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
+      else if (hd == 64) rc = launch_attn<DT, 64>(a, nchunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
+      else rc = launch_attn<DT, 128>(a, nchunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
     }
     if (rc) return rc;
 
