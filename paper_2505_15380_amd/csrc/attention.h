@@ -153,12 +153,6 @@ __global__ void __launch_bounds__(WAVE) k_attn_combine(AttnArgs a) {
 // reductions of the kernel before it: 56 us on average over a prefill of 4096); 16 x 7 rows at about 2200: 10 + 3.6 us (15.6 + 4.7).
 constexpr int ATT_WAVES = 8, ATT_TILES = 4;              // waves and row tiles of a workgroup
 
-__device__ __forceinline__ float max_over_groups(float v) {  // over the four lanes l, l ^ 16, l ^ 32, l ^ 48
-  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-}
 template <int HD>
 __global__ void __launch_bounds__(ATT_WAVES * 64, 2) k_attn_mfma(AttnArgs a) {
   constexpr int WQ = ATT_TILES, WK = ATT_WAVES / WQ, KS = HD / 32, DT = HD / 16;

@@ -153,6 +153,20 @@ __device__ __forceinline__ float row16_max(float v) {
   return v;
 }
 
+// All-reduce over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the lanes of a matrix-core tile that hold one row).
+__device__ __forceinline__ float max_over_groups(float v) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+__device__ __forceinline__ float sum_over_groups(float v) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+
 // --------------------------------------------------------------------------------------- bf16 / MFMA
 // Activations are kept in fp32 and fed to the matrix core as a sum of two bf16 values, x = hi + lo with
 // hi = the upper 16 bits of x and lo = bf16(x - hi): two MFMAs per weight fragment instead of one, which

@@ -18,7 +18,7 @@
 
 namespace ssd {
 
-enum { EPI_PARTIAL = 0, EPI_QKV = 1, EPI_SWIGLU = 2 };
+enum { EPI_PARTIAL = 0, EPI_QKV = 1, EPI_SWIGLU = 2, EPI_RESID = 3 };
 
 struct GemmArgs {
   const void* A;     // activations [M][lda]
@@ -41,6 +41,15 @@ struct GemmArgs {
   // EPI_SWIGLU
   void* act;            // [M][N]
   int act_split_kt;     // > 0: act is written as split rows (common.h) with this many k-tiles per row (N / 32)
+  // the norm between two GEMMs without a pass of its own (bf16).  EPI_RESID adds the residual and leaves what the next GEMM
+  // needs: its operand h * gain, and each row's sum of squares over every 16 columns.  EPI_SWIGLU with rms_d > 0 divides
+  // its results by the row's r.m.s. computed from these.
+  float* h;             // EPI_RESID: residual stream [M][N], updated
+  const float* gain;    // EPI_RESID: gain of the norm that follows
+  void* hg;             // EPI_RESID: h * gain as split rows
+  float* sumsq;         // [M][rms_d / 16] written by EPI_RESID, read by EPI_SWIGLU
+  int rms_d;            // columns of the normalised row; 0: the operand is normalised already
+  float rms_eps;
 };
 
 // ------------------------------------------------------------------------------------------ epilogues

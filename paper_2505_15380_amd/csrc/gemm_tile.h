@@ -30,7 +30,7 @@ __device__ __forceinline__ bool tile_block(const TilePlan& p, int& colb, int& ro
 // pairs that the rotary embedding turns.
 template <int EPI, int TN>
 __device__ __forceinline__ int slot_tile(int cb, int j, int hd) {
-  if (EPI == EPI_PARTIAL) return cb * TN + j;
+  if (EPI == EPI_PARTIAL || EPI == EPI_RESID) return cb * TN + j;
   const int p = cb * (TN / 2) + (j % (TN / 2));
   if (EPI == EPI_SWIGLU) return p;
   const int per_head = hd >> 5;
@@ -51,12 +51,66 @@ __device__ __forceinline__ RowDest row_dest(const GemmArgs& g, int row) {
   return d;
 }
 
+// 1 / r.m.s. of the rows of row tile mt for the epilogue's lanes (row = lane % 16), from the sums of squares that EPI_RESID left:
+// each lane group sums a quarter of a row's.  In two steps: the loads go out ahead of the operands', the sum is taken while
+// those travel.
+struct RowSums {
+  const float* p;
+  float x[16];
+};
+__device__ __forceinline__ RowSums row_sums_load(const GemmArgs& g, int mt) {
+  const int lane = threadIdx.x & 63, nt = g.rms_d >> 4;
+  RowSums r;
+  r.p = g.sumsq + (size_t)min(mt * 16 + (lane & 15), g.M - 1) * nt + (lane >> 4);
+#pragma unroll
+  for (int u = 0; u < 16; ++u) r.x[u] = 4 * u + (lane >> 4) < nt ? r.p[4 * u] : 0.f;
+  return r;
+}
+__device__ __forceinline__ float row_inv_rms(const GemmArgs& g, const RowSums& r) {
+  const int nt = g.rms_d >> 4, lg = (threadIdx.x & 63) >> 4;
+  float s = 0.f;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) s += r.x[u];
+  for (int u0 = 16; 4 * u0 < nt; u0 += 8) {                // (d_model > 1024)
+    float y[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) y[u] = 4 * (u0 + u) + lg < nt ? r.p[4 * (u0 + u)] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += y[u];
+  }
+  return 1.0f / sqrtf(sum_over_groups(s) / (float)g.rms_d + g.rms_eps);
+}
+
 // Epilogue of four consecutive features of one row: tile slot j < TN/2 (v0) and its partner j + TN/2 (v1); for partial
 // outputs two independent tiles.  `col` = 4 (lane / 16).
 template <int EPI>
 __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, int t0, int t1, int slice, int row, int col, f32x4 v0, f32x4 v1,
-                                              const RowDest rd) {
+                                              const RowDest rd, float inv) {
   const int ntiles = (g.N + 15) >> 4;
+  if (EPI == EPI_RESID) {                                  // (all lanes stay: the sums cross them)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int t = q ? t1 : t0, n = t * 16 + col;
+      const bool ok = row < g.M && t < ntiles;
+      f32x4 v = q ? v1 : v0;
+      float ss = 0.f;
+      if (ok) {
+        float* hp = g.h + (size_t)row * g.N + n;
+        const f32x4 gn = *(const f32x4*)(g.gain + n);
+        v += *(const f32x4*)hp;
+        *(f32x4*)hp = v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ss = fmaf(v[r], v[r], ss);
+        const f32x4 y = v * gn;
+        bf16_t* o = (bf16_t*)g.hg + split_index(row, n, g.N >> 5);
+        *(uint2*)o = hi_pairs(y);
+        *(uint2*)(o + 512) = lo_pairs(y);
+      }
+      ss = sum_over_groups(ss);
+      if (ok && col == 0) g.sumsq[(size_t)row * ntiles + t] = ss;
+    }
+    return;
+  }
   if (row >= g.M || t0 >= ntiles) return;
   if (EPI == EPI_PARTIAL) {
     float* o = g.out + (size_t)slice * g.out_split_stride + (size_t)row * g.ldo;
@@ -74,7 +128,10 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, int t0, int t1,
   } else if (EPI == EPI_SWIGLU) {
     f32x4 y;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) y[r] = v0[r] / (1.0f + expf(-v0[r])) * v1[r];
+    for (int r = 0; r < 4; ++r) {
+      const float a = v0[r] * inv;
+      y[r] = a / (1.0f + expf(-a)) * (v1[r] * inv);
+    }
     bf16_t* o = (bf16_t*)g.act + split_index(row, t0 * 16 + col, g.act_split_kt);
     *(uint2*)o = hi_pairs(y);
     *(uint2*)(o + 512) = lo_pairs(y);
@@ -165,10 +222,18 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
   RowDest rd[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) rd[i] = EPI == EPI_QKV ? row_dest(g, ((rowb * W + wave) * TM + i) * 16 + (lane & 15)) : RowDest{0, -1};
+  const bool scaled = EPI == EPI_SWIGLU && g.rms_d > 0;
+  RowSums rs[TM];
+  if (scaled)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) rs[i] = row_sums_load(g, (rowb * W + wave) * TM + i);
 #pragma unroll
   for (int b = 0; b < NBUF - 1; ++b) request_w(min(b, nk - 1), b);
 #pragma unroll
   for (int u = 0; u < UA; ++u) request_a(u, min(u, nk - 1));
+  float inv[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) inv[i] = scaled ? row_inv_rms(g, rs[i]) : 1.0f;
   f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -213,9 +278,9 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
 #pragma unroll
     for (int j = 0; j < TN / 2; ++j)
       tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), slot_tile<EPI, TN>(colb, j + TN / 2, hd), slice, row, 4 * (lane >> 4), acc[i][j],
-                         acc[i][j + TN / 2], rd[i]);
+                         acc[i][j + TN / 2], rd[i], inv[i]);
     if (TN % 2)
-      tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, TN - 1, hd), 0x7FFFFF, slice, row, 4 * (lane >> 4), acc[i][TN - 1], acc[i][TN - 1], rd[i]);
+      tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, TN - 1, hd), 0x7FFFFF, slice, row, 4 * (lane >> 4), acc[i][TN - 1], acc[i][TN - 1], rd[i], inv[i]);
   }
 }
 
@@ -227,6 +292,7 @@ template <int EPI, int TM, int TN, int W, int U>
 __global__ void __launch_bounds__(W * 64, 1) k_gemm_kwave(GemmArgs g, TilePlan p) {
   constexpr int RPR = (128 / (W * TN)) < 1 ? 1 : (128 / (W * TN)) > TM ? TM : 128 / (W * TN);     // row tiles per round of the reduction
   __shared__ f32x4 red[W][RPR * TN][64];
+  __shared__ float inv_rms[TM][16];
   int colb, rowb, slice;
   if (!tile_block(p, colb, rowb, slice)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -252,9 +318,16 @@ __global__ void __launch_bounds__(W * 64, 1) k_gemm_kwave(GemmArgs g, TilePlan p
       a[u][m][1] = ap[m][(size_t)kt * 128 + 64];
     }
   };
+  const bool scaled = EPI == EPI_SWIGLU && g.rms_d > 0 && wave < TM;
+  RowSums rs;
+  if (scaled) rs = row_sums_load(g, rowb * TM + wave);
 #pragma unroll
   for (int u = 0; u < U; ++u)
     if (u < nw) request(u, u);
+  if (scaled) {                                            // (read in the epilogue, after a barrier)
+    const float v = row_inv_rms(g, rs);
+    if (lane < 16) inv_rms[wave][lane] = v;
+  }
   f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -308,7 +381,8 @@ __global__ void __launch_bounds__(W * 64, 1) k_gemm_kwave(GemmArgs g, TilePlan p
 #pragma unroll
         for (int x = 1; x < W; ++x) { v0 += red[x][i * TN + j][lane]; v1 += red[x][i * TN + j1][lane]; }
         tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), j1 == j ? 0x7FFFFF : slot_tile<EPI, TN>(colb, j1, hd), slice,
-                           (rowb * TM + i0 + i) * 16 + (lane & 15), 4 * (lane >> 4), v0, v1, rd[q]);
+                           (rowb * TM + i0 + i) * 16 + (lane & 15), 4 * (lane >> 4), v0, v1, rd[q],
+                           EPI == EPI_SWIGLU && g.rms_d > 0 ? inv_rms[i0 + i][lane & 15] : 1.0f);
       }
     }
   }

@@ -576,15 +576,16 @@ static int launch_gemm_f32(const GemmArgs& g, int items, hipStream_t st) {
 
 // Launch of a bf16 GEMM (gemm_tile.h): picks the kernel, the tile and the k-slices from the sizes alone.  Returns the
 // number of k-slices (1 unless `max_slices` allows more: outputs that are k-split partials).
-//   - Few rows (up to 64; for the QKV projection, whose k range cannot be split over workgroups, up to 512): k_gemm_kwave
+//   - Few rows (up to 64; for the QKV and output projections, whose k range is not split over workgroups, up to 512): k_gemm_kwave
 //     with the smallest tile that leaves no more workgroups than compute units.  What bounds it is how long a workgroup's
 //     operand stream takes, so the work is spread as far as one round of workgroups allows; k-split outputs get 8 slices
 //     (4 where k is short) while that round lasts.
 //   - Else k_gemm_tile at the tile and slices of the least estimated time.  The estimate was fitted to measurements of
 //     both model shapes at 72 to 1024 rows: a workgroup's k-tile costs 16.6 cycles per 16x16 tile of its output (twice
 //     what the matrix cores alone would take) or 24 cycles per KB that it loads, whichever is more, workgroups of a
-//     compute unit share it, and one alone cannot hide 160 cycles of latency per k-tile; partial outputs cost their
-//     write and their read at 5 TB/s.  It is within 10 % of the best measured tile at every size that was measured.
+//     compute unit share it, and one alone cannot hide 160 cycles of latency per k-tile (40 cycles per KB where the rows take
+//     much of an L2, beyond 1.5 MB); partial outputs cost their write and their read at 5 TB/s.  It is within 10 % of the
+//     best measured tile at nearly every size that was measured.
 //     Tiles that leave a compute unit one workgroup of four waves keep eight k-tiles in flight instead of four (weights
 //     that come from HBM take more than a microsecond: 97 rows of gate / up 13.1 -> 12.1 us).
 template <int EPI>
@@ -603,7 +604,7 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
   auto wgs = [](const TilePlan& p) { return p.n_colb * p.n_rowb * p.n_slices; };
 #define KWAVE(TM, TN, U)                                                                             \
   if (tm == TM && tn == TN) hipLaunchKernelGGL((k_gemm_kwave<EPI, TM, TN, 8, U>), dim3(8 * p.per_xcd), dim3(512), 0, st, g, p)
-  if (MT <= 4 || (EPI == EPI_QKV && MT <= 32)) {
+  if (MT <= 4 || ((EPI == EPI_QKV || EPI == EPI_RESID) && MT <= 32)) {
     static const int shapes[][2] = {{1, 2}, {2, 2}, {1, 4}, {3, 2}, {1, 6}, {2, 4}, {2, 6}, {3, 4}, {4, 4}, {3, 6}, {4, 6}};   // by area
     int tm = 0, tn = 0;
     TilePlan p{};
@@ -633,17 +634,18 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
 #undef KWAVE
   struct Shape { int tm, tn, w; };
   static const Shape shapes[] = {{1, 4, 4}, {1, 6, 4}, {1, 8, 4}, {1, 10, 4}, {1, 7, 4}, {1, 8, 8}, {1, 7, 8}, {1, 10, 8}, {2, 12, 4}, {2, 8, 8}};
+  const double kb_cycles = (size_t)g.M * g.K * 4 > 1536u * 1024 ? 40.0 : 24.0;
   int best = -1;
   double best_us = 0;
   TilePlan p{};
   for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
     const Shape& c = shapes[i];
-    const bool ok = EPI == EPI_PARTIAL ? c.tn == 4 || c.tn == 7 || c.tn == 8 : EPI == EPI_SWIGLU ? c.tn != 7 && !(c.tm == 2 && c.tn == 8) : c.tn == 4;
+    const bool ok = EPI == EPI_PARTIAL || EPI == EPI_RESID ? c.tn == 4 || c.tn == 7 || c.tn == 8 : EPI == EPI_SWIGLU ? c.tn != 7 && !(c.tm == 2 && c.tn == 8) : c.tn == 4;
     if (!ok) continue;
     for (int ns = 1; ns <= std::min(8, max_slices) && (ns == 1 || KT / ns >= 7); ns *= 2) {
       const TilePlan q = plan(c.tm * c.w, c.tn, ns);
       const int rounds = cdiv(wgs(q), cus);
-      const double cyc = std::max(16.6 * c.tm * c.w * c.tn, 24.0 * (2 * c.tm * c.w + c.tn));
+      const double cyc = std::max(16.6 * c.tm * c.w * c.tn, kb_cycles * (2 * c.tm * c.w + c.tn));
       const double us = q.slice_kt * (rounds * cyc + (rounds == 1 ? 160.0 : 0.0)) / 2400.0 +
                         (max_slices > 1 ? (double)q.n_slices * g.M * g.N * 8.0 / 5e6 : 0.0);
       if (best < 0 || us < best_us * (c.tm * c.w * c.tn > shapes[best].tm * shapes[best].w * shapes[best].tn ? 1.001 : 0.999)) {
@@ -663,7 +665,7 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
   else if constexpr (EPI == EPI_SWIGLU) {
     TILE(1, 6, 4); else TILE(1, 8, 4); else TILE(1, 10, 4); else TILE(1, 8, 8); else TILE(1, 10, 8); else TILE(2, 12, 4);
     else TILE_DEEP(6); else TILE_DEEP(8); else TILE_DEEP(10);
-  } else if constexpr (EPI == EPI_PARTIAL) {
+  } else if constexpr (EPI == EPI_PARTIAL || EPI == EPI_RESID) {
     TILE(1, 7, 4); else TILE(1, 8, 4); else TILE(1, 7, 8); else TILE(1, 8, 8); else TILE(2, 8, 8);
     else TILE_DEEP(7); else TILE_DEEP(8);
   }
@@ -850,6 +852,10 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
   const size_t part_stride = (size_t)M * d;
   constexpr bool bf16 = std::is_same<DT, BF16>::value;     // bf16: GEMM operands are kept as split rows (common.h)
   const int npairs_d = cdiv(cdiv(d, 16), 2);
+  // Up to 512 rows the output projection is not k-split: its epilogue adds the residual and prepares the norm before gate /
+  // up, and no add + norm kernel runs between them.  With more rows the unsplit projection leaves too few workgroups
+  // (1024 rows of the 1.5B shape: 24.8 us against 15 for two slices and 9 for the add + norm kernel).
+  const bool fused_norm = bf16 && M <= 512;
   auto add_norm = [&](int n_part_, const float* gain) -> int {
     const dim3 block(std::min(1024, cdiv(d / 4, WAVE) * WAVE));
     hipLaunchKernelGGL((k_add_norm<bf16>), dim3(M), block, 0, st, kv->h, kv->part, n_part_, part_stride, gain, c.rms_eps, kv->xn, d);
@@ -888,16 +894,24 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     g.out = kv->part; g.out_split_stride = part_stride; g.ldo = d;
     {
       ProfScope ps(PROF_O, st);
-      if constexpr (bf16) { n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, MAX_SPLITS, st); rc = std::min(0, n_part); }
-      else { g.gs = n_part = pick_splits(nqd, npairs_d); rc = launch_gemm_f32<EPI_PARTIAL>(g, npairs_d * n_part, st); }
+      if (fused_norm) {
+        g.h = kv->h; g.gain = L.ln2; g.hg = kv->xn; g.sumsq = kv->part;
+        rc = std::min(0, launch_gemm<EPI_RESID>(g, kv->cus, 1, st));
+      } else if constexpr (bf16) {
+        n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, MAX_SPLITS, st);
+        rc = std::min(0, n_part);
+      } else {
+        g.gs = n_part = pick_splits(nqd, npairs_d);
+        rc = launch_gemm_f32<EPI_PARTIAL>(g, npairs_d * n_part, st);
+      }
     }
     if (rc) return rc;
-
-    if ((rc = add_norm(n_part, L.ln2))) return rc;
+    if (!fused_norm && (rc = add_norm(n_part, L.ln2))) return rc;
 
     g = g0;                                                // gate / up + SwiGLU
     g.A = kv->xn; g.lda = d; g.W0 = L.wgate; g.W1 = L.wup; g.N = c.d_ffn; g.K = d; g.gs = 1; g.act = kv->act;
     g.act_split_kt = bf16 ? c.d_ffn / 32 : 0;
+    g.sumsq = kv->part; g.rms_d = fused_norm ? d : 0; g.rms_eps = c.rms_eps;
     {
       ProfScope ps(PROF_GATEUP, st);
       if constexpr (bf16) rc = std::min(0, launch_gemm<EPI_SWIGLU>(g, kv->cus, 1, st));
