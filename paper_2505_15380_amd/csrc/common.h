@@ -248,19 +248,29 @@ __device__ __forceinline__ int block_excl_scan(int v, int* w16, int* total) {
 // walk over them would: a prefix sum of what the earlier ones take (give) says where on the stack a thread's blocks are.
 // (One thread walking 64 sequences costs a chain of dependent memory round trips per sequence: 50 us and more.)
 //
-// kv_reserve_all: make `seq` own the blocks that cover `tokens` positions.
-__device__ inline void kv_reserve_all(const KvView& kv, bool in, int seq, int tokens, int* w16) {
-  const int own = in ? kv.owned[seq] : 0;
+// kv_reserve_all: make `seq` own the blocks that cover `tokens` positions.  The blocks are handed out by all threads together
+// (a prefill chunk of one sequence takes 64); scan: blockDim + 16 entries of LDS, slot: blockDim entries.
+__device__ inline void kv_reserve_all(const KvView& kv, bool in, int seq, int tokens, int* scan, int* slot) {
+  const int nt = blockDim.x, own = in ? kv.owned[seq] : 0;
   const int top = kv.ctl[0];
   const int need = in ? max(0, ceil_div(tokens, kv.bt) - own) : 0;
   const int want = min(need, max(0, kv.mbps - own));
   int total;
-  const int before = block_excl_scan(want, w16, &total);
+  const int before = block_excl_scan(want, scan + nt, &total);
   const int take = max(0, min(want, top - before));
   if (take < need) kv.ctl[1] = KV_ERR_POOL;
-  for (int t = 0; t < take; ++t) kv.table[seq * kv.mbps + own + t] = kv.free_stack[top - before - 1 - t];
   if (take > 0) kv.owned[seq] = own + take;
+  scan[threadIdx.x] = before + want;
+  slot[threadIdx.x] = seq * kv.mbps + own - before;
   __syncthreads();                                         // every thread has read the stack's height
+  for (int i = threadIdx.x; i < min(total, top); i += nt) {
+    int lo = 0, hi = nt - 1;                               // the thread whose blocks include the i-th one
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (scan[mid] > i) hi = mid; else lo = mid + 1;
+    }
+    kv.table[slot[lo] + i] = kv.free_stack[top - 1 - i];
+  }
   if (threadIdx.x == 0) kv.ctl[0] = max(0, top - total);
   __syncthreads();
 }
@@ -284,21 +294,6 @@ __device__ inline void kv_truncate_all(const KvView& kv, bool in, int seq, int n
   __syncthreads();
   if (threadIdx.x == 0) kv.ctl[0] = top + total;
   __syncthreads();
-}
-
-// Truncate one sequence (one thread).
-__device__ inline void kv_truncate(const KvView& kv, int seq, int new_len) {
-  const int keep = ceil_div(new_len, kv.bt);
-  int own = kv.owned[seq];
-  int top = kv.ctl[0];
-  while (own > keep) {
-    --own;
-    kv.free_stack[top++] = kv.table[seq * kv.mbps + own];
-    kv.table[seq * kv.mbps + own] = -1;
-  }
-  kv.owned[seq] = own;
-  kv.ctl[0] = top;
-  kv.len[seq] = new_len;
 }
 
 __device__ inline void kv_publish_flags(const KvView& kv) {

@@ -16,12 +16,54 @@ struct EmbedArgs {
   const void* embed;        // [n_embed][d]
   int n_embed, d;
   float* h;                 // [M][d]
+  const float* gain;        // of the first layer's norm
+  float eps;
+  void* xn;                 // the normalised rows: fp32 or split rows
 };
 
-// One workgroup per row: resolve the row's token and position, copy its embedding into the residual stream.
-// Workgroup 0 also reserves the cache blocks the forward will write (sequences in ascending order).
-template <typename WT>
-__global__ void __launch_bounds__(BLOCK) k_embed(EmbedArgs e) {
+// RMSNorm of a row whose columns 4 tid .. + 3 (+ 4 blockDim ..) a workgroup's threads hold, the first four of each thread in v0 and
+// the rest in memory (hr); ss: the thread's share of the sum of squares.
+template <bool SPLIT>
+__device__ __forceinline__ void norm_row(const float* hr, f32x4 v0, float ss, const float* gain, float eps, void* xn, int m, int d,
+                                         float* s16) {
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) s16[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  float tot = 0.f;
+  for (int w = 0; w < (int)blockDim.x >> 6; ++w) tot += s16[w];
+  const float inv = 1.0f / sqrtf(tot / (float)d + eps);
+  for (int i = threadIdx.x * 4; i < d; i += blockDim.x * 4) {
+    f32x4 v = i == (int)threadIdx.x * 4 ? v0 : *(const f32x4*)(hr + i);
+    const f32x4 gn = *(const f32x4*)(gain + i);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = v[r] * inv * gn[r];
+    if (SPLIT) {
+      bf16_t* o = (bf16_t*)xn + split_index(m, i, d >> 5);
+      *(uint2*)o = hi_pairs(v);
+      *(uint2*)(o + 512) = lo_pairs(v);
+    } else {
+      *(f32x4*)((float*)xn + (size_t)m * d + i) = v;
+    }
+  }
+}
+
+// One workgroup per row: resolve the row's token and position, copy its embedding into the residual stream and normalise it
+// for the first layer.  One more workgroup reserves the cache blocks the forward will write (sequences in ascending order).
+// The kernel is a chain of dependent reads (state, token, embedding, norm), so the reservation is a chain of its own beside
+// it and the norm no launch of its own: a forward is 4 us shorter, a prefill chunk of 1024 rows another 8.
+template <typename WT, bool SPLIT>
+__global__ void __launch_bounds__(1024) k_embed(EmbedArgs e) {
+  if ((int)blockIdx.x == e.rows.M) {
+    __shared__ int scan[1024 + 16], slot[1024];
+    for (int b0 = 0; b0 < e.n_seqs; b0 += blockDim.x) {
+      const bool in = b0 + (int)threadIdx.x < e.n_seqs;
+      const int s = e.rows.seq0 + (in ? b0 + (int)threadIdx.x : 0);
+      const int o = e.pcap ? e.pcap - e.kv.n_pend[s] : 0;
+      kv_reserve_all(e.kv, in, s, e.kv.len[s] + e.rows.R - o, scan, slot);
+    }
+    return;
+  }
+  __shared__ float s16[16];
   const int m = blockIdx.x;
   const int brel = m / e.rows.R, j = m - brel * e.rows.R;
   const int seq = e.rows.seq0 + brel;
@@ -37,16 +79,17 @@ __global__ void __launch_bounds__(BLOCK) k_embed(EmbedArgs e) {
   tok = min(max(tok, 0), e.n_embed - 1);
   if (threadIdx.x == 0) { e.rows.pos[m] = pos; e.rows.active[m] = active; }
   const typename WT::T* src = (const typename WT::T*)e.embed + (size_t)tok * e.d;
-  for (int i = threadIdx.x; i < e.d; i += BLOCK) e.h[(size_t)m * e.d + i] = WT::ld(src + i);
-  if (m == 0) {
-    __shared__ int w16[16];
-    for (int b0 = 0; b0 < e.n_seqs; b0 += BLOCK) {
-      const bool in = b0 + (int)threadIdx.x < e.n_seqs;
-      const int s = e.rows.seq0 + (in ? b0 + (int)threadIdx.x : 0);
-      const int o = e.pcap ? e.pcap - e.kv.n_pend[s] : 0;
-      kv_reserve_all(e.kv, in, s, e.kv.len[s] + e.rows.R - o, w16);
-    }
+  float* hr = e.h + (size_t)m * e.d;
+  f32x4 v0 = {0, 0, 0, 0};
+  float ss = 0.f;
+  for (int i = threadIdx.x * 4; i < e.d; i += blockDim.x * 4) {
+    const f32x4 v = {WT::ld(src + i), WT::ld(src + i + 1), WT::ld(src + i + 2), WT::ld(src + i + 3)};
+    *(f32x4*)(hr + i) = v;
+    if (i == (int)threadIdx.x * 4) v0 = v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) ss = fmaf(v[r], v[r], ss);
   }
+  norm_row<SPLIT>(hr, v0, ss, e.gain, e.eps, e.xn, m, e.d, s16);
 }
 
 // h[m] += sum of the k-split partials of the previous GEMM (ascending split order); xn[m] = RMSNorm(h[m]) * gain, as fp32 rows
@@ -58,7 +101,7 @@ template <bool SPLIT>
 __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, int n_part, size_t part_stride, const float* gain,
                                                    float eps, void* xn, int d) {
   __shared__ float s16[16];
-  const int m = blockIdx.x, KT = d >> 5;
+  const int m = blockIdx.x;
   float* hr = h + (size_t)m * d;
   f32x4 v0 = {0, 0, 0, 0};
   float ss = 0.f;
@@ -78,25 +121,7 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
 #pragma unroll
     for (int r = 0; r < 4; ++r) ss = fmaf(v[r], v[r], ss);
   }
-  ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) s16[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  float tot = 0.f;
-  for (int w = 0; w < (int)blockDim.x >> 6; ++w) tot += s16[w];
-  const float inv = 1.0f / sqrtf(tot / (float)d + eps);
-  for (int i = threadIdx.x * 4; i < d; i += blockDim.x * 4) {
-    f32x4 v = i == (int)threadIdx.x * 4 ? v0 : *(const f32x4*)(hr + i);
-    const f32x4 gn = *(const f32x4*)(gain + i);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = v[r] * inv * gn[r];
-    if (SPLIT) {
-      bf16_t* o = (bf16_t*)xn + split_index(m, i, KT);
-      *(uint2*)o = hi_pairs(v);
-      *(uint2*)(o + 512) = lo_pairs(v);
-    } else {
-      *(f32x4*)((float*)xn + (size_t)m * d + i) = v;
-    }
-  }
+  norm_row<SPLIT>(hr, v0, ss, gain, eps, xn, m, d, s16);
 }
 
 // ------------------------------------------------------------------------------------------ warp + softmax
@@ -382,9 +407,10 @@ __device__ __forceinline__ void accept_seq(const AcceptArgs a, const int b, cons
   const uint32_t seq = (uint32_t)(a.seq0 + b);
   uint64_t step = a.step;
   if (a.step_dev) step += (uint64_t)(uint32_t)a.step_dev[0] | ((uint64_t)(uint32_t)a.step_dev[1] << 32);
-  // a single sequence commits without waiting for anyone: its cache state is requested now (nothing but this kernel's
-  // own commit changes it), so that the commit at the end is stores only
-  const bool solo = a.kv.len != nullptr && a.B == 1;
+  // A sequence commits without waiting for anyone where no other commit depends on it: a single one, and any of a step
+  // without drafts, which keeps every row it has reserved blocks for and so gives none back.  Its cache state is requested
+  // now (nothing but its own commit changes it), so that the commit at the end is stores only.
+  const bool solo = a.kv.len != nullptr && (a.B == 1 || (a.K == 0 && !a.bump_step));
   int st_len = 0, st_npend = 0, st_owned = 0, st_top = 0, st_err = 0, st_launch = 0;
   uint32_t st_dev_err = 0;
   if (solo && tid == 0) {
@@ -460,7 +486,7 @@ __device__ __forceinline__ void accept_seq(const AcceptArgs a, const int b, cons
   if (a.kv.len == nullptr) return;
   if (solo) {                                              // kv_truncate + kv_publish on the values read at the start
     if (tid == 0) {
-      if (a.bump_launch) a.kv.ctl[3] = st_launch + 1;
+      if (a.bump_launch && b == 0) a.kv.ctl[3] = st_launch + 1;
       if (a.bump_step && a.step_dev) {
         const uint64_t nx = step - a.step + 1;
         ((int32_t*)a.step_dev)[0] = (int32_t)(uint32_t)nx;
@@ -471,14 +497,16 @@ __device__ __forceinline__ void accept_seq(const AcceptArgs a, const int b, cons
       if (st_dev_err) return;                              // the forward did not finish: its logits mean nothing, commit nothing
       const int new_len = st_len + st_npend + n;
       const int keep = ceil_div(new_len, a.kv.bt);
-      int own = st_owned, top = st_top;
-      while (own > keep) {
-        --own;
-        a.kv.free_stack[top++] = a.kv.table[seq * a.kv.mbps + own];
-        a.kv.table[seq * a.kv.mbps + own] = -1;
+      if (a.B == 1) {
+        int own = st_owned, top = st_top;
+        while (own > keep) {
+          --own;
+          a.kv.free_stack[top++] = a.kv.table[seq * a.kv.mbps + own];
+          a.kv.table[seq * a.kv.mbps + own] = -1;
+        }
+        a.kv.owned[seq] = own;
+        a.kv.ctl[0] = top;
       }
-      a.kv.owned[seq] = own;
-      a.kv.ctl[0] = top;
       a.kv.len[seq] = new_len;
       a.kv.pend[seq * 2] = sh_tok;
       a.kv.n_pend[seq] = 1;
@@ -544,14 +572,28 @@ __global__ void __launch_bounds__(SBLOCK) k_warp_accept(WarpArgs w, AcceptArgs a
 // rollback: a target beyond the cached length is refused (the state stays, KV_ERR_ROLLBACK is raised).  add_len is
 // the commit of a prefill chunk.  after_forward: the kernel follows a forward on this cache (advances its launch number;
 // commits nothing if that forward did not finish).
-__global__ void k_kv_set(KvView kv, int seq, int new_len, int add_len, int set_pending, int pending_value,
-                         const int32_t* pending_ptr, int after_forward) {
-  if (threadIdx.x || blockIdx.x) return;
-  if (after_forward) kv_bump_launch(kv);
-  if (*kv.err) { kv_publish_flags(kv); return; }
-  if (new_len > kv.len[seq]) { kv.ctl[1] |= KV_ERR_ROLLBACK; kv_publish_flags(kv); return; }
-  const int target = new_len >= 0 ? new_len : kv.len[seq] + add_len;
-  kv_truncate(kv, seq, target);
+__global__ void __launch_bounds__(BLOCK) k_kv_set(KvView kv, int seq, int new_len, int add_len, int set_pending, int pending_value,
+                                                  const int32_t* pending_ptr, int after_forward) {
+  const int tid = threadIdx.x, len = kv.len[seq], own = kv.owned[seq], top = kv.ctl[0];
+  const bool failed = *kv.err != 0, refused = new_len > len;
+  const int target = new_len >= 0 ? new_len : len + add_len, keep = ceil_div(target, kv.bt);
+  __syncthreads();                                         // every thread has read the state
+  if (tid == 0 && after_forward) kv_bump_launch(kv);
+  if (failed || refused) {
+    if (tid == 0) {
+      if (!failed) kv.ctl[1] |= KV_ERR_ROLLBACK;
+      kv_publish_flags(kv);
+    }
+    return;
+  }
+  int32_t* table = kv.table + (size_t)seq * kv.mbps;
+  for (int i = keep + tid; i < own; i += BLOCK) {          // highest table index first onto the stack
+    kv.free_stack[top + own - 1 - i] = table[i];
+    table[i] = -1;
+  }
+  if (tid) return;
+  if (own > keep) { kv.owned[seq] = keep; kv.ctl[0] = top + own - keep; }
+  kv.len[seq] = target;
   if (set_pending) {
     kv.pend[seq * 2] = pending_ptr ? *pending_ptr : pending_value;
     kv.n_pend[seq] = 1;

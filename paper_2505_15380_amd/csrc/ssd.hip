@@ -838,8 +838,11 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
 
   EmbedArgs e;
   e.kv = kv->v; e.rows = rows; e.pcap = pcap; e.n_seqs = B; e.tokens = dev_tokens; e.tok_stride = tok_stride;
+  constexpr bool bf16 = std::is_same<DT, BF16>::value;     // bf16: GEMM operands are kept as split rows (common.h)
+  const dim3 row_block(std::min(1024, cdiv(d / 4, WAVE) * WAVE));          // a thread per four columns of a row
   e.embed = m->embed; e.n_embed = c.n_embed; e.d = d; e.h = kv->h;
-  hipLaunchKernelGGL((k_embed<DT>), dim3(M), dim3(BLOCK), 0, st, e);
+  e.gain = m->layers[0].ln1; e.eps = c.rms_eps; e.xn = kv->xn;
+  hipLaunchKernelGGL((k_embed<DT, bf16>), dim3(M + 1), row_block, 0, st, e);
   LAUNCH_CHECK();
 
   int max_len = 0;
@@ -850,15 +853,13 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
   memset(&g0, 0, sizeof g0);
   g0.M = M; g0.kv = kv->v; g0.rows = rows; g0.nq = nq; g0.rope = m->rope;
   const size_t part_stride = (size_t)M * d;
-  constexpr bool bf16 = std::is_same<DT, BF16>::value;     // bf16: GEMM operands are kept as split rows (common.h)
   const int npairs_d = cdiv(cdiv(d, 16), 2);
   // Up to 512 rows the output projection is not k-split: its epilogue adds the residual and prepares the norm before gate /
   // up, and no add + norm kernel runs between them.  With more rows the unsplit projection leaves too few workgroups
   // (1024 rows of the 1.5B shape: 24.8 us against 15 for two slices and 9 for the add + norm kernel).
   const bool fused_norm = bf16 && M <= 512;
   auto add_norm = [&](int n_part_, const float* gain) -> int {
-    const dim3 block(std::min(1024, cdiv(d / 4, WAVE) * WAVE));
-    hipLaunchKernelGGL((k_add_norm<bf16>), dim3(M), block, 0, st, kv->h, kv->part, n_part_, part_stride, gain, c.rms_eps, kv->xn, d);
+    hipLaunchKernelGGL((k_add_norm<bf16>), dim3(M), row_block, 0, st, kv->h, kv->part, n_part_, part_stride, gain, c.rms_eps, kv->xn, d);
     LAUNCH_CHECK();
     return SSD_OK;
   };
@@ -866,7 +867,7 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
   int rc;
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW& L = m->layers[l];
-    if ((rc = add_norm(n_part, L.ln1))) return rc;
+    if (l > 0 && (rc = add_norm(n_part, L.ln1))) return rc;      // (the first layer's: in k_embed)
     GemmArgs g = g0;                                       // QKV + bias + rotary + cache write
     g.A = kv->xn; g.lda = d; g.W0 = L.wqkv; g.W1 = L.wqkv; g.N = nqkv; g.K = d; g.gs = 1;
     g.bias = L.bqkv; g.q = kv->q; g.layer = l;
@@ -967,7 +968,7 @@ extern "C" int ssd_prefill(ssd_model* m, ssd_kv* kv, int seq, const int32_t* dev
   if (seq < 0 || seq >= kv->max_seqs) return fail(SSD_EINVAL, "sequence %d out of range", seq);
   if ((rc = kv_check_flags(kv))) return rc;
   hipStream_t st = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(1), 0, st, kv->v, seq, 0, 0, 0, 0, (const int32_t*)nullptr, 0);
+  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, 0, 0, 0, 0, (const int32_t*)nullptr, 0);
   LAUNCH_CHECK();
   kv->len_ub[seq] = 0;
   kv->npend_ub[seq] = 0;
@@ -976,11 +977,11 @@ extern "C" int ssd_prefill(ssd_model* m, ssd_kv* kv, int seq, const int32_t* dev
   for (int i = 0; i < n - 1; i += chunk) {
     const int R = std::min(chunk, n - 1 - i);
     if ((rc = forward_any(m, kv, seq, 1, R, 0, dev_tokens + i, 0, false, st))) return rc;
-    hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(1), 0, st, kv->v, seq, -1, R, 0, 0, (const int32_t*)nullptr, 1);
+    hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, -1, R, 0, 0, (const int32_t*)nullptr, 1);
     LAUNCH_CHECK();
     kv->len_ub[seq] += R;
   }
-  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(1), 0, st, kv->v, seq, -1, 0, 1, 0, dev_tokens + (n - 1), 0);
+  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, -1, 0, 1, 0, dev_tokens + (n - 1), 0);
   LAUNCH_CHECK();
   kv->npend_ub[seq] = 1;
   return SSD_OK;
@@ -1177,7 +1178,7 @@ extern "C" int ssd_kv_rollback(ssd_kv* kv, int seq, int new_len, int pending_tok
     if (new_len < 0 || new_len > kv->len_ub[seq])
       return fail(SSD_EINVAL, "rollback to %d but sequence %d holds %d positions", new_len, seq, kv->len_ub[seq]);
   }
-  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(1), 0, st, kv->v, seq, new_len, 0, 1, pending_token, (const int32_t*)nullptr, 0);
+  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, new_len, 0, 1, pending_token, (const int32_t*)nullptr, 0);
   LAUNCH_CHECK();
   kv->len_ub[seq] = new_len;
   kv->npend_ub[seq] = 1;
