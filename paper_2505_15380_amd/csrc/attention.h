@@ -22,7 +22,8 @@ struct AttnArgs {
   int NC;               // chunk capacity of the partial buffers
   void* out;            // [M][nq*hd] (combine)
   int split_kt;         // > 0: `out` is written as split rows (common.h) with this many k-tiles per row (nq*hd / 32)
-  int nparts, part_keys;      // k_attn_mfma: grid.x = nparts x groups of row tiles; keys per part (a multiple of 64)
+  int nparts, part_keys;      // k_attn_mfma: grid.x = nparts x groups of row tiles; keys per part (a multiple of 64).  k_attn_f32:
+                              // chunks of the longest sequence
 };
 
 template <int HD, typename KVT>
@@ -129,6 +130,118 @@ __global__ void __launch_bounds__(WAVE) k_attn_combine(AttnArgs a) {
       if (a.split_kt > 0) st_split_value((bf16_t*)a.out, a.split_kt, m, hq * HD + d, o[i] / l);
       else AT::st(out + d, o[i] / l);
     }
+  }
+}
+
+// The same for fp32 caches in one launch, on v_mfma_f32_16x16x4_f32 (full fp32 products and sums).  A workgroup takes 16 of the query
+// rows that share a kv head of a sequence; its waves walk the 64-key chunks w, w + W, .. with a running (max, sum, weighted
+// values) per row and meet in LDS, so a row's order of sums depends on its position alone.  Scores and outputs are computed
+// transposed: a lane holds one row's scores of the keys 4 kg .. 4 kg + 3 of a tile, which is what the product with the
+// values wants from it, and both operands come from the cache as 16 bytes per lane (dims of a key, tokens of a dim).
+// A chain of launch, block table, cache, merge bounds it: 6.1 us at five rows and 68 cached positions, where the two kernels
+// above take 7.2 + 3.0 (a vector-unit version of this kernel took 7.9: twice the instructions, fetched cold on every launch).
+template <int HD>
+constexpr int att_f32_waves() { return HD <= 64 ? 8 : 4; }
+
+template <int HD>
+__global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArgs a) {
+  constexpr int W = att_f32_waves<HD>(), DT = HD / 16;
+  __shared__ float po[W][16][HD + 4];
+  __shared__ float pm[W][16], pl[W][16];
+  const int kvh = blockIdx.y, brel = blockIdx.z, seq = a.rows.seq0 + brel;
+  const int G = a.nq / a.kv.nkv, nrows = a.rows.R * G, m_first = brel * a.rows.R;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int li = lane & 15, kg = lane >> 4;
+  const float* pool = (const float*)a.kv.pool;
+  auto q_of = [&](int r, int& m) {                         // query row r of the group: its row of the forward and its values
+    const int j = r / G;
+    m = m_first + j;
+    return ((size_t)m * a.nq + kvh * G + r - j * G) * HD;
+  };
+  int m;
+  const f32x4* qp = (const f32x4*)(a.q + q_of(min((int)blockIdx.x * 16 + li, nrows - 1), m)) + kg;
+  const int pos = a.rows.pos[m], pos_max = a.rows.pos[m_first + a.rows.R - 1];
+  f32x4 q[DT];
+#pragma unroll
+  for (int s = 0; s < DT; ++s) q[s] = qp[s * 4];
+  f32x4 o[DT];
+#pragma unroll
+  for (int s = 0; s < DT; ++s) o[s] = f32x4{0, 0, 0, 0};
+  float mrow = -INFINITY, lrow = 0.f;
+  for (int c = wave; c < a.nparts; c += W) {               // (a.nparts: chunks of the longest sequence)
+    const int p0 = c * ATT_CHUNK;
+    const int32_t* tab = a.kv.table + (size_t)seq * a.kv.mbps;
+    f32x4 k[4][DT];
+    int blk[4];                                            // a tile of 16 keys is a block
+#pragma unroll
+    for (int t = 0; t < 4; ++t) blk[t] = tab[min(c * 4 + t, a.kv.mbps - 1)];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const f32x4* kp = (const f32x4*)(pool + kv_offset(a.kv, a.layer, 0, max(blk[t], 0), kvh, li)) + kg;
+#pragma unroll
+      for (int s = 0; s < DT; ++s) k[t][s] = kp[s * 4];
+    }
+    if (p0 > pos_max) break;
+    f32x4 w[4];
+    float mx = mrow;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      w[t] = f32x4{0, 0, 0, 0};
+#pragma unroll
+      for (int s = 0; s < DT; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[t][s][e], q[s][e], w[t], 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        w[t][e] = p0 + t * 16 + kg * 4 + e <= pos ? (blk[t] >= 0 ? w[t][e] * a.scale : 0.f) : -INFINITY;
+        mx = fmaxf(mx, w[t][e]);
+      }
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
+    const float base = mx == -INFINITY ? 0.f : mx;         // (no key of the chunk is the row's: all weights are 0)
+    const float keep = expf(mrow - base);
+    float sum = 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { w[t][e] = expf(w[t][e] - base); sum += w[t][e]; }
+    sum += __shfl_xor(sum, 16, WAVE);
+    sum += __shfl_xor(sum, 32, WAVE);
+    lrow = lrow * keep + sum;
+    mrow = mx;
+#pragma unroll
+    for (int s = 0; s < DT; ++s) {
+      o[s] *= keep;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int pv = p0 + t * 16 + kg * 4;
+        const f32x4 v = *(const f32x4*)(pool + kv_offset(a.kv, a.layer, 1, max(blk[t], 0), kvh, 0) + (s * 16 + li) * 16 + kg * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)                        // what lies beyond may never have been written
+          o[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(blk[t] >= 0 && pv + e <= pos_max ? v[e] : 0.f, w[t][e], o[s], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < DT; ++s) *(f32x4*)&po[wave][li][s * 16 + kg * 4] = o[s];
+  if (kg == 0) { pm[wave][li] = mrow; pl[wave][li] = lrow; }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 16 * (HD / 4); i += W * WAVE) {
+    const int r = i / (HD / 4), d = (i - r * (HD / 4)) * 4;
+    if ((int)blockIdx.x * 16 + r >= nrows) break;
+    float mx = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int x = 0; x < W; ++x) mx = fmaxf(mx, pm[x][r]);  // (position 0 is every row's: finite)
+    f32x4 acc = {0, 0, 0, 0};
+#pragma unroll
+    for (int x = 0; x < W; ++x) {
+      const float f = expf(pm[x][r] - mx);
+      l = fmaf(pl[x][r], f, l);
+      acc += *(const f32x4*)&po[x][r][d] * f;
+    }
+    int mm;
+    *(f32x4*)((float*)a.out + q_of((int)blockIdx.x * 16 + r, mm) + d) = acc / l;
   }
 }
 

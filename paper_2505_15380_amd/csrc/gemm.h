@@ -1,17 +1,12 @@
-// Skinny GEMMs of the decoder: Y[M,N] = X[M,Kd] . W[N,Kd]^T with M = rows of one forward (<= 512).
-// Up to a few tens of rows the work is weight streaming: every weight byte is read once, coalesced, and the
-// contraction runs on MFMA 16x16x32 bf16 tiles (rows padded to 16; padded rows cost nothing that matters).
+// GEMMs of the decoder, Y[M,N] = X[M,K] . W[N,K]^T with M = rows of one forward: what both storage types share (arguments,
+// epilogues) and the fp32 kernel.  The bf16 kernels are in gemm_tile.h.
 //
-// Work decomposition, identical for both storage types:
-//   a workgroup (4 waves) owns two 16-column tiles (t0 from W0, t1 from W1) and one global k-split;
-//   its waves split the k range between them, partial tiles are summed through LDS in a fixed order,
-//   and one thread per (row, col) applies the epilogue.  Nothing is accumulated with atomics, so every output
-//   element has one summation order that does not depend on M: a row computed alone (autoregressive step)
-//   and the same row computed among K+1 (verification) give the same bits.
+// No output element is accumulated with atomics: each has one summation order that does not depend on M, so a row computed
+// alone (autoregressive step) and the same row computed among K+1 (verification) give the same bits.
 //
 // bf16 weights are pre-packed so that a wave reads one tile (16 out-features x 32 in-features) as 64
 // consecutive 16-byte pieces: piece l of tile (nt, kt) = W[nt*16 + l%16][kt*32 + 8*(l/16) .. +7], tiles ordered
-// [nt][kt].  That is exactly the B-operand fragment of the MFMA, so a weight goes from HBM to the matrix
+// [nt][kt].  That is exactly an operand fragment of the MFMA, so a weight goes from HBM to the matrix
 // core through one dwordx4 load and nothing else.
 #pragma once
 #include "common.h"
@@ -21,12 +16,10 @@ namespace ssd {
 enum { EPI_PARTIAL = 0, EPI_QKV = 1, EPI_SWIGLU = 2, EPI_RESID = 3 };
 
 struct GemmArgs {
-  const void* A;     // activations [M][lda]
-  int lda;
+  const void* A;     // activations: fp32 [M][K], or split rows (common.h)
   const void* W0;    // weight matrix of tile slot 0 (packed bf16, or canonical fp32 [N][K])
   const void* W1;    // weight matrix of tile slot 1
   int M, N, K;       // N = out features of one matrix (unpadded)
-  int gs;            // global k-splits
   // EPI_PARTIAL: out[s][m][n]
   float* out;
   size_t out_split_stride;
@@ -41,11 +34,12 @@ struct GemmArgs {
   // EPI_SWIGLU
   void* act;            // [M][N]
   int act_split_kt;     // > 0: act is written as split rows (common.h) with this many k-tiles per row (N / 32)
-  // the norm between two GEMMs without a pass of its own (bf16).  EPI_RESID adds the residual and leaves what the next GEMM
+  // the norm before a GEMM without a pass of its own.  fp32: A is the residual stream, and a kernel given a `gain` normalises
+  // its rows itself (and EPI_RESID only adds to the residual stream).  bf16: EPI_RESID adds the residual and leaves what the next GEMM
   // needs: its operand h * gain, and each row's sum of squares over every 16 columns.  EPI_SWIGLU with rms_d > 0 divides
   // its results by the row's r.m.s. computed from these.
   float* h;             // EPI_RESID: residual stream [M][N], updated
-  const float* gain;    // EPI_RESID: gain of the norm that follows
+  const float* gain;    // fp32: gain of the norm before; bf16, EPI_RESID: gain of the norm that follows
   void* hg;             // EPI_RESID: h * gain as split rows
   float* sumsq;         // [M][rms_d / 16] written by EPI_RESID, read by EPI_SWIGLU
   int rms_d;            // columns of the normalised row; 0: the operand is normalised already
@@ -53,31 +47,27 @@ struct GemmArgs {
 };
 
 // ------------------------------------------------------------------------------------------ epilogues
-template <int EPI, typename AT, typename KVT>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, int t0, int t1, int split, int row, int col,
-                                              float v0, float v1) {
-  if (row >= g.M) return;
+// One output row's columns `col` of the tiles t0 and t1 (t1 beyond the last tile: nothing there).
+template <int EPI>
+__device__ __forceinline__ void gemm_epilogue_f32(const GemmArgs& g, int t0, int t1, int row, int col, float v0, float v1, int pos, int blk,
+                                                  float2 cs) {
+  const int n0 = t0 * 16 + col, n1 = t1 * 16 + col;
   if (EPI == EPI_PARTIAL) {
-    float* o = g.out + (size_t)split * g.out_split_stride + (size_t)row * g.ldo;
-    const int n0 = t0 * 16 + col, n1 = t1 * 16 + col;
+    float* o = g.out + (size_t)row * g.ldo;
     if (n0 < g.N) o[n0] = v0;
     if (n1 < g.N) o[n1] = v1;
+  } else if (EPI == EPI_RESID) {
+    float* o = g.h + (size_t)row * g.N;
+    if (n0 < g.N) o[n0] += v0;
+    if (n1 < g.N) o[n1] += v1;
   } else if (EPI == EPI_SWIGLU) {
-    const int n = t0 * 16 + col;
-    if (n < g.N) {
-      const float s = v0 / (1.0f + expf(-v0));
-      if (g.act_split_kt > 0) st_split_value((bf16_t*)g.act, g.act_split_kt, row, n, s * v1);
-      else AT::st((typename AT::T*)g.act + (size_t)row * g.N + n, s * v1);
-    }
+    if (n0 < g.N) ((float*)g.act)[(size_t)row * g.N + n0] = v0 / (1.0f + expf(-v0)) * v1;
   } else {  // EPI_QKV: the two tiles hold dims d and d + hd/2 of one head
     const int hd = g.kv.hd, half = hd >> 1;
-    const int n0 = t0 * 16 + col;
     const int head = n0 / hd, d = n0 - head * hd;
     if (g.bias) { v0 += g.bias[n0]; v1 += g.bias[n0 + half]; }
     const int nq = g.nq, nkv = g.kv.nkv;
-    const int pos = g.rows.pos[row];
     if (head < nq + nkv) {
-      const float2 cs = g.rope[(size_t)pos * half + d];
       const float r0 = v0 * cs.x - v1 * cs.y;
       const float r1 = v1 * cs.x + v0 * cs.y;
       v0 = r0; v1 = r1;
@@ -85,102 +75,113 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, int t0, int t1,
     if (head < nq) {
       float* qo = g.q + (size_t)row * nq * hd + head * hd + d;
       qo[0] = v0; qo[half] = v1;
-    } else if (g.rows.active[row]) {
+    } else if (blk >= 0) {
       const int which = head < nq + nkv ? 0 : 1;
       const int kvh = head - nq - which * nkv;
-      const int seq = g.rows.seq0 + row / g.rows.R;
-      const int blk = g.kv.table[seq * g.kv.mbps + pos / g.kv.bt];
-      if (blk >= 0) {
-        typename KVT::T* base = (typename KVT::T*)g.kv.pool + kv_offset(g.kv, g.layer, which, blk, kvh, 0);
-        const int tok = pos % g.kv.bt;
-        if (which == 0) {                                   // keys: [token][dim]
-          KVT::st(base + tok * hd + d, v0);
-          KVT::st(base + tok * hd + d + half, v1);
-        } else {                                            // values: [dim][token] (token-minor)
-          KVT::st(base + d * g.kv.bt + tok, v0);
-          KVT::st(base + (d + half) * g.kv.bt + tok, v1);
-        }
+      float* base = (float*)g.kv.pool + kv_offset(g.kv, g.layer, which, blk, kvh, 0);
+      const int tok = pos % g.kv.bt;
+      if (which == 0) {                                     // keys: [token][dim]
+        base[tok * hd + d] = v0;
+        base[tok * hd + d + half] = v1;
+      } else {                                              // values: [dim][token] (token-minor)
+        base[d * g.kv.bt + tok] = v0;
+        base[(d + half) * g.kv.bt + tok] = v1;
       }
     }
   }
 }
+
+// ------------------------------------------------------------------------------------------------------------ fp32
+// Weights canonical fp32 [N][K], K % 32 == 0, on v_mfma_f32_16x16x4_f32: full fp32 products and sums.  A workgroup owns 16
+// rows x two column tiles (t0 from W0, t1 from W1; EPI_QKV: the tiles that hold dims d and d + hd/2 of one head) and its 4 to
+// 16 waves share the k range in steps of 16: a lane loads 16 bytes of each operand, four consecutive k, and the step's four
+// instructions take one of them each from every lane.  The waves' sums meet in LDS in wave order.
+//
+// With a gain, A is the residual stream and the kernel normalises it: it multiplies by the gain as it loads, sums the
+// squares beside the products and divides the results by the r.m.s. at the end, so no kernel runs between two GEMMs.
+//
+// What bounds it at the sizes that fp32 is used at (a few rows, widths of 64 to 512) is the length of one workgroup's chain -
+// launch, operands, reduction, epilogue - so a wave has at most four steps, all requested at once, before more waves run
+// out.  Five rows of width 128: 3.5 to 4.8 us, where a kernel on vector units with a scalar load per k took 9.6.
+constexpr int GF_MAX_WAVES = 16;
 
 template <int EPI>
-__device__ __forceinline__ bool gemm_tiles(const GemmArgs& g, int item, int hd, int& t0, int& t1, int& split) {
+__global__ void __launch_bounds__(GF_MAX_WAVES * 64) k_gemm_f32(GemmArgs g) {
+  __shared__ float red[GF_MAX_WAVES][2][256];
+  __shared__ float red_ss[GF_MAX_WAVES][16];
   const int ntiles = (g.N + 15) >> 4;
-  if (EPI == EPI_PARTIAL) {
-    const int npairs = (ntiles + 1) >> 1;
-    split = item / npairs;
-    const int p = item - split * npairs;
-    t0 = 2 * p; t1 = 2 * p + 1;
+  int t0, t1;
+  if (EPI == EPI_QKV) {
+    const int per_head = g.kv.hd >> 5, head = blockIdx.x / per_head, i = blockIdx.x - head * per_head;
+    t0 = head * (g.kv.hd >> 4) + i; t1 = t0 + per_head;
   } else if (EPI == EPI_SWIGLU) {
-    split = 0; t0 = item; t1 = item;
+    t0 = t1 = blockIdx.x;
   } else {
-    const int per_head = hd >> 5;              // pairs of tiles per head
-    const int head = item / per_head, i = item - head * per_head;
-    split = 0; t0 = head * (hd >> 4) + i; t1 = t0 + per_head;
+    t0 = 2 * blockIdx.x; t1 = t0 + 1;
   }
-  return t0 < ntiles;
-}
-
-// Sum the four waves' partial tiles (fixed order) and run the epilogue: thread tid owns (row tid/16, col tid%16).
-template <int EPI, typename AT, typename KVT>
-__device__ __forceinline__ void gemm_reduce_tile(const GemmArgs& g, float (*red)[2][256], int t0, int t1, int split,
-                                                 int mt) {
-  const int tid = threadIdx.x;
-  const float v0 = (red[0][0][tid] + red[1][0][tid]) + (red[2][0][tid] + red[3][0][tid]);
-  const float v1 = (red[0][1][tid] + red[1][1][tid]) + (red[2][1][tid] + red[3][1][tid]);
-  gemm_epilogue<EPI, AT, KVT>(g, t0, t1, split, mt * 16 + (tid >> 4), tid & 15, v0, v1);
-}
-
-// -------------------------------------------------------------------------------------- fp32 / VALU
-// Same decomposition for the fp32 parity configuration; weights canonical [N][K] fp32, K % 32 == 0.
-template <int EPI, typename KVT>
-__global__ void __launch_bounds__(BLOCK) k_gemm_f32(GemmArgs g) {
-  __shared__ float red[4][2][256];
-  int t0, t1, split;
-  if (!gemm_tiles<EPI>(g, blockIdx.x, g.kv.hd, t0, t1, split)) return;
-  const int ntiles = (g.N + 15) >> 4;
-  const bool has1 = (EPI != EPI_PARTIAL) || (t1 < ntiles);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int KT = g.K >> 5;
-  const int per_s = KT / g.gs, rem_s = KT - per_s * g.gs;
-  const int wg_b = split * per_s + min(split, rem_s), wg_n = per_s + (split < rem_s ? 1 : 0);
-  const int per_w = wg_n >> 2, rem_w = wg_n & 3;
-  const int kb = wg_b + wave * per_w + min(wave, rem_w), ke = kb + per_w + (wave < rem_w ? 1 : 0);
-  const int col = lane & 15, kg = lane >> 4;
-  const int n0 = min(t0 * 16 + col, g.N - 1), n1 = min((has1 ? t1 : t0) * 16 + col, g.N - 1);
-  const float* w0 = (const float*)g.W0 + (size_t)n0 * g.K;
-  const float* w1 = (const float*)g.W1 + (size_t)n1 * g.K;
-  const float* A = (const float*)g.A;
-  const int MTn = (g.M + 15) >> 4;
-  for (int mt = 0; mt < MTn; ++mt) {
-    float a0[16], a1[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+  const int steps = g.K >> 4, per = steps / nw, rem = steps - per * nw;
+  const int kb = wave * per + min(wave, rem), ke = kb + per + (wave < rem ? 1 : 0);
+  const int li = lane & 15, kg = lane >> 4, m0 = blockIdx.y * 16;
+  const f32x4* w0 = (const f32x4*)((const float*)g.W0 + (size_t)min(t0 * 16 + li, g.N - 1) * g.K) + kg;
+  const f32x4* w1 = (const f32x4*)((const float*)g.W1 + (size_t)min(t1 * 16 + li, g.N - 1) * g.K) + kg;
+  const f32x4* ap = (const f32x4*)((const float*)g.A + (size_t)min(m0 + li, g.M - 1) * g.K) + kg;
+  const f32x4* gp = (const f32x4*)g.gain + kg;
+  constexpr int U = 4;
+  f32x4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
+  float ss = 0.f;
+  // EPI_QKV: where the row's key and value go and its rotation, requested behind the operands
+  const int row = m0 + (tid >> 4);
+  const bool mine = tid < 256 && row < g.M;
+  int pos = 0, active = 0, blk = -1;
+  float2 cs = {0.f, 0.f};
+  if (EPI == EPI_QKV && mine) { pos = g.rows.pos[row]; active = g.rows.active[row]; }
+  for (int k = kb; k < ke; k += U) {
+    f32x4 a[U], x0[U], x1[U], gn[U];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { a0[r] = 0.f; a1[r] = 0.f; }
-    const int rows = min(16, g.M - mt * 16);
-    for (int k = kb * 32 + kg; k < ke * 32; k += 4) {
-      const float x0 = w0[k], x1 = w1[k];
+    for (int u = 0; u < U; ++u) {
+      const int kk = min(k + u, ke - 1) * 4;
+      a[u] = ap[kk]; x0[u] = w0[kk]; x1[u] = w1[kk];
+      if (g.gain) gn[u] = gp[kk];
+    }
+    if (EPI == EPI_QKV && mine && k == kb) {
+      cs = g.rope[(size_t)pos * (g.kv.hd >> 1) + (t0 * 16 + (tid & 15)) % g.kv.hd];
+      blk = g.kv.table[(g.rows.seq0 + row / g.rows.R) * g.kv.mbps + pos / g.kv.bt];
+    }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        if (r < rows) {
-          const float a = A[(size_t)(mt * 16 + r) * g.lda + k];
-          a0[r] = fmaf(a, x0, a0[r]);
-          a1[r] = fmaf(a, x1, a1[r]);
-        }
+    for (int u = 0; u < U; ++u) {
+      if (k + u >= ke) break;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float x = a[u][j];
+        if (g.gain) { ss = fmaf(x, x, ss); x *= gn[u][j]; }
+        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x, x0[u][j], acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x, x1[u][j], acc1, 0, 0, 0);
       }
     }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float s0 = a0[r], s1 = a1[r];
-      s0 += __shfl_xor(s0, 16, WAVE); s0 += __shfl_xor(s0, 32, WAVE);
-      s1 += __shfl_xor(s1, 16, WAVE); s1 += __shfl_xor(s1, 32, WAVE);
-      if (kg == 0) { red[wave][0][r * 16 + col] = s0; red[wave][1][r * 16 + col] = s1; }
-    }
-    __syncthreads();
-    gemm_reduce_tile<EPI, F32, KVT>(g, red, t0, has1 ? t1 : ntiles, split, mt);
   }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    red[wave][0][(4 * kg + r) * 16 + li] = acc0[r];
+    red[wave][1][(4 * kg + r) * 16 + li] = acc1[r];
+  }
+  if (g.gain) {
+    ss += __shfl_xor(ss, 16, WAVE); ss += __shfl_xor(ss, 32, WAVE);
+    if (kg == 0) red_ss[wave][li] = ss;
+  }
+  __syncthreads();
+  if (!mine) return;
+  float v0 = 0.f, v1 = 0.f, tot = 0.f;
+  for (int w = 0; w < nw; ++w) {
+    v0 += red[w][0][tid];
+    v1 += red[w][1][tid];
+    tot += g.gain ? red_ss[w][tid >> 4] : 0.f;
+  }
+  if (g.gain) {
+    const float inv = 1.0f / sqrtf(tot / (float)g.K + g.rms_eps);
+    v0 *= inv; v1 *= inv;
+  }
+  gemm_epilogue_f32<EPI>(g, t0, t1, row, tid & 15, v0, v1, pos, active ? blk : -1, cs);
 }
 
 // Repack a canonical bf16 matrix [N][K] into MFMA B-fragment tiles (see the top of this file).

@@ -18,13 +18,12 @@ struct EmbedArgs {
   float* h;                 // [M][d]
   const float* gain;        // of the first layer's norm
   float eps;
-  void* xn;                 // the normalised rows: fp32 or split rows
+  bf16_t* xn;               // the normalised rows as split rows (null: the next kernel normalises)
 };
 
 // RMSNorm of a row whose columns 4 tid .. + 3 (+ 4 blockDim ..) a workgroup's threads hold, the first four of each thread in v0 and
 // the rest in memory (hr); ss: the thread's share of the sum of squares.
-template <bool SPLIT>
-__device__ __forceinline__ void norm_row(const float* hr, f32x4 v0, float ss, const float* gain, float eps, void* xn, int m, int d,
+__device__ __forceinline__ void norm_row(const float* hr, f32x4 v0, float ss, const float* gain, float eps, bf16_t* xn, int m, int d,
                                          float* s16) {
   ss = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) s16[threadIdx.x >> 6] = ss;
@@ -37,13 +36,9 @@ __device__ __forceinline__ void norm_row(const float* hr, f32x4 v0, float ss, co
     const f32x4 gn = *(const f32x4*)(gain + i);
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[r] = v[r] * inv * gn[r];
-    if (SPLIT) {
-      bf16_t* o = (bf16_t*)xn + split_index(m, i, d >> 5);
-      *(uint2*)o = hi_pairs(v);
-      *(uint2*)(o + 512) = lo_pairs(v);
-    } else {
-      *(f32x4*)((float*)xn + (size_t)m * d + i) = v;
-    }
+    bf16_t* o = xn + split_index(m, i, d >> 5);
+    *(uint2*)o = hi_pairs(v);
+    *(uint2*)(o + 512) = lo_pairs(v);
   }
 }
 
@@ -51,7 +46,7 @@ __device__ __forceinline__ void norm_row(const float* hr, f32x4 v0, float ss, co
 // for the first layer.  One more workgroup reserves the cache blocks the forward will write (sequences in ascending order).
 // The kernel is a chain of dependent reads (state, token, embedding, norm), so the reservation is a chain of its own beside
 // it and the norm no launch of its own: a forward is 4 us shorter, a prefill chunk of 1024 rows another 8.
-template <typename WT, bool SPLIT>
+template <typename WT>
 __global__ void __launch_bounds__(1024) k_embed(EmbedArgs e) {
   if ((int)blockIdx.x == e.rows.M) {
     __shared__ int scan[1024 + 16], slot[1024];
@@ -89,7 +84,7 @@ __global__ void __launch_bounds__(1024) k_embed(EmbedArgs e) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) ss = fmaf(v[r], v[r], ss);
   }
-  norm_row<SPLIT>(hr, v0, ss, e.gain, e.eps, e.xn, m, e.d, s16);
+  if (e.xn) norm_row(hr, v0, ss, e.gain, e.eps, e.xn, m, e.d, s16);
 }
 
 // h[m] += sum of the k-split partials of the previous GEMM (ascending split order); xn[m] = RMSNorm(h[m]) * gain, as fp32 rows
@@ -97,9 +92,8 @@ __global__ void __launch_bounds__(1024) k_embed(EmbedArgs e) {
 // row of up to 4 * blockDim columns stays in registers between the two passes.  The partials of a thread are requested
 // eight at a time: their loads, not their sum, are what the kernel waits for (one at a time, 8 partials of 1024 rows of
 // 896 took 9.0 us).
-template <bool SPLIT>
 __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, int n_part, size_t part_stride, const float* gain,
-                                                   float eps, void* xn, int d) {
+                                                   float eps, bf16_t* xn, int d) {
   __shared__ float s16[16];
   const int m = blockIdx.x;
   float* hr = h + (size_t)m * d;
@@ -121,7 +115,7 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
 #pragma unroll
     for (int r = 0; r < 4; ++r) ss = fmaf(v[r], v[r], ss);
   }
-  norm_row<SPLIT>(hr, v0, ss, gain, eps, xn, m, d, s16);
+  norm_row(hr, v0, ss, gain, eps, xn, m, d, s16);
 }
 
 // ------------------------------------------------------------------------------------------ warp + softmax

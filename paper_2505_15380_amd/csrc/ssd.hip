@@ -560,16 +560,10 @@ static int kv_check_room(ssd_kv* kv, int seq0, int B, int R, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------------------------------------ forward
-static int pick_splits(int K, int npairs) {                // k-splits of the fp32 GEMM
-  const int KT = K / 32;
-  int gs = std::max(1, 256 / std::max(1, npairs));
-  gs = std::min(gs, std::max(1, KT / 8));
-  return std::min(gs, MAX_SPLITS);
-}
-
 template <int EPI>
 static int launch_gemm_f32(const GemmArgs& g, int items, hipStream_t st) {
-  hipLaunchKernelGGL((k_gemm_f32<EPI, F32>), dim3(items), dim3(BLOCK), 0, st, g);
+  const int waves = std::min(GF_MAX_WAVES, std::max(4, cdiv(g.K / 16, 4)));      // the epilogue has 256 threads
+  hipLaunchKernelGGL((k_gemm_f32<EPI>), dim3(items, cdiv(g.M, 16)), dim3(waves * WAVE), 0, st, g);
   LAUNCH_CHECK();
   return SSD_OK;
 }
@@ -702,6 +696,16 @@ template <typename DT, int HD>
 static int launch_attn(AttnArgs a, int nchunks, int nkv, int B, int M, bool mfma, int cus, hipStream_t st) {
   if constexpr (std::is_same<DT, BF16>::value && (HD == 64 || HD == 128)) {
     if (mfma && a.kv.bt == 16) return launch_attn_mfma<HD>(a, nchunks, nkv, B, M, cus, st);
+  }
+  if constexpr (std::is_same<DT, F32>::value) {
+    // a tile of keys is a block; a few long sequences give it too few workgroups for its walk
+    const int tiles = cdiv(a.rows.R * (a.nq / nkv), 16);
+    if (a.kv.bt == 16 && (nchunks <= 16 || tiles * nkv * B >= cus / 2)) {
+      a.nparts = nchunks;
+      hipLaunchKernelGGL((k_attn_f32<HD>), dim3(tiles, nkv, B), dim3(att_f32_waves<HD>() * WAVE), 0, st, a);
+      LAUNCH_CHECK();
+      return SSD_OK;
+    }
   }
   hipLaunchKernelGGL((k_attn_chunk<HD, DT>), dim3(nchunks, nkv, B), dim3(BLOCK), 0, st, a);
   LAUNCH_CHECK();
@@ -841,8 +845,8 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
   constexpr bool bf16 = std::is_same<DT, BF16>::value;     // bf16: GEMM operands are kept as split rows (common.h)
   const dim3 row_block(std::min(1024, cdiv(d / 4, WAVE) * WAVE));          // a thread per four columns of a row
   e.embed = m->embed; e.n_embed = c.n_embed; e.d = d; e.h = kv->h;
-  e.gain = m->layers[0].ln1; e.eps = c.rms_eps; e.xn = kv->xn;
-  hipLaunchKernelGGL((k_embed<DT, bf16>), dim3(M + 1), row_block, 0, st, e);
+  e.gain = m->layers[0].ln1; e.eps = c.rms_eps; e.xn = bf16 ? (bf16_t*)kv->xn : nullptr;
+  hipLaunchKernelGGL((k_embed<DT>), dim3(M + 1), row_block, 0, st, e);
   LAUNCH_CHECK();
 
   int max_len = 0;
@@ -851,15 +855,17 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
 
   GemmArgs g0;
   memset(&g0, 0, sizeof g0);
-  g0.M = M; g0.kv = kv->v; g0.rows = rows; g0.nq = nq; g0.rope = m->rope;
+  g0.M = M; g0.kv = kv->v; g0.rows = rows; g0.nq = nq; g0.rope = m->rope; g0.rms_eps = c.rms_eps;
+  const void* const normed = bf16 ? (const void*)kv->xn : kv->h;           // fp32: the GEMM normalises its operand itself
   const size_t part_stride = (size_t)M * d;
-  const int npairs_d = cdiv(cdiv(d, 16), 2);
+  const int pairs_d = cdiv(d, 32);
   // Up to 512 rows the output projection is not k-split: its epilogue adds the residual and prepares the norm before gate /
   // up, and no add + norm kernel runs between them.  With more rows the unsplit projection leaves too few workgroups
   // (1024 rows of the 1.5B shape: 24.8 us against 15 for two slices and 9 for the add + norm kernel).
-  const bool fused_norm = bf16 && M <= 512;
+  const bool fused_norm = !bf16 || M <= 512;
   auto add_norm = [&](int n_part_, const float* gain) -> int {
-    hipLaunchKernelGGL((k_add_norm<bf16>), dim3(M), row_block, 0, st, kv->h, kv->part, n_part_, part_stride, gain, c.rms_eps, kv->xn, d);
+    if (!bf16) return SSD_OK;
+    hipLaunchKernelGGL(k_add_norm, dim3(M), row_block, 0, st, kv->h, kv->part, n_part_, part_stride, gain, c.rms_eps, (bf16_t*)kv->xn, d);
     LAUNCH_CHECK();
     return SSD_OK;
   };
@@ -869,12 +875,12 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     const LayerW& L = m->layers[l];
     if (l > 0 && (rc = add_norm(n_part, L.ln1))) return rc;      // (the first layer's: in k_embed)
     GemmArgs g = g0;                                       // QKV + bias + rotary + cache write
-    g.A = kv->xn; g.lda = d; g.W0 = L.wqkv; g.W1 = L.wqkv; g.N = nqkv; g.K = d; g.gs = 1;
+    g.A = normed; g.W0 = L.wqkv; g.W1 = L.wqkv; g.N = nqkv; g.K = d;
     g.bias = L.bqkv; g.q = kv->q; g.layer = l;
     {
       ProfScope ps(PROF_QKV, st);
       if constexpr (bf16) rc = std::min(0, launch_gemm<EPI_QKV>(g, kv->cus, 1, st));
-      else rc = launch_gemm_f32<EPI_QKV>(g, (nq + 2 * nkv) * (hd / 32), st);
+      else { g.gain = L.ln1; rc = launch_gemm_f32<EPI_QKV>(g, (nq + 2 * nkv) * (hd / 32), st); }
     }
     if (rc) return rc;
 
@@ -890,54 +896,54 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     }
     if (rc) return rc;
 
-    g = g0;                                                // output projection -> k-split partials
-    g.A = kv->attn; g.lda = nqd; g.W0 = L.wo; g.W1 = L.wo; g.N = d; g.K = nqd;
+    g = g0;                                                // output projection
+    g.A = kv->attn; g.W0 = L.wo; g.W1 = L.wo; g.N = d; g.K = nqd;
     g.out = kv->part; g.out_split_stride = part_stride; g.ldo = d;
     {
       ProfScope ps(PROF_O, st);
-      if (fused_norm) {
-        g.h = kv->h; g.gain = L.ln2; g.hg = kv->xn; g.sumsq = kv->part;
+      g.h = kv->h;
+      if constexpr (!bf16) {
+        rc = launch_gemm_f32<EPI_RESID>(g, pairs_d, st);
+      } else if (fused_norm) {
+        g.gain = L.ln2; g.hg = kv->xn; g.sumsq = kv->part;
         rc = std::min(0, launch_gemm<EPI_RESID>(g, kv->cus, 1, st));
-      } else if constexpr (bf16) {
+      } else {
         n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, MAX_SPLITS, st);
         rc = std::min(0, n_part);
-      } else {
-        g.gs = n_part = pick_splits(nqd, npairs_d);
-        rc = launch_gemm_f32<EPI_PARTIAL>(g, npairs_d * n_part, st);
       }
     }
     if (rc) return rc;
     if (!fused_norm && (rc = add_norm(n_part, L.ln2))) return rc;
 
     g = g0;                                                // gate / up + SwiGLU
-    g.A = kv->xn; g.lda = d; g.W0 = L.wgate; g.W1 = L.wup; g.N = c.d_ffn; g.K = d; g.gs = 1; g.act = kv->act;
+    g.A = normed; g.W0 = L.wgate; g.W1 = L.wup; g.N = c.d_ffn; g.K = d; g.act = kv->act;
     g.act_split_kt = bf16 ? c.d_ffn / 32 : 0;
-    g.sumsq = kv->part; g.rms_d = fused_norm ? d : 0; g.rms_eps = c.rms_eps;
+    g.sumsq = kv->part; g.rms_d = fused_norm ? d : 0;
     {
       ProfScope ps(PROF_GATEUP, st);
       if constexpr (bf16) rc = std::min(0, launch_gemm<EPI_SWIGLU>(g, kv->cus, 1, st));
-      else rc = launch_gemm_f32<EPI_SWIGLU>(g, cdiv(c.d_ffn, 16), st);
+      else { g.gain = L.ln2; rc = launch_gemm_f32<EPI_SWIGLU>(g, cdiv(c.d_ffn, 16), st); }
     }
     if (rc) return rc;
 
-    g = g0;                                                // down projection -> k-split partials
-    g.A = kv->act; g.lda = c.d_ffn; g.W0 = L.wdown; g.W1 = L.wdown; g.N = d; g.K = c.d_ffn;
+    g = g0;                                                // down projection
+    g.A = kv->act; g.W0 = L.wdown; g.W1 = L.wdown; g.N = d; g.K = c.d_ffn;
     g.out = kv->part; g.out_split_stride = part_stride; g.ldo = d;
     {
       ProfScope ps(PROF_DOWN, st);
       if constexpr (bf16) { n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, MAX_SPLITS, st); rc = std::min(0, n_part); }
-      else { g.gs = n_part = pick_splits(c.d_ffn, npairs_d); rc = launch_gemm_f32<EPI_PARTIAL>(g, npairs_d * n_part, st); }
+      else { g.h = kv->h; rc = launch_gemm_f32<EPI_RESID>(g, pairs_d, st); }
     }
     if (rc) return rc;
   }
   if (!with_head) return SSD_OK;
   if ((rc = add_norm(n_part, m->final_norm))) return rc;
   GemmArgs g = g0;
-  g.A = kv->xn; g.lda = d; g.W0 = m->head; g.W1 = m->head; g.N = c.vocab; g.K = d; g.gs = 1;
+  g.A = normed; g.W0 = m->head; g.W1 = m->head; g.N = c.vocab; g.K = d;
   g.out = kv->logits; g.out_split_stride = 0; g.ldo = c.vocab;
   ProfScope ps(PROF_HEAD, st);
   if constexpr (bf16) return std::min(0, launch_gemm<EPI_PARTIAL>(g, kv->cus, 1, st));
-  else return launch_gemm_f32<EPI_PARTIAL>(g, cdiv(cdiv(c.vocab, 16), 2), st);
+  else { g.gain = m->final_norm; return launch_gemm_f32<EPI_PARTIAL>(g, cdiv(c.vocab, 32), st); }
 }
 
 static int forward_any(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int pcap, const int32_t* dev_tokens,

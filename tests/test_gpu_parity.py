@@ -139,6 +139,39 @@ def test_tiny_topk_temperature_and_greedy():
     run_verify_parity("tiny", steps=4, K=3, beta=0.0, atol_logits=1e-5, atol_probs=1e-5, greedy=True)
 
 
+# ---- operator-by-operator forward: edges of row tiles, column tiles, k-tiles, chunks and parts ----------------------
+@pytest.mark.parametrize("dtype,hd,groups,n_prefix,B,K", [
+    ("fp32", 32, 1, 2, 1, 0),        # one row, two keys
+    ("fp32", 32, 3, 64, 2, 4),       # 15 query rows per key head, a chunk that is just full
+    ("fp32", 64, 2, 509, 1, 8),      # 18 query rows: two tiles; new positions in a ninth chunk (second round of a wave)
+    ("fp32", 128, 1, 130, 3, 6),     # head size with half the waves; 21 rows: two row tiles
+    ("fp32", 32, 2, 1030, 1, 2),     # more chunks than the one-launch attention takes
+    ("bf16", 128, 3, 2, 1, 0),       # one row
+    ("bf16", 64, 7, 60, 17, 0),      # 17 rows: one more than a tile
+    ("bf16", 64, 2, 129, 4, 15),     # 64 rows; a prompt of 128 cached positions in one chunk of rows
+    ("bf16", 128, 2, 66, 5, 12),     # 65 rows
+    ("bf16", 64, 1, 514, 1, 15),     # prompt in 513 rows: one more than take the norm in the projection's epilogue
+    ("bf16", 128, 3, 1025, 1, 4)])   # prompt in 1024 rows, 17 chunks of keys
+def test_forward_at_the_edges_of_tiles(dtype, hd, groups, n_prefix, B, K):
+    """Widths of 9, 25 and odd numbers of tiles, a ragged vocabulary: cache contents after the prompt (one forward of
+    n_prefix - 1 rows) and two verifications of B x (K + 1) rows against the oracle."""
+    from tests.parity import Pair, verify_parity_step
+    shape = dict(n_layers=2, d_model=288, n_q_heads=2 * groups, n_kv_heads=2, head_dim=hd, d_ffn=800, vocab=333,
+                 n_embed=340, dtype=dtype, qkv_bias=1, rope_base=1.0e5, rms_eps=1e-6)
+    atol = 2e-5 if dtype == "fp32" else 2e-2
+    rows = min(max(n_prefix - 1, K + 1), 1024 // B)
+    pair = Pair(None, 77, n_prefix + 2 * (K + 1) + 16, max_seqs=B, max_rows=rows, shape=shape)
+    rng = np.random.default_rng(78)
+    for b in range(B):
+        pair.prefill(b, rng.integers(0, 340, max(2, n_prefix - 5 * b)))
+        pair.check_state(b, atol)
+    for s in range(2):
+        verify_parity_step(pair, dict(beta=0.3, seed=79), K, s, rng, atol, atol, seqs=range(B))
+    for b in range(B):
+        pair.check_state(b, atol)
+    pair.check_free_stack()
+
+
 # ---- the barrier-free persistent forward (bf16 shapes, <= 16 rows) ------------------------------------------------
 @pytest.mark.gpu
 @pytest.mark.parametrize("n_prefix,K", [(250, 4), (254, 12), (600, 4), (1290, 7)])
