@@ -245,9 +245,9 @@ int ssd_profile_end(double* total_ms, int* launches);
  * 2 one persistent kernel with grid barriers between phases, 3 one persistent kernel whose phases are ordered by
  * tagged data words (the default for bf16 storage and at most 16 rows; the environment variable
  * SSD_FORWARD=barrier, read at ssd_kv_create, selects 2 instead; 2 is also what runs when a launch exceeds the
- * limits of 3), 4 the same kernel with the attention of a short prefix
- * (at most 1520 cached positions) done by one workgroup per row tile instead of 256-key parts (the default for caches
- * created with pending_cap 2; SSD_ATTN_WHOLE=1 selects it for every cache, 0 for none). */
+ * limits of 3), 4 the same kernel where no part of a prefix can meet another one's: at most 1520 cached positions on a cache
+ * created with pending_cap 2 (SSD_ATTN_WHOLE=1: on every cache, 0: on none; the attention of such prefixes is one
+ * workgroup per row tile in 3 as well, longer ones go in parts of 1024 keys). */
 int ssd_kv_last_forward_path(const ssd_kv* kv);
 
 /* Phase trace of the persistent forward kernels, recorded only by builds with -DSSD_TRACE (otherwise SSD_ENOSUP

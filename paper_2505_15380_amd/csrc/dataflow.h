@@ -1,6 +1,6 @@
 // The decoder forward of one verification (Eq. 4) as one persistent kernel WITHOUT grid barriers between phases.
 //
-// Phases per layer: QKV (+bias, rotary, cache append) -> attention (parts of 256 keys, then the merge of the parts)
+// Phases per layer: QKV (+bias, rotary, cache append) -> attention (in parts, then their merge, for long prefixes)
 // -> output projection (+residual) -> MLP (gate/up + SwiGLU + down projection fused inside a workgroup) -> sum of the
 // MLP partials (+residual).  Weights are packed as matrix-core fragments; a unit of 4 waves takes an item.
 //
@@ -52,9 +52,11 @@ constexpr long DF_SPIN_LIMIT = 1L << 18;
 // LDS words: staging | sums of squares | unit reduction buffers, overlaid by the attention buffers of the two units
 constexpr int DF_SQ_WORDS = 1024;
 constexpr int DF_RED_WORDS = 2 * 2048;
-constexpr int DF_ATT_UNIT = 4096 + 512 + 512 + 4096 + 4096 + 128;      // Q | new K | new V | P | merge O | merge m,l
-constexpr int DF_LDS_WORDS = (DF_AW + DF_SQ_WORDS + DF_RED_WORDS) > 2 * DF_ATT_UNIT ? (DF_AW + DF_SQ_WORDS + DF_RED_WORDS)
-                                                                                  : 2 * DF_ATT_UNIT;
+constexpr int DF_QS = 68;                 // words from one row to the next of the queries and of the merge buffers in LDS: rows 64
+                                          // words apart would put a fragment's 16 rows into the same banks
+constexpr int DF_ATT_WORDS = 16 * DF_QS + 512 + 512 + 8 * 16 * DF_QS + 256;      // Q | new K | new V | merge O | merge m,l
+constexpr int DF_LDS_WORDS = DF_AW + DF_SQ_WORDS + DF_RED_WORDS;
+static_assert(DF_ATT_WORDS <= DF_LDS_WORDS, "");
 
 // Which single word a wave watches after a failed first flight (see df_wait_hint): the phases with many consumers (QKV,
 // MLP) watch a word of their OWN operands, the others a word of the preceding phase's operands.
@@ -87,7 +89,7 @@ struct DArgs {
   u64* rowblk;            // [16] per row: the pool block that takes the row's new key and value (-1: none), from the reservation
   float* logits;
   size_t st_h, st_sq, st_q, st_kvn, st_att_p;   // strides in words
-  int NP, n_parts;
+  int NP, n_parts, part_chunks;
   int g_mlp;              // workgroups [0, g_mlp) take the MLP items; the phases with few items start on the workgroups after them
   int small_stride;       // 2: a small-phase item has a workgroup to itself; 1: two items per workgroup
   uint32_t* bar;          // [64] error flag (sticky until the host reads it); [0], [32] belong to the kernel with grid barriers
@@ -99,6 +101,12 @@ __device__ __forceinline__ void st_word(u64* p, uint32_t payload, uint32_t tag) 
   __hip_atomic_store(p, (u64)payload | ((u64)tag << 32), __ATOMIC_RELAXED, AG);
 }
 __device__ __forceinline__ void st_wordf(u64* p, float x, uint32_t tag) { st_word(p, __float_as_uint(x), tag); }
+// Four consecutive words (16-byte aligned) with two stores of two words each: a word is still stored by one instruction, and each
+// of them has its tag.
+__device__ __forceinline__ void st_words4(u64* p, uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, uint32_t tag) {
+  const u32x4 a = {x0, tag, x1, tag}, b = {x2, tag, x3, tag};
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\tglobal_store_dwordx4 %0, %2, off offset:16 sc1\n\ts_nop 0" ::"v"(p), "v"(a), "v"(b) : "memory");
+}
 __device__ __forceinline__ uint32_t split_payload(float x) {
   const uint32_t u = __float_as_uint(x), h = u & 0xFFFF0000u;
   return (h >> 16) | ((uint32_t)f_to_bf16(x - __uint_as_float(h)) << 16);
@@ -271,8 +279,10 @@ __device__ __forceinline__ void frag_from_lds(const uint32_t* p, u32x4& hi, u32x
 // Clock samples per workgroup and phase, only in builds with -DSSD_TRACE (see ssd_trace_barriers).
 #ifdef SSD_TRACE
 #define DF_STAMP(slot) do { if (a.trace && threadIdx.x == 0) a.trace[(size_t)blockIdx.x * 512 + (slot)] = wall_clock64(); } while (0)
+#define DF_STAMP2(k) do { if (a.trace && threadIdx.x == 0) a.trace[(size_t)blockIdx.x * 512 + 256 + (slot - 2) / 10 * 10 + (k)] = wall_clock64(); } while (0)
 #else
 #define DF_STAMP(slot) do { } while (0)
+#define DF_STAMP2(k) do { } while (0)
 #endif
 
 // Item of round 0 that `unit` takes when items start at unit `shift` and take every `stride`-th unit (stride 2: one
@@ -324,6 +334,16 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
         wl.b1[u] = __builtin_nontemporal_load(w1 + (size_t)kt * 64);
       }
     }
+    // ---- epilogue operands that do not depend on the product: requested with the weights
+    float bias0 = 0.f, bias1 = 0.f, gn0 = 0.f, gn1 = 0.f;
+    float2 cs = float2{1.f, 0.f};
+    int pos = 0, active = 0, rblk = -1;
+    if (EPI == PE_QKV && live) {
+      if (ph.bias) { bias0 = ph.bias[n0]; bias1 = ph.bias[n0 + 32]; }
+      pos = srow[row]; active = srow[16 + row]; rblk = srow[32 + row];
+      cs = a.rope[(size_t)pos * 32 + (n0 & 63)];
+    }
+    if (EPI == PE_RESID && live) { gn0 = ph.gain_next[n0]; gn1 = ph.gain_next[n1]; }
     // ---- operands (both units of the workgroup consume the same rows); the unit that finishes residual rows takes
     //      its residual inputs in the same flight
     uint32_t hx0 = 0xFFFFFFFFu, hx1 = 0xFFFFFFFFu, hv0 = 0u, hv1 = 0u;
@@ -337,16 +357,6 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
     if (!ok) *sdead = 1;
     __syncthreads();
     if (*sdead) return true;
-    // ---- epilogue operands that do not depend on the product
-    float bias0 = 0.f, bias1 = 0.f, gn0 = 0.f, gn1 = 0.f;
-    float2 cs = float2{1.f, 0.f};
-    int pos = 0, active = 0, rblk = -1;
-    if (EPI == PE_QKV && live) {
-      if (ph.bias) { bias0 = ph.bias[n0]; bias1 = ph.bias[n0 + 32]; }
-      pos = srow[row]; active = srow[16 + row]; rblk = srow[32 + row];
-      cs = a.rope[(size_t)pos * 32 + (n0 & 63)];
-    }
-    if (EPI == PE_RESID && live) { gn0 = ph.gain_next[n0]; gn1 = ph.gain_next[n1]; }
     if (rd == 0) DF_STAMP(slot);
     // ---- products
     f32x4 acc0 = f32x4{0, 0, 0, 0}, acc1 = f32x4{0, 0, 0, 0};
@@ -535,6 +545,7 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
                   acc0, acc1);
       }
     }
+    DF_STAMP2(0);
     const int obase = (g * 4) * 16 + (lane & 15);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -545,6 +556,7 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
     if (row < M)
       for (int p = col; p < KT; p += 16) sq += sqs[row * KT + p];
     __syncthreads();
+    DF_STAMP2(1);
     float v0 = (red[0][0][ut] + red[1][0][ut]) + (red[2][0][ut] + red[3][0][ut]);
     float v1 = (red[0][1][ut] + red[1][1][ut]) + (red[2][1][ut] + red[3][1][ut]);
     sq = row16_sum(sq);
@@ -554,34 +566,28 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
     const float actv = (live && n0 < ph.N) ? v0 / (1.0f + expf(-v0)) * v1 : 0.f;
     sact[row * 36 + usel * 16 + col] = split_payload(actv);          // [16 rows][32 columns of the workgroup's k-tile]
     __syncthreads();
+    DF_STAMP2(2);
     // ---- down projection of the workgroup's 32 columns: wave takes output tiles wave, wave + 8, ...
     if ((rd * NU + blockIdx.x * 2) < ph.items) {
       u32x4 xh = u32x4{0u, 0u, 0u, 0u}, xl = xh;
       if (arow < M) frag_from_lds(sact + arow * 36 + g * 8, xh, xl);
       const bf16x8 ah = __builtin_bit_cast(bf16x8, xh), al = __builtin_bit_cast(bf16x8, xl);
       u64* po = part2 + ((size_t)kt2 * PR) * a.d;
-#pragma unroll
-      for (int i = 0; i < DF_DN; ++i) {
-        const int nt = wave + 8 * i;
-        if (nt < ntiles_d) {
-          const bf16x8 bv = __builtin_bit_cast(bf16x8, wd.b[i]);
-          f32x4 acc = f32x4{0, 0, 0, 0};
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bv, acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bv, acc, 0, 0, 0);
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (4 * g + r < M) st_wordf(po + (size_t)(4 * g + r) * a.d + nt * 16 + c16, acc[r], tag2);
-        }
-      }
-      for (int nt = wave + 8 * DF_DN; nt < ntiles_d; nt += 8) {      // wider models: the remaining tiles, not prefetched
-        const bf16x8 bv = __builtin_bit_cast(bf16x8, __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + lane));
+      // computed transposed: a lane holds four consecutive columns of row c16, which two stores publish
+      auto tile = [&](int nt, const u32x4 w) {
+        const bf16x8 bv = __builtin_bit_cast(bf16x8, w);
         f32x4 acc = f32x4{0, 0, 0, 0};
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bv, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bv, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, al, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, ah, acc, 0, 0, 0);
+        if (c16 < M)
+          st_words4(po + (size_t)c16 * a.d + nt * 16 + 4 * g, __float_as_uint(acc[0]), __float_as_uint(acc[1]), __float_as_uint(acc[2]),
+                    __float_as_uint(acc[3]), tag2);
+      };
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (4 * g + r < M) st_wordf(po + (size_t)(4 * g + r) * a.d + nt * 16 + c16, acc[r], tag2);
-      }
+      for (int i = 0; i < DF_DN; ++i)
+        if (wave + 8 * i < ntiles_d) tile(wave + 8 * i, wd.b[i]);
+      for (int nt = wave + 8 * DF_DN; nt < ntiles_d; nt += 8)        // wider models: the remaining tiles, not prefetched
+        tile(nt, __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + lane));
     }
     if (rd == 0) DF_STAMP(slot + 1);
     __syncthreads();
@@ -619,6 +625,7 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t t
     float sum = 0.f;
     u64 hw = (u64)tag << 32;
     const bool want_h = valid && grp == 0;
+    const float gain = want_h ? gain_next[32 * p + c] : 0.f;
     for (int b0 = 0; b0 < cnt || (b0 == 0 && want_h); b0 += DF_RW) {
       u64 v[DF_RW];
 #pragma unroll
@@ -659,7 +666,7 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t t
       v += __uint_as_float((uint32_t)hw);
       const size_t o = (size_t)m * d + 32 * p + c;
       st_wordf(h_out + o, v, tag);
-      st_word(hg_out + o, split_payload(v * gain_next[32 * p + c]), tag);
+      st_word(hg_out + o, split_payload(v * gain), tag);
       float q2 = v * v;
 #pragma unroll
       for (int off = 16; off > 0; off >>= 1) q2 += __shfl_xor(q2, off, 32);
@@ -772,13 +779,16 @@ __device__ __forceinline__ void df_reserve_blocks(const DArgs& a, const int tag_
 }
 
 // ------------------------------------------------------------------------------------------------ attention
-// Item = (sequence, kv head, part of 256 keys, tile of 16 query rows); the query rows of a sequence are its R rows
-// times the G query heads of the group, row index qr = j * G + head-in-group.  Wave w of the unit takes keys
-// [256 part + 64 w, +64).  Scores are kept in the base-2 domain (scale * log2 e folded in), so that the
-// exponentials are single instructions.
+// Item = (sequence, kv head, part of the keys, tile of 16 query rows) on a workgroup; the query rows of a sequence are its R
+// rows times the G query heads of the group, row index qr = j * G + head-in-group.  A part is `part_chunks` (at most
+// DF_PART_CHUNKS) chunks of 64 keys, cut at absolute positions; wave w walks its chunks w, w + 8, w + 16 with a running (max,
+// sum, weighted values) per row and the eight waves meet once in LDS.  Up to DF_PART_CHUNKS chunks are one part, whose result
+// goes out as operand words; the partials of several are merged by their workgroups (see the end of df_attn_phase).  Scores
+// are kept in the base-2 domain (scale * log2 e folded in), so that the exponentials are single instructions.
+constexpr int DF_PART_CHUNKS = 24;
 struct DAttItem {
-  int valid, b, kvh, part, rt, seq, len, nact, off, pos_last, nparts_b;
-  int koff[4], voff[2];
+  int valid, b, kvh, part, rt, len, nact, off, pos_last;
+  int c0, nch, nparts_b;                                 // first chunk and chunks of the part, parts of the sequence
 };
 
 // Everything here is requested at once (one memory round trip, not six): the cached length and the pending count do
@@ -786,7 +796,7 @@ struct DAttItem {
 // whose positions are at or beyond the cached length may be reserved concurrently by this launch: whatever id is read
 // for it is only checked to be inside the pool, since each of its positions is either a row of this launch (taken from
 // the tagged side buffer, never from the pool) or masked.
-__device__ __forceinline__ DAttItem df_att_item(const DArgs& a, int item, int ntile, int uw, int lane) {
+__device__ __forceinline__ DAttItem df_att_item(const DArgs& a, int item, int ntile, int* sblk) {
   DAttItem it;
   it.valid = item < a.n_seqs * a.nkv * a.n_parts * ntile;
   it.b = 0; it.kvh = 0; it.part = 0; it.rt = 0;
@@ -798,265 +808,306 @@ __device__ __forceinline__ DAttItem df_att_item(const DArgs& a, int item, int nt
     it.kvh = t % a.nkv;
     it.part = t / a.nkv;
   }
-  it.seq = a.rows.seq0 + it.b;
-  const int kbase = it.part * ATT_PART + uw * 64;
-  // (only by the waves that have an item: a few hundred workgroups asking for the same words queue up at one channel)
-  int len_v = 0, npend_v = 0;
-  int braw[4] = {-1, -1, -1, -1};
-  if (it.valid) {
-    len_v = ld_state(a.kv.len + it.seq);
-    npend_v = a.pcap ? ld_state(a.kv.n_pend + it.seq) : 0;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int bi = (kbase >> 4) + t;
-      if (bi < a.kv.mbps) braw[t] = ld_state(a.kv.table + it.seq * a.kv.mbps + bi);
-    }
-  }
+  const int seq = a.rows.seq0 + it.b;
+  it.c0 = it.part * a.part_chunks;
+  // (only by the workgroups that have an item: a few hundred asking for the same words queue up at one channel)
+  const int len_v = it.valid ? ld_state(a.kv.len + seq) : 0;
+  const int npend_v = (it.valid && a.pcap) ? ld_state(a.kv.n_pend + seq) : 0;
+  const int i = threadIdx.x, bi = it.c0 * 4 + i;
+  int bid = -1;
+  if (i < DF_PART_CHUNKS * 4 && it.valid && bi < a.kv.mbps) bid = ld_state(a.kv.table + seq * a.kv.mbps + bi);
   it.len = __builtin_amdgcn_readfirstlane(len_v);
   const int npend = __builtin_amdgcn_readfirstlane(npend_v);
   it.off = a.pcap - npend;
   it.nact = a.rows.R - it.off;
   it.pos_last = it.len + it.nact - 1;
-  it.valid = it.valid && it.part * ATT_PART <= it.pos_last;
-  it.nparts_b = it.pos_last / ATT_PART + 1;
-  const int g = lane >> 4, c16 = lane & 15;
-  // The four block ids go through a shared array indexed by the thread id.  As a private array the compiler moves them
-  // to LDS on its own and indexes by a flat thread id that it derives from the dispatch packet: a read of host memory
-  // by every workgroup, 4-15 us at each launch.  (Measured: forms that keep the ids in registers run the layer loop
-  // 4 % slower at identical instruction counts; this form is the one that is fast in both parts.)
-  __shared__ int blk_all[PBLOCK * 4];
-  int* blk = blk_all + threadIdx.x * 4;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int bi = (kbase >> 4) + t;
-    const int b = (it.valid && bi * 16 <= it.pos_last) ? __builtin_amdgcn_readfirstlane(braw[t]) : -1;
-    blk[t] = (b < 0 || b >= a.kv.n_blocks) ? 0 : b;            // masked keys may read any block
-    it.koff[t] = ((blk[t] * a.nkv + it.kvh) * 16 + c16) * 64 + g * 8;
-  }
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const int vblk = (g >> 1) ? blk[2 * ks + 1] : blk[2 * ks];
-    it.voff[ks] = (vblk * a.nkv + it.kvh) * 1024 + c16 * 16 + (g & 1) * 8;
-  }
+  const int nch = it.pos_last / 64 + 1;
+  it.nch = min(a.part_chunks, nch - it.c0);
+  it.nparts_b = (nch + a.part_chunks - 1) / a.part_chunks;
+  it.valid = it.valid && it.nch > 0;
+  // block ids of the part's positions (masked positions may read any block)
+  if (i < DF_PART_CHUNKS * 4) sblk[i] = (bid < 0 || bid >= a.kv.n_blocks || bi * 16 > it.pos_last) ? 0 : bid;
   return it;
 }
 
-// The 16 fragment loads of a wave's chunk from the pool.  Positions at or beyond the sequence's cached length hold
-// whatever an earlier launch left there; they are patched or masked later, never used.
-__device__ __forceinline__ void df_load_kv(const DArgs& a, int layer, const DAttItem& it, KVPre& kv) {
-  const size_t plane = (size_t)a.kv.n_blocks * a.kv.nkv * 1024;
-  const bf16_t* kp = (const bf16_t*)a.kv.pool + (size_t)(2 * layer) * plane;
-  const bf16_t* vp = kp + plane;
+// A wave's chunk of 64 keys is computed transposed: the keys are the rows of the score tiles and the query rows their
+// columns, so a lane holds, of ONE query row (lane % 16), the scores of keys 4 g .. 4 g + 3 of each of the chunk's four blocks
+// (g = lane / 16).  The row's maximum and sum are in-lane operations and two exchanges between the lane groups, and the
+// weights are where the product with the values wants them: its contraction takes the lane's eight keys of two blocks as
+// its eight k, so the values come as 8 bytes (four tokens of a dim) from each of the two.  Nothing goes through LDS.
+// (With query rows as rows of the tiles a lane had four rows' statistics, each a chain of 16-lane reductions, and the weights
+// took a way through LDS: the attention of one row and 1024 keys took 5.5 us of a layer, 3.7 now.)
+struct DfK { u32x4 f[4][2]; };                           // [block][dims 0-31 / 32-63]
+struct DfV { u32x4 f[2][4]; };                           // [pair of blocks][16 dims]
+
+// Positions at or beyond the sequence's cached length hold whatever an earlier launch left there; they are patched or
+// masked later, never used.
+__device__ __forceinline__ void df_load_k(const DArgs& a, int layer, const int (&boff)[4], int lane, DfK& k) {
+  const bf16_t* kp = (const bf16_t*)a.kv.pool + (size_t)(2 * layer) * ((size_t)a.kv.n_blocks * a.kv.nkv * 1024);
+  const int g = lane >> 4, c16 = lane & 15;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    kv.kf[t][0] = *(const u32x4*)(kp + it.koff[t]);
-    kv.kf[t][1] = *(const u32x4*)(kp + it.koff[t] + 32);
+    k.f[t][0] = *(const u32x4*)(kp + boff[t] + c16 * 64 + g * 8);
+    k.f[t][1] = *(const u32x4*)(kp + boff[t] + c16 * 64 + g * 8 + 32);
   }
+}
+__device__ __forceinline__ void df_load_v(const DArgs& a, int layer, const int (&boff)[4], int lane, DfV& v) {
+  const bf16_t* vp = (const bf16_t*)a.kv.pool + (size_t)(2 * layer + 1) * ((size_t)a.kv.n_blocks * a.kv.nkv * 1024);
+  const int g = lane >> 4, c16 = lane & 15;
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) kv.vf[ks][dt] = *(const u32x4*)(vp + it.voff[ks] + dt * 256);
+    for (int dt = 0; dt < 4; ++dt) {
+      const uint2 x = *(const uint2*)(vp + boff[2 * ks] + dt * 256 + c16 * 16 + g * 4);
+      const uint2 y = *(const uint2*)(vp + boff[2 * ks + 1] + dt * 256 + c16 * 16 + g * 4);
+      v.f[ks][dt] = u32x4{x.x, x.y, y.x, y.y};
+    }
+}
+
+// Positions written by this launch: their keys and values come from the side buffer, at the pool's fragment slots.
+__device__ __forceinline__ void df_patch_k(DfK& k, int kbase, int len, int nact, const bf16_t* Kn, int lane) {
+  const int g = lane >> 4, c16 = lane & 15;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int jn = kbase + 16 * t + c16 - len;
+    if ((unsigned)jn < (unsigned)nact) {
+      k.f[t][0] = *(const u32x4*)(Kn + jn * 64 + g * 8);
+      k.f[t][1] = *(const u32x4*)(Kn + jn * 64 + 32 + g * 8);
+    }
+  }
+}
+__device__ __forceinline__ void df_patch_v(DfV& v, int kbase, int len, int nact, const bf16_t* Vn, int lane) {
+  const int g = lane >> 4, c16 = lane & 15;
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) {
+      const int dim = 16 * dt + c16;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        uint32_t x = v.f[ks][dt][w];
+        const int j0 = kbase + 32 * ks + 16 * (w >> 1) + 4 * g + 2 * (w & 1) - len, j1 = j0 + 1;
+        if ((unsigned)j0 < (unsigned)nact) x = (x & 0xFFFF0000u) | (uint32_t)Vn[j0 * 64 + dim];
+        if ((unsigned)j1 < (unsigned)nact) x = (x & 0x0000FFFFu) | ((uint32_t)Vn[j1 * 64 + dim] << 16);
+        v.f[ks][dt][w] = x;
+      }
+    }
 }
 
 __device__ __forceinline__ float df_exp2(float x) { return __builtin_amdgcn_exp2f(x); }     // x <= 0 here, or -inf
 
+// The lane's query row: running maximum (base-2 domain), sum (the same in all lane groups) and weighted values, dims
+// 16 dt + 4 g + r.
+struct DfRow { float m, l; f32x4 o[4]; };
 
-__device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag, int layer, const DAttItem& it, uint32_t* lds,
+// One chunk, in two halves: the weights (s) and the weighted values.  qpos: position of the lane's query row (-1: none).
+__device__ __forceinline__ void df_weights(const DfK& k, const u32x4 (&qh)[2], const u32x4 (&ql)[2], int kbase, int qpos, bool masked, float sc2,
+                                           int lane, DfRow& r, f32x4 (&s)[4]) {
+  const int g = lane >> 4;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const bf16x8 k0 = __builtin_bit_cast(bf16x8, k.f[t][0]), k1 = __builtin_bit_cast(bf16x8, k.f[t][1]);
+    f32x4 z = f32x4{0, 0, 0, 0};
+    z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0, __builtin_bit_cast(bf16x8, ql[0]), z, 0, 0, 0);
+    z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1, __builtin_bit_cast(bf16x8, ql[1]), z, 0, 0, 0);
+    z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0, __builtin_bit_cast(bf16x8, qh[0]), z, 0, 0, 0);
+    z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1, __builtin_bit_cast(bf16x8, qh[1]), z, 0, 0, 0);
+    s[t] = z;
+  }
+  if (masked) {                                            // (wave-uniform: only chunks that reach the new positions)
+    const int last = qpos - kbase - 4 * g;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[t][e] = 16 * t + e <= last ? s[t][e] : -INFINITY;
+  }
+  f32x4 m4 = s[0];
+#pragma unroll
+  for (int t = 1; t < 4; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m4[e] = fmaxf(m4[e], s[t][e]);
+  const float mnew = fmaxf(r.m, max_over_groups(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]))) * sc2);
+  const float base = mnew == -INFINITY ? 0.f : mnew;      // (the row has seen no key yet: every weight is 0)
+  const float alpha = df_exp2(r.m - base);
+  f32x4 sum4 = f32x4{0, 0, 0, 0};
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s[t][e] = df_exp2(fmaf(s[t][e], sc2, -base));
+      sum4[e] += s[t][e];
+    }
+  const float sum = (sum4[0] + sum4[1]) + (sum4[2] + sum4[3]);
+  r.m = mnew;
+  r.l = fmaf(r.l, alpha, sum_over_groups(sum));
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) r.o[dt] *= alpha;
+}
+__device__ __forceinline__ void df_values(const DfV& v, const f32x4 (&s)[4], DfRow& r) {
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const uint2 h0 = hi_pairs(s[2 * ks]), h1 = hi_pairs(s[2 * ks + 1]), l0 = lo_pairs(s[2 * ks]), l1 = lo_pairs(s[2 * ks + 1]);
+    const bf16x8 ph = __builtin_bit_cast(bf16x8, u32x4{h0.x, h0.y, h1.x, h1.y}), pl = __builtin_bit_cast(bf16x8, u32x4{l0.x, l0.y, l1.x, l1.y});
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) {
+      const bf16x8 vv = __builtin_bit_cast(bf16x8, v.f[ks][dt]);
+      r.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, pl, r.o[dt], 0, 0, 0);
+      r.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, ph, r.o[dt], 0, 0, 0);
+    }
+  }
+}
+
+// A wave's rows into the merge buffers [wave][row][dim], [wave][row][max, sum]
+__device__ __forceinline__ void df_put_row(const DfRow& r, float* MO, float* ML, int wave, int lane) {
+  const int g = lane >> 4, c16 = lane & 15;
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) *(f32x4*)(MO + (wave * 16 + c16) * DF_QS + 16 * dt + 4 * g) = r.o[dt];
+  if (g == 0) { ML[(wave * 16 + c16) * 2] = r.m; ML[(wave * 16 + c16) * 2 + 1] = r.l; }
+}
+
+// Merge of the waves' (ascending) share of a row: maximum, sum and the four dims d0 .. d0 + 3.
+__device__ __forceinline__ void df_merge_row(const float* MO, const float* ML, int row, int d0, float& mx, float& l, f32x4& o) {
+  mx = -INFINITY; l = 0.f; o = f32x4{0, 0, 0, 0};
+#pragma unroll
+  for (int w = 0; w < 8; ++w) mx = fmaxf(mx, ML[(w * 16 + row) * 2]);
+  const float base = mx == -INFINITY ? 0.f : mx;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    const float e = df_exp2(ML[(w * 16 + row) * 2] - base);
+    l = fmaf(ML[(w * 16 + row) * 2 + 1], e, l);
+    const f32x4 x = *(const f32x4*)(MO + (w * 16 + row) * DF_QS + d0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = fmaf(x[i], e, o[i]);
+  }
+}
+
+template <int SB>
+__device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag, int layer, const DAttItem& it, uint32_t* lds, const int* sblk,
                                               const int* srow, int* sdead, int slot) {
-  // The pool fragments are requested first: the queries of this layer are not there yet in any case.
-  KVPre kvp;
-  df_load_kv(a, layer, it, kvp);
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int usel = wave >> 2, uw = wave & 3, ut = tid & 255;
-  uint32_t* ub = lds + usel * DF_ATT_UNIT;
-  uint32_t* Qs = ub;                                   // [16 rows][64] operand words
-  bf16_t* Kn = (bf16_t*)(ub + 4096);                   // [16][64] new keys
-  bf16_t* Vn = (bf16_t*)(ub + 4096 + 512);             // [16][64] new values
-  float* Pw = (float*)(ub + 4096 + 1024) + uw * 1024;  // [16][64] per wave
-  float* MO = (float*)(ub + 4096 + 1024 + 4096);       // [4][16][64]
-  float* ML = (float*)(ub + 4096 + 1024 + 8192);       // [4][16][2]
-  const int R = a.rows.R, G = a.nq / a.nkv, nqd = a.nq * 64, RG = R * G;
   const int g = lane >> 4, c16 = lane & 15;
-  const int kbase = it.part * ATT_PART + uw * 64;
+  // The wave's keys and its first two chunks' values are requested before anything else: the queries are not there yet in any
+  // case.  The third chunk's values follow as soon as the first keys' registers are free.
+  DfK kf[3];
+  DfV vf[3];
+  auto request = [&](int j, bool k, bool v) {
+    int boff[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) boff[t] = (sblk[(wave + 8 * j) * 4 + t] * a.kv.nkv + it.kvh) * 1024;
+    if (k) df_load_k(a, layer, boff, lane, kf[j]);
+    if (v) df_load_v(a, layer, boff, lane, vf[j]);
+  };
+  const bool live0 = it.valid && wave < it.nch, live1 = it.valid && wave + 8 < it.nch, live2 = it.valid && wave + 16 < it.nch;
+  if (live0) request(0, true, true);
+  if (live1) request(1, true, true);
+  if (live2) request(2, true, false);
+  uint32_t* Qs = lds;                                  // [16 rows][64] operand words
+  bf16_t* Kn = (bf16_t*)(lds + 16 * DF_QS);            // [16][64] new keys
+  bf16_t* Vn = (bf16_t*)(lds + 16 * DF_QS + 512);      // [16][64] new values
+  float* MO = (float*)(lds + 16 * DF_QS + 1024);       // [8 waves][16][64]
+  float* ML = MO + 8 * 16 * DF_QS;                     // [8 waves][16][2]
+  const int R = a.rows.R, G = a.nq / a.nkv, nqd = a.nq * 64, RG = R * G;
   const int r0 = 16 * it.rt, nrt = min(16, RG - r0);                         // first query row and rows of this tile
-  const bool wlive = it.valid && kbase <= it.pos_last;
-  const bool unew = it.valid && it.part * ATT_PART + ATT_PART > it.len;      // the part reaches this launch's positions
+  const bool unew = (it.c0 + it.nch) * 64 > it.len;                          // the part reaches this launch's positions
   const u64* q = a.q + (size_t)layer * a.st_q;
   const u64* kvn = a.kvn + (size_t)layer * a.st_kvn;
   u64* attn = a.attn + (size_t)layer * a.st_q;
   u64* att_p = a.att_p + (size_t)layer * a.st_att_p;
   const int* rowpos = srow + it.b * R;                 // positions of the sequence's rows
   const float sc2 = a.scale * 1.44269504088896340736f;
-  int qpos[4];                                         // positions of the 4 query rows this lane holds scores of
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int qr = r0 + 4 * g + r;
-    qpos[r] = qr < RG ? rowpos[qr / G] : -1;
-  }
+  const int qpos = r0 + c16 < RG ? rowpos[(r0 + c16) / G] : -1;              // position of the lane's query row
   bool bad = false;
-  // ---- one flight per thread: the queries of the tile's rows and this launch's keys / values of the kv head
+  // ---- the queries of the tile's rows and this launch's keys / values of the kv head
   if (it.valid) {
-    const int nQ = nrt * 64, total = nQ + (unew ? it.nact * 128 : 0);       // <= 1024 + 2048 words
+    constexpr int NB = SB <= 4 ? 3 : 6;                 // words a thread keeps in flight: one flight for 4 / all 16 new rows
+    const int nQ = nrt * 64, total = nQ + (unew ? it.nact * 128 : 0);        // <= 1024 + 2048 words
     const uint32_t q_off = (uint32_t)(q - a.tw), n_off = (uint32_t)(kvn - a.tw);
-    uint32_t off[DF_B], out[DF_B];
+    for (int base = 0; base < total; base += NB * PBLOCK) {
+      uint32_t off[NB], out[NB];
 #pragma unroll
-    for (int u = 0; u < DF_B; ++u) {
-      const int idx = u * 256 + ut;
-      off[u] = 0xFFFFFFFFu;
-      if (idx < nQ) {
-        const int r = r0 + (idx >> 6), dd = idx & 63, j = r / G, gq = r - j * G;
-        off[u] = q_off + (uint32_t)((it.b * R + j) * nqd + (it.kvh * G + gq) * 64 + dd);
-      } else if (idx < total) {
-        const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
-        off[u] = n_off + (uint32_t)((((it.b * R + it.off + jn) * 2 + which) * a.nkv + it.kvh) * 64 + dd);
+      for (int u = 0; u < NB; ++u) {
+        const int idx = base + u * PBLOCK + tid;
+        off[u] = 0xFFFFFFFFu;
+        if (idx < nQ) {
+          const int r = r0 + (idx >> 6), dd = idx & 63, j = r / G, gq = r - j * G;
+          off[u] = q_off + (uint32_t)((it.b * R + j) * nqd + (it.kvh * G + gq) * 64 + dd);
+        } else if (idx < total) {
+          const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
+          off[u] = n_off + (uint32_t)((((it.b * R + it.off + jn) * 2 + which) * a.nkv + it.kvh) * 64 + dd);
+        }
+      }
+      bad = !poll_words<NB>(a.tw, off, tag, out, a.bar + 64, a.hg + (size_t)(2 * layer) * a.st_h, tag) || bad;
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        const int idx = base + u * PBLOCK + tid;
+        if (idx < nQ) Qs[(idx >> 6) * DF_QS + (idx & 63)] = out[u];
+        else if (idx < total) {
+          const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
+          (which ? Vn : Kn)[jn * 64 + dd] = (bf16_t)out[u];
+        }
       }
     }
-    bad = !poll_words<DF_B>(a.tw, off, tag, out, a.bar + 64, a.hg + (size_t)(2 * layer) * a.st_h, tag);
-#pragma unroll
-    for (int u = 0; u < DF_B; ++u) {
-      const int idx = u * 256 + ut;
-      if (idx < nQ) Qs[idx] = out[u];
-      else if (idx < total) {
-        const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
-        (which ? Vn : Kn)[jn * 64 + dd] = (bf16_t)out[u];
-      }
-    }
-    for (int idx = nQ + ut; idx < 1024; idx += 256) Qs[idx] = 0u;           // padding rows of the tile
+    for (int idx = nQ + tid; idx < 1024; idx += PBLOCK) Qs[(idx >> 6) * DF_QS + (idx & 63)] = 0u;       // padding rows of the tile
   }
   if (bad) *sdead = 1;
   __syncthreads();
   if (*sdead) return true;
   DF_STAMP(slot);
-  // ---- fragments of positions written by this launch come from the side buffer, at the pool's fragment slots
-  if (wlive && kbase + 64 > it.len) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int jn = kbase + 16 * t + c16 - it.len;
-      if ((unsigned)jn < (unsigned)it.nact) {
-        kvp.kf[t][0] = *(const u32x4*)(Kn + jn * 64 + g * 8);
-        kvp.kf[t][1] = *(const u32x4*)(Kn + jn * 64 + 32 + g * 8);
-      }
-    }
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        const int dim = 16 * dt + c16;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          uint32_t x = kvp.vf[ks][dt][w];
-          const int j0 = kbase + 32 * ks + 8 * g + 2 * w - it.len, j1 = j0 + 1;
-          if ((unsigned)j0 < (unsigned)it.nact) x = (x & 0xFFFF0000u) | (uint32_t)Vn[j0 * 64 + dim];
-          if ((unsigned)j1 < (unsigned)it.nact) x = (x & 0x0000FFFFu) | ((uint32_t)Vn[j1 * 64 + dim] << 16);
-          kvp.vf[ks][dt][w] = x;
-        }
-      }
-  }
-  float mrow[4], lrow[4];
-  f32x4 oacc[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) { mrow[r] = -INFINITY; lrow[r] = 0.f; oacc[r] = f32x4{0, 0, 0, 0}; }
-  if (wlive) {
+  DfRow rs = {-INFINITY, 0.f, {f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}}};
+  if (live0) {
     u32x4 qh[2], ql[2];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) frag_from_lds(Qs + c16 * 64 + ks * 32 + g * 8, qh[ks], ql[ks]);
-    f32x4 s[4];
+    for (int ks = 0; ks < 2; ++ks) frag_from_lds(Qs + c16 * DF_QS + ks * 32 + g * 8, qh[ks], ql[ks]);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const bf16x8 k0 = __builtin_bit_cast(bf16x8, kvp.kf[t][0]), k1 = __builtin_bit_cast(bf16x8, kvp.kf[t][1]);
-      f32x4 z = f32x4{0, 0, 0, 0};
-      z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ql[0]), k0, z, 0, 0, 0);
-      z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ql[1]), k1, z, 0, 0, 0);
-      z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qh[0]), k0, z, 0, 0, 0);
-      z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qh[1]), k1, z, 0, 0, 0);
-      s[t] = z;
-    }
-    // element (reg r, tile t) = (query row r0 + 4g + r, key kbase + 16t + c16)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int pos = qpos[r];
-      float mx = -INFINITY;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const bool ok = kbase + 16 * t + c16 <= pos;
-        s[t][r] = ok ? s[t][r] * sc2 : -INFINITY;
-        mx = fmaxf(mx, s[t][r]);
-      }
-      mx = row16_max(mx);
-      float sum = 0.f;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const float p = (s[t][r] == -INFINITY) ? 0.f : df_exp2(s[t][r] - mx);
-        Pw[(4 * g + r) * 64 + 16 * t + c16] = p;
-        sum += p;
-      }
-      sum = row16_sum(sum);
-      mrow[r] = mx;
-      lrow[r] = sum;
-    }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const u32x4* pp = (const u32x4*)(Pw + c16 * 64 + ks * 32 + g * 8);
-      const SplitA pf = split_bf16(pp[0], pp[1]);
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        const bf16x8 vv = __builtin_bit_cast(bf16x8, kvp.vf[ks][dt]);
-        oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf.lo, vv, oacc[dt], 0, 0, 0);
-        oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf.hi, vv, oacc[dt], 0, 0, 0);
+    for (int j = 0; j < 3; ++j) {
+      const bool livej = j == 0 ? live0 : (j == 1 ? live1 : live2);
+      if (livej) {
+        const int kbase = 64 * (it.c0 + wave + 8 * j);
+        const bool fresh = kbase + 64 > it.len;          // the chunk reaches new positions: patches, masks
+        if (fresh) df_patch_k(kf[j], kbase, it.len, it.nact, Kn, lane);
+        f32x4 s[4];
+        df_weights(kf[j], qh, ql, kbase, qpos, fresh, sc2, lane, rs, s);
+        if (j == 0 && live2) request(2, false, true);
+        if (fresh) df_patch_v(vf[j], kbase, it.len, it.nact, Vn, lane);
+        df_values(vf[j], s, rs);
       }
     }
   }
-  // ---- merge the unit's four chunks (ascending key order) and publish the part
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = 4 * g + r;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) MO[(uw * 16 + row) * 64 + 16 * dt + c16] = oacc[dt][r];
-    if (c16 == 0) { ML[(uw * 16 + row) * 2] = mrow[r]; ML[(uw * 16 + row) * 2 + 1] = lrow[r]; }
-  }
+  DF_STAMP2(3);
+  // ---- the eight waves meet (fixed order: wave 0 .. 7); a single part's rows go out as operand words
+  df_put_row(rs, MO, ML, wave, lane);
   __syncthreads();
-  {
-    const int row = ut >> 4, ch = ut & 15, d0 = ch * 4, qr = r0 + row;
-    if (it.valid && qr < RG) {
-      const int j = qr / G, gq = qr - j * G, m = it.b * R + j, head = it.kvh * G + gq;
-      const int np_row = rowpos[j] / ATT_PART + 1;
-      if (it.part < np_row) {
-        float mx = -INFINITY;
-        for (int w = 0; w < 4; ++w) mx = fmaxf(mx, ML[(w * 16 + row) * 2]);
-        float l = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int w = 0; w < 4; ++w) {
-          const float mw = ML[(w * 16 + row) * 2];
-          if (mw == -INFINITY) continue;
-          const float e = df_exp2(mw - mx);
-          l = fmaf(ML[(w * 16 + row) * 2 + 1], e, l);
+  DF_STAMP2(4);
+  const int row = tid >> 4, ch = tid & 15, d0 = ch * 4;
+  if (tid < 256 && it.valid && row < nrt) {
+    const int qr = r0 + row, j = qr / G, gq = qr - j * G, m = it.b * R + j, head = it.kvh * G + gq;
+    const int np_row = rowpos[j] / (64 * a.part_chunks) + 1;                 // parts that hold keys of the row
+    if (it.part < np_row) {
+      float mx, l;
+      f32x4 o;
+      df_merge_row(MO, ML, row, d0, mx, l, o);
+      if (np_row == 1) {
+        st_words4(attn + (size_t)m * nqd + head * 64 + d0, split_payload(o[0] / l), split_payload(o[1] / l), split_payload(o[2] / l),
+                  split_payload(o[3] / l), tag);
+      } else {
+        u64* pp = att_p + ((((size_t)m * a.nq + head) * a.NP + it.part) * 16 + ch) * 6;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) o[i] = fmaf(MO[(w * 16 + row) * 64 + d0 + i], e, o[i]);
-        }
-        if (np_row == 1) {                                  // a single part: this is the result
-#pragma unroll
-          for (int i = 0; i < 4; ++i) st_word(attn + (size_t)m * nqd + head * 64 + d0 + i, split_payload(o[i] / l), tag);
-        } else {
-          u64* pp = att_p + ((((size_t)m * a.nq + head) * a.NP + it.part) * 16 + ch) * 6;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) st_wordf(pp + i, o[i], tag);
-          st_wordf(pp + 4, mx, tag);
-          st_wordf(pp + 5, l, tag);
-        }
+        for (int i = 0; i < 4; ++i) st_wordf(pp + i, o[i], tag);
+        st_wordf(pp + 4, mx, tag);
+        st_wordf(pp + 5, l, tag);
       }
     }
   }
-  // ---- merge of the parts: of the tile's rows, the unit of part p finishes those with row index = p mod P
+  // ---- merge of the parts: of the tile's rows, the workgroup of part p finishes those with row index = p mod P
   if (it.valid && it.nparts_b > 1) {
     const int P = it.nparts_b;
-    const int ri = ut >> 4, ch = ut & 15, d0 = ch * 4;
-    const int first = ((it.part - r0) % P + P) % P;                          // first row of the tile this unit finishes
-    const int qr = r0 + first + ri * P;
-    if (first + ri * P < nrt) {
+    const int first = ((it.part - r0) % P + P) % P;                          // first row of the tile this workgroup finishes
+    const int qr = r0 + first + row * P;
+    if (tid < 256 && first + row * P < nrt) {
       const int j = qr / G, gq = qr - j * G, m = it.b * R + j, head = it.kvh * G + gq;
-      const int np_row = rowpos[j] / ATT_PART + 1;
+      const int np_row = rowpos[j] / (64 * a.part_chunks) + 1;
       if (np_row > 1) {
         const uint32_t p_off = (uint32_t)(att_p - a.tw) + (uint32_t)(((m * a.nq + head) * a.NP) * 96 + ch * 6);
         float mx = -INFINITY, l = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1083,8 +1134,8 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
               for (int i = 0; i < 4; ++i) o[i] = fmaf(__uint_as_float(out[p * 6 + i]), e, o[i]);
             }
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) st_word(attn + (size_t)m * nqd + head * 64 + d0 + i, split_payload(o[i] / l), tag);
+        st_words4(attn + (size_t)m * nqd + head * 64 + d0, split_payload(o[0] / l), split_payload(o[1] / l), split_payload(o[2] / l),
+                  split_payload(o[3] / l), tag);
       }
     }
   }
@@ -1092,259 +1143,6 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   if (bad) *sdead = 1;
   __syncthreads();
   return *sdead != 0;
-}
-
-// ------------------------------------------------------------------------------------------------ attention, short prefixes
-// Up to DF_WHOLE_CHUNKS chunks of 64 keys (the host decides from its bound of the cached lengths, the same for a
-// verification and an autoregressive step from one state): item = (sequence, kv head, row tile) on a workgroup of its
-// own, no parts.  Wave w walks chunks w, w + 8, w + 16 with a running (max, sum, weighted values) per row, the eight
-// waves meet once in LDS, and the result goes out as operand words: no partial leaves the workgroup, which takes the
-// parts' hand-over (store, find, merge) out of every layer.
-constexpr int DF_WHOLE_CHUNKS = 24;
-struct DAttWhole {
-  int valid, b, kvh, rt, seq, len, nact, off, pos_last, nch;
-};
-
-__device__ __forceinline__ DAttWhole df_att_whole_item(const DArgs& a, int item, int ntile, int* sblk) {
-  DAttWhole it;
-  it.valid = item < a.n_seqs * a.nkv * ntile;
-  it.b = 0; it.kvh = 0; it.rt = 0;
-  if (it.valid) {
-    it.rt = item % ntile;
-    const int t = item / ntile;
-    it.b = t % a.n_seqs;
-    it.kvh = t / a.n_seqs;
-  }
-  it.seq = a.rows.seq0 + it.b;
-  // one round trip for all of it (see df_att_item)
-  const int len_v = it.valid ? ld_state(a.kv.len + it.seq) : 0;
-  const int npend_v = (it.valid && a.pcap) ? ld_state(a.kv.n_pend + it.seq) : 0;
-  const int i = threadIdx.x;
-  int bid = -1;
-  if (i < DF_WHOLE_CHUNKS * 4 && it.valid && i < a.kv.mbps) bid = ld_state(a.kv.table + it.seq * a.kv.mbps + i);
-  it.len = __builtin_amdgcn_readfirstlane(len_v);
-  const int npend = __builtin_amdgcn_readfirstlane(npend_v);
-  it.off = a.pcap - npend;
-  it.nact = a.rows.R - it.off;
-  it.pos_last = it.len + it.nact - 1;
-  it.nch = min(DF_WHOLE_CHUNKS, it.pos_last / 64 + 1);
-  // block ids of the sequence's positions (masked positions may read any block)
-  if (i < DF_WHOLE_CHUNKS * 4) sblk[i] = (bid < 0 || bid >= a.kv.n_blocks || i * 16 > it.pos_last) ? 0 : bid;
-  return it;
-}
-
-__device__ __forceinline__ void df_load_kv_chunk(const DArgs& a, int layer, int kvh, int chunk, const int* sblk, int lane, KVPre& kv) {
-  const size_t plane = (size_t)a.kv.n_blocks * a.kv.nkv * 1024;
-  const bf16_t* kp = (const bf16_t*)a.kv.pool + (size_t)(2 * layer) * plane;
-  const bf16_t* vp = kp + plane;
-  const int g = lane >> 4, c16 = lane & 15;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int koff = ((sblk[chunk * 4 + t] * a.kv.nkv + kvh) * 16 + c16) * 64 + g * 8;
-    kv.kf[t][0] = *(const u32x4*)(kp + koff);
-    kv.kf[t][1] = *(const u32x4*)(kp + koff + 32);
-  }
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const int vblk = sblk[chunk * 4 + 2 * ks + (g >> 1)];
-    const int voff = (vblk * a.kv.nkv + kvh) * 1024 + c16 * 16 + (g & 1) * 8;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) kv.vf[ks][dt] = *(const u32x4*)(vp + voff + dt * 256);
-  }
-}
-
-__device__ __forceinline__ bool df_attn_whole(const DArgs& a, const uint32_t tag, int layer, const DAttWhole& it, uint32_t* lds, const int* sblk,
-                                              const int* srow, int* sdead, int slot) {
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 4, c16 = lane & 15;
-  // the first two chunks of the wave are requested before anything else: the queries are not there yet in any case
-  KVPre kvp[2];
-  const bool live0 = it.valid && wave < it.nch, live1 = it.valid && wave + 8 < it.nch, live2 = it.valid && wave + 16 < it.nch;
-  if (live0) df_load_kv_chunk(a, layer, it.kvh, wave, sblk, lane, kvp[0]);
-  if (live1) df_load_kv_chunk(a, layer, it.kvh, wave + 8, sblk, lane, kvp[1]);
-  uint32_t* Qs = lds;                                  // [16 rows][64] operand words
-  bf16_t* Kn = (bf16_t*)(lds + 1024);                  // [16][64] new keys
-  bf16_t* Vn = (bf16_t*)(lds + 1536);                  // [16][64] new values
-  float* Pw = (float*)(lds + 2048) + wave * 1024;      // [16][64] per wave
-  float* MO = (float*)(lds + 2048 + 8192);             // [8 waves][16][64]
-  float* ML = (float*)(lds + 2048 + 16384);            // [8 waves][16][2]
-  const int R = a.rows.R, G = a.nq / a.nkv, nqd = a.nq * 64, RG = R * G;
-  const int r0 = 16 * it.rt, nrt = min(16, RG - r0);
-  const u64* q = a.q + (size_t)layer * a.st_q;
-  const u64* kvn = a.kvn + (size_t)layer * a.st_kvn;
-  u64* attn = a.attn + (size_t)layer * a.st_q;
-  const int* rowpos = srow + it.b * R;
-  const float sc2 = a.scale * 1.44269504088896340736f;
-  int qpos[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int qr = r0 + 4 * g + r;
-    qpos[r] = qr < RG ? rowpos[qr / G] : -1;
-  }
-  bool bad = false;
-  // ---- one flight per thread: the queries of the tile's rows and this launch's keys / values of the kv head
-  if (it.valid) {
-    constexpr int NB = 6;                               // 6 x 512 threads >= 1024 + 2048 words
-    const int nQ = nrt * 64, total = nQ + it.nact * 128;
-    const uint32_t q_off = (uint32_t)(q - a.tw), n_off = (uint32_t)(kvn - a.tw);
-    uint32_t off[NB], out[NB];
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      const int idx = u * PBLOCK + tid;
-      off[u] = 0xFFFFFFFFu;
-      if (idx < nQ) {
-        const int r = r0 + (idx >> 6), dd = idx & 63, j = r / G, gq = r - j * G;
-        off[u] = q_off + (uint32_t)((it.b * R + j) * nqd + (it.kvh * G + gq) * 64 + dd);
-      } else if (idx < total) {
-        const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
-        off[u] = n_off + (uint32_t)((((it.b * R + it.off + jn) * 2 + which) * a.nkv + it.kvh) * 64 + dd);
-      }
-    }
-    bad = !poll_words<NB>(a.tw, off, tag, out, a.bar + 64, a.hg + (size_t)(2 * layer) * a.st_h, tag);
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      const int idx = u * PBLOCK + tid;
-      if (idx < nQ) Qs[idx] = out[u];
-      else if (idx < total) {
-        const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
-        (which ? Vn : Kn)[jn * 64 + dd] = (bf16_t)out[u];
-      }
-    }
-    for (int idx = nQ + tid; idx < 1024; idx += PBLOCK) Qs[idx] = 0u;       // padding rows of the tile
-  }
-  if (bad) *sdead = 1;
-  __syncthreads();
-  if (*sdead) return true;
-  DF_STAMP(slot);
-  float mrow[4], lrow[4];
-  f32x4 oacc[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) { mrow[r] = -INFINITY; lrow[r] = 0.f; oacc[r] = f32x4{0, 0, 0, 0}; }
-  if (live0) {
-    u32x4 qh[2], ql[2];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) frag_from_lds(Qs + c16 * 64 + ks * 32 + g * 8, qh[ks], ql[ks]);
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const bool livej = j == 0 ? live0 : (j == 1 ? live1 : live2);
-      if (livej) {
-        KVPre& kc = kvp[j & 1];
-        const int kbase = 64 * (wave + 8 * j);
-        // fragments of positions written by this launch come from the side buffer, at the pool's fragment slots
-        if (kbase + 64 > it.len) {
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const int jn = kbase + 16 * t + c16 - it.len;
-            if ((unsigned)jn < (unsigned)it.nact) {
-              kc.kf[t][0] = *(const u32x4*)(Kn + jn * 64 + g * 8);
-              kc.kf[t][1] = *(const u32x4*)(Kn + jn * 64 + 32 + g * 8);
-            }
-          }
-#pragma unroll
-          for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt) {
-              const int dim = 16 * dt + c16;
-#pragma unroll
-              for (int w = 0; w < 4; ++w) {
-                uint32_t x = kc.vf[ks][dt][w];
-                const int j0 = kbase + 32 * ks + 8 * g + 2 * w - it.len, j1 = j0 + 1;
-                if ((unsigned)j0 < (unsigned)it.nact) x = (x & 0xFFFF0000u) | (uint32_t)Vn[j0 * 64 + dim];
-                if ((unsigned)j1 < (unsigned)it.nact) x = (x & 0x0000FFFFu) | ((uint32_t)Vn[j1 * 64 + dim] << 16);
-                kc.vf[ks][dt][w] = x;
-              }
-            }
-        }
-        f32x4 s[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const bf16x8 k0 = __builtin_bit_cast(bf16x8, kc.kf[t][0]), k1 = __builtin_bit_cast(bf16x8, kc.kf[t][1]);
-          f32x4 z = f32x4{0, 0, 0, 0};
-          z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ql[0]), k0, z, 0, 0, 0);
-          z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ql[1]), k1, z, 0, 0, 0);
-          z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qh[0]), k0, z, 0, 0, 0);
-          z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qh[1]), k1, z, 0, 0, 0);
-          s[t] = z;
-        }
-        // element (reg r, tile t) = (query row r0 + 4g + r, key kbase + 16t + c16)
-        float alpha[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int pos = qpos[r];
-          float mx = -INFINITY;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const bool ok = kbase + 16 * t + c16 <= pos;
-            s[t][r] = ok ? s[t][r] * sc2 : -INFINITY;
-            mx = fmaxf(mx, s[t][r]);
-          }
-          const float mnew = fmaxf(mrow[r], row16_max(mx));
-          alpha[r] = (mrow[r] == -INFINITY) ? 0.f : df_exp2(mrow[r] - mnew);
-          float sum = 0.f;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const float p = (s[t][r] == -INFINITY) ? 0.f : df_exp2(s[t][r] - mnew);
-            Pw[(4 * g + r) * 64 + 16 * t + c16] = p;
-            sum += p;
-          }
-          mrow[r] = mnew;
-          lrow[r] = fmaf(lrow[r], alpha[r], row16_sum(sum));
-        }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) oacc[dt][r] *= alpha[r];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          const u32x4* pp = (const u32x4*)(Pw + c16 * 64 + ks * 32 + g * 8);
-          const SplitA pf = split_bf16(pp[0], pp[1]);
-#pragma unroll
-          for (int dt = 0; dt < 4; ++dt) {
-            const bf16x8 vv = __builtin_bit_cast(bf16x8, kc.vf[ks][dt]);
-            oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf.lo, vv, oacc[dt], 0, 0, 0);
-            oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf.hi, vv, oacc[dt], 0, 0, 0);
-          }
-        }
-        __builtin_amdgcn_wave_barrier();               // P is rewritten by the next chunk
-        if (j == 0 && live2) df_load_kv_chunk(a, layer, it.kvh, wave + 16, sblk, lane, kvp[0]);   // its fragments are free now
-      }
-    }
-  }
-  // ---- the eight waves meet (fixed order: wave 0 .. 7) and the tile's rows go out as operand words
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = 4 * g + r;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) MO[(wave * 16 + row) * 64 + 16 * dt + c16] = oacc[dt][r];
-    if (c16 == 0) { ML[(wave * 16 + row) * 2] = mrow[r]; ML[(wave * 16 + row) * 2 + 1] = lrow[r]; }
-  }
-  __syncthreads();
-  if (tid < 256) {
-    const int row = tid >> 4, ch = tid & 15, d0 = ch * 4, qr = r0 + row;
-    if (it.valid && qr < RG) {
-      const int j = qr / G, gq = qr - j * G, m = it.b * R + j, head = it.kvh * G + gq;
-      float mx = -INFINITY;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) mx = fmaxf(mx, ML[(w * 16 + row) * 2]);
-      float l = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int w = 0; w < 8; ++w) {
-        const float mw = ML[(w * 16 + row) * 2];
-        const float e = (mw == -INFINITY) ? 0.f : df_exp2(mw - mx);
-        l = fmaf(ML[(w * 16 + row) * 2 + 1], e, l);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = fmaf(MO[(w * 16 + row) * 64 + d0 + i], e, o[i]);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) st_word(attn + (size_t)m * nqd + head * 64 + d0 + i, split_payload(o[i] / l), tag);
-    }
-  }
-  DF_STAMP(slot + 1);
-  __syncthreads();
-  return false;
 }
 
 // ------------------------------------------------------------------------------------------------ the kernel
@@ -1358,10 +1156,10 @@ __device__ __forceinline__ const DArgs& df_args() {
   return *(const DArgs*)p;
 }
 
-// WHOLE: attention of short prefixes without parts (df_attn_whole).  SB: tagged words a thread keeps in flight while
+// SB: tagged words a thread keeps in flight while
 // it stages GEMM operands -- every slot costs instructions whether it is used or not, and a second flight costs a
 // round trip, so the host picks the smallest SB whose single flight (512 threads x SB) holds the launch's rows.
-template <bool WHOLE, int SB>
+template <int SB>
 __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
   const DArgs& a = df_args();
   __shared__ __attribute__((aligned(16))) uint32_t lds[DF_LDS_WORDS];
@@ -1377,11 +1175,11 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
   const int NU = gridDim.x * 2;
   // items of every phase kind, and the unit that takes item 0 (the kinds with few items go to different workgroups)
   const int n_qkv = (a.nq + 2 * a.nkv) * 2, ntile = (a.rows.R * (a.nq / a.nkv) + 15) >> 4,
-            n_att = a.n_seqs * a.nkv * (WHOLE ? 1 : a.n_parts) * ntile, n_o = np, n_gu = a.ffn >> 4,
+            n_att = a.n_seqs * a.nkv * a.n_parts * ntile, n_o = np, n_gu = a.ffn >> 4,
             n_lg = (((a.vocab + 15) >> 4) + 1) >> 1;
   const int st = a.small_stride;
   const int st_lg = 2 * n_lg <= NU ? 2 : 1;               // the head's items: a workgroup each where there are enough (a CU's intake bounds an item's weight stream)
-  const int s_qkv = (2 * a.g_mlp) % NU, s_att = (s_qkv + st * n_qkv) % NU, s_o = (s_att + st * n_att) % NU,
+  const int s_qkv = (2 * a.g_mlp) % NU, s_att = (s_qkv + st * n_qkv) % NU, s_o = (s_att + 2 * n_att) % NU,
             s_red = (s_o + st * n_o) % NU;
   auto make_qkv = [&](const DArgs& a, int l) {
     const PLayer Y = layer_ptrs(a, l);
@@ -1419,14 +1217,12 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     x.W0 = a.head; x.W1 = a.head; x.N = a.vocab; x.K = a.d; x.gs = 1; x.items = n_lg; x.shift = 0; x.stride = st_lg; x.logits = a.logits;
     return x;
   };
-  // which phase kinds this wave's unit / this workgroup has a round-0 item in
-  const int wave_k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int unit = blockIdx.x * 2 + (wave_k >> 2);
+  // which phase kinds this workgroup has a round-0 item in
   auto has = [&](int u, int shift, int items, int stride = 1) { return df_item_of_unit(u, shift, NU, stride) < items; };
   const int n_red = a.rows.M * np;
   const int u0 = blockIdx.x * 2, u1 = u0 + 1;
   const bool g_q = has(u0, s_qkv, n_qkv, st) || has(u1, s_qkv, n_qkv, st) || st * n_qkv > NU,
-             g_a = has(u0, s_att, n_att, st) || has(u1, s_att, n_att, st),
+             g_a = has(u0, s_att, n_att, 2),                  // (an attention item has the workgroup)
              g_o = has(u0, s_o, n_o, st) || has(u1, s_o, n_o, st), g_g = (int)blockIdx.x < a.g_mlp,
              g_r = df_item_of_unit((int)blockIdx.x, s_red >> 1, (int)gridDim.x) < n_red || n_red > (int)gridDim.x, g_l = has(u0, 0, n_lg, st_lg) || has(u1, 0, n_lg, st_lg) || st_lg * n_lg > NU;
 
@@ -1434,11 +1230,8 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
   df_reserve_blocks(a, tag_v);
   // What the launch needs of the cache state (none of it changes during the launch): the waves' attention items, and
   // per row its position and whether it is active.
-  __shared__ int sblk[DF_WHOLE_CHUNKS * 4];
-  DAttItem ait = DAttItem{};
-  DAttWhole aw = DAttWhole{};
-  if (WHOLE) aw = df_att_whole_item(a, df_item_of_unit(u0, s_att, NU, st), ntile, sblk);     // the item has the workgroup (stride 2)
-  else ait = df_att_item(a, df_item_of_unit(unit, s_att, NU, st), ntile, wave_k & 3, threadIdx.x & 63);
+  __shared__ int sblk[DF_PART_CHUNKS * 4];
+  const DAttItem ait = df_att_item(a, df_item_of_unit(u0, s_att, NU, 2), ntile, sblk);
   if ((g_q || g_a) && threadIdx.x < a.rows.M) {           // the QKV epilogue and the attention masks use them
     const int m = threadIdx.x, brel = m / a.rows.R, j = m - brel * a.rows.R, seq = a.rows.seq0 + brel;
     const int len = ld_state(a.kv.len + seq);
@@ -1476,7 +1269,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     }
     if (g_a) {
       const DArgs& a = df_args();
-      if (WHOLE ? df_attn_whole(a, tag, l, aw, lds, sblk, srow, &sdead, s0 + 2) : df_attn_phase(a, tag, l, ait, lds, srow, &sdead, s0 + 2)) return;
+      if (df_attn_phase<SB>(a, tag, l, ait, lds, sblk, srow, &sdead, s0 + 2)) return;
     }
     if (g_o) {
       const DArgs& a = df_args();

@@ -311,8 +311,7 @@ struct ssd_kv {
   u64 *t_base = nullptr, *t_h, *t_hg, *t_sq, *t_q, *t_kvn, *t_attn, *t_att_p, *t_part2, *t_rowblk;
   size_t t_words = 0;
   bool dataflow = false;
-  bool attn_whole = false;   // barrier-free kernel: attention of short prefixes without parts.  Default: caches with two
-                             // pending slots (draft caches: one-row steps gain 10 %); SSD_ATTN_WHOLE=0 never, 1 every cache
+  bool attn_whole = false;   // ssd_kv_last_forward_path tells launches whose attention is one part (4) from others (3) on this cache
   bool attn_mfma = true;     // per-operator path: matrix-core attention where it applies (SSD_ATTN=valu: the scalar kernel)
   int32_t* ticket_alt = nullptr;   // ssd_verify_noalloc: the commit's arrival counter in the library's static scratch
   bool capturing = false;          // a cycle is being captured on this cache: no synchronisation, no fallback kernels
@@ -759,23 +758,21 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   const int nqd = c.n_q_heads * c.head_dim, grp = c.n_q_heads / c.n_kv_heads;
   int max_len = 0;
   for (int s = rows.seq0; s < rows.seq0 + B; ++s) max_len = std::max(max_len, kv->len_ub[s]);
-  const int n_parts = std::min(kv->NP, cdiv(max_len + rows.R, ATT_PART));
+  // Parts of the attention: one up to DF_PART_CHUNKS chunks, else parts of 16, decided from the host's bound of the cached lengths
+  // alone, so that every forward from one cache state sums a row in the same order whatever its row count.  (Merging costs a
+  // hand-over and about 2.5 us per layer, a further round of a part's eight waves 1.2.)
+  const int part_chunks = cdiv(max_len + 16, 64) <= DF_PART_CHUNKS ? DF_PART_CHUNKS : 16;
+  const int n_parts = cdiv(max_len + rows.R, 64 * part_chunks);
   // Workgroups [0, g_mlp) take the MLP items (two 16-column items each); the phases with few items (QKV, attention,
   // output projection) get workgroups of their own after them, as far as the device has compute units.
   const int g_mlp = std::min(kv->persistent_wgs, cdiv(c.d_ffn / 16, 2));
-  // short prefixes: attention without parts (decided from the host's bound of the cached lengths alone, so that every
-  // forward from one cache state takes the same path whatever its row count)
-  const int att_tiles = B * c.n_kv_heads * cdiv(rows.R * grp, 16);
-  const bool whole = kv->attn_whole && max_len + 16 <= DF_WHOLE_CHUNKS * 64 &&
-                     g_mlp + (c.n_q_heads + 2 * c.n_kv_heads) * 2 + att_tiles + npairs <= kv->cus;
-  const int n_att_items = whole ? att_tiles : att_tiles * n_parts;
-  const int n_small = (c.n_q_heads + 2 * c.n_kv_heads) * 2 + n_att_items + npairs;
-  // with compute units to spare every small-phase item gets a workgroup of its own (its waves then do not share their
-  // SIMDs with a second item), else two items share one
-  const int small_stride = g_mlp + n_small <= kv->cus ? 2 : 1;
-  const int G = std::min(kv->cus, g_mlp + cdiv(small_stride * n_small, 2)), NU = 2 * G;
-  // limits: one round of attention (its units wait for each other's parts), query rows of an item, LDS staging capacity
-  const bool fits = M <= 16 && rows.R * grp <= DF_ATT_ROWS && small_stride * n_att_items <= NU &&
+  const int n_att = B * c.n_kv_heads * cdiv(rows.R * grp, 16) * n_parts, n_other = (c.n_q_heads + 2 * c.n_kv_heads) * 2 + npairs;
+  // with compute units to spare every item of the other small phases gets a workgroup of its own, as attention's always do (its
+  // waves then do not share their SIMDs with a second item), else two items share one
+  const int small_stride = g_mlp + n_att + n_other <= kv->cus ? 2 : 1;
+  const int G = std::min(kv->cus, g_mlp + n_att + cdiv(small_stride * n_other, 2));
+  // limits: one round of attention (its workgroups wait for each other's parts), query rows of an item, LDS staging capacity
+  const bool fits = M <= 16 && rows.R * grp <= DF_ATT_ROWS && n_att <= G && n_parts <= kv->NP &&
                     M * (c.d_model + 4) <= DF_AW && M * (nqd + 4) <= DF_AW && M * (c.d_model / 32) <= DF_SQ_WORDS &&
                     c.n_layers <= 128 && 2 + 10 * c.n_layers + 2 <= 512;
   if (!fits) return -1;
@@ -795,17 +792,16 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   a.st_att_p = PR * c.n_q_heads * kv->NP * 96;
   a.rowblk = kv->t_rowblk;
   a.part2 = kv->t_part2; a.st_part2 = (size_t)(c.d_ffn / 32) * PR * c.d_model;
-  a.NP = kv->NP; a.n_parts = n_parts; a.g_mlp = g_mlp; a.small_stride = small_stride;
+  a.NP = kv->NP; a.n_parts = n_parts; a.part_chunks = part_chunks; a.g_mlp = g_mlp; a.small_stride = small_stride;
   a.bar = kv->bar;
   a.trace = kv->trace_on ? kv->trace : nullptr;
   ProfScope ps(PROF_PERSISTENT, st);
-  kv->last_whole = whole;
+  kv->last_whole = kv->attn_whole && n_parts == 1;
   // words of one operand staging: the rows' operand words and their sums of squares; one flight holds 512 x SB
   const int stage_words = M * (std::max(c.d_model, nqd) + c.d_model / 32);
   const int sb = kv->df_sb ? kv->df_sb : stage_words <= 2 * PBLOCK ? 2 : stage_words <= 4 * PBLOCK ? 4 : stage_words <= 10 * PBLOCK ? 10 : 12;
-#define DF_LAUNCH(W, S) hipLaunchKernelGGL((k_forward_dataflow<W, S>), dim3(G), dim3(PBLOCK), 0, st, a)
-  if (whole) { if (sb == 2) DF_LAUNCH(true, 2); else if (sb == 4) DF_LAUNCH(true, 4); else DF_LAUNCH(true, 12); }
-  else { if (sb == 2) DF_LAUNCH(false, 2); else if (sb == 4) DF_LAUNCH(false, 4); else if (sb == 10) DF_LAUNCH(false, 10); else DF_LAUNCH(false, 12); }
+#define DF_LAUNCH(S) hipLaunchKernelGGL((k_forward_dataflow<S>), dim3(G), dim3(PBLOCK), 0, st, a)
+  if (sb == 2) DF_LAUNCH(2); else if (sb == 4) DF_LAUNCH(4); else if (sb == 10) DF_LAUNCH(10); else DF_LAUNCH(12);
 #undef DF_LAUNCH
   LAUNCH_CHECK();
   return SSD_OK;
