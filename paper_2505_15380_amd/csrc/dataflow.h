@@ -54,9 +54,9 @@ constexpr int DF_SQ_WORDS = 1024;
 constexpr int DF_RED_WORDS = 2 * 2048;
 constexpr int DF_QS = 68;                 // words from one row to the next of the queries and of the merge buffers in LDS: rows 64
                                           // words apart would put a fragment's 16 rows into the same banks
-constexpr int DF_ATT_WORDS = 16 * DF_QS + 512 + 512 + 8 * 16 * DF_QS + 256;      // Q | new K | new V | merge O | merge m,l
-constexpr int DF_LDS_WORDS = DF_AW + DF_SQ_WORDS + DF_RED_WORDS;
-static_assert(DF_ATT_WORDS <= DF_LDS_WORDS, "");
+constexpr int DF_ATT_V = 16 * DF_QS + 512 + 512 + 8 * 16 * DF_QS + 256;           // Q | new K | new V | merge O | merge m,l |
+constexpr int DF_ATT_WORDS = DF_ATT_V + 8 * 2048;                                 // values of a chunk per wave
+constexpr int DF_LDS_WORDS = DF_AW + DF_SQ_WORDS + DF_RED_WORDS > DF_ATT_WORDS ? DF_AW + DF_SQ_WORDS + DF_RED_WORDS : DF_ATT_WORDS;
 
 // Which single word a wave watches after a failed first flight (see df_wait_hint): the phases with many consumers (QKV,
 // MLP) watch a word of their OWN operands, the others a word of the preceding phase's operands.
@@ -876,21 +876,30 @@ __device__ __forceinline__ void df_patch_k(DfK& k, int kbase, int len, int nact,
     }
   }
 }
-__device__ __forceinline__ void df_patch_v(DfV& v, int kbase, int len, int nact, const bf16_t* Vn, int lane) {
+// Values of a chunk by way of LDS: its four blocks as they are in the pool, [block][dim][token] (2 KB each, one wave's direct
+// loads; the wave waits for them itself).
+__device__ __forceinline__ void df_v_to_lds(const DArgs& a, int layer, const int (&boff)[4], int lane, uint32_t* v2) {
+  const bf16_t* vp = (const bf16_t*)a.kv.pool + (size_t)(2 * layer + 1) * ((size_t)a.kv.n_blocks * a.kv.nkv * 1024) + lane * 8;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(vp + boff[i >> 1] + (i & 1) * 512),
+                                     (__attribute__((address_space(3))) void*)(v2 + i * 256), 16, 0, 0);
+}
+__device__ __forceinline__ void df_v_from_lds(uint32_t* v2, int kbase, int len, int nact, const bf16_t* Vn, int lane, DfV& v) {
   const int g = lane >> 4, c16 = lane & 15;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  for (int jn = max(0, kbase - len); jn < min(nact, kbase + 64 - len); ++jn) {       // this launch's positions, lane = dim
+    const int tok = len + jn - kbase;
+    ((bf16_t*)v2)[(tok >> 4) * 1024 + lane * 16 + (tok & 15)] = Vn[jn * 64 + lane];
+  }
+  asm volatile("" ::: "memory");
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) {
-      const int dim = 16 * dt + c16;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        uint32_t x = v.f[ks][dt][w];
-        const int j0 = kbase + 32 * ks + 16 * (w >> 1) + 4 * g + 2 * (w & 1) - len, j1 = j0 + 1;
-        if ((unsigned)j0 < (unsigned)nact) x = (x & 0xFFFF0000u) | (uint32_t)Vn[j0 * 64 + dim];
-        if ((unsigned)j1 < (unsigned)nact) x = (x & 0x0000FFFFu) | ((uint32_t)Vn[j1 * 64 + dim] << 16);
-        v.f[ks][dt][w] = x;
-      }
+      const uint2 x = *(const uint2*)(v2 + ks * 1024 + (16 * dt + c16) * 8 + g * 2);
+      const uint2 y = *(const uint2*)(v2 + ks * 1024 + 512 + (16 * dt + c16) * 8 + g * 2);
+      v.f[ks][dt] = u32x4{x.x, x.y, y.x, y.y};
     }
 }
 
@@ -988,21 +997,26 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, c16 = lane & 15;
-  // The wave's keys and its first two chunks' values are requested before anything else: the queries are not there yet in any
-  // case.  The third chunk's values follow as soon as the first keys' registers are free.
+  // The wave's keys and values are requested before anything else: the queries are not there yet in any case.  The values of one
+  // chunk go to LDS: the third, for which there are no registers (requested when the first keys' registers were free they held
+  // the wave up for 1.2 us), or the one with new positions, which is the wave's last and is patched there (by element in
+  // registers that took 1.5 us).
   DfK kf[3];
   DfV vf[3];
-  auto request = [&](int j, bool k, bool v) {
+  uint32_t* v2 = lds + DF_ATT_V + wave * 2048;
+  auto fresh = [&](int j) { return 64 * (it.c0 + wave + 8 * j) + 64 > it.len; };     // the chunk reaches new positions
+  auto request = [&](int j) {
     int boff[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) boff[t] = (sblk[(wave + 8 * j) * 4 + t] * a.kv.nkv + it.kvh) * 1024;
-    if (k) df_load_k(a, layer, boff, lane, kf[j]);
-    if (v) df_load_v(a, layer, boff, lane, vf[j]);
+    df_load_k(a, layer, boff, lane, kf[j]);
+    if (j == 2 || fresh(j)) df_v_to_lds(a, layer, boff, lane, v2);
+    else df_load_v(a, layer, boff, lane, vf[j]);
   };
   const bool live0 = it.valid && wave < it.nch, live1 = it.valid && wave + 8 < it.nch, live2 = it.valid && wave + 16 < it.nch;
-  if (live0) request(0, true, true);
-  if (live1) request(1, true, true);
-  if (live2) request(2, true, false);
+  if (live0) request(0);
+  if (live1) request(1);
+  if (live2) request(2);
   uint32_t* Qs = lds;                                  // [16 rows][64] operand words
   bf16_t* Kn = (bf16_t*)(lds + 16 * DF_QS);            // [16][64] new keys
   bf16_t* Vn = (bf16_t*)(lds + 16 * DF_QS + 512);      // [16][64] new values
@@ -1065,12 +1079,10 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
       const bool livej = j == 0 ? live0 : (j == 1 ? live1 : live2);
       if (livej) {
         const int kbase = 64 * (it.c0 + wave + 8 * j);
-        const bool fresh = kbase + 64 > it.len;          // the chunk reaches new positions: patches, masks
-        if (fresh) df_patch_k(kf[j], kbase, it.len, it.nact, Kn, lane);
+        if (fresh(j)) df_patch_k(kf[j], kbase, it.len, it.nact, Kn, lane);
         f32x4 s[4];
-        df_weights(kf[j], qh, ql, kbase, qpos, fresh, sc2, lane, rs, s);
-        if (j == 0 && live2) request(2, false, true);
-        if (fresh) df_patch_v(vf[j], kbase, it.len, it.nact, Vn, lane);
+        df_weights(kf[j], qh, ql, kbase, qpos, fresh(j), sc2, lane, rs, s);
+        if (j == 2 || fresh(j)) df_v_from_lds(v2, kbase, it.len, it.nact, Vn, lane, vf[j]);
         df_values(vf[j], s, rs);
       }
     }
