@@ -101,11 +101,12 @@ __device__ __forceinline__ void st_word(u64* p, uint32_t payload, uint32_t tag) 
   __hip_atomic_store(p, (u64)payload | ((u64)tag << 32), __ATOMIC_RELAXED, AG);
 }
 __device__ __forceinline__ void st_wordf(u64* p, float x, uint32_t tag) { st_word(p, __float_as_uint(x), tag); }
-// Four consecutive words (16-byte aligned) with two stores of two words each: a word is still stored by one instruction, and each
-// of them has its tag.
-__device__ __forceinline__ void st_words4(u64* p, uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, uint32_t tag) {
-  const u32x4 a = {x0, tag, x1, tag}, b = {x2, tag, x3, tag};
-  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\tglobal_store_dwordx4 %0, %2, off offset:16 sc1\n\ts_nop 0" ::"v"(p), "v"(a), "v"(b) : "memory");
+// Two consecutive words (16-byte aligned) with one store: a word is still stored by one instruction, and each has its tag.  (The
+// s_nop: store data of more than 8 bytes must not be overwritten by the next two vector instructions.)
+template <int OFFSET = 0>
+__device__ __forceinline__ void st_words2(u64* p, uint32_t x0, uint32_t x1, uint32_t tag) {
+  const u32x4 a = {x0, tag, x1, tag};
+  asm volatile("global_store_dwordx4 %0, %1, off offset:%2 sc1\n\ts_nop 1" ::"v"(p), "v"(a), "n"(OFFSET) : "memory");
 }
 __device__ __forceinline__ uint32_t split_payload(float x) {
   const uint32_t u = __float_as_uint(x), h = u & 0xFFFF0000u;
@@ -463,6 +464,10 @@ struct WDown { u32x4 b[DF_DN]; };
 
 __device__ __forceinline__ uint32_t df_tag2(const uint32_t tag, int layer) { return tag * 128u + (uint32_t)layer; }
 
+// The piece of a weight fragment that a lane takes where row 4 g + r of the product is to be the tile's column 2 g + r (r < 2) or
+// 8 + 2 g + r - 2.
+__device__ __forceinline__ int down_lane(int lane) { return (lane & 48) + ((lane & 2) << 2) + ((lane & 12) >> 1) + (lane & 1); }
+
 // Fragments (n-tile wave + 8 i, k-tile kt2) of the down projection for i < DF_DN; exactly DF_DN loads.
 __device__ __forceinline__ void df_prefetch_down(const DArgs& a, const void* wdown, int kt2, WDown& wd) {
   int tid = threadIdx.x;
@@ -472,7 +477,7 @@ __device__ __forceinline__ void df_prefetch_down(const DArgs& a, const void* wdo
 #pragma unroll
   for (int i = 0; i < DF_DN; ++i) {
     const int nt = (wave + 8 * i < ntiles) ? wave + 8 * i : wave;
-    wd.b[i] = __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + lane);
+    wd.b[i] = __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + down_lane(lane));
   }
 }
 
@@ -573,21 +578,27 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
       if (arow < M) frag_from_lds(sact + arow * 36 + g * 8, xh, xl);
       const bf16x8 ah = __builtin_bit_cast(bf16x8, xh), al = __builtin_bit_cast(bf16x8, xl);
       u64* po = part2 + ((size_t)kt2 * PR) * a.d;
-      // computed transposed: a lane holds four consecutive columns of row c16, which two stores publish
+      // Computed transposed: a lane holds four columns of row c16, which two stores publish.  They are columns 2g, 2g + 1, 8 + 2g and
+      // 9 + 2g (see down_lane), so that the four lanes of a row store 64 contiguous bytes at a time.
+      // The weights have arrived long ago; waiting for all of them here tells the compiler so.  It does not count the stores below,
+      // and its own wait for the i-th tile's weights would wait for acknowledged stores (0.8 us).
+      __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt(0)
       auto tile = [&](int nt, const u32x4 w) {
         const bf16x8 bv = __builtin_bit_cast(bf16x8, w);
         f32x4 acc = f32x4{0, 0, 0, 0};
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, al, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, ah, acc, 0, 0, 0);
-        if (c16 < M)
-          st_words4(po + (size_t)c16 * a.d + nt * 16 + 4 * g, __float_as_uint(acc[0]), __float_as_uint(acc[1]), __float_as_uint(acc[2]),
-                    __float_as_uint(acc[3]), tag2);
+        if (c16 < M) {
+          u64* o = po + (size_t)c16 * a.d + nt * 16 + 2 * g;
+          st_words2(o, __float_as_uint(acc[0]), __float_as_uint(acc[1]), tag2);
+          st_words2<64>(o, __float_as_uint(acc[2]), __float_as_uint(acc[3]), tag2);
+        }
       };
 #pragma unroll
       for (int i = 0; i < DF_DN; ++i)
         if (wave + 8 * i < ntiles_d) tile(wave + 8 * i, wd.b[i]);
       for (int nt = wave + 8 * DF_DN; nt < ntiles_d; nt += 8)        // wider models: the remaining tiles, not prefetched
-        tile(nt, __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + lane));
+        tile(nt, __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + down_lane(lane)));
     }
     if (rd == 0) DF_STAMP(slot + 1);
     __syncthreads();
@@ -974,9 +985,9 @@ __device__ __forceinline__ void df_put_row(const DfRow& r, float* MO, float* ML,
   if (g == 0) { ML[(wave * 16 + c16) * 2] = r.m; ML[(wave * 16 + c16) * 2 + 1] = r.l; }
 }
 
-// Merge of the waves' (ascending) share of a row: maximum, sum and the four dims d0 .. d0 + 3.
-__device__ __forceinline__ void df_merge_row(const float* MO, const float* ML, int row, int d0, float& mx, float& l, f32x4& o) {
-  mx = -INFINITY; l = 0.f; o = f32x4{0, 0, 0, 0};
+// Merge of the waves' (ascending) share of a row: maximum, sum and the two dims d0, d0 + 1.
+__device__ __forceinline__ void df_merge_row(const float* MO, const float* ML, int row, int d0, float& mx, float& l, float (&o)[2]) {
+  mx = -INFINITY; l = 0.f; o[0] = o[1] = 0.f;
 #pragma unroll
   for (int w = 0; w < 8; ++w) mx = fmaxf(mx, ML[(w * 16 + row) * 2]);
   const float base = mx == -INFINITY ? 0.f : mx;
@@ -984,9 +995,9 @@ __device__ __forceinline__ void df_merge_row(const float* MO, const float* ML, i
   for (int w = 0; w < 8; ++w) {
     const float e = df_exp2(ML[(w * 16 + row) * 2] - base);
     l = fmaf(ML[(w * 16 + row) * 2 + 1], e, l);
-    const f32x4 x = *(const f32x4*)(MO + (w * 16 + row) * DF_QS + d0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = fmaf(x[i], e, o[i]);
+    const float2 x = *(const float2*)(MO + (w * 16 + row) * DF_QS + d0);
+    o[0] = fmaf(x.x, e, o[0]);
+    o[1] = fmaf(x.y, e, o[1]);
   }
 }
 
@@ -1092,28 +1103,24 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   df_put_row(rs, MO, ML, wave, lane);
   __syncthreads();
   DF_STAMP2(4);
-  const int row = tid >> 4, ch = tid & 15, d0 = ch * 4;
-  if (tid < 256 && it.valid && row < nrt) {
+  if (const int row = tid >> 5, d0 = (tid & 31) * 2; it.valid && row < nrt) {
     const int qr = r0 + row, j = qr / G, gq = qr - j * G, m = it.b * R + j, head = it.kvh * G + gq;
     const int np_row = rowpos[j] / (64 * a.part_chunks) + 1;                 // parts that hold keys of the row
     if (it.part < np_row) {
-      float mx, l;
-      f32x4 o;
+      float mx, l, o[2];
       df_merge_row(MO, ML, row, d0, mx, l, o);
       if (np_row == 1) {
-        st_words4(attn + (size_t)m * nqd + head * 64 + d0, split_payload(o[0] / l), split_payload(o[1] / l), split_payload(o[2] / l),
-                  split_payload(o[3] / l), tag);
+        st_words2(attn + (size_t)m * nqd + head * 64 + d0, split_payload(o[0] / l), split_payload(o[1] / l), tag);
       } else {
-        u64* pp = att_p + ((((size_t)m * a.nq + head) * a.NP + it.part) * 16 + ch) * 6;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) st_wordf(pp + i, o[i], tag);
-        st_wordf(pp + 4, mx, tag);
-        st_wordf(pp + 5, l, tag);
+        u64* pp = att_p + ((((size_t)m * a.nq + head) * a.NP + it.part) * 16 + (d0 >> 2)) * 6;
+        st_words2(pp + (d0 & 2), __float_as_uint(o[0]), __float_as_uint(o[1]), tag);
+        if (!(d0 & 2)) st_words2(pp + 4, __float_as_uint(mx), __float_as_uint(l), tag);
       }
     }
   }
   // ---- merge of the parts: of the tile's rows, the workgroup of part p finishes those with row index = p mod P
   if (it.valid && it.nparts_b > 1) {
+    const int row = tid >> 4, ch = tid & 15, d0 = ch * 4;
     const int P = it.nparts_b;
     const int first = ((it.part - r0) % P + P) % P;                          // first row of the tile this workgroup finishes
     const int qr = r0 + first + row * P;
@@ -1146,8 +1153,9 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
               for (int i = 0; i < 4; ++i) o[i] = fmaf(__uint_as_float(out[p * 6 + i]), e, o[i]);
             }
         }
-        st_words4(attn + (size_t)m * nqd + head * 64 + d0, split_payload(o[0] / l), split_payload(o[1] / l), split_payload(o[2] / l),
-                  split_payload(o[3] / l), tag);
+        u64* out = attn + (size_t)m * nqd + head * 64 + d0;
+        st_words2(out, split_payload(o[0] / l), split_payload(o[1] / l), tag);
+        st_words2<16>(out, split_payload(o[2] / l), split_payload(o[3] / l), tag);
       }
     }
   }
