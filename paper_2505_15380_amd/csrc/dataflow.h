@@ -38,6 +38,8 @@
 // The launch number is not a kernel argument: it is read from the cache's control words, and the kernel that follows
 // every forward on the stream advances it, so a captured graph of launches can be replayed.
 #pragma once
+#include <utility>
+
 #include "persistent.h"
 
 namespace ssd {
@@ -103,6 +105,8 @@ __device__ __forceinline__ void st_word(u64* p, uint32_t payload, uint32_t tag) 
 __device__ __forceinline__ void st_wordf(u64* p, float x, uint32_t tag) { st_word(p, __float_as_uint(x), tag); }
 // Two consecutive words (16-byte aligned) with one store: a word is still stored by one instruction, and each has its tag.  (The
 // s_nop: store data of more than 8 bytes must not be overwritten by the next two vector instructions.)
+template <typename F, int... I>
+__device__ __forceinline__ void for_each_index(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }
 template <int OFFSET = 0>
 __device__ __forceinline__ void st_words2(u64* p, uint32_t x0, uint32_t x1, uint32_t tag) {
   const u32x4 a = {x0, tag, x1, tag};
@@ -583,22 +587,34 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
       // The weights have arrived long ago; waiting for all of them here tells the compiler so.  It does not count the stores below,
       // and its own wait for the i-th tile's weights would wait for acknowledged stores (0.8 us).
       __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt(0)
-      auto tile = [&](int nt, const u32x4 w) {
-        const bf16x8 bv = __builtin_bit_cast(bf16x8, w);
-        f32x4 acc = f32x4{0, 0, 0, 0};
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, al, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, ah, acc, 0, 0, 0);
-        if (c16 < M) {
-          u64* o = po + (size_t)c16 * a.d + nt * 16 + 2 * g;
-          st_words2(o, __float_as_uint(acc[0]), __float_as_uint(acc[1]), tag2);
-          st_words2<64>(o, __float_as_uint(acc[2]), __float_as_uint(acc[3]), tag2);
-        }
-      };
+      f32x4 acc[DF_DN];
 #pragma unroll
       for (int i = 0; i < DF_DN; ++i)
-        if (wave + 8 * i < ntiles_d) tile(wave + 8 * i, wd.b[i]);
-      for (int nt = wave + 8 * DF_DN; nt < ntiles_d; nt += 8)        // wider models: the remaining tiles, not prefetched
-        tile(nt, __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + down_lane(lane)));
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd.b[i]), al, f32x4{0, 0, 0, 0}, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < DF_DN; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd.b[i]), ah, acc[i], 0, 0, 0);
+      u64* o = po + (size_t)c16 * a.d + wave * 16 + 2 * g;           // tile wave + 8 i is 1 KB i further
+      if (c16 < M) {
+        auto put = [&](auto i) {
+          constexpr int I = decltype(i)::value;
+          if (wave + 8 * I < ntiles_d) {
+            st_words2<I % 4 * 1024>(o + I / 4 * 512, __float_as_uint(acc[I][0]), __float_as_uint(acc[I][1]), tag2);
+            st_words2<I % 4 * 1024 + 64>(o + I / 4 * 512, __float_as_uint(acc[I][2]), __float_as_uint(acc[I][3]), tag2);
+          }
+        };
+        for_each_index(put, std::make_integer_sequence<int, DF_DN>());
+      }
+      for (int nt = wave + 8 * DF_DN; nt < ntiles_d; nt += 8) {      // wider models: the remaining tiles, not prefetched
+        const bf16x8 bv = __builtin_bit_cast(bf16x8, __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + down_lane(lane)));
+        f32x4 x = f32x4{0, 0, 0, 0};
+        x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, al, x, 0, 0, 0);
+        x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, ah, x, 0, 0, 0);
+        if (c16 < M) {
+          u64* on = o + (nt - wave) * 16;
+          st_words2(on, __float_as_uint(x[0]), __float_as_uint(x[1]), tag2);
+          st_words2<64>(on, __float_as_uint(x[2]), __float_as_uint(x[3]), tag2);
+        }
+      }
     }
     if (rd == 0) DF_STAMP(slot + 1);
     __syncthreads();
