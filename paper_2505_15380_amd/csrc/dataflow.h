@@ -80,13 +80,14 @@ struct DArgs {
   u64* tw;                // base of the tagged workspace; the members below point into it
   u64* h;                 // [2L+1][PR][d]      fp32: residual stream entering layer l at 2l, after attention at 2l+1
   u64* hg;                // [2L+1][PR][d]      operand: h times the gain of the RMSNorm that consumes it
-  u64* sq;                // [2L+1][PR][d/32]   fp32: sums of squares of h over 32 columns
+  u64* sq;                // [2L+1][PR][d/8]    fp32: sums of squares of h over 32 columns (after the MLP: over df_red_cols columns)
   u64* q;                 // [L][PR][nq*64]     operand: rotated queries
   u64* kvn;               // [L][PR][2][nkv*64] bf16: this launch's keys (rotated) and values
   u64* attn;              // [L][PR][nq*64]     operand: attention output
   u64* att_p;             // [L][PR][nq][NP][16][6] fp32: per part and 4-dim chunk: 4 weighted values, max, sum
-  u64* part2;             // [2][ffn/32][PR][d] fp32: down-projection partials of one 32-column slice of the SwiGLU output each,
-                          // tagged with launch and layer (buffer = layer parity)
+  u64* part2;             // [2][row][d/32][ffn/32][32] fp32: down-projection partials of one 32-column slice of the SwiGLU output each,
+                          // tagged with launch and layer (buffer = layer parity).  What a sum task reads is contiguous: with a
+                          // row per workgroup, 112 KB apart, its pieces and all workgroups' stores fell on few memory channels
   size_t st_part2;
   u64* rowblk;            // [16] per row: the pool block that takes the row's new key and value (-1: none), from the reservation
   float* logits;
@@ -188,6 +189,10 @@ __device__ __forceinline__ bool poll_parts(const u64* base, uint32_t off0, int n
   return ok;
 }
 
+// Columns of a task of df_reduce_phase, and of a sum of squares that it publishes.
+template <int SB>
+constexpr int df_red_cols() { return SB <= 4 ? 8 : 32; }
+
 // ------------------------------------------------------------------------------------------------ GEMM phases
 struct DPhase {
   const u64* A;           // operand rows [PR][K]
@@ -211,16 +216,16 @@ struct DPhase {
 };
 
 // Operand words of rows [0, M) (K words each, the rows contiguous) -> As[row * (K + 4) + k], and the rows' sums of
-// squares [M][KT] -> sqs.  Thread gt of gn; the whole group polls in parallel.  Two more words per thread (x0, x1:
+// squares [M][nsq] -> sqs.  Thread gt of gn; the whole group polls in parallel.  Two more words per thread (x0, x1:
 // offsets, or ~0) ride in the first flight and come back in xo0, xo1.  Word offsets are recomputed for a repeated
 // load instead of being kept in registers; with whole rows a word's offset is its index, and only the padded LDS
 // address needs the row (every slot of a flight costs its instructions whether it holds a word or not).
 template <int SB>
-__device__ __forceinline__ bool stage_operand(const DArgs& a, const u64* A, int K, const u64* sq, int KT,
+__device__ __forceinline__ bool stage_operand(const DArgs& a, const u64* A, int K, const u64* sq, int nsq,
                                               uint32_t* As, float* sqs, int gt, int gn, uint32_t x0, uint32_t x1,
                                               uint32_t& xo0, uint32_t& xo1, const u64* hint, uint32_t hint_tag,
                                               const uint32_t tag) {
-  const int M = a.rows.M, kn = K, nA = M * kn, total = nA + (sq ? M * KT : 0);
+  const int M = a.rows.M, kn = K, nA = M * kn, total = nA + (sq ? M * nsq : 0);
   const uint32_t a_off = (uint32_t)(A - a.tw), s_off = sq ? (uint32_t)(sq - a.tw) : 0u;
   const float rkn = 1.0f / (float)kn;
   uint32_t* err = a.bar + 64;
@@ -273,12 +278,14 @@ __device__ __forceinline__ bool stage_operand(const DArgs& a, const u64* A, int 
 }
 
 // hi / lo fragments (8 consecutive k each) of a lane from 8 staged payload words
-__device__ __forceinline__ void frag_from_lds(const uint32_t* p, u32x4& hi, u32x4& lo) {
-  const u32x4 w0 = *(const u32x4*)p, w1 = *(const u32x4*)(p + 4);
+__device__ __forceinline__ void split_words(const u32x4 w0, const u32x4 w1, u32x4& hi, u32x4& lo) {
   hi = u32x4{__builtin_amdgcn_perm(w0[1], w0[0], 0x05040100u), __builtin_amdgcn_perm(w0[3], w0[2], 0x05040100u),
              __builtin_amdgcn_perm(w1[1], w1[0], 0x05040100u), __builtin_amdgcn_perm(w1[3], w1[2], 0x05040100u)};
   lo = u32x4{__builtin_amdgcn_perm(w0[1], w0[0], 0x07060302u), __builtin_amdgcn_perm(w0[3], w0[2], 0x07060302u),
              __builtin_amdgcn_perm(w1[1], w1[0], 0x07060302u), __builtin_amdgcn_perm(w1[3], w1[2], 0x07060302u)};
+}
+__device__ __forceinline__ void frag_from_lds(const uint32_t* p, u32x4& hi, u32x4& lo) {
+  split_words(*(const u32x4*)p, *(const u32x4*)(p + 4), hi, lo);
 }
 
 // Clock samples per workgroup and phase, only in builds with -DSSD_TRACE (see ssd_trace_barriers).
@@ -298,6 +305,70 @@ __device__ __forceinline__ int df_item_of_unit(int unit, int shift, int NU, int 
   if (stride == 2) return (i & 1) ? 0x3FFFFFFF : (i >> 1);
   return i;
 }
+
+// Products of a wave's k-tiles [kb, ke) with two weight tiles (the first PF_K k-tiles' weights are in wl) into acc0, acc1: element
+// (r, lane) = (row 4 g + r, column lane % 16).  The hi and the lo halves of the operands have a sum each, which meet at the
+// end.  Up to 8 rows (PACK) one instruction takes both: rows 0 .. 7 of its operand are the hi halves, 8 .. 15 the lo halves, and
+// the sums meet across the wave's halves; only rows 0 .. 7 of the result mean anything then.  Half the matrix and half the
+// unpacking instructions: gate / up of one row 1.0 -> 0.7 us of a layer, QKV 1.6 -> 1.2.
+template <bool PACK>
+__device__ __forceinline__ void df_products(const uint32_t* As, int K, int M, int kb, int ke, int lane, const WPre& wl, const u32x4* w0,
+                                            const u32x4* w1, f32x4& acc0, f32x4& acc1) {
+  // (lanes of rows that are not there take the last one: what they yield is never looked at)
+  const uint32_t* p = As + min(PACK ? lane & 7 : lane & 15, M - 1) * (K + 4) + (lane >> 4) * 8;
+  const uint32_t sel = lane & 8 ? 0x07060302u : 0x05040100u;
+  f32x4 lo0 = f32x4{0, 0, 0, 0}, lo1 = f32x4{0, 0, 0, 0};
+  // all operand fragments first (their LDS latencies overlap), then the products
+  u32x4 x[PF_K], y[PF_K];
+#pragma unroll
+  for (int u = 0; u < PF_K; ++u) {
+    const int kt = min(kb + u, ke - 1);
+    x[u] = *(const u32x4*)(p + kt * 32);
+    y[u] = *(const u32x4*)(p + kt * 32 + 4);
+  }
+#define DF_MULTIPLY(X, Y, B0, B1)                                                                                            \
+  {                                                                                                                          \
+    const bf16x8 bv0 = __builtin_bit_cast(bf16x8, B0), bv1 = __builtin_bit_cast(bf16x8, B1);                                 \
+    if (PACK) {                                                                                                              \
+      const u32x4 f = {__builtin_amdgcn_perm(X[1], X[0], sel), __builtin_amdgcn_perm(X[3], X[2], sel),                       \
+                       __builtin_amdgcn_perm(Y[1], Y[0], sel), __builtin_amdgcn_perm(Y[3], Y[2], sel)};                      \
+      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f), bv0, acc0, 0, 0, 0);                     \
+      acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f), bv1, acc1, 0, 0, 0);                     \
+    } else {                                                                                                                 \
+      u32x4 fh, fl;                                                                                                          \
+      split_words(X, Y, fh, fl);                                                                                             \
+      lo0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fl), bv0, lo0, 0, 0, 0);                      \
+      lo1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fl), bv1, lo1, 0, 0, 0);                      \
+      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fh), bv0, acc0, 0, 0, 0);                    \
+      acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fh), bv1, acc1, 0, 0, 0);                    \
+    }                                                                                                                        \
+  }
+#pragma unroll
+  for (int u = 0; u < PF_K; ++u)
+    if (kb + u < ke) DF_MULTIPLY(x[u], y[u], wl.b0[u], wl.b1[u])
+  for (int kt = kb + PF_K; kt < ke; ++kt) {                // waves with more than PF_K k-tiles
+    const u32x4 xk = *(const u32x4*)(p + kt * 32), yk = *(const u32x4*)(p + kt * 32 + 4);
+    const u32x4 b0 = __builtin_nontemporal_load(w0 + (size_t)kt * 64), b1 = __builtin_nontemporal_load(w1 + (size_t)kt * 64);
+    DF_MULTIPLY(xk, yk, b0, b1)
+  }
+#undef DF_MULTIPLY
+  if (PACK) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc0[r]), __float_as_uint(acc0[r]), false, false);
+      const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc1[r]), __float_as_uint(acc1[r]), false, false);
+      acc0[r] = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+      acc1[r] = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    }
+  } else {
+    acc0 += lo0;
+    acc1 += lo1;
+  }
+}
+// Rows that the products' PACK form takes; the instantiations for few words in flight use it.
+template <int SB>
+constexpr bool df_pack() { return SB <= 10; }
+constexpr int DF_PACK_ROWS = 8;
 
 // One GEMM phase (QKV, output projection, head); the caller skips it for a workgroup none of whose units has an
 // item.  The weight fragments of the unit's item are requested at entry, into registers, before the wait for the
@@ -358,33 +429,14 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
       hx1 = h_off + n1;
     }
     bool ok = true;
-    if (rd == 0) ok = stage_operand<SB>(a, ph.A, ph.K, ph.sq, KT, As, sqs, tid, PBLOCK, hx0, hx1, hv0, hv1, ph.hint, ph.hint_tag, tag);
+    if (rd == 0) ok = stage_operand<SB>(a, ph.A, ph.K, ph.sq, ph.K / df_red_cols<SB>(), As, sqs, tid, PBLOCK, hx0, hx1, hv0, hv1, ph.hint, ph.hint_tag, tag);
     if (!ok) *sdead = 1;
     __syncthreads();
     if (*sdead) return true;
     if (rd == 0) DF_STAMP(slot);
     // ---- products
     f32x4 acc0 = f32x4{0, 0, 0, 0}, acc1 = f32x4{0, 0, 0, 0};
-    const uint32_t* arow_p = As + arow * (ph.K + 4) + g * 8;
-    if (valid) {
-      // all operand fragments first (their LDS latencies overlap), then the products
-      u32x4 fh[PF_K], fl[PF_K];
-#pragma unroll
-      for (int u = 0; u < PF_K; ++u) {
-        fh[u] = u32x4{0u, 0u, 0u, 0u};
-        fl[u] = fh[u];
-        if (kb + u < ke && arow < M) frag_from_lds(arow_p + (kb + u) * 32, fh[u], fl[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < PF_K; ++u)
-        if (kb + u < ke) mfma_pair(fh[u], fl[u], wl.b0[u], wl.b1[u], acc0, acc1);
-      for (int kt = kb + PF_K; kt < ke; ++kt) {                       // waves with more than PF_K k-tiles
-        u32x4 xh = u32x4{0u, 0u, 0u, 0u}, xl = xh;
-        if (arow < M) frag_from_lds(arow_p + kt * 32, xh, xl);
-        mfma_pair(xh, xl, __builtin_nontemporal_load(w0 + (size_t)kt * 64), __builtin_nontemporal_load(w1 + (size_t)kt * 64),
-                  acc0, acc1);
-      }
-    }
+    if (valid) df_products<df_pack<SB>()>(As, ph.K, M, kb, ke, lane, wl, w0, w1, acc0, acc1);
     const int obase = (g * 4) * 16 + (lane & 15);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -392,8 +444,15 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
       red[uw][1][obase + r * 16] = acc1[r];
     }
     float sq = 0.f;
-    if (ph.sq && row < M)
-      for (int p = col; p < KT; p += 16) sq += sqs[row * KT + p];
+    if (ph.sq && row < M)                                  // sums over 32 columns, as the halves of df_reduce_phase's tree
+      for (int p = col; p < KT; p += 16) {
+        if (df_red_cols<SB>() == 8) {
+          const f32x4 q = *(const f32x4*)(sqs + (row * KT + p) * 4);
+          sq += (q[0] + q[1]) + (q[2] + q[3]);
+        } else {
+          sq += sqs[row * KT + p];
+        }
+      }
     __syncthreads();
     float v0 = (red[0][0][ut] + red[1][0][ut]) + (red[2][0][ut] + red[3][0][ut]);
     float v1 = (red[0][1][ut] + red[1][1][ut]) + (red[2][1][ut] + red[3][1][ut]);
@@ -532,28 +591,9 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
     if (*sdead) return true;
     if (rd == 0) DF_STAMP(slot);
     f32x4 acc0 = f32x4{0, 0, 0, 0}, acc1 = f32x4{0, 0, 0, 0};
-    const uint32_t* arow_p = As + arow * (ph.K + 4) + g * 8;
-    if (valid) {
-      const u32x4* w0 = (const u32x4*)ph.W0 + (size_t)item * KT * 64 + lane;
-      const u32x4* w1 = (const u32x4*)ph.W1 + (size_t)item * KT * 64 + lane;
-      // all operand fragments first (their LDS latencies overlap), then the products
-      u32x4 fh[PF_K], fl[PF_K];
-#pragma unroll
-      for (int u = 0; u < PF_K; ++u) {
-        fh[u] = u32x4{0u, 0u, 0u, 0u};
-        fl[u] = fh[u];
-        if (kb + u < ke && arow < M) frag_from_lds(arow_p + (kb + u) * 32, fh[u], fl[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < PF_K; ++u)
-        if (kb + u < ke) mfma_pair(fh[u], fl[u], pre.b0[u], pre.b1[u], acc0, acc1);
-      for (int kt = kb + PF_K; kt < ke; ++kt) {
-        u32x4 xh = u32x4{0u, 0u, 0u, 0u}, xl = xh;
-        if (arow < M) frag_from_lds(arow_p + kt * 32, xh, xl);
-        mfma_pair(xh, xl, __builtin_nontemporal_load(w0 + (size_t)kt * 64), __builtin_nontemporal_load(w1 + (size_t)kt * 64),
-                  acc0, acc1);
-      }
-    }
+    if (valid)
+      df_products<df_pack<SB>()>(As, ph.K, M, kb, ke, lane, pre, (const u32x4*)ph.W0 + (size_t)item * KT * 64 + lane,
+                                 (const u32x4*)ph.W1 + (size_t)item * KT * 64 + lane, acc0, acc1);
     DF_STAMP2(0);
     const int obase = (g * 4) * 16 + (lane & 15);
 #pragma unroll
@@ -581,7 +621,6 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
       u32x4 xh = u32x4{0u, 0u, 0u, 0u}, xl = xh;
       if (arow < M) frag_from_lds(sact + arow * 36 + g * 8, xh, xl);
       const bf16x8 ah = __builtin_bit_cast(bf16x8, xh), al = __builtin_bit_cast(bf16x8, xl);
-      u64* po = part2 + ((size_t)kt2 * PR) * a.d;
       // Computed transposed: a lane holds four columns of row c16, which two stores publish.  They are columns 2g, 2g + 1, 8 + 2g and
       // 9 + 2g (see down_lane), so that the four lanes of a row store 64 contiguous bytes at a time.
       // The weights have arrived long ago; waiting for all of them here tells the compiler so.  It does not count the stores below,
@@ -593,13 +632,16 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd.b[i]), al, f32x4{0, 0, 0, 0}, 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < DF_DN; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd.b[i]), ah, acc[i], 0, 0, 0);
-      u64* o = po + (size_t)c16 * a.d + wave * 16 + 2 * g;           // tile wave + 8 i is 1 KB i further
+      // tile nt of row c16; tile wave + 8 i is 4 i blocks of 32 columns further
+      const int nW = a.ffn >> 5;
+      u64* o = part2 + ((size_t)(c16 * (a.d >> 5) + (wave >> 1)) * nW + kt2) * 32 + (wave & 1) * 16 + 2 * g;
       if (c16 < M) {
         auto put = [&](auto i) {
           constexpr int I = decltype(i)::value;
           if (wave + 8 * I < ntiles_d) {
-            st_words2<I % 4 * 1024>(o + I / 4 * 512, __float_as_uint(acc[I][0]), __float_as_uint(acc[I][1]), tag2);
-            st_words2<I % 4 * 1024 + 64>(o + I / 4 * 512, __float_as_uint(acc[I][2]), __float_as_uint(acc[I][3]), tag2);
+            u64* oi = o + (size_t)(4 * I * 32) * nW;
+            st_words2(oi, __float_as_uint(acc[I][0]), __float_as_uint(acc[I][1]), tag2);
+            st_words2<64>(oi, __float_as_uint(acc[I][2]), __float_as_uint(acc[I][3]), tag2);
           }
         };
         for_each_index(put, std::make_integer_sequence<int, DF_DN>());
@@ -610,7 +652,7 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
         x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, al, x, 0, 0, 0);
         x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, ah, x, 0, 0, 0);
         if (c16 < M) {
-          u64* on = o + (nt - wave) * 16;
+          u64* on = o + (size_t)((nt - wave) * 16) * nW;
           st_words2(on, __float_as_uint(x[0]), __float_as_uint(x[1]), tag2);
           st_words2<64>(on, __float_as_uint(x[2]), __float_as_uint(x[3]), tag2);
         }
@@ -622,47 +664,64 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
   return false;
 }
 
-// Sum of the ffn/32 down-projection partials in ascending order, residual, and the operand / statistics of the next
-// RMSNorm.  Task = (row, 32 output columns) on a whole workgroup; thread (column c, group g of 16) sums the partials of
-// its group, the groups meet in LDS in ascending order.  (With a task per 4-wave unit and 8 groups a thread had 19
-// words in flight and two tasks polled through one CU: 30 us more per five-row forward.)
-constexpr int DF_RG = 16;                 // groups of partials per task: 512 threads = 32 columns x 16 groups
-constexpr int DF_RW = 10;                 // partials a thread keeps in flight
+// Sum of the ffn/32 down-projection partials, residual, and the operand / statistics of the next RMSNorm.  Task = (row, C
+// output columns) on a whole workgroup.  What bounds it is a compute unit's intake of the partials (32 columns are 39 KB, 1.5 us),
+// so few rows are cut finer: C = 8 where the launch has the workgroups (the instantiations for few words, one or two
+// rows of the 0.5B shape; one row: 3.0 -> 1.9 us from the end of the MLP to the sum), else 32.
+// The order of a sum does not depend on C: the partials form 64 blocks of consecutive ones, summed in ascending order, and the
+// blocks of a wave meet as a binary tree - in the thread, which holds C / 8 of them, and between the lanes -, the waves in ascending
+// order in LDS.  So it is with the squares: a tree over columns whose nodes over 8 or 32 are published.
+// (With a task per 4-wave unit and 19 words per thread in flight the five-row forward took 30 us longer.)
+constexpr int DF_RBLOCKS = 64;
+constexpr int DF_RW = 3;                  // partials of a block in flight
+template <int C>
 __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t tag, int layer, const u64* part2, uint32_t tag2, const u64* h_in,
                                                 u64* h_out, u64* hg_out, u64* sq_out, const float* gain_next, int shift,
                                                 uint32_t* lds, int* sdead, int slot) {
+  constexpr int TB = C / 8;                                // blocks of a thread
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int NW = gridDim.x;
-  const int M = a.rows.M, d = a.d, np = d >> 5, nW = a.ffn >> 5, PR = (int)(a.st_h / a.d);
+  const int M = a.rows.M, d = a.d, np = d / C, nW = a.ffn >> 5;
   const int tasks = M * np, rounds = (tasks + NW - 1) / NW;
   const int witem = df_item_of_unit(blockIdx.x, shift >> 1, NW);     // a task has the whole workgroup
-  float* rs = (float*)(lds + DF_AW + DF_SQ_WORDS);                     // [16 groups][32]
-  const int c = tid & 31, grp = tid >> 5;
-  const int per = (nW + DF_RG - 1) / DF_RG;
+  float* rs = (float*)(lds + DF_AW + DF_SQ_WORDS);                     // [8 waves][C]
+  const int c = tid % C, b0 = tid / C * TB;                // column, first block
+  const int bs = (nW + DF_RBLOCKS - 1) / DF_RBLOCKS;
   uint32_t* err = a.bar + 64;
   bool bad = false;
   for (int rd = 0; rd < rounds; ++rd) {
     const int task = rd * NW + witem;
     const bool valid = task < tasks;
     const int m = valid ? task / np : 0, p = valid ? task - m * np : 0;
-    const int w0 = grp * per, cnt = valid ? max(0, min(per, nW - w0)) : 0;
-    const u64* src = part2 + ((size_t)w0 * PR + m) * d + 32 * p + c;
-    const size_t wstride = (size_t)PR * d;
-    float sum = 0.f;
-    u64 hw = (u64)tag << 32;
-    const bool want_h = valid && grp == 0;
-    const float gain = want_h ? gain_next[32 * p + c] : 0.f;
-    for (int b0 = 0; b0 < cnt || (b0 == 0 && want_h); b0 += DF_RW) {
-      u64 v[DF_RW];
+    int w0[TB], cnt[TB];                                   // first partial and partials of the blocks
 #pragma unroll
-      for (int i = 0; i < DF_RW; ++i) v[i] = (b0 + i < cnt) ? ld_word(src + (size_t)(b0 + i) * wstride) : ((u64)tag2 << 32);
-      if (b0 == 0 && want_h) hw = ld_word(h_in + (size_t)m * d + 32 * p + c);
+    for (int t = 0; t < TB; ++t) {
+      w0[t] = (b0 + t) * nW / DF_RBLOCKS;
+      cnt[t] = valid ? (b0 + t + 1) * nW / DF_RBLOCKS - w0[t] : 0;
+    }
+    const u64* src = part2 + (size_t)(m * (d >> 5) + C * p / 32) * nW * 32 + C * p % 32 + c;
+    constexpr int wstride = 32;
+    float s[TB];
+#pragma unroll
+    for (int t = 0; t < TB; ++t) s[t] = 0.f;
+    u64 hw = (u64)tag << 32;
+    const bool want_h = valid && tid < C;
+    const float gain = want_h ? gain_next[C * p + c] : 0.f;
+    for (int k0 = 0; k0 < bs; k0 += DF_RW) {
+      u64 v[TB][DF_RW];
+#pragma unroll
+      for (int t = 0; t < TB; ++t)
+#pragma unroll
+        for (int i = 0; i < DF_RW; ++i) v[t][i] = (k0 + i < cnt[t]) ? ld_word(src + (w0[t] + k0 + i) * wstride) : ((u64)tag2 << 32);
+      if (k0 == 0 && want_h) hw = ld_word(h_in + (size_t)m * d + C * p + c);
       long spins = 0;
       for (;;) {
         bool all = (uint32_t)(hw >> 32) == tag;
 #pragma unroll
-        for (int i = 0; i < DF_RW; ++i) all = all && ((uint32_t)(v[i] >> 32) == tag2);
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+          for (int i = 0; i < DF_RW; ++i) all = all && ((uint32_t)(v[t][i] >> 32) == tag2);
         if (all) break;
         // a workgroup that comes here from its own MLP item is not early: no hint for it
         if (spins == 0 && (int)blockIdx.x >= a.g_mlp) df_wait_hint(a.hg + (size_t)(2 * layer + 1) * a.st_h, tag, err);
@@ -673,30 +732,37 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t t
         }
         __builtin_amdgcn_s_sleep(1);
 #pragma unroll
-        for (int i = 0; i < DF_RW; ++i)
-          if ((uint32_t)(v[i] >> 32) != tag2) v[i] = ld_word(src + (size_t)(b0 + i) * wstride);
-        if ((uint32_t)(hw >> 32) != tag) hw = ld_word(h_in + (size_t)m * d + 32 * p + c);
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+          for (int i = 0; i < DF_RW; ++i)
+            if ((uint32_t)(v[t][i] >> 32) != tag2) v[t][i] = ld_word(src + (w0[t] + k0 + i) * wstride);
+        if ((uint32_t)(hw >> 32) != tag) hw = ld_word(h_in + (size_t)m * d + C * p + c);
       }
 #pragma unroll
-      for (int i = 0; i < DF_RW; ++i)
-        if (b0 + i < cnt) sum += __uint_as_float((uint32_t)v[i]);
+      for (int t = 0; t < TB; ++t)
+#pragma unroll
+        for (int i = 0; i < DF_RW; ++i)
+          if (k0 + i < cnt[t]) s[t] += __uint_as_float((uint32_t)v[t][i]);
     }
-    rs[grp * 32 + c] = sum;
+    float sum = TB == 1 ? s[0] : (s[0] + s[1 % TB]) + (s[2 % TB] + s[3 % TB]);
+#pragma unroll
+    for (int o = C; o < WAVE; o <<= 1) sum += __shfl_xor(sum, o, WAVE);
+    if ((tid & 63) < C) rs[(tid >> 6) * C + c] = sum;
     if (bad) *sdead = 1;
     __syncthreads();
     if (*sdead) return true;
     if (rd == 0) DF_STAMP(slot);
-    if (valid && tid < 32) {
-      float v = rs[c];
+    if (want_h) {
+      float r[8];
 #pragma unroll
-      for (int gq = 1; gq < DF_RG; ++gq) v += rs[gq * 32 + c];
-      v += __uint_as_float((uint32_t)hw);
-      const size_t o = (size_t)m * d + 32 * p + c;
+      for (int w = 0; w < 8; ++w) r[w] = rs[w * C + c];
+      const float v = (((((((r[0] + r[1]) + r[2]) + r[3]) + r[4]) + r[5]) + r[6]) + r[7]) + __uint_as_float((uint32_t)hw);
+      const size_t o = (size_t)m * d + C * p + c;
       st_wordf(h_out + o, v, tag);
       st_word(hg_out + o, split_payload(v * gain), tag);
       float q2 = v * v;
 #pragma unroll
-      for (int off = 16; off > 0; off >>= 1) q2 += __shfl_xor(q2, off, 32);
+      for (int off = 1; off < C; off <<= 1) q2 += __shfl_xor(q2, off, 32);
       if (c == 0) st_wordf(sq_out + (size_t)m * np + p, q2, tag);
     }
     if (rd == 0) DF_STAMP(slot + 1);
@@ -707,6 +773,7 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t t
 
 // ------------------------------------------------------------------------------------------------ phase 0
 // Rows and embedding.  Item = row.
+template <int C>
 __device__ __forceinline__ void df_embed_phase(const DArgs& a, const uint32_t tag) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), usel = wave >> 2, ut = tid & 255;
   const int unit = blockIdx.x * 2 + usel, NU = gridDim.x * 2;
@@ -738,8 +805,8 @@ __device__ __forceinline__ void df_embed_phase(const DArgs& a, const uint32_t ta
       st_word(a.hg + (size_t)m * d + c, split_payload(v * gain[c]), tag);
       float sq = v * v;
 #pragma unroll
-      for (int o = 16; o > 0; o >>= 1) sq += __shfl_xor(sq, o, WAVE);
-      if ((ut & 31) == 0) st_wordf(a.sq + (size_t)m * (d >> 5) + p, sq, tag);
+      for (int o = 1; o < C; o <<= 1) sq += __shfl_xor(sq, o, WAVE);       // as df_reduce_phase leaves them
+      if ((ut & (C - 1)) == 0) st_wordf(a.sq + (size_t)m * (d / C) + c / C, sq, tag);
     }
   }
 }
@@ -1255,7 +1322,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
   };
   // which phase kinds this workgroup has a round-0 item in
   auto has = [&](int u, int shift, int items, int stride = 1) { return df_item_of_unit(u, shift, NU, stride) < items; };
-  const int n_red = a.rows.M * np;
+  const int n_red = a.rows.M * (a.d / df_red_cols<SB>());
   const int u0 = blockIdx.x * 2, u1 = u0 + 1;
   const bool g_q = has(u0, s_qkv, n_qkv, st) || has(u1, s_qkv, n_qkv, st) || st * n_qkv > NU,
              g_a = has(u0, s_att, n_att, 2),                  // (an attention item has the workgroup)
@@ -1281,7 +1348,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_fetch_or(a.bar + 64, DEV_ERR_TAGS, __ATOMIC_RELAXED, AG);
     return;
   }
-  df_embed_phase(a, tag);
+  df_embed_phase<df_red_cols<SB>()>(a, tag);
   if (g_q && threadIdx.x < a.rows.M) {                    // the QKV epilogue appends keys and values: block of each row's position
     u64 w = ld_word(a.rowblk + threadIdx.x);
     for (long spins = 0; (uint32_t)(w >> 32) != tag; w = ld_word(a.rowblk + threadIdx.x)) {
@@ -1322,7 +1389,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
       const DArgs& a = df_args();
       const size_t hi = (size_t)(2 * l + 1);
       const float* gain_next = l + 1 < L ? layer_ptrs(a, l + 1).ln1 : a.final_norm;
-      if (df_reduce_phase(a, tag, l, a.part2 + (size_t)(l & 1) * a.st_part2, df_tag2(tag, l), a.h + hi * a.st_h, a.h + (hi + 1) * a.st_h,
+      if (df_reduce_phase<df_red_cols<SB>()>(a, tag, l, a.part2 + (size_t)(l & 1) * a.st_part2, df_tag2(tag, l), a.h + hi * a.st_h, a.h + (hi + 1) * a.st_h,
                           a.hg + (hi + 1) * a.st_h, a.sq + (hi + 1) * a.st_sq, gain_next, s_red, lds, &sdead, s0 + 8)) return;
     }
   }

@@ -367,7 +367,7 @@ static size_t kv_layout(const ssd_model* m, int max_seqs, int max_rows, int n_bl
   unsigned long long* trace = cv.take<unsigned long long>(p_ok ? 256 * 512 : 0);
   // tagged words of the barrier-free forward: one block, zeroed at creation
   const size_t TR = PR;
-  const size_t w_h = (size_t)(2 * L + 1) * TR * c.d_model, w_sq = (size_t)(2 * L + 1) * TR * (c.d_model / 32);
+  const size_t w_h = (size_t)(2 * L + 1) * TR * c.d_model, w_sq = (size_t)(2 * L + 1) * TR * (c.d_model / 8);
   const size_t w_q = (size_t)L * TR * nqd, w_kvn = (size_t)L * TR * 2 * c.n_kv_heads * 64;
   const size_t w_attp = (size_t)L * TR * c.n_q_heads * NP * 96;
   const size_t w_part2 = (size_t)2 * (c.d_ffn / 32) * TR * c.d_model;
@@ -788,7 +788,7 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   const size_t PR = kv->p_rows;
   a.tw = kv->t_base; a.h = kv->t_h; a.hg = kv->t_hg; a.sq = kv->t_sq; a.q = kv->t_q; a.kvn = kv->t_kvn; a.attn = kv->t_attn;
   a.att_p = kv->t_att_p; a.logits = kv->logits;
-  a.st_h = PR * c.d_model; a.st_sq = PR * (c.d_model / 32); a.st_q = PR * nqd; a.st_kvn = PR * 2 * c.n_kv_heads * 64;
+  a.st_h = PR * c.d_model; a.st_sq = PR * (c.d_model / 8); a.st_q = PR * nqd; a.st_kvn = PR * 2 * c.n_kv_heads * 64;
   a.st_att_p = PR * c.n_q_heads * kv->NP * 96;
   a.rowblk = kv->t_rowblk;
   a.part2 = kv->t_part2; a.st_part2 = (size_t)(c.d_ffn / 32) * PR * c.d_model;
@@ -798,8 +798,12 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   ProfScope ps(PROF_PERSISTENT, st);
   kv->last_whole = kv->attn_whole && n_parts == 1;
   // words of one operand staging: the rows' operand words and their sums of squares; one flight holds 512 x SB
-  const int stage_words = M * (std::max(c.d_model, nqd) + c.d_model / 32);
-  const int sb = kv->df_sb ? kv->df_sb : stage_words <= 2 * PBLOCK ? 2 : stage_words <= 4 * PBLOCK ? 4 : stage_words <= 10 * PBLOCK ? 10 : 12;
+  auto holds = [&](int n) {                                // (n <= 4: sums of squares over 8 columns, see df_reduce_phase)
+    return M * (std::max(c.d_model, nqd) + c.d_model / (n <= 4 ? 8 : 32)) <= n * PBLOCK;
+  };
+  int sb = kv->df_sb ? kv->df_sb : holds(2) ? 2 : holds(4) ? 4 : holds(10) ? 10 : 12;
+  if (sb <= 4 && M * (c.d_model / 8) > DF_SQ_WORDS) sb = 10;
+  if (M > DF_PACK_ROWS) sb = 12;
 #define DF_LAUNCH(S) hipLaunchKernelGGL((k_forward_dataflow<S>), dim3(G), dim3(PBLOCK), 0, st, a)
   if (sb == 2) DF_LAUNCH(2); else if (sb == 4) DF_LAUNCH(4); else if (sb == 10) DF_LAUNCH(10); else DF_LAUNCH(12);
 #undef DF_LAUNCH
