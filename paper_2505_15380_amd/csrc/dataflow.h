@@ -18,7 +18,7 @@
 // keys / values are bf16 bits.
 //
 // A workgroup stages the operand rows it needs in LDS once (all its threads poll in parallel, SB words in flight
-// each: the kernel is instantiated for SB = 2, 4, 10, 12 and the host picks the smallest that holds the launch's rows
+// each: the kernel is instantiated for SB = 2, 4, 10, 16, 18 and the host picks the smallest that holds the launch's rows
 // in one flight) and feeds the matrix cores from LDS.  The weights of an item are requested at the entry of its phase, into
 // registers, before that wait: workgroups arrive at a phase before its operands do, so the wait hides the HBM latency.
 // The phases with few items (QKV, attention, output projection) run on workgroups of their own, beyond those that
@@ -45,8 +45,7 @@
 namespace ssd {
 
 typedef unsigned long long u64;
-constexpr int DF_B = 12;                  // tagged words a thread keeps in flight while it stages attention operands (and the
-                                          // largest choice for the GEMM operands, see SB below)
+constexpr int DF_B = 12;                  // tagged words a thread keeps in flight while it stages attention operands
 constexpr int DF_AW = 21504;              // LDS words of the operand staging area (84 KB)
 constexpr int DF_ATT_ROWS = 256;          // query rows of a sequence (rows x heads of a group): at most 16 tiles of 16
 constexpr int DF_NPF = 5;                 // attention parts merged per flight
@@ -215,40 +214,55 @@ struct DPhase {
   float* logits;          // PE_LOGITS
 };
 
+// Two consecutive words with one 16-byte agent-scope load; `off`: bytes from the descriptor's base.
+typedef __amdgpu_buffer_rsrc_t df_rsrc;
+__device__ __forceinline__ df_rsrc df_make_rsrc(const u64* base) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)0xFFFFFFE0u, 0x00027000);
+}
+__device__ __forceinline__ u32x4 ld_words2(df_rsrc r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 16 /* sc1 */); }
+
 // Operand words of rows [0, M) (K words each, the rows contiguous) -> As[row * (K + 4) + k], and the rows' sums of
-// squares [M][nsq] -> sqs.  Thread gt of gn; the whole group polls in parallel.  Two more words per thread (x0, x1:
-// offsets, or ~0) ride in the first flight and come back in xo0, xo1.  Word offsets are recomputed for a repeated
-// load instead of being kept in registers; with whole rows a word's offset is its index, and only the padded LDS
-// address needs the row (every slot of a flight costs its instructions whether it holds a word or not).
-template <int SB>
-__device__ __forceinline__ bool stage_operand(const DArgs& a, const u64* A, int K, const u64* sq, int nsq,
-                                              uint32_t* As, float* sqs, int gt, int gn, uint32_t x0, uint32_t x1,
-                                              uint32_t& xo0, uint32_t& xo1, const u64* hint, uint32_t hint_tag,
+// squares [M][nsq] -> sqs.  The whole workgroup polls in parallel, a pair of words per load: half the load instructions of
+// a word each (one row 400 -> 380 us a forward; nine rows, with the flights that hold them now, 760 -> 725).  Lanes without a
+// pair are masked out: a load costs the cycles of its return path even where all its lanes are out of range (five rows 513 ->
+// 543 us with such loads instead of the mask).  RES: two more words per thread (x0, x1: offsets in words, or ~0) ride in the
+// first flight and come back in xo0, xo1.  Offsets are recomputed for a repeated load instead of being kept in registers; with
+// whole rows a pair's offset is its index, and only the padded LDS address needs the row.
+template <int SB, bool RES>
+__device__ __forceinline__ bool stage_operand(const DArgs& a, const u64* A, int K, const u64* sq, int nsq, uint32_t* As, float* sqs, int tid,
+                                              uint32_t x0, uint32_t x1, uint32_t& xo0, uint32_t& xo1, const u64* hint, uint32_t hint_tag,
                                               const uint32_t tag) {
-  const int M = a.rows.M, kn = K, nA = M * kn, total = nA + (sq ? M * nsq : 0);
-  const uint32_t a_off = (uint32_t)(A - a.tw), s_off = sq ? (uint32_t)(sq - a.tw) : 0u;
-  const float rkn = 1.0f / (float)kn;
+  constexpr int SP = SB / 2;
+  const int M = a.rows.M, nA = M * K, nS = sq ? M * nsq : 0, pA = nA >> 1, total = pA + ((nS + 1) >> 1);      // (pairs)
+  const df_rsrc rs = df_make_rsrc(a.tw);
+  const uint32_t a_off = (uint32_t)(A - a.tw) * 8u, s_off = sq ? (uint32_t)(sq - a.tw) * 8u : 0u;
+  const float rkn = 2.0f / (float)K;
   uint32_t* err = a.bar + 64;
   bool ok = true;
-  for (int base = 0; base < total || base == 0; base += gn * SB) {
-    int g2 = gt;
+  for (int base = 0; base < total; base += PBLOCK * SP) {
+    int t2 = tid;
     auto off_of = [&](int u) -> uint32_t {
-      if (u >= SB) return base == 0 ? (u == SB ? x0 : x1) : 0xFFFFFFFFu;
-      const int idx = base + u * gn + g2;
-      if (idx < nA) return a_off + (uint32_t)idx;
-      return idx < total ? s_off + (uint32_t)(idx - nA) : 0xFFFFFFFFu;
+      const int i = base + u * PBLOCK + t2;
+      return i < pA ? a_off + (uint32_t)i * 16u : s_off + (uint32_t)(i - pA) * 16u;
     };
-    u64 v[SB + 2];
+    // (an odd last sum's neighbour is not this launch's)
+    auto there = [&](int u, const u32x4 v) {
+      const int i = base + u * PBLOCK + t2;
+      return i >= total || (v[1] == tag && (v[3] == tag || (i == total - 1 && (nS & 1))));
+    };
+    u32x4 v[SP];
+    u64 h0 = (u64)tag << 32, h1 = h0;
 #pragma unroll
-    for (int u = 0; u < SB + 2; ++u) {
-      const uint32_t o = off_of(u);
-      v[u] = o != 0xFFFFFFFFu ? ld_word(a.tw + o) : ((u64)tag << 32);
+    for (int u = 0; u < SP; ++u) v[u] = base + u * PBLOCK + tid < total ? ld_words2(rs, off_of(u)) : u32x4{0u, tag, 0u, tag};
+    if (RES && base == 0) {
+      if (x0 != 0xFFFFFFFFu) h0 = ld_word(a.tw + x0);
+      if (x1 != 0xFFFFFFFFu) h1 = ld_word(a.tw + x1);
     }
     long spins = 0;
     for (;;) {
-      bool all = true;
+      bool all = !RES || ((uint32_t)(h0 >> 32) == tag && (uint32_t)(h1 >> 32) == tag);
 #pragma unroll
-      for (int u = 0; u < SB + 2; ++u) all = all && ((uint32_t)(v[u] >> 32) == tag);
+      for (int u = 0; u < SP; ++u) all = all && there(u, v[u]);
       if (all) break;
       if (spins == 0 && hint) df_wait_hint(hint, hint_tag, err);       // far too early: wait cheaply for the phase before
       if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
@@ -257,22 +271,26 @@ __device__ __forceinline__ bool stage_operand(const DArgs& a, const u64* A, int 
         break;
       }
       __builtin_amdgcn_s_sleep(1);
-      asm volatile("" : "+v"(g2));                       // keeps the offsets out of registers across the wait
+      asm volatile("" : "+v"(t2) : : "memory");          // keeps the offsets out of registers across the wait; the words may have changed
 #pragma unroll
-      for (int u = 0; u < SB + 2; ++u)
-        if ((uint32_t)(v[u] >> 32) != tag) v[u] = ld_word(a.tw + off_of(u));
-    }
-#pragma unroll
-    for (int u = 0; u < SB; ++u) {
-      const int idx = base + u * gn + gt;
-      if (idx < nA) {
-        const int row = (int)(((float)idx + 0.5f) * rkn);
-        As[idx + 4 * row] = (uint32_t)v[u];
-      } else if (idx < total) {
-        sqs[idx - nA] = __uint_as_float((uint32_t)v[u]);
+      for (int u = 0; u < SP; ++u)
+        if (!there(u, v[u])) v[u] = ld_words2(rs, off_of(u));
+      if (RES) {
+        if ((uint32_t)(h0 >> 32) != tag) h0 = ld_word(a.tw + x0);
+        if ((uint32_t)(h1 >> 32) != tag) h1 = ld_word(a.tw + x1);
       }
     }
-    if (base == 0) { xo0 = (uint32_t)v[SB]; xo1 = (uint32_t)v[SB + 1]; }
+#pragma unroll
+    for (int u = 0; u < SP; ++u) {
+      const int i = base + u * PBLOCK + tid;
+      if (i < pA) {
+        const int row = (int)(((float)i + 0.5f) * rkn);
+        *(uint2*)(As + 2 * i + 4 * row) = make_uint2(v[u][0], v[u][2]);
+      } else if (i < total) {
+        *(uint2*)(sqs + 2 * (i - pA)) = make_uint2(v[u][0], v[u][2]);
+      }
+    }
+    if (RES && base == 0) { xo0 = (uint32_t)h0; xo1 = (uint32_t)h1; }
   }
   return ok;
 }
@@ -367,7 +385,7 @@ __device__ __forceinline__ void df_products(const uint32_t* As, int K, int M, in
 }
 // Rows that the products' PACK form takes; the instantiations for few words in flight use it.
 template <int SB>
-constexpr bool df_pack() { return SB <= 10; }
+constexpr bool df_pack() { return SB <= 16; }
 constexpr int DF_PACK_ROWS = 8;
 
 // One GEMM phase (QKV, output projection, head); the caller skips it for a workgroup none of whose units has an
@@ -429,7 +447,7 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
       hx1 = h_off + n1;
     }
     bool ok = true;
-    if (rd == 0) ok = stage_operand<SB>(a, ph.A, ph.K, ph.sq, ph.K / df_red_cols<SB>(), As, sqs, tid, PBLOCK, hx0, hx1, hv0, hv1, ph.hint, ph.hint_tag, tag);
+    if (rd == 0) ok = stage_operand<SB, EPI == PE_RESID>(a, ph.A, ph.K, ph.sq, ph.K / df_red_cols<SB>(), As, sqs, tid, hx0, hx1, hv0, hv1, ph.hint, ph.hint_tag, tag);
     if (!ok) *sdead = 1;
     __syncthreads();
     if (*sdead) return true;
@@ -585,7 +603,7 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
     if ((rd * NU + blockIdx.x * 2) < ph.items) df_prefetch_down(a, wdown, kt2, wd);
     uint32_t dummy0, dummy1;
     bool ok = true;
-    if (rd == 0) ok = stage_operand<SB>(a, ph.A, ph.K, ph.sq, KT, As, sqs, tid, PBLOCK, 0xFFFFFFFFu, 0xFFFFFFFFu, dummy0, dummy1, ph.hint, ph.hint_tag, tag);
+    if (rd == 0) ok = stage_operand<SB, false>(a, ph.A, ph.K, ph.sq, KT, As, sqs, tid, 0xFFFFFFFFu, 0xFFFFFFFFu, dummy0, dummy1, ph.hint, ph.hint_tag, tag);
     if (!ok) *sdead = 1;
     __syncthreads();
     if (*sdead) return true;

@@ -309,7 +309,7 @@ struct ssd_kv {
   int cus = 0;                     // compute units of the device
   // tagged workspace of the barrier-free forward (see dataflow.h); null when that kernel is not usable
   u64 *t_base = nullptr, *t_h, *t_hg, *t_sq, *t_q, *t_kvn, *t_attn, *t_att_p, *t_part2, *t_rowblk;
-  size_t t_words = 0;
+  size_t t_words = 0, t_attp_at = 0;     // words of it; words ahead of the attention's partials (GEMM operands are among them)
   bool dataflow = false;
   bool attn_whole = false;   // ssd_kv_last_forward_path tells launches whose attention is one part (4) from others (3) on this cache
   bool attn_mfma = true;     // per-operator path: matrix-core attention where it applies (SSD_ATTN=valu: the scalar kernel)
@@ -317,7 +317,7 @@ struct ssd_kv {
   bool capturing = false;          // a cycle is being captured on this cache: no synchronisation, no fallback kernels
   int last_path = 0;               // 1 per-operator launches, 2 barrier kernel, 3 barrier-free kernel, 4 the same with attention without parts
   bool last_whole = false;
-  int df_sb = 0;             // SSD_DF_FLIGHT=2|4|10|12: words in flight per thread of the operand staging (0: chosen per launch)
+  int df_sb = 0;             // SSD_DF_FLIGHT=2|4|10|16|18: words in flight per thread of the operand staging (0: chosen per launch)
   // host
   int32_t* mirror_host;
   std::vector<int> len_ub, npend_ub;
@@ -377,6 +377,7 @@ static size_t kv_layout(const ssd_model* m, int max_seqs, int max_rows, int n_bl
     u64* t = t_base;
     kv->t_base = t_base; kv->t_words = t_words;
     kv->t_h = t; t += w_h; kv->t_hg = t; t += w_h; kv->t_sq = t; t += w_sq; kv->t_q = t; t += w_q; kv->t_attn = t; t += w_q;
+    kv->t_attp_at = w_h * 2 + w_sq + w_q * 2 + w_kvn;
     kv->t_kvn = t; t += w_kvn; kv->t_att_p = t; t += w_attp; kv->t_part2 = t; t += w_part2;
     kv->t_rowblk = t;
 
@@ -463,7 +464,7 @@ extern "C" int ssd_kv_create(const ssd_model* m, int max_seqs, int max_rows, int
   }
   // The barrier-free forward additionally needs its word offsets to fit 32 bits; its words start untagged (zero).
   kv->dataflow = false;
-  if (e == hipSuccess && kv->persistent_wgs > 0 && kv->t_words > 0 && kv->t_words < ((size_t)1 << 32)) {
+  if (e == hipSuccess && kv->persistent_wgs > 0 && kv->t_words > 0 && kv->t_words < ((size_t)1 << 32) && kv->t_attp_at < ((size_t)1 << 28)) {
     e = hipMemsetAsync(kv->t_base, 0, kv->t_words * sizeof(u64), (hipStream_t)stream);
     const char* env = getenv("SSD_FORWARD");
     kv->dataflow = !(env && strcmp(env, "barrier") == 0);
@@ -475,7 +476,8 @@ extern "C" int ssd_kv_create(const ssd_model* m, int max_seqs, int max_rows, int
     kv->attn_whole = env ? (env[0] == '1' || (env[0] == '2' && pending_cap == 2)) : (pending_cap == 2);
     env = getenv("SSD_DF_FLIGHT");
     kv->df_sb = env ? atoi(env) : 0;
-    if (kv->df_sb != 2 && kv->df_sb != 4 && kv->df_sb != 10 && kv->df_sb != 12) kv->df_sb = 0;
+    if (kv->df_sb == 12) kv->df_sb = 18;
+    if (kv->df_sb != 2 && kv->df_sb != 4 && kv->df_sb != 10 && kv->df_sb != 16 && kv->df_sb != 18) kv->df_sb = 0;
   }
   if (e != hipSuccess) { (void)hipHostFree(kv->mirror_host); delete kv; return fail(SSD_EHIP, "k_kv_init: %s", hipGetErrorString(e)); }
   *out = kv;
@@ -801,11 +803,11 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   auto holds = [&](int n) {                                // (n <= 4: sums of squares over 8 columns, see df_reduce_phase)
     return M * (std::max(c.d_model, nqd) + c.d_model / (n <= 4 ? 8 : 32)) <= n * PBLOCK;
   };
-  int sb = kv->df_sb ? kv->df_sb : holds(2) ? 2 : holds(4) ? 4 : holds(10) ? 10 : 12;
+  int sb = kv->df_sb ? kv->df_sb : holds(2) ? 2 : holds(4) ? 4 : holds(10) ? 10 : holds(16) ? 16 : 18;
   if (sb <= 4 && M * (c.d_model / 8) > DF_SQ_WORDS) sb = 10;
-  if (M > DF_PACK_ROWS) sb = 12;
+  if (M > DF_PACK_ROWS) sb = 18;
 #define DF_LAUNCH(S) hipLaunchKernelGGL((k_forward_dataflow<S>), dim3(G), dim3(PBLOCK), 0, st, a)
-  if (sb == 2) DF_LAUNCH(2); else if (sb == 4) DF_LAUNCH(4); else if (sb == 10) DF_LAUNCH(10); else DF_LAUNCH(12);
+  if (sb == 2) DF_LAUNCH(2); else if (sb == 4) DF_LAUNCH(4); else if (sb == 10) DF_LAUNCH(10); else if (sb == 16) DF_LAUNCH(16); else DF_LAUNCH(18);
 #undef DF_LAUNCH
   LAUNCH_CHECK();
   return SSD_OK;
