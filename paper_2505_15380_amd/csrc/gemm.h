@@ -136,7 +136,8 @@ __global__ void __launch_bounds__(GF_MAX_WAVES * 64) k_gemm_f32(GemmArgs g) {
   int pos = 0, active = 0, blk = -1;
   float2 cs = {0.f, 0.f};
   if (EPI == EPI_QKV && mine) { pos = g.rows.pos[row]; active = g.rows.active[row]; }
-  for (int k = kb; k < ke; k += U) {
+  int k = kb;
+  do {                                                     // (also by a wave without steps, K / 16 < nw: its threads have rows to request)
     f32x4 a[U], x0[U], x1[U], gn[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -159,7 +160,8 @@ __global__ void __launch_bounds__(GF_MAX_WAVES * 64) k_gemm_f32(GemmArgs g) {
         acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x, x1[u][j], acc1, 0, 0, 0);
       }
     }
-  }
+    k += U;
+  } while (k < ke);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     red[wave][0][(4 * kg + r) * 16 + li] = acc0[r];

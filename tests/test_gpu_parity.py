@@ -172,6 +172,28 @@ def test_forward_at_the_edges_of_tiles(dtype, hd, groups, n_prefix, B, K):
     pair.check_free_stack()
 
 
+@pytest.mark.parametrize("dtype,d,hd,ffn,K", [
+    ("fp32", 32, 32, 32, 8),         # two k-steps for four waves; nine rows
+    ("fp32", 32, 64, 96, 15),
+    ("fp32", 64, 128, 32, 8),
+    ("fp32", 96, 32, 160, 8)])
+def test_narrowest_models(dtype, d, hd, ffn, K):
+    """The smallest widths that a model may have: a prompt in one forward of 25 rows and two verifications of 9 or 16 rows
+    against the oracle."""
+    from tests.parity import Pair, verify_parity_step
+    shape = dict(n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=hd, d_ffn=ffn, vocab=41, n_embed=43, dtype=dtype,
+                 qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
+    atol = 2e-5 if dtype == "fp32" else 2e-2
+    pair = Pair(None, 81, 26 + 2 * (K + 1) + 16, max_rows=25, shape=shape)
+    rng = np.random.default_rng(82)
+    pair.prefill(0, rng.integers(0, 43, 26))
+    pair.check_state(0, atol)
+    for s in range(2):
+        verify_parity_step(pair, dict(beta=0.3, seed=83), K, s, rng, atol, atol)
+        pair.check_state(0, atol)
+    pair.check_free_stack()
+
+
 # ---- the barrier-free persistent forward (bf16 shapes, <= 16 rows) ------------------------------------------------
 @pytest.mark.gpu
 @pytest.mark.parametrize("n_prefix,K", [(250, 4), (254, 12), (600, 4), (1290, 7)])
