@@ -557,7 +557,7 @@ __device__ __forceinline__ void df_prefetch_down(const DArgs& a, const void* wdo
   const int ntiles = a.d >> 4, KTd = a.ffn >> 5;
 #pragma unroll
   for (int i = 0; i < DF_DN; ++i) {
-    const int nt = (wave + 8 * i < ntiles) ? wave + 8 * i : wave;
+    const int nt = min(wave + 8 * i, ntiles - 1);          // (a wave may have fewer tiles than DF_DN, below 128 columns none)
     wd.b[i] = __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + down_lane(lane));
   }
 }

@@ -176,10 +176,16 @@ def test_forward_at_the_edges_of_tiles(dtype, hd, groups, n_prefix, B, K):
     ("fp32", 32, 32, 32, 8),         # two k-steps for four waves; nine rows
     ("fp32", 32, 64, 96, 15),
     ("fp32", 64, 128, 32, 8),
-    ("fp32", 96, 32, 160, 8)])
+    ("fp32", 96, 32, 160, 8),
+    ("bf16", 32, 64, 32, 8),         # one pair of output tiles for the eight waves of the barrier-free kernel
+    ("bf16", 32, 64, 64, 15),
+    ("bf16", 96, 64, 1056, 8),
+    ("bf16", 64, 64, 32, 3),
+    ("bf16", 32, 128, 32, 8),        # one launch per operator
+    ("bf16", 96, 32, 160, 8)])
 def test_narrowest_models(dtype, d, hd, ffn, K):
-    """The smallest widths that a model may have: a prompt in one forward of 25 rows and two verifications of 9 or 16 rows
-    against the oracle."""
+    """The smallest widths that a model may have: a prompt in one forward of 25 rows and two verifications of 4, 9 or 16
+    rows against the oracle."""
     from tests.parity import Pair, verify_parity_step
     shape = dict(n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=hd, d_ffn=ffn, vocab=41, n_embed=43, dtype=dtype,
                  qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
