@@ -22,6 +22,10 @@
  *   - Return value: SSD_OK (0) or a negative error code; ssd_last_error() gives a message for the last
  *     failure on the calling thread.  Arguments are validated on the host before anything is launched;
  *     nothing throws or aborts across this boundary.
+ *   - Reproducibility: the same call on the same state gives the same bits.  Beyond that, of a row that the barrier-free
+ *     forward computes (ssd_kv_last_forward_path 3 or 4), the bits depend on its sequence's tokens, its position and the
+ *     cached keys and values alone: it has them decoded alone (K = 0), among the K + 1 rows of a verification, in a captured
+ *     cycle and beside any other sequence.
  *   - Sequence state (length, pending token(s), block table) lives on the device so that cycles can be
  *     chained without a host round trip.  The host keeps an upper bound of every length and synchronises
  *     the stream only when that bound would exhaust the pool, or when asked for the state.
@@ -245,9 +249,9 @@ int ssd_profile_end(double* total_ms, int* launches);
  * 2 one persistent kernel with grid barriers between phases, 3 one persistent kernel whose phases are ordered by
  * tagged data words (the default for bf16 storage and at most 16 rows; the environment variable
  * SSD_FORWARD=barrier, read at ssd_kv_create, selects 2 instead; 2 is also what runs when a launch exceeds the
- * limits of 3), 4 the same kernel where no part of a prefix can meet another one's: at most 1520 cached positions on a cache
- * created with pending_cap 2 (SSD_ATTN_WHOLE=1: on every cache, 0: on none; the attention of such prefixes is one
- * workgroup per row tile in 3 as well, longer ones go in parts of 1024 keys). */
+ * limits of 3), 4 the same kernel where no part of a prefix can meet another one's: at most 1520 cached positions, by the
+ * host's bound of the lengths, on a cache created with pending_cap 2 (SSD_ATTN_WHOLE=1: on every cache, 0: on none).  The
+ * kernel is the same and so are the results: a row attends in one part up to 1536 positions and in parts of 1024 beyond. */
 int ssd_kv_last_forward_path(const ssd_kv* kv);
 
 /* Phase trace of the persistent forward kernels, recorded only by builds with -DSSD_TRACE (otherwise SSD_ENOSUP

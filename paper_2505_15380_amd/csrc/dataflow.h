@@ -91,7 +91,7 @@ struct DArgs {
   u64* rowblk;            // [16] per row: the pool block that takes the row's new key and value (-1: none), from the reservation
   float* logits;
   size_t st_h, st_sq, st_q, st_kvn, st_att_p;   // strides in words
-  int NP, n_parts, part_chunks;
+  int NP, n_parts;        // parts that the workspace has room for, and that this launch has workgroups for
   int g_mlp;              // workgroups [0, g_mlp) take the MLP items; the phases with few items start on the workgroups after them
   int small_stride;       // 2: a small-phase item has a workgroup to itself; 1: two items per workgroup
   uint32_t* bar;          // [64] error flag (sticky until the host reads it); [0], [32] belong to the kernel with grid barriers
@@ -892,12 +892,21 @@ __device__ __forceinline__ void df_reserve_blocks(const DArgs& a, const int tag_
 
 // ------------------------------------------------------------------------------------------------ attention
 // Item = (sequence, kv head, part of the keys, tile of 16 query rows) on a workgroup; the query rows of a sequence are its R
-// rows times the G query heads of the group, row index qr = j * G + head-in-group.  A part is `part_chunks` (at most
-// DF_PART_CHUNKS) chunks of 64 keys, cut at absolute positions; wave w walks its chunks w, w + 8, w + 16 with a running (max,
-// sum, weighted values) per row and the eight waves meet once in LDS.  Up to DF_PART_CHUNKS chunks are one part, whose result
-// goes out as operand words; the partials of several are merged by their workgroups (see the end of df_attn_phase).  Scores
-// are kept in the base-2 domain (scale * log2 e folded in), so that the exponentials are single instructions.
-constexpr int DF_PART_CHUNKS = 24;
+// rows times the G query heads of the group, row index qr = j * G + head-in-group.  Wave w walks chunks w, w + 8, w + 16 (of 64
+// keys) of its part with a running (max, sum, weighted values) per row and the eight waves meet once in LDS.  Scores are kept
+// in the base-2 domain (scale * log2 e folded in), so that the exponentials are single instructions.
+//
+// How a row's keys are cut follows from its position alone, so that it has the same bits alone, in a verification, in a captured
+// cycle and beside any other sequence: a row below DF_ONE_PART attends in one part of up to DF_ONE_CHUNKS chunks, whose result goes
+// out as operand words; any other in parts of DF_PART_CHUNKS chunks cut at absolute positions, which their workgroups merge (see the
+// end of df_attn_phase).  Merging costs a hand-over and about 2.5 us per layer, a third round of chunks 1.2: hence one part as far
+// as three rounds reach, and two rounds beyond.  The host only provides the workgroups, from its bound of the lengths: those
+// without keys have nothing to do.  Where rows of one sequence lie on both sides of the line, part 0 walks its third round too,
+// masked for the rows beyond (their maximum, sum and values keep their bits: factors of 1, terms of 0).
+constexpr int DF_ONE_CHUNKS = 24, DF_ONE_PART = 64 * DF_ONE_CHUNKS, DF_PART_CHUNKS = 16;
+__host__ __device__ constexpr int df_parts(int positions) {     // parts of a row that attends to this many positions
+  return positions <= DF_ONE_PART ? 1 : (positions + 64 * DF_PART_CHUNKS - 1) / (64 * DF_PART_CHUNKS);
+}
 struct DAttItem {
   int valid, b, kvh, part, rt, len, nact, off, pos_last;
   int c0, nch, nparts_b;                                 // first chunk and chunks of the part, parts of the sequence
@@ -921,24 +930,24 @@ __device__ __forceinline__ DAttItem df_att_item(const DArgs& a, int item, int nt
     it.part = t / a.nkv;
   }
   const int seq = a.rows.seq0 + it.b;
-  it.c0 = it.part * a.part_chunks;
+  it.c0 = it.part * DF_PART_CHUNKS;
   // (only by the workgroups that have an item: a few hundred asking for the same words queue up at one channel)
   const int len_v = it.valid ? ld_state(a.kv.len + seq) : 0;
   const int npend_v = (it.valid && a.pcap) ? ld_state(a.kv.n_pend + seq) : 0;
   const int i = threadIdx.x, bi = it.c0 * 4 + i;
   int bid = -1;
-  if (i < DF_PART_CHUNKS * 4 && it.valid && bi < a.kv.mbps) bid = ld_state(a.kv.table + seq * a.kv.mbps + bi);
+  if (i < DF_ONE_CHUNKS * 4 && it.valid && bi < a.kv.mbps) bid = ld_state(a.kv.table + seq * a.kv.mbps + bi);
   it.len = __builtin_amdgcn_readfirstlane(len_v);
   const int npend = __builtin_amdgcn_readfirstlane(npend_v);
   it.off = a.pcap - npend;
   it.nact = a.rows.R - it.off;
   it.pos_last = it.len + it.nact - 1;
   const int nch = it.pos_last / 64 + 1;
-  it.nch = min(a.part_chunks, nch - it.c0);
-  it.nparts_b = (nch + a.part_chunks - 1) / a.part_chunks;
-  it.valid = it.valid && it.nch > 0;
+  it.nparts_b = df_parts(it.pos_last + 1);
+  it.nch = min(it.part == 0 && it.len < DF_ONE_PART ? DF_ONE_CHUNKS : DF_PART_CHUNKS, nch - it.c0);     // (a row stands at `len`)
+  it.valid = it.valid && it.part < it.nparts_b;
   // block ids of the part's positions (masked positions may read any block)
-  if (i < DF_PART_CHUNKS * 4) sblk[i] = (bid < 0 || bid >= a.kv.n_blocks || bi * 16 > it.pos_last) ? 0 : bid;
+  if (i < DF_ONE_CHUNKS * 4) sblk[i] = (bid < 0 || bid >= a.kv.n_blocks || bi * 16 > it.pos_last) ? 0 : bid;
   return it;
 }
 
@@ -1193,7 +1202,8 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
         const int kbase = 64 * (it.c0 + wave + 8 * j);
         if (fresh(j)) df_patch_k(kf[j], kbase, it.len, it.nact, Kn, lane);
         f32x4 s[4];
-        df_weights(kf[j], qh, ql, kbase, qpos, fresh(j), sc2, lane, rs, s);
+        const int qp = j < 2 || qpos < DF_ONE_PART ? qpos : -1;            // the third round is not for rows in several parts
+        df_weights(kf[j], qh, ql, kbase, qp, fresh(j) || (j == 2 && it.nparts_b > 1), sc2, lane, rs, s);
         if (j == 2 || fresh(j)) df_v_from_lds(v2, kbase, it.len, it.nact, Vn, lane, vf[j]);
         df_values(vf[j], s, rs);
       }
@@ -1206,7 +1216,7 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   DF_STAMP2(4);
   if (const int row = tid >> 5, d0 = (tid & 31) * 2; it.valid && row < nrt) {
     const int qr = r0 + row, j = qr / G, gq = qr - j * G, m = it.b * R + j, head = it.kvh * G + gq;
-    const int np_row = rowpos[j] / (64 * a.part_chunks) + 1;                 // parts that hold keys of the row
+    const int np_row = df_parts(rowpos[j] + 1);                              // parts that hold keys of the row
     if (it.part < np_row) {
       float mx, l, o[2];
       df_merge_row(MO, ML, row, d0, mx, l, o);
@@ -1227,7 +1237,7 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
     const int qr = r0 + first + row * P;
     if (tid < 256 && first + row * P < nrt) {
       const int j = qr / G, gq = qr - j * G, m = it.b * R + j, head = it.kvh * G + gq;
-      const int np_row = rowpos[j] / (64 * a.part_chunks) + 1;
+      const int np_row = df_parts(rowpos[j] + 1);
       if (np_row > 1) {
         const uint32_t p_off = (uint32_t)(att_p - a.tw) + (uint32_t)(((m * a.nq + head) * a.NP) * 96 + ch * 6);
         float mx = -INFINITY, l = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1351,7 +1361,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
   df_reserve_blocks(a, tag_v);
   // What the launch needs of the cache state (none of it changes during the launch): the waves' attention items, and
   // per row its position and whether it is active.
-  __shared__ int sblk[DF_PART_CHUNKS * 4];
+  __shared__ int sblk[DF_ONE_CHUNKS * 4];
   const DAttItem ait = df_att_item(a, df_item_of_unit(u0, s_att, NU, 2), ntile, sblk);
   if ((g_q || g_a) && threadIdx.x < a.rows.M) {           // the QKV epilogue and the attention masks use them
     const int m = threadIdx.x, brel = m / a.rows.R, j = m - brel * a.rows.R, seq = a.rows.seq0 + brel;

@@ -760,11 +760,9 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   const int nqd = c.n_q_heads * c.head_dim, grp = c.n_q_heads / c.n_kv_heads;
   int max_len = 0;
   for (int s = rows.seq0; s < rows.seq0 + B; ++s) max_len = std::max(max_len, kv->len_ub[s]);
-  // Parts of the attention: one up to DF_PART_CHUNKS chunks, else parts of 16, decided from the host's bound of the cached lengths
-  // alone, so that every forward from one cache state sums a row in the same order whatever its row count.  (Merging costs a
-  // hand-over and about 2.5 us per layer, a further round of a part's eight waves 1.2.)
-  const int part_chunks = cdiv(max_len + 16, 64) <= DF_PART_CHUNKS ? DF_PART_CHUNKS : 16;
-  const int n_parts = cdiv(max_len + rows.R, 64 * part_chunks);
+  // Workgroups for the attention's parts: as many as the host's bound of the lengths allows for (the cut of a row's keys follows
+  // from its position, see dataflow.h).
+  const int n_parts = df_parts(max_len + rows.R);
   // Workgroups [0, g_mlp) take the MLP items (two 16-column items each); the phases with few items (QKV, attention,
   // output projection) get workgroups of their own after them, as far as the device has compute units.
   const int g_mlp = std::min(kv->persistent_wgs, cdiv(c.d_ffn / 16, 2));
@@ -794,11 +792,11 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   a.st_att_p = PR * c.n_q_heads * kv->NP * 96;
   a.rowblk = kv->t_rowblk;
   a.part2 = kv->t_part2; a.st_part2 = (size_t)(c.d_ffn / 32) * PR * c.d_model;
-  a.NP = kv->NP; a.n_parts = n_parts; a.part_chunks = part_chunks; a.g_mlp = g_mlp; a.small_stride = small_stride;
+  a.NP = kv->NP; a.n_parts = n_parts; a.g_mlp = g_mlp; a.small_stride = small_stride;
   a.bar = kv->bar;
   a.trace = kv->trace_on ? kv->trace : nullptr;
   ProfScope ps(PROF_PERSISTENT, st);
-  kv->last_whole = kv->attn_whole && n_parts == 1;
+  kv->last_whole = kv->attn_whole && max_len + 16 <= DF_ONE_PART;      // (reported only)
   // words of one operand staging: the rows' operand words and their sums of squares; one flight holds 512 x SB
   auto holds = [&](int n) {                                // (n <= 4: sums of squares over 8 columns, see df_reduce_phase)
     return M * (std::max(c.d_model, nqd) + c.d_model / (n <= 4 ? 8 : 32)) <= n * PBLOCK;

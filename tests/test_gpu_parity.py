@@ -202,10 +202,11 @@ def test_narrowest_models(dtype, d, hd, ffn, K):
 
 # ---- the barrier-free persistent forward (bf16 shapes, <= 16 rows) ------------------------------------------------
 @pytest.mark.gpu
-@pytest.mark.parametrize("n_prefix,K", [(250, 4), (254, 12), (600, 4), (1290, 7)])
+@pytest.mark.parametrize("n_prefix,K", [(250, 4), (254, 12), (600, 4), (1290, 7), (1532, 7)])
 def test_mini_bf16_long_prefix_parts_and_boundaries(n_prefix, K):
-    """Prefix lengths whose new positions cross a 64-key chunk or a 256-key part, several parts, and more parts than
-    one merge flight takes (1290 keys: 6 parts), against the oracle; the barrier-free kernel must be the one that ran."""
+    """Prefix lengths whose new positions cross a 64-key chunk, one, two and three rounds of chunks per wave, and rows on both
+    sides of the 1536 positions up to which a row attends in one part, against the oracle; the barrier-free kernel must be the
+    one that ran."""
     from tests.parity import run_verify_parity
     r = run_verify_parity("mini", steps=3, K=K, beta=0.3, atol_logits=2e-2, atol_probs=2e-2, n_prefix=n_prefix)
     assert r["dlogits"] < 2e-2
