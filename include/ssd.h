@@ -26,6 +26,9 @@
  *     forward computes (ssd_kv_last_forward_path 3 or 4), the bits depend on its sequence's tokens, its position and the
  *     cached keys and values alone: it has them decoded alone (K = 0), among the K + 1 rows of a verification, in a captured
  *     cycle and beside any other sequence.
+ *     Of a row of a bf16 forward with one launch per operator (path 1), they depend on the launch's shape (n_seqs and K, or
+ *     a prompt's rows per launch) as well, since it decides how the products are cut, but not on the other sequences' tokens
+ *     or lengths.  The paths differ from one another by the rounding of fp32 sums in another order.
  *   - Sequence state (length, pending token(s), block table) lives on the device so that cycles can be
  *     chained without a host round trip.  The host keeps an upper bound of every length and synchronises
  *     the stream only when that bound would exhaust the pool, or when asked for the state.

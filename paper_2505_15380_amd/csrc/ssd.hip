@@ -670,14 +670,20 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
   return p.n_slices;
 }
 
-// Matrix-core attention: parts so that a launch has about a workgroup per CU and a key group at least one chunk; one part,
-// and no merge kernel, where the tiles alone fill half the device or the keys are few.
+// Matrix-core attention: parts so that a launch has about a workgroup per CU and a key group at least one chunk; one part, and no
+// merge kernel, where the tiles alone fill half the device or the keys are few.  `plan_chunks`: the chunks of a sequence that the
+// parts are cut for.  A prompt's launch gives its own (the host knows them: they follow from the call).  Any other gives
+// ATT_PLAN_CHUNKS, so that the cut, and with it the bits of a row, depends on the launch's shape and not on the lengths of
+// other sequences or on the host's bound of its own.  64 (4096 positions) was as fast as cutting for the longest sequence of the
+// launch on every batch measured (16 x 7 rows at 256 to 4096 positions 2521 us a cycle either way, 64 x 8 at 128 to 1024 3536,
+// 8 x 9 of the 1.5B shape 3850); 48, 32 and 16 were up to 2, 5 and 8 % slower.
+constexpr int ATT_PLAN_CHUNKS = 64;
 template <int HD>
-static int launch_attn_mfma(AttnArgs a, int nchunks, int nkv, int B, int M, int cus, hipStream_t st) {
+static int launch_attn_mfma(AttnArgs a, int nchunks, int plan_chunks, int nkv, int B, int M, int cus, hipStream_t st) {
   constexpr int wk = ATT_WAVES / ATT_TILES;
   const int n_tg = cdiv(cdiv(a.rows.R * (a.nq / nkv), 16), ATT_TILES);
-  const int want = std::min(std::max(1, cus / (n_tg * nkv * B)), cdiv(nchunks, wk));
-  const int part_chunks = cdiv(cdiv(nchunks, want), wk) * wk;
+  const int want = std::min(std::max(1, cus / (n_tg * nkv * B)), cdiv(plan_chunks, wk));
+  const int part_chunks = cdiv(cdiv(plan_chunks, want), wk) * wk;
   a.part_keys = part_chunks * 64;
   a.nparts = cdiv(nchunks, part_chunks);
   constexpr int LDS = wk * 2 * 2 * HD * 128;              // two buffers of 64 keys and 64 values per key group
@@ -694,9 +700,9 @@ static int launch_attn_mfma(AttnArgs a, int nchunks, int nkv, int B, int M, int 
 }
 
 template <typename DT, int HD>
-static int launch_attn(AttnArgs a, int nchunks, int nkv, int B, int M, bool mfma, int cus, hipStream_t st) {
+static int launch_attn(AttnArgs a, int nchunks, int plan_chunks, int nkv, int B, int M, bool mfma, int cus, hipStream_t st) {
   if constexpr (std::is_same<DT, BF16>::value && (HD == 64 || HD == 128)) {
-    if (mfma && a.kv.bt == 16) return launch_attn_mfma<HD>(a, nchunks, nkv, B, M, cus, st);
+    if (mfma && a.kv.bt == 16) return launch_attn_mfma<HD>(a, nchunks, plan_chunks, nkv, B, M, cus, st);
   }
   if constexpr (std::is_same<DT, F32>::value) {
     // a tile of keys is a block; a few long sequences give it too few workgroups for its walk
@@ -851,7 +857,7 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
 
   int max_len = 0;
   for (int s = seq0; s < seq0 + B; ++s) max_len = std::max(max_len, kv->len_ub[s]);
-  const int nchunks = cdiv(max_len + R, ATT_CHUNK);
+  const int nchunks = cdiv(max_len + R, ATT_CHUNK), plan_chunks = pcap ? ATT_PLAN_CHUNKS : nchunks;
 
   GemmArgs g0;
   memset(&g0, 0, sizeof g0);
@@ -890,9 +896,9 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     a.split_kt = bf16 ? nqd / 32 : 0;
     {
       ProfScope ps(PROF_ATTN, st);
-      if (hd == 32) rc = launch_attn<DT, 32>(a, nchunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
-      else if (hd == 64) rc = launch_attn<DT, 64>(a, nchunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
-      else rc = launch_attn<DT, 128>(a, nchunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
+      if (hd == 32) rc = launch_attn<DT, 32>(a, nchunks, plan_chunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
+      else if (hd == 64) rc = launch_attn<DT, 64>(a, nchunks, plan_chunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
+      else rc = launch_attn<DT, 128>(a, nchunks, plan_chunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
     }
     if (rc) return rc;
 

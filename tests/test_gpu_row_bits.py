@@ -92,7 +92,10 @@ def test_captured_cycle_has_the_bits_of_the_eager_one_at_long_prefixes(n_prefix)
 
 
 @pytest.mark.parametrize("shape_name,B,K,cached,others", [
-    ("mini_bf16", 2, 4, 1300, (40, 1700))])    # 10 rows: the barrier-free kernel
+    ("mini_bf16", 2, 4, 1300, (40, 1700)),     # 10 rows: the barrier-free kernel
+    ("mini_bf16", 32, 1, 300, (40, 900)),      # 64 rows: one launch per operator
+    ("mini128_bf16", 32, 1, 300, (40, 900)),
+    ("mini128_bf16", 4, 4, 620, (40, 1700))])
 def test_a_sequences_bits_do_not_depend_on_the_lengths_of_the_others(shape_name, B, K, cached, others):
     """The same first sequence in two batches of one shape, beside short sequences and beside long ones."""
     shape = si.model_shape(shape_name)
