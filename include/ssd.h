@@ -22,8 +22,8 @@
  *   - Return value: SSD_OK (0) or a negative error code; ssd_last_error() gives a message for the last
  *     failure on the calling thread.  Arguments are validated on the host before anything is launched;
  *     nothing throws or aborts across this boundary.
- *   - Reproducibility: the same call on the same state gives the same bits.  Beyond that, of a row that the barrier-free
- *     forward computes (ssd_kv_last_forward_path 3 or 4), the bits depend on its sequence's tokens, its position and the
+ *   - Reproducibility: the same call on the same state gives the same bits.  Beyond that, of a row with fp32 storage, or that
+ *     the barrier-free forward computes (ssd_kv_last_forward_path 3 or 4), the bits depend on its sequence's tokens, its position and the
  *     cached keys and values alone: it has them decoded alone (K = 0), among the K + 1 rows of a verification, in a captured
  *     cycle and beside any other sequence.
  *     Of a row of a bf16 forward with one launch per operator (path 1), they depend on the launch's shape (n_seqs and K, or

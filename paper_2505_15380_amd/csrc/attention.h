@@ -22,8 +22,8 @@ struct AttnArgs {
   int NC;               // chunk capacity of the partial buffers
   void* out;            // [M][nq*hd] (combine)
   int split_kt;         // > 0: `out` is written as split rows (common.h) with this many k-tiles per row (nq*hd / 32)
-  int nparts, part_keys;      // k_attn_mfma: grid.x = nparts x groups of row tiles; keys per part (a multiple of 64).  k_attn_f32:
-                              // chunks of the longest sequence
+  int nparts, part_keys;      // k_attn_mfma, k_attn_f32: grid.x = nparts x (groups of) row tiles; keys per part, a multiple of 64
+  int nchunks;                // k_attn_f32: chunks of the longest sequence
 };
 
 template <int HD, typename KVT>
@@ -98,12 +98,14 @@ __global__ void __launch_bounds__(BLOCK) k_attn_chunk(AttnArgs a) {
   }
 }
 
-// One wave per (row, query head): merge the row's chunk partials in ascending chunk order.
+// One wave per (row, query head): merge the row's partials - of chunks, or of k_attn_f32's parts, which leaves nothing to do
+// for a row of one part - in ascending order.
 template <int HD, typename AT>
 __global__ void __launch_bounds__(WAVE) k_attn_combine(AttnArgs a) {
   const int m = blockIdx.x / a.nq, hq = blockIdx.x - m * a.nq;
   const int lane = threadIdx.x;
-  const int nc = a.rows.pos[m] / ATT_CHUNK + 1;
+  const int nc = a.rows.pos[m] / a.part_keys + 1;
+  if (a.part_keys > ATT_CHUNK && nc == 1) return;
   const size_t base = ((size_t)m * a.nq + hq) * a.NC;
   float mx = -INFINITY;
   for (int c = 0; c < nc; ++c) mx = fmaxf(mx, a.ml_part[(base + c) * 2]);
@@ -133,22 +135,29 @@ __global__ void __launch_bounds__(WAVE) k_attn_combine(AttnArgs a) {
   }
 }
 
-// The same for fp32 caches in one launch, on v_mfma_f32_16x16x4_f32 (full fp32 products and sums).  A workgroup takes 16 of the query
-// rows that share a kv head of a sequence; its waves walk the 64-key chunks w, w + W, .. with a running (max, sum, weighted
-// values) per row and meet in LDS, so a row's order of sums depends on its position alone.  Scores and outputs are computed
+// The same for fp32 caches with 16-token blocks, on v_mfma_f32_16x16x4_f32 (full fp32 products and sums).  A workgroup takes 16 of the
+// query rows that share a kv head of a sequence, and a part of the keys: two 64-key chunks per wave, cut at absolute positions.
+// Its waves walk the part's chunks w, w + W with a running (max, sum, weighted values) per row and meet in LDS.  A row of one part
+// (1024 positions; head size 128: 512) is finished there, the parts of a longer one are merged by k_attn_combine: a row's order
+// of sums depends on its position alone, whatever the launch.  (The chunk kernels above for long sequences in small batches, this
+// one for the rest, would give it two; five rows at 960 / 2048 / 8000 positions: 23 / 27 / 29 us with head size 64 where they
+// take 23 / 39 / 73, 33 / 35 / 45 with head size 128: 52 / 55 / 115.)  Scores and outputs are computed
 // transposed: a lane holds one row's scores of the keys 4 kg .. 4 kg + 3 of a tile, which is what the product with the
 // values wants from it, and both operands come from the cache as 16 bytes per lane (dims of a key, tokens of a dim).
 // A chain of launch, block table, cache, merge bounds it: 6.1 us at five rows and 68 cached positions, where the two kernels
 // above take 7.2 + 3.0 (a vector-unit version of this kernel took 7.9: twice the instructions, fetched cold on every launch).
 template <int HD>
 constexpr int att_f32_waves() { return HD <= 64 ? 8 : 4; }
+template <int HD>
+constexpr int att_f32_part() { return 2 * att_f32_waves<HD>(); }      // chunks of a part
 
 template <int HD>
 __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArgs a) {
-  constexpr int W = att_f32_waves<HD>(), DT = HD / 16;
+  constexpr int W = att_f32_waves<HD>(), PC = att_f32_part<HD>(), DT = HD / 16;
   __shared__ float po[W][16][HD + 4];
   __shared__ float pm[W][16], pl[W][16];
   const int kvh = blockIdx.y, brel = blockIdx.z, seq = a.rows.seq0 + brel;
+  const int part = blockIdx.x % a.nparts, r0 = blockIdx.x / a.nparts * 16, c0 = part * PC;
   const int G = a.nq / a.kv.nkv, nrows = a.rows.R * G, m_first = brel * a.rows.R;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int li = lane & 15, kg = lane >> 4;
@@ -159,8 +168,9 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
     return ((size_t)m * a.nq + kvh * G + r - j * G) * HD;
   };
   int m;
-  const f32x4* qp = (const f32x4*)(a.q + q_of(min((int)blockIdx.x * 16 + li, nrows - 1), m)) + kg;
+  const f32x4* qp = (const f32x4*)(a.q + q_of(min(r0 + li, nrows - 1), m)) + kg;
   const int pos = a.rows.pos[m], pos_max = a.rows.pos[m_first + a.rows.R - 1];
+  if (c0 * ATT_CHUNK > pos_max) return;                    // no row of the sequence reaches the part
   f32x4 q[DT];
 #pragma unroll
   for (int s = 0; s < DT; ++s) q[s] = qp[s * 4];
@@ -168,7 +178,8 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
 #pragma unroll
   for (int s = 0; s < DT; ++s) o[s] = f32x4{0, 0, 0, 0};
   float mrow = -INFINITY, lrow = 0.f;
-  for (int c = wave; c < a.nparts; c += W) {               // (a.nparts: chunks of the longest sequence)
+  const int c_end = min(c0 + PC, a.nchunks);
+  for (int c = c0 + wave; c < c_end; c += W) {
     const int p0 = c * ATT_CHUNK;
     const int32_t* tab = a.kv.table + (size_t)seq * a.kv.mbps;
     f32x4 k[4][DT];
@@ -229,10 +240,14 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
   __syncthreads();
   for (int i = threadIdx.x; i < 16 * (HD / 4); i += W * WAVE) {
     const int r = i / (HD / 4), d = (i - r * (HD / 4)) * 4;
-    if ((int)blockIdx.x * 16 + r >= nrows) break;
+    if (r0 + r >= nrows) break;
+    int mm;
+    const size_t at = q_of(r0 + r, mm);
+    const int row_pos = a.rows.pos[mm];
+    if (c0 * ATT_CHUNK > row_pos) continue;                // (no key of the part is the row's, and its merge does not look here)
     float mx = -INFINITY, l = 0.f;
 #pragma unroll
-    for (int x = 0; x < W; ++x) mx = fmaxf(mx, pm[x][r]);  // (position 0 is every row's: finite)
+    for (int x = 0; x < W; ++x) mx = fmaxf(mx, pm[x][r]);  // (the part's first position is the row's: finite)
     f32x4 acc = {0, 0, 0, 0};
 #pragma unroll
     for (int x = 0; x < W; ++x) {
@@ -240,8 +255,13 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
       l = fmaf(pl[x][r], f, l);
       acc += *(const f32x4*)&po[x][r][d] * f;
     }
-    int mm;
-    *(f32x4*)((float*)a.out + q_of((int)blockIdx.x * 16 + r, mm) + d) = acc / l;
+    if (row_pos < PC * ATT_CHUNK) {
+      *(f32x4*)((float*)a.out + at + d) = acc / l;
+    } else {
+      const size_t pidx = at / HD * a.NC + part;
+      *(f32x4*)(a.o_part + pidx * HD + d) = acc;
+      if (d == 0) { a.ml_part[pidx * 2] = mx; a.ml_part[pidx * 2 + 1] = l; }
+    }
   }
 }
 

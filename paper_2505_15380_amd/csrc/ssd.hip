@@ -705,15 +705,21 @@ static int launch_attn(AttnArgs a, int nchunks, int plan_chunks, int nkv, int B,
     if (mfma && a.kv.bt == 16) return launch_attn_mfma<HD>(a, nchunks, plan_chunks, nkv, B, M, cus, st);
   }
   if constexpr (std::is_same<DT, F32>::value) {
-    // a tile of keys is a block; a few long sequences give it too few workgroups for its walk
     const int tiles = cdiv(a.rows.R * (a.nq / nkv), 16);
-    if (a.kv.bt == 16 && (nchunks <= 16 || tiles * nkv * B >= cus / 2)) {
-      a.nparts = nchunks;
-      hipLaunchKernelGGL((k_attn_f32<HD>), dim3(tiles, nkv, B), dim3(att_f32_waves<HD>() * WAVE), 0, st, a);
+    if (a.kv.bt == 16) {                                   // (a tile of keys is a block)
+      a.nchunks = nchunks;
+      a.nparts = cdiv(nchunks, att_f32_part<HD>());
+      a.part_keys = att_f32_part<HD>() * ATT_CHUNK;
+      hipLaunchKernelGGL((k_attn_f32<HD>), dim3(a.nparts * tiles, nkv, B), dim3(att_f32_waves<HD>() * WAVE), 0, st, a);
       LAUNCH_CHECK();
+      if (a.nparts > 1) {
+        hipLaunchKernelGGL((k_attn_combine<HD, F32>), dim3(M * a.nq), dim3(WAVE), 0, st, a);
+        LAUNCH_CHECK();
+      }
       return SSD_OK;
     }
   }
+  a.part_keys = ATT_CHUNK;
   hipLaunchKernelGGL((k_attn_chunk<HD, DT>), dim3(nchunks, nkv, B), dim3(BLOCK), 0, st, a);
   LAUNCH_CHECK();
   hipLaunchKernelGGL((k_attn_combine<HD, F32>), dim3(M * a.nq), dim3(WAVE), 0, st, a);

@@ -145,7 +145,9 @@ def test_tiny_topk_temperature_and_greedy():
     ("fp32", 32, 3, 64, 2, 4),       # 15 query rows per key head, a chunk that is just full
     ("fp32", 64, 2, 509, 1, 8),      # 18 query rows: two tiles; new positions in a ninth chunk (second round of a wave)
     ("fp32", 128, 1, 130, 3, 6),     # head size with half the waves; 21 rows: two row tiles
-    ("fp32", 32, 2, 1030, 1, 2),     # more chunks than the one-launch attention takes
+    ("fp32", 32, 2, 1030, 1, 2),     # more chunks than one part of the attention has
+    ("fp32", 64, 2, 2044, 1, 4),     # rows on both sides of the end of a second part, 16 rows of a tile in one of them
+    ("fp32", 128, 3, 508, 2, 6),     # the smaller parts of head size 128
     ("bf16", 128, 3, 2, 1, 0),       # one row
     ("bf16", 64, 7, 60, 17, 0),      # 17 rows: one more than a tile
     ("bf16", 64, 2, 129, 4, 15),     # 64 rows; a prompt of 128 cached positions in one chunk of rows

@@ -46,7 +46,10 @@ def _verify_logits(model, kv, B, x):
     ("mini_bf16", 4, 1521),
     ("mini_bf16", 7, 1530),        # some rows are the last that attend in one part, the others go in several
     ("mini_bf16", 12, 1535),
-    ("mini_bf16", 4, 2046)])       # a further part begins
+    ("mini_bf16", 4, 2046),        # a further part begins
+    ("tiny", 4, 62),
+    ("tiny", 4, 1022),             # fp32: rows on both sides of the end of the first part
+    ("tiny", 4, 2045)])
 def test_rows_verified_together_have_the_bits_of_rows_decoded_alone(shape_name, K, cached):
     """The logits of the K + 1 rows of a verification against K + 1 autoregressive steps over the same tokens."""
     import paper_2505_15380_amd as ssd
@@ -95,7 +98,9 @@ def test_captured_cycle_has_the_bits_of_the_eager_one_at_long_prefixes(n_prefix)
     ("mini_bf16", 2, 4, 1300, (40, 1700)),     # 10 rows: the barrier-free kernel
     ("mini_bf16", 32, 1, 300, (40, 900)),      # 64 rows: one launch per operator
     ("mini128_bf16", 32, 1, 300, (40, 900)),
-    ("mini128_bf16", 4, 4, 620, (40, 1700))])
+    ("mini128_bf16", 4, 4, 620, (40, 1700)),
+    ("tiny", 2, 4, 1000, (40, 1100)),
+    ("tiny", 2, 4, 1100, (40, 2100))])
 def test_a_sequences_bits_do_not_depend_on_the_lengths_of_the_others(shape_name, B, K, cached, others):
     """The same first sequence in two batches of one shape, beside short sequences and beside long ones."""
     shape = si.model_shape(shape_name)
