@@ -229,6 +229,8 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
     for (int i = 0; i < TM; ++i) rs[i] = row_sums_load(g, (rowb * W + wave) * TM + i);
 #pragma unroll
   for (int b = 0; b < NBUF - 1; ++b) request_w(min(b, nk - 1), b);
+  asm volatile("" ::: "memory");                           // the first waits count the activations' requests as the later ones
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int u = 0; u < UA; ++u) request_a(u, min(u, nk - 1));
   float inv[TM];
