@@ -47,32 +47,6 @@ __device__ __forceinline__ float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
   return v;
 }
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-  return v;
-}
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-  return v;
-}
-
-// Block-wide (256 threads) reductions through a 4-entry LDS array; all threads get the result.
-__device__ __forceinline__ float block_sum(float v, float* s4) {
-  v = wave_sum(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) s4[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return (s4[0] + s4[1]) + (s4[2] + s4[3]);
-}
-__device__ __forceinline__ float block_max(float v, float* s4) {
-  v = wave_max(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) s4[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return fmaxf(fmaxf(s4[0], s4[1]), fmaxf(s4[2], s4[3]));
-}
 
 // Philox-4x32-10 (Salmon et al., SC'11).  Counter (slot, seq, step_lo, step_hi), key (seed_lo, seed_hi).
 // Returns output word 0; the uniform of a slot is its top 24 bits times 2^-24.
@@ -143,13 +117,6 @@ __device__ __forceinline__ float row16_sum(float v) {
   v += dpp_f<0x4E>(v);       // quad_perm [2,3,0,1]
   v += dpp_f<0x141>(v);      // row_half_mirror
   v += dpp_f<0x140>(v);      // row_mirror
-  return v;
-}
-__device__ __forceinline__ float row16_max(float v) {
-  v = fmaxf(v, dpp_f<0xB1>(v));
-  v = fmaxf(v, dpp_f<0x4E>(v));
-  v = fmaxf(v, dpp_f<0x141>(v));
-  v = fmaxf(v, dpp_f<0x140>(v));
   return v;
 }
 

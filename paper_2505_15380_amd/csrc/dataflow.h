@@ -45,7 +45,6 @@
 namespace ssd {
 
 typedef unsigned long long u64;
-constexpr int DF_B = 12;                  // tagged words a thread keeps in flight while it stages attention operands
 constexpr int DF_AW = 21504;              // LDS words of the operand staging area (84 KB)
 constexpr int DF_ATT_ROWS = 256;          // query rows of a sequence (rows x heads of a group): at most 16 tiles of 16
 constexpr int DF_NPF = 5;                 // attention parts merged per flight
@@ -573,7 +572,7 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
   uint32_t* As = lds;
   float* sqs = (float*)(lds + DF_AW);
   float (*red)[2][256] = (float (*)[2][256])((float*)(lds + DF_AW + DF_SQ_WORDS) + usel * 2048);
-  const int M = a.rows.M, PR = (int)(a.st_h / a.d);
+  const int M = a.rows.M;
   const int KT = ph.K >> 5, ntiles_d = a.d >> 4, KTd = a.ffn >> 5;
   const int arow = lane & 15, g = lane >> 4, c16 = lane & 15;
   const int row = ut >> 4, col = ut & 15;

@@ -569,64 +569,31 @@ static int launch_gemm_f32(const GemmArgs& g, int items, hipStream_t st) {
   return SSD_OK;
 }
 
-// Launch of a bf16 GEMM (gemm_tile.h): picks the kernel, the tile and the k-slices from the sizes alone.  Returns the
-// number of k-slices (1 unless `max_slices` allows more: outputs that are k-split partials).
-//   - Few rows (up to 64; for the QKV and output projections, whose k range is not split over workgroups, up to 512): k_gemm_kwave
-//     with the smallest tile that leaves no more workgroups than compute units.  What bounds it is how long a workgroup's
-//     operand stream takes, so the work is spread as far as one round of workgroups allows; k-split outputs get 8 slices
-//     (4 where k is short) while that round lasts.
-//   - Else k_gemm_tile at the tile and slices of the least estimated time.  The estimate was fitted to measurements of
-//     both model shapes at 72 to 1024 rows: a workgroup's k-tile costs 16.6 cycles per 16x16 tile of its output (twice
-//     what the matrix cores alone would take) or 24 cycles per KB that it loads, whichever is more, workgroups of a
-//     compute unit share it, and one alone cannot hide 160 cycles of latency per k-tile (40 cycles per KB where the rows take
-//     much of an L2, beyond 1.5 MB); partial outputs cost their write and their read at 5 TB/s.  It is within 10 % of the
-//     best measured tile at nearly every size that was measured.
-//     Tiles that leave a compute unit one workgroup of four waves keep eight k-tiles in flight instead of four (weights
-//     that come from HBM take more than a microsecond: 97 rows of gate / up 13.1 -> 12.1 us).
+// The output of a bf16 GEMM (gemm_tile.h) cut into workgroups of rows x cols tiles and k-slices.
 template <int EPI>
-static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t st) {
-  const int KT = g.K / 32, MT = cdiv(g.M, 16);
-  const int n_wt = EPI == EPI_SWIGLU ? 2 * cdiv(g.N, 16) : cdiv(g.N, 16);     // weight tiles (gate and up both count)
-  auto plan = [&](int rows, int cols, int slices) {        // rows, cols: tiles of a workgroup
-    TilePlan p;
-    p.n_colb = cdiv(n_wt, cols);
-    p.n_rowb = cdiv(MT, rows);
-    p.slice_kt = cdiv(KT, slices);
-    p.n_slices = cdiv(KT, p.slice_kt);
-    p.per_xcd = cdiv(p.n_colb * p.n_rowb * p.n_slices, 8);
-    return p;
-  };
-  auto wgs = [](const TilePlan& p) { return p.n_colb * p.n_rowb * p.n_slices; };
-#define KWAVE(TM, TN, U)                                                                             \
-  if (tm == TM && tn == TN) hipLaunchKernelGGL((k_gemm_kwave<EPI, TM, TN, 8, U>), dim3(8 * p.per_xcd), dim3(512), 0, st, g, p)
-  if (MT <= 4 || ((EPI == EPI_QKV || EPI == EPI_RESID) && MT <= 32)) {
-    static const int shapes[][2] = {{1, 2}, {2, 2}, {1, 4}, {3, 2}, {1, 6}, {2, 4}, {2, 6}, {3, 4}, {4, 4}, {3, 6}, {4, 6}};   // by area
-    int tm = 0, tn = 0;
-    TilePlan p{};
-    auto usable = [&](const int* c) {
-      return c[0] <= MT && (EPI == EPI_SWIGLU ? c[0] < 4 || c[1] == 6 : c[1] <= 4);
-    };
-    for (int ns = max_slices >= 8 && KT >= 64 ? 8 : max_slices >= 4 && KT >= 16 ? 4 : 1; ns >= 1 && !tm; ns /= 2)
-      for (const auto& c : shapes) {
-        if (!usable(c)) continue;
-        const TilePlan q = plan(c[0], c[1], ns);
-        if (wgs(q) <= cus) { tm = c[0]; tn = c[1]; p = q; break; }
-      }
-    if (!tm)                                               // more than one round whatever the tile: the largest usable one
-      for (const auto& c : shapes)
-        if (usable(c)) { tm = c[0]; tn = c[1]; p = plan(tm, tn, 1); }
-    KWAVE(1, 2, 4);
-    else KWAVE(2, 2, 4);
-    else KWAVE(1, 4, 4);
-    else KWAVE(3, 2, 4);
-    else KWAVE(2, 4, 2);
-    else KWAVE(3, 4, 2);
-    else if constexpr (EPI == EPI_SWIGLU) { KWAVE(1, 6, 4); else KWAVE(2, 6, 2); else KWAVE(3, 6, 1); else KWAVE(4, 6, 1); }
-    else { KWAVE(4, 4, 2); }
-    LAUNCH_CHECK();
-    return p.n_slices;
-  }
-#undef KWAVE
+static TilePlan gemm_plan(const GemmArgs& g, int rows, int cols, int slices) {
+  const int KT = g.K / 32, n_wt = EPI == EPI_SWIGLU ? 2 * cdiv(g.N, 16) : cdiv(g.N, 16);       // weight tiles (gate and up both count)
+  TilePlan p;
+  p.n_colb = cdiv(n_wt, cols);
+  p.n_rowb = cdiv(cdiv(g.M, 16), rows);
+  p.slice_kt = cdiv(KT, slices);
+  p.n_slices = cdiv(KT, p.slice_kt);
+  p.per_xcd = cdiv(p.n_colb * p.n_rowb * p.n_slices, 8);
+  return p;
+}
+static int plan_wgs(const TilePlan& p) { return p.n_colb * p.n_rowb * p.n_slices; }
+
+// Many rows: k_gemm_tile at the tile and slices of the least estimated time.  The estimate was fitted to measurements of
+// both model shapes at 72 to 1024 rows: a workgroup's k-tile costs 16.6 cycles per 16x16 tile of its output (twice
+// what the matrix cores alone would take) or 24 cycles per KB that it loads, whichever is more, workgroups of a
+// compute unit share it, and one alone cannot hide 160 cycles of latency per k-tile (40 cycles per KB where the rows take
+// much of an L2, beyond 1.5 MB); partial outputs cost their write and their read at 5 TB/s.  It is within 10 % of the
+// best measured tile at nearly every size that was measured.
+// Tiles that leave a compute unit one workgroup of four waves keep eight k-tiles in flight instead of four (weights
+// that come from HBM take more than a microsecond: 97 rows of gate / up 13.1 -> 12.1 us).
+template <int EPI>
+static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStream_t st) {
+  const int KT = g.K / 32;
   struct Shape { int tm, tn, w; };
   static const Shape shapes[] = {{1, 4, 4}, {1, 6, 4}, {1, 8, 4}, {1, 10, 4}, {1, 7, 4}, {1, 8, 8}, {1, 7, 8}, {1, 10, 8}, {2, 12, 4}, {2, 8, 8}};
   const double kb_cycles = (size_t)g.M * g.K * 4 > 1536u * 1024 ? 40.0 : 24.0;
@@ -635,11 +602,11 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
   TilePlan p{};
   for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
     const Shape& c = shapes[i];
-    const bool ok = EPI == EPI_PARTIAL || EPI == EPI_RESID ? c.tn == 4 || c.tn == 7 || c.tn == 8 : EPI == EPI_SWIGLU ? c.tn != 7 && !(c.tm == 2 && c.tn == 8) : c.tn == 4;
+    const bool ok = EPI == EPI_PARTIAL ? c.tn == 4 || c.tn == 7 || c.tn == 8 : EPI == EPI_SWIGLU ? c.tn != 7 && !(c.tm == 2 && c.tn == 8) : c.tn == 4;
     if (!ok) continue;
     for (int ns = 1; ns <= std::min(8, max_slices) && (ns == 1 || KT / ns >= 7); ns *= 2) {
-      const TilePlan q = plan(c.tm * c.w, c.tn, ns);
-      const int rounds = cdiv(wgs(q), cus);
+      const TilePlan q = gemm_plan<EPI>(g, c.tm * c.w, c.tn, ns);
+      const int rounds = cdiv(plan_wgs(q), cus);
       const double cyc = std::max(16.6 * c.tm * c.w * c.tn, kb_cycles * (2 * c.tm * c.w + c.tn));
       const double us = q.slice_kt * (rounds * cyc + (rounds == 1 ? 160.0 : 0.0)) / 2400.0 +
                         (max_slices > 1 ? (double)q.n_slices * g.M * g.N * 8.0 / 5e6 : 0.0);
@@ -649,7 +616,7 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
     }
   }
   const Shape c = shapes[best];
-  const bool deep = c.tm == 1 && c.w == 4 && wgs(p) <= cus;
+  const bool deep = c.tm == 1 && c.w == 4 && plan_wgs(p) <= cus;
 #define TILE(TM, TN, W)                                                                                         \
   if (!deep && c.tm == TM && c.tn == TN && c.w == W)                                                             \
   hipLaunchKernelGGL((k_gemm_tile<EPI, TM, TN, W, 4, 4, TM == 2 && W == 8 ? 1 : 2>), dim3(8 * p.per_xcd), dim3(W * 64), 0, st, g, p)
@@ -660,7 +627,7 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
   else if constexpr (EPI == EPI_SWIGLU) {
     TILE(1, 6, 4); else TILE(1, 8, 4); else TILE(1, 10, 4); else TILE(1, 8, 8); else TILE(1, 10, 8); else TILE(2, 12, 4);
     else TILE_DEEP(6); else TILE_DEEP(8); else TILE_DEEP(10);
-  } else if constexpr (EPI == EPI_PARTIAL || EPI == EPI_RESID) {
+  } else if constexpr (EPI == EPI_PARTIAL) {
     TILE(1, 7, 4); else TILE(1, 8, 4); else TILE(1, 7, 8); else TILE(1, 8, 8); else TILE(2, 8, 8);
     else TILE_DEEP(7); else TILE_DEEP(8);
   }
@@ -668,6 +635,50 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
 #undef TILE_DEEP
   LAUNCH_CHECK();
   return p.n_slices;
+}
+
+// Launch of a bf16 GEMM: picks the kernel, the tile and the k-slices from the sizes alone.  Returns the number of k-slices (1 unless
+// `max_slices` allows more: outputs that are k-split partials).
+// Few rows (up to 64; for the QKV and output projections, whose k range is not split over workgroups, up to 512): k_gemm_kwave
+// with the smallest tile that leaves no more workgroups than compute units.  What bounds it is how long a workgroup's
+// operand stream takes, so the work is spread as far as one round of workgroups allows; k-split outputs get 8 slices
+// (4 where k is short) while that round lasts.
+template <int EPI>
+static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t st) {
+  const int KT = g.K / 32, MT = cdiv(g.M, 16);
+  constexpr bool whole_k = EPI == EPI_QKV || EPI == EPI_RESID;
+  if (MT > (whole_k ? 32 : 4)) {
+    if constexpr (EPI == EPI_RESID) return fail(SSD_ENOSUP, "the projection with a residual takes up to 512 rows");     // (its callers' limit)
+    else return launch_gemm_tile<EPI>(g, cus, max_slices, st);
+  }
+#define KWAVE(TM, TN, U)                                                                             \
+  if (tm == TM && tn == TN) hipLaunchKernelGGL((k_gemm_kwave<EPI, TM, TN, 8, U>), dim3(8 * p.per_xcd), dim3(512), 0, st, g, p)
+  static const int shapes[][2] = {{1, 2}, {2, 2}, {1, 4}, {3, 2}, {1, 6}, {2, 4}, {2, 6}, {3, 4}, {4, 4}, {3, 6}, {4, 6}};   // by area
+  int tm = 0, tn = 0;
+  TilePlan p{};
+  auto usable = [&](const int* c) {
+    return c[0] <= MT && (EPI == EPI_SWIGLU ? c[0] < 4 || c[1] == 6 : c[1] <= 4);
+  };
+  for (int ns = max_slices >= 8 && KT >= 64 ? 8 : max_slices >= 4 && KT >= 16 ? 4 : 1; ns >= 1 && !tm; ns /= 2)
+    for (const auto& c : shapes) {
+      if (!usable(c)) continue;
+      const TilePlan q = gemm_plan<EPI>(g, c[0], c[1], ns);
+      if (plan_wgs(q) <= cus) { tm = c[0]; tn = c[1]; p = q; break; }
+    }
+  if (!tm)                                               // more than one round whatever the tile: the largest usable one
+    for (const auto& c : shapes)
+      if (usable(c)) { tm = c[0]; tn = c[1]; p = gemm_plan<EPI>(g, tm, tn, 1); }
+  KWAVE(1, 2, 4);
+  else KWAVE(2, 2, 4);
+  else KWAVE(1, 4, 4);
+  else KWAVE(3, 2, 4);
+  else KWAVE(2, 4, 2);
+  else KWAVE(3, 4, 2);
+  else if constexpr (EPI == EPI_SWIGLU) { KWAVE(1, 6, 4); else KWAVE(2, 6, 2); else KWAVE(3, 6, 1); else KWAVE(4, 6, 1); }
+  else { KWAVE(4, 4, 2); }
+  LAUNCH_CHECK();
+  return p.n_slices;
+#undef KWAVE
 }
 
 // Matrix-core attention: parts so that a launch has about a workgroup per CU and a key group at least one chunk; one part, and no
