@@ -317,7 +317,7 @@ struct ssd_kv {
   bool capturing = false;          // a cycle is being captured on this cache: no synchronisation, no fallback kernels
   int last_path = 0;               // 1 per-operator launches, 2 barrier kernel, 3 barrier-free kernel, 4 the same with attention without parts
   bool last_whole = false;
-  int df_sb = 0;             // SSD_DF_FLIGHT=2|4|10|16|18: words in flight per thread of the operand staging (0: chosen per launch)
+  int df_sb = 0;             // SSD_DF_FLIGHT=2|4|10|16|18: words in flight per thread of the operand staging, up to 8 rows (0: chosen per launch)
   // host
   int32_t* mirror_host;
   std::vector<int> len_ub, npend_ub;
@@ -476,7 +476,6 @@ extern "C" int ssd_kv_create(const ssd_model* m, int max_seqs, int max_rows, int
     kv->attn_whole = env ? (env[0] == '1' || (env[0] == '2' && pending_cap == 2)) : (pending_cap == 2);
     env = getenv("SSD_DF_FLIGHT");
     kv->df_sb = env ? atoi(env) : 0;
-    if (kv->df_sb == 12) kv->df_sb = 18;
     if (kv->df_sb != 2 && kv->df_sb != 4 && kv->df_sb != 10 && kv->df_sb != 16 && kv->df_sb != 18) kv->df_sb = 0;
   }
   if (e != hipSuccess) { (void)hipHostFree(kv->mirror_host); delete kv; return fail(SSD_EHIP, "k_kv_init: %s", hipGetErrorString(e)); }

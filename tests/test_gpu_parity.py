@@ -227,11 +227,12 @@ def test_mini_bf16_attention_without_parts(n_prefix, K, monkeypatch):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("flight,K", [("2", 0), ("2", 12), ("4", 4), ("10", 12), ("12", 0), ("", 1), ("", 3)])
+@pytest.mark.parametrize("flight,K", [("2", 0), ("2", 7), ("4", 3), ("4", 7), ("10", 7), ("16", 0), ("18", 0), ("2", 12),
+                                      ("", 1), ("", 3)])
 def test_mini_bf16_operand_staging_flights(flight, K, monkeypatch):
     """The barrier-free kernel is instantiated per number of tagged words a thread keeps in flight while it stages GEMM
-    operands (chosen per launch from the row count): every size with rows that fit one flight and rows that need
-    several, and the launch's own choice."""
+    operands (chosen per launch from the row count): every size, 2 and 4 also with rows that need several flights, more
+    than the 8 rows up to which a size can be asked for, and the launch's own choice."""
     from tests.parity import run_verify_parity
     if flight:
         monkeypatch.setenv("SSD_DF_FLIGHT", flight)

@@ -111,3 +111,22 @@ def test_a_sequences_bits_do_not_depend_on_the_lengths_of_the_others(shape_name,
         logits, path = _verify_logits(model, kv, B, x)
         got.append(logits[0])
     assert torch.equal(got[0], got[1]), f"differs by {float((got[0] - got[1]).abs().max())}"
+
+
+@pytest.mark.parametrize("K", [0, 4, 7])
+def test_words_in_flight_do_not_change_bits(K, monkeypatch):
+    """Every instantiation of the barrier-free kernel on the same rows of width 896: one flight or several (eight rows need two
+    of the 10-word ones), both halves of an operand in one matrix instruction or in two, sums of squares over 8 or 32 columns."""
+    shape = si.model_shape("half_b_draft")
+    shape.update(n_layers=1, vocab=300, n_embed=300)
+    x = torch.from_numpy(np.random.default_rng(7).integers(0, 300, (1, K)).astype(np.int32)).cuda()
+    got = []
+    for flight in ("", "2", "4", "10", "16", "18"):
+        if flight:
+            monkeypatch.setenv("SSD_DF_FLIGHT", flight)
+        else:
+            monkeypatch.delenv("SSD_DF_FLIGHT", raising=False)
+        logits, path = _verify_logits(*_target(shape, [70], 64), 1, x)
+        assert path == 3
+        got.append(logits)
+    assert all(torch.equal(g, got[0]) for g in got[1:])
