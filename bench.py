@@ -152,7 +152,7 @@ def main():
         for i in range(20):
             verify_once(i)
         k_ms, k_n = ssd.ssd_profile_end()
-        kernel_name = "k_gemm_bf16<gate/up + SwiGLU>"
+        kernel_name = "k_gemm_kwave / k_gemm_tile <gate/up + SwiGLU>"
         fwd_bytes = 2 * tshape["d_model"] * tshape["d_ffn"] * 2
     gu_ms = k_ms / max(k_n, 1)
     gu_gbs = fwd_bytes / (gu_ms * 1e-3) / 1e9

@@ -1,11 +1,11 @@
 // Multi-query decode attention over the paged cache (Eq. 4: the K+1 rows of a verification attend to the
-// whole prefix and causally to each other).
-//
-// Work item = (chunk of 64 key positions, kv head, sequence).  The workgroup stages the chunk's keys and
-// values in LDS once and serves every query row that shares them: R rows of the sequence x the G query
-// heads of the group.  Each query row gets a partial (max, sum, weighted values) per chunk; k_attn_combine
-// merges the chunks in ascending order.  Chunks are cut at absolute positions, so the partials a row
-// combines - and therefore its bits - do not depend on how many rows are verified together.
+// whole prefix and causally to each other), as launches of its own:
+//   k_attn_mfma   bf16, 16-token blocks, head size 64 or 128: the matrix cores on hi + lo halves (k_attn_combine_parts merges)
+//   k_attn_f32    fp32, 16-token blocks: the fp32 matrix instructions (k_attn_combine merges)
+//   k_attn_chunk  every other block size, head size 32 in bf16, and SSD_ATTN=valu: vector units (k_attn_combine merges)
+// Parts and chunks are cut at absolute positions and merged in ascending order.  Those of the fp32 and of the chunk kernels
+// have one size, so what a row combines - and therefore its bits - does not depend on how many rows are verified
+// together; the size of k_attn_mfma's parts follows from the launch's shape.
 #pragma once
 #include "common.h"
 
@@ -26,6 +26,9 @@ struct AttnArgs {
   int nchunks;                // k_attn_f32: chunks of the longest sequence
 };
 
+// Work item = (chunk of 64 key positions, kv head, sequence).  The workgroup stages the chunk's keys and values in LDS once
+// and serves every query row that shares them: R rows of the sequence x the G query heads of the group.  Each query row gets a
+// partial (max, sum, weighted values) per chunk.
 template <int HD, typename KVT>
 __global__ void __launch_bounds__(BLOCK) k_attn_chunk(AttnArgs a) {
   __shared__ float Ks[ATT_CHUNK][HD + 1];

@@ -161,7 +161,7 @@ __device__ __forceinline__ SplitA split_bf16(const u32x4 a, const u32x4 b) {
 }
 
 // "Split rows": GEMM operand rows [M][K] kept as the matrix core takes them, for the kernels that serve many rows
-// (gemm_rows.h).  Value x of (row, k) is stored as hi = upper 16 bits of x and lo = bf16(x - hi); the fragment of row
+// (gemm_tile.h).  Value x of (row, k) is stored as hi = upper 16 bits of x and lo = bf16(x - hi); the fragment of row
 // tile mt = row / 16 and k-tile kt = k / 32 is 64 lanes x 8 bf16 with lane = row % 16 + 16 * ((k % 32) / 8), element k % 8:
 // 1 KB of hi followed by 1 KB of lo, fragments ordered [mt][kt].  A wave loads a fragment with one contiguous 16-byte
 // load per lane.  Index (in bf16 elements) of the hi value; the lo value is 512 elements further.

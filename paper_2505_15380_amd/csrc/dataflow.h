@@ -4,10 +4,13 @@
 // -> output projection (+residual) -> MLP (gate/up + SwiGLU + down projection fused inside a workgroup) -> sum of the
 // MLP partials (+residual).  Weights are packed as matrix-core fragments; a unit of 4 waves takes an item.
 //
-// Dependent phases are ordered by the data itself: everything a workgroup hands to another workgroup is an 8-byte
-// word {payload, tag}, stored with one agent-scope 64-bit store, where tag is the number of this launch.  A consumer
-// loads the words it needs with agent-scope 64-bit loads and repeats the loads whose tag is not yet this launch's.
-// An aligned 8-byte store is observed whole, so a matching tag proves the payload; no store has to be acknowledged
+// Dependent phases are ordered by the data itself: everything a workgroup hands to another workgroup is made of 8-byte
+// words {payload, tag}, where tag is the number of this launch.  Words are stored and loaded with agent-scope 64-bit accesses,
+// or, where two lie side by side (GEMM operands, attention rows and partials, MLP partials), with 16-byte accesses past the
+// same caches.  A consumer repeats the loads whose tag is not yet this launch's.  A word is observed whole, so a matching tag
+// proves its payload.  For a 64-bit access the memory model promises that.  That each aligned 8-byte half of a 16-byte access
+// is whole as well is a property of this hardware, where a lane's 16 bytes are one piece of one cache line in every request;
+// of the two halves together nothing is assumed, each has its tag.  No store has to be acknowledged
 // before a flag is raised, no counter is shared, and a dependency costs one store plus one load instead of the
 // chain of memory round trips of a barrier.  Every word is written exactly once per launch (each layer and phase
 // has its own buffers; the MLP partials alternate between two buffers and carry the layer in their tag), and
@@ -18,8 +21,8 @@
 // keys / values are bf16 bits.
 //
 // A workgroup stages the operand rows it needs in LDS once (all its threads poll in parallel, SB words in flight
-// each: the kernel is instantiated for SB = 2, 4, 10, 16, 18 and the host picks the smallest that holds the launch's rows
-// in one flight) and feeds the matrix cores from LDS.  The weights of an item are requested at the entry of its phase, into
+// each: the kernel is instantiated for SB = 2, 4, 10, 16, 18 and the host picks, up to 8 rows, the smallest that holds the
+// launch's rows in one flight, 18 for more) and feeds the matrix cores from LDS.  The weights of an item are requested at the entry of its phase, into
 // registers, before that wait: workgroups arrive at a phase before its operands do, so the wait hides the HBM latency.
 // The phases with few items (QKV, attention, output projection) run on workgroups of their own, beyond those that
 // take the MLP items, so that no workgroup is late for the MLP, the phase every workgroup waits for.
@@ -27,9 +30,9 @@
 // single word of the PRECEDING phase's operands with long sleeps, and polls in earnest only from then on.
 //
 // Attention never reads this launch's new keys from the cache pool: the QKV phase stores them in the pool for
-// later launches and, tagged, in a side buffer; a wave whose 64-key chunk reaches the new positions patches its
-// key / value fragments from that buffer at the same fragment slots the pool would have supplied, so a row's bits
-// do not depend on how many rows are verified together.
+// later launches and, tagged, in a side buffer; a wave whose 64-key chunk reaches the new positions patches its key
+// fragments from that buffer at the same slots the pool would have supplied, and its values in LDS, through which that
+// chunk's go.  A row's bits do not depend on how many rows are verified together.
 //
 // There is no grid barrier: phase 0 (row bookkeeping, embedding, block reservation) hands over like every other phase.
 // All waits are bounded; a timeout raises the error word and every workgroup leaves; the kernel that follows the

@@ -1,8 +1,9 @@
 // GEMMs of the decoder, Y[M,N] = X[M,K] . W[N,K]^T with M = rows of one forward: what both storage types share (arguments,
 // epilogues) and the fp32 kernel.  The bf16 kernels are in gemm_tile.h.
 //
-// No output element is accumulated with atomics: each has one summation order that does not depend on M, so a row computed
-// alone (autoregressive step) and the same row computed among K+1 (verification) give the same bits.
+// No output element is accumulated with atomics, so a launch gives the same bits every time.  fp32: an element's order of sums
+// follows from K alone, and a row has the same bits alone (autoregressive step) and among K + 1 (verification).  bf16: the
+// kernel, its tile and the k-slices are chosen from the launch's sizes, and the order of sums with them.
 //
 // bf16 weights are pre-packed so that a wave reads one tile (16 out-features x 32 in-features) as 64
 // consecutive 16-byte pieces: piece l of tile (nt, kt) = W[nt*16 + l%16][kt*32 + 8*(l/16) .. +7], tiles ordered

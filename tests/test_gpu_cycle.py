@@ -187,8 +187,8 @@ def test_batched_ragged_verify_parity(workload, tol):
 
 
 def test_draft_attention_mode_changes_with_the_prefix():
-    """The draft's launches take attention without parts while the host's bound of the cached length allows it (1520
-    positions) and attention in parts beyond: cycles in lockstep with the oracle across that length."""
+    """The draft's rows attend in one part up to 1536 positions and in several beyond (launches are reported as 4 while the
+    host's bound of the cached length is at most 1520, as 3 beyond): cycles in lockstep with the oracle across those lengths."""
     sess = run_cycles_in_lockstep("mini", 2e-2, 0.4, K=3, steps=12, require_both=False, n_prefix=1490)
     assert sess.draft_paths_seen == {3, 4}
     assert sess.kv_d.state(0)["len"] > 1520
@@ -290,7 +290,7 @@ def test_many_sequences_reserve_blocks_in_one_launch():
 
 def test_batched_verify_beyond_one_row_tile_uses_matrix_core_attention():
     """Five ragged sequences x (K+1 = 5) rows = 25 rows: more than the persistent kernels take, so every operator is
-    its own launch and attention runs as 256-key parts on the matrix cores.  Lengths put new positions on both sides
+    its own launch and attention runs on the matrix cores, as 256-key parts at this batch.  Lengths put new positions on both sides
     of a part boundary (250 -> 256), in a second and third part, and inside the first chunk."""
     from tests.parity import Pair, verify_parity_step
     wl = si.workload("mini")
@@ -314,18 +314,16 @@ def test_batched_verify_beyond_one_row_tile_uses_matrix_core_attention():
     assert 0 < worst < 2e-2
 
 
-@pytest.mark.parametrize("shape_name,gemm,attn", [("mini_bf16", "", ""), ("mini128_bf16", "", ""), ("mini_bf16", "narrow", ""),
-                                                  ("mini128_bf16", "", "valu")])
-def test_batched_verify_many_rows_kernels(shape_name, gemm, attn, monkeypatch):
+@pytest.mark.parametrize("shape_name,attn", [("mini_bf16", ""), ("mini128_bf16", ""), ("mini_bf16", "valu"), ("mini128_bf16", "valu")])
+def test_batched_verify_many_rows_kernels(shape_name, attn, monkeypatch):
     """Five ragged sequences x (K+1 = 8) rows = 40 rows: three row tiles, so the batched kernels run (matrix-core
-    attention for head_dim 64 and 128, the LDS-shared gate/up GEMM with a ragged last row group), and the generic
-    kernels they replace when switched off; all against the oracle."""
+    attention for head_dim 64 and 128, the wave-split GEMM with a ragged last row tile), and the attention on vector units
+    that takes its place when it is switched off; all against the oracle."""
     from tests.parity import Pair, verify_parity_step
-    for k, v in (("SSD_GEMM", gemm), ("SSD_ATTN", attn)):
-        if v:
-            monkeypatch.setenv(k, v)
-        else:
-            monkeypatch.delenv(k, raising=False)
+    if attn:
+        monkeypatch.setenv("SSD_ATTN", attn)
+    else:
+        monkeypatch.delenv("SSD_ATTN", raising=False)
     shape = si.model_shape(shape_name)
     B, K, steps = 5, 7, 2
     lens = [40, 250, 300, 515, 64]

@@ -118,8 +118,8 @@ def _sampled_batch_parity(workload, sample, atol, max_prefix=None, atol_exact=No
 @pytest.mark.timeout(900)
 def test_half_b_batch16_sampled_parity():
     """The batch-16 configuration (ragged prefixes in [256, 4096], K=6, 16-token blocks) at full size: 112 rows in one
-    verification; the oracle checks the shortest and the longest sequence (3789 positions: fifteen 256-key attention
-    parts on the path with one launch per operator)."""
+    verification; the oracle checks the shortest and the longest sequence (3789 positions: eight attention
+    parts of 512 keys on the path with one launch per operator)."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     path = _sampled_batch_parity("half_b_batch16", sample=(0, 15), atol=2e-2, prefill_rows=512)
@@ -128,7 +128,7 @@ def test_half_b_batch16_sampled_parity():
 
 @pytest.mark.timeout(900)
 def test_half_b_long_prefix_topk_parity():
-    """The long-utterance configuration at full size: prefix 4096 (17 attention parts of 256 keys), top-k 25 on the
+    """The long-utterance configuration at full size: prefix 4096 (five attention parts of 1024 keys), top-k 25 on the
     target; one verification each at K = 8, 2 and 12 (nine, three and thirteen rows; K = 4 is what every other
     full-size test runs) against the oracle, through the barrier-free kernel."""
     if not torch.cuda.is_available():
@@ -166,7 +166,7 @@ def test_half_b_long_prefix_topk_draft_step():
     cfg = ssd.sample_config(temperature=1.0, top_k=25, seed=wl["seeds"]["rng"] + 1)
     ssd.ssd_draft_step(model, kv, 1, cfg, 3, 1, tok, 1, pd, V)
     torch.cuda.synchronize()
-    assert kv.last_forward_path() == 3                      # 4095 cached positions: attention in 256-key parts
+    assert kv.last_forward_path() == 3                      # 4095 cached positions: attention in 1024-key parts
     gp = pd.cpu().numpy()[0]
     om = OD.Model(ds, dw)
     oc = OD.Cache(ds, max_pos)
