@@ -124,6 +124,10 @@ __device__ __forceinline__ uint32_t order_key(float f) {      // larger float <-
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+__device__ __forceinline__ float key_order(uint32_t k) {      // its inverse
+  return __uint_as_float(k & 0x80000000u ? k & 0x7FFFFFFFu : ~k);
+}
+
 struct WarpArgs {
   const float* logits;   // [rows][ld]
   int ld, V;
@@ -168,7 +172,8 @@ __device__ __forceinline__ void warp_softmax_row(const WarpArgs w, const int row
   __shared__ int i16[16];
   __shared__ int cnt16[2][16];
   __shared__ unsigned long long cand[TOPK_CAND];
-  __shared__ uint32_t sh_kth;
+  __shared__ __align__(16) uint32_t group_max[SBLOCK / 8];
+  __shared__ uint32_t sh_kth, sh_best;
   __shared__ int sh_n, sh_idxmax;
   const int tid = threadIdx.x;
   const float* x = w.logits + (size_t)row * w.ld;
@@ -206,26 +211,54 @@ __device__ __forceinline__ void warp_softmax_row(const WarpArgs w, const int row
     return;
   }
 
-  // The cut of the top-k set.  Two steps: a binary search over the order-preserving integer keys for a threshold that between
-  // k and `cap` entries reach (a step counts with wave ballots: no atomics, one barrier), then the candidates are collected
-  // in LDS and ranked against each other by (value, index), four threads per candidate.  Peaked speech logits need about
-  // eight steps.  (A radix select by LDS histograms serialised on the few leading bytes that logits share and on one thread's
-  // walk over the bins: 44 us for 112 rows of 6564 with k = 25, against the 6 us that the rest of the kernel takes.)
+  // The cut of the top-k set, in three steps.
+  //  1. A lower bound of the k-th largest key: the k-th largest of the maxima of 128 disjoint groups of entries (eight threads'
+  //     each) is reached by at least k entries.  Eight threads rank a group's maximum against the others, two barriers in all.
+  //     Logits without order over the vocabulary leave little more than k entries above it (k = 25: about 28, k = 50: 62).
+  //  2. Where more than `cap` entries reach the bound (k > 128, or large entries that share groups), a binary search from there
+  //     over the order-preserving integer keys for a threshold that between k and `cap` reach (a step counts with wave ballots: no
+  //     atomics, one barrier).
+  //  3. The candidates are collected in LDS and ranked against each other by (value, index), four threads per candidate.
+  // (112 rows of 6564 with k = 25: 8.9 us, where the search alone, about eight steps from zero, took 12.8, and a radix select by LDS
+  // histograms 44, serialised on the few leading bytes that logits share.  One row with its draw: 11.9 against 17.0.)
   uint32_t kth = 0;          // keep keys > kth, and keys == kth with index <= idxmax
   int idxmax = 0x7fffffff;
   const bool use_k = w.top_k > 0 && w.top_k < V;
+  float best = -INFINITY;    // the thread's largest entry, with top-k the row's
   if (use_k) {
     const int k = w.top_k;
     const int cap = k <= 128 ? 256 : k <= TOPK_CAND / 2 ? TOPK_CAND : 0;   // 0: search down to the exact key
-    uint32_t key[SP];
-    float best = -INFINITY;
+    uint32_t key[SP], top = 0;
 #pragma unroll
     for (int e = 0; e < SP; ++e) {
       const bool in = tid + e * SBLOCK < V;
       key[e] = in ? order_key(xv[e]) : 0u;                   // (padding: below every number)
-      best = fmaxf(best, xv[e]);
+      top = max(top, key[e]);
     }
-    best = sblock_max(best, s16);
+    // groups of eight lanes: pairs, quads, half rows (common.h)
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0xB1, 0xF, 0xF, true));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x4E, 0xF, 0xF, true));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x141, 0xF, 0xF, true));
+    if ((tid & 7) == 0) group_max[tid >> 3] = top;
+    if (tid == 0) { sh_n = 0; sh_kth = 0; }
+    __syncthreads();
+    {                                                        // rank of this group's maximum, ties by the group's number
+      const int g = tid >> 3, g0 = (tid & 7) * 16;
+      const uint32_t mine = group_max[g];
+      int rank = 0;
+#pragma unroll
+      for (int j = 0; j < 16; j += 4) {
+        const u32x4 o = *(const u32x4*)&group_max[g0 + j];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rank += o[i] > mine || (o[i] == mine && g0 + j + i < g);
+      }
+      rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xF, 0xF, true);
+      rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, true);
+      rank += __builtin_amdgcn_update_dpp(0, rank, 0x141, 0xF, 0xF, true);
+      if ((tid & 7) == 0 && rank == 0) sh_best = mine;
+      if ((tid & 7) == 0 && rank == k - 1) sh_kth = mine;    // (no group where k exceeds their number: the bound stays 0)
+    }
+    __syncthreads();
     int turn = 0;
     auto reach = [&](uint32_t t) {                           // entries with key >= t (t > 0)
       int c = 0;
@@ -239,20 +272,22 @@ __device__ __forceinline__ void warp_softmax_row(const WarpArgs w, const int row
       for (int i = 0; i < 16; ++i) n += cnt16[turn][i];
       return n;
     };
-    uint32_t lo = 0, hi = order_key(best);
-    int c_lo = V, c_hi = reach(hi);
-    if (c_hi >= k) { lo = hi; c_lo = c_hi; c_hi = 0; }       // k or more entries equal the maximum
-    else {
-      while (c_lo > cap && hi - lo > 1) {
-        const uint32_t mid = lo + ((hi - lo) >> 1);
-        const int c = reach(mid);
-        if (c >= k) { lo = mid; c_lo = c; }
-        else { hi = mid; c_hi = c; }
+    uint32_t lo = sh_kth, hi = sh_best;
+    best = key_order(hi);
+    int c_lo = lo ? reach(lo) : V, c_hi = 0;
+    if (c_lo > cap) {
+      c_hi = reach(hi);
+      if (c_hi >= k) { lo = hi; c_lo = c_hi; c_hi = 0; }     // k or more entries equal the maximum
+      else {
+        while (c_lo > cap && hi - lo > 1) {
+          const uint32_t mid = lo + ((hi - lo) >> 1);
+          const int c = reach(mid);
+          if (c >= k) { lo = mid; c_lo = c; }
+          else { hi = mid; c_hi = c; }
+        }
       }
     }
     if (c_lo <= cap) {
-      if (tid == 0) sh_n = 0;
-      __syncthreads();
 #pragma unroll
       for (int e = 0; e < SP; ++e)
         if (tid + e * SBLOCK < V && key[e] >= lo)
@@ -285,33 +320,39 @@ __device__ __forceinline__ void warp_softmax_row(const WarpArgs w, const int row
       }
     }
   }
+  // The kernel is bound by instruction issue (four waves per SIMD), and a division or an exponential is ten instructions and more: a
+  // temperature of 1 divides nothing, and with top-k a wave passes over the steps in which it holds no kept entry (at most k
+  // of the row's 16 x SP; the largest entry is kept, so the maximum is known).
   const float T = w.temperature;
+  const bool scale = T != 1.0f;
   float z[SP];
   float mx = -INFINITY;
+  bool some[SP];
 #pragma unroll
   for (int e = 0; e < SP; ++e) {
     const int i = tid + e * SBLOCK;
-    z[e] = -INFINITY;
-    if (i < V) {
-      const uint32_t k = order_key(xv[e]);
-      const bool keep = !use_k || k > kth || (k == kth && i <= idxmax);
-      if (keep) z[e] = xv[e] / T;
-    }
+    const uint32_t k = order_key(xv[e]);
+    const bool keep = i < V && (!use_k || k > kth || (k == kth && i <= idxmax));
+    some[e] = !use_k || __any(keep);
+    z[e] = keep ? xv[e] : -INFINITY;
+    if (scale && some[e]) z[e] /= T;
     mx = fmaxf(mx, z[e]);
   }
-  mx = sblock_max(mx, s16);
+  mx = use_k ? (scale ? best / T : best) : sblock_max(mx, s16);
   float sum = 0.f;
 #pragma unroll
   for (int e = 0; e < SP; ++e) {
-    z[e] = (z[e] == -INFINITY) ? 0.f : expf(z[e] - mx);
+    if (some[e]) z[e] = (z[e] == -INFINITY) ? 0.f : expf(z[e] - mx);
+    else z[e] = 0.f;
     sum += z[e];
   }
   sum = sblock_sum(sum, s16);
+  const bool sound = sum > 0.f;                              // else every entry of the row is 0 / sum
 #pragma unroll
   for (int e = 0; e < SP; ++e) {
     const int i = tid + e * SBLOCK;
     if (i < V) {
-      const float q = z[e] / sum;
+      const float q = some[e] || !sound ? z[e] / sum : 0.f;
       p[i] = q;
       if (lds_probs) lds_probs[i] = q;                        // k_warp_accept: the draw reads the row from LDS
     }

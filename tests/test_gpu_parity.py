@@ -113,6 +113,28 @@ def test_top_k_cut_at_the_edges_of_the_candidate_set(k):
     assert np.abs(got - ref).max() < 1e-6
 
 
+@pytest.mark.parametrize("V,k", [(2, 1), (9, 5), (60, 25), (260, 50), (1030, 25), (6564, 25), (6564, 50), (6564, 128), (9000, 128), (16384, 300)])
+def test_top_k_cut_where_large_entries_share_their_threads(V, k):
+    """The kernel bounds the cut by the maxima of 128 groups of entries (i % 1024 // 8).  Rows whose large entries lie in one group,
+    in few groups, in exactly k groups, one per group, or are infinite; and vocabularies with fewer groups than k."""
+    import paper_2505_15380_amd as ssd
+    from oracle.warp import warp_probs
+    rng = np.random.default_rng(V + k)
+    z = rng.standard_normal((7, V)).astype(np.float32)
+    group = np.arange(V) % 1024 // 8
+    z[1, group == group.max() // 2] += 9.0
+    z[2, group < 5] += 9.0
+    z[3, group < k] += 9.0
+    z[4, group >= min(k, 128) - 1] -= 20.0
+    z[5, ::3] = -np.inf
+    z[6] = np.sort(z[6])
+    got = ssd.ssd_warp_probs(torch.from_numpy(z).cuda(), ssd.sample_config(top_k=k, temperature=0.9)).cpu().numpy()
+    ref = warp_probs(z.astype(np.float64), 0.9, k, False)
+    assert np.abs(got - ref).max() < 1e-6
+    kept = ref > 1e-30                       # (what lies far below the maximum underflows in single precision)
+    assert (got[kept] > 0).all() and (got[ref == 0] == 0).all()
+
+
 # ------------------------------------------------------------------------------ the whole verify step
 @pytest.mark.parametrize("beta", [0.0, 0.4])
 def test_tiny_fp32_verify_parity(beta):
