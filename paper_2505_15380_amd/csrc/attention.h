@@ -7,6 +7,8 @@
 // have one size, so what a row combines - and therefore its bits - does not depend on how many rows are verified
 // together; the size of k_attn_mfma's parts follows from the launch's shape.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 namespace ssd {
@@ -271,8 +273,8 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
 // ------------------------------------------------------------------------------------------------ matrix-core variant
 // The same operation for bf16 caches with 16-token blocks and head_dim 64 or 128.  The query rows that share keys - R rows
 // of a sequence x the G query heads of a group - form tiles of 16.  A workgroup takes WQ = 4 tiles and a part of the keys
-// (`part_keys`, cut at absolute positions); its 8 waves are 4 tiles x WK = 2 key groups, and key group k walks the part's
-// 64-key chunks k, k + WK, .. with a running (max, sum, weighted values) per row.  The key groups meet once in LDS.  Where
+// (`part_keys`, cut at absolute positions); its waves are 4 tiles x WK key groups, and key group k walks the part's
+// 64-key chunks k, k + WK, .. with a running (reference, sum, weighted values) per row.  The key groups meet once in LDS.  Where
 // one part covers all keys the row is finished here; else its partial goes to memory and k_attn_combine_parts merges
 // the parts in ascending order.
 //
@@ -286,16 +288,27 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
 // head size, 64 to 4000 cached positions, 1 to 64 sequences and scores of spread 0.5 to 6), which is the 2^-17 of the split
 // operands: 0.998 times (geometric mean) what fp32 sums of the unsplit weights give, and 1.000 times what accumulators that
 // start at zero give instead of minus the maximum.  (The fp32 sums cost 5 % with head size 128, nothing with 64.)
-// Keys and values go from the paged cache to LDS with direct loads, a chunk ahead.  What bounds a long prefix is issue: the
-// 16x16x32 matrix instructions (36 per wave and chunk, 16 cycles each) leave the vector unit (130 instructions and 16
-// exponentials) no slots, so the two add up; with few keys per workgroup it is the chain of dependent latencies.
-// 1024 rows of the 0.5B shape at 512 / 3072 cached positions: 20.9 / 46.6 us (with the parts, their merge and the sixteen-step
-// reductions of the kernel before it: 56 us on average over a prefill of 4096); 16 x 7 rows at about 2200: 10 + 3.6 us (15.6 + 4.7).
-constexpr int ATT_WAVES = 8, ATT_TILES = 4;              // waves and row tiles of a workgroup
+// Keys and values go from the paged cache to LDS with direct loads, a chunk ahead.  What bounds a long prefix is issue: beside the
+// 16x16x32 matrix instructions (36 per wave and chunk, 16 cycles each) a SIMD issues about two vector instructions for nothing, and
+// a wave has 80 a chunk, half of them for the split of P, and 16 exponentials.  With few keys per workgroup it is the chain of
+// dependent latencies, and the code itself, fetched cold by every launch.
+// So there are two forms.  WK = 2 takes short parts: eight waves, one copy of the loop, the reference is the running maximum.  WK = 4 takes
+// prompts whose parts have more than 16 chunks (and head size 64: 128 KB of LDS): sixteen waves to overlap matrix and vector
+// instructions, and the reference, the maximum of the row's first chunk, moves only to a score that exceeds it by ATT_LAZY, so that
+// the usual chunk asks each lane for its own largest score and no more (some row of sixteen has a new maximum in most chunks: a
+// maximum across lanes and 40 instructions of scaling).  The heaviest key then weighs anything up to 2^8 instead of 1, which the
+// truncating split holds exactly; the split of later chunks rounds hi to nearest in return (error against 64 bits 0.85 times the other
+// form's over 24 shapes; 1.02 times without).  1024 rows of the 0.5B shape at 0 / 1024 / 3072 cached positions: 14.6 / 22.8 / 38.7 us, with
+// WK = 2 15.8 / 25.0 / 47.1; the same form with WK = 2 14.6 / 24.2 / 43.1 but 0.5 us more for the batches' launches; 97 rows 7.7 against
+// 6.1.  Two row tiles per wave, which read keys and values half as often, took as long with as many waves and a quarter longer with half.
+constexpr int ATT_TILES = 4;                             // row tiles of a workgroup
+constexpr float ATT_LAZY = 8.0f;                         // weights may reach 2^8 before the reference moves (fp32 sums and the hi + lo split of
+                                                         // a weight are as exact at any scale)
 
-template <int HD>
-__global__ void __launch_bounds__(ATT_WAVES * 64, 2) k_attn_mfma(AttnArgs a) {
-  constexpr int WQ = ATT_TILES, WK = ATT_WAVES / WQ, KS = HD / 32, DT = HD / 16;
+template <int HD, int WK>
+__global__ void __launch_bounds__(ATT_TILES * WK * 64, WK) k_attn_mfma(AttnArgs a) {
+  constexpr int WQ = ATT_TILES, KS = HD / 32, DT = HD / 16;
+  constexpr bool LAZY = WK == 4;
   constexpr int NB = 2, NL = NB * KS;                      // blocks, and direct loads, of a wave and chunk
   static_assert(WQ == 4, "two waves of a key group load its keys, two its values");
   extern __shared__ u32x4 kvs[];                           // [key group][keys, values][buffer][block][KS][64]
@@ -370,22 +383,23 @@ __global__ void __launch_bounds__(ATT_WAVES * 64, 2) k_attn_mfma(AttnArgs a) {
     for (int ks = 0; ks < KS; ++ks)
       qf[ks] = split_bf16(__builtin_bit_cast(u32x4, qp[8 * ks] * scale2), __builtin_bit_cast(u32x4, qp[8 * ks + 1] * scale2));
   }
-  // running state of a row: mrow, and o and l (all four registers of l hold the row's sum: P times a matrix of ones)
+  // running state of a row: the reference mrow of its weights, and o and l (all four registers of l hold the row's sum: P times a matrix of ones)
   float mrow = 0.f;
-  bool first = true;                                       // the wave's first chunk sets the maximum, whatever its sign
   f32x4 o[DT], l = {0, 0, 0, 0};
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0, 0, 0, 0};
   const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u});
-  for (int it = 0; it < nit; ++it) {
+  // (`first`: a bool, or its value as a type where the first chunk is code of its own)
+  auto chunk = [&](int it, auto& first) {
+    constexpr bool later = std::is_same<decltype(first), std::false_type&>::value;
     // the chunk has arrived, and every wave of the group has read the one whose buffer the next request overwrites
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if (it + 1 < nit) { request(it + 1); look_up(min(it + 2, nit - 1)); }
     const int kbase = pbase + 64 * (it * WK + kg);
-    if (kbase > reach) continue;                           // (uniform over the wave; always so for a wave without rows)
-    // Scores minus the running maximum (the accumulators start at -mrow).  Element (tile t, register r): key
+    if (kbase > reach) return;                             // (uniform over the wave; always so for a wave without rows)
+    // Scores minus the row's reference (the accumulators start at -mrow).  Element (tile t, register r): key
     // kbase + 32 (t / 2) + 8 g + 4 (t % 2) + r of row c16.  Independent chains of matrix-core instructions side by side.
     const u32x4* kk = my + (it & 1) * (4 * KS * 64) + (8 * (c16 >> 2) + (c16 & 3)) * (4 * KS);       // row 8 (c16 / 4) + c16 % 4 of a pair
     const u32x4* vv = my + (2 + (it & 1)) * (4 * KS * 64) + (g >> 1) * (KS * 64) + 2 * c16 + (g & 1);
@@ -418,10 +432,12 @@ __global__ void __launch_bounds__(ATT_WAVES * 64, 2) k_attn_mfma(AttnArgs a) {
     for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[t][r]);
-    mx = max_over_groups(mx);
-    if (first || __any(mx > 0.f)) {                        // a new maximum: what is there shrinks
-      const float up = first ? (mx == -INFINITY ? 0.f : mx) : fmaxf(mx, 0.f), alpha = first ? 0.f : __builtin_amdgcn_exp2f(-up);
-      first = false;
+    constexpr float keep = LAZY ? ATT_LAZY : 0.f;
+    if (!LAZY) mx = max_over_groups(mx);                   // (taken in most chunks: better ahead of the branch)
+    if (first || __any(mx > keep)) {                       // the first scores, or larger ones: what is there shrinks
+      if (LAZY) mx = max_over_groups(mx);
+      const float up = first ? (mx == -INFINITY ? 0.f : mx) : LAZY ? (mx > keep ? mx : 0.f) : fmaxf(mx, 0.f), alpha = first ? 0.f : __builtin_amdgcn_exp2f(-up);
+      if constexpr (!LAZY) first = false;
       mrow += up;
       l *= alpha;
 #pragma unroll
@@ -437,7 +453,7 @@ __global__ void __launch_bounds__(ATT_WAVES * 64, 2) k_attn_mfma(AttnArgs a) {
       for (int r = 0; r < 4; ++r) s[t][r] = __builtin_amdgcn_exp2f(s[t][r]);
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
-      const SplitA pf = split_bf16(__builtin_bit_cast(u32x4, s[2 * p]), __builtin_bit_cast(u32x4, s[2 * p + 1]));
+      const SplitA pf = later ? split_bf16_near(s[2 * p], s[2 * p + 1]) : split_bf16(__builtin_bit_cast(u32x4, s[2 * p]), __builtin_bit_cast(u32x4, s[2 * p + 1]));
       bf16x8 vf[DT];
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) vf[dt] = __builtin_bit_cast(bf16x8, vv[p * (2 * KS * 64) + dt * 32]);
@@ -448,6 +464,15 @@ __global__ void __launch_bounds__(ATT_WAVES * 64, 2) k_attn_mfma(AttnArgs a) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pf.hi, o[dt], 0, 0, 0);
     }
+  };
+  if constexpr (LAZY) {
+    std::true_type first;
+    std::false_type later;
+    chunk(0, first);
+    for (int it = 1; it < nit; ++it) chunk(it, later);
+  } else {
+    bool first = true;
+    for (int it = 0; it < nit; ++it) chunk(it, first);
   }
   if (l[0] == 0.f) mrow = -1e30f;                          // no key of the row in this key group
   // key groups 1 .. WK-1 hand their state over, group 0 adds them in ascending order
@@ -490,7 +515,7 @@ __global__ void __launch_bounds__(ATT_WAVES * 64, 2) k_attn_mfma(AttnArgs a) {
   if (g == 0) { a.ml_part[pidx * 2] = mrow; a.ml_part[pidx * 2 + 1] = lr; }
 }
 
-// Merges a row's part partials (base-2 maxima) in ascending part order: HD / 4 lanes per (row, query head), four dims each.
+// Merges a row's part partials (base-2 references) in ascending part order: HD / 4 lanes per (row, query head), four dims each.
 template <int HD>
 __global__ void __launch_bounds__(BLOCK) k_attn_combine_parts(AttnArgs a) {
   constexpr int L = HD / 4;

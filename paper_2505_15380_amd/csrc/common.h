@@ -160,6 +160,22 @@ __device__ __forceinline__ SplitA split_bf16(const u32x4 a, const u32x4 b) {
   return s;
 }
 
+// The same with hi rounded to nearest: lo is half as large, and so is what its own rounding leaves (2^-18 relative).  As many
+// instructions; for operands that never leave the registers.
+__device__ __forceinline__ SplitA split_bf16_near(const f32x4 a, const f32x4 b) {
+  const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    h[i] = f2_to_bf16x2(x[2 * i], x[2 * i + 1]);
+    l[i] = f2_to_bf16x2(x[2 * i] - __uint_as_float(h[i] << 16), x[2 * i + 1] - __uint_as_float(h[i] & 0xFFFF0000u));       // exact differences
+  }
+  SplitA s;
+  s.hi = __builtin_bit_cast(bf16x8, u32x4{h[0], h[1], h[2], h[3]});
+  s.lo = __builtin_bit_cast(bf16x8, u32x4{l[0], l[1], l[2], l[3]});
+  return s;
+}
+
 // "Split rows": GEMM operand rows [M][K] kept as the matrix core takes them, for the kernels that serve many rows
 // (gemm_tile.h).  Value x of (row, k) is stored as hi = upper 16 bits of x and lo = bf16(x - hi); the fragment of row
 // tile mt = row / 16 and k-tile kt = k / 32 is 64 lanes x 8 bf16 with lane = row % 16 + 16 * ((k % 32) / 8), element k % 8:

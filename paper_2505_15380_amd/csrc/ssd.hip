@@ -688,20 +688,28 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
 // launch on every batch measured (16 x 7 rows at 256 to 4096 positions 2521 us a cycle either way, 64 x 8 at 128 to 1024 3536,
 // 8 x 9 of the 1.5B shape 3850); 48, 32 and 16 were up to 2, 5 and 8 % slower.
 constexpr int ATT_PLAN_CHUNKS = 64;
+template <int HD, int WK>
+static int launch_attn_mfma_parts(const AttnArgs& a, int n_tg, int nkv, int B, hipStream_t st) {
+  constexpr int LDS = WK * 2 * 2 * HD * 128;              // two buffers of 64 keys and 64 values per key group
+  static const hipError_t lds_ok =                        // more than 64 KB of dynamic LDS is opt-in, once per process
+      hipFuncSetAttribute((const void*)k_attn_mfma<HD, WK>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  if (lds_ok != hipSuccess) return fail(SSD_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(lds_ok));
+  hipLaunchKernelGGL((k_attn_mfma<HD, WK>), dim3(a.nparts * n_tg, nkv, B), dim3(ATT_TILES * WK * 64), LDS, st, a);
+  LAUNCH_CHECK();
+  return SSD_OK;
+}
 template <int HD>
-static int launch_attn_mfma(AttnArgs a, int nchunks, int plan_chunks, int nkv, int B, int M, int cus, hipStream_t st) {
-  constexpr int wk = ATT_WAVES / ATT_TILES;
+static int launch_attn_mfma(AttnArgs a, int nchunks, int plan_chunks, bool prompt, int nkv, int B, int M, int cus, hipStream_t st) {
+  constexpr int wk = 2;                                    // (parts are cut for two key groups whichever kernel takes them)
   const int n_tg = cdiv(cdiv(a.rows.R * (a.nq / nkv), 16), ATT_TILES);
   const int want = std::min(std::max(1, cus / (n_tg * nkv * B)), cdiv(plan_chunks, wk));
   const int part_chunks = cdiv(cdiv(plan_chunks, want), wk) * wk;
   a.part_keys = part_chunks * 64;
   a.nparts = cdiv(nchunks, part_chunks);
-  constexpr int LDS = wk * 2 * 2 * HD * 128;              // two buffers of 64 keys and 64 values per key group
-  static const hipError_t lds_ok =                        // more than 64 KB of dynamic LDS is opt-in, once per process
-      hipFuncSetAttribute((const void*)k_attn_mfma<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-  if (lds_ok != hipSuccess) return fail(SSD_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(lds_ok));
-  hipLaunchKernelGGL((k_attn_mfma<HD>), dim3(a.nparts * n_tg, nkv, B), dim3(ATT_WAVES * 64), LDS, st, a);
-  LAUNCH_CHECK();
+  int rc;
+  if constexpr (HD == 64) rc = prompt && part_chunks > 16 ? launch_attn_mfma_parts<HD, 4>(a, n_tg, nkv, B, st) : launch_attn_mfma_parts<HD, 2>(a, n_tg, nkv, B, st);
+  else rc = launch_attn_mfma_parts<HD, 2>(a, n_tg, nkv, B, st);
+  if (rc) return rc;
   if (a.nparts > 1) {
     hipLaunchKernelGGL((k_attn_combine_parts<HD>), dim3(cdiv(M * a.nq, BLOCK / (HD / 4))), dim3(BLOCK), 0, st, a);
     LAUNCH_CHECK();
@@ -710,9 +718,9 @@ static int launch_attn_mfma(AttnArgs a, int nchunks, int plan_chunks, int nkv, i
 }
 
 template <typename DT, int HD>
-static int launch_attn(AttnArgs a, int nchunks, int plan_chunks, int nkv, int B, int M, bool mfma, int cus, hipStream_t st) {
+static int launch_attn(AttnArgs a, int nchunks, int plan_chunks, bool prompt, int nkv, int B, int M, bool mfma, int cus, hipStream_t st) {
   if constexpr (std::is_same<DT, BF16>::value && (HD == 64 || HD == 128)) {
-    if (mfma && a.kv.bt == 16) return launch_attn_mfma<HD>(a, nchunks, plan_chunks, nkv, B, M, cus, st);
+    if (mfma && a.kv.bt == 16) return launch_attn_mfma<HD>(a, nchunks, plan_chunks, prompt, nkv, B, M, cus, st);
   }
   if constexpr (std::is_same<DT, F32>::value) {
     const int tiles = cdiv(a.rows.R * (a.nq / nkv), 16);
@@ -912,9 +920,9 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     a.split_kt = bf16 ? nqd / 32 : 0;
     {
       ProfScope ps(PROF_ATTN, st);
-      if (hd == 32) rc = launch_attn<DT, 32>(a, nchunks, plan_chunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
-      else if (hd == 64) rc = launch_attn<DT, 64>(a, nchunks, plan_chunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
-      else rc = launch_attn<DT, 128>(a, nchunks, plan_chunks, nkv, B, M, kv->attn_mfma, kv->cus, st);
+      if (hd == 32) rc = launch_attn<DT, 32>(a, nchunks, plan_chunks, pcap == 0, nkv, B, M, kv->attn_mfma, kv->cus, st);
+      else if (hd == 64) rc = launch_attn<DT, 64>(a, nchunks, plan_chunks, pcap == 0, nkv, B, M, kv->attn_mfma, kv->cus, st);
+      else rc = launch_attn<DT, 128>(a, nchunks, plan_chunks, pcap == 0, nkv, B, M, kv->attn_mfma, kv->cus, st);
     }
     if (rc) return rc;
 
