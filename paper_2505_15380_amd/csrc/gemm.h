@@ -42,7 +42,8 @@ struct GemmArgs {
   float* h;             // EPI_RESID: residual stream [M][N], updated
   const float* gain;    // fp32: gain of the norm before; bf16, EPI_RESID: gain of the norm that follows
   void* hg;             // EPI_RESID: h * gain as split rows
-  float* sumsq;         // [M][rms_d / 16] written by EPI_RESID, read by EPI_SWIGLU
+  float* sumsq;         // written by EPI_RESID, read by EPI_SWIGLU: [M][rms_d / 16], or [M][sum_pieces rounded up to 16]
+  int sum_pieces;       // bf16: > 0: pieces that a row's sum of squares is in; 0: one per 16 columns (EPI_RESID: any other value asks for pieces)
   int rms_d;            // columns of the normalised row; 0: the operand is normalised already
   float rms_eps;
 };

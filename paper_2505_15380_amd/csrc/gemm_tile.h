@@ -53,41 +53,84 @@ __device__ __forceinline__ RowDest row_dest(const GemmArgs& g, int row) {
 
 // 1 / r.m.s. of the rows of row tile mt for the epilogue's lanes (row = lane % 16), from the sums of squares that EPI_RESID left:
 // each lane group sums a quarter of a row's.  In two steps: the loads go out ahead of the operands', the sum is taken while
-// those travel.
+// those travel.  Two forms: a sum per 16 columns (up to 64 rows, where a few workgroups read them), or one per workgroup or pair of
+// tiles that made them, 16 bytes a lane: 56 scattered loads per row and workgroup cost gate / up of 1024 rows of width 896 2 us, of
+// width 1536 9 us.
 struct RowSums {
   const float* p;
   float x[16];
 };
+template <bool FINE>
 __device__ __forceinline__ RowSums row_sums_load(const GemmArgs& g, int mt) {
-  const int lane = threadIdx.x & 63, nt = g.rms_d >> 4;
+  const int lane = threadIdx.x & 63, lg = lane >> 4, row = min(mt * 16 + (lane & 15), g.M - 1);
   RowSums r;
-  r.p = g.sumsq + (size_t)min(mt * 16 + (lane & 15), g.M - 1) * nt + (lane >> 4);
+  if (FINE) {
+    const int nt = g.rms_d >> 4;
+    r.p = g.sumsq + (size_t)row * nt + lg;
 #pragma unroll
-  for (int u = 0; u < 16; ++u) r.x[u] = 4 * u + (lane >> 4) < nt ? r.p[4 * u] : 0.f;
+    for (int u = 0; u < 16; ++u) r.x[u] = 4 * u + lg < nt ? r.p[4 * u] : 0.f;
+  } else {
+    r.p = g.sumsq + (size_t)row * ((g.sum_pieces + 15) & ~15) + 4 * lg;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {                          // (what lies between the last piece and the next multiple of 16 was never written)
+      const f32x4 v = 16 * u < g.sum_pieces ? *(const f32x4*)(r.p + 16 * u) : f32x4{0, 0, 0, 0};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r.x[4 * u + i] = 16 * u + 4 * lg + i < g.sum_pieces ? v[i] : 0.f;
+    }
+  }
   return r;
 }
+template <bool FINE>
 __device__ __forceinline__ float row_inv_rms(const GemmArgs& g, const RowSums& r) {
-  const int nt = g.rms_d >> 4, lg = (threadIdx.x & 63) >> 4;
+  const int lg = (threadIdx.x & 63) >> 4;
   float s = 0.f;
 #pragma unroll
   for (int u = 0; u < 16; ++u) s += r.x[u];
-  for (int u0 = 16; 4 * u0 < nt; u0 += 8) {                // (d_model > 1024)
-    float y[8];
+  if (FINE) {
+    const int nt = g.rms_d >> 4;
+    for (int u0 = 16; 4 * u0 < nt; u0 += 8) {              // (d_model > 1024)
+      float y[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) y[u] = 4 * (u0 + u) + lg < nt ? r.p[4 * (u0 + u)] : 0.f;
+      for (int u = 0; u < 8; ++u) y[u] = 4 * (u0 + u) + lg < nt ? r.p[4 * (u0 + u)] : 0.f;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s += y[u];
+      for (int u = 0; u < 8; ++u) s += y[u];
+    }
+  } else {
+    for (int u = 64; u < g.sum_pieces; u += 16)            // (more than 64 pieces: d_model > 2048)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s += u + 4 * lg + i < g.sum_pieces ? r.p[u + i] : 0.f;
   }
   return 1.0f / sqrtf(sum_over_groups(s) / (float)g.rms_d + g.rms_eps);
 }
 
-// Epilogue of four consecutive features of one row: tile slot j < TN/2 (v0) and its partner j + TN/2 (v1); for partial
-// outputs two independent tiles.  `col` = 4 (lane / 16).
+// What EPI_RESID's epilogue of a pair of tiles needs from memory besides the sums: the residual stream and the gain of the lane's
+// features.  Requested ahead of the contraction, so that its latency is not one more link of the chain at the kernel's end (1024 rows
+// of width 896 in tiles of 4 x 4 11.0 -> 10.7 us, 97 rows 5.5 -> 5.3).
+struct ResidOperands {
+  f32x4 h[2], gain[2];
+};
 template <int EPI>
-__device__ __forceinline__ void tile_epilogue(const GemmArgs& g, int t0, int t1, int slice, int row, int col, f32x4 v0, f32x4 v1,
-                                              const RowDest rd, float inv) {
+__device__ __forceinline__ ResidOperands resid_operands(const GemmArgs& g, int t0, int t1, int row, int col) {
+  ResidOperands e;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int t = q ? t1 : t0, n = t * 16 + col;
+    const bool ok = EPI == EPI_RESID && row < g.M && t < (g.N + 15) >> 4;
+    e.h[q] = ok ? *(const f32x4*)(g.h + (size_t)row * g.N + n) : f32x4{0, 0, 0, 0};
+    e.gain[q] = ok ? *(const f32x4*)(g.gain + n) : f32x4{0, 0, 0, 0};
+  }
+  return e;
+}
+
+// Epilogue of four consecutive features of one row: tile slot j < TN/2 (v0) and its partner j + TN/2 (v1); for partial
+// outputs two independent tiles.  `col` = 4 (lane / 16).  EPI_RESID returns the lane's share of the row's sum of squares over them
+// (where the pieces are not 16 columns: else they are written here).
+template <int EPI>
+__device__ __forceinline__ float tile_epilogue(const GemmArgs& g, int t0, int t1, int slice, int row, int col, f32x4 v0, f32x4 v1,
+                                              const RowDest rd, const ResidOperands& e, float inv) {
   const int ntiles = (g.N + 15) >> 4;
   if (EPI == EPI_RESID) {                                  // (all lanes stay: the sums cross them)
+    float sum = 0.f;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const int t = q ? t1 : t0, n = t * 16 + col;
@@ -96,22 +139,24 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, int t0, int t1,
       float ss = 0.f;
       if (ok) {
         float* hp = g.h + (size_t)row * g.N + n;
-        const f32x4 gn = *(const f32x4*)(g.gain + n);
-        v += *(const f32x4*)hp;
+        v += e.h[q];
         *(f32x4*)hp = v;
 #pragma unroll
         for (int r = 0; r < 4; ++r) ss = fmaf(v[r], v[r], ss);
-        const f32x4 y = v * gn;
+        const f32x4 y = v * e.gain[q];
         bf16_t* o = (bf16_t*)g.hg + split_index(row, n, g.N >> 5);
         *(uint2*)o = hi_pairs(y);
         *(uint2*)(o + 512) = lo_pairs(y);
       }
-      ss = sum_over_groups(ss);
-      if (ok && col == 0) g.sumsq[(size_t)row * ntiles + t] = ss;
+      if (g.sum_pieces) sum += ss;
+      else {
+        ss = sum_over_groups(ss);
+        if (ok && col == 0) g.sumsq[(size_t)row * ntiles + t] = ss;
+      }
     }
-    return;
+    return sum;
   }
-  if (row >= g.M || t0 >= ntiles) return;
+  if (row >= g.M || t0 >= ntiles) return 0.f;
   if (EPI == EPI_PARTIAL) {
     float* o = g.out + (size_t)slice * g.out_split_stride + (size_t)row * g.ldo;
     const int n0 = t0 * 16 + col, n1 = t1 * 16 + col;
@@ -173,6 +218,12 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, int t0, int t1,
       }
     }
   }
+  return 0.f;
+}
+// The piece of a row's sum of squares that this wave has made (all lanes call it).
+__device__ __forceinline__ void store_row_sum(const GemmArgs& g, int row, int piece, int pieces, float sum) {
+  sum = sum_over_groups(sum);
+  if (row < g.M && (threadIdx.x & 63) < 16) g.sumsq[(size_t)row * ((pieces + 15) & ~15) + piece] = sum;
 }
 
 // ------------------------------------------------------------------------------------------ large tiles
@@ -222,11 +273,19 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
   RowDest rd[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) rd[i] = EPI == EPI_QKV ? row_dest(g, ((rowb * W + wave) * TM + i) * 16 + (lane & 15)) : RowDest{0, -1};
+  constexpr int PAIRS = (TN + 1) / 2;
+  ResidOperands ro[TM][PAIRS];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < PAIRS; ++j)
+      ro[i][j] = resid_operands<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), j + TN / 2 < TN ? slot_tile<EPI, TN>(colb, j + TN / 2, hd) : 0x7FFFFF,
+                                     ((rowb * W + wave) * TM + i) * 16 + (lane & 15), 4 * (lane >> 4));
   const bool scaled = EPI == EPI_SWIGLU && g.rms_d > 0;
   RowSums rs[TM];
   if (scaled)
 #pragma unroll
-    for (int i = 0; i < TM; ++i) rs[i] = row_sums_load(g, (rowb * W + wave) * TM + i);
+    for (int i = 0; i < TM; ++i) rs[i] = row_sums_load<false>(g, (rowb * W + wave) * TM + i);
 #pragma unroll
   for (int b = 0; b < NBUF - 1; ++b) request_w(min(b, nk - 1), b);
   asm volatile("" ::: "memory");                           // the first waits count the activations' requests as the later ones
@@ -235,7 +294,7 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
   for (int u = 0; u < UA; ++u) request_a(u, min(u, nk - 1));
   float inv[TM];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) inv[i] = scaled ? row_inv_rms(g, rs[i]) : 1.0f;
+  for (int i = 0; i < TM; ++i) inv[i] = scaled ? row_inv_rms<false>(g, rs[i]) : 1.0f;
   f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -277,12 +336,14 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int row = ((rowb * W + wave) * TM + i) * 16 + (lane & 15);
+    float sum = 0.f;
 #pragma unroll
     for (int j = 0; j < TN / 2; ++j)
-      tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), slot_tile<EPI, TN>(colb, j + TN / 2, hd), slice, row, 4 * (lane >> 4), acc[i][j],
-                         acc[i][j + TN / 2], rd[i], inv[i]);
+      sum += tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), slot_tile<EPI, TN>(colb, j + TN / 2, hd), slice, row, 4 * (lane >> 4), acc[i][j],
+                         acc[i][j + TN / 2], rd[i], ro[i][j], inv[i]);
     if (TN % 2)
-      tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, TN - 1, hd), 0x7FFFFF, slice, row, 4 * (lane >> 4), acc[i][TN - 1], acc[i][TN - 1], rd[i], inv[i]);
+      sum += tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, TN - 1, hd), 0x7FFFFF, slice, row, 4 * (lane >> 4), acc[i][TN - 1], acc[i][TN - 1], rd[i], ro[i][PAIRS - 1], inv[i]);
+    if (EPI == EPI_RESID) store_row_sum(g, row, colb, p.n_colb, sum);
   }
 }
 
@@ -320,14 +381,22 @@ __global__ void __launch_bounds__(W * 64, 1) k_gemm_kwave(GemmArgs g, TilePlan p
       a[u][m][1] = ap[m][(size_t)kt * 128 + 64];
     }
   };
+  // the waves' tiles meet in LDS, RPR row tiles at a time; unit (row tile, slot pair) u is summed and written by wave u mod W
+  constexpr int PAIRS = (TN + 1) / 2;
+  static_assert(EPI != EPI_RESID || (RPR == TM && TM * PAIRS <= W), "one unit per wave: its operands are requested here");
+  const int my_i = wave / PAIRS, my_j = wave - my_i * PAIRS, my_j1 = min(my_j + TN / 2 + TN % 2, TN - 1);
+  ResidOperands ro;
+  if (EPI == EPI_RESID && my_i < TM)
+    ro = resid_operands<EPI>(g, slot_tile<EPI, TN>(colb, my_j, hd), my_j1 == my_j ? 0x7FFFFF : slot_tile<EPI, TN>(colb, my_j1, hd),
+                             (rowb * TM + my_i) * 16 + (lane & 15), 4 * (lane >> 4));
   const bool scaled = EPI == EPI_SWIGLU && g.rms_d > 0 && wave < TM;
   RowSums rs;
-  if (scaled) rs = row_sums_load(g, rowb * TM + wave);
+  if (scaled) rs = row_sums_load<true>(g, rowb * TM + wave);
 #pragma unroll
   for (int u = 0; u < U; ++u)
     if (u < nw) request(u, u);
   if (scaled) {                                            // (read in the epilogue, after a barrier)
-    const float v = row_inv_rms(g, rs);
+    const float v = row_inv_rms<true>(g, rs);
     if (lane < 16) inv_rms[wave][lane] = v;
   }
   f32x4 acc[TM][TN];
@@ -358,8 +427,6 @@ __global__ void __launch_bounds__(W * 64, 1) k_gemm_kwave(GemmArgs g, TilePlan p
 #pragma unroll
   for (int u = 0; u < U - 1; ++u)
     if (kfull + u < nw) contract(u);
-  // the waves' tiles meet in LDS, RPR row tiles at a time; unit (row tile, slot pair) u is summed and written by wave u mod W
-  constexpr int PAIRS = (TN + 1) / 2;
 #pragma unroll
   for (int i0 = 0; i0 < TM; i0 += RPR) {
     RowDest rd[(RPR * PAIRS + W - 1) / W];
@@ -382,9 +449,10 @@ __global__ void __launch_bounds__(W * 64, 1) k_gemm_kwave(GemmArgs g, TilePlan p
         f32x4 v0 = red[0][i * TN + j][lane], v1 = red[0][i * TN + j1][lane];
 #pragma unroll
         for (int x = 1; x < W; ++x) { v0 += red[x][i * TN + j][lane]; v1 += red[x][i * TN + j1][lane]; }
-        tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), j1 == j ? 0x7FFFFF : slot_tile<EPI, TN>(colb, j1, hd), slice,
-                           (rowb * TM + i0 + i) * 16 + (lane & 15), 4 * (lane >> 4), v0, v1, rd[q],
+        const float sum = tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), j1 == j ? 0x7FFFFF : slot_tile<EPI, TN>(colb, j1, hd), slice,
+                           (rowb * TM + i0 + i) * 16 + (lane & 15), 4 * (lane >> 4), v0, v1, rd[q], ro,
                            EPI == EPI_SWIGLU && g.rms_d > 0 ? inv_rms[i0 + i][lane & 15] : 1.0f);
+        if (EPI == EPI_RESID && g.sum_pieces) store_row_sum(g, (rowb * TM + i) * 16 + (lane & 15), colb * PAIRS + j, p.n_colb * PAIRS, sum);
       }
     }
   }

@@ -601,7 +601,8 @@ static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStrea
   TilePlan p{};
   for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
     const Shape& c = shapes[i];
-    const bool ok = EPI == EPI_PARTIAL ? c.tn == 4 || c.tn == 7 || c.tn == 8 : EPI == EPI_SWIGLU ? c.tn != 7 && !(c.tm == 2 && c.tn == 8) : c.tn == 4;
+    const bool ok = EPI == EPI_PARTIAL ? c.tn == 4 || c.tn == 7 || c.tn == 8 : EPI == EPI_SWIGLU ? c.tn != 7 && !(c.tm == 2 && c.tn == 8)
+                                       : EPI == EPI_QKV ? c.tn == 4 && c.w == 4 : c.w == 4 && (c.tn == 4 || c.tn == 6 || c.tn == 8);
     if (!ok) continue;
     for (int ns = 1; ns <= std::min(8, max_slices) && (ns == 1 || KT / ns >= 7); ns *= 2) {
       const TilePlan q = gemm_plan<EPI>(g, c.tm * c.w, c.tn, ns);
@@ -629,16 +630,19 @@ static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStrea
   } else if constexpr (EPI == EPI_PARTIAL) {
     TILE(1, 7, 4); else TILE(1, 8, 4); else TILE(1, 7, 8); else TILE(1, 8, 8); else TILE(2, 8, 8);
     else TILE_DEEP(7); else TILE_DEEP(8);
+  } else if constexpr (EPI == EPI_RESID) {
+    TILE(1, 6, 4); else TILE(1, 8, 4); else TILE_DEEP(6); else TILE_DEEP(8);
   }
 #undef TILE
 #undef TILE_DEEP
   LAUNCH_CHECK();
-  return p.n_slices;
+  return EPI == EPI_RESID ? p.n_colb : p.n_slices;
 }
 
 // Launch of a bf16 GEMM: picks the kernel, the tile and the k-slices from the sizes alone.  Returns the number of k-slices (1 unless
-// `max_slices` allows more: outputs that are k-split partials).
-// Few rows (up to 64; for the QKV and output projections, whose k range is not split over workgroups, up to 512): k_gemm_kwave
+// `max_slices` allows more: outputs that are k-split partials); EPI_RESID: of the pieces of a row's sum of squares.
+// Few rows (up to 64; for the QKV and output projections, whose k range is not split over workgroups, up to 512, and the output
+// projection as long as tiles of 4 x 4 fill one round: 1024 rows of width 896 10.8 us, 12.0 with k_gemm_tile; of width 1536 26 and 21): k_gemm_kwave
 // with the smallest tile that leaves no more workgroups than compute units.  What bounds it is how long a workgroup's
 // operand stream takes, so the work is spread as far as one round of workgroups allows; k-split outputs get 8 slices
 // (4 where k is short) while that round lasts.
@@ -646,10 +650,7 @@ template <int EPI>
 static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t st) {
   const int KT = g.K / 32, MT = cdiv(g.M, 16);
   constexpr bool whole_k = EPI == EPI_QKV || EPI == EPI_RESID;
-  if (MT > (whole_k ? 32 : 4)) {
-    if constexpr (EPI == EPI_RESID) return fail(SSD_ENOSUP, "the projection with a residual takes up to 512 rows");     // (its callers' limit)
-    else return launch_gemm_tile<EPI>(g, cus, max_slices, st);
-  }
+  if (MT > (whole_k ? 32 : 4) && !(EPI == EPI_RESID && plan_wgs(gemm_plan<EPI>(g, 4, 4, 1)) <= cus)) return launch_gemm_tile<EPI>(g, cus, max_slices, st);
 #define KWAVE(TM, TN, U)                                                                             \
   if (tm == TM && tn == TN) hipLaunchKernelGGL((k_gemm_kwave<EPI, TM, TN, 8, U>), dim3(8 * p.per_xcd), dim3(512), 0, st, g, p)
   static const int shapes[][2] = {{1, 2}, {2, 2}, {1, 4}, {3, 2}, {1, 6}, {2, 4}, {2, 6}, {3, 4}, {4, 4}, {3, 6}, {4, 6}};   // by area
@@ -676,7 +677,7 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
   else if constexpr (EPI == EPI_SWIGLU) { KWAVE(1, 6, 4); else KWAVE(2, 6, 2); else KWAVE(3, 6, 1); else KWAVE(4, 6, 1); }
   else { KWAVE(4, 4, 2); }
   LAUNCH_CHECK();
-  return p.n_slices;
+  return EPI == EPI_RESID ? p.n_colb * (tn / 2) : p.n_slices;
 #undef KWAVE
 }
 
@@ -889,17 +890,16 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
   const void* const normed = bf16 ? (const void*)kv->xn : kv->h;           // fp32: the GEMM normalises its operand itself
   const size_t part_stride = (size_t)M * d;
   const int pairs_d = cdiv(d, 32);
-  // Up to 512 rows the output projection is not k-split: its epilogue adds the residual and prepares the norm before gate /
-  // up, and no add + norm kernel runs between them.  With more rows the unsplit projection leaves too few workgroups
-  // (1024 rows of the 1.5B shape: 24.8 us against 15 for two slices and 9 for the add + norm kernel).
-  const bool fused_norm = !bf16 || M <= 512;
+  // The output projection is not k-split: its epilogue adds the residual and prepares the norm before gate / up, and no add + norm
+  // kernel runs between them (1024 rows: 10.8 us of width 896 and 21.4 of 1536, where two k-slices and the add + norm kernel took 9.8 + 7.6
+  // and 16.2 + 12).
   auto add_norm = [&](int n_part_, const float* gain) -> int {
     if (!bf16) return SSD_OK;
     hipLaunchKernelGGL(k_add_norm, dim3(M), row_block, 0, st, kv->h, kv->part, n_part_, part_stride, gain, c.rms_eps, (bf16_t*)kv->xn, d);
     LAUNCH_CHECK();
     return SSD_OK;
   };
-  int n_part = 0;
+  int n_part = 0, pieces = 0;
   int rc;
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW& L = m->layers[l];
@@ -934,21 +934,18 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
       g.h = kv->h;
       if constexpr (!bf16) {
         rc = launch_gemm_f32<EPI_RESID>(g, pairs_d, st);
-      } else if (fused_norm) {
-        g.gain = L.ln2; g.hg = kv->xn; g.sumsq = kv->part;
-        rc = std::min(0, launch_gemm<EPI_RESID>(g, kv->cus, 1, st));
       } else {
-        n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, MAX_SPLITS, st);
-        rc = std::min(0, n_part);
+        g.gain = L.ln2; g.hg = kv->xn; g.sumsq = kv->part; g.sum_pieces = M > 64 ? 1 : 0;        // (gate / up by k_gemm_kwave reads 16-column sums)
+        rc = launch_gemm<EPI_RESID>(g, kv->cus, 1, st);
+        if (rc > 0) { if (M > 64) pieces = rc; rc = SSD_OK; }
       }
     }
     if (rc) return rc;
-    if (!fused_norm && (rc = add_norm(n_part, L.ln2))) return rc;
 
     g = g0;                                                // gate / up + SwiGLU
     g.A = normed; g.W0 = L.wgate; g.W1 = L.wup; g.N = c.d_ffn; g.K = d; g.act = kv->act;
     g.act_split_kt = bf16 ? c.d_ffn / 32 : 0;
-    g.sumsq = kv->part; g.rms_d = fused_norm ? d : 0;
+    g.sumsq = kv->part; g.rms_d = bf16 ? d : 0; g.sum_pieces = pieces;
     {
       ProfScope ps(PROF_GATEUP, st);
       if constexpr (bf16) rc = std::min(0, launch_gemm<EPI_SWIGLU>(g, kv->cus, 1, st));

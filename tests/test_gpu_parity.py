@@ -224,6 +224,21 @@ def test_narrowest_models(dtype, d, hd, ffn, K):
     pair.check_free_stack()
 
 
+@pytest.mark.parametrize("d,rows", [(32, 65), (96, 80), (544, 64), (544, 65), (1056, 513), (2112, 81), (1600, 1009)])
+def test_norm_between_the_projections_of_a_prompt(d, rows):
+    """The output projection leaves a row's sum of squares in pieces that gate / up adds: one per 16 columns up to 64 rows, above that one
+    per pair of tiles or per workgroup - fewer than 16 pieces, ragged, more than 64 (d = 2112), both kernels (1600 x 1009 does not
+    fit one round of the first).  Two layers: keys and values of the second against the oracle with the cache's format."""
+    from tests.parity import Pair
+    shape = dict(n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=96, vocab=41, n_embed=43, dtype="bf16",
+                 qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
+    pair = Pair(None, 85, rows + 32, max_rows=1024, shape=shape, store="bf16")
+    pair.prefill(0, np.random.default_rng(86).integers(0, 43, rows + 1))
+    assert pair.kv.last_forward_path() == 1
+    pair.check_state(0, 2e-2)
+    pair.check_free_stack()
+
+
 # ---- the barrier-free persistent forward (bf16 shapes, <= 16 rows) ------------------------------------------------
 @pytest.mark.gpu
 @pytest.mark.parametrize("n_prefix,K", [(250, 4), (254, 12), (600, 4), (1290, 7), (1532, 7)])
