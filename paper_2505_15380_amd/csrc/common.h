@@ -35,19 +35,6 @@ struct BF16 {
   static __device__ __forceinline__ void st(T* p, float v) { *p = f_to_bf16(v); }
 };
 
-// Butterfly reductions over the 64 lanes of a wave: every lane ends with the same value, and the
-// association order is fixed, so results do not depend on anything but the inputs.
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-  return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
-  return v;
-}
-
 // Philox-4x32-10 (Salmon et al., SC'11).  Counter (slot, seq, step_lo, step_hi), key (seed_lo, seed_hi).
 // Returns output word 0; the uniform of a slot is its top 24 bits times 2^-24.
 __device__ __forceinline__ uint32_t philox_word0(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
@@ -118,6 +105,44 @@ __device__ __forceinline__ float row16_sum(float v) {
   v += dpp_f<0x141>(v);      // row_half_mirror
   v += dpp_f<0x140>(v);      // row_mirror
   return v;
+}
+
+// Butterfly reductions over the 64 lanes of a wave: every lane ends with the same value, and the association order is fixed (lanes
+// l ^ 32, l ^ 16, l ^ 8, l ^ 4, l ^ 2, l ^ 1), so results do not depend on anything but the inputs.  Without LDS shuffles, whose
+// latency of more than a hundred cycles a step was most of a reduction.  (A rotation by 8 within 16 lanes is l ^ 8; one by 4 brings the
+// value of l ^ 4 or of l ^ 12, which are the same after that step.)
+template <typename OP>
+__device__ __forceinline__ float wave_reduce(float v, OP op) {
+  auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  v = op(v, dpp_f<0x128>(v));          // row_ror:8
+  v = op(v, dpp_f<0x124>(v));          // row_ror:4
+  v = op(v, dpp_f<0x4E>(v));           // quad_perm [2,3,0,1]
+  return op(v, dpp_f<0xB1>(v));        // quad_perm [1,0,3,2]
+}
+__device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, [](float x, float y) { return x + y; }); }
+__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, [](float x, float y) { return fmaxf(x, y); }); }
+
+// Inclusive prefix sum over the 64 lanes of a wave (integers: exact in any order): within rows of 16 lanes by row_shr, then the
+// totals of the rows before.
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xF, 0xF, true), hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, 0xF, 0xF, true);
+  return ((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo;
+}
+__device__ __forceinline__ unsigned long long lane_u64(unsigned long long v, int lane) {
+  return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+}
+__device__ __forceinline__ unsigned long long wave_inclusive_scan(unsigned long long v) {
+  v += dpp_u64<0x111>(v);              // row_shr:1
+  v += dpp_u64<0x112>(v);
+  v += dpp_u64<0x114>(v);
+  v += dpp_u64<0x118>(v);
+  const unsigned long long r0 = lane_u64(v, 15), r1 = r0 + lane_u64(v, 31), r2 = r1 + lane_u64(v, 47);
+  const int row = (threadIdx.x & 63) >> 4;
+  return v + (row == 0 ? 0ull : row == 1 ? r0 : row == 2 ? r1 : r2);
 }
 
 // All-reduce over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the lanes of a matrix-core tile that hold one row).

@@ -559,6 +559,15 @@ static int kv_check_room(ssd_kv* kv, int seq0, int B, int R, hipStream_t st) {
   return fail(SSD_ENOMEM, "KV cache cannot hold %d more positions for sequences %d..%d", R, seq0, seq0 + B - 1);
 }
 
+// The sampler kernels are unrolled over a thread's entries of the vocabulary: 1, 8 or 16 (what is not needed is instructions to fetch
+// and to pass over: one row of a vocabulary of 512 with its draw 8.1 us with 8, 4.9 with 1).
+#define SAMPLER(kernel, V, blocks, st, ...)                                                                              \
+  do {                                                                                                                   \
+    if ((V) <= SBLOCK) hipLaunchKernelGGL(kernel<1>, dim3(blocks), dim3(SBLOCK), 0, st, __VA_ARGS__);                     \
+    else if ((V) <= 8 * SBLOCK) hipLaunchKernelGGL(kernel<8>, dim3(blocks), dim3(SBLOCK), 0, st, __VA_ARGS__);            \
+    else hipLaunchKernelGGL(kernel<16>, dim3(blocks), dim3(SBLOCK), 0, st, __VA_ARGS__);                                  \
+  } while (0)
+
 // ------------------------------------------------------------------------------------------------ forward
 template <int EPI>
 static int launch_gemm_f32(const GemmArgs& g, int items, hipStream_t st) {
@@ -1063,8 +1072,7 @@ static int step(ssd_model* m, ssd_kv* kv, int B, int K, const int32_t* dev_x, co
   }
   const bool one_row = probs_last_row_only || (K == 0 && pcap == 1);     // one row per sequence: fused with the sampling
   if (!one_row) {
-    if (w.V <= 8 * SBLOCK) hipLaunchKernelGGL(k_warp_softmax<8>, dim3(M), dim3(SBLOCK), 0, st, w);
-    else hipLaunchKernelGGL(k_warp_softmax<16>, dim3(M), dim3(SBLOCK), 0, st, w);
+    SAMPLER(k_warp_softmax, V, M, st, w);
     LAUNCH_CHECK();
   }
   a.pd = dev_pd; a.x = dev_x; a.uniforms = nullptr; a.seed = cfg->seed; a.step = step_ctr;
@@ -1074,14 +1082,8 @@ static int step(ssd_model* m, ssd_kv* kv, int B, int K, const int32_t* dev_x, co
   a.kv = kv->v; a.seq0 = 0;
   a.ticket = kv->ticket_alt ? kv->ticket_alt : kv->v.ctl + 2;
   a.slot_base = slot_base;
-  const bool sp8 = a.V <= 8 * SBLOCK;
-  if (one_row) {
-    if (sp8) hipLaunchKernelGGL(k_warp_accept<8>, dim3(B), dim3(SBLOCK), 0, st, w, a);
-    else hipLaunchKernelGGL(k_warp_accept<16>, dim3(B), dim3(SBLOCK), 0, st, w, a);
-  } else {
-    if (sp8) hipLaunchKernelGGL(k_accept<8>, dim3(B), dim3(SBLOCK), 0, st, a);
-    else hipLaunchKernelGGL(k_accept<16>, dim3(B), dim3(SBLOCK), 0, st, a);
-  }
+  if (one_row) SAMPLER(k_warp_accept, V, B, st, w, a);
+  else SAMPLER(k_accept, V, B, st, a);
   LAUNCH_CHECK();
   return SSD_OK;
 }
@@ -1247,8 +1249,7 @@ extern "C" int ssd_verify_from_probs(const float* dev_pt, const float* dev_pd, c
   a.pt = dev_pt; a.pt_seq_stride = (size_t)(K + 1) * V; a.pd = dev_pd; a.x = dev_tokens; a.uniforms = dev_uniforms;
   a.B = B; a.K = K; a.V = V; a.beta = beta; a.n_acc = dev_n_accepted; a.next_tok = dev_next_token; a.tok_stride = 1;
   a.flags = dev_flags;
-  if (a.V <= 8 * SBLOCK) hipLaunchKernelGGL(k_accept<8>, dim3(B), dim3(SBLOCK), 0, (hipStream_t)stream, a);
-  else hipLaunchKernelGGL(k_accept<16>, dim3(B), dim3(SBLOCK), 0, (hipStream_t)stream, a);
+  SAMPLER(k_accept, V, B, (hipStream_t)stream, a);
   LAUNCH_CHECK();
   return SSD_OK;
 }
@@ -1261,8 +1262,7 @@ extern "C" int ssd_warp_probs(const float* dev_logits, int rows, int V, const ss
   WarpArgs w;
   w.logits = dev_logits; w.ld = V; w.V = V; w.temperature = cfg->temperature; w.top_k = cfg->top_k; w.greedy = cfg->greedy;
   w.probs = dev_probs; w.probs_stride = V;
-  if (w.V <= 8 * SBLOCK) hipLaunchKernelGGL(k_warp_softmax<8>, dim3(rows), dim3(SBLOCK), 0, (hipStream_t)stream, w);
-  else hipLaunchKernelGGL(k_warp_softmax<16>, dim3(rows), dim3(SBLOCK), 0, (hipStream_t)stream, w);
+  SAMPLER(k_warp_softmax, V, rows, (hipStream_t)stream, w);
   LAUNCH_CHECK();
   return SSD_OK;
 }
