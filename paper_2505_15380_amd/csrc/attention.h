@@ -197,6 +197,12 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
 #pragma unroll
       for (int s = 0; s < DT; ++s) k[t][s] = kp[s * 4];
     }
+    f32x4 v[DT][4];                                        // (requested with the keys: their latency is then that of one load, not of two)
+#pragma unroll
+    for (int s = 0; s < DT; ++s)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        v[s][t] = *(const f32x4*)(pool + kv_offset(a.kv, a.layer, 1, max(blk[t], 0), kvh, 0) + (s * 16 + li) * 16 + kg * 4);
     if (p0 > pos_max) break;
     f32x4 w[4];
     float mx = mrow;
@@ -232,10 +238,9 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int pv = p0 + t * 16 + kg * 4;
-        const f32x4 v = *(const f32x4*)(pool + kv_offset(a.kv, a.layer, 1, max(blk[t], 0), kvh, 0) + (s * 16 + li) * 16 + kg * 4);
 #pragma unroll
         for (int e = 0; e < 4; ++e)                        // what lies beyond may never have been written
-          o[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(blk[t] >= 0 && pv + e <= pos_max ? v[e] : 0.f, w[t][e], o[s], 0, 0, 0);
+          o[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(blk[t] >= 0 && pv + e <= pos_max ? v[s][t][e] : 0.f, w[t][e], o[s], 0, 0, 0);
       }
     }
   }
