@@ -277,8 +277,8 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
 
 // ------------------------------------------------------------------------------------------------ matrix-core variant
 // The same operation for bf16 caches with 16-token blocks and head_dim 64 or 128.  The query rows that share keys - R rows
-// of a sequence x the G query heads of a group - form tiles of 16.  A workgroup takes WQ = 4 tiles and a part of the keys
-// (`part_keys`, cut at absolute positions); its waves are 4 tiles x WK key groups, and key group k walks the part's
+// of a sequence x the G query heads of a group - form tiles of 16.  A workgroup takes WQ tiles and a part of the keys
+// (`part_keys`, cut at absolute positions); its waves are WQ tiles x WK key groups, and key group k walks the part's
 // 64-key chunks k, k + WK, .. with a running (reference, sum, weighted values) per row.  The key groups meet once in LDS.  Where
 // one part covers all keys the row is finished here; else its partial goes to memory and k_attn_combine_parts merges
 // the parts in ascending order.
@@ -297,25 +297,24 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
 // 16x16x32 matrix instructions (36 per wave and chunk, 16 cycles each) a SIMD issues about two vector instructions for nothing, and
 // a wave has 80 a chunk, half of them for the split of P, and 16 exponentials.  With few keys per workgroup it is the chain of
 // dependent latencies, and the code itself, fetched cold by every launch.
-// So there are two forms.  WK = 2 takes short parts: eight waves, one copy of the loop, the reference is the running maximum.  WK = 4 takes
-// prompts whose parts have more than 16 chunks (and head size 64: 128 KB of LDS): sixteen waves to overlap matrix and vector
+// So there are two forms.  Eight waves (4 tiles x 2 key groups, or 2 x 4: the launch's choice) take short parts: one copy of the loop,
+// the reference is the running maximum.  4 x 4 takes prompts whose parts have more than 16 chunks (and head size 64: 128 KB of LDS): sixteen waves to overlap matrix and vector
 // instructions, and the reference, the maximum of the row's first chunk, moves only to a score that exceeds it by ATT_LAZY, so that
 // the usual chunk asks each lane for its own largest score and no more (some row of sixteen has a new maximum in most chunks: a
 // maximum across lanes and 40 instructions of scaling).  The heaviest key then weighs anything up to 2^8 instead of 1, which the
 // truncating split holds exactly; the split of later chunks rounds hi to nearest in return (error against 64 bits 0.85 times the other
 // form's over 24 shapes; 1.02 times without).  1024 rows of the 0.5B shape at 0 / 1024 / 3072 cached positions: 14.6 / 22.8 / 38.7 us, with
-// WK = 2 15.8 / 25.0 / 47.1; the same form with WK = 2 14.6 / 24.2 / 43.1 but 0.5 us more for the batches' launches; 97 rows 7.7 against
+// 4 x 2 15.8 / 25.0 / 47.1; the same form with 4 x 2 14.6 / 24.2 / 43.1 but 0.5 us more for the batches' launches; 97 rows 7.7 against
 // 6.1.  Two row tiles per wave, which read keys and values half as often, took as long with as many waves and a quarter longer with half.
-constexpr int ATT_TILES = 4;                             // row tiles of a workgroup
 constexpr float ATT_LAZY = 8.0f;                         // weights may reach 2^8 before the reference moves (fp32 sums and the hi + lo split of
                                                          // a weight are as exact at any scale)
 
-template <int HD, int WK>
-__global__ void __launch_bounds__(ATT_TILES * WK * 64, WK) k_attn_mfma(AttnArgs a) {
-  constexpr int WQ = ATT_TILES, KS = HD / 32, DT = HD / 16;
-  constexpr bool LAZY = WK == 4;
-  constexpr int NB = 2, NL = NB * KS;                      // blocks, and direct loads, of a wave and chunk
-  static_assert(WQ == 4, "two waves of a key group load its keys, two its values");
+template <int HD, int WQ, int WK>
+__global__ void __launch_bounds__(WQ * WK * 64, WQ * WK / 4) k_attn_mfma(AttnArgs a) {
+  constexpr int KS = HD / 32, DT = HD / 16;
+  constexpr bool LAZY = WQ * WK == 16;
+  constexpr int NB = 8 / WQ;                               // blocks that a wave loads of a chunk: half of a key group's waves keys, half values
+  static_assert(WQ == 2 || WQ == 4, "");
   extern __shared__ u32x4 kvs[];                           // [key group][keys, values][buffer][block][KS][64]
   const int part = blockIdx.x % a.nparts, tgroup = blockIdx.x / a.nparts, kvh = blockIdx.y, brel = blockIdx.z;
   const int seq = a.rows.seq0 + brel;
@@ -341,7 +340,8 @@ __global__ void __launch_bounds__(ATT_TILES * WK * 64, WK) k_attn_mfma(AttnArgs 
   // Direct loads: each brings 1 KB of consecutive memory of one block (sixteen lanes that touch sixteen rows would load at a
   // quarter of the rate).  Keys are parked row by row with the 16-byte units of row t of a block permuted by XOR with
   // (t & 3) + 4 (t / 8), so that the rows of a key tile read their units from distinct banks; values as they are, dim by dim.
-  const bool values = wq >= 2;
+  const bool values = wq >= WQ / 2;
+  const int b0 = NB * (wq % (WQ / 2));                     // first of this wave's blocks of a chunk
   const size_t block_elems = (size_t)nkv * 16 * HD, plane = (size_t)a.kv.n_blocks * block_elems;
   const bf16_t* pool = (const bf16_t*)a.kv.pool + (size_t)(2 * a.layer + (values ? 1 : 0)) * plane + (size_t)kvh * 16 * HD;
   int voff[KS];
@@ -356,13 +356,13 @@ __global__ void __launch_bounds__(ATT_TILES * WK * 64, WK) k_attn_mfma(AttnArgs 
   const int last_bi = min(a.kv.mbps - 1, wg_reach >> 4);
   int blk[NB];                                             // block ids of what this wave requests next
   auto look_up = [&](int it) {                             // ... which is its share of this key group's chunk of iteration `it`
-    const int bi = (pbase >> 4) + 4 * (it * WK + kg) + 2 * (wq & 1);
+    const int bi = (pbase >> 4) + 4 * (it * WK + kg) + b0;
 #pragma unroll
     for (int t = 0; t < NB; ++t) blk[t] = table[min(bi + t, last_bi)];
   };
   u32x4* my = kvs + (size_t)kg * (4 * 4 * KS * 64);
   auto request = [&](int it) {
-    u32x4* dst = my + ((values ? 2 : 0) + (it & 1)) * (4 * KS * 64) + 2 * (wq & 1) * (KS * 64);
+    u32x4* dst = my + ((values ? 2 : 0) + (it & 1)) * (4 * KS * 64) + b0 * (KS * 64);
 #pragma unroll
     for (int t = 0; t < NB; ++t)
 #pragma unroll

@@ -698,27 +698,35 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
 // launch on every batch measured (16 x 7 rows at 256 to 4096 positions 2521 us a cycle either way, 64 x 8 at 128 to 1024 3536,
 // 8 x 9 of the 1.5B shape 3850); 48, 32 and 16 were up to 2, 5 and 8 % slower.
 constexpr int ATT_PLAN_CHUNKS = 64;
-template <int HD, int WK>
+template <int HD, int WQ, int WK>
 static int launch_attn_mfma_parts(const AttnArgs& a, int n_tg, int nkv, int B, hipStream_t st) {
   constexpr int LDS = WK * 2 * 2 * HD * 128;              // two buffers of 64 keys and 64 values per key group
   static const hipError_t lds_ok =                        // more than 64 KB of dynamic LDS is opt-in, once per process
-      hipFuncSetAttribute((const void*)k_attn_mfma<HD, WK>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+      hipFuncSetAttribute((const void*)k_attn_mfma<HD, WQ, WK>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
   if (lds_ok != hipSuccess) return fail(SSD_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(lds_ok));
-  hipLaunchKernelGGL((k_attn_mfma<HD, WK>), dim3(a.nparts * n_tg, nkv, B), dim3(ATT_TILES * WK * 64), LDS, st, a);
+  hipLaunchKernelGGL((k_attn_mfma<HD, WQ, WK>), dim3(a.nparts * n_tg, nkv, B), dim3(WQ * WK * 64), LDS, st, a);
   LAUNCH_CHECK();
   return SSD_OK;
 }
 template <int HD>
 static int launch_attn_mfma(AttnArgs a, int nchunks, int plan_chunks, bool prompt, int nkv, int B, int M, int cus, hipStream_t st) {
-  constexpr int wk = 2;                                    // (parts are cut for two key groups whichever kernel takes them)
-  const int n_tg = cdiv(cdiv(a.rows.R * (a.nq / nkv), 16), ATT_TILES);
+  const int tiles = cdiv(a.rows.R * (a.nq / nkv), 16);
+  // Two tiles x four key groups (head size 64) where workgroups of four tiles would be for a quarter to half of the device: a chain
+  // of half as many chunks, on twice the compute units where there are tiles for them (64 sequences x 8 rows at 128 to 1024 positions
+  // 15.7 -> 13.6 us a launch).  With fewer workgroups than that the parts fill the device, and four tiles x two groups take 11.7 us for
+  // 16 sequences x 7 rows where two x four take 13.0.
+  const int four = B * nkv * cdiv(tiles, 4);
+  const bool narrow = HD == 64 && four <= cus / 2 && four >= cus / 4;
+  const int wq = narrow ? 2 : 4, wk = narrow ? 4 : 2, n_tg = cdiv(tiles, wq);
   const int want = std::min(std::max(1, cus / (n_tg * nkv * B)), cdiv(plan_chunks, wk));
   const int part_chunks = cdiv(cdiv(plan_chunks, want), wk) * wk;
   a.part_keys = part_chunks * 64;
   a.nparts = cdiv(nchunks, part_chunks);
   int rc;
-  if constexpr (HD == 64) rc = prompt && part_chunks > 16 ? launch_attn_mfma_parts<HD, 4>(a, n_tg, nkv, B, st) : launch_attn_mfma_parts<HD, 2>(a, n_tg, nkv, B, st);
-  else rc = launch_attn_mfma_parts<HD, 2>(a, n_tg, nkv, B, st);
+  if constexpr (HD == 64)
+    rc = narrow ? launch_attn_mfma_parts<HD, 2, 4>(a, n_tg, nkv, B, st)
+         : prompt && part_chunks > 16 ? launch_attn_mfma_parts<HD, 4, 4>(a, n_tg, nkv, B, st) : launch_attn_mfma_parts<HD, 4, 2>(a, n_tg, nkv, B, st);
+  else rc = launch_attn_mfma_parts<HD, 4, 2>(a, n_tg, nkv, B, st);
   if (rc) return rc;
   if (a.nparts > 1) {
     hipLaunchKernelGGL((k_attn_combine_parts<HD>), dim3(cdiv(M * a.nq, BLOCK / (HD / 4))), dim3(BLOCK), 0, st, a);

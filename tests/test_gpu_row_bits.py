@@ -130,3 +130,24 @@ def test_words_in_flight_do_not_change_bits(K, monkeypatch):
         assert path == 3
         got.append(logits)
     assert all(torch.equal(g, got[0]) for g in got[1:])
+
+
+@pytest.mark.parametrize("B,R", [(33, 1), (40, 5), (40, 7), (64, 3)])
+def test_attention_of_launches_that_leave_half_of_the_device_idle(B, R, monkeypatch):
+    """Between a quarter and half of the device's compute units in workgroups of four row tiles: the launch takes two tiles x four
+    key groups instead (one row tile, an odd number of them, up to twelve chunks, one chunk and fewer).  Against the vector-unit
+    kernel on the same cache: both keep 16 bits and more of every operand (2^-17 relative), so the logits, of the order of 1, agree to 1e-3."""
+    import paper_2505_15380_amd as ssd
+    shape = si.model_shape("mini_bf16")
+    rng = np.random.default_rng(5)
+    lens = [int(n) for n in rng.integers(1, 760, B)]
+    lens[:4] = [1, 63, 64, 759]
+    x = torch.from_numpy(rng.integers(0, shape["vocab"], (B, R - 1)).astype(np.int32)).cuda()
+    got = {}
+    for mode in ("valu", ""):
+        monkeypatch.setenv("SSD_ATTN", mode)
+        model, kv = _target(shape, lens, 1024 // B)
+        got[mode], path = _verify_logits(model, kv, B, x)
+        assert path == 1
+    assert (got["valu"] - got[""]).abs().max() < 1e-3
+    assert got[""].abs().max() > 0.1
