@@ -593,30 +593,33 @@ static int plan_wgs(const TilePlan& p) { return p.n_colb * p.n_rowb * p.n_slices
 
 // Many rows: k_gemm_tile at the tile and slices of the least estimated time.  The estimate was fitted to measurements of
 // both model shapes at 72 to 1024 rows: a workgroup's k-tile costs 16.6 cycles per 16x16 tile of its output (twice
-// what the matrix cores alone would take) or 24 cycles per KB that it loads, whichever is more, workgroups of a
+// what the matrix cores alone would take; 12 where eight waves of two row tiles each read a weight fragment half as often, 15.2 with the
+// SwiGLU epilogue in it) or 24 cycles per KB that it loads, whichever is more, workgroups of a
 // compute unit share it, and one alone cannot hide 160 cycles of latency per k-tile (40 cycles per KB where the rows take
 // much of an L2, beyond 1.5 MB); partial outputs cost their write and their read at 5 TB/s.  It is within 10 % of the
-// best measured tile at nearly every size that was measured.
+// best measured tile at nearly every size that was measured.  (Tiles of 16 x 6 and 16 x 10, eight waves: down projection of 1024 and 476
+// rows of the 1.5B shape 58.7 -> 50.0 and 33.4 -> 29.3 us, gate / up of 512 rows 56.7 -> 53.5, of 1024 rows of the 0.5B shape 36.5 -> 35.3.)
 // Tiles that leave a compute unit one workgroup of four waves keep eight k-tiles in flight instead of four (weights
 // that come from HBM take more than a microsecond: 97 rows of gate / up 13.1 -> 12.1 us).
 template <int EPI>
 static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStream_t st) {
   const int KT = g.K / 32;
   struct Shape { int tm, tn, w; };
-  static const Shape shapes[] = {{1, 4, 4}, {1, 6, 4}, {1, 8, 4}, {1, 10, 4}, {1, 7, 4}, {1, 8, 8}, {1, 7, 8}, {1, 10, 8}, {2, 12, 4}, {2, 8, 8}};
+  static const Shape shapes[] = {{1, 4, 4}, {1, 6, 4}, {1, 8, 4}, {1, 10, 4}, {1, 7, 4}, {1, 8, 8}, {1, 7, 8}, {1, 10, 8}, {2, 12, 4}, {2, 6, 8}, {2, 8, 8}, {2, 10, 8}};
   const double kb_cycles = (size_t)g.M * g.K * 4 > 1536u * 1024 ? 40.0 : 24.0;
   int best = -1;
   double best_us = 0;
   TilePlan p{};
   for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
     const Shape& c = shapes[i];
-    const bool ok = EPI == EPI_PARTIAL ? c.tn == 4 || c.tn == 7 || c.tn == 8 : EPI == EPI_SWIGLU ? c.tn != 7 && !(c.tm == 2 && c.tn == 8)
+    const bool wide = c.tm == 2 && c.w == 8;
+    const bool ok = EPI == EPI_PARTIAL ? (wide ? c.tn != 10 : c.tm == 1 && (c.tn == 4 || c.tn == 7 || c.tn == 8)) : EPI == EPI_SWIGLU ? (wide ? c.tn == 10 : c.tn != 7)
                                        : EPI == EPI_QKV ? c.tn == 4 && c.w == 4 : c.w == 4 && (c.tn == 4 || c.tn == 6 || c.tn == 8);
     if (!ok) continue;
     for (int ns = 1; ns <= std::min(8, max_slices) && (ns == 1 || KT / ns >= 7); ns *= 2) {
       const TilePlan q = gemm_plan<EPI>(g, c.tm * c.w, c.tn, ns);
       const int rounds = cdiv(plan_wgs(q), cus);
-      const double cyc = std::max(16.6 * c.tm * c.w * c.tn, kb_cycles * (2 * c.tm * c.w + c.tn));
+      const double cyc = std::max((!wide ? 16.6 : EPI == EPI_SWIGLU ? 15.2 : 12.0) * c.tm * c.w * c.tn, kb_cycles * (2 * c.tm * c.w + c.tn));
       const double us = q.slice_kt * (rounds * cyc + (rounds == 1 ? 160.0 : 0.0)) / 2400.0 +
                         (max_slices > 1 ? (double)q.n_slices * g.M * g.N * 8.0 / 5e6 : 0.0);
       if (best < 0 || us < best_us * (c.tm * c.w * c.tn > shapes[best].tm * shapes[best].w * shapes[best].tn ? 1.001 : 0.999)) {
@@ -634,10 +637,10 @@ static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStrea
   TILE(1, 4, 4);
   else TILE_DEEP(4);
   else if constexpr (EPI == EPI_SWIGLU) {
-    TILE(1, 6, 4); else TILE(1, 8, 4); else TILE(1, 10, 4); else TILE(1, 8, 8); else TILE(1, 10, 8); else TILE(2, 12, 4);
+    TILE(1, 6, 4); else TILE(1, 8, 4); else TILE(1, 10, 4); else TILE(1, 8, 8); else TILE(1, 10, 8); else TILE(2, 12, 4); else TILE(2, 10, 8);
     else TILE_DEEP(6); else TILE_DEEP(8); else TILE_DEEP(10);
   } else if constexpr (EPI == EPI_PARTIAL) {
-    TILE(1, 7, 4); else TILE(1, 8, 4); else TILE(1, 7, 8); else TILE(1, 8, 8); else TILE(2, 8, 8);
+    TILE(1, 7, 4); else TILE(1, 8, 4); else TILE(1, 7, 8); else TILE(1, 8, 8); else TILE(2, 6, 8); else TILE(2, 8, 8);
     else TILE_DEEP(7); else TILE_DEEP(8);
   } else if constexpr (EPI == EPI_RESID) {
     TILE(1, 6, 4); else TILE(1, 8, 4); else TILE_DEEP(6); else TILE_DEEP(8);
