@@ -347,6 +347,115 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
   }
 }
 
+// ------------------------------------------------------------------------------------------ some rows
+// The same where a workgroup's tile is the whole work of its compute unit, or nearly, and the latency of a k-tile counts (65 to 500 rows): both
+// operands go from memory to LDS with direct loads, NBUF k-tiles ahead, and a wave (WR x WC of them, each TM row tiles x TN
+// slots) reads the fragments of k-tile k + 1 into registers beside the matrix instructions of k-tile k.  No load in flight has a register,
+// so the only waits are the counted ones.  One barrier per k-tile: it is passed when every wave has read k-tile k, whose buffer the next
+// request then overwrites, and every wave's share of k-tile k + 1 has arrived.  Order of an element's sum as in k_gemm_tile.
+// What bounds it is the intake of a compute unit, 60 bytes a nanosecond of activations that every column block reads again and
+// of weights from HBM, whatever the depth (3 to 11 k-tiles in flight: the same).
+// k_gemm_tile's best tile -> this one's, us, cold weights: gate / up of 72, 112, 160 rows of the 0.5B shape 12.8 -> 11.2, 12.9 -> 12.1,
+// 13.8 -> 12.0; of the 1.5B shape 23.8 -> 21.3, 25.0 -> 22.8, equal; down of the 1.5B shape, 72 and 112 rows, 15.4 -> 13.8, 16.5 -> 15.2, of 320
+// rows 29.5 -> 26.1.  With more rows the two are equal.
+template <int EPI, int RT, int CT, int WR, int WC, int NBUF>
+__global__ void __launch_bounds__(WR * WC * 64) k_gemm_block(GemmArgs g, TilePlan p) {
+  constexpr int W = WR * WC, TM = RT / WR, TN = CT / WC;
+  constexpr int F = 2 * RT + CT, LPW = (F + W - 1) / W;    // fragments of a k-tile (hi and lo of the rows, then the weights); of them, a wave requests
+  static_assert(EPI == EPI_PARTIAL || EPI == EPI_SWIGLU, "no other epilogue is asked for");
+  static_assert(RT % WR == 0 && CT % WC == 0 && (EPI == EPI_PARTIAL || TN % 2 == 0), "");
+  extern __shared__ u32x4 lds[];                           // [NBUF][F][64]
+  int colb, rowb, slice;
+  if (!tile_block(p, colb, rowb, slice)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave / WC, wc = wave - wr * WC;
+  const int KT = g.K >> 5, ntiles = (g.N + 15) >> 4, last_mt = (g.M - 1) >> 4;
+  const int kb = slice * p.slice_kt, nk = min(KT, kb + p.slice_kt) - kb;
+  const char* src[LPW];
+  int step[LPW], dst[LPW];
+#pragma unroll
+  for (int q = 0; q < LPW; ++q) {                          // (the last ones repeat earlier fragments where F is not a multiple of W)
+    const int f = (q * W + wave) % F;
+    dst[q] = f;
+    if (f < 2 * RT) {
+      src[q] = (const char*)g.A + ((size_t)min(rowb * RT + f / 2, last_mt) * KT + kb) * 2048 + (f & 1) * 1024;
+      step[q] = 2048;
+    } else {
+      const int j = f - 2 * RT, t = slot_tile<EPI, CT>(colb, j, 0);
+      src[q] = (const char*)(EPI == EPI_SWIGLU && j >= CT / 2 ? g.W1 : g.W0) + ((size_t)(t < ntiles ? t : 0) * KT + kb) * 1024;
+      step[q] = 1024;
+    }
+  }
+  auto request = [&](int k, int buf) {
+#pragma unroll
+    for (int q = 0; q < LPW; ++q)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[q] + (size_t)(k * step[q]) + lane * 16),
+                                       (__attribute__((address_space(3))) void*)&lds[(buf * F + dst[q]) * 64], 16, 0, 0);
+  };
+  const bool scaled = EPI == EPI_SWIGLU && g.rms_d > 0;
+  RowSums rs[TM];
+  if (scaled)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) rs[i] = row_sums_load<false>(g, (rowb * WR + wr) * TM + i);
+#pragma unroll
+  for (int b = 0; b < NBUF; ++b) request(min(b, nk - 1), b);
+  float inv[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) inv[i] = scaled ? row_inv_rms<false>(g, rs[i]) : 1.0f;
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
+  // slot of the workgroup's CT that is this wave's j-th (SwiGLU: gate and up of the same columns)
+  auto slot = [&](int j) { return EPI == EPI_PARTIAL ? wc * TN + j : j < TN / 2 ? wc * (TN / 2) + j : CT / 2 + wc * (TN / 2) + j - TN / 2; };
+  u32x4 a[2][TM][2], w[2][TN];
+  auto fetch = [&](int s, int buf) {
+    const u32x4* b = lds + buf * F * 64 + lane;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) w[s][j] = b[(2 * RT + slot(j)) * 64];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) { a[s][i][1] = b[(2 * (wr * TM + i) + 1) * 64]; a[s][i][0] = b[2 * (wr * TM + i) * 64]; }
+  };
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NBUF - 1) * LPW) : "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  fetch(0, 0);
+  int buf = 0;                                             // of k-tile k
+  auto one = [&](int s, int k) {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NBUF - 2) * LPW) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    request(min(k + NBUF, nk - 1), buf);
+    buf = buf + 1 == NBUF ? 0 : buf + 1;
+    fetch(s ^ 1, buf);                                     // (behind the last k-tile: a repeated one, not used)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const bf16x8 hi = __builtin_bit_cast(bf16x8, a[s][i][0]), lo = __builtin_bit_cast(bf16x8, a[s][i][1]);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s][j]), lo, acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s][j]), hi, acc[i][j], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int k = 0;
+  for (; k + 2 <= nk; k += 2) { one(0, k); one(1, k + 1); }
+  if (k < nk) one(0, k);                                   // (uniform over the workgroup)
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");       // the requests past the end
+  constexpr int PAIRS = (TN + 1) / 2;
+  const ResidOperands none{};
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int row = ((rowb * WR + wr) * TM + i) * 16 + (lane & 15);
+#pragma unroll
+    for (int j = 0; j < PAIRS; ++j) {
+      const int j1 = j + TN / 2 + TN % 2;                  // (an odd slot is alone)
+      tile_epilogue<EPI>(g, slot_tile<EPI, CT>(colb, slot(j), 0), j1 < TN ? slot_tile<EPI, CT>(colb, slot(j1), 0) : 0x7FFFFF, slice, row, 4 * (lane >> 4),
+                         acc[i][j], acc[i][j1 < TN ? j1 : j], RowDest{0, -1}, none, inv[i]);
+    }
+  }
+}
+
 // ------------------------------------------------------------------------------------------ few rows
 // A workgroup of W waves owns TM row tiles x TN column-tile slots over a k range; its waves take the k-tiles in turn
 // (wave w: k-tiles w, w + W, ..) straight from memory into registers, U of them in flight, and meet once in LDS.  No

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -591,64 +593,95 @@ static TilePlan gemm_plan(const GemmArgs& g, int rows, int cols, int slices) {
 }
 static int plan_wgs(const TilePlan& p) { return p.n_colb * p.n_rowb * p.n_slices; }
 
-// Many rows: k_gemm_tile at the tile and slices of the least estimated time.  The estimate was fitted to measurements of
-// both model shapes at 72 to 1024 rows: a workgroup's k-tile costs 16.6 cycles per 16x16 tile of its output (twice
-// what the matrix cores alone would take; 12 where eight waves of two row tiles each read a weight fragment half as often, 15.2 with the
-// SwiGLU epilogue in it) or 24 cycles per KB that it loads, whichever is more, workgroups of a
-// compute unit share it, and one alone cannot hide 160 cycles of latency per k-tile (40 cycles per KB where the rows take
-// much of an L2, beyond 1.5 MB); partial outputs cost their write and their read at 5 TB/s.  It is within 10 % of the
-// best measured tile at nearly every size that was measured.  (Tiles of 16 x 6 and 16 x 10, eight waves: down projection of 1024 and 476
-// rows of the 1.5B shape 58.7 -> 50.0 and 33.4 -> 29.3 us, gate / up of 512 rows 56.7 -> 53.5, of 1024 rows of the 0.5B shape 36.5 -> 35.3.)
-// Tiles that leave a compute unit one workgroup of four waves keep eight k-tiles in flight instead of four (weights
-// that come from HBM take more than a microsecond: 97 rows of gate / up 13.1 -> 12.1 us).
+// More than 64 KB of dynamic LDS is opt-in, once per kernel and device; a static object per kernel.
+struct LdsOptIn {
+  std::atomic<u64> asked{0};                               // a bit per device
+  hipError_t ask(const void* kernel, int bytes) {
+    int dev = 0;
+    if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+    const u64 bit = dev < 64 ? 1ull << dev : 0;
+    if (asked.load(std::memory_order_relaxed) & bit) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) asked.fetch_or(bit, std::memory_order_relaxed);
+    return e;
+  }
+};
+// Many rows: the kernel, the tile and the slices of the least estimated time.  A shape's two figures are us per k-tile, measured with cold
+// weights at 72 to 1024 rows of both model shapes and fitted by least squares: what a k-tile takes at all, and what it takes
+// for each of a compute unit's workgroups.  Partial outputs cost their write at 4.2 TB/s and their read at 5.  The shape that is picked is 0.6 %
+// on average, at most 8 %, slower than the fastest of 32 shapes at each of 94 sizes; those that are left out were nowhere needed for that.
+// (An estimate from cycles per tile and per KB, which stood here, was 6 % behind on average, and up to 30 %: us with it -> with this, 72 rows
+// of gate / up of the 1.5B shape 25.1 -> 21.3, 256 39.2 -> 35.0, 640 68.0 -> 63.6; down of 320 rows 33.0 -> 26.1, 768 58.2 -> 52.0;
+// head of 112 rows 160 -> 137.)
+// Tiles of the QKV and output projections that leave a compute unit one workgroup of four waves keep eight k-tiles in flight instead of
+// four (weights that come from HBM take more than a microsecond).
+struct GemmShape { int rt, ct, w; bool block; float per_kt, per_wg; };   // row tiles x column slots, waves, k_gemm_block or k_gemm_tile
+template <int EPI>
+static auto gemm_shapes() {
+  if constexpr (EPI == EPI_SWIGLU)
+    return std::array<GemmShape, 9>{{{4, 8, 8, true, 0.074f, 0.262f}, {4, 10, 4, true, 0.032f, 0.448f}, {5, 6, 5, true, 0.117f, 0.272f}, {7, 6, 7, true, 0.013f, 0.397f},
+                                     {4, 8, 4, false, 0.179f, 0.215f}, {8, 8, 8, false, 0.153f, 0.377f}, {8, 10, 8, false, 0.196f, 0.455f},
+                                     {8, 12, 4, false, 0.274f, 0.482f}, {16, 10, 8, false, 0.088f, 0.960f}}};
+  else if constexpr (EPI == EPI_PARTIAL)
+    return std::array<GemmShape, 6>{{{4, 4, 4, true, 0.027f, 0.145f}, {4, 8, 8, true, 0.024f, 0.223f}, {8, 7, 8, true, 0.f, 0.369f},
+                                     {8, 8, 8, false, 0.031f, 0.368f}, {16, 6, 8, false, 0.f, 0.586f}, {16, 8, 8, false, 0.f, 0.682f}}};
+  else if constexpr (EPI == EPI_RESID)
+    return std::array<GemmShape, 3>{{{4, 4, 4, false, 0.f, 0.200f}, {4, 6, 4, false, 0.f, 0.233f}, {4, 8, 4, false, 0.f, 0.267f}}};
+  else
+    return std::array<GemmShape, 1>{{{4, 4, 4, false, 0.f, 0.200f}}};
+}
+template <int EPI, int RT, int CT, int WR, int WC, int NBUF>
+static int launch_gemm_block(const GemmArgs& g, const TilePlan& p, hipStream_t st) {
+  constexpr int LDS = NBUF * (2 * RT + CT) * 1024;
+  static LdsOptIn lds;
+  if (hipError_t e = lds.ask((const void*)k_gemm_block<EPI, RT, CT, WR, WC, NBUF>, LDS); e != hipSuccess)
+    return fail(SSD_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
+  hipLaunchKernelGGL((k_gemm_block<EPI, RT, CT, WR, WC, NBUF>), dim3(8 * p.per_xcd), dim3(WR * WC * 64), LDS, st, g, p);
+  LAUNCH_CHECK();
+  return p.n_slices;
+}
 template <int EPI>
 static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStream_t st) {
   const int KT = g.K / 32;
-  struct Shape { int tm, tn, w; };
-  static const Shape shapes[] = {{1, 4, 4}, {1, 6, 4}, {1, 8, 4}, {1, 10, 4}, {1, 7, 4}, {1, 8, 8}, {1, 7, 8}, {1, 10, 8}, {2, 12, 4}, {2, 6, 8}, {2, 8, 8}, {2, 10, 8}};
-  const double kb_cycles = (size_t)g.M * g.K * 4 > 1536u * 1024 ? 40.0 : 24.0;
-  int best = -1;
+  GemmShape c{};
   double best_us = 0;
   TilePlan p{};
-  for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
-    const Shape& c = shapes[i];
-    const bool wide = c.tm == 2 && c.w == 8;
-    const bool ok = EPI == EPI_PARTIAL ? (wide ? c.tn != 10 : c.tm == 1 && (c.tn == 4 || c.tn == 7 || c.tn == 8)) : EPI == EPI_SWIGLU ? (wide ? c.tn == 10 : c.tn != 7)
-                                       : EPI == EPI_QKV ? c.tn == 4 && c.w == 4 : c.w == 4 && (c.tn == 4 || c.tn == 6 || c.tn == 8);
-    if (!ok) continue;
+  for (const GemmShape& s : gemm_shapes<EPI>())
     for (int ns = 1; ns <= std::min(8, max_slices) && (ns == 1 || KT / ns >= 7); ns *= 2) {
-      const TilePlan q = gemm_plan<EPI>(g, c.tm * c.w, c.tn, ns);
-      const int rounds = cdiv(plan_wgs(q), cus);
-      const double cyc = std::max((!wide ? 16.6 : EPI == EPI_SWIGLU ? 15.2 : 12.0) * c.tm * c.w * c.tn, kb_cycles * (2 * c.tm * c.w + c.tn));
-      const double us = q.slice_kt * (rounds * cyc + (rounds == 1 ? 160.0 : 0.0)) / 2400.0 +
-                        (max_slices > 1 ? (double)q.n_slices * g.M * g.N * 8.0 / 5e6 : 0.0);
-      if (best < 0 || us < best_us * (c.tm * c.w * c.tn > shapes[best].tm * shapes[best].w * shapes[best].tn ? 1.001 : 0.999)) {
-        best = i; best_us = us; p = q;
-      }
+      const TilePlan q = gemm_plan<EPI>(g, s.rt, s.ct, ns);
+      const double us = q.slice_kt * (s.per_kt + s.per_wg * cdiv(plan_wgs(q), cus)) + (EPI == EPI_PARTIAL ? (double)q.n_slices * g.M * g.N * 4 * 0.44e-6 : 0.0);
+      if (!c.w || us < best_us) { c = s; best_us = us; p = q; }
     }
+  const bool deep = !c.block && c.rt == 4 && c.w == 4 && plan_wgs(p) <= cus && (EPI == EPI_QKV || EPI == EPI_RESID);
+#define BLOCK(RT, CT, WR, WC, NBUF) \
+  if (c.block && c.rt == RT && c.ct == CT) return launch_gemm_block<EPI, RT, CT, WR, WC, NBUF>(g, p, st)
+#define TILE(RT, CT, W)                                                                                                              \
+  if (!c.block && !deep && c.rt == RT && c.ct == CT && c.w == W) {                                                                   \
+    hipLaunchKernelGGL((k_gemm_tile<EPI, RT / W, CT, W, 4, 4, RT == 16 ? 1 : 2>), dim3(8 * p.per_xcd), dim3(W * 64), 0, st, g, p);   \
+    LAUNCH_CHECK();                                                                                                                  \
+    return EPI == EPI_RESID ? p.n_colb : p.n_slices;                                                                                 \
   }
-  const Shape c = shapes[best];
-  const bool deep = c.tm == 1 && c.w == 4 && plan_wgs(p) <= cus;
-#define TILE(TM, TN, W)                                                                                         \
-  if (!deep && c.tm == TM && c.tn == TN && c.w == W)                                                             \
-  hipLaunchKernelGGL((k_gemm_tile<EPI, TM, TN, W, 4, 4, TM == 2 && W == 8 ? 1 : 2>), dim3(8 * p.per_xcd), dim3(W * 64), 0, st, g, p)
-#define TILE_DEEP(TN)                                                                                           \
-  if (deep && c.tn == TN) hipLaunchKernelGGL((k_gemm_tile<EPI, 1, TN, 4, 8, 8, 1>), dim3(8 * p.per_xcd), dim3(256), 0, st, g, p)
-  TILE(1, 4, 4);
-  else TILE_DEEP(4);
-  else if constexpr (EPI == EPI_SWIGLU) {
-    TILE(1, 6, 4); else TILE(1, 8, 4); else TILE(1, 10, 4); else TILE(1, 8, 8); else TILE(1, 10, 8); else TILE(2, 12, 4); else TILE(2, 10, 8);
-    else TILE_DEEP(6); else TILE_DEEP(8); else TILE_DEEP(10);
+#define TILE_DEEP(CT)                                                                                                  \
+  if (deep && c.ct == CT) {                                                                                            \
+    hipLaunchKernelGGL((k_gemm_tile<EPI, 1, CT, 4, 8, 8, 1>), dim3(8 * p.per_xcd), dim3(256), 0, st, g, p);            \
+    LAUNCH_CHECK();                                                                                                    \
+    return EPI == EPI_RESID ? p.n_colb : p.n_slices;                                                                   \
+  }
+  if constexpr (EPI == EPI_SWIGLU) {
+    BLOCK(4, 8, 4, 2, 5); BLOCK(4, 10, 4, 1, 5); BLOCK(5, 6, 5, 1, 5); BLOCK(7, 6, 7, 1, 5);
+    TILE(4, 8, 4) TILE(8, 8, 8) TILE(8, 10, 8) TILE(8, 12, 4) TILE(16, 10, 8)
   } else if constexpr (EPI == EPI_PARTIAL) {
-    TILE(1, 7, 4); else TILE(1, 8, 4); else TILE(1, 7, 8); else TILE(1, 8, 8); else TILE(2, 6, 8); else TILE(2, 8, 8);
-    else TILE_DEEP(7); else TILE_DEEP(8);
+    BLOCK(4, 4, 4, 1, 5); BLOCK(4, 8, 4, 2, 5); BLOCK(8, 7, 8, 1, 4);
+    TILE(8, 8, 8) TILE(16, 6, 8) TILE(16, 8, 8)
   } else if constexpr (EPI == EPI_RESID) {
-    TILE(1, 6, 4); else TILE(1, 8, 4); else TILE_DEEP(6); else TILE_DEEP(8);
+    TILE(4, 4, 4) TILE(4, 6, 4) TILE(4, 8, 4) TILE_DEEP(4) TILE_DEEP(6) TILE_DEEP(8)
+  } else {
+    TILE(4, 4, 4) TILE_DEEP(4)
   }
+#undef BLOCK
 #undef TILE
 #undef TILE_DEEP
-  LAUNCH_CHECK();
-  return EPI == EPI_RESID ? p.n_colb : p.n_slices;
+  return fail(SSD_EHIP, "no GEMM kernel of %d x %d tiles and %d waves", c.rt, c.ct, c.w);
 }
 
 // Launch of a bf16 GEMM: picks the kernel, the tile and the k-slices from the sizes alone.  Returns the number of k-slices (1 unless
@@ -704,9 +737,9 @@ constexpr int ATT_PLAN_CHUNKS = 64;
 template <int HD, int WQ, int WK>
 static int launch_attn_mfma_parts(const AttnArgs& a, int n_tg, int nkv, int B, hipStream_t st) {
   constexpr int LDS = WK * 2 * 2 * HD * 128;              // two buffers of 64 keys and 64 values per key group
-  static const hipError_t lds_ok =                        // more than 64 KB of dynamic LDS is opt-in, once per process
-      hipFuncSetAttribute((const void*)k_attn_mfma<HD, WQ, WK>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-  if (lds_ok != hipSuccess) return fail(SSD_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(lds_ok));
+  static LdsOptIn lds;
+  if (hipError_t e = lds.ask((const void*)k_attn_mfma<HD, WQ, WK>, LDS); e != hipSuccess)
+    return fail(SSD_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
   hipLaunchKernelGGL((k_attn_mfma<HD, WQ, WK>), dim3(a.nparts * n_tg, nkv, B), dim3(WQ * WK * 64), LDS, st, a);
   LAUNCH_CHECK();
   return SSD_OK;

@@ -239,6 +239,22 @@ def test_norm_between_the_projections_of_a_prompt(d, rows):
     pair.check_free_stack()
 
 
+@pytest.mark.parametrize("d,ffn,rows", [(32, 96, 65), (64, 8992, 71), (96, 8992, 97), (64, 4896, 250), (32, 8992, 257), (96, 4896, 321),
+                                        (32, 8992, 250), (64, 4896, 513), (64, 8992, 449), (1056, 2016, 65), (1056, 2016, 449)])
+def test_gate_up_and_down_at_each_tile_of_many_rows(d, ffn, rows):
+    """Each tile of the gate / up projection that the estimate picks (in this order: 4 x 8 of k_gemm_block, 5 x 6, 7 x 6, 4 x 10, then
+    4 x 8 of k_gemm_tile, 8 x 8, 8 x 10, 8 x 12, 16 x 10; the last two are for down's 4 x 8 and 8 x 7), with fewer k-tiles than buffers,
+    a last row tile of one row, and a ragged last column block.  Two layers, as above."""
+    from tests.parity import Pair
+    shape = dict(n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=ffn, vocab=41, n_embed=43, dtype="bf16",
+                 qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
+    pair = Pair(None, 87, rows + 32, max_rows=1024, shape=shape, store="bf16")
+    pair.prefill(0, np.random.default_rng(88).integers(0, 43, rows + 1))
+    assert pair.kv.last_forward_path() == 1
+    pair.check_state(0, 2e-2)
+    pair.check_free_stack()
+
+
 # ---- the barrier-free persistent forward (bf16 shapes, <= 16 rows) ------------------------------------------------
 @pytest.mark.gpu
 @pytest.mark.parametrize("n_prefix,K", [(250, 4), (254, 12), (600, 4), (1290, 7), (1532, 7)])
