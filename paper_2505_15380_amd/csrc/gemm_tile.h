@@ -235,7 +235,7 @@ __device__ __forceinline__ void store_row_sum(const GemmArgs& g, int row, int pi
 template <int EPI, int TM, int TN, int W, int NBUF, int UA, int MINB>
 __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan p) {
   constexpr int LW = (TN + W - 1) / W;                     // weight fragments a wave requests per k-tile
-  static_assert(UA >= NBUF - 1, "the first waits rely on it");
+  static_assert(EPI != EPI_QKV && UA >= NBUF - 1, "the first waits rely on it");
   __shared__ u32x4 stage[NBUF][TN][64];
   int colb, rowb, slice;
   if (!tile_block(p, colb, rowb, slice)) return;
@@ -270,9 +270,6 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
       a[u][i][1] = ap[i][(size_t)k * 128 + 64];
     }
   };
-  RowDest rd[TM];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) rd[i] = EPI == EPI_QKV ? row_dest(g, ((rowb * W + wave) * TM + i) * 16 + (lane & 15)) : RowDest{0, -1};
   constexpr int PAIRS = (TN + 1) / 2;
   ResidOperands ro[TM][PAIRS];
 #pragma unroll
@@ -340,9 +337,10 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
 #pragma unroll
     for (int j = 0; j < TN / 2; ++j)
       sum += tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), slot_tile<EPI, TN>(colb, j + TN / 2, hd), slice, row, 4 * (lane >> 4), acc[i][j],
-                         acc[i][j + TN / 2], rd[i], ro[i][j], inv[i]);
+                         acc[i][j + TN / 2], RowDest{0, -1}, ro[i][j], inv[i]);
     if (TN % 2)
-      sum += tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, TN - 1, hd), 0x7FFFFF, slice, row, 4 * (lane >> 4), acc[i][TN - 1], acc[i][TN - 1], rd[i], ro[i][PAIRS - 1], inv[i]);
+      sum += tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, TN - 1, hd), 0x7FFFFF, slice, row, 4 * (lane >> 4), acc[i][TN - 1], acc[i][TN - 1],
+                              RowDest{0, -1}, ro[i][PAIRS - 1], inv[i]);
     if (EPI == EPI_RESID) store_row_sum(g, row, colb, p.n_colb, sum);
   }
 }
@@ -357,19 +355,20 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
 // of weights from HBM, whatever the depth (3 to 11 k-tiles in flight: the same).
 // k_gemm_tile's best tile -> this one's, us, cold weights: gate / up of 72, 112, 160 rows of the 0.5B shape 12.8 -> 11.2, 12.9 -> 12.1,
 // 13.8 -> 12.0; of the 1.5B shape 23.8 -> 21.3, 25.0 -> 22.8, equal; down of the 1.5B shape, 72 and 112 rows, 15.4 -> 13.8, 16.5 -> 15.2, of 320
-// rows 29.5 -> 26.1.  With more rows the two are equal.
+// rows 29.5 -> 26.1.  With more rows the two are equal, but for the QKV projection, whose tiles are small: 1024 rows of the 0.5B shape
+// 14.9 -> 13.8, of the 1.5B shape 25.3 -> 21.0.  (Its output projection: no gain over k_gemm_kwave up to 512 rows, and above that 0.7 us at
+// 1024 rows of the 0.5B shape and a loss elsewhere.)
 template <int EPI, int RT, int CT, int WR, int WC, int NBUF>
 __global__ void __launch_bounds__(WR * WC * 64) k_gemm_block(GemmArgs g, TilePlan p) {
   constexpr int W = WR * WC, TM = RT / WR, TN = CT / WC;
   constexpr int F = 2 * RT + CT, LPW = (F + W - 1) / W;    // fragments of a k-tile (hi and lo of the rows, then the weights); of them, a wave requests
-  static_assert(EPI == EPI_PARTIAL || EPI == EPI_SWIGLU, "no other epilogue is asked for");
-  static_assert(RT % WR == 0 && CT % WC == 0 && (EPI == EPI_PARTIAL || TN % 2 == 0), "");
+  static_assert(EPI != EPI_RESID && RT % WR == 0 && CT % WC == 0 && (EPI == EPI_PARTIAL || TN % 2 == 0), "");
   extern __shared__ u32x4 lds[];                           // [NBUF][F][64]
   int colb, rowb, slice;
   if (!tile_block(p, colb, rowb, slice)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave / WC, wc = wave - wr * WC;
   const int KT = g.K >> 5, ntiles = (g.N + 15) >> 4, last_mt = (g.M - 1) >> 4;
-  const int kb = slice * p.slice_kt, nk = min(KT, kb + p.slice_kt) - kb;
+  const int kb = slice * p.slice_kt, nk = min(KT, kb + p.slice_kt) - kb, hd = g.kv.hd;
   const char* src[LPW];
   int step[LPW], dst[LPW];
 #pragma unroll
@@ -380,7 +379,7 @@ __global__ void __launch_bounds__(WR * WC * 64) k_gemm_block(GemmArgs g, TilePla
       src[q] = (const char*)g.A + ((size_t)min(rowb * RT + f / 2, last_mt) * KT + kb) * 2048 + (f & 1) * 1024;
       step[q] = 2048;
     } else {
-      const int j = f - 2 * RT, t = slot_tile<EPI, CT>(colb, j, 0);
+      const int j = f - 2 * RT, t = slot_tile<EPI, CT>(colb, j, hd);
       src[q] = (const char*)(EPI == EPI_SWIGLU && j >= CT / 2 ? g.W1 : g.W0) + ((size_t)(t < ntiles ? t : 0) * KT + kb) * 1024;
       step[q] = 1024;
     }
@@ -391,6 +390,16 @@ __global__ void __launch_bounds__(WR * WC * 64) k_gemm_block(GemmArgs g, TilePla
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[q] + (size_t)(k * step[q]) + lane * 16),
                                        (__attribute__((address_space(3))) void*)&lds[(buf * F + dst[q]) * 64], 16, 0, 0);
   };
+  // slot of the workgroup's CT that is this wave's j-th (paired tiles: the pairs of the same columns)
+  auto slot = [&](int j) {
+    return EPI == EPI_PARTIAL ? wc * TN + j : j < TN / 2 ? wc * (TN / 2) + j : CT / 2 + wc * (TN / 2) + j - TN / 2;
+  };
+  auto tile = [&](int j) { return j < TN ? slot_tile<EPI, CT>(colb, slot(j), hd) : 0x7FFFFF; };
+  auto row_of = [&](int i) { return ((rowb * WR + wr) * TM + i) * 16 + (lane & 15); };
+  constexpr int PAIRS = (TN + 1) / 2, HALF = TN / 2 + TN % 2;       // (an odd slot is alone)
+  RowDest rd[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) rd[i] = EPI == EPI_QKV ? row_dest(g, row_of(i)) : RowDest{0, -1};
   const bool scaled = EPI == EPI_SWIGLU && g.rms_d > 0;
   RowSums rs[TM];
   if (scaled)
@@ -406,8 +415,6 @@ __global__ void __launch_bounds__(WR * WC * 64) k_gemm_block(GemmArgs g, TilePla
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
-  // slot of the workgroup's CT that is this wave's j-th (SwiGLU: gate and up of the same columns)
-  auto slot = [&](int j) { return EPI == EPI_PARTIAL ? wc * TN + j : j < TN / 2 ? wc * (TN / 2) + j : CT / 2 + wc * (TN / 2) + j - TN / 2; };
   u32x4 a[2][TM][2], w[2][TN];
   auto fetch = [&](int s, int buf) {
     const u32x4* b = lds + buf * F * 64 + lane;
@@ -442,18 +449,12 @@ __global__ void __launch_bounds__(WR * WC * 64) k_gemm_block(GemmArgs g, TilePla
   for (; k + 2 <= nk; k += 2) { one(0, k); one(1, k + 1); }
   if (k < nk) one(0, k);                                   // (uniform over the workgroup)
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");       // the requests past the end
-  constexpr int PAIRS = (TN + 1) / 2;
   const ResidOperands none{};
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int row = ((rowb * WR + wr) * TM + i) * 16 + (lane & 15);
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < PAIRS; ++j) {
-      const int j1 = j + TN / 2 + TN % 2;                  // (an odd slot is alone)
-      tile_epilogue<EPI>(g, slot_tile<EPI, CT>(colb, slot(j), 0), j1 < TN ? slot_tile<EPI, CT>(colb, slot(j1), 0) : 0x7FFFFF, slice, row, 4 * (lane >> 4),
-                         acc[i][j], acc[i][j1 < TN ? j1 : j], RowDest{0, -1}, none, inv[i]);
-    }
-  }
+    for (int j = 0; j < PAIRS; ++j)
+      tile_epilogue<EPI>(g, tile(j), tile(j + HALF), slice, row_of(i), 4 * (lane >> 4), acc[i][j], acc[i][j + HALF < TN ? j + HALF : j], rd[i], none, inv[i]);
 }
 
 // ------------------------------------------------------------------------------------------ few rows

@@ -613,8 +613,8 @@ struct LdsOptIn {
 // (An estimate from cycles per tile and per KB, which stood here, was 6 % behind on average, and up to 30 %: us with it -> with this, 72 rows
 // of gate / up of the 1.5B shape 25.1 -> 21.3, 256 39.2 -> 35.0, 640 68.0 -> 63.6; down of 320 rows 33.0 -> 26.1, 768 58.2 -> 52.0;
 // head of 112 rows 160 -> 137.)
-// Tiles of the QKV and output projections that leave a compute unit one workgroup of four waves keep eight k-tiles in flight instead of
-// four (weights that come from HBM take more than a microsecond).
+// Tiles of the output projection that leave a compute unit one workgroup keep eight k-tiles in flight instead of four (weights that come
+// from HBM take more than a microsecond).
 struct GemmShape { int rt, ct, w; bool block; float per_kt, per_wg; };   // row tiles x column slots, waves, k_gemm_block or k_gemm_tile
 template <int EPI>
 static auto gemm_shapes() {
@@ -625,10 +625,8 @@ static auto gemm_shapes() {
   else if constexpr (EPI == EPI_PARTIAL)
     return std::array<GemmShape, 6>{{{4, 4, 4, true, 0.027f, 0.145f}, {4, 8, 8, true, 0.024f, 0.223f}, {8, 7, 8, true, 0.f, 0.369f},
                                      {8, 8, 8, false, 0.031f, 0.368f}, {16, 6, 8, false, 0.f, 0.586f}, {16, 8, 8, false, 0.f, 0.682f}}};
-  else if constexpr (EPI == EPI_RESID)
-    return std::array<GemmShape, 3>{{{4, 4, 4, false, 0.f, 0.200f}, {4, 6, 4, false, 0.f, 0.233f}, {4, 8, 4, false, 0.f, 0.267f}}};
   else
-    return std::array<GemmShape, 1>{{{4, 4, 4, false, 0.f, 0.200f}}};
+    return std::array<GemmShape, 3>{{{4, 4, 4, false, 0.f, 0.200f}, {4, 6, 4, false, 0.f, 0.233f}, {4, 8, 4, false, 0.f, 0.267f}}};
 }
 template <int EPI, int RT, int CT, int WR, int WC, int NBUF>
 static int launch_gemm_block(const GemmArgs& g, const TilePlan& p, hipStream_t st) {
@@ -642,6 +640,14 @@ static int launch_gemm_block(const GemmArgs& g, const TilePlan& p, hipStream_t s
 }
 template <int EPI>
 static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStream_t st) {
+  if constexpr (EPI == EPI_QKV) {
+    // Tiles of 4 x 4 while few compute units have two of them (640 to 1024 rows of the 0.5B shape, 160 to 288 workgroups, 1.1 to 1.4 us less than
+    // k_gemm_tile; 640 rows of the 1.5B shape, 320: 1.8), else of 4 x 8 (768 to 1024 rows of that, 384 to 512 workgroups of 4 x 4: 3 to 4 us less,
+    // where those take 0.7 more).
+    const TilePlan small = gemm_plan<EPI>(g, 4, 4, 1);
+    if (plan_wgs(small) <= cus + cus / 4) return launch_gemm_block<EPI, 4, 4, 4, 1, 5>(g, small, st);
+    return launch_gemm_block<EPI, 4, 8, 4, 2, 5>(g, gemm_plan<EPI>(g, 4, 8, 1), st);
+  }
   const int KT = g.K / 32;
   GemmShape c{};
   double best_us = 0;
@@ -652,7 +658,7 @@ static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStrea
       const double us = q.slice_kt * (s.per_kt + s.per_wg * cdiv(plan_wgs(q), cus)) + (EPI == EPI_PARTIAL ? (double)q.n_slices * g.M * g.N * 4 * 0.44e-6 : 0.0);
       if (!c.w || us < best_us) { c = s; best_us = us; p = q; }
     }
-  const bool deep = !c.block && c.rt == 4 && c.w == 4 && plan_wgs(p) <= cus && (EPI == EPI_QKV || EPI == EPI_RESID);
+  const bool deep = !c.block && c.rt == 4 && c.w == 4 && plan_wgs(p) <= cus && EPI == EPI_RESID;
 #define BLOCK(RT, CT, WR, WC, NBUF) \
   if (c.block && c.rt == RT && c.ct == CT) return launch_gemm_block<EPI, RT, CT, WR, WC, NBUF>(g, p, st)
 #define TILE(RT, CT, W)                                                                                                              \
@@ -675,8 +681,6 @@ static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStrea
     TILE(8, 8, 8) TILE(16, 6, 8) TILE(16, 8, 8)
   } else if constexpr (EPI == EPI_RESID) {
     TILE(4, 4, 4) TILE(4, 6, 4) TILE(4, 8, 4) TILE_DEEP(4) TILE_DEEP(6) TILE_DEEP(8)
-  } else {
-    TILE(4, 4, 4) TILE_DEEP(4)
   }
 #undef BLOCK
 #undef TILE

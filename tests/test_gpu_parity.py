@@ -255,6 +255,19 @@ def test_gate_up_and_down_at_each_tile_of_many_rows(d, ffn, rows):
     pair.check_free_stack()
 
 
+@pytest.mark.parametrize("nq,nkv,hd,rows", [(2, 1, 64, 513), (15, 3, 64, 1009), (5, 1, 128, 640), (9, 1, 128, 1024)])
+def test_qkv_projection_of_more_than_512_rows(nq, nkv, hd, rows):
+    """Both of its tiles, 4 x 4 and (336 and 352 workgroups of that) 4 x 8, with last blocks of half a head and of a few rows."""
+    from tests.parity import Pair
+    shape = dict(n_layers=2, d_model=64, n_q_heads=nq, n_kv_heads=nkv, head_dim=hd, d_ffn=96, vocab=41, n_embed=43, dtype="bf16",
+                 qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
+    pair = Pair(None, 89, rows + 32, max_rows=1024, shape=shape, store="bf16")
+    pair.prefill(0, np.random.default_rng(90).integers(0, 43, rows + 1))
+    assert pair.kv.last_forward_path() == 1
+    pair.check_state(0, 2e-2)
+    pair.check_free_stack()
+
+
 # ---- the barrier-free persistent forward (bf16 shapes, <= 16 rows) ------------------------------------------------
 @pytest.mark.gpu
 @pytest.mark.parametrize("n_prefix,K", [(250, 4), (254, 12), (600, 4), (1290, 7), (1532, 7)])
