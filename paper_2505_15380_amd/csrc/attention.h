@@ -521,25 +521,32 @@ __global__ void __launch_bounds__(WQ * WK * 64, WQ * WK / 4) k_attn_mfma(AttnArg
 }
 
 // Merges a row's part partials (base-2 references) in ascending part order: HD / 4 lanes per (row, query head), four dims each.
+// A chain of two loads once the first parts' no longer wait for the row's position: 16 sequences x 7 rows 4.3 -> 3.9 us a launch.
 template <int HD>
 __global__ void __launch_bounds__(BLOCK) k_attn_combine_parts(AttnArgs a) {
   constexpr int L = HD / 4;
   const int rh = blockIdx.x * (BLOCK / L) + threadIdx.x / L, d = (threadIdx.x % L) * 4;
   if (rh >= a.rows.M * a.nq) return;
   const int m = rh / a.nq, hq = rh - m * a.nq;
-  const int np = a.rows.pos[m] / a.part_keys + 1;
+  const int pos = a.rows.pos[m];
   const size_t base = (size_t)rh * a.NC;
   float mx = -INFINITY, l = 0.f;
   f32x4 o = {0, 0, 0, 0};
-  for (int p0 = 0; p0 < np; p0 += 4) {                     // four parts' loads in flight
-    float2 ml[4];
-    f32x4 x[4];
+  float2 ml[4];
+  f32x4 x[4];
+  auto load = [&](int p0) {                                // four parts' loads in flight; the first four do not wait for the position
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int p = min(p0 + u, np - 1);
+      const int p = min(p0 + u, a.nparts - 1);             // (what lies in parts that the row does not reach is not looked at)
       ml[u] = *(const float2*)(a.ml_part + (base + p) * 2);
       x[u] = *(const f32x4*)(a.o_part + (base + p) * HD + d);
     }
+  };
+  load(0);
+  asm volatile("" ::: "memory");                           // (else they sink below the loop's first test)
+  const int np = pos / a.part_keys + 1;
+  for (int p0 = 0; p0 < np; p0 += 4) {
+    if (p0) load(p0);
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (p0 + u < np) {
