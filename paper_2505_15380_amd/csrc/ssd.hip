@@ -952,7 +952,8 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
   // and 16.2 + 12).
   auto add_norm = [&](int n_part_, const float* gain) -> int {
     if (!bf16) return SSD_OK;
-    hipLaunchKernelGGL(k_add_norm, dim3(M), row_block, 0, st, kv->h, kv->part, n_part_, part_stride, gain, c.rms_eps, (bf16_t*)kv->xn, d);
+    const auto kernel = n_part_ <= 4 ? k_add_norm<4> : k_add_norm<8>;       // (launch_gemm cuts k into 8 slices at most)
+    hipLaunchKernelGGL(kernel, dim3(M), row_block, 0, st, kv->h, kv->part, n_part_, part_stride, gain, c.rms_eps, (bf16_t*)kv->xn, d);
     LAUNCH_CHECK();
     return SSD_OK;
   };
