@@ -370,23 +370,27 @@ __global__ void __launch_bounds__(WQ * WK * 64, WQ * WK / 4) k_attn_mfma(AttnArg
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(pool + (size_t)max(blk[t], 0) * block_elems + voff[i]),      // (masked keys may read any block)
                                          (__attribute__((address_space(3))) void*)(dst + (t * KS + i) * 64), 16, 0, 0);
   };
-  look_up(0);
-  request(0);
-  look_up(min(1, nit - 1));
-
   // query row c16 of the tile, scaled into the base-2 domain and split
   const int qr = r0 + c16;
   const bool qok = qr < RG;
   const int j = qok ? qr / G : 0, gq = qok ? qr - j * G : 0;
   const int m = m_first + j, hq = kvh * G + gq;
   const int pos = qok ? a.rows.pos[m] : -1;
+  f32x4 q[KS][2];
+  {
+    const f32x4* qp = (const f32x4*)(a.q + ((size_t)m * a.nq + hq) * HD + g * 8);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) { q[ks][0] = qp[8 * ks]; q[ks][1] = qp[8 * ks + 1]; }
+  }
+  asm volatile("" ::: "memory");                           // (requested ahead of the keys, which wait for the block table; split while those travel: 0.5 us a launch)
+  look_up(0);
+  request(0);
+  look_up(min(1, nit - 1));
   SplitA qf[KS];
   {
     const float scale2 = a.scale * 1.4426950408889634f;
-    const f32x4* qp = (const f32x4*)(a.q + ((size_t)m * a.nq + hq) * HD + g * 8);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      qf[ks] = split_bf16(__builtin_bit_cast(u32x4, qp[8 * ks] * scale2), __builtin_bit_cast(u32x4, qp[8 * ks + 1] * scale2));
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = split_bf16(__builtin_bit_cast(u32x4, q[ks][0] * scale2), __builtin_bit_cast(u32x4, q[ks][1] * scale2));
   }
   // running state of a row: the reference mrow of its weights, and o and l (all four registers of l hold the row's sum: P times a matrix of ones)
   float mrow = 0.f;
