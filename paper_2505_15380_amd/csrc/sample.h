@@ -484,12 +484,16 @@ __device__ __forceinline__ void accept_seq(const AcceptArgs a, const int b, cons
   if (tid == WAVE)                                         // the uniform of the draw: one thread of the second wave
     sh_u = a.uniforms ? a.uniforms[b * (K + 1) + K] : philox_uniform(a.seed, seq, step, a.slot_base + K);
   __syncthreads();
-  const int n = sh_n;
+  const int n = __builtin_amdgcn_readfirstlane(sh_n);       // (the row is the whole workgroup's: scalar addresses)
   const float u = sh_u;
   const float* prow = (lds_row0 && n == 0) ? lds_row0 : pt + (size_t)n * V;
   const float* drow = pd + (size_t)n * V;                   // only read when n < K
   const int per = (V + SBLOCK - 1) / SBLOCK;                // contiguous span of indices per thread (<= SP)
   const int j0 = tid * per;
+  // It is read as SP entries that start at jb, of which those of the span count: a load behind a condition of its own waits for the one
+  // before it, and addresses that are clamped one by one are 16 pairs of registers, which 1024 threads do not have.  (One sequence of
+  // 6564 / 9000 / 16384, K = 6: 4.1 / 4.9 / 5.6 us; with both, and the spilled fixed-point weights below, 5.8 / 20 / 20.)
+  const int jb = min(j0, V - SP);                           // (the instantiation has V >= SP)
   int fallback = 0;
   bool residual = n < K;
   unsigned long long total, excl, mine;
@@ -497,11 +501,17 @@ __device__ __forceinline__ void accept_seq(const AcceptArgs a, const int b, cons
   for (;;) {
     // the thread's span of weights, all loads in flight together
 #pragma unroll
-    for (int e = 0; e < SP; ++e) {
-      const int j = j0 + e;
-      wgt[e] = 0.f;
-      if (e < per && j < V) wgt[e] = residual ? fmaxf(__fsub_rn(prow[j], drow[j]), 0.f) : prow[j];
+    for (int e = 0; e < SP; ++e) wgt[e] = prow[jb + e];
+    if (residual) {
+      float d[SP];
+#pragma unroll
+      for (int e = 0; e < SP; ++e) d[e] = drow[jb + e];
+#pragma unroll
+      for (int e = 0; e < SP; ++e) wgt[e] = fmaxf(__fsub_rn(wgt[e], d[e]), 0.f);
     }
+#pragma unroll
+    for (int e = 0; e < SP; ++e)
+      if (jb + e < j0 || jb + e >= j0 + per) wgt[e] = 0.f;
     mine = 0;
 #pragma unroll
     for (int e = 0; e < SP; ++e) mine += fix40(wgt[e]);
@@ -520,8 +530,9 @@ __device__ __forceinline__ void accept_seq(const AcceptArgs a, const int b, cons
       bool found = false;
 #pragma unroll
       for (int e = 0; e < SP; ++e) {
+        asm volatile("" : "+v"(wgt[e]));                   // (converted again by the one thread that draws, not kept by all as 64-bit numbers)
         c += fix40(wgt[e]);
-        if (!found && c > tgt) { tok = j0 + e; found = true; }
+        if (!found && c > tgt) { tok = jb + e; found = true; }
       }
       sh_tok = tok;
     }

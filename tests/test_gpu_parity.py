@@ -73,6 +73,27 @@ def test_decisions_degenerate_rows():
             assert (int(n[b]), int(nxt[b]), bool(fl[b])) == want, (r0, b, want)
 
 
+@pytest.mark.parametrize("V", [3, 1024, 1025, 6564, 8192, 8193, 9000, 16383])
+def test_draw_reaches_every_index_at_both_ends_of_a_row(V):
+    """A thread draws from a contiguous span of indices, and those at the row's end from one that overlaps their neighbours' loads: all the mass
+    on one index, as the row itself (no drafts) and as the residual of a rejected draft."""
+    import paper_2505_15380_amd as ssd
+    j = np.unique(np.concatenate([np.arange(min(V, 20)), np.arange(max(V - 40, 0), V)]))
+    j = j[j > 0]                             # (the draft's token is 0)
+    B = len(j)
+    pt, pd = np.zeros((B, 2, V), np.float32), np.zeros((B, 1, V), np.float32)
+    pt[np.arange(B), 0, j] = 1.0
+    pd[:, 0, 0] = 1.0
+    for u in (0.0, 0.5, 1.0 - 2.0 ** -24):
+        uu = grid24(np.full((B, 2), u))
+        uu[:, 0] = 0.5
+        n, nxt, _ = ssd.ssd_verify_from_probs(torch.from_numpy(pt).cuda(), torch.from_numpy(pd).cuda(), torch.zeros(B, 1, dtype=torch.int32).cuda(),
+                                              torch.from_numpy(uu).cuda(), 0.0)
+        assert (n.cpu().numpy() == 0).all() and (nxt.cpu().numpy() == j).all(), u
+        n, nxt, _ = ssd.ssd_verify_from_probs(torch.from_numpy(pt[:, :1].copy()).cuda(), None, None, torch.from_numpy(uu[:, 1:].copy()).cuda(), 0.0)
+        assert (nxt.cpu().numpy() == j).all(), u
+
+
 # ------------------------------------------------------------------------------ warp + softmax alone
 @pytest.mark.parametrize("V", [512, 6564, 1000, 8192, 8193, 16384])
 def test_warp_probs_against_oracle(V):
