@@ -614,7 +614,7 @@ struct LdsOptIn {
 // of gate / up of the 1.5B shape 25.1 -> 21.3, 256 39.2 -> 35.0, 640 68.0 -> 63.6; down of 320 rows 33.0 -> 26.1, 768 58.2 -> 52.0;
 // head of 112 rows 160 -> 137.)
 // Tiles of the output projection that leave a compute unit one workgroup keep eight k-tiles in flight instead of four (weights that come
-// from HBM take more than a microsecond).
+// from HBM take more than a microsecond); 4 x 6 or 4 x 8 then, since 4 x 4 that do are k_gemm_kwave's.
 struct GemmShape { int rt, ct, w; bool block; float per_kt, per_wg; };   // row tiles x column slots, waves, k_gemm_block or k_gemm_tile
 template <int EPI>
 static auto gemm_shapes() {
@@ -680,7 +680,7 @@ static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStrea
     BLOCK(4, 4, 4, 1, 5); BLOCK(4, 8, 4, 2, 5); BLOCK(8, 7, 8, 1, 4);
     TILE(8, 8, 8) TILE(16, 6, 8) TILE(16, 8, 8)
   } else if constexpr (EPI == EPI_RESID) {
-    TILE(4, 4, 4) TILE(4, 6, 4) TILE(4, 8, 4) TILE_DEEP(4) TILE_DEEP(6) TILE_DEEP(8)
+    TILE(4, 4, 4) TILE(4, 6, 4) TILE(4, 8, 4) TILE_DEEP(6) TILE_DEEP(8)
   }
 #undef BLOCK
 #undef TILE
