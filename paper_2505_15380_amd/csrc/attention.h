@@ -278,10 +278,10 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
 // ------------------------------------------------------------------------------------------------ matrix-core variant
 // The same operation for bf16 caches with 16-token blocks and head_dim 64 or 128.  The query rows that share keys - R rows
 // of a sequence x the G query heads of a group - form tiles of 16.  A workgroup takes WQ tiles and a part of the keys
-// (`part_keys`, cut at absolute positions); its waves are WQ tiles x WK key groups, and key group k walks the part's
-// 64-key chunks k, k + WK, .. with a running (reference, sum, weighted values) per row.  The key groups meet once in LDS.  Where
-// one part covers all keys the row is finished here; else its partial goes to memory and k_attn_combine_parts merges
-// the parts in ascending order.
+// (`part_keys`, cut at absolute positions; a multiple of WK chunks, so that no key group walks into the next part); its waves are WQ
+// tiles x WK key groups, and key group k walks the part's 64-key chunks k, k + WK, .. with a running (reference, sum, weighted values)
+// per row.  The key groups meet once in LDS.  Where one part covers all keys the row is finished here; else its partial goes to memory
+// and k_attn_combine_parts merges the parts in ascending order.
 //
 // S is computed transposed, S^T = K Q^T, and so is O^T = V^T P^T: a lane then holds scores and outputs of ONE query row
 // (lane % 16), so the row maximum needs two cross-lane steps instead of sixteen, and P goes from the accumulators

@@ -757,15 +757,20 @@ static int launch_attn_mfma(AttnArgs a, int nchunks, int plan_chunks, bool promp
   // 16 sequences x 7 rows where two x four take 13.0.
   const int four = B * nkv * cdiv(tiles, 4);
   const bool narrow = HD == 64 && four <= cus / 2 && four >= cus / 4;
-  const int wq = narrow ? 2 : 4, wk = narrow ? 4 : 2, n_tg = cdiv(tiles, wq);
+  const int wq = narrow ? 2 : 4, n_tg = cdiv(tiles, wq);
+  int wk = narrow ? 4 : 2;
   const int want = std::min(std::max(1, cus / (n_tg * nkv * B)), cdiv(plan_chunks, wk));
-  const int part_chunks = cdiv(cdiv(plan_chunks, want), wk) * wk;
+  int part_chunks = cdiv(cdiv(plan_chunks, want), wk) * wk;
+  if (HD == 64 && !narrow && prompt && part_chunks > 16) {
+    wk = 4;
+    part_chunks = cdiv(part_chunks, wk) * wk;              // (a part is whole rounds of the key groups: they would walk into the next one)
+  }
   a.part_keys = part_chunks * 64;
   a.nparts = cdiv(nchunks, part_chunks);
   int rc;
   if constexpr (HD == 64)
     rc = narrow ? launch_attn_mfma_parts<HD, 2, 4>(a, n_tg, nkv, B, st)
-         : prompt && part_chunks > 16 ? launch_attn_mfma_parts<HD, 4, 4>(a, n_tg, nkv, B, st) : launch_attn_mfma_parts<HD, 4, 2>(a, n_tg, nkv, B, st);
+         : wk == 4 ? launch_attn_mfma_parts<HD, 4, 4>(a, n_tg, nkv, B, st) : launch_attn_mfma_parts<HD, 4, 2>(a, n_tg, nkv, B, st);
   else rc = launch_attn_mfma_parts<HD, 4, 2>(a, n_tg, nkv, B, st);
   if (rc) return rc;
   if (a.nparts > 1) {

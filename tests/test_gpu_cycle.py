@@ -368,30 +368,31 @@ def test_prefill_in_large_chunks_then_verify(shape_name, max_rows, n_tokens):
         pair.check_state(0, 2e-2, layers=[shape["n_layers"] - 1])
 
 
-@pytest.mark.parametrize("n_q_heads", [10, 4])
-def test_prompt_attention_where_later_scores_exceed_the_first(n_q_heads):
-    """A prompt of 3099 positions in launches of 1024 rows whose scores have a spread of 10, so that the weights' reference of many
-    rows moves after their first chunk.  Ten query heads over two kv heads: one part of up to 48 chunks per launch, walked by four
-    key groups; four heads: parts of up to 14 chunks by two.  Keys and values of the second layer follow from the attention of the
-    first: against the oracle with the cache's format.  Where a key rounds the other way on one side (one element in 4000: fp32
+@pytest.mark.parametrize("nq,nkv,rows,positions", [(10, 2, 1024, 3099), (4, 2, 1024, 3099), (7, 1, 560, 4480)])
+def test_prompt_attention_where_later_scores_exceed_the_first(nq, nkv, rows, positions):
+    """A prompt in launches of `rows` whose scores have a spread of 10, so that the weights' reference of many
+    rows moves after their first chunk.  Ten query heads over two kv heads: one part per launch, of 16 chunks by two key groups, then of 32 and
+    48 by four with the reference that rarely moves; four heads: two tiles by four key groups, two parts of 8, 16 and 24 chunks; seven heads over
+    one kv head: the last launch's 70 chunks in parts of 20, by four key groups (18, a quarter, would not be whole rounds of the groups).
+    Keys and values of the second layer follow from the attention of the first: against the oracle with the cache's format.  Where a key rounds the other way on one side (one element in 4000: fp32
     against a step of bf16), scores of this spread move by up to 0.09 and the rows that hang on that key by as many per cent, so
     the bound is one of the 2-norm: 64 elements a key, 1.7 % of the rows by about 3 %, 4e-3; twice that and the format's own 2^-9."""
     from tests.parity import Pair
-    shape = dict(n_layers=2, d_model=128, n_q_heads=n_q_heads, n_kv_heads=2, head_dim=64, d_ffn=64, vocab=61, n_embed=61, dtype="bf16",
+    shape = dict(n_layers=2, d_model=128, n_q_heads=nq, n_kv_heads=nkv, head_dim=64, d_ffn=64, vocab=61, n_embed=61, dtype="bf16",
                  qkv_bias=0, rope_base=1.0e4, rms_eps=1e-6)
     w = si.make_weights(shape, 91)
     for l in range(2):
-        w[f"l{l}.wqkv"][:(n_q_heads + 2) * 64] *= 14.0           # (the storage rounding is relative: still bf16 after a rounding)
-        w[f"l{l}.wqkv"][(n_q_heads + 2) * 64:] *= 4.0
+        w[f"l{l}.wqkv"][:(nq + nkv) * 64] *= 14.0                # (the storage rounding is relative: still bf16 after a rounding)
+        w[f"l{l}.wqkv"][(nq + nkv) * 64:] *= 4.0
         w[f"l{l}.wo"] *= 2.0
         for n in ("wqkv", "wo"):
             w[f"l{l}.{n}"] = torch.from_numpy(w[f"l{l}.{n}"].astype(np.float32)).bfloat16().float().numpy()
-    pair = Pair(None, 0, 3200, max_rows=1024, shape=shape, weights=w, store="bf16")
-    pair.prefill(0, np.random.default_rng(92).integers(0, 61, 3100))
+    pair = Pair(None, 0, positions + 64, max_rows=rows, shape=shape, weights=w, store="bf16")
+    pair.prefill(0, np.random.default_rng(92).integers(0, 61, positions + 1))
     assert pair.kv.last_forward_path() == 1
     oc = pair.ocache[0]
     q = oc.k[0, :64, 0]
-    assert np.std(q @ oc.k[0, :3099, 0].T) / 8.0 > 5.0            # (keys stand in for queries: the same distribution)
+    assert np.std(q @ oc.k[0, :positions, 0].T) / 8.0 > 5.0      # (keys stand in for queries: the same distribution)
     for l in range(2):
         k, v = pair.kv.gather(0, l, oc.length)
         for got, ref in ((k, oc.k[l, :oc.length]), (v, oc.v[l, :oc.length])):
