@@ -267,6 +267,14 @@ int ssd_kv_last_forward_path(const ssd_kv* kv);
 int ssd_trace_barriers(ssd_kv* kv, int enable, void* stream, unsigned long long* out, int cap, int* n_wgs,
                        int* n_samples);
 
+/* What a bf16 forward with one launch per operator picks on a device of `cus` compute units, for tests that mean to reach a certain kernel
+ * (host only; nothing is launched).  ssd_gemm_plan: `kind` as in ssd_profile_begin (0, 2 .. 5), an output of rows x n, k inputs; plan =
+ * {kernel: 0 waves share the k range (k_gemm_kwave), 1 both operands through LDS (k_gemm_block), 2 large tiles (k_gemm_tile), 3 the same
+ * with eight k-tiles in flight; row tiles, column slots, k-slices of a workgroup}.  ssd_attention_plan: prompt_positions = cached positions
+ * after a prompt's launch, 0 for any other launch; plan = {row tiles, key groups of a workgroup; 64-key chunks of a part}. */
+int ssd_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4]);
+int ssd_attention_plan(int head_dim, int n_q_heads, int n_kv_heads, int n_seqs, int rows, int prompt_positions, int cus, int plan[3]);
+
 const char* ssd_strerror(int code);
 const char* ssd_last_error(void);
 

@@ -638,42 +638,56 @@ static int launch_gemm_block(const GemmArgs& g, const TilePlan& p, hipStream_t s
   LAUNCH_CHECK();
   return p.n_slices;
 }
+enum GemmKernel { KERNEL_KWAVE, KERNEL_BLOCK, KERNEL_TILE, KERNEL_TILE_DEEP };
+struct GemmPick {
+  GemmKernel kernel;
+  int rt, ct, w;                                           // row tiles x column slots of a workgroup; its waves (k_gemm_tile)
+  TilePlan p;
+};
 template <int EPI>
-static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStream_t st) {
+static GemmPick pick_gemm_tile(const GemmArgs& g, int cus, int max_slices) {
   if constexpr (EPI == EPI_QKV) {
     // Tiles of 4 x 4 while few compute units have two of them (640 to 1024 rows of the 0.5B shape, 160 to 288 workgroups, 1.1 to 1.4 us less than
     // k_gemm_tile; 640 rows of the 1.5B shape, 320: 1.8), else of 4 x 8 (768 to 1024 rows of that, 384 to 512 workgroups of 4 x 4: 3 to 4 us less,
     // where those take 0.7 more).
     const TilePlan small = gemm_plan<EPI>(g, 4, 4, 1);
-    if (plan_wgs(small) <= cus + cus / 4) return launch_gemm_block<EPI, 4, 4, 4, 1, 5>(g, small, st);
-    return launch_gemm_block<EPI, 4, 8, 4, 2, 5>(g, gemm_plan<EPI>(g, 4, 8, 1), st);
+    if (plan_wgs(small) <= cus + cus / 4) return {KERNEL_BLOCK, 4, 4, 4, small};
+    return {KERNEL_BLOCK, 4, 8, 8, gemm_plan<EPI>(g, 4, 8, 1)};
+  } else {
+    const int KT = g.K / 32;
+    GemmShape c{};
+    double best_us = 0;
+    TilePlan p{};
+    for (const GemmShape& s : gemm_shapes<EPI>())
+      for (int ns = 1; ns <= std::min(8, max_slices) && (ns == 1 || KT / ns >= 7); ns *= 2) {
+        const TilePlan q = gemm_plan<EPI>(g, s.rt, s.ct, ns);
+        const double us = q.slice_kt * (s.per_kt + s.per_wg * cdiv(plan_wgs(q), cus)) + (EPI == EPI_PARTIAL ? (double)q.n_slices * g.M * g.N * 4 * 0.44e-6 : 0.0);
+        if (!c.w || us < best_us) { c = s; best_us = us; p = q; }
+      }
+    const bool deep = EPI == EPI_RESID && plan_wgs(p) <= cus;
+    return {c.block ? KERNEL_BLOCK : deep ? KERNEL_TILE_DEEP : KERNEL_TILE, c.rt, c.ct, c.w, p};
   }
-  const int KT = g.K / 32;
-  GemmShape c{};
-  double best_us = 0;
-  TilePlan p{};
-  for (const GemmShape& s : gemm_shapes<EPI>())
-    for (int ns = 1; ns <= std::min(8, max_slices) && (ns == 1 || KT / ns >= 7); ns *= 2) {
-      const TilePlan q = gemm_plan<EPI>(g, s.rt, s.ct, ns);
-      const double us = q.slice_kt * (s.per_kt + s.per_wg * cdiv(plan_wgs(q), cus)) + (EPI == EPI_PARTIAL ? (double)q.n_slices * g.M * g.N * 4 * 0.44e-6 : 0.0);
-      if (!c.w || us < best_us) { c = s; best_us = us; p = q; }
-    }
-  const bool deep = !c.block && c.rt == 4 && c.w == 4 && plan_wgs(p) <= cus && EPI == EPI_RESID;
+}
+template <int EPI>
+static int launch_gemm_tile(const GemmArgs& g, const GemmPick& c, hipStream_t st) {
+  const TilePlan& p = c.p;
 #define BLOCK(RT, CT, WR, WC, NBUF) \
-  if (c.block && c.rt == RT && c.ct == CT) return launch_gemm_block<EPI, RT, CT, WR, WC, NBUF>(g, p, st)
+  if (c.kernel == KERNEL_BLOCK && c.rt == RT && c.ct == CT) return launch_gemm_block<EPI, RT, CT, WR, WC, NBUF>(g, p, st)
 #define TILE(RT, CT, W)                                                                                                              \
-  if (!c.block && !deep && c.rt == RT && c.ct == CT && c.w == W) {                                                                   \
+  if (c.kernel == KERNEL_TILE && c.rt == RT && c.ct == CT && c.w == W) {                                                             \
     hipLaunchKernelGGL((k_gemm_tile<EPI, RT / W, CT, W, 4, 4, RT == 16 ? 1 : 2>), dim3(8 * p.per_xcd), dim3(W * 64), 0, st, g, p);   \
     LAUNCH_CHECK();                                                                                                                  \
     return EPI == EPI_RESID ? p.n_colb : p.n_slices;                                                                                 \
   }
 #define TILE_DEEP(CT)                                                                                                  \
-  if (deep && c.ct == CT) {                                                                                            \
+  if (c.kernel == KERNEL_TILE_DEEP && c.ct == CT) {                                                                    \
     hipLaunchKernelGGL((k_gemm_tile<EPI, 1, CT, 4, 8, 8, 1>), dim3(8 * p.per_xcd), dim3(256), 0, st, g, p);            \
     LAUNCH_CHECK();                                                                                                    \
     return EPI == EPI_RESID ? p.n_colb : p.n_slices;                                                                   \
   }
-  if constexpr (EPI == EPI_SWIGLU) {
+  if constexpr (EPI == EPI_QKV) {
+    BLOCK(4, 4, 4, 1, 5); BLOCK(4, 8, 4, 2, 5);
+  } else if constexpr (EPI == EPI_SWIGLU) {
     BLOCK(4, 8, 4, 2, 5); BLOCK(4, 10, 4, 1, 5); BLOCK(5, 6, 5, 1, 5); BLOCK(7, 6, 7, 1, 5);
     TILE(4, 8, 4) TILE(8, 8, 8) TILE(8, 10, 8) TILE(8, 12, 4) TILE(16, 10, 8)
   } else if constexpr (EPI == EPI_PARTIAL) {
@@ -688,35 +702,42 @@ static int launch_gemm_tile(const GemmArgs& g, int cus, int max_slices, hipStrea
   return fail(SSD_EHIP, "no GEMM kernel of %d x %d tiles and %d waves", c.rt, c.ct, c.w);
 }
 
-// Launch of a bf16 GEMM: picks the kernel, the tile and the k-slices from the sizes alone.  Returns the number of k-slices (1 unless
-// `max_slices` allows more: outputs that are k-split partials); EPI_RESID: of the pieces of a row's sum of squares.
+// What a bf16 GEMM runs, from the sizes alone.
 // Few rows (up to 64; for the QKV and output projections, whose k range is not split over workgroups, up to 512, and the output
 // projection as long as tiles of 4 x 4 fill one round: 1024 rows of width 896 10.8 us, 12.0 with k_gemm_tile; of width 1536 26 and 21): k_gemm_kwave
 // with the smallest tile that leaves no more workgroups than compute units.  What bounds it is how long a workgroup's
 // operand stream takes, so the work is spread as far as one round of workgroups allows; k-split outputs get 8 slices
 // (4 where k is short) while that round lasts.
 template <int EPI>
-static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t st) {
+static GemmPick pick_gemm(const GemmArgs& g, int cus, int max_slices) {
   const int KT = g.K / 32, MT = cdiv(g.M, 16);
   constexpr bool whole_k = EPI == EPI_QKV || EPI == EPI_RESID;
-  if (MT > (whole_k ? 32 : 4) && !(EPI == EPI_RESID && plan_wgs(gemm_plan<EPI>(g, 4, 4, 1)) <= cus)) return launch_gemm_tile<EPI>(g, cus, max_slices, st);
-#define KWAVE(TM, TN, U)                                                                             \
-  if (tm == TM && tn == TN) hipLaunchKernelGGL((k_gemm_kwave<EPI, TM, TN, 8, U>), dim3(8 * p.per_xcd), dim3(512), 0, st, g, p)
+  if (MT > (whole_k ? 32 : 4) && !(EPI == EPI_RESID && plan_wgs(gemm_plan<EPI>(g, 4, 4, 1)) <= cus)) return pick_gemm_tile<EPI>(g, cus, max_slices);
   static const int shapes[][2] = {{1, 2}, {2, 2}, {1, 4}, {3, 2}, {1, 6}, {2, 4}, {2, 6}, {3, 4}, {4, 4}, {3, 6}, {4, 6}};   // by area
-  int tm = 0, tn = 0;
-  TilePlan p{};
   auto usable = [&](const int* c) {
     return c[0] <= MT && (EPI == EPI_SWIGLU ? c[0] < 4 || c[1] == 6 : c[1] <= 4);
   };
-  for (int ns = max_slices >= 8 && KT >= 64 ? 8 : max_slices >= 4 && KT >= 16 ? 4 : 1; ns >= 1 && !tm; ns /= 2)
-    for (const auto& c : shapes) {
-      if (!usable(c)) continue;
-      const TilePlan q = gemm_plan<EPI>(g, c[0], c[1], ns);
-      if (plan_wgs(q) <= cus) { tm = c[0]; tn = c[1]; p = q; break; }
+  GemmPick c{KERNEL_KWAVE, 0, 0, 8, {}};
+  for (int ns = max_slices >= 8 && KT >= 64 ? 8 : max_slices >= 4 && KT >= 16 ? 4 : 1; ns >= 1 && !c.rt; ns /= 2)
+    for (const auto& t : shapes) {
+      if (!usable(t)) continue;
+      const TilePlan q = gemm_plan<EPI>(g, t[0], t[1], ns);
+      if (plan_wgs(q) <= cus) { c.rt = t[0]; c.ct = t[1]; c.p = q; break; }
     }
-  if (!tm)                                               // more than one round whatever the tile: the largest usable one
-    for (const auto& c : shapes)
-      if (usable(c)) { tm = c[0]; tn = c[1]; p = gemm_plan<EPI>(g, tm, tn, 1); }
+  if (!c.rt)                                             // more than one round whatever the tile: the largest usable one
+    for (const auto& t : shapes)
+      if (usable(t)) { c.rt = t[0]; c.ct = t[1]; c.p = gemm_plan<EPI>(g, c.rt, c.ct, 1); }
+  return c;
+}
+// Returns the number of k-slices (1 unless `max_slices` allows more: outputs that are k-split partials); EPI_RESID: of the pieces of a
+// row's sum of squares.
+template <int EPI>
+static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t st) {
+  const GemmPick c = pick_gemm<EPI>(g, cus, max_slices);
+  if (c.kernel != KERNEL_KWAVE) return launch_gemm_tile<EPI>(g, c, st);
+  const TilePlan& p = c.p;
+#define KWAVE(TM, TN, U)                                                                             \
+  if (c.rt == TM && c.ct == TN) hipLaunchKernelGGL((k_gemm_kwave<EPI, TM, TN, 8, U>), dim3(8 * p.per_xcd), dim3(512), 0, st, g, p)
   KWAVE(1, 2, 4);
   else KWAVE(2, 2, 4);
   else KWAVE(1, 4, 4);
@@ -726,7 +747,7 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
   else if constexpr (EPI == EPI_SWIGLU) { KWAVE(1, 6, 4); else KWAVE(2, 6, 2); else KWAVE(3, 6, 1); else KWAVE(4, 6, 1); }
   else { KWAVE(4, 4, 2); }
   LAUNCH_CHECK();
-  return EPI == EPI_RESID ? p.n_colb * (tn / 2) : p.n_slices;
+  return EPI == EPI_RESID ? p.n_colb * (c.ct / 2) : p.n_slices;
 #undef KWAVE
 }
 
@@ -748,30 +769,35 @@ static int launch_attn_mfma_parts(const AttnArgs& a, int n_tg, int nkv, int B, h
   LAUNCH_CHECK();
   return SSD_OK;
 }
-template <int HD>
-static int launch_attn_mfma(AttnArgs a, int nchunks, int plan_chunks, bool prompt, int nkv, int B, int M, int cus, hipStream_t st) {
-  const int tiles = cdiv(a.rows.R * (a.nq / nkv), 16);
+struct AttnPick { int wq, wk, n_tg, part_chunks; };        // row tiles x key groups of a workgroup, groups of tiles, chunks of a part
+static AttnPick pick_attn_mfma(int hd, int rows, int group, int plan_chunks, bool prompt, int nkv, int B, int cus) {
+  const int tiles = cdiv(rows * group, 16);
   // Two tiles x four key groups (head size 64) where workgroups of four tiles would be for a quarter to half of the device: a chain
   // of half as many chunks, on twice the compute units where there are tiles for them (64 sequences x 8 rows at 128 to 1024 positions
   // 15.7 -> 13.6 us a launch).  With fewer workgroups than that the parts fill the device, and four tiles x two groups take 11.7 us for
   // 16 sequences x 7 rows where two x four take 13.0.
   const int four = B * nkv * cdiv(tiles, 4);
-  const bool narrow = HD == 64 && four <= cus / 2 && four >= cus / 4;
-  const int wq = narrow ? 2 : 4, n_tg = cdiv(tiles, wq);
-  int wk = narrow ? 4 : 2;
-  const int want = std::min(std::max(1, cus / (n_tg * nkv * B)), cdiv(plan_chunks, wk));
-  int part_chunks = cdiv(cdiv(plan_chunks, want), wk) * wk;
-  if (HD == 64 && !narrow && prompt && part_chunks > 16) {
-    wk = 4;
-    part_chunks = cdiv(part_chunks, wk) * wk;              // (a part is whole rounds of the key groups: they would walk into the next one)
+  const bool narrow = hd == 64 && four <= cus / 2 && four >= cus / 4;
+  AttnPick c{narrow ? 2 : 4, narrow ? 4 : 2, 0, 0};
+  c.n_tg = cdiv(tiles, c.wq);
+  const int want = std::min(std::max(1, cus / (c.n_tg * nkv * B)), cdiv(plan_chunks, c.wk));
+  c.part_chunks = cdiv(cdiv(plan_chunks, want), c.wk) * c.wk;
+  if (hd == 64 && !narrow && prompt && c.part_chunks > 16) {
+    c.wk = 4;
+    c.part_chunks = cdiv(c.part_chunks, c.wk) * c.wk;      // (a part is whole rounds of the key groups: they would walk into the next one)
   }
-  a.part_keys = part_chunks * 64;
-  a.nparts = cdiv(nchunks, part_chunks);
+  return c;
+}
+template <int HD>
+static int launch_attn_mfma(AttnArgs a, int nchunks, int plan_chunks, bool prompt, int nkv, int B, int M, int cus, hipStream_t st) {
+  const AttnPick c = pick_attn_mfma(HD, a.rows.R, a.nq / nkv, plan_chunks, prompt, nkv, B, cus);
+  a.part_keys = c.part_chunks * 64;
+  a.nparts = cdiv(nchunks, c.part_chunks);
   int rc;
   if constexpr (HD == 64)
-    rc = narrow ? launch_attn_mfma_parts<HD, 2, 4>(a, n_tg, nkv, B, st)
-         : wk == 4 ? launch_attn_mfma_parts<HD, 4, 4>(a, n_tg, nkv, B, st) : launch_attn_mfma_parts<HD, 4, 2>(a, n_tg, nkv, B, st);
-  else rc = launch_attn_mfma_parts<HD, 4, 2>(a, n_tg, nkv, B, st);
+    rc = c.wq == 2 ? launch_attn_mfma_parts<HD, 2, 4>(a, c.n_tg, nkv, B, st)
+         : c.wk == 4 ? launch_attn_mfma_parts<HD, 4, 4>(a, c.n_tg, nkv, B, st) : launch_attn_mfma_parts<HD, 4, 2>(a, c.n_tg, nkv, B, st);
+  else rc = launch_attn_mfma_parts<HD, 4, 2>(a, c.n_tg, nkv, B, st);
   if (rc) return rc;
   if (a.nparts > 1) {
     hipLaunchKernelGGL((k_attn_combine_parts<HD>), dim3(cdiv(M * a.nq, BLOCK / (HD / 4))), dim3(BLOCK), 0, st, a);
@@ -1552,4 +1578,33 @@ extern "C" int ssd_trace_barriers(ssd_kv* kv, int enable, void* stream, unsigned
   kv->trace_on = enable != 0;
   return SSD_OK;
 #endif
+}
+
+// ------------------------------------------------------------------------------------------------ launch plans (host only)
+extern "C" int ssd_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4]) {
+  if (!plan || rows < 1 || rows > MAX_ROWS || n < 1 || k < 32 || k % 32 || cus < 1) return fail(SSD_EINVAL, "bad GEMM size");
+  GemmArgs g;
+  memset(&g, 0, sizeof g);
+  g.M = rows; g.N = n; g.K = k;
+  GemmPick c;
+  switch (kind) {
+    case PROF_QKV: c = pick_gemm<EPI_QKV>(g, cus, 1); break;
+    case PROF_O: c = pick_gemm<EPI_RESID>(g, cus, 1); break;
+    case PROF_GATEUP: c = pick_gemm<EPI_SWIGLU>(g, cus, 1); break;
+    case PROF_DOWN: c = pick_gemm<EPI_PARTIAL>(g, cus, MAX_SPLITS); break;
+    case PROF_HEAD: c = pick_gemm<EPI_PARTIAL>(g, cus, 1); break;
+    default: return fail(SSD_EINVAL, "no GEMM of kind %d", kind);
+  }
+  plan[0] = c.kernel; plan[1] = c.rt; plan[2] = c.ct; plan[3] = c.p.n_slices;
+  return SSD_OK;
+}
+
+extern "C" int ssd_attention_plan(int head_dim, int n_q_heads, int n_kv_heads, int n_seqs, int rows, int prompt_positions, int cus, int plan[3]) {
+  if (!plan || (head_dim != 64 && head_dim != 128) || n_kv_heads < 1 || n_q_heads < n_kv_heads || n_q_heads % n_kv_heads || n_seqs < 1 || rows < 1 ||
+      rows * n_seqs > MAX_ROWS || prompt_positions < 0 || cus < 1)
+    return fail(SSD_EINVAL, "bad attention size");
+  const AttnPick c = pick_attn_mfma(head_dim, rows, n_q_heads / n_kv_heads, prompt_positions ? cdiv(prompt_positions, ATT_CHUNK) : ATT_PLAN_CHUNKS,
+                                    prompt_positions > 0, n_kv_heads, n_seqs, cus);
+  plan[0] = c.wq; plan[1] = c.wk; plan[2] = c.part_chunks;
+  return SSD_OK;
 }

@@ -64,10 +64,39 @@ class Pair:
         assert worst <= atol_kv, f"cache contents differ by {worst}"
         return worst
 
+    def check_rows(self, seq, rel):
+        """Each cached position's keys, and its values, of each layer against the oracle's: relative error of the row in the 2-norm."""
+        oc, worst = self.ocache[seq], 0.0
+        for l in range(self.shape["n_layers"]):
+            for got, ref in zip(self.kv.gather(seq, l, oc.length), (oc.k[l, :oc.length], oc.v[l, :oc.length])):
+                diff, size = (np.linalg.norm(a.reshape(oc.length, -1), axis=1) for a in (got - ref, ref))
+                worst = max(worst, (diff / size).max())
+        assert worst <= rel, f"a row's keys or values differ by {worst} of their norm"
+        return worst
+
     def check_free_stack(self):
         free, err = self.kv.free_stack()
         assert err == 0
         assert free == self.alloc.free, "free stack differs from the allocator model"
+
+
+def loud_weights(shape, seed):
+    """Weights with which every stage of a layer moves what the next layer stores: scores of spread 2, attention, SwiGLU and
+    down projection of the residual stream's own size.  (With make_weights' 0.02 the share of a tile of 16 columns in a row of a narrow
+    model is below any tolerance for the row.)  Rounded to bf16."""
+    w = si.make_weights(shape, seed)
+    d, nqd, ffn = shape["d_model"], shape["n_q_heads"] * shape["head_dim"], shape["d_ffn"]
+    nqk = nqd + shape["n_kv_heads"] * shape["head_dim"]
+    for l in range(shape["n_layers"]):
+        w[f"l{l}.wqkv"][:nqk] *= 70 / np.sqrt(d)
+        w[f"l{l}.wqkv"][nqk:] *= 50 / np.sqrt(d)
+        w[f"l{l}.wo"] *= 75 / np.sqrt(nqd)
+        w[f"l{l}.wgate"] *= 75 / np.sqrt(d)
+        w[f"l{l}.wup"] *= 75 / np.sqrt(d)
+        w[f"l{l}.wdown"] *= 50 / np.sqrt(ffn)
+        for n in ("wqkv", "wo", "wgate", "wup", "wdown"):
+            w[f"l{l}.{n}"] = torch.from_numpy(w[f"l{l}.{n}"].astype(np.float32)).bfloat16().float().numpy()
+    return w
 
 
 def draw_drafts(rng, V, K, pt_hint=None, alpha=2.0):

@@ -245,47 +245,69 @@ def test_narrowest_models(dtype, d, hd, ffn, K):
     pair.check_free_stack()
 
 
-@pytest.mark.parametrize("d,rows", [(32, 65), (96, 80), (544, 64), (544, 65), (1056, 513), (2112, 81), (1600, 1009)])
+def check_prompt(shape, rows, seed, tweak=None):
+    """A prompt of `rows` positions in one forward with one launch per operator, on two layers of weights with which a tile counts
+    (tests.parity.loud_weights), against the oracle with the cache's format.  Keys and values then differ where they round the other
+    way, by at most one step of bf16, 2^-7 of the element: no row of a position by more than that of its norm."""
+    from tests.parity import Pair, loud_weights
+    w = loud_weights(shape, seed)
+    if tweak:
+        tweak(w)
+    pair = Pair(None, 0, rows + 32, max_rows=1024, shape=shape, weights=w, store="bf16")
+    pair.prefill(0, np.random.default_rng(seed + 1).integers(0, 43, rows + 1))
+    assert pair.kv.last_forward_path() == 1
+    pair.check_rows(0, 2.0 ** -7)
+    pair.check_state(0, 2.0 ** -4)           # (a step of a value between 8 and 16)
+    pair.check_free_stack()
+
+
+@pytest.mark.parametrize("d,rows", [(32, 65), (96, 80), (544, 64), (544, 65), (1056, 513), (2112, 81), (1056, 961), (1600, 1009), (2464, 769),
+                                    (2080, 961), (3104, 961)])
 def test_norm_between_the_projections_of_a_prompt(d, rows):
     """The output projection leaves a row's sum of squares in pieces that gate / up adds: one per 16 columns up to 64 rows, above that one
-    per pair of tiles or per workgroup - fewer than 16 pieces, ragged, more than 64 (d = 2112), both kernels (1600 x 1009 does not
-    fit one round of the first).  Two layers: keys and values of the second against the oracle with the cache's format."""
-    from tests.parity import Pair
-    shape = dict(n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=96, vocab=41, n_embed=43, dtype="bf16",
-                 qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
-    pair = Pair(None, 85, rows + 32, max_rows=1024, shape=shape, store="bf16")
-    pair.prefill(0, np.random.default_rng(86).integers(0, 43, rows + 1))
-    assert pair.kv.last_forward_path() == 1
-    pair.check_state(0, 2e-2)
-    pair.check_free_stack()
+    per pair of tiles or per workgroup - fewer than 16 pieces, ragged, more than 64 (d = 2112), both kernels and every tile of theirs
+    (test_launch_plans_cpu.py).  The last 32 columns are made a third of a row's sum or more."""
+    def tweak(w):
+        for l in range(2):
+            w[f"l{l}.wo"][-32:] *= 8.0
+
+    check_prompt(dict(n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=96, vocab=41, n_embed=43, dtype="bf16",
+                      qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6), rows, 85, tweak)
 
 
 @pytest.mark.parametrize("d,ffn,rows", [(32, 96, 65), (64, 8992, 71), (96, 8992, 97), (64, 4896, 250), (32, 8992, 257), (96, 4896, 321),
-                                        (32, 8992, 250), (64, 4896, 513), (64, 8992, 449), (1056, 2016, 65), (1056, 2016, 449)])
+                                        (32, 8992, 250), (64, 4896, 513), (64, 8992, 449), (1056, 2016, 65), (1056, 2016, 449),
+                                        (3616, 96, 897), (4128, 96, 961)])
 def test_gate_up_and_down_at_each_tile_of_many_rows(d, ffn, rows):
     """Each tile of the gate / up projection that the estimate picks (in this order: 4 x 8 of k_gemm_block, 5 x 6, 7 x 6, 4 x 10, then
-    4 x 8 of k_gemm_tile, 8 x 8, 8 x 10, 8 x 12, 16 x 10; the last two are for down's 4 x 8 and 8 x 7), with fewer k-tiles than buffers,
-    a last row tile of one row, and a ragged last column block.  Two layers, as above."""
-    from tests.parity import Pair
-    shape = dict(n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=ffn, vocab=41, n_embed=43, dtype="bf16",
-                 qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
-    pair = Pair(None, 87, rows + 32, max_rows=1024, shape=shape, store="bf16")
-    pair.prefill(0, np.random.default_rng(88).integers(0, 43, rows + 1))
-    assert pair.kv.last_forward_path() == 1
-    pair.check_state(0, 2e-2)
-    pair.check_free_stack()
+    4 x 8 of k_gemm_tile, 8 x 8, 8 x 10, 8 x 12, 16 x 10; the last four are for down's 4 x 8, 8 x 7, 8 x 8 and 16 x 6; test_launch_plans_cpu.py
+    holds the choice), with fewer k-tiles than buffers, a last row tile of one row, and a ragged last column block.  The last 16 of a row's SwiGLU
+    columns move its keys and values in the second layer by 1.2 % or more."""
+    check_prompt(dict(n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=ffn, vocab=41, n_embed=43, dtype="bf16",
+                      qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6), rows, 87)
 
 
 @pytest.mark.parametrize("nq,nkv,hd,rows", [(2, 1, 64, 513), (15, 3, 64, 1009), (5, 1, 128, 640), (9, 1, 128, 1024)])
 def test_qkv_projection_of_more_than_512_rows(nq, nkv, hd, rows):
-    """Both of its tiles, 4 x 4 and (336 and 352 workgroups of that) 4 x 8, with last blocks of half a head and of a few rows."""
-    from tests.parity import Pair
-    shape = dict(n_layers=2, d_model=64, n_q_heads=nq, n_kv_heads=nkv, head_dim=hd, d_ffn=96, vocab=41, n_embed=43, dtype="bf16",
+    """Both of its tiles, 4 x 4 and (336 and 352 workgroups of that) 4 x 8, with last blocks of half a head and of a few rows.  16 dims of
+    one query head of a row move its values in the second layer by 5 % or more."""
+    check_prompt(dict(n_layers=2, d_model=64, n_q_heads=nq, n_kv_heads=nkv, head_dim=hd, d_ffn=96, vocab=41, n_embed=43, dtype="bf16",
+                      qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6), rows, 89)
+
+
+def test_head_of_many_rows():
+    """97 sequences x 8 rows: the head in tiles of 16 x 8, with a last block of eight of its 48 row tiles and a ragged last column block
+    (test_launch_plans_cpu.py)."""
+    from tests.parity import Pair, verify_parity_step
+    shape = dict(n_layers=1, d_model=64, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=96, vocab=6564, n_embed=6564, dtype="bf16",
                  qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
-    pair = Pair(None, 89, rows + 32, max_rows=1024, shape=shape, store="bf16")
-    pair.prefill(0, np.random.default_rng(90).integers(0, 43, rows + 1))
+    B, K = 97, 7
+    pair = Pair(None, 93, 32, max_seqs=B, max_rows=K + 1, shape=shape, store="bf16")
+    rng = np.random.default_rng(94)
+    for b in range(B):
+        pair.prefill(b, rng.integers(0, 6564, 2 + b % 9))
+    verify_parity_step(pair, dict(beta=0.3, seed=95), K, 0, rng, 4e-3, 4e-3, seqs=range(B))
     assert pair.kv.last_forward_path() == 1
-    pair.check_state(0, 2e-2)
     pair.check_free_stack()
 
 
