@@ -199,7 +199,10 @@ def test_batched_cycles_in_lockstep_with_oracle(B, K, target_path):
     """Whole SSD cycles of several sequences at once: after a verification some sequences have one pending draft row and
     some two (everything accepted), so one draft launch mixes active and inactive rows, the draft caches roll back by
     different amounts, and every sequence is followed by an oracle of its own.  Four sequences stay on the persistent
-    kernels throughout; sixteen have 16-row draft steps there, 32-row first steps and the verification per operator."""
+    kernels throughout; sixteen have 16-row draft steps there, 32-row first steps and the verification per operator.
+    With beta = 0.1 a sequence accepts all of its drafts in about two cycles of three (oracle, four seeds: 0.56 to 0.72 of them with four
+    sequences, 0.65 to 0.81 with sixteen): a cycle in which all do, or none, has a probability of at most 0.28, and less than two
+    mixed ones of eight of 1e-3."""
     import paper_2505_15380_amd as ssd
     from oracle import decoder as OD, ssd as OS
     from oracle.accept import sample_canonical
@@ -211,7 +214,7 @@ def test_batched_cycles_in_lockstep_with_oracle(B, K, target_path):
     steps, tol = 8, 2e-2
     lens = [21, 40, 33, 64, 17, 90, 48, 31, 16, 75, 52, 29, 63, 44, 36, 81][:B]
     toks = [si.make_prefix(ts, 4, n - 4, 500 + b) for b, n in enumerate(lens)]
-    cfg = dict(beta=0.5, temperature=1.0, top_k=0, greedy=False, seed=31)
+    cfg = dict(beta=0.1, temperature=1.0, top_k=0, greedy=False, seed=31)
     dcfg = dict(beta=0.0, temperature=1.0, top_k=0, greedy=False, seed=32)
     max_pos = max(lens) + steps * (K + 1) + 40
     sess = ssd.SSDSession(ts, tw, ds, dw, B, K, max_pos, ssd.sample_config(**cfg), ssd.sample_config(**dcfg))
@@ -223,7 +226,7 @@ def test_batched_cycles_in_lockstep_with_oracle(B, K, target_path):
         OD.prefill(t, tc[b], toks[b][:-1]); OD.prefill(d, dc[b], toks[b][:-1])
         pending.append(int(toks[b][-1])); dpend.append([int(toks[b][-1])])
     V = ts["vocab"]
-    mixed = False
+    mixed = 0
     for step in range(steps):
         out = dict(n_accepted=torch.zeros(B, dtype=torch.int32, device="cuda"),
                    next_token=torch.zeros(B, dtype=torch.int32, device="cuda"),
@@ -256,8 +259,8 @@ def test_batched_cycles_in_lockstep_with_oracle(B, K, target_path):
             st, sd = sess.kv.state(b), sess.kv_d.state(b)
             assert st["len"] == tc[b].length and st["pending"] == [pending[b]], (step, b)
             assert sd["len"] == dc[b].length and sd["pending"] == dpend[b], (step, b)
-        mixed = mixed or (K in ns and any(n < K for n in ns))
-    assert mixed                                          # one and two pending draft rows occurred in the same launch
+        mixed += K in ns and any(n < K for n in ns)
+    assert mixed >= 2                                     # one and two pending draft rows occurred in the same launch
 
 
 def test_many_sequences_reserve_blocks_in_one_launch():
