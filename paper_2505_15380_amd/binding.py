@@ -102,12 +102,19 @@ def _check(rc):
         raise SSDError(rc, load_library().ssd_last_error().decode())
 
 
+# torch.cuda.current_stream() builds a Stream object around the handle: 4 us a call, of the 20 us that the host needs for ssd_warp_probs and
+# ssd_verify_from_probs together.  The two functions it asks are not public, so a torch without them gets the public call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    """Handle of the current device's current stream.  (torch.cuda.current_stream() builds a Stream object of it: 4 us a call, of
-    the 20 us that the host needs for ssd_warp_probs and ssd_verify_from_probs together.)"""
+    """Handle of the current device's current stream."""
     if not torch.cuda.is_initialized():
         torch.cuda.init()
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _ptr(t):

@@ -402,6 +402,19 @@ def test_prompt_attention_where_later_scores_exceed_the_first(nq, nkv, rows, pos
             assert np.linalg.norm(got - ref) <= 1e-2 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("missing", [None, "_raw_stream", "_current_device"])
+def test_calls_go_to_the_current_stream(missing, monkeypatch):
+    """The handle that every call passes on, by torch's private functions and by the public call where one of those is missing."""
+    from paper_2505_15380_amd import binding
+    if missing:
+        monkeypatch.setattr(binding, missing, None)
+    side = torch.cuda.Stream()
+    assert binding._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert binding._stream() == side.cuda_stream
+    assert binding._stream() == torch.cuda.current_stream().cuda_stream != side.cuda_stream
+
+
 def test_rollback_and_reverify():
     """After a verification that rejected drafts, positions below the new length are untouched, stale positions
     are overwritten by the next call, and an explicit rollback frees whole blocks in the documented order."""
