@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
 
 // ------------------------------------------------------------------------------------------ warp + softmax
 __device__ __forceinline__ uint32_t order_key(float f) {      // larger float <-> larger key
-  const uint32_t u = __float_as_uint(f);
+  const uint32_t u = __float_as_uint(f + 0.0f);              // (-0 is +0: they tie)
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 

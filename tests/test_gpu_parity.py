@@ -134,6 +134,22 @@ def test_top_k_cut_at_the_edges_of_the_candidate_set(k):
     assert np.abs(got - ref).max() < 1e-6
 
 
+@pytest.mark.parametrize("V,k", [(5, 2), (600, 200), (6564, 25), (6564, 3300), (9000, 513)])
+def test_top_k_cut_among_zeros_of_both_signs(V, k):
+    """-0 and +0 are one value: where the cut falls among them, the lower indices stay.  And subnormal numbers are not zeros."""
+    import paper_2505_15380_amd as ssd
+    from oracle.warp import warp_probs
+    rng = np.random.default_rng(V + k)
+    z = np.where(rng.random((4, V)) < 0.5, np.float32(0.0), np.float32(-0.0))
+    z[1] = np.where(rng.random(V) < 0.5 * k / V, np.float32(1.0), z[1])
+    z[2] = np.where(rng.random(V) < 0.3, np.float32(-1.0), z[2])
+    z[3] = rng.integers(-3, 4, V).astype(np.float32) * np.float32(1e-41)
+    got = ssd.ssd_warp_probs(torch.from_numpy(z).cuda(), ssd.sample_config(top_k=k)).cpu().numpy()
+    ref = warp_probs(z.astype(np.float64), 1.0, k, False)
+    assert ((got > 0) == (ref > 0)).all()
+    assert np.abs(got - ref).max() < 1e-6
+
+
 @pytest.mark.parametrize("V,k", [(2, 1), (9, 5), (60, 25), (260, 50), (1030, 25), (6564, 25), (6564, 50), (6564, 128), (9000, 128), (16384, 300)])
 def test_top_k_cut_where_large_entries_share_their_threads(V, k):
     """The kernel bounds the cut by the maxima of 128 groups of entries (i % 1024 // 8).  Rows whose large entries lie in one group,
