@@ -146,7 +146,8 @@ __global__ void __launch_bounds__(WAVE) k_attn_combine(AttnArgs a) {
 // (1024 positions; head size 128: 512) is finished there, the parts of a longer one are merged by k_attn_combine: a row's order
 // of sums depends on its position alone, whatever the launch.  (The chunk kernels above for long sequences in small batches, this
 // one for the rest, would give it two; five rows at 960 / 2048 / 8000 positions: 23 / 27 / 29 us with head size 64 where they
-// take 23 / 39 / 73, 33 / 35 / 45 with head size 128: 52 / 55 / 115.)  Scores and outputs are computed
+// take 23 / 39 / 73, 33 / 35 / 45 with head size 128: 52 / 55 / 115.  With values and keys requested together, 64: 23 / 26 / 28,
+// and four heads of size 32 14.7 / 18.2 / 20.3 where they were 17.6 / 21.0 / 23.6; 128: no difference.)  Scores and outputs are computed
 // transposed: a lane holds one row's scores of the keys 4 kg .. 4 kg + 3 of a tile, which is what the product with the
 // values wants from it, and both operands come from the cache as 16 bytes per lane (dims of a key, tokens of a dim).
 // A chain of launch, block table, cache, merge bounds it: 6.1 us at five rows and 68 cached positions, where the two kernels
@@ -297,15 +298,15 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
 // 16x16x32 matrix instructions (36 per wave and chunk, 16 cycles each) a SIMD issues about two vector instructions for nothing, and
 // a wave has 80 a chunk, half of them for the split of P, and 16 exponentials.  With few keys per workgroup it is the chain of
 // dependent latencies, and the code itself, fetched cold by every launch.
-// So there are two forms.  Eight waves (4 tiles x 2 key groups, or 2 x 4: the launch's choice) take short parts: one copy of the loop,
-// the reference is the running maximum.  4 x 4 takes prompts whose parts have more than 16 chunks (and head size 64: 128 KB of LDS): sixteen waves to overlap matrix and vector
-// instructions, and the reference, the maximum of the row's first chunk, moves only to a score that exceeds it by ATT_LAZY, so that
+// So there are two loops.  Eight waves (4 tiles x 2 key groups, or 2 x 4: the launch's choice) take short parts: one copy of the code,
+// the reference is the running maximum.  4 x 4 takes prompts whose parts have more than 16 chunks (and head size 64: 128 KB of LDS):
+// sixteen waves to overlap matrix and vector instructions, and the reference, the maximum of the row's first chunk, moves only to a score that exceeds it by ATT_LAZY, so that
 // the usual chunk asks each lane for its own largest score and no more (some row of sixteen has a new maximum in most chunks: a
 // maximum across lanes and 40 instructions of scaling).  The heaviest key then weighs anything up to 2^8 instead of 1, which the
 // truncating split holds exactly; the split of later chunks rounds hi to nearest in return (error against 64 bits 0.85 times the other
 // form's over 24 shapes; 1.02 times without).  1024 rows of the 0.5B shape at 0 / 1024 / 3072 cached positions: 14.6 / 22.8 / 38.7 us, with
-// 4 x 2 15.8 / 25.0 / 47.1; the same form with 4 x 2 14.6 / 24.2 / 43.1 but 0.5 us more for the batches' launches; 97 rows 7.7 against
-// 6.1.  Two row tiles per wave, which read keys and values half as often, took as long with as many waves and a quarter longer with half.
+// 4 x 2 15.8 / 25.0 / 47.1; the same loop with 4 x 2 14.6 / 24.2 / 43.1 but 0.5 us more for the batches' launches; 97 rows 7.7 against
+// 6.1.  (Those times are of the kernel alone.  Where the line lies between the forms: pick_attn_mfma.)  Two row tiles per wave, which read keys and values half as often, took as long with as many waves and a quarter longer with half.
 constexpr float ATT_LAZY = 8.0f;                         // weights may reach 2^8 before the reference moves (fp32 sums and the hi + lo split of
                                                          // a weight are as exact at any scale)
 

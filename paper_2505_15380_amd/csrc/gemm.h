@@ -37,8 +37,8 @@ struct GemmArgs {
   int act_split_kt;     // > 0: act is written as split rows (common.h) with this many k-tiles per row (N / 32)
   // the norm before a GEMM without a pass of its own.  fp32: A is the residual stream, and a kernel given a `gain` normalises
   // its rows itself (and EPI_RESID only adds to the residual stream).  bf16: EPI_RESID adds the residual and leaves what the next GEMM
-  // needs: its operand h * gain, and each row's sum of squares over every 16 columns.  EPI_SWIGLU with rms_d > 0 divides
-  // its results by the row's r.m.s. computed from these.
+  // needs: its operand h * gain, and each row's sum of squares, over every 16 columns (launches of up to 64 rows) or in sum_pieces
+  // pieces.  EPI_SWIGLU with rms_d > 0 divides its results by the row's r.m.s. computed from these.
   float* h;             // EPI_RESID: residual stream [M][N], updated
   const float* gain;    // fp32: gain of the norm before; bf16, EPI_RESID: gain of the norm that follows
   void* hg;             // EPI_RESID: h * gain as split rows

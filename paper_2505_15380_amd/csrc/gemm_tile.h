@@ -232,6 +232,9 @@ __device__ __forceinline__ void store_row_sum(const GemmArgs& g, int row, int pi
 // that all waves need go from memory to LDS with direct loads (16 bytes per lane, a fragment per instruction, no
 // registers), NBUF - 1 k-tiles ahead.  One barrier per k-tile: it is passed when every wave's share of k-tile k has
 // arrived and every wave has read k-tile k - 1, whose buffer the next request then overwrites.
+// What bounds it: matrix instructions and the intake of operands hide only part of each other.  Gate / up of 1024 rows of the 0.5B shape (16 x 10,
+// cold weights) 37.9 us; without the loop's requests 30.4, without its matrix instructions 26.0; some 9 of each are launch, first
+// operands and epilogue.  Of the 1.5B shape 96.6, 79.5 and 68.3; its down projection (16 x 6, four slices) 50.7, 36.2 and 48.1.
 template <int EPI, int TM, int TN, int W, int NBUF, int UA, int MINB>
 __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan p) {
   constexpr int LW = (TN + W - 1) / W;                     // weight fragments a wave requests per k-tile
@@ -351,8 +354,10 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
 // slots) reads the fragments of k-tile k + 1 into registers beside the matrix instructions of k-tile k.  No load in flight has a register,
 // so the only waits are the counted ones.  One barrier per k-tile: it is passed when every wave has read k-tile k, whose buffer the next
 // request then overwrites, and every wave's share of k-tile k + 1 has arrived.  Order of an element's sum as in k_gemm_tile.
-// What bounds it is the intake of a compute unit, 60 bytes a nanosecond of activations that every column block reads again and
-// of weights from HBM, whatever the depth (3 to 11 k-tiles in flight: the same).
+// What bounds it up to about 250 rows is the intake of a compute unit, 60 bytes a nanosecond of activations that every column block
+// reads again and of weights from HBM, whatever the depth (3 to 11 k-tiles in flight: the same): gate / up of 97 rows (7 x 6) 14.6 us, without
+// the loop's requests 10.9, without its matrix instructions 13.6.  With more rows it is as with k_gemm_tile: down of 1024 rows of the 0.5B shape (8 x 7,
+// four slices) 19.8, 16.6 and 15.1.
 // k_gemm_tile's best tile -> this one's, us, cold weights: gate / up of 72, 112, 160 rows of the 0.5B shape 12.8 -> 11.2, 12.9 -> 12.1,
 // 13.8 -> 12.0; of the 1.5B shape 23.8 -> 21.3, 25.0 -> 22.8, equal; down of the 1.5B shape, 72 and 112 rows, 15.4 -> 13.8, 16.5 -> 15.2, of 320
 // rows 29.5 -> 26.1.  With more rows the two are equal, but for the QKV projection, whose tiles are small: 1024 rows of the 0.5B shape

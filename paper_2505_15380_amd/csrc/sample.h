@@ -145,8 +145,8 @@ struct WarpArgs {
 };
 
 constexpr int SBLOCK = 1024;          // threads of the two sampler kernels (16 waves): short unrolled loops, small code
-constexpr int SPER = 16;              // elements per thread at most: vocab <= 16384.  The kernels are instantiated for 8 and 16
-                                      // (the loops over a thread's elements are unrolled to that count, so a small vocabulary pays for 8)
+constexpr int SPER = 16;              // elements per thread at most: vocab <= 16384.  The kernels are instantiated for 1, 8 and 16: the
+                                      // loops over a thread's elements are unrolled to that count, and what a vocabulary does not fill costs
 constexpr int TOPK_CAND = 1024;       // top-k candidates that are ranked in LDS
 
 // Reductions over the 16 waves of a sampler workgroup through 16 LDS entries, which are this reduction's alone (a later one that

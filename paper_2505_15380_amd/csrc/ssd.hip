@@ -610,6 +610,7 @@ struct LdsOptIn {
 // weights at 72 to 1024 rows of both model shapes and fitted by least squares: what a k-tile takes at all, and what it takes
 // for each of a compute unit's workgroups.  Partial outputs cost their write at 4.2 TB/s and their read at 5.  The shape that is picked is 0.6 %
 // on average, at most 8 %, slower than the fastest of 32 shapes at each of 94 sizes; those that are left out were nowhere needed for that.
+// (Other widths follow the same two figures; none was measured.)
 // (An estimate from cycles per tile and per KB, which stood here, was 6 % behind on average, and up to 30 %: us with it -> with this, 72 rows
 // of gate / up of the 1.5B shape 25.1 -> 21.3, 256 39.2 -> 35.0, 640 68.0 -> 63.6; down of 320 rows 33.0 -> 26.1, 768 58.2 -> 52.0;
 // head of 112 rows 160 -> 137.)
@@ -774,8 +775,12 @@ static AttnPick pick_attn_mfma(int hd, int rows, int group, int plan_chunks, boo
   const int tiles = cdiv(rows * group, 16);
   // Two tiles x four key groups (head size 64) where workgroups of four tiles would be for a quarter to half of the device: a chain
   // of half as many chunks, on twice the compute units where there are tiles for them (64 sequences x 8 rows at 128 to 1024 positions
-  // 15.7 -> 13.6 us a launch).  With fewer workgroups than that the parts fill the device, and four tiles x two groups take 11.7 us for
-  // 16 sequences x 7 rows where two x four take 13.0.
+  // 15.7 -> 13.6 us a launch; a prompt of 293 to 585 rows of the 0.5B shape, with the merge and between events, 12.4 -> 10.2 at 300 rows,
+  // 14.5 -> 10.7 at 512, 15.8 -> 11.9 at 576).  With fewer workgroups than that the parts fill the device, and four tiles x two groups take
+  // 11.7 us for 16 sequences x 7 rows where two x four take 13.0.
+  // Four x four for prompts whose parts have more than 16 chunks, all of which gain (attention.h).  From 11 chunks on some do: a
+  // prompt's first launch of the 0.5B shape, us between events with 4 x 2 and with 4 x 4: 592 rows (10 chunks) 13.6 and 14.1, 700 (11)
+  // 14.9 and 14.6, 832 (13) 16.6 and 15.9, 1024 (16) 18.3 and 17.1.
   const int four = B * nkv * cdiv(tiles, 4);
   const bool narrow = hd == 64 && four <= cus / 2 && four >= cus / 4;
   AttnPick c{narrow ? 2 : 4, narrow ? 4 : 2, 0, 0};
