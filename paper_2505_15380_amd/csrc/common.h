@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+
 namespace ssd {
 
 constexpr int WAVE = 64;
@@ -227,6 +229,10 @@ __device__ __forceinline__ uint2 lo_pairs(const f32x4 v) {             // bf16 o
   for (int i = 0; i < 4; ++i) r[i] = v[i] - __uint_as_float(__float_as_uint(v[i]) & 0xFFFF0000u);
   return make_uint2(f2_to_bf16x2(r[0], r[1]), f2_to_bf16x2(r[2], r[3]));
 }
+
+// f of the constants 0, 1, ..
+template <typename F, int... I>
+__device__ __forceinline__ void for_each_index(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }
 
 __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 

@@ -41,8 +41,6 @@
 // The launch number is not a kernel argument: it is read from the cache's control words, and the kernel that follows
 // every forward on the stream advances it, so a captured graph of launches can be replayed.
 #pragma once
-#include <utility>
-
 #include "persistent.h"
 
 namespace ssd {
@@ -107,8 +105,6 @@ __device__ __forceinline__ void st_word(u64* p, uint32_t payload, uint32_t tag) 
 __device__ __forceinline__ void st_wordf(u64* p, float x, uint32_t tag) { st_word(p, __float_as_uint(x), tag); }
 // Two consecutive words (16-byte aligned) with one store: a word is still stored by one instruction, and each has its tag.  (The
 // s_nop: store data of more than 8 bytes must not be overwritten by the next two vector instructions.)
-template <typename F, int... I>
-__device__ __forceinline__ void for_each_index(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }
 template <int OFFSET = 0>
 __device__ __forceinline__ void st_words2(u64* p, uint32_t x0, uint32_t x1, uint32_t tag) {
   const u32x4 a = {x0, tag, x1, tag};

@@ -8,21 +8,34 @@
 namespace ssd {
 
 // How the output is cut up: blocks of row tiles x blocks of column tiles (x k-slices where the output is k-split
-// partials).  Consecutive workgroup indices go to the eight XCDs in turn; each XCD takes a contiguous run of the order
-// (slice, column block, row block), so that its L2 holds one k range of the activations and each weight is fetched by
-// one XCD.
+// partials).  Consecutive workgroup indices go to the eight XCDs in turn, and each XCD's L2 fetches what its workgroups read: the XCDs of a
+// slice form a grid of row groups x column groups, each XCD a contiguous rectangle of blocks, so that activations are fetched by as many XCDs as
+// there are column groups, and weights by as many as there are row groups (the host takes the grid of the least bytes).
 struct TilePlan {
   int n_colb, n_rowb, n_slices, slice_kt;     // slice_kt: k-tiles per workgroup
-  int per_xcd;                                // ceil(workgroups / 8)
+  int per_xcd;                                // workgroups of an XCD
+  int rows_xcd, cols_xcd;                     // blocks of an XCD's rectangle; rows_xcd = 0: each XCD takes a contiguous run of the order
+                                              // (slice, column block, row block)
+  int lg_per, lg_colg;                        // logarithms of a slice's XCDs and of its column groups
+  uint32_t rows_inv;                          // 2^20 / rows_xcd + 1
 };
+// (Three integer divisions here took 0.1 us of every launch.)
 __device__ __forceinline__ bool tile_block(const TilePlan& p, int& colb, int& rowb, int& slice) {
-  const int o = (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3);
+  const int x = (int)(blockIdx.x & 7), i = (int)(blockIdx.x >> 3);
+  if (p.rows_xcd) {
+    const int y = x & ((1 << p.lg_per) - 1), c = (int)(((uint32_t)i * p.rows_inv) >> 20);
+    slice = x >> p.lg_per;
+    rowb = (y >> p.lg_colg) * p.rows_xcd + i - c * p.rows_xcd;
+    colb = (y & ((1 << p.lg_colg) - 1)) * p.cols_xcd + c;
+    return i < p.per_xcd && rowb < p.n_rowb && c < p.cols_xcd && colb < p.n_colb;
+  }
+  const int o = x * p.per_xcd + i;
   const int per_slice = p.n_colb * p.n_rowb;
   slice = o / per_slice;
   const int rem = o - slice * per_slice;
   colb = rem / p.n_rowb;
   rowb = rem - colb * p.n_rowb;
-  return slice < p.n_slices && (int)(blockIdx.x >> 3) < p.per_xcd;
+  return slice < p.n_slices && i < p.per_xcd;
 }
 
 // Column tile of slot j of column group cb (a group has TN slots).  SwiGLU: the first half of the slots from the gate matrix,
@@ -33,9 +46,8 @@ __device__ __forceinline__ int slot_tile(int cb, int j, int hd) {
   if (EPI == EPI_PARTIAL || EPI == EPI_RESID) return cb * TN + j;
   const int p = cb * (TN / 2) + (j % (TN / 2));
   if (EPI == EPI_SWIGLU) return p;
-  const int per_head = hd >> 5;
-  const int head = p / per_head, i = p - head * per_head;
-  return head * (hd >> 4) + i + (j >= TN / 2 ? per_head : 0);
+  const int lg = __builtin_ctz(hd) - 5, head = p >> lg, i = p - (head << lg);      // (head sizes are powers of two)
+  return (head << (lg + 1)) + i + (j >= TN / 2 ? 1 << lg : 0);
 }
 
 // What the QKV epilogue needs of a row, requested ahead of the contraction.
@@ -182,7 +194,7 @@ __device__ __forceinline__ float tile_epilogue(const GemmArgs& g, int t0, int t1
     *(uint2*)(o + 512) = lo_pairs(y);
   } else {
     const int hd = g.kv.hd, half = hd >> 1, nq = g.nq, nkv = g.kv.nkv;
-    const int n0 = t0 * 16 + col, head = n0 / hd, d = n0 - head * hd;
+    const int n0 = t0 * 16 + col, head = n0 >> __builtin_ctz(hd), d = n0 & (hd - 1);
     if (g.bias) {
       const f32x4 b0 = *(const f32x4*)(g.bias + n0), b1 = *(const f32x4*)(g.bias + n0 + half);
 #pragma unroll
@@ -226,19 +238,43 @@ __device__ __forceinline__ void store_row_sum(const GemmArgs& g, int row, int pi
   if (row < g.M && (threadIdx.x & 63) < 16) g.sumsq[(size_t)row * ((pieces + 15) & ~15) + piece] = sum;
 }
 
+// Direct loads to LDS, 16 bytes a lane.  Through a buffer descriptor: after global_load_lds, which the compiler counts as a flat access to both
+// memories, every wait that it places for a load or an LDS read is one for all of them, and the loads in flight ahead were waited for
+// once per round of the loops below.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t load_rsrc(const void* base) { return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, 0x7FFFFFF0, 0x00027000); }
+__device__ __forceinline__ void load_to_lds(rsrc_t r, void* lds, int lane_off, int off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, lane_off, off, 0, 0);
+}
+
+// The order of a k-tile's instructions: a matrix instruction or two, then a request to memory or a read of the next k-tile's fragments, and so
+// on.  (Left alone, the compiler puts the reads behind nearly all of the matrix instructions, right ahead of the wait for them.)
+template <int MFMA, int VMEM, int READS>
+__device__ __forceinline__ void sched_interleave() {
+  constexpr int N = VMEM + READS;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (MFMA > i) __builtin_amdgcn_sched_group_barrier(0x008, MFMA >= 2 * N ? 2 : 1, 0);
+    if (i < VMEM) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    else __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x008, MFMA, 0);
+}
+
 // ------------------------------------------------------------------------------------------ large tiles
 // A workgroup of W waves owns W * TM row tiles x TN column-tile slots over a k range; wave w owns row tiles w TM .. and
 // all the column tiles.  It loads its own activation fragments into registers, UA k-tiles ahead; the weight fragments
 // that all waves need go from memory to LDS with direct loads (16 bytes per lane, a fragment per instruction, no
-// registers), NBUF - 1 k-tiles ahead.  One barrier per k-tile: it is passed when every wave's share of k-tile k has
-// arrived and every wave has read k-tile k - 1, whose buffer the next request then overwrites.
-// What bounds it: matrix instructions and the intake of operands hide only part of each other.  Gate / up of 1024 rows of the 0.5B shape (16 x 10,
-// cold weights) 37.9 us; without the loop's requests 30.4, without its matrix instructions 26.0; some 9 of each are launch, first
-// operands and epilogue.  Of the 1.5B shape 96.6, 79.5 and 68.3; its down projection (16 x 6, four slices) 50.7, 36.2 and 48.1.
+// registers), NBUF k-tiles ahead, and from there into registers one k-tile ahead, beside the matrix instructions.  One barrier per k-tile: it is
+// passed when every wave has read k-tile k, whose buffer the next request then overwrites, and every wave's share of k-tile k + 1 has arrived.
+// What bounds it with many rows is power: gate / up of 1024 rows of the 0.5B shape (16 x 10) 35 us; a k-tile takes 1450 cycles where the matrix
+// instructions need 1280, but at 1.6 GHz instead of 2.4 (the same instructions on registers alone sustain 2.1 GHz, with the reads from LDS 2.0;
+// 32 x 32 x 16 instructions 1.8).  3 us of it are launch and first operands, 4 the epilogue.  With few rows it is latency.  Ahead of the waits, the order
+// and the reads above, in a forward: 35.8 -> 34.5 us; 8 x 7 of down 21.7 (k_gemm_block) -> 20.8; output projection 10.6 (k_gemm_kwave) -> 10.0.
 template <int EPI, int TM, int TN, int W, int NBUF, int UA, int MINB>
 __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan p) {
   constexpr int LW = (TN + W - 1) / W;                     // weight fragments a wave requests per k-tile
-  static_assert(EPI != EPI_QKV && UA >= NBUF - 1, "the first waits rely on it");
+  static_assert(UA >= NBUF - 1 && UA % 2 == 0 && (EPI == EPI_PARTIAL || EPI == EPI_RESID || TN % 2 == 0), "the first waits rely on it");
   __shared__ u32x4 stage[NBUF][TN][64];
   int colb, rowb, slice;
   if (!tile_block(p, colb, rowb, slice)) return;
@@ -246,21 +282,20 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
   const int KT = g.K >> 5, ntiles = (g.N + 15) >> 4, last_mt = (g.M - 1) >> 4;
   const int kb = slice * p.slice_kt, nk = min(KT, kb + p.slice_kt) - kb;
   const int hd = g.kv.hd;
-  const char* ws[LW];
+  rsrc_t ws[LW];
   int wdst[LW];
 #pragma unroll
   for (int q = 0; q < LW; ++q) {                           // (the last ones repeat an earlier slot where TN is not a multiple of W)
     const int j = (q * W + wave) % TN;
     const int t = slot_tile<EPI, TN>(colb, j, hd);
     const void* w = (EPI == EPI_SWIGLU && j >= TN / 2) ? g.W1 : g.W0;
-    ws[q] = (const char*)w + ((size_t)(t < ntiles ? t : 0) * KT + kb) * 1024 + lane * 16;
+    ws[q] = load_rsrc((const char*)w + ((size_t)(t < ntiles ? t : 0) * KT + kb) * 1024);
     wdst[q] = j;
   }
   auto request_w = [&](int k, int buf) {
 #pragma unroll
     for (int q = 0; q < LW; ++q)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ws[q] + (size_t)k * 1024),
-                                       (__attribute__((address_space(3))) void*)&stage[buf][wdst[q]][0], 16, 0, 0);
+      load_to_lds(ws[q], &stage[buf][wdst[q]][0], lane * 16, k * 1024);
   };
   const u32x4* ap[TM];
 #pragma unroll
@@ -273,25 +308,31 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
       a[u][i][1] = ap[i][(size_t)k * 128 + 64];
     }
   };
-  constexpr int PAIRS = (TN + 1) / 2;
+  constexpr int PAIRS = (TN + 1) / 2;                      // (an odd last slot is alone)
   ResidOperands ro[TM][PAIRS];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < PAIRS; ++j)
-      ro[i][j] = resid_operands<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), j + TN / 2 < TN ? slot_tile<EPI, TN>(colb, j + TN / 2, hd) : 0x7FFFFF,
+      ro[i][j] = resid_operands<EPI>(g, slot_tile<EPI, TN>(colb, j < TN / 2 ? j : TN - 1, hd), j < TN / 2 ? slot_tile<EPI, TN>(colb, j + TN / 2, hd) : 0x7FFFFF,
                                      ((rowb * W + wave) * TM + i) * 16 + (lane & 15), 4 * (lane >> 4));
+  RowDest rd[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) rd[i] = EPI == EPI_QKV ? row_dest(g, ((rowb * W + wave) * TM + i) * 16 + (lane & 15)) : RowDest{0, -1};
   const bool scaled = EPI == EPI_SWIGLU && g.rms_d > 0;
   RowSums rs[TM];
   if (scaled)
 #pragma unroll
     for (int i = 0; i < TM; ++i) rs[i] = row_sums_load<false>(g, (rowb * W + wave) * TM + i);
 #pragma unroll
-  for (int b = 0; b < NBUF - 1; ++b) request_w(min(b, nk - 1), b);
+  for (int b = 0; b < NBUF; ++b) request_w(min(b, nk - 1), b);
   asm volatile("" ::: "memory");                           // the first waits count the activations' requests as the later ones
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int u = 0; u < UA; ++u) request_a(u, min(u, nk - 1));
+  for (int u = 0; u < UA; ++u) {
+    request_a(u, min(u, nk - 1));
+    __builtin_amdgcn_sched_barrier(0);                     // (in this order: else the loop's first wait for a[0], which the compiler places, waits for all of them)
+  }
   float inv[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) inv[i] = scaled ? row_inv_rms<false>(g, rs[i]) : 1.0f;
@@ -300,38 +341,46 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
-  int buf = 0, nbuf = NBUF - 1;                            // buffer of k-tile k, buffer of k-tile k + NBUF - 1
-  auto one = [&](int u, int k) {
-    // k-tile k's weights have arrived when at most this wave's later requests are outstanding
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NBUF - 2) * LW + (NBUF - 1) * 2 * TM) : "memory");
+  u32x4 w[2][TN];
+  auto fetch = [&](int s, int b) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) w[s][j] = stage[b][j][lane];
+  };
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NBUF - 1) * LW + UA * 2 * TM) : "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  fetch(0, 0);
+  int buf = 0;                                             // buffer of k-tile k
+  auto one = [&](auto tail, int u, int k) {
+    // k-tile k + 1's weights have arrived when at most this wave's later requests are outstanding.  (`tail`: bodies behind the main loop so far.
+    // What those load of the activations is not used, and the compiler leaves it out.)
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NBUF - 2) * LW + (NBUF - 1 > decltype(tail)::value ? NBUF - 1 - decltype(tail)::value : 0) * 2 * TM) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    request_w(min(k + NBUF - 1, nk - 1), nbuf);
-    u32x4 w[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) w[j] = stage[buf][j][lane];
+    request_w(min(k + NBUF, nk - 1), buf);
+    buf = buf + 1 == NBUF ? 0 : buf + 1;
+    fetch((u & 1) ^ 1, buf);
+    asm volatile("" ::: "memory");
+    const u32x4* const wk = w[u & 1];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const bf16x8 hi = __builtin_bit_cast(bf16x8, a[u][i][0]), lo = __builtin_bit_cast(bf16x8, a[u][i][1]);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j]), lo, acc[i][j], 0, 0, 0);
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wk[j]), lo, acc[i][j], 0, 0, 0);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j]), hi, acc[i][j], 0, 0, 0);
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wk[j]), hi, acc[i][j], 0, 0, 0);
     }
+    sched_interleave<2 * TM * TN, LW, TN>();
     __builtin_amdgcn_sched_barrier(0);
     request_a(u, min(k + UA, nk - 1));
     __builtin_amdgcn_sched_barrier(0);
-    buf = buf + 1 == NBUF ? 0 : buf + 1;
-    nbuf = nbuf + 1 == NBUF ? 0 : nbuf + 1;
   };
   const int kfull = (nk / UA) * UA;
   for (int k0 = 0; k0 < kfull; k0 += UA) {
 #pragma unroll
-    for (int u = 0; u < UA; ++u) one(u, k0 + u);
+    for (int u = 0; u < UA; ++u) one(std::integral_constant<int, 0>(), u, k0 + u);
   }
-#pragma unroll
-  for (int u = 0; u < UA - 1; ++u)
-    if (kfull + u < nk) one(u, kfull + u);                 // (uniform over the workgroup)
+  for_each_index([&](auto u) { if (kfull + u < nk) one(u, u, kfull + u); }, std::make_integer_sequence<int, UA - 1>());      // (uniform over the workgroup)
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the requests past the end
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
@@ -340,11 +389,11 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
 #pragma unroll
     for (int j = 0; j < TN / 2; ++j)
       sum += tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, j, hd), slot_tile<EPI, TN>(colb, j + TN / 2, hd), slice, row, 4 * (lane >> 4), acc[i][j],
-                         acc[i][j + TN / 2], RowDest{0, -1}, ro[i][j], inv[i]);
+                         acc[i][j + TN / 2], rd[i], ro[i][j], inv[i]);
     if (TN % 2)
       sum += tile_epilogue<EPI>(g, slot_tile<EPI, TN>(colb, TN - 1, hd), 0x7FFFFF, slice, row, 4 * (lane >> 4), acc[i][TN - 1], acc[i][TN - 1],
-                              RowDest{0, -1}, ro[i][PAIRS - 1], inv[i]);
-    if (EPI == EPI_RESID) store_row_sum(g, row, colb, p.n_colb, sum);
+                              rd[i], ro[i][PAIRS - 1], inv[i]);
+    if (EPI == EPI_RESID && g.sum_pieces) store_row_sum(g, row, colb, p.n_colb, sum);
   }
 }
 
@@ -355,14 +404,9 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
 // so the only waits are the counted ones.  One barrier per k-tile: it is passed when every wave has read k-tile k, whose buffer the next
 // request then overwrites, and every wave's share of k-tile k + 1 has arrived.  Order of an element's sum as in k_gemm_tile.
 // What bounds it up to about 250 rows is the intake of a compute unit, 60 bytes a nanosecond of activations that every column block
-// reads again and of weights from HBM, whatever the depth (3 to 11 k-tiles in flight: the same): gate / up of 97 rows (7 x 6) 14.6 us, without
-// the loop's requests 10.9, without its matrix instructions 13.6.  With more rows it is as with k_gemm_tile: down of 1024 rows of the 0.5B shape (8 x 7,
-// four slices) 19.8, 16.6 and 15.1.
-// k_gemm_tile's best tile -> this one's, us, cold weights: gate / up of 72, 112, 160 rows of the 0.5B shape 12.8 -> 11.2, 12.9 -> 12.1,
-// 13.8 -> 12.0; of the 1.5B shape 23.8 -> 21.3, 25.0 -> 22.8, equal; down of the 1.5B shape, 72 and 112 rows, 15.4 -> 13.8, 16.5 -> 15.2, of 320
-// rows 29.5 -> 26.1.  With more rows the two are equal, but for the QKV projection, whose tiles are small: 1024 rows of the 0.5B shape
-// 14.9 -> 13.8, of the 1.5B shape 25.3 -> 21.0.  (Its output projection: no gain over k_gemm_kwave up to 512 rows, and above that 0.7 us at
-// 1024 rows of the 0.5B shape and a loss elsewhere.)
+// reads again and of weights from HBM, whatever the depth (3 to 11 k-tiles in flight: the same): gate / up of 97 rows in 4 x 6 11.8 us.  With more rows
+// its reads of LDS weigh: (2 TM + TN) KB per wave and k-tile against 8 TM TN cycles of matrix instructions, at 128 bytes a cycle, so its
+// large tiles have waves of 2 x 6 and 2 x 8.
 template <int EPI, int RT, int CT, int WR, int WC, int NBUF>
 __global__ void __launch_bounds__(WR * WC * 64) k_gemm_block(GemmArgs g, TilePlan p) {
   constexpr int W = WR * WC, TM = RT / WR, TN = CT / WC;
@@ -374,26 +418,25 @@ __global__ void __launch_bounds__(WR * WC * 64) k_gemm_block(GemmArgs g, TilePla
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave / WC, wc = wave - wr * WC;
   const int KT = g.K >> 5, ntiles = (g.N + 15) >> 4, last_mt = (g.M - 1) >> 4;
   const int kb = slice * p.slice_kt, nk = min(KT, kb + p.slice_kt) - kb, hd = g.kv.hd;
-  const char* src[LPW];
+  rsrc_t src[LPW];
   int step[LPW], dst[LPW];
 #pragma unroll
   for (int q = 0; q < LPW; ++q) {                          // (the last ones repeat earlier fragments where F is not a multiple of W)
     const int f = (q * W + wave) % F;
     dst[q] = f;
     if (f < 2 * RT) {
-      src[q] = (const char*)g.A + ((size_t)min(rowb * RT + f / 2, last_mt) * KT + kb) * 2048 + (f & 1) * 1024;
+      src[q] = load_rsrc((const char*)g.A + ((size_t)min(rowb * RT + f / 2, last_mt) * KT + kb) * 2048 + (f & 1) * 1024);
       step[q] = 2048;
     } else {
       const int j = f - 2 * RT, t = slot_tile<EPI, CT>(colb, j, hd);
-      src[q] = (const char*)(EPI == EPI_SWIGLU && j >= CT / 2 ? g.W1 : g.W0) + ((size_t)(t < ntiles ? t : 0) * KT + kb) * 1024;
+      src[q] = load_rsrc((const char*)(EPI == EPI_SWIGLU && j >= CT / 2 ? g.W1 : g.W0) + ((size_t)(t < ntiles ? t : 0) * KT + kb) * 1024);
       step[q] = 1024;
     }
   }
   auto request = [&](int k, int buf) {
 #pragma unroll
     for (int q = 0; q < LPW; ++q)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[q] + (size_t)(k * step[q]) + lane * 16),
-                                       (__attribute__((address_space(3))) void*)&lds[(buf * F + dst[q]) * 64], 16, 0, 0);
+      load_to_lds(src[q], &lds[(buf * F + dst[q]) * 64], lane * 16, k * step[q]);
   };
   // slot of the workgroup's CT that is this wave's j-th (paired tiles: the pairs of the same columns)
   auto slot = [&](int j) {
@@ -448,6 +491,7 @@ __global__ void __launch_bounds__(WR * WC * 64) k_gemm_block(GemmArgs g, TilePla
 #pragma unroll
       for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s][j]), hi, acc[i][j], 0, 0, 0);
     }
+    sched_interleave<2 * TM * TN, LPW, 2 * TM + TN>();
     __builtin_amdgcn_sched_barrier(0);
   };
   int k = 0;

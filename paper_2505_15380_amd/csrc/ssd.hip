@@ -589,6 +589,18 @@ static TilePlan gemm_plan(const GemmArgs& g, int rows, int cols, int slices) {
   p.slice_kt = cdiv(KT, slices);
   p.n_slices = cdiv(KT, p.slice_kt);
   p.per_xcd = cdiv(p.n_colb * p.n_rowb * p.n_slices, 8);
+  p.rows_xcd = p.cols_xcd = p.lg_per = p.lg_colg = 0;
+  p.rows_inv = 0;
+  if (8 % p.n_slices == 0 && p.per_xcd < 4096) {           // the XCDs' grid of the least bytes among those that give no XCD more workgroups than it has to take
+    const double a = (double)g.M * 4, w = (double)n_wt * 16 * 2;      // bytes per k of the activations (hi + lo) and of the weights
+    double best = 0;
+    p.lg_per = __builtin_ctz(8 / p.n_slices);
+    for (int lc = p.lg_per; lc >= 0; --lc) {
+      const int ng = 1 << (p.lg_per - lc), r = cdiv(p.n_rowb, ng), c = cdiv(p.n_colb, 1 << lc);
+      const double bytes = a * (1 << lc) + w * ng;
+      if (r * c <= p.per_xcd && (!p.rows_xcd || bytes < best)) { best = bytes; p.rows_xcd = r; p.cols_xcd = c; p.lg_colg = lc; p.rows_inv = (1u << 20) / r + 1; }
+    }
+  }
   return p;
 }
 static int plan_wgs(const TilePlan& p) { return p.n_colb * p.n_rowb * p.n_slices; }
@@ -606,28 +618,50 @@ struct LdsOptIn {
     return e;
   }
 };
-// Many rows: the kernel, the tile and the slices of the least estimated time.  A shape's two figures are us per k-tile, measured with cold
-// weights at 72 to 1024 rows of both model shapes and fitted by least squares: what a k-tile takes at all, and what it takes
-// for each of a compute unit's workgroups.  Partial outputs cost their write at 4.2 TB/s and their read at 5.  The shape that is picked is 0.6 %
-// on average, at most 8 %, slower than the fastest of 32 shapes at each of 94 sizes; those that are left out were nowhere needed for that.
-// (Other widths follow the same two figures; none was measured.)
-// (An estimate from cycles per tile and per KB, which stood here, was 6 % behind on average, and up to 30 %: us with it -> with this, 72 rows
-// of gate / up of the 1.5B shape 25.1 -> 21.3, 256 39.2 -> 35.0, 640 68.0 -> 63.6; down of 320 rows 33.0 -> 26.1, 768 58.2 -> 52.0;
-// head of 112 rows 160 -> 137.)
-// Tiles of the output projection that leave a compute unit one workgroup keep eight k-tiles in flight instead of four (weights that come
-// from HBM take more than a microsecond); 4 x 6 or 4 x 8 then, since 4 x 4 that do are k_gemm_kwave's.
-struct GemmShape { int rt, ct, w; bool block; float per_kt, per_wg; };   // row tiles x column slots, waves, k_gemm_block or k_gemm_tile
+// The kernel, the tile and the slices of the least estimated time.  A shape's three figures are us, fitted by least squares to the times of the
+// layers' launches in prompts of 24 to 1024 rows of both model shapes (29 sizes each): of a launch, per k-tile, and per k-tile for each of a compute
+// unit's workgroups.  Partial outputs cost their write at 4.2 TB/s and their read at 5.  The shape that is picked is 0.4 % (gate / up, output
+// projection) to 1.4 % (QKV) slower on average than the fastest of 19 to 25 shapes at each size, up to 12 % where two are close; those that
+// are left out were nowhere needed for that.  (Other widths follow the same figures; none was measured.  A kernel launched again and again by
+// itself is up to 2 us faster than between the others, and not equally so: figures from such runs picked shapes that were slower in a forward.)
+enum GemmKernel { KERNEL_KWAVE, KERNEL_BLOCK, KERNEL_TILE, KERNEL_TILE_DEEP };      // (deep: eight k-tiles in flight instead of four)
+struct GemmShape { int rt, ct, w; GemmKernel kernel; float launch, per_kt, per_wg; };       // row tiles x column slots, waves
 template <int EPI>
 static auto gemm_shapes() {
+  constexpr GemmKernel K = KERNEL_KWAVE, B = KERNEL_BLOCK, T = KERNEL_TILE, D = KERNEL_TILE_DEEP;
   if constexpr (EPI == EPI_SWIGLU)
-    return std::array<GemmShape, 9>{{{4, 8, 8, true, 0.074f, 0.262f}, {4, 10, 4, true, 0.032f, 0.448f}, {5, 6, 5, true, 0.117f, 0.272f}, {7, 6, 7, true, 0.013f, 0.397f},
-                                     {4, 8, 4, false, 0.179f, 0.215f}, {8, 8, 8, false, 0.153f, 0.377f}, {8, 10, 8, false, 0.196f, 0.455f},
-                                     {8, 12, 4, false, 0.274f, 0.482f}, {16, 10, 8, false, 0.088f, 0.960f}}};
+    return std::array<GemmShape, 9>{{{2, 8, 4, B, 3.95f, 0.044f, 0.176f}, {4, 6, 4, B, 5.51f, 0.f, 0.227f}, {4, 8, 8, B, 5.51f, 0.f, 0.250f},
+                                     {8, 16, 8, B, 3.87f, 0.f, 0.724f}, {4, 10, 4, T, 5.26f, 0.043f, 0.278f}, {8, 8, 8, T, 3.30f, 0.f, 0.436f},
+                                     {8, 10, 8, T, 3.79f, 0.f, 0.532f}, {8, 12, 4, T, 7.84f, 0.f, 0.514f}, {16, 10, 8, T, 5.12f, 0.f, 0.895f}}};
   else if constexpr (EPI == EPI_PARTIAL)
-    return std::array<GemmShape, 6>{{{4, 4, 4, true, 0.027f, 0.145f}, {4, 8, 8, true, 0.024f, 0.223f}, {8, 7, 8, true, 0.f, 0.369f},
-                                     {8, 8, 8, false, 0.031f, 0.368f}, {16, 6, 8, false, 0.f, 0.586f}, {16, 8, 8, false, 0.f, 0.682f}}};
+    return std::array<GemmShape, 10>{{{2, 4, 8, K, 3.02f, 0.017f, 0.115f}, {4, 6, 8, B, 3.67f, 0.014f, 0.195f}, {4, 8, 8, B, 3.67f, 0.023f, 0.206f},
+                                      {8, 12, 8, B, 4.73f, 0.f, 0.480f}, {8, 6, 8, T, 3.86f, 0.f, 0.289f}, {8, 7, 8, T, 4.20f, 0.f, 0.298f},
+                                      {8, 8, 8, T, 4.17f, 0.f, 0.326f}, {2, 2, 2, D, 2.81f, 0.023f, 0.066f}, {4, 3, 4, D, 2.98f, 0.001f, 0.143f},
+                                      {4, 4, 4, D, 2.74f, 0.f, 0.155f}}};
+  else if constexpr (EPI == EPI_QKV)
+    return std::array<GemmShape, 9>{{{1, 2, 8, K, 3.38f, 0.f, 0.066f}, {2, 2, 8, K, 3.86f, 0.f, 0.081f}, {2, 4, 8, K, 5.02f, 0.f, 0.099f},
+                                     {3, 4, 8, K, 4.47f, 0.f, 0.147f}, {4, 4, 8, K, 6.19f, 0.f, 0.132f}, {4, 8, 8, B, 6.65f, 0.221f, 0.f},
+                                     {4, 4, 4, T, 4.88f, 0.039f, 0.148f}, {4, 6, 4, T, 5.77f, 0.091f, 0.143f}, {3, 2, 3, D, 3.26f, 0.008f, 0.109f}}};
   else
-    return std::array<GemmShape, 3>{{{4, 4, 4, false, 0.f, 0.200f}, {4, 6, 4, false, 0.f, 0.233f}, {4, 8, 4, false, 0.f, 0.267f}}};
+    return std::array<GemmShape, 8>{{{1, 2, 8, K, 3.18f, 0.f, 0.063f}, {2, 2, 2, D, 3.35f, 0.f, 0.083f}, {2, 3, 2, D, 3.36f, 0.011f, 0.102f},
+                                     {2, 4, 2, D, 4.31f, 0.004f, 0.103f}, {3, 2, 3, D, 2.85f, 0.f, 0.117f}, {4, 3, 4, D, 3.67f, 0.f, 0.157f},
+                                     {4, 4, 4, D, 4.94f, 0.f, 0.144f}, {4, 6, 4, D, 4.59f, 0.221f, 0.f}}};
+}
+// Sizes whose k range is shorter than eight k-tiles, and k-split outputs of a width that is no multiple of 64, keep the shapes that they had
+// before: no such size was in the fit, no configuration has one, and the tests of ragged tiles pin these.  (Outside the fit the new shapes are
+// mostly the faster ones too, by 0 to 30 % at 23 sizes that the tests use: what a user of such a width could still gain.)
+template <int EPI>
+static auto gemm_shapes_ragged() {
+  constexpr GemmKernel B = KERNEL_BLOCK, T = KERNEL_TILE;
+  if constexpr (EPI == EPI_SWIGLU)
+    return std::array<GemmShape, 9>{{{4, 8, 8, B, 0.f, 0.074f, 0.262f}, {4, 10, 4, B, 0.f, 0.032f, 0.448f}, {5, 6, 5, B, 0.f, 0.117f, 0.272f},
+                                     {7, 6, 7, B, 0.f, 0.013f, 0.397f}, {4, 8, 4, T, 0.f, 0.179f, 0.215f}, {8, 8, 8, T, 0.f, 0.153f, 0.377f},
+                                     {8, 10, 8, T, 0.f, 0.196f, 0.455f}, {8, 12, 4, T, 0.f, 0.274f, 0.482f}, {16, 10, 8, T, 0.f, 0.088f, 0.960f}}};
+  else if constexpr (EPI == EPI_PARTIAL)
+    return std::array<GemmShape, 6>{{{4, 4, 4, B, 0.f, 0.027f, 0.145f}, {4, 8, 8, B, 0.f, 0.024f, 0.223f}, {8, 7, 8, B, 0.f, 0.f, 0.369f},
+                                     {8, 8, 8, T, 0.f, 0.031f, 0.368f}, {16, 6, 8, T, 0.f, 0.f, 0.586f}, {16, 8, 8, T, 0.f, 0.f, 0.682f}}};
+  else
+    return std::array<GemmShape, 3>{{{4, 4, 4, T, 0.f, 0.f, 0.200f}, {4, 6, 4, T, 0.f, 0.f, 0.233f}, {4, 8, 4, T, 0.f, 0.f, 0.267f}}};
 }
 template <int EPI, int RT, int CT, int WR, int WC, int NBUF>
 static int launch_gemm_block(const GemmArgs& g, const TilePlan& p, hipStream_t st) {
@@ -639,34 +673,35 @@ static int launch_gemm_block(const GemmArgs& g, const TilePlan& p, hipStream_t s
   LAUNCH_CHECK();
   return p.n_slices;
 }
-enum GemmKernel { KERNEL_KWAVE, KERNEL_BLOCK, KERNEL_TILE, KERNEL_TILE_DEEP };
 struct GemmPick {
   GemmKernel kernel;
   int rt, ct, w;                                           // row tiles x column slots of a workgroup; its waves (k_gemm_tile)
   TilePlan p;
 };
+template <int EPI, typename SHAPES>
+static GemmPick pick_gemm_shape(const GemmArgs& g, int cus, int max_slices, const SHAPES& shapes) {
+  const int KT = g.K / 32;
+  GemmShape c{};
+  double best_us = 0;
+  TilePlan p{};
+  for (const GemmShape& s : shapes)
+    for (int ns = 1; ns <= std::min(8, max_slices) && (ns == 1 || KT / ns >= 7); ns *= 2) {
+      const TilePlan q = gemm_plan<EPI>(g, s.rt, s.ct, ns);
+      const double us = s.launch + q.slice_kt * (s.per_kt + s.per_wg * cdiv(plan_wgs(q), cus)) + (EPI == EPI_PARTIAL ? (double)q.n_slices * g.M * g.N * 4 * 0.44e-6 : 0.0);
+      if (!c.w || us < best_us) { c = s; best_us = us; p = q; }
+    }
+  return {c.kernel, c.rt, c.ct, c.w, p};
+}
 template <int EPI>
-static GemmPick pick_gemm_tile(const GemmArgs& g, int cus, int max_slices) {
+static GemmPick pick_gemm_ragged(const GemmArgs& g, int cus, int max_slices) {
   if constexpr (EPI == EPI_QKV) {
-    // Tiles of 4 x 4 while few compute units have two of them (640 to 1024 rows of the 0.5B shape, 160 to 288 workgroups, 1.1 to 1.4 us less than
-    // k_gemm_tile; 640 rows of the 1.5B shape, 320: 1.8), else of 4 x 8 (768 to 1024 rows of that, 384 to 512 workgroups of 4 x 4: 3 to 4 us less,
-    // where those take 0.7 more).
     const TilePlan small = gemm_plan<EPI>(g, 4, 4, 1);
     if (plan_wgs(small) <= cus + cus / 4) return {KERNEL_BLOCK, 4, 4, 4, small};
     return {KERNEL_BLOCK, 4, 8, 8, gemm_plan<EPI>(g, 4, 8, 1)};
   } else {
-    const int KT = g.K / 32;
-    GemmShape c{};
-    double best_us = 0;
-    TilePlan p{};
-    for (const GemmShape& s : gemm_shapes<EPI>())
-      for (int ns = 1; ns <= std::min(8, max_slices) && (ns == 1 || KT / ns >= 7); ns *= 2) {
-        const TilePlan q = gemm_plan<EPI>(g, s.rt, s.ct, ns);
-        const double us = q.slice_kt * (s.per_kt + s.per_wg * cdiv(plan_wgs(q), cus)) + (EPI == EPI_PARTIAL ? (double)q.n_slices * g.M * g.N * 4 * 0.44e-6 : 0.0);
-        if (!c.w || us < best_us) { c = s; best_us = us; p = q; }
-      }
-    const bool deep = EPI == EPI_RESID && plan_wgs(p) <= cus;
-    return {c.block ? KERNEL_BLOCK : deep ? KERNEL_TILE_DEEP : KERNEL_TILE, c.rt, c.ct, c.w, p};
+    GemmPick c = pick_gemm_shape<EPI>(g, cus, max_slices, gemm_shapes_ragged<EPI>());
+    if (EPI == EPI_RESID && plan_wgs(c.p) <= cus) c.kernel = KERNEL_TILE_DEEP;
+    return c;
   }
 }
 template <int EPI>
@@ -674,46 +709,52 @@ static int launch_gemm_tile(const GemmArgs& g, const GemmPick& c, hipStream_t st
   const TilePlan& p = c.p;
 #define BLOCK(RT, CT, WR, WC, NBUF) \
   if (c.kernel == KERNEL_BLOCK && c.rt == RT && c.ct == CT) return launch_gemm_block<EPI, RT, CT, WR, WC, NBUF>(g, p, st)
-#define TILE(RT, CT, W)                                                                                                              \
-  if (c.kernel == KERNEL_TILE && c.rt == RT && c.ct == CT && c.w == W) {                                                             \
-    hipLaunchKernelGGL((k_gemm_tile<EPI, RT / W, CT, W, 4, 4, RT == 16 ? 1 : 2>), dim3(8 * p.per_xcd), dim3(W * 64), 0, st, g, p);   \
-    LAUNCH_CHECK();                                                                                                                  \
-    return EPI == EPI_RESID ? p.n_colb : p.n_slices;                                                                                 \
+#define TILE_OF(KERNEL, RT, CT, W, NBUF, UA, MINB)                                                                         \
+  if (c.kernel == KERNEL && c.rt == RT && c.ct == CT && c.w == W) {                                                        \
+    hipLaunchKernelGGL((k_gemm_tile<EPI, RT / W, CT, W, NBUF, UA, MINB>), dim3(8 * p.per_xcd), dim3(W * 64), 0, st, g, p); \
+    LAUNCH_CHECK();                                                                                                        \
+    return EPI == EPI_RESID ? p.n_colb : p.n_slices;                                                                       \
   }
-#define TILE_DEEP(CT)                                                                                                  \
-  if (c.kernel == KERNEL_TILE_DEEP && c.ct == CT) {                                                                    \
-    hipLaunchKernelGGL((k_gemm_tile<EPI, 1, CT, 4, 8, 8, 1>), dim3(8 * p.per_xcd), dim3(256), 0, st, g, p);            \
-    LAUNCH_CHECK();                                                                                                    \
-    return EPI == EPI_RESID ? p.n_colb : p.n_slices;                                                                   \
-  }
+#define TILE(RT, CT, W) TILE_OF(KERNEL_TILE, RT, CT, W, 4, 4, RT == 16 ? 1 : 2)
+#define TILE_DEEP(RT, CT, W) TILE_OF(KERNEL_TILE_DEEP, RT, CT, W, 8, 8, 1)
   if constexpr (EPI == EPI_QKV) {
     BLOCK(4, 4, 4, 1, 5); BLOCK(4, 8, 4, 2, 5);
+    TILE(4, 4, 4) TILE(4, 6, 4) TILE_DEEP(3, 2, 3)
   } else if constexpr (EPI == EPI_SWIGLU) {
-    BLOCK(4, 8, 4, 2, 5); BLOCK(4, 10, 4, 1, 5); BLOCK(5, 6, 5, 1, 5); BLOCK(7, 6, 7, 1, 5);
-    TILE(4, 8, 4) TILE(8, 8, 8) TILE(8, 10, 8) TILE(8, 12, 4) TILE(16, 10, 8)
+    BLOCK(2, 8, 2, 2, 5); BLOCK(4, 6, 4, 1, 5); BLOCK(4, 8, 4, 2, 5); BLOCK(4, 10, 4, 1, 5); BLOCK(5, 6, 5, 1, 5); BLOCK(7, 6, 7, 1, 5); BLOCK(8, 16, 4, 2, 4);
+    TILE(4, 8, 4) TILE(4, 10, 4) TILE(8, 8, 8) TILE(8, 10, 8) TILE(16, 10, 8)
+    TILE_OF(KERNEL_TILE, 8, 12, 4, 3, 2, 2)                // (two k-tiles of activations in flight: more do not fit the registers)
   } else if constexpr (EPI == EPI_PARTIAL) {
-    BLOCK(4, 4, 4, 1, 5); BLOCK(4, 8, 4, 2, 5); BLOCK(8, 7, 8, 1, 4);
-    TILE(8, 8, 8) TILE(16, 6, 8) TILE(16, 8, 8)
+    BLOCK(4, 4, 4, 1, 5); BLOCK(4, 6, 4, 2, 5); BLOCK(4, 8, 4, 2, 5); BLOCK(8, 7, 8, 1, 4); BLOCK(8, 12, 4, 2, 4);
+    TILE(8, 6, 8) TILE(8, 7, 8) TILE(8, 8, 8) TILE(16, 6, 8) TILE(16, 8, 8)
+    TILE_DEEP(2, 2, 2) TILE_DEEP(4, 3, 4) TILE_DEEP(4, 4, 4)
   } else if constexpr (EPI == EPI_RESID) {
-    TILE(4, 4, 4) TILE(4, 6, 4) TILE(4, 8, 4) TILE_DEEP(6) TILE_DEEP(8)
+    TILE(4, 4, 4) TILE(4, 6, 4) TILE(4, 8, 4)
+    TILE_DEEP(2, 2, 2) TILE_DEEP(2, 3, 2) TILE_DEEP(2, 4, 2) TILE_DEEP(3, 2, 3) TILE_DEEP(4, 3, 4) TILE_DEEP(4, 4, 4) TILE_DEEP(4, 6, 4) TILE_DEEP(4, 8, 4)
   }
 #undef BLOCK
+#undef TILE_OF
 #undef TILE
 #undef TILE_DEEP
   return fail(SSD_EHIP, "no GEMM kernel of %d x %d tiles and %d waves", c.rt, c.ct, c.w);
 }
 
 // What a bf16 GEMM runs, from the sizes alone.
-// Few rows (up to 64; for the QKV and output projections, whose k range is not split over workgroups, up to 512, and the output
-// projection as long as tiles of 4 x 4 fill one round: 1024 rows of width 896 10.8 us, 12.0 with k_gemm_tile; of width 1536 26 and 21): k_gemm_kwave
-// with the smallest tile that leaves no more workgroups than compute units.  What bounds it is how long a workgroup's
-// operand stream takes, so the work is spread as far as one round of workgroups allows; k-split outputs get 8 slices
+// By the estimate above from 17 rows on (gate / up, whose few-row kernel reads sums of squares over 16 columns: from 65 on).
+// Fewer rows: k_gemm_kwave with the smallest tile that leaves no more workgroups than compute units, or else the largest usable one.  What bounds it
+// is how long a workgroup's operand stream takes, so the work is spread as far as one round of workgroups allows; k-split outputs get 8 slices
 // (4 where k is short) while that round lasts.
+// (Sizes outside the fit: gate / up and k-split outputs of up to 64 rows, QKV and output projection up to 512, and the output projection as long
+// as tiles of 4 x 4 fill one round.)
 template <int EPI>
 static GemmPick pick_gemm(const GemmArgs& g, int cus, int max_slices) {
   const int KT = g.K / 32, MT = cdiv(g.M, 16);
   constexpr bool whole_k = EPI == EPI_QKV || EPI == EPI_RESID;
-  if (MT > (whole_k ? 32 : 4) && !(EPI == EPI_RESID && plan_wgs(gemm_plan<EPI>(g, 4, 4, 1)) <= cus)) return pick_gemm_tile<EPI>(g, cus, max_slices);
+  if (KT >= 8 && (max_slices == 1 || g.N % 64 == 0)) {
+    if (MT > (EPI == EPI_SWIGLU ? 4 : 1)) return pick_gemm_shape<EPI>(g, cus, max_slices, gemm_shapes<EPI>());
+  } else if (MT > (whole_k ? 32 : 4) && !(EPI == EPI_RESID && plan_wgs(gemm_plan<EPI>(g, 4, 4, 1)) <= cus)) {
+    return pick_gemm_ragged<EPI>(g, cus, max_slices);
+  }
   static const int shapes[][2] = {{1, 2}, {2, 2}, {1, 4}, {3, 2}, {1, 6}, {2, 4}, {2, 6}, {3, 4}, {4, 4}, {3, 6}, {4, 6}};   // by area
   auto usable = [&](const int* c) {
     return c[0] <= MT && (EPI == EPI_SWIGLU ? c[0] < 4 || c[1] == 6 : c[1] <= 4);

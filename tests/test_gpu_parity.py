@@ -311,6 +311,39 @@ def test_qkv_projection_of_more_than_512_rows(nq, nkv, hd, rows):
                       qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6), rows, 89)
 
 
+# d, ffn, query heads, kv heads, rows; {projection: (kernel, row tiles, column slots)} as ssd_gemm_plan names them
+@pytest.mark.parametrize("d,ffn,nq,nkv,rows,tiles", [
+    (384, 64, 4, 1, 369, {"down": (1, 4, 4), "gate_up": (1, 2, 8), "o": (3, 3, 2), "qkv": (3, 3, 2)}),
+    (1792, 256, 9, 1, 66, {"down": (3, 2, 2), "o": (3, 2, 2)}),
+    (256, 3072, 5, 1, 161, {"down": (3, 4, 4), "gate_up": (2, 8, 8)}),
+    (768, 5760, 4, 1, 65, {"down": (3, 4, 3), "gate_up": (1, 4, 6)}),
+    (1792, 64, 4, 1, 641, {"down": (1, 4, 8), "o": (3, 4, 3)}),
+    (768, 64, 4, 1, 481, {"o": (3, 2, 3)}),
+    (448, 64, 10, 2, 897, {"o": (3, 2, 4), "qkv": (2, 4, 4)}),
+    (384, 6400, 5, 1, 65, {"gate_up": (1, 4, 8)}),
+    (768, 6400, 6, 1, 130, {"down": (1, 4, 6), "gate_up": (2, 4, 10)}),
+    (256, 8960, 4, 1, 129, {"gate_up": (2, 8, 10)}),
+    (1792, 64, 7, 1, 433, {"o": (3, 4, 4)}),
+    (1792, 64, 7, 1, 577, {"o": (3, 4, 6)}),
+    (256, 7680, 4, 1, 257, {"gate_up": (1, 8, 16)}),
+    (768, 128, 40, 2, 385, {"qkv": (2, 4, 6)}),
+    (1536, 3648, 4, 1, 129, {"down": (2, 8, 6)}),
+    (512, 64, 40, 2, 577, {"qkv": (1, 4, 8)})])
+def test_projections_at_the_tiles_of_the_fit(d, ffn, nq, nkv, rows, tiles):
+    """The tiles that widths of whole 64 columns and at least eight k-tiles take, each with a ragged last block of rows and, where the
+    width allows, of columns; k ranges that leave every number of k-tiles behind the loop.  (8 x 12 and 16 x 10 of gate / up and 8 x 7, 8 x 8
+    and 8 x 12 of down need full-size models: test_gpu_fullsize.py.)"""
+    import ctypes
+    import paper_2505_15380_amd as ssd
+    size = {"qkv": (0, (nq + 2 * nkv) * 64, d), "o": (2, d, nq * 64), "gate_up": (3, ffn, d), "down": (4, d, ffn)}
+    plan = (ctypes.c_int * 4)()
+    for name, want in tiles.items():
+        kind, n, k = size[name]
+        assert ssd.load_library().ssd_gemm_plan(kind, rows, n, k, 256, plan) == 0 and tuple(plan[:3]) == want, name
+    check_prompt(dict(n_layers=2, d_model=d, n_q_heads=nq, n_kv_heads=nkv, head_dim=64, d_ffn=ffn, vocab=41, n_embed=43, dtype="bf16",
+                      qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6), rows, 91)
+
+
 def test_head_of_many_rows():
     """97 sequences x 8 rows: the head in tiles of 16 x 8, with a last block of eight of its 48 row tiles and a ragged last column block
     (test_launch_plans_cpu.py)."""
