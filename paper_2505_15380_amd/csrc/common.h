@@ -230,6 +230,15 @@ __device__ __forceinline__ uint2 lo_pairs(const f32x4 v) {             // bf16 o
   return make_uint2(f2_to_bf16x2(r[0], r[1]), f2_to_bf16x2(r[2], r[3]));
 }
 
+// Direct loads to LDS, 16 bytes a lane.  Through a buffer descriptor: after global_load_lds, which the compiler counts as a flat access to both
+// memories, every wait that it places for a load or an LDS read is one for all of them, and the loads in flight ahead were waited for
+// once per round of a loop.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t load_rsrc(const void* base) { return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, 0x7FFFFFF0, 0x00027000); }
+__device__ __forceinline__ void load_to_lds(rsrc_t r, void* lds, int lane_off, int off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, lane_off, off, 0, 0);
+}
+
 // f of the constants 0, 1, ..
 template <typename F, int... I>
 __device__ __forceinline__ void for_each_index(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }

@@ -57,7 +57,10 @@ constexpr int DF_QS = 68;                 // words from one row to the next of t
                                           // words apart would put a fragment's 16 rows into the same banks
 constexpr int DF_ATT_V = 16 * DF_QS + 512 + 512 + 8 * 16 * DF_QS + 256;           // Q | new K | new V | merge O | merge m,l |
 constexpr int DF_ATT_WORDS = DF_ATT_V + 8 * 2048;                                 // values of a chunk per wave
-constexpr int DF_LDS_WORDS = DF_AW + DF_SQ_WORDS + DF_RED_WORDS > DF_ATT_WORDS ? DF_AW + DF_SQ_WORDS + DF_RED_WORDS : DF_ATT_WORDS;
+constexpr int DF_DN = 7;                  // down-projection output tiles a wave keeps prefetched
+constexpr int DF_TR = DF_AW + DF_SQ_WORDS + DF_RED_WORDS;                         // the MLP's partials on their way out: per wave [8 rows][DF_DN tiles][16]
+constexpr int DF_LDS_WORDS = DF_TR + 8 * 8 * DF_DN * 16;
+static_assert(DF_ATT_WORDS <= DF_LDS_WORDS && DF_LDS_WORDS <= 39 * 1024, "");
 
 // Which single word a wave watches after a failed first flight (see df_wait_hint): the phases with many consumers (QKV,
 // MLP) watch a word of their OWN operands, the others a word of the preceding phase's operands.
@@ -219,8 +222,10 @@ __device__ __forceinline__ df_rsrc df_make_rsrc(const u64* base) {
 }
 __device__ __forceinline__ u32x4 ld_words2(df_rsrc r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 16 /* sc1 */); }
 
-// Operand words of rows [0, M) (K words each, the rows contiguous) -> As[row * (K + 4) + k], and the rows' sums of
-// squares [M][nsq] -> sqs.  The whole workgroup polls in parallel, a pair of words per load: half the load instructions of
+// Operand words of rows [0, M) (K words each, the rows contiguous) -> As, and the rows' sums of squares [M][nsq] -> sqs.  In As a
+// row has K + 4 words: of every eight consecutive k the hi halves (four words), then the lo halves, as the matrix core takes them.  (With the words
+// as they come a lane read both halves of its operand and picked one: twice the LDS reads, which took 900 cycles of a phase, and eight
+// permutations a k-tile.)  The whole workgroup polls in parallel, a pair of words per load: half the load instructions of
 // a word each (one row 400 -> 380 us a forward; nine rows, with the flights that hold them now, 760 -> 725).  Lanes without a
 // pair are masked out: a load costs the cycles of its return path even where all its lanes are out of range (five rows 513 ->
 // 543 us with such loads instead of the mask).  RES: two more words per thread (x0, x1: offsets in words, or ~0) ride in the
@@ -283,7 +288,9 @@ __device__ __forceinline__ bool stage_operand(const DArgs& a, const u64* A, int 
       const int i = base + u * PBLOCK + tid;
       if (i < pA) {
         const int row = (int)(((float)i + 0.5f) * rkn);
-        *(uint2*)(As + 2 * i + 4 * row) = make_uint2(v[u][0], v[u][2]);
+        uint32_t* w = As + 2 * i + 4 * row - (i & 3);
+        w[0] = __builtin_amdgcn_perm(v[u][2], v[u][0], 0x05040100u);
+        w[4] = __builtin_amdgcn_perm(v[u][2], v[u][0], 0x07060302u);
       } else if (i < total) {
         *(uint2*)(sqs + 2 * (i - pA)) = make_uint2(v[u][0], v[u][2]);
       }
@@ -325,49 +332,49 @@ __device__ __forceinline__ int df_item_of_unit(int unit, int shift, int NU, int 
 // Products of a wave's k-tiles [kb, ke) with two weight tiles (the first PF_K k-tiles' weights are in wl) into acc0, acc1: element
 // (r, lane) = (row 4 g + r, column lane % 16).  The hi and the lo halves of the operands have a sum each, which meet at the
 // end.  Up to 8 rows (PACK) one instruction takes both: rows 0 .. 7 of its operand are the hi halves, 8 .. 15 the lo halves, and
-// the sums meet across the wave's halves; only rows 0 .. 7 of the result mean anything then.  Half the matrix and half the
+// the sums meet across the wave's halves (df_meet: what does not need them comes in between); only rows 0 .. 7 of the result mean anything then.  Half the matrix and half the
 // unpacking instructions: gate / up of one row 1.0 -> 0.7 us of a layer, QKV 1.6 -> 1.2.
 template <bool PACK>
 __device__ __forceinline__ void df_products(const uint32_t* As, int K, int M, int kb, int ke, int lane, const WPre& wl, const u32x4* w0,
                                             const u32x4* w1, f32x4& acc0, f32x4& acc1) {
   // (lanes of rows that are not there take the last one: what they yield is never looked at)
-  const uint32_t* p = As + min(PACK ? lane & 7 : lane & 15, M - 1) * (K + 4) + (lane >> 4) * 8;
-  const uint32_t sel = lane & 8 ? 0x07060302u : 0x05040100u;
+  const uint32_t* p = As + min(PACK ? lane & 7 : lane & 15, M - 1) * (K + 4) + (lane >> 4) * 8 + (PACK ? (lane & 8) >> 1 : 0);
   f32x4 lo0 = f32x4{0, 0, 0, 0}, lo1 = f32x4{0, 0, 0, 0};
   // all operand fragments first (their LDS latencies overlap), then the products
-  u32x4 x[PF_K], y[PF_K];
+  u32x4 x[PF_K], y[PF_K];                                  // hi and lo halves (PACK: the lane's one of them)
 #pragma unroll
   for (int u = 0; u < PF_K; ++u) {
     const int kt = min(kb + u, ke - 1);
     x[u] = *(const u32x4*)(p + kt * 32);
-    y[u] = *(const u32x4*)(p + kt * 32 + 4);
+    if (!PACK) y[u] = *(const u32x4*)(p + kt * 32 + 4);
   }
 #define DF_MULTIPLY(X, Y, B0, B1)                                                                                            \
   {                                                                                                                          \
-    const bf16x8 bv0 = __builtin_bit_cast(bf16x8, B0), bv1 = __builtin_bit_cast(bf16x8, B1);                                 \
-    if (PACK) {                                                                                                              \
-      const u32x4 f = {__builtin_amdgcn_perm(X[1], X[0], sel), __builtin_amdgcn_perm(X[3], X[2], sel),                       \
-                       __builtin_amdgcn_perm(Y[1], Y[0], sel), __builtin_amdgcn_perm(Y[3], Y[2], sel)};                      \
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f), bv0, acc0, 0, 0, 0);                     \
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f), bv1, acc1, 0, 0, 0);                     \
-    } else {                                                                                                                 \
-      u32x4 fh, fl;                                                                                                          \
-      split_words(X, Y, fh, fl);                                                                                             \
-      lo0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fl), bv0, lo0, 0, 0, 0);                      \
-      lo1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fl), bv1, lo1, 0, 0, 0);                      \
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fh), bv0, acc0, 0, 0, 0);                    \
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fh), bv1, acc1, 0, 0, 0);                    \
+    const bf16x8 bv0 = __builtin_bit_cast(bf16x8, B0), bv1 = __builtin_bit_cast(bf16x8, B1), fx = __builtin_bit_cast(bf16x8, X); \
+    if (!PACK) {                                                                                                             \
+      const bf16x8 fl = __builtin_bit_cast(bf16x8, Y);                                                                       \
+      lo0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl, bv0, lo0, 0, 0, 0);                                                  \
+      lo1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl, bv1, lo1, 0, 0, 0);                                                  \
     }                                                                                                                        \
+    acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx, bv0, acc0, 0, 0, 0);                                                  \
+    acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx, bv1, acc1, 0, 0, 0);                                                  \
   }
 #pragma unroll
   for (int u = 0; u < PF_K; ++u)
     if (kb + u < ke) DF_MULTIPLY(x[u], y[u], wl.b0[u], wl.b1[u])
   for (int kt = kb + PF_K; kt < ke; ++kt) {                // waves with more than PF_K k-tiles
-    const u32x4 xk = *(const u32x4*)(p + kt * 32), yk = *(const u32x4*)(p + kt * 32 + 4);
+    const u32x4 xk = *(const u32x4*)(p + kt * 32), yk = PACK ? xk : *(const u32x4*)(p + kt * 32 + 4);
     const u32x4 b0 = __builtin_nontemporal_load(w0 + (size_t)kt * 64), b1 = __builtin_nontemporal_load(w1 + (size_t)kt * 64);
     DF_MULTIPLY(xk, yk, b0, b1)
   }
 #undef DF_MULTIPLY
+  if (!PACK) {
+    acc0 += lo0;
+    acc1 += lo1;
+  }
+}
+template <bool PACK>
+__device__ __forceinline__ void df_meet(f32x4& acc0, f32x4& acc1) {
   if (PACK) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -376,9 +383,6 @@ __device__ __forceinline__ void df_products(const uint32_t* As, int K, int M, in
       acc0[r] = __uint_as_float(a[0]) + __uint_as_float(a[1]);
       acc1[r] = __uint_as_float(b[0]) + __uint_as_float(b[1]);
     }
-  } else {
-    acc0 += lo0;
-    acc1 += lo1;
   }
 }
 // Rows that the products' PACK form takes; the instantiations for few words in flight use it.
@@ -453,31 +457,31 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
     // ---- products
     f32x4 acc0 = f32x4{0, 0, 0, 0}, acc1 = f32x4{0, 0, 0, 0};
     if (valid) df_products<df_pack<SB>()>(As, ph.K, M, kb, ke, lane, wl, w0, w1, acc0, acc1);
+    float inv = 1.0f;                                      // (while the matrix cores work)
+    if (ph.sq) {
+      float sq = 0.f;
+      if (row < M)                                         // sums over 32 columns, as the halves of df_reduce_phase's tree
+        for (int p = col; p < KT; p += 16) {
+          if (df_red_cols<SB>() == 8) {
+            const f32x4 q = *(const f32x4*)(sqs + (row * KT + p) * 4);
+            sq += (q[0] + q[1]) + (q[2] + q[3]);
+          } else {
+            sq += sqs[row * KT + p];
+          }
+        }
+      inv = 1.0f / sqrtf(row16_sum(sq) / (float)ph.K + a.eps);
+    }
+    df_meet<df_pack<SB>()>(acc0, acc1);
     const int obase = (g * 4) * 16 + (lane & 15);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       red[uw][0][obase + r * 16] = acc0[r];
       red[uw][1][obase + r * 16] = acc1[r];
     }
-    float sq = 0.f;
-    if (ph.sq && row < M)                                  // sums over 32 columns, as the halves of df_reduce_phase's tree
-      for (int p = col; p < KT; p += 16) {
-        if (df_red_cols<SB>() == 8) {
-          const f32x4 q = *(const f32x4*)(sqs + (row * KT + p) * 4);
-          sq += (q[0] + q[1]) + (q[2] + q[3]);
-        } else {
-          sq += sqs[row * KT + p];
-        }
-      }
     __syncthreads();
     float v0 = (red[0][0][ut] + red[1][0][ut]) + (red[2][0][ut] + red[3][0][ut]);
     float v1 = (red[0][1][ut] + red[1][1][ut]) + (red[2][1][ut] + red[3][1][ut]);
-    if (ph.sq) {
-      sq = row16_sum(sq);
-      const float inv = 1.0f / sqrtf(sq / (float)ph.K + a.eps);
-      v0 *= inv;
-      v1 *= inv;
-    }
+    if (ph.sq) { v0 *= inv; v1 *= inv; }
     if (EPI == PE_QKV) {
       if (live) {
         const int head = n0 >> 6, dd = n0 & 63;                      // dd < 32
@@ -538,14 +542,9 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
 // SwiGLU output, which is exactly one k-tile of the down projection; the workgroup multiplies it with that k-tile of
 // every output tile (8 waves x DF_DN tiles) and publishes a partial of the whole row.  The SwiGLU output never
 // leaves the workgroup, and one dependency per layer disappears; the price is ffn/32 partials per output.
-constexpr int DF_DN = 7;                  // down-projection output tiles a wave keeps prefetched
 struct WDown { u32x4 b[DF_DN]; };
 
 __device__ __forceinline__ uint32_t df_tag2(const uint32_t tag, int layer) { return tag * 128u + (uint32_t)layer; }
-
-// The piece of a weight fragment that a lane takes where row 4 g + r of the product is to be the tile's column 2 g + r (r < 2) or
-// 8 + 2 g + r - 2.
-__device__ __forceinline__ int down_lane(int lane) { return (lane & 48) + ((lane & 2) << 2) + ((lane & 12) >> 1) + (lane & 1); }
 
 // Fragments (n-tile wave + 8 i, k-tile kt2) of the down projection for i < DF_DN; exactly DF_DN loads.
 __device__ __forceinline__ void df_prefetch_down(const DArgs& a, const void* wdown, int kt2, WDown& wd) {
@@ -556,7 +555,7 @@ __device__ __forceinline__ void df_prefetch_down(const DArgs& a, const void* wdo
 #pragma unroll
   for (int i = 0; i < DF_DN; ++i) {
     const int nt = min(wave + 8 * i, ntiles - 1);          // (a wave may have fewer tiles than DF_DN, below 128 columns none)
-    wd.b[i] = __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + down_lane(lane));
+    wd.b[i] = __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + lane);
   }
 }
 
@@ -610,6 +609,11 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
     if (valid)
       df_products<df_pack<SB>()>(As, ph.K, M, kb, ke, lane, pre, (const u32x4*)ph.W0 + (size_t)item * KT * 64 + lane,
                                  (const u32x4*)ph.W1 + (size_t)item * KT * 64 + lane, acc0, acc1);
+    float sq = 0.f;                                        // (while the matrix cores work)
+    if (row < M)
+      for (int p = col; p < KT; p += 16) sq += sqs[row * KT + p];
+    const float inv = 1.0f / sqrtf(row16_sum(sq) / (float)ph.K + a.eps);
+    df_meet<df_pack<SB>()>(acc0, acc1);
     DF_STAMP2(0);
     const int obase = (g * 4) * 16 + (lane & 15);
 #pragma unroll
@@ -617,15 +621,10 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
       red[uw][0][obase + r * 16] = acc0[r];
       red[uw][1][obase + r * 16] = acc1[r];
     }
-    float sq = 0.f;
-    if (row < M)
-      for (int p = col; p < KT; p += 16) sq += sqs[row * KT + p];
     __syncthreads();
     DF_STAMP2(1);
     float v0 = (red[0][0][ut] + red[1][0][ut]) + (red[2][0][ut] + red[3][0][ut]);
     float v1 = (red[0][1][ut] + red[1][1][ut]) + (red[2][1][ut] + red[3][1][ut]);
-    sq = row16_sum(sq);
-    const float inv = 1.0f / sqrtf(sq / (float)ph.K + a.eps);
     v0 *= inv;
     v1 *= inv;
     const float actv = (live && n0 < ph.N) ? v0 / (1.0f + expf(-v0)) * v1 : 0.f;
@@ -637,8 +636,9 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
       u32x4 xh = u32x4{0u, 0u, 0u, 0u}, xl = xh;
       if (arow < M) frag_from_lds(sact + arow * 36 + g * 8, xh, xl);
       const bf16x8 ah = __builtin_bit_cast(bf16x8, xh), al = __builtin_bit_cast(bf16x8, xl);
-      // Computed transposed: a lane holds four columns of row c16, which two stores publish.  They are columns 2g, 2g + 1, 8 + 2g and
-      // 9 + 2g (see down_lane), so that the four lanes of a row store 64 contiguous bytes at a time.
+      // Computed transposed: a lane holds four consecutive columns of row c16.  They go out by way of LDS, row by row: a wave's seven tiles of a
+      // row with one store, 128 contiguous bytes per tile.  (Straight from the registers, two stores per tile of which most lanes are masked, this
+      // section took 0.8 us with one row, 0.5 so; with nine rows the sums' operands are there 0.8 us earlier.)
       // The weights have arrived long ago; waiting for all of them here tells the compiler so.  It does not count the stores below,
       // and its own wait for the i-th tile's weights would wait for acknowledged stores (0.8 us).
       __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt(0)
@@ -648,29 +648,34 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd.b[i]), al, f32x4{0, 0, 0, 0}, 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < DF_DN; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd.b[i]), ah, acc[i], 0, 0, 0);
-      // tile nt of row c16; tile wave + 8 i is 4 i blocks of 32 columns further
       const int nW = a.ffn >> 5;
-      u64* o = part2 + ((size_t)(c16 * (a.d >> 5) + (wave >> 1)) * nW + kt2) * 32 + (wave & 1) * 16 + 2 * g;
-      if (c16 < M) {
-        auto put = [&](auto i) {
-          constexpr int I = decltype(i)::value;
-          if (wave + 8 * I < ntiles_d) {
-            u64* oi = o + (size_t)(4 * I * 32) * nW;
-            st_words2(oi, __float_as_uint(acc[I][0]), __float_as_uint(acc[I][1]), tag2);
-            st_words2<64>(oi, __float_as_uint(acc[I][2]), __float_as_uint(acc[I][3]), tag2);
+      float* tr = (float*)(lds + DF_TR) + wave * (8 * DF_DN * 16);
+      const size_t row_words = (size_t)(a.d >> 5) * nW * 32;
+      const int nt_out = wave + 8 * (lane >> 3);                     // this lane's tile and columns 2 (lane % 8), + 1 of every row
+      u64* out = part2 + ((size_t)(nt_out >> 1) * nW + kt2) * 32 + (nt_out & 1) * 16 + 2 * (lane & 7);
+      for (int r0 = 0; r0 < M; r0 += 8) {
+        if ((c16 & 8) == r0 && c16 < M)
+#pragma unroll
+          for (int i = 0; i < DF_DN; ++i) *(f32x4*)(tr + ((c16 & 7) * DF_DN + i) * 16 + 4 * g) = acc[i];
+        const float* from = tr + 2 * lane;
+        const int re = min(M, r0 + 8);
+        for (int r = r0; r < re; r += 2, from += 2 * DF_DN * 16, out += 2 * row_words) {
+          const float2 v = *(const float2*)from, v1 = *(const float2*)(from + DF_DN * 16);
+          if (lane < 8 * DF_DN && nt_out < ntiles_d) {
+            st_words2(out, __float_as_uint(v.x), __float_as_uint(v.y), tag2);
+            if (r + 1 < re) st_words2(out + row_words, __float_as_uint(v1.x), __float_as_uint(v1.y), tag2);
           }
-        };
-        for_each_index(put, std::make_integer_sequence<int, DF_DN>());
+        }
       }
       for (int nt = wave + 8 * DF_DN; nt < ntiles_d; nt += 8) {      // wider models: the remaining tiles, not prefetched
-        const bf16x8 bv = __builtin_bit_cast(bf16x8, __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + down_lane(lane)));
+        const bf16x8 bv = __builtin_bit_cast(bf16x8, __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + lane));
         f32x4 x = f32x4{0, 0, 0, 0};
         x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, al, x, 0, 0, 0);
         x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, ah, x, 0, 0, 0);
         if (c16 < M) {
-          u64* on = o + (size_t)((nt - wave) * 16) * nW;
+          u64* on = part2 + (size_t)c16 * row_words + ((size_t)(nt >> 1) * nW + kt2) * 32 + (nt & 1) * 16 + 4 * g;
           st_words2(on, __float_as_uint(x[0]), __float_as_uint(x[1]), tag2);
-          st_words2<64>(on, __float_as_uint(x[2]), __float_as_uint(x[3]), tag2);
+          st_words2<16>(on, __float_as_uint(x[2]), __float_as_uint(x[3]), tag2);
         }
       }
     }
@@ -998,11 +1003,9 @@ __device__ __forceinline__ void df_patch_k(DfK& k, int kbase, int len, int nact,
 // Values of a chunk by way of LDS: its four blocks as they are in the pool, [block][dim][token] (2 KB each, one wave's direct
 // loads; the wave waits for them itself).
 __device__ __forceinline__ void df_v_to_lds(const DArgs& a, int layer, const int (&boff)[4], int lane, uint32_t* v2) {
-  const bf16_t* vp = (const bf16_t*)a.kv.pool + (size_t)(2 * layer + 1) * ((size_t)a.kv.n_blocks * a.kv.nkv * 1024) + lane * 8;
+  const df_rsrc r = df_make_rsrc((const u64*)((const bf16_t*)a.kv.pool + (size_t)(2 * layer + 1) * ((size_t)a.kv.n_blocks * a.kv.nkv * 1024)));
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(vp + boff[i >> 1] + (i & 1) * 512),
-                                     (__attribute__((address_space(3))) void*)(v2 + i * 256), 16, 0, 0);
+  for (int i = 0; i < 8; ++i) load_to_lds(r, v2 + i * 256, (int)(2u * (uint32_t)boff[i >> 1] + (uint32_t)(lane * 16 + (i & 1) * 1024)), 0);      // (32 bits: a plane has fewer than 2^31 elements)
 }
 __device__ __forceinline__ void df_v_from_lds(uint32_t* v2, int kbase, int len, int nact, const bf16_t* Vn, int lane, DfV& v) {
   const int g = lane >> 4, c16 = lane & 15;
@@ -1024,24 +1027,19 @@ __device__ __forceinline__ void df_v_from_lds(uint32_t* v2, int kbase, int len, 
 
 __device__ __forceinline__ float df_exp2(float x) { return __builtin_amdgcn_exp2f(x); }     // x <= 0 here, or -inf
 
-// The lane's query row: running maximum (base-2 domain), sum (the same in all lane groups) and weighted values, dims
-// 16 dt + 4 g + r.
+// The lane's query row: maximum (base-2 domain), sum (the same in all lane groups) and weighted values, dims 16 dt + 4 g + r.
 struct DfRow { float m, l; f32x4 o[4]; };
 
-// One chunk, in two halves: the weights (s) and the weighted values.  qpos: position of the lane's query row (-1: none).
-__device__ __forceinline__ void df_weights(const DfK& k, const u32x4 (&qh)[2], const u32x4 (&ql)[2], int kbase, int qpos, bool masked, float sc2,
-                                           int lane, DfRow& r, f32x4 (&s)[4]) {
+// Scores of one chunk's keys.  qpos: position of the lane's query row (-1: none).
+__device__ __forceinline__ void df_scores(const DfK& k, const u32x4 (&qh)[2], const u32x4 (&ql)[2], int kbase, int qpos, bool masked, int lane, f32x4 (&s)[4]) {
   const int g = lane >> 4;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const bf16x8 k0 = __builtin_bit_cast(bf16x8, k.f[t][0]), k1 = __builtin_bit_cast(bf16x8, k.f[t][1]);
-    f32x4 z = f32x4{0, 0, 0, 0};
-    z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0, __builtin_bit_cast(bf16x8, ql[0]), z, 0, 0, 0);
-    z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1, __builtin_bit_cast(bf16x8, ql[1]), z, 0, 0, 0);
-    z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0, __builtin_bit_cast(bf16x8, qh[0]), z, 0, 0, 0);
-    z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1, __builtin_bit_cast(bf16x8, qh[1]), z, 0, 0, 0);
-    s[t] = z;
-  }
+  for (int t = 0; t < 4; ++t) s[t] = f32x4{0, 0, 0, 0};
+  auto product = [&](int ks, const u32x4 q) {              // (four chains side by side)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k.f[t][ks]), __builtin_bit_cast(bf16x8, q), s[t], 0, 0, 0);
+  };
+  product(0, ql[0]); product(1, ql[1]); product(0, qh[0]); product(1, qh[1]);
   if (masked) {                                            // (wave-uniform: only chunks that reach the new positions)
     const int last = qpos - kbase - 4 * g;
 #pragma unroll
@@ -1049,14 +1047,17 @@ __device__ __forceinline__ void df_weights(const DfK& k, const u32x4 (&qh)[2], c
 #pragma unroll
       for (int e = 0; e < 4; ++e) s[t][e] = 16 * t + e <= last ? s[t][e] : -INFINITY;
   }
+}
+__device__ __forceinline__ float df_max16(const f32x4 (&s)[4]) {
   f32x4 m4 = s[0];
 #pragma unroll
   for (int t = 1; t < 4; ++t)
 #pragma unroll
     for (int e = 0; e < 4; ++e) m4[e] = fmaxf(m4[e], s[t][e]);
-  const float mnew = fmaxf(r.m, max_over_groups(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]))) * sc2);
-  const float base = mnew == -INFINITY ? 0.f : mnew;      // (the row has seen no key yet: every weight is 0)
-  const float alpha = df_exp2(r.m - base);
+  return fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
+}
+// Scores -> weights against the maximum; their sum over the lane's keys.
+__device__ __forceinline__ float df_weights(f32x4 (&s)[4], float sc2, float base) {
   f32x4 sum4 = f32x4{0, 0, 0, 0};
 #pragma unroll
   for (int t = 0; t < 4; ++t)
@@ -1065,11 +1066,7 @@ __device__ __forceinline__ void df_weights(const DfK& k, const u32x4 (&qh)[2], c
       s[t][e] = df_exp2(fmaf(s[t][e], sc2, -base));
       sum4[e] += s[t][e];
     }
-  const float sum = (sum4[0] + sum4[1]) + (sum4[2] + sum4[3]);
-  r.m = mnew;
-  r.l = fmaf(r.l, alpha, sum_over_groups(sum));
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt) r.o[dt] *= alpha;
+  return (sum4[0] + sum4[1]) + (sum4[2] + sum4[3]);
 }
 __device__ __forceinline__ void df_values(const DfV& v, const f32x4 (&s)[4], DfRow& r) {
 #pragma unroll
@@ -1077,11 +1074,9 @@ __device__ __forceinline__ void df_values(const DfV& v, const f32x4 (&s)[4], DfR
     const uint2 h0 = hi_pairs(s[2 * ks]), h1 = hi_pairs(s[2 * ks + 1]), l0 = lo_pairs(s[2 * ks]), l1 = lo_pairs(s[2 * ks + 1]);
     const bf16x8 ph = __builtin_bit_cast(bf16x8, u32x4{h0.x, h0.y, h1.x, h1.y}), pl = __builtin_bit_cast(bf16x8, u32x4{l0.x, l0.y, l1.x, l1.y});
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-      const bf16x8 vv = __builtin_bit_cast(bf16x8, v.f[ks][dt]);
-      r.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, pl, r.o[dt], 0, 0, 0);
-      r.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, ph, r.o[dt], 0, 0, 0);
-    }
+    for (int dt = 0; dt < 4; ++dt) r.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v.f[ks][dt]), pl, r.o[dt], 0, 0, 0);
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) r.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v.f[ks][dt]), ph, r.o[dt], 0, 0, 0);
   }
 }
 
@@ -1151,6 +1146,10 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   const int* rowpos = srow + it.b * R;                 // positions of the sequence's rows
   const float sc2 = a.scale * 1.44269504088896340736f;
   const int qpos = r0 + c16 < RG ? rowpos[(r0 + c16) / G] : -1;              // position of the lane's query row
+  // the row and the two dims that this thread finishes when the waves meet (looked up ahead of the wait): its row of the launch, head and parts
+  const int row = tid >> 5, d0 = (tid & 31) * 2, row_j = min(r0 + row, RG - 1) / G;
+  const int out_m = it.b * R + row_j, out_head = it.kvh * G + min(r0 + row, RG - 1) - row_j * G;
+  const int np_row = it.valid ? df_parts(rowpos[row_j] + 1) : 0;             // parts that hold keys of the row
   bool bad = false;
   // ---- the queries of the tile's rows and this launch's keys / values of the kv head
   if (it.valid) {
@@ -1193,35 +1192,46 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
     u32x4 qh[2], ql[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) frag_from_lds(Qs + c16 * DF_QS + ks * 32 + g * 8, qh[ks], ql[ks]);
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const bool livej = j == 0 ? live0 : (j == 1 ? live1 : live2);
-      if (livej) {
-        const int kbase = 64 * (it.c0 + wave + 8 * j);
-        if (fresh(j)) df_patch_k(kf[j], kbase, it.len, it.nact, Kn, lane);
-        f32x4 s[4];
-        const int qp = j < 2 || qpos < DF_ONE_PART ? qpos : -1;            // the third round is not for rows in several parts
-        df_weights(kf[j], qh, ql, kbase, qp, fresh(j) || (j == 2 && it.nparts_b > 1), sc2, lane, rs, s);
-        if (j == 2 || fresh(j)) df_v_from_lds(v2, kbase, it.len, it.nact, Vn, lane, vf[j]);
-        df_values(vf[j], s, rs);
-      }
-    }
+    // All scores first, one maximum and one sum over the wave's chunks, then the values: a chain of reductions across lanes once, not once per chunk.
+    // (The third round is not for rows in several parts.)
+    f32x4 sc[3][4];
+    float mx = -INFINITY;
+    auto scores = [&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      const int kbase = 64 * (it.c0 + wave + 8 * j);
+      if (fresh(j)) df_patch_k(kf[j], kbase, it.len, it.nact, Kn, lane);
+      df_scores(kf[j], qh, ql, kbase, j < 2 || qpos < DF_ONE_PART ? qpos : -1, fresh(j) || (j == 2 && it.nparts_b > 1), lane, sc[j]);
+      mx = fmaxf(mx, df_max16(sc[j]));
+    };
+    scores(std::integral_constant<int, 0>());
+    if (live1) scores(std::integral_constant<int, 1>());
+    if (live2) scores(std::integral_constant<int, 2>());
+    rs.m = max_over_groups(mx) * sc2;
+    const float base = rs.m == -INFINITY ? 0.f : rs.m;     // (the row sees none of these keys: every weight is 0)
+    auto values = [&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      rs.l += df_weights(sc[j], sc2, base);
+      if (j == 2 || fresh(j)) df_v_from_lds(v2, 64 * (it.c0 + wave + 8 * j), it.len, it.nact, Vn, lane, vf[j]);
+      df_values(vf[j], sc[j], rs);
+    };
+    values(std::integral_constant<int, 0>());
+    if (live1) values(std::integral_constant<int, 1>());
+    if (live2) values(std::integral_constant<int, 2>());
+    rs.l = sum_over_groups(rs.l);
   }
   DF_STAMP2(3);
   // ---- the eight waves meet (fixed order: wave 0 .. 7); a single part's rows go out as operand words
   df_put_row(rs, MO, ML, wave, lane);
   __syncthreads();
   DF_STAMP2(4);
-  if (const int row = tid >> 5, d0 = (tid & 31) * 2; it.valid && row < nrt) {
-    const int qr = r0 + row, j = qr / G, gq = qr - j * G, m = it.b * R + j, head = it.kvh * G + gq;
-    const int np_row = df_parts(rowpos[j] + 1);                              // parts that hold keys of the row
+  if (it.valid && row < nrt) {
     if (it.part < np_row) {
       float mx, l, o[2];
       df_merge_row(MO, ML, row, d0, mx, l, o);
       if (np_row == 1) {
-        st_words2(attn + (size_t)m * nqd + head * 64 + d0, split_payload(o[0] / l), split_payload(o[1] / l), tag);
+        st_words2(attn + (size_t)out_m * nqd + out_head * 64 + d0, split_payload(o[0] / l), split_payload(o[1] / l), tag);
       } else {
-        u64* pp = att_p + ((((size_t)m * a.nq + head) * a.NP + it.part) * 16 + (d0 >> 2)) * 6;
+        u64* pp = att_p + ((((size_t)out_m * a.nq + out_head) * a.NP + it.part) * 16 + (d0 >> 2)) * 6;
         st_words2(pp + (d0 & 2), __float_as_uint(o[0]), __float_as_uint(o[1]), tag);
         if (!(d0 & 2)) st_words2(pp + 4, __float_as_uint(mx), __float_as_uint(l), tag);
       }

@@ -238,15 +238,6 @@ __device__ __forceinline__ void store_row_sum(const GemmArgs& g, int row, int pi
   if (row < g.M && (threadIdx.x & 63) < 16) g.sumsq[(size_t)row * ((pieces + 15) & ~15) + piece] = sum;
 }
 
-// Direct loads to LDS, 16 bytes a lane.  Through a buffer descriptor: after global_load_lds, which the compiler counts as a flat access to both
-// memories, every wait that it places for a load or an LDS read is one for all of them, and the loads in flight ahead were waited for
-// once per round of the loops below.
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-__device__ __forceinline__ rsrc_t load_rsrc(const void* base) { return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, 0x7FFFFFF0, 0x00027000); }
-__device__ __forceinline__ void load_to_lds(rsrc_t r, void* lds, int lane_off, int off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, lane_off, off, 0, 0);
-}
-
 // The order of a k-tile's instructions: a matrix instruction or two, then a request to memory or a read of the next k-tile's fragments, and so
 // on.  (Left alone, the compiler puts the reads behind nearly all of the matrix instructions, right ahead of the wait for them.)
 template <int MFMA, int VMEM, int READS>
