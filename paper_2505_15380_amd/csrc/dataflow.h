@@ -131,62 +131,37 @@ __device__ __forceinline__ void df_wait_hint(const u64* word, uint32_t tag, uint
   }
 }
 
-// Loads the words base[off[i]] (off == ~0: none) until every tag is this launch's.  False on a timeout.
-template <int N>
-__device__ __forceinline__ bool poll_words(const u64* base, const uint32_t (&off)[N], uint32_t tag, uint32_t (&out)[N],
-                                           uint32_t* err, const u64* hint = nullptr, uint32_t hint_tag = 0u) {
-  u64 v[N];
+// Two consecutive words with one 16-byte agent-scope load; `off`: bytes from the descriptor's base.
+typedef __amdgpu_buffer_rsrc_t df_rsrc;
+__device__ __forceinline__ df_rsrc df_make_rsrc(const u64* base) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)0xFFFFFFE0u, 0x00027000);
+}
+__device__ __forceinline__ u32x4 ld_words2(df_rsrc r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 16 /* sc1 */); }
+
+// Loads the pairs of words at off(at, i) (bytes; ~0: none) until every tag is this launch's.  False on a timeout.  (Offsets are worked out again
+// from `at` for a repeated load instead of being kept in registers.)
+template <int N, typename OFF>
+__device__ __forceinline__ bool poll_pairs(df_rsrc r, uint32_t at, OFF off, uint32_t tag, u32x4 (&v)[N], uint32_t* err,
+                                           const u64* hint = nullptr, uint32_t hint_tag = 0u) {
 #pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = off[i] != 0xFFFFFFFFu ? ld_word(base + off[i]) : ((u64)tag << 32);
+  for (int i = 0; i < N; ++i) v[i] = off(at, i) != 0xFFFFFFFFu ? ld_words2(r, off(at, i)) : u32x4{0u, tag, 0u, tag};
   long spins = 0;
-  bool ok = true;
   for (;;) {
     bool all = true;
 #pragma unroll
-    for (int i = 0; i < N; ++i) all = all && ((uint32_t)(v[i] >> 32) == tag);
-    if (all) break;
+    for (int i = 0; i < N; ++i) all = all && v[i][1] == tag && v[i][3] == tag;
+    if (all) return true;
     if (spins == 0 && hint) df_wait_hint(hint, hint_tag, err);
     if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
       __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, AG);
-      ok = false;
-      break;
+      return false;
     }
     __builtin_amdgcn_s_sleep(1);
+    asm volatile("" : "+v"(at) : : "memory");              // (the words may have changed)
 #pragma unroll
     for (int i = 0; i < N; ++i)
-      if ((uint32_t)(v[i] >> 32) != tag) v[i] = ld_word(base + off[i]);
+      if (v[i][1] != tag || v[i][3] != tag) v[i] = ld_words2(r, off(at, i));
   }
-#pragma unroll
-  for (int i = 0; i < N; ++i) out[i] = (uint32_t)v[i];
-  return ok;
-}
-
-// The 6 words of up to DF_NPF consecutive attention parts (96 words apart) of one 4-dim chunk.
-__device__ __forceinline__ bool poll_parts(const u64* base, uint32_t off0, int nparts, uint32_t tag, uint32_t (&out)[DF_NPF * 6],
-                                           uint32_t* err) {
-  u64 v[DF_NPF * 6];
-#pragma unroll
-  for (int i = 0; i < DF_NPF * 6; ++i) v[i] = (i / 6 < nparts) ? ld_word(base + off0 + (i / 6) * 96 + i % 6) : ((u64)tag << 32);
-  long spins = 0;
-  bool ok = true;
-  for (;;) {
-    bool all = true;
-#pragma unroll
-    for (int i = 0; i < DF_NPF * 6; ++i) all = all && ((uint32_t)(v[i] >> 32) == tag);
-    if (all) break;
-    if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
-      __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, AG);
-      ok = false;
-      break;
-    }
-    __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-    for (int i = 0; i < DF_NPF * 6; ++i)
-      if ((uint32_t)(v[i] >> 32) != tag) v[i] = ld_word(base + off0 + (i / 6) * 96 + i % 6);
-  }
-#pragma unroll
-  for (int i = 0; i < DF_NPF * 6; ++i) out[i] = (uint32_t)v[i];
-  return ok;
 }
 
 // Columns of a task of df_reduce_phase, and of a sum of squares that it publishes.
@@ -214,13 +189,6 @@ struct DPhase {
   u64* kvn;               // PE_QKV: side buffer of the new keys / values
   float* logits;          // PE_LOGITS
 };
-
-// Two consecutive words with one 16-byte agent-scope load; `off`: bytes from the descriptor's base.
-typedef __amdgpu_buffer_rsrc_t df_rsrc;
-__device__ __forceinline__ df_rsrc df_make_rsrc(const u64* base) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)0xFFFFFFE0u, 0x00027000);
-}
-__device__ __forceinline__ u32x4 ld_words2(df_rsrc r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 16 /* sc1 */); }
 
 // Operand words of rows [0, M) (K words each, the rows contiguous) -> As, and the rows' sums of squares [M][nsq] -> sqs.  In As a
 // row has K + 4 words: of every eight consecutive k the hi halves (four words), then the lo halves, as the matrix core takes them.  (With the words
@@ -1153,31 +1121,29 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   bool bad = false;
   // ---- the queries of the tile's rows and this launch's keys / values of the kv head
   if (it.valid) {
-    constexpr int NB = SB <= 4 ? 3 : 6;                 // words a thread keeps in flight: one flight for 4 / all 16 new rows
+    constexpr int NB = SB <= 4 ? 2 : 3;                  // pairs of words a thread keeps in flight: one flight for 4 / all 16 new rows
     const int nQ = nrt * 64, total = nQ + (unew ? it.nact * 128 : 0);        // <= 1024 + 2048 words
+    const df_rsrc rs = df_make_rsrc(a.tw);
     const uint32_t q_off = (uint32_t)(q - a.tw), n_off = (uint32_t)(kvn - a.tw);
-    for (int base = 0; base < total; base += NB * PBLOCK) {
-      uint32_t off[NB], out[NB];
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int idx = base + u * PBLOCK + tid;
-        off[u] = 0xFFFFFFFFu;
+    for (int base = 0; base < total; base += 2 * NB * PBLOCK) {
+      u32x4 v[NB];
+      auto off = [&](uint32_t t, int u) -> uint32_t {
+        const int idx = base + 2 * (u * PBLOCK + (int)t);
         if (idx < nQ) {
           const int r = r0 + (idx >> 6), dd = idx & 63, j = r / G, gq = r - j * G;
-          off[u] = q_off + (uint32_t)((it.b * R + j) * nqd + (it.kvh * G + gq) * 64 + dd);
-        } else if (idx < total) {
-          const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
-          off[u] = n_off + (uint32_t)((((it.b * R + it.off + jn) * 2 + which) * a.nkv + it.kvh) * 64 + dd);
+          return 8u * (q_off + (uint32_t)((it.b * R + j) * nqd + (it.kvh * G + gq) * 64 + dd));
         }
-      }
-      bad = !poll_words<NB>(a.tw, off, tag, out, a.bar + 64, a.hg + (size_t)(2 * layer) * a.st_h, tag) || bad;
+        const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
+        return idx < total ? 8u * (n_off + (uint32_t)((((it.b * R + it.off + jn) * 2 + which) * a.nkv + it.kvh) * 64 + dd)) : 0xFFFFFFFFu;
+      };
+      bad = !poll_pairs<NB>(rs, (uint32_t)tid, off, tag, v, a.bar + 64, a.hg + (size_t)(2 * layer) * a.st_h, tag) || bad;
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
-        const int idx = base + u * PBLOCK + tid;
-        if (idx < nQ) Qs[(idx >> 6) * DF_QS + (idx & 63)] = out[u];
+        const int idx = base + 2 * (u * PBLOCK + tid);
+        if (idx < nQ) *(uint2*)(Qs + (idx >> 6) * DF_QS + (idx & 63)) = make_uint2(v[u][0], v[u][2]);
         else if (idx < total) {
           const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
-          (which ? Vn : Kn)[jn * 64 + dd] = (bf16_t)out[u];
+          *(uint32_t*)((which ? Vn : Kn) + jn * 64 + dd) = (v[u][0] & 0xFFFFu) | (v[u][2] << 16);
         }
       }
     }
@@ -1237,44 +1203,45 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
       }
     }
   }
-  // ---- merge of the parts: of the tile's rows, the workgroup of part p finishes those with row index = p mod P
+  // ---- merge of the parts: of the tile's rows, the workgroup of part p finishes those with row index = p mod P, two dims a thread
   if (it.valid && it.nparts_b > 1) {
-    const int row = tid >> 4, ch = tid & 15, d0 = ch * 4;
     const int P = it.nparts_b;
     const int first = ((it.part - r0) % P + P) % P;                          // first row of the tile this workgroup finishes
     const int qr = r0 + first + row * P;
-    if (tid < 256 && first + row * P < nrt) {
+    if (first + row * P < nrt) {
       const int j = qr / G, gq = qr - j * G, m = it.b * R + j, head = it.kvh * G + gq;
-      const int np_row = df_parts(rowpos[j] + 1);
-      if (np_row > 1) {
-        const uint32_t p_off = (uint32_t)(att_p - a.tw) + (uint32_t)(((m * a.nq + head) * a.NP) * 96 + ch * 6);
-        float mx = -INFINITY, l = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int p0 = 0; p0 < np_row; p0 += DF_NPF) {
-          uint32_t out[DF_NPF * 6];
-          bad = !poll_parts(a.tw, p_off + (uint32_t)(p0 * 96), np_row - p0, tag, out, a.bar + 64) || bad;
+      const int np = df_parts(rowpos[j] + 1);
+      if (np > 1) {
+        const df_rsrc rs = df_make_rsrc(att_p);
+        const uint32_t p_off = 8u * (uint32_t)(((m * a.nq + head) * a.NP) * 96 + (d0 >> 2) * 6);
+        float mx = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;
+        for (int p0 = 0; p0 < np; p0 += DF_NPF) {
+          u32x4 v[DF_NPF * 2];                               // per part: the two values; maximum and sum
+          auto off = [&](uint32_t at, int i) -> uint32_t {
+            return i / 2 < np - p0 ? at + (uint32_t)((p0 + i / 2) * 768 + (i % 2 ? 32 : (d0 & 2) * 8)) : 0xFFFFFFFFu;
+          };
+          bad = !poll_pairs<DF_NPF * 2>(rs, p_off, off, tag, v, a.bar + 64) || bad;
           float gm = mx;
 #pragma unroll
           for (int p = 0; p < DF_NPF; ++p)
-            if (p0 + p < np_row) gm = fmaxf(gm, __uint_as_float(out[p * 6 + 4]));
+            if (p0 + p < np) gm = fmaxf(gm, __uint_as_float(v[2 * p + 1][0]));
           if (p0 > 0) {                                      // more than DF_NPF parts: rescale what is already summed
             const float e = df_exp2(mx - gm);
             l *= e;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] *= e;
+            o0 *= e;
+            o1 *= e;
           }
           mx = gm;
 #pragma unroll
           for (int p = 0; p < DF_NPF; ++p)
-            if (p0 + p < np_row) {
-              const float e = df_exp2(__uint_as_float(out[p * 6 + 4]) - mx);
-              l = fmaf(__uint_as_float(out[p * 6 + 5]), e, l);
-#pragma unroll
-              for (int i = 0; i < 4; ++i) o[i] = fmaf(__uint_as_float(out[p * 6 + i]), e, o[i]);
+            if (p0 + p < np) {
+              const float e = df_exp2(__uint_as_float(v[2 * p + 1][0]) - mx);
+              l = fmaf(__uint_as_float(v[2 * p + 1][2]), e, l);
+              o0 = fmaf(__uint_as_float(v[2 * p][0]), e, o0);
+              o1 = fmaf(__uint_as_float(v[2 * p][2]), e, o1);
             }
         }
-        u64* out = attn + (size_t)m * nqd + head * 64 + d0;
-        st_words2(out, split_payload(o[0] / l), split_payload(o[1] / l), tag);
-        st_words2<16>(out, split_payload(o[2] / l), split_payload(o[3] / l), tag);
+        st_words2(attn + (size_t)m * nqd + head * 64 + d0, split_payload(o0 / l), split_payload(o1 / l), tag);
       }
     }
   }

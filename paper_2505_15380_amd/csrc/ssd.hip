@@ -466,7 +466,8 @@ extern "C" int ssd_kv_create(const ssd_model* m, int max_seqs, int max_rows, int
   }
   // The barrier-free forward additionally needs its word offsets to fit 32 bits; its words start untagged (zero).
   kv->dataflow = false;
-  if (e == hipSuccess && kv->persistent_wgs > 0 && kv->t_words > 0 && kv->t_words < ((size_t)1 << 32) && kv->t_attp_at < ((size_t)1 << 28)) {
+  if (e == hipSuccess && kv->persistent_wgs > 0 && kv->t_words > 0 && kv->t_words < ((size_t)1 << 32) && kv->t_attp_at < ((size_t)1 << 28) &&
+      (size_t)kv->p_rows * m->c.n_q_heads * kv->NP * 96 < ((size_t)1 << 28)) {      // (pairs of words are addressed by 32 bits of bytes: ahead of the parts, and in a layer's parts)
     e = hipMemsetAsync(kv->t_base, 0, kv->t_words * sizeof(u64), (hipStream_t)stream);
     const char* env = getenv("SSD_FORWARD");
     kv->dataflow = !(env && strcmp(env, "barrier") == 0);
