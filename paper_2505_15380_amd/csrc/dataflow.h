@@ -20,8 +20,8 @@
 // bf16 whose sum the matrix core consumes); residual rows, sums of squares and partial results are fp32 bits; new
 // keys / values are bf16 bits.
 //
-// A workgroup stages the operand rows it needs in LDS once (all its threads poll in parallel, SB words in flight
-// each: the kernel is instantiated for SB = 2, 4, 10, 16, 18 and the host picks, up to 8 rows, the smallest that holds the
+// A workgroup stages the operand rows it needs in LDS once (all its threads poll in parallel, a pair of words of each of SB / 2
+// rows in flight: the kernel is instantiated for SB = 2, 4, 10, 16, 18 and the host picks, up to 8 rows, the smallest that holds the
 // launch's rows in one flight, 18 for more) and feeds the matrix cores from LDS.  The weights of an item are requested at the entry of its phase, into
 // registers, before that wait: workgroups arrive at a phase before its operands do, so the wait hides the HBM latency.
 // The phases with few items (QKV, attention, output projection) run on workgroups of their own, beyond those that
@@ -193,77 +193,83 @@ struct DPhase {
 // Operand words of rows [0, M) (K words each, the rows contiguous) -> As, and the rows' sums of squares [M][nsq] -> sqs.  In As a
 // row has K + 4 words: of every eight consecutive k the hi halves (four words), then the lo halves, as the matrix core takes them.  (With the words
 // as they come a lane read both halves of its operand and picked one: twice the LDS reads, which took 900 cycles of a phase, and eight
-// permutations a k-tile.)  The whole workgroup polls in parallel, a pair of words per load: half the load instructions of
-// a word each (one row 400 -> 380 us a forward; nine rows, with the flights that hold them now, 760 -> 725).  Lanes without a
-// pair are masked out: a load costs the cycles of its return path even where all its lanes are out of range (five rows 513 ->
-// 543 us with such loads instead of the mask).  RES: two more words per thread (x0, x1: offsets in words, or ~0) ride in the
-// first flight and come back in xo0, xo1.  Offsets are recomputed for a repeated load instead of being kept in registers; with
-// whole rows a pair's offset is its index, and only the padded LDS address needs the row.
+// permutations a k-tile.)  The whole workgroup polls in parallel, a pair of words per load.  What bounds it are a thread's instructions per pair,
+// so a thread has the same columns of every row: a row's place is then one scalar offset for the load and one sum for the LDS
+// write, and rows that are not there are skipped by scalar branches.  Of eight waves an eighth idles at 896 columns.  (With the pairs
+// dealt out over all threads as they lie, each pair has a row to find and a limit to keep: five rows 0.8 us a layer more, nine rows
+// 1.6, one row 0.2.)  Lanes without a pair are masked out: a load costs the cycles of its return path even where all its lanes are out of
+// range (five rows 513 -> 543 us with such loads instead of the mask).  A thread's first sum of squares rides in the flight, and so do, RES, two
+// more words (x0, x1: offsets in words, or ~0) that come back in xo0, xo1; whatever is late is asked for again together, so that
+// nothing costs a round trip of its own after the operands.  (Watching a word per producer first, and requesting the
+// operands once all of them are there, saves polls but adds that round trip: 0.8 us a layer more with one row, 0.9 with five or nine.)
 template <int SB, bool RES>
 __device__ __forceinline__ bool stage_operand(const DArgs& a, const u64* A, int K, const u64* sq, int nsq, uint32_t* As, float* sqs, int tid,
                                               uint32_t x0, uint32_t x1, uint32_t& xo0, uint32_t& xo1, const u64* hint, uint32_t hint_tag,
                                               const uint32_t tag) {
-  constexpr int SP = SB / 2;
-  const int M = a.rows.M, nA = M * K, nS = sq ? M * nsq : 0, pA = nA >> 1, total = pA + ((nS + 1) >> 1);      // (pairs)
+  constexpr int SP = SB / 2;                               // rows in flight
+  const int M = a.rows.M, nS = sq ? M * nsq : 0;
   const df_rsrc rs = df_make_rsrc(a.tw);
-  const uint32_t a_off = (uint32_t)(A - a.tw) * 8u, s_off = sq ? (uint32_t)(sq - a.tw) * 8u : 0u;
-  const float rkn = 2.0f / (float)K;
+  const uint32_t a_off = (uint32_t)(A - a.tw) * 8u;
   uint32_t* err = a.bar + 64;
   bool ok = true;
-  for (int base = 0; base < total; base += PBLOCK * SP) {
-    int t2 = tid;
-    auto off_of = [&](int u) -> uint32_t {
-      const int i = base + u * PBLOCK + t2;
-      return i < pA ? a_off + (uint32_t)i * 16u : s_off + (uint32_t)(i - pA) * 16u;
-    };
-    // (an odd last sum's neighbour is not this launch's)
-    auto there = [&](int u, const u32x4 v) {
-      const int i = base + u * PBLOCK + t2;
-      return i >= total || (v[1] == tag && (v[3] == tag || (i == total - 1 && (nS & 1))));
-    };
-    u32x4 v[SP];
-    u64 h0 = (u64)tag << 32, h1 = h0;
-#pragma unroll
-    for (int u = 0; u < SP; ++u) v[u] = base + u * PBLOCK + tid < total ? ld_words2(rs, off_of(u)) : u32x4{0u, tag, 0u, tag};
-    if (RES && base == 0) {
-      if (x0 != 0xFFFFFFFFu) h0 = ld_word(a.tw + x0);
-      if (x1 != 0xFFFFFFFFu) h1 = ld_word(a.tw + x1);
+  auto give_up = [&](long& spins) -> bool {
+    if (spins == 0 && hint) df_wait_hint(hint, hint_tag, err);         // far too early: wait cheaply for the phase before
+    if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
+      __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, AG);
+      ok = false;
+      return true;
     }
-    long spins = 0;
-    for (;;) {
-      bool all = !RES || ((uint32_t)(h0 >> 32) == tag && (uint32_t)(h1 >> 32) == tag);
+    __builtin_amdgcn_s_sleep(1);
+    return false;
+  };
+  u64 w = (u64)tag << 32, h0 = w, h1 = w;
+  if (!RES && tid < nS) w = ld_word(sq + tid);
+  if (RES && x0 != 0xFFFFFFFFu) h0 = ld_word(a.tw + x0);
+  if (RES && x1 != 0xFFFFFFFFu) h1 = ld_word(a.tw + x1);
+  for (int c0 = 0; c0 < K >> 1; c0 += PBLOCK)
+    for (int r0 = 0; r0 < M; r0 += SP) {
+      const bool on = c0 + tid < K >> 1;
+      uint32_t at = (uint32_t)(c0 + tid) * 16u;
+      auto request = [&](int u) -> u32x4 {
+        return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)at, (int)(a_off + (uint32_t)((r0 + u) * K) * 8u), 16 /* sc1 */);
+      };
+      u32x4 v[SP];
 #pragma unroll
-      for (int u = 0; u < SP; ++u) all = all && there(u, v[u]);
-      if (all) break;
-      if (spins == 0 && hint) df_wait_hint(hint, hint_tag, err);       // far too early: wait cheaply for the phase before
-      if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
-        __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, AG);
-        ok = false;
-        break;
+      for (int u = 0; u < SP; ++u) v[u] = on && r0 + u < M ? request(u) : u32x4{0u, tag, 0u, tag};
+      for (long spins = 0;;) {
+        uint32_t late = RES ? ((uint32_t)(h0 >> 32) ^ tag) | ((uint32_t)(h1 >> 32) ^ tag) : (uint32_t)(w >> 32) ^ tag;
+#pragma unroll
+        for (int u = 0; u < SP; ++u) late |= (v[u][1] ^ tag) | (v[u][3] ^ tag);
+        if (late == 0u || give_up(spins)) break;
+        asm volatile("" : "+v"(at) : : "memory");          // (the words may have changed)
+#pragma unroll
+        for (int u = 0; u < SP; ++u)
+          if (v[u][1] != tag || v[u][3] != tag) v[u] = request(u);
+        if (!RES && (uint32_t)(w >> 32) != tag) w = ld_word(sq + tid);
+        if (RES && (uint32_t)(h0 >> 32) != tag) h0 = ld_word(a.tw + x0);
+        if (RES && (uint32_t)(h1 >> 32) != tag) h1 = ld_word(a.tw + x1);
       }
-      __builtin_amdgcn_s_sleep(1);
-      asm volatile("" : "+v"(t2) : : "memory");          // keeps the offsets out of registers across the wait; the words may have changed
+      if (on) {
+        uint32_t* to = As + r0 * (K + 4) + 2 * (c0 + tid) - (tid & 3);
 #pragma unroll
-      for (int u = 0; u < SP; ++u)
-        if (!there(u, v[u])) v[u] = ld_words2(rs, off_of(u));
-      if (RES) {
-        if ((uint32_t)(h0 >> 32) != tag) h0 = ld_word(a.tw + x0);
-        if ((uint32_t)(h1 >> 32) != tag) h1 = ld_word(a.tw + x1);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < SP; ++u) {
-      const int i = base + u * PBLOCK + tid;
-      if (i < pA) {
-        const int row = (int)(((float)i + 0.5f) * rkn);
-        uint32_t* w = As + 2 * i + 4 * row - (i & 3);
-        w[0] = __builtin_amdgcn_perm(v[u][2], v[u][0], 0x05040100u);
-        w[4] = __builtin_amdgcn_perm(v[u][2], v[u][0], 0x07060302u);
-      } else if (i < total) {
-        *(uint2*)(sqs + 2 * (i - pA)) = make_uint2(v[u][0], v[u][2]);
+        for (int u = 0; u < SP; ++u)
+          if (r0 + u < M) {
+            to[u * (K + 4)] = __builtin_amdgcn_perm(v[u][2], v[u][0], 0x05040100u);
+            to[u * (K + 4) + 4] = __builtin_amdgcn_perm(v[u][2], v[u][0], 0x07060302u);
+          }
       }
     }
-    if (RES && base == 0) { xo0 = (uint32_t)h0; xo1 = (uint32_t)h1; }
+  if (!RES) {
+    if (tid < nS) sqs[tid] = __uint_as_float((uint32_t)w);
+    for (int i = PBLOCK + tid; i < nS; i += PBLOCK) {      // (more than 512 sums)
+      w = ld_word(sq + i);
+      for (long spins = 0; (uint32_t)(w >> 32) != tag && !give_up(spins);) w = ld_word(sq + i);
+      sqs[i] = __uint_as_float((uint32_t)w);
+    }
+  }
+  if (RES) {
+    xo0 = (uint32_t)h0;
+    xo1 = (uint32_t)h1;
   }
   return ok;
 }
@@ -358,6 +364,12 @@ template <int SB>
 constexpr bool df_pack() { return SB <= 16; }
 constexpr int DF_PACK_ROWS = 8;
 
+// Every request of this thread that the compiler knows of has come back.  Its own waits count requests, stores among them, but not the
+// stores of st_words2; where it believes that some path has left a register with a request pending, it waits for a count that those
+// stores have grown past, which is a wait for their acknowledgement: 0.8 us and more behind the MLP's.  So each phase says, where its operands
+// are there and before it stores, that nothing is pending, on every path (with five rows the sums' operands are there 0.3 us earlier).
+__device__ __forceinline__ void df_loads_done() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
+
 // One GEMM phase (QKV, output projection, head); the caller skips it for a workgroup none of whose units has an
 // item.  The weight fragments of the unit's item are requested at entry, into registers, before the wait for the
 // operands: units arrive well before their operands do, so the weights' HBM latency is hidden by that wait.
@@ -420,6 +432,7 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
     if (rd == 0) ok = stage_operand<SB, EPI == PE_RESID>(a, ph.A, ph.K, ph.sq, ph.K / df_red_cols<SB>(), As, sqs, tid, hx0, hx1, hv0, hv1, ph.hint, ph.hint_tag, tag);
     if (!ok) *sdead = 1;
     __syncthreads();
+    df_loads_done();
     if (*sdead) return true;
     if (rd == 0) DF_STAMP(slot);
     // ---- products
@@ -571,6 +584,7 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
     if (rd == 0) ok = stage_operand<SB, false>(a, ph.A, ph.K, ph.sq, KT, As, sqs, tid, 0xFFFFFFFFu, 0xFFFFFFFFu, dummy0, dummy1, ph.hint, ph.hint_tag, tag);
     if (!ok) *sdead = 1;
     __syncthreads();
+    df_loads_done();
     if (*sdead) return true;
     if (rd == 0) DF_STAMP(slot);
     f32x4 acc0 = f32x4{0, 0, 0, 0}, acc1 = f32x4{0, 0, 0, 0};
@@ -607,9 +621,6 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
       // Computed transposed: a lane holds four consecutive columns of row c16.  They go out by way of LDS, row by row: a wave's seven tiles of a
       // row with one store, 128 contiguous bytes per tile.  (Straight from the registers, two stores per tile of which most lanes are masked, this
       // section took 0.8 us with one row, 0.5 so; with nine rows the sums' operands are there 0.8 us earlier.)
-      // The weights have arrived long ago; waiting for all of them here tells the compiler so.  It does not count the stores below,
-      // and its own wait for the i-th tile's weights would wait for acknowledged stores (0.8 us).
-      __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt(0)
       f32x4 acc[DF_DN];
 #pragma unroll
       for (int i = 0; i < DF_DN; ++i)
@@ -739,6 +750,7 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t t
     if ((tid & 63) < C) rs[(tid >> 6) * C + c] = sum;
     if (bad) *sdead = 1;
     __syncthreads();
+    df_loads_done();
     if (*sdead) return true;
     if (rd == 0) DF_STAMP(slot);
     if (want_h) {
@@ -1189,6 +1201,7 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   // ---- the eight waves meet (fixed order: wave 0 .. 7); a single part's rows go out as operand words
   df_put_row(rs, MO, ML, wave, lane);
   __syncthreads();
+  df_loads_done();
   DF_STAMP2(4);
   if (it.valid && row < nrt) {
     if (it.part < np_row) {
@@ -1365,6 +1378,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     srow[32 + threadIdx.x] = (int)(uint32_t)w;
   }
   __syncthreads();
+  df_loads_done();
   DF_STAMP(0);
   for (int l = 0; l < L; ++l) {
     const int s0 = 2 + l * 10;

@@ -963,9 +963,10 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   a.trace = kv->trace_on ? kv->trace : nullptr;
   ProfScope ps(PROF_PERSISTENT, st);
   kv->last_whole = kv->attn_whole && max_len + 16 <= DF_ONE_PART;      // (reported only)
-  // words of one operand staging: the rows' operand words and their sums of squares; one flight holds 512 x SB
+  // one flight of an operand staging holds SB / 2 rows; the words that it brings, the rows' operands and their sums of squares, are
+  // at most 512 x SB (wider rows take several flights, and more of them in flight at once)
   auto holds = [&](int n) {                                // (n <= 4: sums of squares over 8 columns, see df_reduce_phase)
-    return M * (std::max(c.d_model, nqd) + c.d_model / (n <= 4 ? 8 : 32)) <= n * PBLOCK;
+    return 2 * M <= n && M * (std::max(c.d_model, nqd) + c.d_model / (n <= 4 ? 8 : 32)) <= n * PBLOCK;
   };
   int sb = kv->df_sb ? kv->df_sb : holds(2) ? 2 : holds(4) ? 4 : holds(10) ? 10 : holds(16) ? 16 : 18;
   if (sb <= 4 && M * (c.d_model / 8) > DF_SQ_WORDS) sb = 10;
