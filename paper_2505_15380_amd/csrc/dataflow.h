@@ -6,15 +6,21 @@
 //
 // Dependent phases are ordered by the data itself: everything a workgroup hands to another workgroup is made of 8-byte
 // words {payload, tag}, where tag is the number of this launch.  Words are stored and loaded with agent-scope 64-bit accesses,
-// or, where two lie side by side (GEMM operands, attention rows and partials, MLP partials), with 16-byte accesses past the
+// or, where two lie side by side (GEMM operands, attention rows and partials), with 16-byte accesses past the
 // same caches.  A consumer repeats the loads whose tag is not yet this launch's.  A word is observed whole, so a matching tag
 // proves its payload.  For a 64-bit access the memory model promises that.  That each aligned 8-byte half of a 16-byte access
 // is whole as well is a property of this hardware, where a lane's 16 bytes are one piece of one cache line in every request;
 // of the two halves together nothing is assumed, each has its tag.  No store has to be acknowledged
 // before a flag is raised, no counter is shared, and a dependency costs one store plus one load instead of the
 // chain of memory round trips of a barrier.  Every word is written exactly once per launch (each layer and phase
-// has its own buffers; the MLP partials alternate between two buffers and carry the layer in their tag), and
-// launches on one cache workspace are ordered by the stream, so a tag cannot be matched by an older value.
+// has its own buffers), and launches on one cache workspace are ordered by the stream, so a tag cannot be matched by an older value.
+//
+// The MLP's partials have no tags: there are ffn/32 of them per output, and with a tag beside every value their way to memory and back, 11 MB
+// a layer with five rows, was what their sums waited for.  A partial is four bytes, zero while it is not there (a zero result goes out as
+// -0, which adds the same), and the workgroup that has summed it puts the zero back.  Two buffers take the layers in turn.  The zeros of
+// layer l have reached memory before their workgroup publishes its sums of layer l + 1; an MLP item of layer l + 2 begins after operands
+// that depend on all of those; so no zero overtakes a partial, and a partial that is not zero is this layer's.  Every launch leaves the buffers
+// zero, unless a wait times out; then the workspace is cleared before the cache is used again.
 //
 // Payloads: a GEMM operand value x is hi | lo << 16 with hi = upper 16 bits of x and lo = bf16(x - hi) (the two
 // bf16 whose sum the matrix core consumes); residual rows, sums of squares and partial results are fp32 bits; new
@@ -82,15 +88,15 @@ struct DArgs {
   u64* tw;                // base of the tagged workspace; the members below point into it
   u64* h;                 // [2L+1][PR][d]      fp32: residual stream entering layer l at 2l, after attention at 2l+1
   u64* hg;                // [2L+1][PR][d]      operand: h times the gain of the RMSNorm that consumes it
-  u64* sq;                // [2L+1][PR][d/8]    fp32: sums of squares of h over 32 columns (after the MLP: over df_red_cols columns)
+  u64* sq;                // [2L+1][PR][d/8]    fp32: sums of squares of h over 32 columns (after the MLP: over df_sq_cols columns)
   u64* q;                 // [L][PR][nq*64]     operand: rotated queries
   u64* kvn;               // [L][PR][2][nkv*64] bf16: this launch's keys (rotated) and values
   u64* attn;              // [L][PR][nq*64]     operand: attention output
   u64* att_p;             // [L][PR][nq][NP][16][6] fp32: per part and 4-dim chunk: 4 weighted values, max, sum
-  u64* part2;             // [2][row][d/32][ffn/32][32] fp32: down-projection partials of one 32-column slice of the SwiGLU output each,
-                          // tagged with launch and layer (buffer = layer parity).  What a sum task reads is contiguous: with a
+  float* part;            // [2][row][d/C][ffn/32][C]: down-projection partials of one 32-column slice of the SwiGLU output each (buffer =
+                          // layer parity; C = df_sum_cols, 8 take the room of 16).  What a sum task reads is contiguous: with a
                           // row per workgroup, 112 KB apart, its pieces and all workgroups' stores fell on few memory channels
-  size_t st_part2;
+  size_t st_part;
   u64* rowblk;            // [16] per row: the pool block that takes the row's new key and value (-1: none), from the reservation
   float* logits;
   size_t st_h, st_sq, st_q, st_kvn, st_att_p;   // strides in words
@@ -108,10 +114,9 @@ __device__ __forceinline__ void st_word(u64* p, uint32_t payload, uint32_t tag) 
 __device__ __forceinline__ void st_wordf(u64* p, float x, uint32_t tag) { st_word(p, __float_as_uint(x), tag); }
 // Two consecutive words (16-byte aligned) with one store: a word is still stored by one instruction, and each has its tag.  (The
 // s_nop: store data of more than 8 bytes must not be overwritten by the next two vector instructions.)
-template <int OFFSET = 0>
 __device__ __forceinline__ void st_words2(u64* p, uint32_t x0, uint32_t x1, uint32_t tag) {
   const u32x4 a = {x0, tag, x1, tag};
-  asm volatile("global_store_dwordx4 %0, %1, off offset:%2 sc1\n\ts_nop 1" ::"v"(p), "v"(a), "n"(OFFSET) : "memory");
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(a) : "memory");
 }
 __device__ __forceinline__ uint32_t split_payload(float x) {
   const uint32_t u = __float_as_uint(x), h = u & 0xFFFF0000u;
@@ -133,7 +138,7 @@ __device__ __forceinline__ void df_wait_hint(const u64* word, uint32_t tag, uint
 
 // Two consecutive words with one 16-byte agent-scope load; `off`: bytes from the descriptor's base.
 typedef __amdgpu_buffer_rsrc_t df_rsrc;
-__device__ __forceinline__ df_rsrc df_make_rsrc(const u64* base) {
+__device__ __forceinline__ df_rsrc df_make_rsrc(const void* base) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)0xFFFFFFE0u, 0x00027000);
 }
 __device__ __forceinline__ u32x4 ld_words2(df_rsrc r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 16 /* sc1 */); }
@@ -166,7 +171,9 @@ __device__ __forceinline__ bool poll_pairs(df_rsrc r, uint32_t at, OFF off, uint
 
 // Columns of a task of df_reduce_phase, and of a sum of squares that it publishes.
 template <int SB>
-constexpr int df_red_cols() { return SB <= 4 ? 8 : 32; }
+constexpr int df_sum_cols() { return SB <= 4 ? 8 : SB <= 10 ? 32 : 64; }
+template <int SB>
+constexpr int df_sq_cols() { return SB <= 4 ? 8 : 32; }
 
 // ------------------------------------------------------------------------------------------------ GEMM phases
 struct DPhase {
@@ -189,6 +196,12 @@ struct DPhase {
   u64* kvn;               // PE_QKV: side buffer of the new keys / values
   float* logits;          // PE_LOGITS
 };
+
+// Every request of this thread that the compiler knows of has come back.  Its own waits count requests, stores among them, but not the
+// stores of st_words2; where it believes that some path has left a register with a request pending, it waits for a count that those
+// stores have grown past, which is a wait for their acknowledgement: 0.8 us and more behind the MLP's.  So each phase says, where its operands
+// are there and before it stores, that nothing is pending, on every path (with five rows the sums' operands are there 0.3 us earlier).
+__device__ __forceinline__ void df_loads_done() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 
 // Operand words of rows [0, M) (K words each, the rows contiguous) -> As, and the rows' sums of squares [M][nsq] -> sqs.  In As a
 // row has K + 4 words: of every eight consecutive k the hi halves (four words), then the lo halves, as the matrix core takes them.  (With the words
@@ -249,6 +262,7 @@ __device__ __forceinline__ bool stage_operand(const DArgs& a, const u64* A, int 
         if (RES && (uint32_t)(h0 >> 32) != tag) h0 = ld_word(a.tw + x0);
         if (RES && (uint32_t)(h1 >> 32) != tag) h1 = ld_word(a.tw + x1);
       }
+      df_loads_done();
       if (on) {
         uint32_t* to = As + r0 * (K + 4) + 2 * (c0 + tid) - (tid & 3);
 #pragma unroll
@@ -364,12 +378,6 @@ template <int SB>
 constexpr bool df_pack() { return SB <= 16; }
 constexpr int DF_PACK_ROWS = 8;
 
-// Every request of this thread that the compiler knows of has come back.  Its own waits count requests, stores among them, but not the
-// stores of st_words2; where it believes that some path has left a register with a request pending, it waits for a count that those
-// stores have grown past, which is a wait for their acknowledgement: 0.8 us and more behind the MLP's.  So each phase says, where its operands
-// are there and before it stores, that nothing is pending, on every path (with five rows the sums' operands are there 0.3 us earlier).
-__device__ __forceinline__ void df_loads_done() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
-
 // One GEMM phase (QKV, output projection, head); the caller skips it for a workgroup none of whose units has an
 // item.  The weight fragments of the unit's item are requested at entry, into registers, before the wait for the
 // operands: units arrive well before their operands do, so the weights' HBM latency is hidden by that wait.
@@ -429,7 +437,7 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
       hx1 = h_off + n1;
     }
     bool ok = true;
-    if (rd == 0) ok = stage_operand<SB, EPI == PE_RESID>(a, ph.A, ph.K, ph.sq, ph.K / df_red_cols<SB>(), As, sqs, tid, hx0, hx1, hv0, hv1, ph.hint, ph.hint_tag, tag);
+    if (rd == 0) ok = stage_operand<SB, EPI == PE_RESID>(a, ph.A, ph.K, ph.sq, ph.K / df_sq_cols<SB>(), As, sqs, tid, hx0, hx1, hv0, hv1, ph.hint, ph.hint_tag, tag);
     if (!ok) *sdead = 1;
     __syncthreads();
     df_loads_done();
@@ -443,7 +451,7 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
       float sq = 0.f;
       if (row < M)                                         // sums over 32 columns, as the halves of df_reduce_phase's tree
         for (int p = col; p < KT; p += 16) {
-          if (df_red_cols<SB>() == 8) {
+          if (df_sq_cols<SB>() == 8) {
             const f32x4 q = *(const f32x4*)(sqs + (row * KT + p) * 4);
             sq += (q[0] + q[1]) + (q[2] + q[3]);
           } else {
@@ -518,14 +526,38 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
   return false;
 }
 
+// Brings the weights of the unit's QKV item into the chip's cache, a word of each 128-byte line: for a workgroup that sums partials just before (16
+// rows), with nothing to do until they come.  It requests the item's weights when its sum is out, and from memory they would arrive later
+// than the operands (0.6 us a layer).
+__device__ __forceinline__ void df_touch_weights(const DArgs& a, const DPhase& ph) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int NU = gridDim.x * 2, KT = ph.K >> 5, ntiles = (ph.N + 15) >> 4;
+  int t0, t1, split;
+  if (!gemm_item<PE_QKV>(ph, df_item_of_unit(blockIdx.x * 2 + (wave >> 2), ph.shift, NU, ph.stride), t0, t1, split)) return;
+  const uint32_t* w0 = (const uint32_t*)ph.W0 + (size_t)t0 * KT * 256;
+  const uint32_t* w1 = (const uint32_t*)ph.W0 + (size_t)(t1 < ntiles ? t1 : t0) * KT * 256;
+  uint32_t x = 0u;
+  for (int i = tid & 255; i < KT * 8; i += 256) x |= w0[i * 32] | w1[i * 32];
+  asm volatile("" ::"v"(x));
+}
+
 // ------------------------------------------------------------------------------------------------ fused MLP
 // Gate/up + SwiGLU + down projection inside one workgroup: its two units produce 32 consecutive columns of the
 // SwiGLU output, which is exactly one k-tile of the down projection; the workgroup multiplies it with that k-tile of
 // every output tile (8 waves x DF_DN tiles) and publishes a partial of the whole row.  The SwiGLU output never
 // leaves the workgroup, and one dependency per layer disappears; the price is ffn/32 partials per output.
+constexpr int df_part_pitch(int C) { return C == 8 ? 64 : 4 * C; }     // bytes from one partial of C columns to the next
 struct WDown { u32x4 b[DF_DN]; };
 
-__device__ __forceinline__ uint32_t df_tag2(const uint32_t tag, int layer) { return tag * 128u + (uint32_t)layer; }
+// (a zero would be a partial that is not there)
+__device__ __forceinline__ void df_put_partial(df_rsrc r, uint32_t at, const f32x4 x) {
+  u32x4 b = __builtin_bit_cast(u32x4, x);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) b[i] = b[i] ? b[i] : 0x80000000u;
+  __builtin_amdgcn_raw_buffer_store_b128(b, r, (int)at, 0, 16 /* sc1 */);
+}
 
 // Fragments (n-tile wave + 8 i, k-tile kt2) of the down projection for i < DF_DN; exactly DF_DN loads.
 __device__ __forceinline__ void df_prefetch_down(const DArgs& a, const void* wdown, int kt2, WDown& wd) {
@@ -540,9 +572,10 @@ __device__ __forceinline__ void df_prefetch_down(const DArgs& a, const void* wdo
   }
 }
 
-template <int SB>
-__device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag, const DPhase& ph, const void* wdown, u64* part2, uint32_t tag2,
+template <int SB, typename CLEAR>
+__device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag, const DPhase& ph, const void* wdown, const float* part, CLEAR clear,
                                              uint32_t* lds, uint32_t* sact, int* sdead, int slot) {
+  constexpr int C = df_sum_cols<SB>();
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -579,6 +612,10 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
       }
     }
     if ((rd * NU + blockIdx.x * 2) < ph.items) df_prefetch_down(a, wdown, kt2, wd);
+    if (rd == 0) {
+      df_loads_done();
+      clear();
+    }
     uint32_t dummy0, dummy1;
     bool ok = true;
     if (rd == 0) ok = stage_operand<SB, false>(a, ph.A, ph.K, ph.sq, KT, As, sqs, tid, 0xFFFFFFFFu, 0xFFFFFFFFu, dummy0, dummy1, ph.hint, ph.hint_tag, tag);
@@ -629,33 +666,31 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
       for (int i = 0; i < DF_DN; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd.b[i]), ah, acc[i], 0, 0, 0);
       const int nW = a.ffn >> 5;
       float* tr = (float*)(lds + DF_TR) + wave * (8 * DF_DN * 16);
-      const size_t row_words = (size_t)(a.d >> 5) * nW * 32;
-      const int nt_out = wave + 8 * (lane >> 3);                     // this lane's tile and columns 2 (lane % 8), + 1 of every row
-      u64* out = part2 + ((size_t)(nt_out >> 1) * nW + kt2) * 32 + (nt_out & 1) * 16 + 2 * (lane & 7);
+      const df_rsrc rp = df_make_rsrc(part);
+      const uint32_t row_bytes = (uint32_t)(ceil_div(a.d, C) * nW * df_part_pitch(C));
+      auto place = [&](int nt, int q) {                              // of columns 4 q .. 4 q + 3 of a tile
+        const int n = nt * 16 + 4 * q;
+        return (uint32_t)((n / C * nW + kt2) * df_part_pitch(C) + n % C * 4);
+      };
+      // half a wave stores a row: this lane's row of two, tile, and four columns of it
+      const int half = lane >> 5, ti = (lane & 31) >> 2, nt_out = wave + 8 * ti;
+      const bool stores = ti < DF_DN && nt_out < ntiles_d;
+      uint32_t at = place(nt_out, lane & 3) + (uint32_t)half * row_bytes;
       for (int r0 = 0; r0 < M; r0 += 8) {
         if ((c16 & 8) == r0 && c16 < M)
 #pragma unroll
           for (int i = 0; i < DF_DN; ++i) *(f32x4*)(tr + ((c16 & 7) * DF_DN + i) * 16 + 4 * g) = acc[i];
-        const float* from = tr + 2 * lane;
+        const float* from = tr + (half * DF_DN + ti) * 16 + 4 * (lane & 3);
         const int re = min(M, r0 + 8);
-        for (int r = r0; r < re; r += 2, from += 2 * DF_DN * 16, out += 2 * row_words) {
-          const float2 v = *(const float2*)from, v1 = *(const float2*)(from + DF_DN * 16);
-          if (lane < 8 * DF_DN && nt_out < ntiles_d) {
-            st_words2(out, __float_as_uint(v.x), __float_as_uint(v.y), tag2);
-            if (r + 1 < re) st_words2(out + row_words, __float_as_uint(v1.x), __float_as_uint(v1.y), tag2);
-          }
-        }
+        for (int r = r0; r < re; r += 2, from += 2 * DF_DN * 16, at += 2 * row_bytes)
+          if (stores && r + half < re) df_put_partial(rp, at, *(const f32x4*)from);
       }
       for (int nt = wave + 8 * DF_DN; nt < ntiles_d; nt += 8) {      // wider models: the remaining tiles, not prefetched
         const bf16x8 bv = __builtin_bit_cast(bf16x8, __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + lane));
         f32x4 x = f32x4{0, 0, 0, 0};
         x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, al, x, 0, 0, 0);
         x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, ah, x, 0, 0, 0);
-        if (c16 < M) {
-          u64* on = part2 + (size_t)c16 * row_words + ((size_t)(nt >> 1) * nW + kt2) * 32 + (nt & 1) * 16 + 4 * g;
-          st_words2(on, __float_as_uint(x[0]), __float_as_uint(x[1]), tag2);
-          st_words2<16>(on, __float_as_uint(x[2]), __float_as_uint(x[3]), tag2);
-        }
+        if (c16 < M) df_put_partial(rp, place(nt, g) + (uint32_t)c16 * row_bytes, x);
       }
     }
     if (rd == 0) DF_STAMP(slot + 1);
@@ -665,111 +700,160 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
 }
 
 // Sum of the ffn/32 down-projection partials, residual, and the operand / statistics of the next RMSNorm.  Task = (row, C
-// output columns) on a whole workgroup.  What bounds it is a compute unit's intake of the partials (32 columns are 39 KB, 1.5 us),
-// so few rows are cut finer: C = 8 where the launch has the workgroups (the instantiations for few words, one or two
-// rows of the 0.5B shape; one row: 3.0 -> 1.9 us from the end of the MLP to the sum), else 32.
-// The order of a sum does not depend on C: the partials form 64 blocks of consecutive ones, summed in ascending order, and the
-// blocks of a wave meet as a binary tree - in the thread, which holds C / 8 of them, and between the lanes -, the waves in ascending
+// output columns) on a whole workgroup.  Tasks go to the workgroups with MLP items first, one each.  Their first requests queue behind the
+// acknowledgement of their own stores, and then nearly always find everything there; a workgroup without an MLP item that polls meanwhile
+// delays those stores (five rows 1.2 us a layer more when such workgroups came first), so it watches one word of its last partial.
+// The last ones to get a task are those with QKV or attention items, which begin the next layer: C = 64 for six rows and more leaves
+// them without one up to 13 rows of the 0.5B shape, and gives none a second task (nine rows: 24.3 -> 20.7 us a layer, against C = 32).
+// With few rows what counts is the time to take in a task's partials: C = 8 for one or two (one row: 1.9 us from the end of the MLP to the sum;
+// with 16 columns 2.0, with 32 3.0), else 32.
+// Partials of 4 bytes without a tag instead of 8 with one, and 16-byte loads: from the MLP's end to the sum five rows 3.4 -> 2.2 us, nine 3.5 -> 2.4.
+// The order of a sum does not depend on C: the partials form 64 blocks of consecutive ones, summed in ascending order; eight
+// blocks meet as a binary tree - in the thread, which may hold two, and between the lanes -, and eight such groups in ascending
 // order in LDS.  So it is with the squares: a tree over columns whose nodes over 8 or 32 are published.
-// (With a task per 4-wave unit and 19 words per thread in flight the five-row forward took 30 us longer.)
 constexpr int DF_RBLOCKS = 64;
 constexpr int DF_RW = 3;                  // partials of a block in flight
+// After a failed first flight: until a partial is there (like df_wait_hint).
+__device__ __forceinline__ void df_wait_partial(const float* word, uint32_t* err) {
+  for (int i = 0; i < (1 << 14); ++i) {
+    if (__hip_atomic_load((const uint32_t*)word, __ATOMIC_RELAXED, AG) != 0u) return;
+    if ((i & 63) == 63 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0) return;
+    __builtin_amdgcn_s_sleep(DF_HINT_SLEEP);
+  }
+}
+// A thread's partials in a task: four columns of one block, or of two consecutive ones.  The lanes that share a column and eight
+// consecutive blocks differ in lane bits that the cheap lane exchanges reach in the order of the tree (df_sum_blocks).
 template <int C>
-__device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t tag, int layer, const u64* part2, uint32_t tag2, const u64* h_in,
+struct DfPartials {
+  static constexpr int TB = C == 64 ? 2 : 1;               // blocks
+  int group, cg;                                           // eight blocks; which four columns
+  int w[TB + 1];                                           // first partial of a block, and of the one after the last
+  __device__ __forceinline__ DfPartials(int tid, int nW) {
+    const int l = tid & 63;
+    group = tid >> (C == 8 ? 4 : 6);
+    cg = l & (C / 4 - 1);
+    const int blk = group * 8 + (C == 64 ? l >> 4 << 1 : C == 32 ? l >> 3 : (l >> 3 & 1) | (l >> 1 & 2) | (l << 1 & 4));
+#pragma unroll
+    for (int t = 0; t <= TB; ++t) w[t] = group < 8 ? (blk + t) * nW / DF_RBLOCKS : 0;
+  }
+  __device__ __forceinline__ uint32_t at(int task, int nW) const { return (uint32_t)((task * nW + w[0]) * df_part_pitch(C) + 16 * cg); }     // in bytes
+};
+template <int C>
+__device__ __forceinline__ float df_sum_blocks(float s) {
+  if (C == 64) return sum_over_groups(s);
+  s += dpp_f<0x128>(s);                                    // row_ror:8: that of lane ^ 8
+  if (C == 32) return sum_over_groups(s);
+  s += dpp_f<0x124>(s);                                    // row_ror:4: that of lane ^ 4 or ^ 12, which are the same now
+  return s + dpp_f<0x4E>(s);                               // quad_perm: lane ^ 2
+}
+template <int C>
+__device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t tag, int layer, const float* part, const u64* h_in,
                                                 u64* h_out, u64* hg_out, u64* sq_out, const float* gain_next, int shift,
                                                 uint32_t* lds, int* sdead, int slot) {
-  constexpr int TB = C / 8;                                // blocks of a thread
+  constexpr int TB = DfPartials<C>::TB, CS = C < 32 ? C : 32;        // columns of a sum of squares
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int NW = gridDim.x;
-  const int M = a.rows.M, d = a.d, np = d / C, nW = a.ffn >> 5;
-  const int tasks = M * np, rounds = (tasks + NW - 1) / NW;
-  const int witem = df_item_of_unit(blockIdx.x, shift >> 1, NW);     // a task has the whole workgroup
-  float* rs = (float*)(lds + DF_AW + DF_SQ_WORDS);                     // [8 waves][C]
-  const int c = tid % C, b0 = tid / C * TB;                // column, first block
+  const int d = a.d, np = ceil_div(d, C), nW = a.ffn >> 5, tasks = a.rows.M * np;
+  const int first = df_item_of_unit(blockIdx.x, shift >> 1, NW);       // a task has the whole workgroup
+  float* rs = (float*)(lds + DF_AW + DF_SQ_WORDS);                     // [8 groups of blocks][C]
+  const DfPartials<C> pt(tid, nW);
   const int bs = (nW + DF_RBLOCKS - 1) / DF_RBLOCKS;
+  const df_rsrc rp = df_make_rsrc(part);
   uint32_t* err = a.bar + 64;
   bool bad = false;
-  for (int rd = 0; rd < rounds; ++rd) {
-    const int task = rd * NW + witem;
-    const bool valid = task < tasks;
-    const int m = valid ? task / np : 0, p = valid ? task - m * np : 0;
-    int w0[TB], cnt[TB];                                   // first partial and partials of the blocks
+  for (int task = first; task < tasks; task += NW) {
+    const int m = task / np, col = C * (task - m * np) + tid;
+    const size_t o = (size_t)m * d + col;
+    const bool some = col - tid + 4 * pt.cg < d, want_h = tid < C && col < d;      // (of the last 64 columns the second half may not be there)
+    uint32_t at = pt.at(task, nW);
+    f32x4 s[TB];
 #pragma unroll
-    for (int t = 0; t < TB; ++t) {
-      w0[t] = (b0 + t) * nW / DF_RBLOCKS;
-      cnt[t] = valid ? (b0 + t + 1) * nW / DF_RBLOCKS - w0[t] : 0;
-    }
-    const u64* src = part2 + (size_t)(m * (d >> 5) + C * p / 32) * nW * 32 + C * p % 32 + c;
-    constexpr int wstride = 32;
-    float s[TB];
-#pragma unroll
-    for (int t = 0; t < TB; ++t) s[t] = 0.f;
+    for (int t = 0; t < TB; ++t) s[t] = f32x4{0, 0, 0, 0};
     u64 hw = (u64)tag << 32;
-    const bool want_h = valid && tid < C;
-    const float gain = want_h ? gain_next[C * p + c] : 0.f;
+    const float gain = want_h ? gain_next[col] : 0.f;
     for (int k0 = 0; k0 < bs; k0 += DF_RW) {
-      u64 v[TB][DF_RW];
+      u32x4 v[TB][DF_RW];
+      auto there = [&](int t, int i) { return some && pt.w[t] + k0 + i < pt.w[t + 1]; };
+      auto request = [&](int t, int i) { return __builtin_amdgcn_raw_buffer_load_b128(rp, (int)(at + (uint32_t)((pt.w[t] - pt.w[0] + k0 + i) * df_part_pitch(C))), 0, 16 /* sc1 */); };
+      auto missing = [](const u32x4 x) { return min(min(x[0], x[1]), min(x[2], x[3])) == 0u; };
 #pragma unroll
       for (int t = 0; t < TB; ++t)
 #pragma unroll
-        for (int i = 0; i < DF_RW; ++i) v[t][i] = (k0 + i < cnt[t]) ? ld_word(src + (w0[t] + k0 + i) * wstride) : ((u64)tag2 << 32);
-      if (k0 == 0 && want_h) hw = ld_word(h_in + (size_t)m * d + C * p + c);
-      long spins = 0;
-      for (;;) {
-        bool all = (uint32_t)(hw >> 32) == tag;
+        for (int i = 0; i < DF_RW; ++i) v[t][i] = there(t, i) ? request(t, i) : u32x4{1u, 1u, 1u, 1u};
+      if (k0 == 0 && want_h) hw = ld_word(h_in + o);
+      for (long spins = 0;;) {
+        bool late = (uint32_t)(hw >> 32) != tag;
 #pragma unroll
         for (int t = 0; t < TB; ++t)
 #pragma unroll
-          for (int i = 0; i < DF_RW; ++i) all = all && ((uint32_t)(v[t][i] >> 32) == tag2);
-        if (all) break;
-        // a workgroup that comes here from its own MLP item is not early: no hint for it
-        if (spins == 0 && (int)blockIdx.x >= a.g_mlp) df_wait_hint(a.hg + (size_t)(2 * layer + 1) * a.st_h, tag, err);
+          for (int i = 0; i < DF_RW; ++i) late = late || missing(v[t][i]);
+        if (!late) break;
+        // a workgroup that comes here from its own MLP item is not early; another one first watches a word of the last partial
+        if (spins == 0 && (int)blockIdx.x >= a.g_mlp) df_wait_partial(part + (size_t)((task + 1) * nW - 1) * (df_part_pitch(C) / 4), err);
         if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
           __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, AG);
           bad = true;
           break;
         }
         __builtin_amdgcn_s_sleep(1);
+        asm volatile("" : "+v"(at) : : "memory");          // (the words may have changed)
 #pragma unroll
         for (int t = 0; t < TB; ++t)
 #pragma unroll
           for (int i = 0; i < DF_RW; ++i)
-            if ((uint32_t)(v[t][i] >> 32) != tag2) v[t][i] = ld_word(src + (w0[t] + k0 + i) * wstride);
-        if ((uint32_t)(hw >> 32) != tag) hw = ld_word(h_in + (size_t)m * d + C * p + c);
+            if (missing(v[t][i])) v[t][i] = request(t, i);
+        if ((uint32_t)(hw >> 32) != tag) hw = ld_word(h_in + o);
       }
 #pragma unroll
       for (int t = 0; t < TB; ++t)
 #pragma unroll
         for (int i = 0; i < DF_RW; ++i)
-          if (k0 + i < cnt[t]) s[t] += __uint_as_float((uint32_t)v[t][i]);
+          if (there(t, i)) s[t] += __builtin_bit_cast(f32x4, v[t][i]);
     }
-    float sum = TB == 1 ? s[0] : (s[0] + s[1 % TB]) + (s[2 % TB] + s[3 % TB]);
+    f32x4 x = TB == 1 ? s[0] : s[0] + s[TB - 1];
 #pragma unroll
-    for (int o = C; o < WAVE; o <<= 1) sum += __shfl_xor(sum, o, WAVE);
-    if ((tid & 63) < C) rs[(tid >> 6) * C + c] = sum;
+    for (int i = 0; i < 4; ++i) x[i] = df_sum_blocks<C>(x[i]);
+    if (pt.group < 8 && (tid & (C == 8 ? 15 : 63)) < C / 4) *(f32x4*)(rs + pt.group * C + 4 * pt.cg) = x;
     if (bad) *sdead = 1;
-    __syncthreads();
+    // Besides this task's words: the zeros of the layer before have reached memory.  Nobody stores into their places before he has seen,
+    // by way of the next layers' phases, the sums that every workgroup publishes below.
     df_loads_done();
+    __syncthreads();
     if (*sdead) return true;
-    if (rd == 0) DF_STAMP(slot);
+    if (task == first) DF_STAMP(slot);
     if (want_h) {
       float r[8];
 #pragma unroll
-      for (int w = 0; w < 8; ++w) r[w] = rs[w * C + c];
+      for (int w = 0; w < 8; ++w) r[w] = rs[w * C + tid];
       const float v = (((((((r[0] + r[1]) + r[2]) + r[3]) + r[4]) + r[5]) + r[6]) + r[7]) + __uint_as_float((uint32_t)hw);
-      const size_t o = (size_t)m * d + C * p + c;
       st_wordf(h_out + o, v, tag);
       st_word(hg_out + o, split_payload(v * gain), tag);
       float q2 = v * v;
 #pragma unroll
-      for (int off = 1; off < C; off <<= 1) q2 += __shfl_xor(q2, off, 32);
-      if (c == 0) st_wordf(sq_out + (size_t)m * np + p, q2, tag);
+      for (int off = 1; off < CS; off <<= 1) q2 += __shfl_xor(q2, off, 32);
+      if ((tid & (CS - 1)) == 0) st_wordf(sq_out + (size_t)m * (d / CS) + col / CS, q2, tag);
     }
-    if (rd == 0) DF_STAMP(slot + 1);
+    if (task == first) DF_STAMP(slot + 1);
     __syncthreads();
   }
   return false;
+}
+
+// The partials that this workgroup has read in a layer become zeros again, in the next layer, when it has nothing better to do: behind its own QKV,
+// attention and output items, or when its MLP item's weights have come (right behind the sums these stores delayed the next operands).
+template <int C>
+__device__ __forceinline__ void df_clear_partials(const DArgs& a, const float* part, int shift) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int NW = gridDim.x, nW = a.ffn >> 5, tasks = a.rows.M * ceil_div(a.d, C);
+  const DfPartials<C> pt(tid, nW);
+  const df_rsrc rp = df_make_rsrc(part);
+  for (int task = df_item_of_unit(blockIdx.x, shift >> 1, NW); task < tasks; task += NW) {
+    const uint32_t at = pt.at(task, nW);
+    for (int k = pt.w[0]; k < pt.w[DfPartials<C>::TB]; ++k)
+      __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, rp, (int)(at + (uint32_t)((k - pt.w[0]) * df_part_pitch(C))), 0, 16 /* sc1 */);
+  }
 }
 
 // ------------------------------------------------------------------------------------------------ phase 0
@@ -1298,8 +1382,8 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
             n_lg = (((a.vocab + 15) >> 4) + 1) >> 1;
   const int st = a.small_stride;
   const int st_lg = 2 * n_lg <= NU ? 2 : 1;               // the head's items: a workgroup each where there are enough (a CU's intake bounds an item's weight stream)
-  const int s_qkv = (2 * a.g_mlp) % NU, s_att = (s_qkv + st * n_qkv) % NU, s_o = (s_att + 2 * n_att) % NU,
-            s_red = (s_o + st * n_o) % NU;
+  // (sums go to the first workgroups, which have MLP items; their own stores' acknowledgement comes just before there is something to sum)
+  const int s_att = NU - 2 * n_att, s_qkv = (s_att - st * n_qkv + NU) % NU, s_o = (s_qkv - st * n_o + NU) % NU, s_red = 0;
   auto make_qkv = [&](const DArgs& a, int l) {
     const PLayer Y = layer_ptrs(a, l);
     DPhase x = DPhase{};
@@ -1338,7 +1422,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
   };
   // which phase kinds this workgroup has a round-0 item in
   auto has = [&](int u, int shift, int items, int stride = 1) { return df_item_of_unit(u, shift, NU, stride) < items; };
-  const int n_red = a.rows.M * (a.d / df_red_cols<SB>());
+  const int n_red = a.rows.M * ceil_div(a.d, df_sum_cols<SB>());
   const int u0 = blockIdx.x * 2, u1 = u0 + 1;
   const bool g_q = has(u0, s_qkv, n_qkv, st) || has(u1, s_qkv, n_qkv, st) || st * n_qkv > NU,
              g_a = has(u0, s_att, n_att, 2),                  // (an attention item has the workgroup)
@@ -1364,7 +1448,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_fetch_or(a.bar + 64, DEV_ERR_TAGS, __ATOMIC_RELAXED, AG);
     return;
   }
-  df_embed_phase<df_red_cols<SB>()>(a, tag);
+  df_embed_phase<df_sq_cols<SB>()>(a, tag);
   if (g_q && threadIdx.x < a.rows.M) {                    // the QKV epilogue appends keys and values: block of each row's position
     u64 w = ld_word(a.rowblk + threadIdx.x);
     for (long spins = 0; (uint32_t)(w >> 32) != tag; w = ld_word(a.rowblk + threadIdx.x)) {
@@ -1396,24 +1480,37 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
       const DPhase cur = make_o(a, l);
       if (df_gemm_phase<PE_RESID, SB>(a, tag, cur, lds, srow, &sdead, s0 + 4)) return;
     }
-    if (g_g) {
+    auto clear = [&]() {
+      const DArgs& a = df_args();
+      if (g_r && l > 0) df_clear_partials<df_sum_cols<SB>()>(a, a.part + (size_t)((l - 1) & 1) * a.st_part, s_red);
+    };
+    if (!g_g) {
+      clear();
+    } else {
       const DArgs& a = df_args();
       const DPhase cur = make_swiglu(a, l);
-      u64* p2 = a.part2 + (size_t)(l & 1) * a.st_part2;
-      if (df_mlp_phase<SB>(a, tag, cur, layer_ptrs(a, l).wdown, p2, df_tag2(tag, l), lds, sact, &sdead, s0 + 6)) return;
+      if (df_mlp_phase<SB>(a, tag, cur, layer_ptrs(a, l).wdown, a.part + (size_t)(l & 1) * a.st_part, clear, lds, sact, &sdead, s0 + 6)) return;
+    }
+    if (g_q && g_r && l + 1 < L) {
+      const DArgs& a = df_args();
+      df_touch_weights(a, make_qkv(a, l + 1));
     }
     if (g_r) {
       const DArgs& a = df_args();
       const size_t hi = (size_t)(2 * l + 1);
       const float* gain_next = l + 1 < L ? layer_ptrs(a, l + 1).ln1 : a.final_norm;
-      if (df_reduce_phase<df_red_cols<SB>()>(a, tag, l, a.part2 + (size_t)(l & 1) * a.st_part2, df_tag2(tag, l), a.h + hi * a.st_h, a.h + (hi + 1) * a.st_h,
+      if (df_reduce_phase<df_sum_cols<SB>()>(a, tag, l, a.part + (size_t)(l & 1) * a.st_part, a.h + hi * a.st_h, a.h + (hi + 1) * a.st_h,
                           a.hg + (hi + 1) * a.st_h, a.sq + (hi + 1) * a.st_sq, gain_next, s_red, lds, &sdead, s0 + 8)) return;
     }
   }
   if (a.with_head && g_l) {
     const DArgs& a = df_args();
     const DPhase cur = make_head(a);
-    df_gemm_phase<PE_LOGITS, SB>(a, tag, cur, lds, srow, &sdead, 2 + L * 10);
+    if (df_gemm_phase<PE_LOGITS, SB>(a, tag, cur, lds, srow, &sdead, 2 + L * 10)) return;
+  }
+  if (g_r) {
+    const DArgs& a = df_args();
+    df_clear_partials<df_sum_cols<SB>()>(a, a.part + (size_t)((L - 1) & 1) * a.st_part, s_red);
   }
 }
 

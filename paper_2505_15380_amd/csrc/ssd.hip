@@ -310,7 +310,7 @@ struct ssd_kv {
   int persistent_wgs = 0;          // 0: the persistent kernel is not usable for this cache
   int cus = 0;                     // compute units of the device
   // tagged workspace of the barrier-free forward (see dataflow.h); null when that kernel is not usable
-  u64 *t_base = nullptr, *t_h, *t_hg, *t_sq, *t_q, *t_kvn, *t_attn, *t_att_p, *t_part2, *t_rowblk;
+  u64 *t_base = nullptr, *t_h, *t_hg, *t_sq, *t_q, *t_kvn, *t_attn, *t_att_p, *t_part, *t_rowblk;
   size_t t_words = 0, t_attp_at = 0;     // words of it; words ahead of the attention's partials (GEMM operands are among them)
   bool dataflow = false;
   bool attn_whole = false;   // ssd_kv_last_forward_path tells launches whose attention is one part (4) from others (3) on this cache
@@ -372,15 +372,15 @@ static size_t kv_layout(const ssd_model* m, int max_seqs, int max_rows, int n_bl
   const size_t w_h = (size_t)(2 * L + 1) * TR * c.d_model, w_sq = (size_t)(2 * L + 1) * TR * (c.d_model / 8);
   const size_t w_q = (size_t)L * TR * nqd, w_kvn = (size_t)L * TR * 2 * c.n_kv_heads * 64;
   const size_t w_attp = (size_t)L * TR * c.n_q_heads * NP * 96;
-  const size_t w_part2 = (size_t)2 * (c.d_ffn / 32) * TR * c.d_model;
-  const size_t t_words = w_h * 2 + w_sq + w_q * 2 + w_kvn + w_attp + w_part2 + 16;
+  const size_t w_part = (size_t)2 * (c.d_ffn / 32) * TR * c.d_model;     // (two buffers of fp32, at most twice the rows apart: df_part_pitch)
+  const size_t t_words = w_h * 2 + w_sq + w_q * 2 + w_kvn + w_attp + w_part + 16;
   u64* t_base = cv.take<u64>(t_words);
   if (kv) {
     u64* t = t_base;
     kv->t_base = t_base; kv->t_words = t_words;
     kv->t_h = t; t += w_h; kv->t_hg = t; t += w_h; kv->t_sq = t; t += w_sq; kv->t_q = t; t += w_q; kv->t_attn = t; t += w_q;
     kv->t_attp_at = w_h * 2 + w_sq + w_q * 2 + w_kvn;
-    kv->t_kvn = t; t += w_kvn; kv->t_att_p = t; t += w_attp; kv->t_part2 = t; t += w_part2;
+    kv->t_kvn = t; t += w_kvn; kv->t_att_p = t; t += w_attp; kv->t_part = t; t += w_part;
     kv->t_rowblk = t;
 
     kv->trace = trace;
@@ -936,7 +936,9 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   // with compute units to spare every item of the other small phases gets a workgroup of its own, as attention's always do (its
   // waves then do not share their SIMDs with a second item), else two items share one
   const int small_stride = g_mlp + n_att + n_other <= kv->cus ? 2 : 1;
-  const int G = std::min(kv->cus, g_mlp + n_att + cdiv(small_stride * n_other, 2));
+  // A launch that takes more than half of the compute units has no room for another one beside it, so it takes all: the workgroups without
+  // another item take sums, which those with an MLP item begin only when their stores are acknowledged, and of which a second round takes 2 us.
+  const int n_items = g_mlp + n_att + cdiv(small_stride * n_other, 2), G = 2 * n_items > kv->cus ? kv->cus : n_items;
   // limits: one round of attention (its workgroups wait for each other's parts), query rows of an item, LDS staging capacity
   const bool fits = M <= 16 && rows.R * grp <= DF_ATT_ROWS && n_att <= G && n_parts <= kv->NP &&
                     M * (c.d_model + 4) <= DF_AW && M * (nqd + 4) <= DF_AW && M * (c.d_model / 32) <= DF_SQ_WORDS &&
@@ -957,7 +959,7 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   a.st_h = PR * c.d_model; a.st_sq = PR * (c.d_model / 8); a.st_q = PR * nqd; a.st_kvn = PR * 2 * c.n_kv_heads * 64;
   a.st_att_p = PR * c.n_q_heads * kv->NP * 96;
   a.rowblk = kv->t_rowblk;
-  a.part2 = kv->t_part2; a.st_part2 = (size_t)(c.d_ffn / 32) * PR * c.d_model;
+  a.part = (float*)kv->t_part; a.st_part = (size_t)2 * (c.d_ffn / 32) * PR * c.d_model;
   a.NP = kv->NP; a.n_parts = n_parts; a.g_mlp = g_mlp; a.small_stride = small_stride;
   a.bar = kv->bar;
   a.trace = kv->trace_on ? kv->trace : nullptr;

@@ -401,6 +401,29 @@ def test_mini_bf16_operand_staging_flights(flight, K, monkeypatch):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("d,ffn", [(96, 64), (160, 6208), (64, 2048), (32, 2080)])
+def test_sums_of_down_projection_partials(d, ffn):
+    """The sums over the workgroups' partial results of the down projection, which are there when they are not zero and are put back to
+    zero: fewer partials than blocks of them (2), one per block (64), one more, and four of a block where three are in flight; the last 64 columns with
+    and without their second half.  Every third output column's partials are exact zeros.  Three layers use a buffer twice, and launches
+    of 1, 2, 5, 8, 9 and 16 rows, which have it in three layouts, follow each other on one cache."""
+    from tests.parity import Pair, loud_weights, verify_parity_step
+    shape = dict(n_layers=3, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=ffn, vocab=41, n_embed=43, dtype="bf16",
+                 qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
+    w = loud_weights(shape, 87)
+    for l in range(3):
+        w[f"l{l}.wdown"][::3] = 0.0
+    pair = Pair(None, 0, 128, max_rows=16, shape=shape, weights=w, store="bf16")
+    rng = np.random.default_rng(88)
+    pair.prefill(0, rng.integers(0, 43, 12))
+    for s, K in enumerate((0, 1, 4, 7, 8, 15, 0, 8, 4)):
+        verify_parity_step(pair, dict(beta=0.3, seed=89), K, s, rng, 2.0 ** -4, 2.0 ** -4)       # (as check_prompt's elements)
+        assert pair.kv.last_forward_path() in (3, 4), "the barrier-free persistent kernel did not run"
+        pair.check_rows(0, 2.0 ** -7)
+    pair.check_free_stack()
+
+
+@pytest.mark.gpu
 def test_barrier_and_barrier_free_kernels_agree(monkeypatch):
     """Same model, prefix and drafts through both persistent kernels: logits agree to rounding (they share the
     arithmetic definitions but not every summation order), decisions given equal probabilities are covered above."""
