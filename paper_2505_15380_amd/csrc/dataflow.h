@@ -4,31 +4,35 @@
 // -> output projection (+residual) -> MLP (gate/up + SwiGLU + down projection fused inside a workgroup) -> sum of the
 // MLP partials (+residual).  Weights are packed as matrix-core fragments; a unit of 4 waves takes an item.
 //
-// Dependent phases are ordered by the data itself: everything a workgroup hands to another workgroup is made of 8-byte
-// words {payload, tag}, where tag is the number of this launch.  Words are stored and loaded with agent-scope 64-bit accesses,
-// or, where two lie side by side (GEMM operands, attention rows and partials), with 16-byte accesses past the
-// same caches.  A consumer repeats the loads whose tag is not yet this launch's.  A word is observed whole, so a matching tag
-// proves its payload.  For a 64-bit access the memory model promises that.  That each aligned 8-byte half of a 16-byte access
-// is whole as well is a property of this hardware, where a lane's 16 bytes are one piece of one cache line in every request;
-// of the two halves together nothing is assumed, each has its tag.  No store has to be acknowledged
-// before a flag is raised, no counter is shared, and a dependency costs one store plus one load instead of the
-// chain of memory round trips of a barrier.  Every word is written exactly once per launch (each layer and phase
-// has its own buffers), and launches on one cache workspace are ordered by the stream, so a tag cannot be matched by an older value.
+// Dependent phases are ordered by the data itself: everything a workgroup hands to another workgroup is made of 4-byte words that are
+// zero while they are not there.  A value that is zero goes out as -0, as an operand with the upper half -0, or with a bit beside it:
+// the same value to whoever reads it.  Words are stored and loaded with agent-scope accesses, up to four with one instruction past the same caches; a
+// consumer repeats the loads that brought a zero.  A word is observed whole, so one that is not zero is the payload.  No
+// store has to be acknowledged before a flag is raised, no counter is shared, and a dependency costs one store plus one load instead of the
+// chain of memory round trips of a barrier.  (With a tag beside every word, a launch number to compare, nothing had to be zeroed, but
+// the bytes were twice as many, and they are what a hand-over waits for: per layer 5 rows 17.6 -> 16.3 us without them, 9 rows 20.7 -> 18.8, one
+// row 14.3 -> 13.8; in the partials of the MLP alone, 11 MB a layer with five rows, another 1.5 and 4.)
 //
-// The MLP's partials have no tags: there are ffn/32 of them per output, and with a tag beside every value their way to memory and back, 11 MB
-// a layer with five rows, was what their sums waited for.  A partial is four bytes, zero while it is not there (a zero result goes out as
-// -0, which adds the same), and the workgroup that has summed it puts the zero back.  Two buffers take the layers in turn.  The zeros of
-// layer l have reached memory before their workgroup publishes its sums of layer l + 1; an MLP item of layer l + 2 begins after operands
-// that depend on all of those; so no zero overtakes a partial, and a partial that is not zero is this layer's.  Every launch leaves the buffers
-// zero, unless a wait times out; then the workspace is cleared before the cache is used again.
+// Every word is written once per launch: each layer and phase has its own buffers.  There are two sets of them, which launches take in
+// turn; while it waits, a launch zeroes the rows that the last one left in the other set.  Launches on one cache workspace are ordered by the
+// stream, so a launch finds its set zero.  Which set is its own, and how many rows the other has, it reads from a word that the last launch left.
+// The MLP's partials, ffn/32 per output, are too many to wait for the next launch: the workgroup that has summed one puts the zero
+// back, and two buffers take the layers in turn.  The zeros of layer l have reached memory before their workgroup publishes its sums of layer
+// l + 1; an MLP item of layer l + 2 begins after operands that depend on all of those; so no zero overtakes a partial, and a partial
+// that is not zero is this layer's.  A launch whose wait times out leaves words behind; the workspace is cleared before the cache is used again.
+//
+// Two kinds of words are 8 bytes {payload, tag}, the tag being the launch's number: the attention's partial results, for which
+// the workspace has room by the longest context and which few launches use, and the blocks of the new keys.  They need no zeros.  For a 64-bit access
+// the memory model promises that a word is observed whole.  That each aligned 8-byte half of a 16-byte access is whole as well is a property
+// of this hardware, where a lane's 16 bytes are one piece of one cache line in every request.
 //
 // Payloads: a GEMM operand value x is hi | lo << 16 with hi = upper 16 bits of x and lo = bf16(x - hi) (the two
 // bf16 whose sum the matrix core consumes); residual rows, sums of squares and partial results are fp32 bits; new
 // keys / values are bf16 bits.
 //
-// A workgroup stages the operand rows it needs in LDS once (all its threads poll in parallel, a pair of words of each of SB / 2
-// rows in flight: the kernel is instantiated for SB = 2, 4, 10, 16, 18 and the host picks, up to 8 rows, the smallest that holds the
-// launch's rows in one flight, 18 for more) and feeds the matrix cores from LDS.  The weights of an item are requested at the entry of its phase, into
+// A workgroup stages the operand rows it needs in LDS once (all its threads poll in parallel, four words of each of 2, 4, 6, 8
+// or 10 rows in flight: the kernel is instantiated for SB = 2, 4, 10, 16, 18 and the host picks the smallest that holds the launch's rows in one
+// flight, 18 for more) and feeds the matrix cores from LDS.  The weights of an item are requested at the entry of its phase, into
 // registers, before that wait: workgroups arrive at a phase before its operands do, so the wait hides the HBM latency.
 // The phases with few items (QKV, attention, output projection) run on workgroups of their own, beyond those that
 // take the MLP items, so that no workgroup is late for the MLP, the phase every workgroup waits for.
@@ -36,7 +40,7 @@
 // single word of the PRECEDING phase's operands with long sleeps, and polls in earnest only from then on.
 //
 // Attention never reads this launch's new keys from the cache pool: the QKV phase stores them in the pool for
-// later launches and, tagged, in a side buffer; a wave whose 64-key chunk reaches the new positions patches its key
+// later launches and, as words, in a side buffer; a wave whose 64-key chunk reaches the new positions patches its key
 // fragments from that buffer at the same slots the pool would have supplied, and its values in LDS, through which that
 // chunk's go.  A row's bits do not depend on how many rows are verified together.
 //
@@ -85,13 +89,15 @@ struct DArgs {
   Rows rows;
   int pcap, n_seqs, tok_stride, with_head;
   const int32_t* tokens;
-  u64* tw;                // base of the tagged workspace; the members below point into it
-  u64* h;                 // [2L+1][PR][d]      fp32: residual stream entering layer l at 2l, after attention at 2l+1
-  u64* hg;                // [2L+1][PR][d]      operand: h times the gain of the RMSNorm that consumes it
-  u64* sq;                // [2L+1][PR][d/8]    fp32: sums of squares of h over 32 columns (after the MLP: over df_sq_cols columns)
-  u64* q;                 // [L][PR][nq*64]     operand: rotated queries
-  u64* kvn;               // [L][PR][2][nkv*64] bf16: this launch's keys (rotated) and values
-  u64* attn;              // [L][PR][nq*64]     operand: attention output
+  uint32_t* tw;           // base of the workspace; the members below, up to the parts, point into the first of its two sets
+  uint32_t* h;            // [2L+1][PR][d]      fp32: residual stream entering layer l at 2l, after attention at 2l+1
+  uint32_t* hg;           // [2L+1][PR][d]      operand: h times the gain of the RMSNorm that consumes it
+  uint32_t* sq;           // [2L+1][PR][d/8]    fp32: sums of squares of h over 32 columns (after the MLP: over df_sq_cols columns)
+  uint32_t* q;            // [L][PR][nq*64]     operand: rotated queries
+  uint32_t* kvn;          // [L][PR][2][nkv*64] bf16 (| 1 << 16): this launch's keys (rotated) and values
+  uint32_t* attn;         // [L][PR][nq*64]     operand: attention output
+  size_t st_set;          // words from one set to the other
+  u64* state;             // the last launch: its number, then (rows << 1 | set)
   u64* att_p;             // [L][PR][nq][NP][16][6] fp32: per part and 4-dim chunk: 4 weighted values, max, sum
   float* part;            // [2][row][d/C][ffn/32][C]: down-projection partials of one 32-column slice of the SwiGLU output each (buffer =
                           // layer parity; C = df_sum_cols, 8 take the room of 16).  What a sum task reads is contiguous: with a
@@ -107,12 +113,18 @@ struct DArgs {
   unsigned long long* trace;
 };
 
+// Tagged words.
 __device__ __forceinline__ u64 ld_word(const u64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, AG); }
 __device__ __forceinline__ void st_word(u64* p, uint32_t payload, uint32_t tag) {
   __hip_atomic_store(p, (u64)payload | ((u64)tag << 32), __ATOMIC_RELAXED, AG);
 }
 __device__ __forceinline__ void st_wordf(u64* p, float x, uint32_t tag) { st_word(p, __float_as_uint(x), tag); }
-// Two consecutive words (16-byte aligned) with one store: a word is still stored by one instruction, and each has its tag.  (The
+// Words without a tag, zero while they are not there, and the forms that are never zero.
+__device__ __forceinline__ uint32_t ld_val(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, AG); }
+__device__ __forceinline__ void st_val(uint32_t* p, uint32_t bits) { __hip_atomic_store(p, bits, __ATOMIC_RELAXED, AG); }
+__device__ __forceinline__ void st_val2(uint32_t* p, uint32_t x0, uint32_t x1) { __hip_atomic_store((u64*)p, (u64)x0 | ((u64)x1 << 32), __ATOMIC_RELAXED, AG); }     // (8-byte aligned)
+__device__ __forceinline__ uint32_t float_word(float x) { return __float_as_uint(x) ? __float_as_uint(x) : 0x80000000u; }
+// Two consecutive tagged words (16-byte aligned) with one store: a word is still stored by one instruction, and each has its tag.  (The
 // s_nop: store data of more than 8 bytes must not be overwritten by the next two vector instructions.)
 __device__ __forceinline__ void st_words2(u64* p, uint32_t x0, uint32_t x1, uint32_t tag) {
   const u32x4 a = {x0, tag, x1, tag};
@@ -122,15 +134,20 @@ __device__ __forceinline__ uint32_t split_payload(float x) {
   const uint32_t u = __float_as_uint(x), h = u & 0xFFFF0000u;
   return (h >> 16) | ((uint32_t)f_to_bf16(x - __uint_as_float(h)) << 16);
 }
+__device__ __forceinline__ uint32_t operand_word(float x) {
+  const uint32_t p = split_payload(x);
+  return p ? p : 0x8000u;
+}
+__device__ __forceinline__ bool df_any_zero(const u32x4 x) { return min(min(x[0], x[1]), min(x[2], x[3])) == 0u; }
 
 // A workgroup that arrives at a phase long before its operands would poll them the whole time, and the polls of all
 // such workgroups load the fabric that the producers' stores travel through.  After a first failed flight a wave
 // therefore watches one word of the operands of the PRECEDING phase (one hand-over earlier) with a single
 // address and long sleeps, and resumes the full polling when that word is there.  Purely a hint: bounded, and
 // nothing depends on what it saw.
-__device__ __forceinline__ void df_wait_hint(const u64* word, uint32_t tag, uint32_t* err) {
+__device__ __forceinline__ void df_wait_hint(const uint32_t* word, uint32_t* err) {
   for (int i = 0; i < (1 << 14); ++i) {
-    if ((uint32_t)(ld_word(word) >> 32) == tag) return;
+    if (ld_val(word) != 0u) return;
     if ((i & 63) == 63 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0) return;
     __builtin_amdgcn_s_sleep(DF_HINT_SLEEP);
   }
@@ -146,8 +163,7 @@ __device__ __forceinline__ u32x4 ld_words2(df_rsrc r, uint32_t off) { return __b
 // Loads the pairs of words at off(at, i) (bytes; ~0: none) until every tag is this launch's.  False on a timeout.  (Offsets are worked out again
 // from `at` for a repeated load instead of being kept in registers.)
 template <int N, typename OFF>
-__device__ __forceinline__ bool poll_pairs(df_rsrc r, uint32_t at, OFF off, uint32_t tag, u32x4 (&v)[N], uint32_t* err,
-                                           const u64* hint = nullptr, uint32_t hint_tag = 0u) {
+__device__ __forceinline__ bool poll_pairs(df_rsrc r, uint32_t at, OFF off, uint32_t tag, u32x4 (&v)[N], uint32_t* err) {
 #pragma unroll
   for (int i = 0; i < N; ++i) v[i] = off(at, i) != 0xFFFFFFFFu ? ld_words2(r, off(at, i)) : u32x4{0u, tag, 0u, tag};
   long spins = 0;
@@ -156,7 +172,6 @@ __device__ __forceinline__ bool poll_pairs(df_rsrc r, uint32_t at, OFF off, uint
 #pragma unroll
     for (int i = 0; i < N; ++i) all = all && v[i][1] == tag && v[i][3] == tag;
     if (all) return true;
-    if (spins == 0 && hint) df_wait_hint(hint, hint_tag, err);
     if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
       __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, AG);
       return false;
@@ -169,31 +184,53 @@ __device__ __forceinline__ bool poll_pairs(df_rsrc r, uint32_t at, OFF off, uint
   }
 }
 
+// Loads four untagged words each at off(at, i) until all are there.  False on a timeout.
+template <int N, typename OFF>
+__device__ __forceinline__ bool poll_quads(df_rsrc r, uint32_t at, OFF off, u32x4 (&v)[N], uint32_t* err, const uint32_t* hint) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = off(at, i) != 0xFFFFFFFFu ? ld_words2(r, off(at, i)) : u32x4{1u, 1u, 1u, 1u};
+  for (long spins = 0;;) {
+    bool late = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) late = late || df_any_zero(v[i]);
+    if (!late) return true;
+    if (spins == 0) df_wait_hint(hint, err);
+    if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
+      __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, AG);
+      return false;
+    }
+    __builtin_amdgcn_s_sleep(1);
+    asm volatile("" : "+v"(at) : : "memory");              // (the words may have changed)
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (df_any_zero(v[i])) v[i] = ld_words2(r, off(at, i));
+  }
+}
+
 // Columns of a task of df_reduce_phase, and of a sum of squares that it publishes.
 template <int SB>
-constexpr int df_sum_cols() { return SB <= 4 ? 8 : SB <= 10 ? 32 : 64; }
+constexpr int df_sum_cols() { return SB == 2 ? 8 : SB <= 10 ? 32 : 64; }
 template <int SB>
-constexpr int df_sq_cols() { return SB <= 4 ? 8 : 32; }
+constexpr int df_sq_cols() { return SB == 2 ? 8 : 32; }
 
 // ------------------------------------------------------------------------------------------------ GEMM phases
 struct DPhase {
-  const u64* A;           // operand rows [PR][K]
-  const u64* sq;          // [PR][K/32] sums of squares of the un-gained rows (nullptr: no RMSNorm)
+  const uint32_t* A;           // operand rows [PR][K]
+  const uint32_t* sq;          // [PR][K/32] sums of squares of the un-gained rows (nullptr: no RMSNorm)
   const void* W0;
   const void* W1;
   int N, K, gs, items;    // gs: k-splits, always 1 here (the field the shared k-range helper reads)
   int shift, stride;      // item i of round 0 runs on unit (shift + stride * i) % units
-  const u64* hint;        // a word of the preceding phase's operands (see df_wait_hint), or null
-  uint32_t hint_tag;
+  const uint32_t* hint;        // a word of the preceding phase's operands (see df_wait_hint), or null
   int layer;
   const float* bias;
-  const u64* h_in;        // PE_RESID: residual input and outputs
-  u64* h_out;
-  u64* hg_out;
-  u64* sq_out;
+  const uint32_t* h_in;        // PE_RESID: residual input and outputs
+  uint32_t* h_out;
+  uint32_t* hg_out;
+  uint32_t* sq_out;
   const float* gain_next;
-  u64* out;               // PE_QKV: q
-  u64* kvn;               // PE_QKV: side buffer of the new keys / values
+  uint32_t* out;               // PE_QKV: q
+  uint32_t* kvn;               // PE_QKV: side buffer of the new keys / values
   float* logits;          // PE_LOGITS
 };
 
@@ -206,27 +243,27 @@ __device__ __forceinline__ void df_loads_done() { __builtin_amdgcn_s_waitcnt(0x0
 // Operand words of rows [0, M) (K words each, the rows contiguous) -> As, and the rows' sums of squares [M][nsq] -> sqs.  In As a
 // row has K + 4 words: of every eight consecutive k the hi halves (four words), then the lo halves, as the matrix core takes them.  (With the words
 // as they come a lane read both halves of its operand and picked one: twice the LDS reads, which took 900 cycles of a phase, and eight
-// permutations a k-tile.)  The whole workgroup polls in parallel, a pair of words per load.  What bounds it are a thread's instructions per pair,
-// so a thread has the same columns of every row: a row's place is then one scalar offset for the load and one sum for the LDS
-// write, and rows that are not there are skipped by scalar branches.  Of eight waves an eighth idles at 896 columns.  (With the pairs
-// dealt out over all threads as they lie, each pair has a row to find and a limit to keep: five rows 0.8 us a layer more, nine rows
-// 1.6, one row 0.2.)  Lanes without a pair are masked out: a load costs the cycles of its return path even where all its lanes are out of
+// permutations a k-tile.)  The whole workgroup polls in parallel, four words per load, a row per half of it.  What bounds it are a thread's
+// instructions and the bytes, so a thread has the same columns of every second row: a row's place is then one scalar offset for the load and one
+// sum for the LDS write, and rows that are not there are skipped by scalar branches.  Of eight waves an eighth idles at 896 columns.  (With the
+// words dealt out over all threads as they lie, each request has a row to find and a limit to keep: five rows 0.8 us a layer more, nine rows
+// 1.6, one row 0.2.)  Lanes without words are masked out: a load costs the cycles of its return path even where all its lanes are out of
 // range (five rows 513 -> 543 us with such loads instead of the mask).  A thread's first sum of squares rides in the flight, and so do, RES, two
-// more words (x0, x1: offsets in words, or ~0) that come back in xo0, xo1; whatever is late is asked for again together, so that
+// more words (x0, x1, or null) that come back in xo0, xo1; whatever is late is asked for again together, so that
 // nothing costs a round trip of its own after the operands.  (Watching a word per producer first, and requesting the
 // operands once all of them are there, saves polls but adds that round trip: 0.8 us a layer more with one row, 0.9 with five or nine.)
 template <int SB, bool RES>
-__device__ __forceinline__ bool stage_operand(const DArgs& a, const u64* A, int K, const u64* sq, int nsq, uint32_t* As, float* sqs, int tid,
-                                              uint32_t x0, uint32_t x1, uint32_t& xo0, uint32_t& xo1, const u64* hint, uint32_t hint_tag,
-                                              const uint32_t tag) {
-  constexpr int SP = SB / 2;                               // rows in flight
+__device__ __forceinline__ bool stage_operand(const DArgs& a, const uint32_t* A, int K, const uint32_t* sq, int nsq, uint32_t* As, float* sqs, int tid,
+                                              const uint32_t* x0, const uint32_t* x1, float& xo0, float& xo1, const uint32_t* hint) {
+  constexpr int SP = SB == 4 ? 2 : (SB + 3) / 4;           // rows in flight of each half of the workgroup
   const int M = a.rows.M, nS = sq ? M * nsq : 0;
   const df_rsrc rs = df_make_rsrc(a.tw);
-  const uint32_t a_off = (uint32_t)(A - a.tw) * 8u;
+  const uint32_t a_off = (uint32_t)(A - a.tw) * 4u;
+  const int half = __builtin_amdgcn_readfirstlane(tid >> 8), c = tid & 255;
   uint32_t* err = a.bar + 64;
   bool ok = true;
   auto give_up = [&](long& spins) -> bool {
-    if (spins == 0 && hint) df_wait_hint(hint, hint_tag, err);         // far too early: wait cheaply for the phase before
+    if (spins == 0 && hint) df_wait_hint(hint, err);                   // far too early: wait cheaply for the phase before
     if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
       __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, AG);
       ok = false;
@@ -235,55 +272,58 @@ __device__ __forceinline__ bool stage_operand(const DArgs& a, const u64* A, int 
     __builtin_amdgcn_s_sleep(1);
     return false;
   };
-  u64 w = (u64)tag << 32, h0 = w, h1 = w;
-  if (!RES && tid < nS) w = ld_word(sq + tid);
-  if (RES && x0 != 0xFFFFFFFFu) h0 = ld_word(a.tw + x0);
-  if (RES && x1 != 0xFFFFFFFFu) h1 = ld_word(a.tw + x1);
-  for (int c0 = 0; c0 < K >> 1; c0 += PBLOCK)
-    for (int r0 = 0; r0 < M; r0 += SP) {
-      const bool on = c0 + tid < K >> 1;
-      uint32_t at = (uint32_t)(c0 + tid) * 16u;
+  uint32_t w = 1u, h0 = 1u, h1 = 1u;
+  if (!RES && tid < nS) w = ld_val(sq + tid);
+  if (RES && x0) {
+    h0 = ld_val(x0);
+    h1 = ld_val(x1);
+  }
+  for (int c0 = 0; c0 < K >> 2; c0 += 256)
+    for (int r0 = 0; r0 < M; r0 += 2 * SP) {
+      const bool on = c0 + c < K >> 2;
+      uint32_t at = (uint32_t)(c0 + c) * 16u;
+      auto row = [&](int u) { return r0 + 2 * u + half; };
       auto request = [&](int u) -> u32x4 {
-        return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)at, (int)(a_off + (uint32_t)((r0 + u) * K) * 8u), 16 /* sc1 */);
+        return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)at, (int)(a_off + (uint32_t)(row(u) * K) * 4u), 16 /* sc1 */);
       };
       u32x4 v[SP];
 #pragma unroll
-      for (int u = 0; u < SP; ++u) v[u] = on && r0 + u < M ? request(u) : u32x4{0u, tag, 0u, tag};
+      for (int u = 0; u < SP; ++u) v[u] = on && row(u) < M ? request(u) : u32x4{1u, 1u, 1u, 1u};
       for (long spins = 0;;) {
-        uint32_t late = RES ? ((uint32_t)(h0 >> 32) ^ tag) | ((uint32_t)(h1 >> 32) ^ tag) : (uint32_t)(w >> 32) ^ tag;
+        bool late = RES ? min(h0, h1) == 0u : w == 0u;
 #pragma unroll
-        for (int u = 0; u < SP; ++u) late |= (v[u][1] ^ tag) | (v[u][3] ^ tag);
-        if (late == 0u || give_up(spins)) break;
+        for (int u = 0; u < SP; ++u) late = late || df_any_zero(v[u]);
+        if (!late || give_up(spins)) break;
         asm volatile("" : "+v"(at) : : "memory");          // (the words may have changed)
 #pragma unroll
         for (int u = 0; u < SP; ++u)
-          if (v[u][1] != tag || v[u][3] != tag) v[u] = request(u);
-        if (!RES && (uint32_t)(w >> 32) != tag) w = ld_word(sq + tid);
-        if (RES && (uint32_t)(h0 >> 32) != tag) h0 = ld_word(a.tw + x0);
-        if (RES && (uint32_t)(h1 >> 32) != tag) h1 = ld_word(a.tw + x1);
+          if (df_any_zero(v[u])) v[u] = request(u);
+        if (!RES && w == 0u) w = ld_val(sq + tid);
+        if (RES && h0 == 0u) h0 = ld_val(x0);
+        if (RES && h1 == 0u) h1 = ld_val(x1);
       }
       df_loads_done();
       if (on) {
-        uint32_t* to = As + r0 * (K + 4) + 2 * (c0 + tid) - (tid & 3);
+        uint32_t* to = As + (r0 + half) * (K + 4) + 4 * (c0 + c) - 2 * (c & 1);
 #pragma unroll
         for (int u = 0; u < SP; ++u)
-          if (r0 + u < M) {
-            to[u * (K + 4)] = __builtin_amdgcn_perm(v[u][2], v[u][0], 0x05040100u);
-            to[u * (K + 4) + 4] = __builtin_amdgcn_perm(v[u][2], v[u][0], 0x07060302u);
+          if (row(u) < M) {
+            *(uint2*)(to + 2 * u * (K + 4)) = make_uint2(__builtin_amdgcn_perm(v[u][1], v[u][0], 0x05040100u), __builtin_amdgcn_perm(v[u][3], v[u][2], 0x05040100u));
+            *(uint2*)(to + 2 * u * (K + 4) + 4) = make_uint2(__builtin_amdgcn_perm(v[u][1], v[u][0], 0x07060302u), __builtin_amdgcn_perm(v[u][3], v[u][2], 0x07060302u));
           }
       }
     }
   if (!RES) {
-    if (tid < nS) sqs[tid] = __uint_as_float((uint32_t)w);
+    if (tid < nS) sqs[tid] = __uint_as_float(w);
     for (int i = PBLOCK + tid; i < nS; i += PBLOCK) {      // (more than 512 sums)
-      w = ld_word(sq + i);
-      for (long spins = 0; (uint32_t)(w >> 32) != tag && !give_up(spins);) w = ld_word(sq + i);
-      sqs[i] = __uint_as_float((uint32_t)w);
+      w = ld_val(sq + i);
+      for (long spins = 0; w == 0u && !give_up(spins);) w = ld_val(sq + i);
+      sqs[i] = __uint_as_float(w);
     }
   }
   if (RES) {
-    xo0 = (uint32_t)h0;
-    xo1 = (uint32_t)h1;
+    xo0 = __uint_as_float(h0);
+    xo1 = __uint_as_float(h1);
   }
   return ok;
 }
@@ -430,14 +470,11 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
     if (EPI == PE_RESID && live) { gn0 = ph.gain_next[n0]; gn1 = ph.gain_next[n1]; }
     // ---- operands (both units of the workgroup consume the same rows); the unit that finishes residual rows takes
     //      its residual inputs in the same flight
-    uint32_t hx0 = 0xFFFFFFFFu, hx1 = 0xFFFFFFFFu, hv0 = 0u, hv1 = 0u;
-    if (EPI == PE_RESID && live) {
-      const uint32_t h_off = (uint32_t)(ph.h_in - a.tw) + (uint32_t)(row * ph.N);
-      hx0 = h_off + n0;
-      hx1 = h_off + n1;
-    }
+    const bool res = EPI == PE_RESID && live;
+    const uint32_t *hx0 = res ? ph.h_in + (size_t)row * ph.N + n0 : nullptr, *hx1 = res ? ph.h_in + (size_t)row * ph.N + n1 : nullptr;
+    float hv0 = 0.f, hv1 = 0.f;
     bool ok = true;
-    if (rd == 0) ok = stage_operand<SB, EPI == PE_RESID>(a, ph.A, ph.K, ph.sq, ph.K / df_sq_cols<SB>(), As, sqs, tid, hx0, hx1, hv0, hv1, ph.hint, ph.hint_tag, tag);
+    if (rd == 0) ok = stage_operand<SB, EPI == PE_RESID>(a, ph.A, ph.K, ph.sq, ph.K / df_sq_cols<SB>(), As, sqs, tid, hx0, hx1, hv0, hv1, ph.hint);
     if (!ok) *sdead = 1;
     __syncthreads();
     df_loads_done();
@@ -480,16 +517,16 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
           v0 = r0; v1 = r1;
         }
         if (head < a.nq) {
-          u64* qo = ph.out + (size_t)row * (a.nq * 64) + head * 64 + dd;
-          st_word(qo, split_payload(v0), tag);
-          st_word(qo + 32, split_payload(v1), tag);
+          uint32_t* qo = ph.out + (size_t)row * (a.nq * 64) + head * 64 + dd;
+          st_val(qo, operand_word(v0));
+          st_val(qo + 32, operand_word(v1));
         } else {
           const int which = head < a.nq + a.nkv ? 0 : 1;
           const int kvh = head - a.nq - which * a.nkv;
           const bf16_t b0 = f_to_bf16(v0), b1 = f_to_bf16(v1);
-          u64* ko = ph.kvn + ((size_t)row * 2 + which) * (a.nkv * 64) + kvh * 64 + dd;
-          st_word(ko, b0, tag);
-          st_word(ko + 32, b1, tag);
+          uint32_t* ko = ph.kvn + ((size_t)row * 2 + which) * (a.nkv * 64) + kvh * 64 + dd;
+          st_val(ko, b0 | 0x10000u);
+          st_val(ko + 32, b1 | 0x10000u);
           if (active && rblk >= 0) {
             bf16_t* base = (bf16_t*)a.kv.pool + kv_offset(a.kv, ph.layer, which, rblk, kvh, 0);
             const int tok = pos & 15;
@@ -508,16 +545,16 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
         const int pair = t0 >> 1;
         float q2 = 0.f;
         if (row < M) {
-          v0 += __uint_as_float(hv0);
-          v1 += __uint_as_float(hv1);
-          st_wordf(ph.h_out + (size_t)row * ph.N + n0, v0, tag);
-          st_wordf(ph.h_out + (size_t)row * ph.N + n1, v1, tag);
-          st_word(ph.hg_out + (size_t)row * ph.N + n0, split_payload(v0 * gn0), tag);
-          st_word(ph.hg_out + (size_t)row * ph.N + n1, split_payload(v1 * gn1), tag);
+          v0 += hv0;
+          v1 += hv1;
+          st_val(ph.h_out + (size_t)row * ph.N + n0, float_word(v0));
+          st_val(ph.h_out + (size_t)row * ph.N + n1, float_word(v1));
+          st_val(ph.hg_out + (size_t)row * ph.N + n0, operand_word(v0 * gn0));
+          st_val(ph.hg_out + (size_t)row * ph.N + n1, operand_word(v1 * gn1));
           q2 = v0 * v0 + v1 * v1;
         }
         q2 = row16_sum(q2);
-        if (col == 0 && row < M) st_wordf(ph.sq_out + (size_t)row * (ph.N >> 5) + pair, q2, tag);
+        if (col == 0 && row < M) st_val(ph.sq_out + (size_t)row * (ph.N >> 5) + pair, float_word(q2));
       }
     }
     if (rd == 0) DF_STAMP(slot + 1);
@@ -616,9 +653,9 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
       df_loads_done();
       clear();
     }
-    uint32_t dummy0, dummy1;
+    float dummy0, dummy1;
     bool ok = true;
-    if (rd == 0) ok = stage_operand<SB, false>(a, ph.A, ph.K, ph.sq, KT, As, sqs, tid, 0xFFFFFFFFu, 0xFFFFFFFFu, dummy0, dummy1, ph.hint, ph.hint_tag, tag);
+    if (rd == 0) ok = stage_operand<SB, false>(a, ph.A, ph.K, ph.sq, KT, As, sqs, tid, nullptr, nullptr, dummy0, dummy1, ph.hint);
     if (!ok) *sdead = 1;
     __syncthreads();
     df_loads_done();
@@ -713,14 +750,6 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
 // order in LDS.  So it is with the squares: a tree over columns whose nodes over 8 or 32 are published.
 constexpr int DF_RBLOCKS = 64;
 constexpr int DF_RW = 3;                  // partials of a block in flight
-// After a failed first flight: until a partial is there (like df_wait_hint).
-__device__ __forceinline__ void df_wait_partial(const float* word, uint32_t* err) {
-  for (int i = 0; i < (1 << 14); ++i) {
-    if (__hip_atomic_load((const uint32_t*)word, __ATOMIC_RELAXED, AG) != 0u) return;
-    if ((i & 63) == 63 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0) return;
-    __builtin_amdgcn_s_sleep(DF_HINT_SLEEP);
-  }
-}
 // A thread's partials in a task: four columns of one block, or of two consecutive ones.  The lanes that share a column and eight
 // consecutive blocks differ in lane bits that the cheap lane exchanges reach in the order of the tree (df_sum_blocks).
 template <int C>
@@ -747,8 +776,8 @@ __device__ __forceinline__ float df_sum_blocks(float s) {
   return s + dpp_f<0x4E>(s);                               // quad_perm: lane ^ 2
 }
 template <int C>
-__device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t tag, int layer, const float* part, const u64* h_in,
-                                                u64* h_out, u64* hg_out, u64* sq_out, const float* gain_next, int shift,
+__device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t tag, int layer, const float* part, const uint32_t* h_in,
+                                                uint32_t* h_out, uint32_t* hg_out, uint32_t* sq_out, const float* gain_next, int shift,
                                                 uint32_t* lds, int* sdead, int slot) {
   constexpr int TB = DfPartials<C>::TB, CS = C < 32 ? C : 32;        // columns of a sum of squares
   int tid = threadIdx.x;
@@ -770,27 +799,26 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t t
     f32x4 s[TB];
 #pragma unroll
     for (int t = 0; t < TB; ++t) s[t] = f32x4{0, 0, 0, 0};
-    u64 hw = (u64)tag << 32;
+    uint32_t hw = 1u;
     const float gain = want_h ? gain_next[col] : 0.f;
     for (int k0 = 0; k0 < bs; k0 += DF_RW) {
       u32x4 v[TB][DF_RW];
       auto there = [&](int t, int i) { return some && pt.w[t] + k0 + i < pt.w[t + 1]; };
       auto request = [&](int t, int i) { return __builtin_amdgcn_raw_buffer_load_b128(rp, (int)(at + (uint32_t)((pt.w[t] - pt.w[0] + k0 + i) * df_part_pitch(C))), 0, 16 /* sc1 */); };
-      auto missing = [](const u32x4 x) { return min(min(x[0], x[1]), min(x[2], x[3])) == 0u; };
 #pragma unroll
       for (int t = 0; t < TB; ++t)
 #pragma unroll
         for (int i = 0; i < DF_RW; ++i) v[t][i] = there(t, i) ? request(t, i) : u32x4{1u, 1u, 1u, 1u};
-      if (k0 == 0 && want_h) hw = ld_word(h_in + o);
+      if (k0 == 0 && want_h) hw = ld_val(h_in + o);
       for (long spins = 0;;) {
-        bool late = (uint32_t)(hw >> 32) != tag;
+        bool late = hw == 0u;
 #pragma unroll
         for (int t = 0; t < TB; ++t)
 #pragma unroll
-          for (int i = 0; i < DF_RW; ++i) late = late || missing(v[t][i]);
+          for (int i = 0; i < DF_RW; ++i) late = late || df_any_zero(v[t][i]);
         if (!late) break;
         // a workgroup that comes here from its own MLP item is not early; another one first watches a word of the last partial
-        if (spins == 0 && (int)blockIdx.x >= a.g_mlp) df_wait_partial(part + (size_t)((task + 1) * nW - 1) * (df_part_pitch(C) / 4), err);
+        if (spins == 0 && (int)blockIdx.x >= a.g_mlp) df_wait_hint((const uint32_t*)part + (size_t)((task + 1) * nW - 1) * (df_part_pitch(C) / 4), err);
         if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
           __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, AG);
           bad = true;
@@ -802,8 +830,8 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t t
         for (int t = 0; t < TB; ++t)
 #pragma unroll
           for (int i = 0; i < DF_RW; ++i)
-            if (missing(v[t][i])) v[t][i] = request(t, i);
-        if ((uint32_t)(hw >> 32) != tag) hw = ld_word(h_in + o);
+            if (df_any_zero(v[t][i])) v[t][i] = request(t, i);
+        if (hw == 0u) hw = ld_val(h_in + o);
       }
 #pragma unroll
       for (int t = 0; t < TB; ++t)
@@ -826,13 +854,13 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t t
       float r[8];
 #pragma unroll
       for (int w = 0; w < 8; ++w) r[w] = rs[w * C + tid];
-      const float v = (((((((r[0] + r[1]) + r[2]) + r[3]) + r[4]) + r[5]) + r[6]) + r[7]) + __uint_as_float((uint32_t)hw);
-      st_wordf(h_out + o, v, tag);
-      st_word(hg_out + o, split_payload(v * gain), tag);
+      const float v = (((((((r[0] + r[1]) + r[2]) + r[3]) + r[4]) + r[5]) + r[6]) + r[7]) + __uint_as_float(hw);
+      st_val(h_out + o, float_word(v));
+      st_val(hg_out + o, operand_word(v * gain));
       float q2 = v * v;
 #pragma unroll
       for (int off = 1; off < CS; off <<= 1) q2 += __shfl_xor(q2, off, 32);
-      if ((tid & (CS - 1)) == 0) st_wordf(sq_out + (size_t)m * (d / CS) + col / CS, q2, tag);
+      if ((tid & (CS - 1)) == 0) st_val(sq_out + (size_t)m * (d / CS) + col / CS, float_word(q2));
     }
     if (task == first) DF_STAMP(slot + 1);
     __syncthreads();
@@ -856,10 +884,33 @@ __device__ __forceinline__ void df_clear_partials(const DArgs& a, const float* p
   }
 }
 
+// The words of a layer that the launch before left in its set become zeros: by the workgroups with MLP items, while they wait.
+__device__ __forceinline__ void df_clear_layer(const DArgs& a, const size_t set, int rows, int l) {
+  if (rows == 0) return;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  int wg = blockIdx.x;                                     // the words of one kind begin where those of another end
+  auto zero = [&](uint32_t* p, int words) {
+    const int n = min((words + 2047) >> 11, a.g_mlp);      // workgroups
+    const df_rsrc r = df_make_rsrc(p);
+    for (int i = (wg * PBLOCK + tid) * 4; i < words; i += a.g_mlp * PBLOCK * 4) __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, r, i * 4, 0, 16 /* sc1 */);
+    wg -= n;
+    if (wg < 0) wg += a.g_mlp;
+  };
+  for (int hi = l ? 2 * l + 1 : 0; hi <= 2 * l + 2; ++hi) {
+    zero(a.h + set + (size_t)hi * a.st_h, rows * a.d);
+    zero(a.hg + set + (size_t)hi * a.st_h, rows * a.d);
+    zero(a.sq + set + (size_t)hi * a.st_sq, rows * (a.d >> 3));
+  }
+  zero(a.q + set + (size_t)l * a.st_q, rows * a.nq * 64);
+  zero(a.attn + set + (size_t)l * a.st_q, rows * a.nq * 64);
+  zero(a.kvn + set + (size_t)l * a.st_kvn, rows * a.nkv * 128);
+}
+
 // ------------------------------------------------------------------------------------------------ phase 0
 // Rows and embedding.  Item = row.
 template <int C>
-__device__ __forceinline__ void df_embed_phase(const DArgs& a, const uint32_t tag) {
+__device__ __forceinline__ void df_embed_phase(const DArgs& a, const size_t set) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), usel = wave >> 2, ut = tid & 255;
   const int unit = blockIdx.x * 2 + usel, NU = gridDim.x * 2;
   const int M = a.rows.M, R = a.rows.R, d = a.d;
@@ -886,12 +937,12 @@ __device__ __forceinline__ void df_embed_phase(const DArgs& a, const uint32_t ta
     for (int p = ut >> 5; p < (d >> 5); p += 8) {
       const int c = p * 32 + (ut & 31);
       const float v = bf16_to_f(src[c]);
-      st_wordf(a.h + (size_t)m * d + c, v, tag);
-      st_word(a.hg + (size_t)m * d + c, split_payload(v * gain[c]), tag);
+      st_val(a.h + set + (size_t)m * d + c, float_word(v));
+      st_val(a.hg + set + (size_t)m * d + c, operand_word(v * gain[c]));
       float sq = v * v;
 #pragma unroll
       for (int o = 1; o < C; o <<= 1) sq += __shfl_xor(sq, o, WAVE);       // as df_reduce_phase leaves them
-      if ((ut & (C - 1)) == 0) st_wordf(a.sq + (size_t)m * (d / C) + c / C, sq, tag);
+      if ((ut & (C - 1)) == 0) st_val(a.sq + set + (size_t)m * (d / C) + c / C, float_word(sq));
     }
   }
 }
@@ -983,7 +1034,7 @@ struct DAttItem {
 // not change during the launch, and the block ids of positions below the cached length do not either.  A block all of
 // whose positions are at or beyond the cached length may be reserved concurrently by this launch: whatever id is read
 // for it is only checked to be inside the pool, since each of its positions is either a row of this launch (taken from
-// the tagged side buffer, never from the pool) or masked.
+// the side buffer, never from the pool) or masked.
 __device__ __forceinline__ DAttItem df_att_item(const DArgs& a, int item, int ntile, int* sblk) {
   DAttItem it;
   it.valid = item < a.n_seqs * a.nkv * a.n_parts * ntile;
@@ -1169,7 +1220,7 @@ __device__ __forceinline__ void df_merge_row(const float* MO, const float* ML, i
 }
 
 template <int SB>
-__device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag, int layer, const DAttItem& it, uint32_t* lds, const int* sblk,
+__device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag, const size_t set, int layer, const DAttItem& it, uint32_t* lds, const int* sblk,
                                               const int* srow, int* sdead, int slot) {
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
@@ -1203,9 +1254,9 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   const int R = a.rows.R, G = a.nq / a.nkv, nqd = a.nq * 64, RG = R * G;
   const int r0 = 16 * it.rt, nrt = min(16, RG - r0);                         // first query row and rows of this tile
   const bool unew = (it.c0 + it.nch) * 64 > it.len;                          // the part reaches this launch's positions
-  const u64* q = a.q + (size_t)layer * a.st_q;
-  const u64* kvn = a.kvn + (size_t)layer * a.st_kvn;
-  u64* attn = a.attn + (size_t)layer * a.st_q;
+  const uint32_t* q = a.q + set + (size_t)layer * a.st_q;
+  const uint32_t* kvn = a.kvn + set + (size_t)layer * a.st_kvn;
+  uint32_t* attn = a.attn + set + (size_t)layer * a.st_q;
   u64* att_p = a.att_p + (size_t)layer * a.st_att_p;
   const int* rowpos = srow + it.b * R;                 // positions of the sequence's rows
   const float sc2 = a.scale * 1.44269504088896340736f;
@@ -1217,29 +1268,29 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   bool bad = false;
   // ---- the queries of the tile's rows and this launch's keys / values of the kv head
   if (it.valid) {
-    constexpr int NB = SB <= 4 ? 2 : 3;                  // pairs of words a thread keeps in flight: one flight for 4 / all 16 new rows
+    constexpr int NB = SB == 2 ? 1 : 2;                  // requests of four words that a thread keeps in flight: one flight for 4 / all 16 new rows
     const int nQ = nrt * 64, total = nQ + (unew ? it.nact * 128 : 0);        // <= 1024 + 2048 words
     const df_rsrc rs = df_make_rsrc(a.tw);
     const uint32_t q_off = (uint32_t)(q - a.tw), n_off = (uint32_t)(kvn - a.tw);
-    for (int base = 0; base < total; base += 2 * NB * PBLOCK) {
+    for (int base = 0; base < total; base += 4 * NB * PBLOCK) {
       u32x4 v[NB];
       auto off = [&](uint32_t t, int u) -> uint32_t {
-        const int idx = base + 2 * (u * PBLOCK + (int)t);
+        const int idx = base + 4 * (u * PBLOCK + (int)t);
         if (idx < nQ) {
           const int r = r0 + (idx >> 6), dd = idx & 63, j = r / G, gq = r - j * G;
-          return 8u * (q_off + (uint32_t)((it.b * R + j) * nqd + (it.kvh * G + gq) * 64 + dd));
+          return 4u * (q_off + (uint32_t)((it.b * R + j) * nqd + (it.kvh * G + gq) * 64 + dd));
         }
         const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
-        return idx < total ? 8u * (n_off + (uint32_t)((((it.b * R + it.off + jn) * 2 + which) * a.nkv + it.kvh) * 64 + dd)) : 0xFFFFFFFFu;
+        return idx < total ? 4u * (n_off + (uint32_t)((((it.b * R + it.off + jn) * 2 + which) * a.nkv + it.kvh) * 64 + dd)) : 0xFFFFFFFFu;
       };
-      bad = !poll_pairs<NB>(rs, (uint32_t)tid, off, tag, v, a.bar + 64, a.hg + (size_t)(2 * layer) * a.st_h, tag) || bad;
+      bad = !poll_quads<NB>(rs, (uint32_t)tid, off, v, a.bar + 64, a.hg + set + (size_t)(2 * layer) * a.st_h) || bad;
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
-        const int idx = base + 2 * (u * PBLOCK + tid);
-        if (idx < nQ) *(uint2*)(Qs + (idx >> 6) * DF_QS + (idx & 63)) = make_uint2(v[u][0], v[u][2]);
+        const int idx = base + 4 * (u * PBLOCK + tid);
+        if (idx < nQ) *(u32x4*)(Qs + (idx >> 6) * DF_QS + (idx & 63)) = v[u];
         else if (idx < total) {
           const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
-          *(uint32_t*)((which ? Vn : Kn) + jn * 64 + dd) = (v[u][0] & 0xFFFFu) | (v[u][2] << 16);
+          *(uint2*)((which ? Vn : Kn) + jn * 64 + dd) = make_uint2(__builtin_amdgcn_perm(v[u][1], v[u][0], 0x05040100u), __builtin_amdgcn_perm(v[u][3], v[u][2], 0x05040100u));
         }
       }
     }
@@ -1292,7 +1343,7 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
       float mx, l, o[2];
       df_merge_row(MO, ML, row, d0, mx, l, o);
       if (np_row == 1) {
-        st_words2(attn + (size_t)out_m * nqd + out_head * 64 + d0, split_payload(o[0] / l), split_payload(o[1] / l), tag);
+        st_val2(attn + (size_t)out_m * nqd + out_head * 64 + d0, operand_word(o[0] / l), operand_word(o[1] / l));
       } else {
         u64* pp = att_p + ((((size_t)out_m * a.nq + out_head) * a.NP + it.part) * 16 + (d0 >> 2)) * 6;
         st_words2(pp + (d0 & 2), __float_as_uint(o[0]), __float_as_uint(o[1]), tag);
@@ -1338,7 +1389,7 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
               o1 = fmaf(__uint_as_float(v[2 * p][2]), e, o1);
             }
         }
-        st_words2(attn + (size_t)m * nqd + head * 64 + d0, split_payload(o0 / l), split_payload(o1 / l), tag);
+        st_val2(attn + (size_t)m * nqd + head * 64 + d0, operand_word(o0 / l), operand_word(o1 / l));
       }
     }
   }
@@ -1359,9 +1410,8 @@ __device__ __forceinline__ const DArgs& df_args() {
   return *(const DArgs*)p;
 }
 
-// SB: tagged words a thread keeps in flight while
-// it stages GEMM operands -- every slot costs instructions whether it is used or not, and a second flight costs a
-// round trip, so the host picks the smallest SB whose single flight (512 threads x SB) holds the launch's rows.
+// SB = 2, 4, 10, 16, 18: 2, 4, 6, 8, 10 rows in flight while it stages GEMM operands -- every slot costs instructions whether it is used or not, and a second
+// flight costs a round trip, so the host picks the smallest SB whose single flight holds the launch's rows.
 template <int SB>
 __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
   const DArgs& a = df_args();
@@ -1373,7 +1423,9 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
   // this launch's number (the kernel that follows a forward on the stream advances the word; nothing in this launch
   // does).  Requested first, looked at after the other start-up loads have been requested.
   const int tag_v = ld_state(a.kv.ctl + 3);
+  const u64 state_v = ld_word(a.state);
   uint32_t tag = 0u;
+  size_t set = 0;                                          // where this launch's set of words begins
   const int nqkv = (a.nq + 2 * a.nkv) * 64, nqd = a.nq * 64, L = a.n_layers, np = a.d >> 5;
   const int NU = gridDim.x * 2;
   // items of every phase kind, and the unit that takes item 0 (the kinds with few items go to different workgroups)
@@ -1387,36 +1439,36 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
   auto make_qkv = [&](const DArgs& a, int l) {
     const PLayer Y = layer_ptrs(a, l);
     DPhase x = DPhase{};
-    x.layer = l; x.A = a.hg + (size_t)(2 * l) * a.st_h; x.sq = a.sq + (size_t)(2 * l) * a.st_sq;
+    x.layer = l; x.A = a.hg + set + (size_t)(2 * l) * a.st_h; x.sq = a.sq + set + (size_t)(2 * l) * a.st_sq;
     x.W0 = Y.wqkv; x.W1 = Y.wqkv; x.N = nqkv; x.K = a.d; x.gs = 1; x.items = n_qkv; x.shift = s_qkv; x.stride = st;
-    x.bias = Y.bqkv; x.out = a.q + (size_t)l * a.st_q; x.kvn = a.kvn + (size_t)l * a.st_kvn;
-    x.hint = x.A + (size_t)(a.rows.M - 1) * a.d + (a.d - 32); x.hint_tag = tag;   // a word of the last sum task
+    x.bias = Y.bqkv; x.out = a.q + set + (size_t)l * a.st_q; x.kvn = a.kvn + set + (size_t)l * a.st_kvn;
+    x.hint = x.A + (size_t)(a.rows.M - 1) * a.d + (a.d - 32);   // a word of the last sum task
     return x;
   };
   auto make_o = [&](const DArgs& a, int l) {
     const PLayer Y = layer_ptrs(a, l);
     DPhase x = DPhase{};
     x.layer = l;
-    x.A = a.attn + (size_t)l * a.st_q;
+    x.A = a.attn + set + (size_t)l * a.st_q;
     x.W0 = Y.wo; x.W1 = Y.wo; x.N = a.d; x.K = nqd; x.gs = 1; x.items = n_o; x.shift = s_o; x.stride = st;
     const size_t hi = (size_t)(2 * l);
-    x.h_in = a.h + hi * a.st_h; x.h_out = a.h + (hi + 1) * a.st_h; x.hg_out = a.hg + (hi + 1) * a.st_h;
-    x.sq_out = a.sq + (hi + 1) * a.st_sq;
+    x.h_in = a.h + set + hi * a.st_h; x.h_out = a.h + set + (hi + 1) * a.st_h; x.hg_out = a.hg + set + (hi + 1) * a.st_h;
+    x.sq_out = a.sq + set + (hi + 1) * a.st_sq;
     x.gain_next = Y.ln2;
-    x.hint = a.q + (size_t)l * a.st_q; x.hint_tag = tag;
+    x.hint = a.q + set + (size_t)l * a.st_q;
     return x;
   };
   auto make_swiglu = [&](const DArgs& a, int l) {
     const PLayer Y = layer_ptrs(a, l);
     DPhase x = DPhase{};
-    x.layer = l; x.A = a.hg + (size_t)(2 * l + 1) * a.st_h; x.sq = a.sq + (size_t)(2 * l + 1) * a.st_sq;
+    x.layer = l; x.A = a.hg + set + (size_t)(2 * l + 1) * a.st_h; x.sq = a.sq + set + (size_t)(2 * l + 1) * a.st_sq;
     x.W0 = Y.wgate; x.W1 = Y.wup; x.N = a.ffn; x.K = a.d; x.gs = 1; x.items = n_gu; x.shift = 0; x.stride = 1;
-    x.hint = a.hg + (size_t)(2 * l + 1) * a.st_h; x.hint_tag = tag;
+    x.hint = a.hg + set + (size_t)(2 * l + 1) * a.st_h;
     return x;
   };
   auto make_head = [&](const DArgs& a) {
     DPhase x = DPhase{};
-    x.A = a.hg + (size_t)(2 * L) * a.st_h; x.sq = a.sq + (size_t)(2 * L) * a.st_sq;
+    x.A = a.hg + set + (size_t)(2 * L) * a.st_h; x.sq = a.sq + set + (size_t)(2 * L) * a.st_sq;
     x.W0 = a.head; x.W1 = a.head; x.N = a.vocab; x.K = a.d; x.gs = 1; x.items = n_lg; x.shift = 0; x.stride = st_lg; x.logits = a.logits;
     return x;
   };
@@ -1448,7 +1500,13 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_fetch_or(a.bar + 64, DEV_ERR_TAGS, __ATOMIC_RELAXED, AG);
     return;
   }
-  df_embed_phase<df_sq_cols<SB>()>(a, tag);
+  // The set of words: the other one than the last launch's.  (The state may already be this launch's: then the launch has gone all its way
+  // but for workgroups without an item in the layers, such as this one.)
+  const uint32_t last_tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)state_v), last = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(state_v >> 32));
+  const uint32_t which = last_tag == tag ? last & 1u : ~last & 1u;
+  const int old_rows = last_tag == tag ? 0 : (int)(last >> 1);
+  set = which * a.st_set;
+  df_embed_phase<df_sq_cols<SB>()>(a, set);
   if (g_q && threadIdx.x < a.rows.M) {                    // the QKV epilogue appends keys and values: block of each row's position
     u64 w = ld_word(a.rowblk + threadIdx.x);
     for (long spins = 0; (uint32_t)(w >> 32) != tag; w = ld_word(a.rowblk + threadIdx.x)) {
@@ -1473,7 +1531,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     }
     if (g_a) {
       const DArgs& a = df_args();
-      if (df_attn_phase<SB>(a, tag, l, ait, lds, sblk, srow, &sdead, s0 + 2)) return;
+      if (df_attn_phase<SB>(a, tag, set, l, ait, lds, sblk, srow, &sdead, s0 + 2)) return;
     }
     if (g_o) {
       const DArgs& a = df_args();
@@ -1483,6 +1541,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     auto clear = [&]() {
       const DArgs& a = df_args();
       if (g_r && l > 0) df_clear_partials<df_sum_cols<SB>()>(a, a.part + (size_t)((l - 1) & 1) * a.st_part, s_red);
+      if (g_g) df_clear_layer(a, (which ^ 1u) * a.st_set, old_rows, l);
     };
     if (!g_g) {
       clear();
@@ -1499,8 +1558,8 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
       const DArgs& a = df_args();
       const size_t hi = (size_t)(2 * l + 1);
       const float* gain_next = l + 1 < L ? layer_ptrs(a, l + 1).ln1 : a.final_norm;
-      if (df_reduce_phase<df_sum_cols<SB>()>(a, tag, l, a.part + (size_t)(l & 1) * a.st_part, a.h + hi * a.st_h, a.h + (hi + 1) * a.st_h,
-                          a.hg + (hi + 1) * a.st_h, a.sq + (hi + 1) * a.st_sq, gain_next, s_red, lds, &sdead, s0 + 8)) return;
+      if (df_reduce_phase<df_sum_cols<SB>()>(a, tag, l, a.part + (size_t)(l & 1) * a.st_part, a.h + set + hi * a.st_h, a.h + set + (hi + 1) * a.st_h,
+                          a.hg + set + (hi + 1) * a.st_h, a.sq + set + (hi + 1) * a.st_sq, gain_next, s_red, lds, &sdead, s0 + 8)) return;
     }
   }
   if (a.with_head && g_l) {
@@ -1512,6 +1571,9 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     const DArgs& a = df_args();
     df_clear_partials<df_sum_cols<SB>()>(a, a.part + (size_t)((L - 1) & 1) * a.st_part, s_red);
   }
+  // (workgroup 0 sums partials of every MLP item: those have all begun long ago)
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    __hip_atomic_store(a.state, (u64)tag | (u64)((uint32_t)a.rows.M << 1 | which) << 32, __ATOMIC_RELAXED, AG);
 }
 
 }  // namespace ssd

@@ -310,7 +310,8 @@ struct ssd_kv {
   int persistent_wgs = 0;          // 0: the persistent kernel is not usable for this cache
   int cus = 0;                     // compute units of the device
   // tagged workspace of the barrier-free forward (see dataflow.h); null when that kernel is not usable
-  u64 *t_base = nullptr, *t_h, *t_hg, *t_sq, *t_q, *t_kvn, *t_attn, *t_att_p, *t_part, *t_rowblk;
+  u64 *t_base = nullptr, *t_att_p, *t_part, *t_rowblk;
+  uint32_t *t_h, *t_hg, *t_sq, *t_q, *t_kvn, *t_attn;
   size_t t_words = 0, t_attp_at = 0;     // words of it; words ahead of the attention's partials (GEMM operands are among them)
   bool dataflow = false;
   bool attn_whole = false;   // ssd_kv_last_forward_path tells launches whose attention is one part (4) from others (3) on this cache
@@ -319,7 +320,7 @@ struct ssd_kv {
   bool capturing = false;          // a cycle is being captured on this cache: no synchronisation, no fallback kernels
   int last_path = 0;               // 1 per-operator launches, 2 barrier kernel, 3 barrier-free kernel, 4 the same with attention without parts
   bool last_whole = false;
-  int df_sb = 0;             // SSD_DF_FLIGHT=2|4|10|16|18: words in flight per thread of the operand staging, up to 8 rows (0: chosen per launch)
+  int df_sb = 0;             // SSD_DF_FLIGHT=2|4|10|16|18: instantiation of the barrier-free forward up to 8 rows (0: chosen per launch)
   // host
   int32_t* mirror_host;
   std::vector<int> len_ub, npend_ub;
@@ -367,21 +368,23 @@ static size_t kv_layout(const ssd_model* m, int max_seqs, int max_rows, int n_bl
   int32_t* tickets = cv.take<int32_t>(std::max(c.d_model / 32 + 1, Mmax * c.n_kv_heads));
   uint32_t* bar = cv.take<uint32_t>(128);
   unsigned long long* trace = cv.take<unsigned long long>(p_ok ? 256 * 512 : 0);
-  // tagged words of the barrier-free forward: one block, zeroed at creation
+  // words of the barrier-free forward: one block, zeroed at creation.  Two sets of 32-bit words, the attention's partials (words of 64 bits
+  // from here on), the MLP's
   const size_t TR = PR;
   const size_t w_h = (size_t)(2 * L + 1) * TR * c.d_model, w_sq = (size_t)(2 * L + 1) * TR * (c.d_model / 8);
   const size_t w_q = (size_t)L * TR * nqd, w_kvn = (size_t)L * TR * 2 * c.n_kv_heads * 64;
   const size_t w_attp = (size_t)L * TR * c.n_q_heads * NP * 96;
   const size_t w_part = (size_t)2 * (c.d_ffn / 32) * TR * c.d_model;     // (two buffers of fp32, at most twice the rows apart: df_part_pitch)
-  const size_t t_words = w_h * 2 + w_sq + w_q * 2 + w_kvn + w_attp + w_part + 16;
+  const size_t t_words = w_h * 2 + w_sq + w_q * 2 + w_kvn + w_attp + w_part + 32;
   u64* t_base = cv.take<u64>(t_words);
   if (kv) {
-    u64* t = t_base;
     kv->t_base = t_base; kv->t_words = t_words;
-    kv->t_h = t; t += w_h; kv->t_hg = t; t += w_h; kv->t_sq = t; t += w_sq; kv->t_q = t; t += w_q; kv->t_attn = t; t += w_q;
-    kv->t_attp_at = w_h * 2 + w_sq + w_q * 2 + w_kvn;
-    kv->t_kvn = t; t += w_kvn; kv->t_att_p = t; t += w_attp; kv->t_part = t; t += w_part;
-    kv->t_rowblk = t;
+    uint32_t* t = (uint32_t*)t_base;
+    kv->t_h = t; t += w_h; kv->t_hg = t; t += w_h; kv->t_sq = t; t += w_sq; kv->t_q = t; t += w_q; kv->t_attn = t; t += w_q; kv->t_kvn = t;
+    kv->t_attp_at = w_h * 2 + w_sq + w_q * 2 + w_kvn;      // (words of 64 bits ahead; 32-bit words of a set)
+    kv->t_att_p = t_base + kv->t_attp_at;
+    kv->t_part = kv->t_att_p + w_attp;
+    kv->t_rowblk = kv->t_part + w_part;
 
     kv->trace = trace;
     kv->p_h = p_h; kv->p_hg = p_hg; kv->p_sumsq = p_sumsq; kv->p_q = p_q; kv->p_attn = p_attn; kv->p_act = p_act; kv->p_part = p_part; kv->p_att_o = p_att_o;
@@ -954,7 +957,7 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   a.kv = kv->v; a.rows = rows; a.pcap = pcap; a.n_seqs = B; a.tok_stride = tok_stride; a.with_head = with_head ? 1 : 0;
   a.tokens = dev_tokens;
   const size_t PR = kv->p_rows;
-  a.tw = kv->t_base; a.h = kv->t_h; a.hg = kv->t_hg; a.sq = kv->t_sq; a.q = kv->t_q; a.kvn = kv->t_kvn; a.attn = kv->t_attn;
+  a.tw = (uint32_t*)kv->t_base; a.st_set = kv->t_attp_at; a.state = kv->t_rowblk + 16; a.h = kv->t_h; a.hg = kv->t_hg; a.sq = kv->t_sq; a.q = kv->t_q; a.kvn = kv->t_kvn; a.attn = kv->t_attn;
   a.att_p = kv->t_att_p; a.logits = kv->logits;
   a.st_h = PR * c.d_model; a.st_sq = PR * (c.d_model / 8); a.st_q = PR * nqd; a.st_kvn = PR * 2 * c.n_kv_heads * 64;
   a.st_att_p = PR * c.n_q_heads * kv->NP * 96;
@@ -965,14 +968,10 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   a.trace = kv->trace_on ? kv->trace : nullptr;
   ProfScope ps(PROF_PERSISTENT, st);
   kv->last_whole = kv->attn_whole && max_len + 16 <= DF_ONE_PART;      // (reported only)
-  // one flight of an operand staging holds SB / 2 rows; the words that it brings, the rows' operands and their sums of squares, are
-  // at most 512 x SB (wider rows take several flights, and more of them in flight at once)
-  auto holds = [&](int n) {                                // (n <= 4: sums of squares over 8 columns, see df_reduce_phase)
-    return 2 * M <= n && M * (std::max(c.d_model, nqd) + c.d_model / (n <= 4 ? 8 : 32)) <= n * PBLOCK;
-  };
-  int sb = kv->df_sb ? kv->df_sb : holds(2) ? 2 : holds(4) ? 4 : holds(10) ? 10 : holds(16) ? 16 : 18;
-  if (sb <= 4 && M * (c.d_model / 8) > DF_SQ_WORDS) sb = 10;
-  if (M > DF_PACK_ROWS) sb = 18;
+  // the smallest instantiation whose flight of an operand staging holds the rows (and, of two rows, the sums of squares over 8 columns)
+  int sb = M <= 2 && M * (c.d_model / 8) <= PBLOCK ? 2 : M <= 4 ? 4 : M <= 6 ? 10 : M <= 8 ? 16 : 18;
+  if (kv->df_sb && M <= DF_PACK_ROWS) sb = kv->df_sb;
+  if (sb == 2 && M * (c.d_model / 8) > DF_SQ_WORDS) sb = 10;
 #define DF_LAUNCH(S) hipLaunchKernelGGL((k_forward_dataflow<S>), dim3(G), dim3(PBLOCK), 0, st, a)
   if (sb == 2) DF_LAUNCH(2); else if (sb == 4) DF_LAUNCH(4); else if (sb == 10) DF_LAUNCH(10); else if (sb == 16) DF_LAUNCH(16); else DF_LAUNCH(18);
 #undef DF_LAUNCH

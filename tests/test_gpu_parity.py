@@ -401,12 +401,13 @@ def test_mini_bf16_operand_staging_flights(flight, K, monkeypatch):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("d,ffn", [(96, 64), (160, 6208), (64, 2048), (32, 2080)])
+@pytest.mark.parametrize("d,ffn", [(96, 64), (160, 6208), (64, 2048), (32, 2080), (1120, 96)])
 def test_sums_of_down_projection_partials(d, ffn):
     """The sums over the workgroups' partial results of the down projection, which are there when they are not zero and are put back to
     zero: fewer partials than blocks of them (2), one per block (64), one more, and four of a block where three are in flight; the last 64 columns with
     and without their second half.  Every third output column's partials are exact zeros.  Three layers use a buffer twice, and launches
-    of 1, 2, 5, 8, 9 and 16 rows, which have it in three layouts, follow each other on one cache."""
+    of 1, 2, 5, 8, 9 and 16 rows, which have it in three layouts, follow each other on one cache, as do the two sets of the other words
+    (1120 columns: more than a flight's)."""
     from tests.parity import Pair, loud_weights, verify_parity_step
     shape = dict(n_layers=3, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=ffn, vocab=41, n_embed=43, dtype="bf16",
                  qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
