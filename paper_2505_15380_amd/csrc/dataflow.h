@@ -859,7 +859,12 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t t
       st_val(hg_out + o, operand_word(v * gain));
       float q2 = v * v;
 #pragma unroll
-      for (int off = 1; off < CS; off <<= 1) q2 += __shfl_xor(q2, off, 32);
+      for (int off = 1; off < 16; off <<= 1)
+        if (off < CS) q2 += off == 1 ? dpp_f<0xB1>(q2) : off == 2 ? dpp_f<0x4E>(q2) : off == 4 ? dpp_f<0x141>(q2) : dpp_f<0x140>(q2);       // (as row16_sum)
+      if (CS == 32) {
+        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(q2), __float_as_uint(q2), false, false);
+        q2 = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+      }
       if ((tid & (CS - 1)) == 0) st_val(sq_out + (size_t)m * (d / CS) + col / CS, float_word(q2));
     }
     if (task == first) DF_STAMP(slot + 1);
