@@ -37,7 +37,7 @@
 // The phases with few items (QKV, attention, output projection) run on workgroups of their own, beyond those that
 // take the MLP items, so that no workgroup is late for the MLP, the phase every workgroup waits for.
 // Polling costs fabric bandwidth that the producers' stores need: a wave whose first flight fails first watches a
-// single word of the PRECEDING phase's operands with long sleeps, and polls in earnest only from then on.
+// single word with long sleeps, and polls in earnest only from then on.
 //
 // Attention never reads this launch's new keys from the cache pool: the QKV phase stores them in the pool for
 // later launches and, as words, in a side buffer; a wave whose 64-key chunk reaches the new positions patches its key
@@ -72,8 +72,10 @@ constexpr int DF_TR = DF_AW + DF_SQ_WORDS + DF_RED_WORDS;                       
 constexpr int DF_LDS_WORDS = DF_TR + 8 * 8 * DF_DN * 16;
 static_assert(DF_ATT_WORDS <= DF_LDS_WORDS && DF_LDS_WORDS <= 39 * 1024, "");
 
-// Which single word a wave watches after a failed first flight (see df_wait_hint): the phases with many consumers (QKV,
-// MLP) watch a word of their OWN operands, the others a word of the preceding phase's operands.
+// Which single word a wave watches after a failed first flight (see df_wait_hint): the phases with many consumers (QKV, attention, MLP)
+// watch a word of their OWN operands, the output projection one of the preceding phase's.  (The MLP watching a word of the phase before: one row
+// 1.1 us a layer more, nine rows 2.4; QKV so 1.5 and 1.1; attention so 1.0 at nine rows of 4096 positions, where 40 workgroups
+// polled beside the ones they waited for.  The output projection watching its own: one row 0.15 more.)
 constexpr int DF_HINT_SLEEP = 2;
 
 struct DArgs {
@@ -142,9 +144,8 @@ __device__ __forceinline__ bool df_any_zero(const u32x4 x) { return min(min(x[0]
 
 // A workgroup that arrives at a phase long before its operands would poll them the whole time, and the polls of all
 // such workgroups load the fabric that the producers' stores travel through.  After a first failed flight a wave
-// therefore watches one word of the operands of the PRECEDING phase (one hand-over earlier) with a single
-// address and long sleeps, and resumes the full polling when that word is there.  Purely a hint: bounded, and
-// nothing depends on what it saw.
+// therefore watches one word (see DF_HINT_SLEEP) with a single address and long sleeps, and resumes the full polling when that
+// word is there.  Purely a hint: bounded, and nothing depends on what it saw.
 __device__ __forceinline__ void df_wait_hint(const uint32_t* word, uint32_t* err) {
   for (int i = 0; i < (1 << 14); ++i) {
     if (ld_val(word) != 0u) return;
@@ -221,7 +222,7 @@ struct DPhase {
   const void* W1;
   int N, K, gs, items;    // gs: k-splits, always 1 here (the field the shared k-range helper reads)
   int shift, stride;      // item i of round 0 runs on unit (shift + stride * i) % units
-  const uint32_t* hint;        // a word of the preceding phase's operands (see df_wait_hint), or null
+  const uint32_t* hint;        // the word to watch while there is nothing (see df_wait_hint), or null
   int layer;
   const float* bias;
   const uint32_t* h_in;        // PE_RESID: residual input and outputs
@@ -263,7 +264,7 @@ __device__ __forceinline__ bool stage_operand(const DArgs& a, const uint32_t* A,
   uint32_t* err = a.bar + 64;
   bool ok = true;
   auto give_up = [&](long& spins) -> bool {
-    if (spins == 0 && hint) df_wait_hint(hint, err);                   // far too early: wait cheaply for the phase before
+    if (spins == 0 && hint) df_wait_hint(hint, err);                   // far too early: wait cheaply
     if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
       __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, AG);
       ok = false;
@@ -1288,7 +1289,7 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
         const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
         return idx < total ? 4u * (n_off + (uint32_t)((((it.b * R + it.off + jn) * 2 + which) * a.nkv + it.kvh) * 64 + dd)) : 0xFFFFFFFFu;
       };
-      bad = !poll_quads<NB>(rs, (uint32_t)tid, off, v, a.bar + 64, a.hg + set + (size_t)(2 * layer) * a.st_h) || bad;
+      bad = !poll_quads<NB>(rs, (uint32_t)tid, off, v, a.bar + 64, q + (size_t)it.b * R * nqd + it.kvh * G * 64) || bad;
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
         const int idx = base + 4 * (u * PBLOCK + tid);
@@ -1447,7 +1448,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     x.layer = l; x.A = a.hg + set + (size_t)(2 * l) * a.st_h; x.sq = a.sq + set + (size_t)(2 * l) * a.st_sq;
     x.W0 = Y.wqkv; x.W1 = Y.wqkv; x.N = nqkv; x.K = a.d; x.gs = 1; x.items = n_qkv; x.shift = s_qkv; x.stride = st;
     x.bias = Y.bqkv; x.out = a.q + set + (size_t)l * a.st_q; x.kvn = a.kvn + set + (size_t)l * a.st_kvn;
-    x.hint = x.A + (size_t)(a.rows.M - 1) * a.d + (a.d - 32);   // a word of the last sum task
+    x.hint = x.A;
     return x;
   };
   auto make_o = [&](const DArgs& a, int l) {
