@@ -250,7 +250,7 @@ int ssd_profile_end(double* total_ms, int* launches);
 /* Which kernels ran the last decoder forward on `kv` (host bookkeeping, no synchronisation):
  * 0 none yet, 1 one launch per operator (fp32 storage, more than 16 rows, head_dim other than 64),
  * 2 one persistent kernel with grid barriers between phases, 3 one persistent kernel whose phases are ordered by
- * tagged data words (the default for bf16 storage and at most 16 rows; the environment variable
+ * the data themselves (the default for bf16 storage and at most 16 rows; the environment variable
  * SSD_FORWARD=barrier, read at ssd_kv_create, selects 2 instead; 2 is also what runs when a launch exceeds the
  * limits of 3), 4 the same kernel where no part of a prefix can meet another one's: at most 1520 cached positions, by the
  * host's bound of the lengths, on a cache created with pending_cap 2 (SSD_ATTN_WHOLE=1: on every cache, 0: on none).  The

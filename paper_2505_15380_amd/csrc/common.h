@@ -82,10 +82,10 @@ struct KvView {
 constexpr int KV_ERR_POOL = 1;        // the device allocator ran out of blocks
 constexpr int KV_ERR_ROLLBACK = 4;    // a rollback asked for more positions than the sequence holds (refused)
 constexpr uint32_t DEV_ERR_TIMEOUT = 1u;   // a bounded wait inside a persistent forward gave up
-constexpr uint32_t DEV_ERR_TAGS = 2u;      // the launch counter reached its limit: the tagged workspace must be cleared
-// Launch numbers tag the hand-over words of the barrier-free forward; the MLP partials carry launch * 128 + layer in
-// 32 bits, so launch numbers stay below 2^25.  The host clears the workspace and restarts the numbering before that;
-// a forward that still finds the limit reached does nothing and raises DEV_ERR_TAGS.
+constexpr uint32_t DEV_ERR_TAGS = 2u;      // the launch counter reached its limit: the workspace must be cleared
+// Launch numbers tag the attention's partial results and the new keys' blocks of the barrier-free forward, in 32 bits.  The numbers that a
+// cache takes end at 2^25, as ssd.h says: the host clears the workspace and restarts the numbering before that; a forward that
+// still finds the limit reached does nothing and raises DEV_ERR_TAGS.
 constexpr uint32_t TAG_LIMIT = (1u << 25) - 1u;
 
 // Element offset of (layer, which(0=K,1=V), block, kv head, token in block, 0) in the pool.  Keys are stored

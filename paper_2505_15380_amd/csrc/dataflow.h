@@ -120,7 +120,6 @@ __device__ __forceinline__ u64 ld_word(const u64* p) { return __hip_atomic_load(
 __device__ __forceinline__ void st_word(u64* p, uint32_t payload, uint32_t tag) {
   __hip_atomic_store(p, (u64)payload | ((u64)tag << 32), __ATOMIC_RELAXED, AG);
 }
-__device__ __forceinline__ void st_wordf(u64* p, float x, uint32_t tag) { st_word(p, __float_as_uint(x), tag); }
 // Words without a tag, zero while they are not there, and the forms that are never zero.
 __device__ __forceinline__ uint32_t ld_val(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, AG); }
 __device__ __forceinline__ void st_val(uint32_t* p, uint32_t bits) { __hip_atomic_store(p, bits, __ATOMIC_RELAXED, AG); }

@@ -701,7 +701,7 @@ __global__ void k_kv_init(KvView kv) {
   }
 }
 
-// Clears the sticky error state (the caller has re-zeroed the barrier words and the tagged workspace on the same stream)
+// Clears the sticky error state (the caller has re-zeroed the barrier words and the barrier-free forward's workspace on the same stream)
 // and restarts the launch numbering; sequence state is left as it is.
 __global__ void k_kv_clear_error(KvView kv) {
   if (threadIdx.x || blockIdx.x) return;

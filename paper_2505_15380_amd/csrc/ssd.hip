@@ -309,7 +309,7 @@ struct ssd_kv {
   uint32_t launch_no = 1;          // host's copy of ctl[3]: the number the next forward on this cache will read
   int persistent_wgs = 0;          // 0: the persistent kernel is not usable for this cache
   int cus = 0;                     // compute units of the device
-  // tagged workspace of the barrier-free forward (see dataflow.h); null when that kernel is not usable
+  // workspace of the barrier-free forward (see dataflow.h); null when that kernel is not usable
   u64 *t_base = nullptr, *t_att_p, *t_part, *t_rowblk;
   uint32_t *t_h, *t_hg, *t_sq, *t_q, *t_kvn, *t_attn;
   size_t t_words = 0, t_attp_at = 0;     // words of it; words ahead of the attention's partials (GEMM operands are among them)
@@ -467,7 +467,7 @@ extern "C" int ssd_kv_create(const ssd_model* m, int max_seqs, int max_rows, int
       kv->cus = cus;
     }
   }
-  // The barrier-free forward additionally needs its word offsets to fit 32 bits; its words start untagged (zero).
+  // The barrier-free forward additionally needs its word offsets to fit 32 bits; its words start as zeros.
   kv->dataflow = false;
   if (e == hipSuccess && kv->persistent_wgs > 0 && kv->t_words > 0 && kv->t_words < ((size_t)1 << 32) && kv->t_attp_at < ((size_t)1 << 28) &&
       (size_t)kv->p_rows * m->c.n_q_heads * kv->NP * 96 < ((size_t)1 << 28)) {      // (pairs of words are addressed by 32 bits of bytes: ahead of the parts, and in a layer's parts)
