@@ -741,8 +741,8 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
 // acknowledgement of their own stores, and then nearly always find everything there; a workgroup without an MLP item that polls meanwhile
 // delays those stores (five rows 1.2 us a layer more when such workgroups came first), so it watches one word of its last partial.
 // The last ones to get a task are those with QKV or attention items, which begin the next layer: C = 64 for six rows and more leaves
-// them without one up to 13 rows of the 0.5B shape, and gives none a second task (nine rows: 24.3 -> 20.7 us a layer, against C = 32).
-// With few rows what counts is the time to take in a task's partials: C = 8 for one or two (one row: 1.9 us from the end of the MLP to the sum;
+// them without one up to 12 rows of the 0.5B shape, and gives none a second task (nine rows: 24.3 -> 20.7 us a layer, against C = 32).
+// With few rows what counts is the time to take in a task's partials: C = 8 for one, or for two that are one round of tasks (one row: 1.9 us from the end of the MLP to the sum;
 // with 16 columns 2.0, with 32 3.0), else 32.
 // Partials of 4 bytes without a tag instead of 8 with one, and 16-byte loads: from the MLP's end to the sum five rows 3.4 -> 2.2 us, nine 3.5 -> 2.4.
 // The order of a sum does not depend on C: the partials form 64 blocks of consecutive ones, summed in ascending order; eight

@@ -939,9 +939,8 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   // with compute units to spare every item of the other small phases gets a workgroup of its own, as attention's always do (its
   // waves then do not share their SIMDs with a second item), else two items share one
   const int small_stride = g_mlp + n_att + n_other <= kv->cus ? 2 : 1;
-  // A launch that takes more than half of the compute units has no room for another one beside it, so it takes all: the workgroups without
-  // another item take sums, which those with an MLP item begin only when their stores are acknowledged, and of which a second round takes 2 us.
-  const int n_items = g_mlp + n_att + cdiv(small_stride * n_other, 2), G = 2 * n_items > kv->cus ? kv->cus : n_items;
+  // (No more workgroups than items: those of a launch wait for each other, and a smaller model's launch on another stream may be in what is left.)
+  const int G = std::min(kv->cus, g_mlp + n_att + cdiv(small_stride * n_other, 2));
   // limits: one round of attention (its workgroups wait for each other's parts), query rows of an item, LDS staging capacity
   const bool fits = M <= 16 && rows.R * grp <= DF_ATT_ROWS && n_att <= G && n_parts <= kv->NP &&
                     M * (c.d_model + 4) <= DF_AW && M * (nqd + 4) <= DF_AW && M * (c.d_model / 32) <= DF_SQ_WORDS &&
@@ -968,8 +967,9 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   a.trace = kv->trace_on ? kv->trace : nullptr;
   ProfScope ps(PROF_PERSISTENT, st);
   kv->last_whole = kv->attn_whole && max_len + 16 <= DF_ONE_PART;      // (reported only)
-  // the smallest instantiation whose flight of an operand staging holds the rows (and, of two rows, the sums of squares over 8 columns)
-  int sb = M <= 2 && M * (c.d_model / 8) <= PBLOCK ? 2 : M <= 4 ? 4 : M <= 6 ? 10 : M <= 8 ? 16 : 18;
+  // The smallest instantiation whose flight of an operand staging holds the rows, where its sum tasks (of 8, 32, 32, 64, 64 columns) go well: those of
+  // two rows in one round (a second one takes 2 us, tasks of 32 columns 1.1), those of 10 on the workgroups with MLP items; 2 also needs room for its sums of squares.
+  int sb = M <= 2 && M * (c.d_model / 8) <= std::min(PBLOCK, G) ? 2 : M <= 4 ? 4 : M <= 6 && M * npairs <= g_mlp ? 10 : M <= 8 ? 16 : 18;
   if (kv->df_sb && M <= DF_PACK_ROWS) sb = kv->df_sb;
   if (sb == 2 && M * (c.d_model / 8) > DF_SQ_WORDS) sb = 10;
 #define DF_LAUNCH(S) hipLaunchKernelGGL((k_forward_dataflow<S>), dim3(G), dim3(PBLOCK), 0, st, a)

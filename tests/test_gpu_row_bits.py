@@ -151,3 +151,38 @@ def test_attention_of_launches_that_leave_half_of_the_device_idle(B, R, monkeypa
         assert path == 1
     assert (got["valu"] - got[""]).abs().max() < 1e-3
     assert got[""].abs().max() > 0.1
+
+
+@pytest.mark.parametrize("K", [0, 1, 5])
+def test_a_small_model_beside_a_large_one_on_another_stream(K):
+    """The workgroups of a barrier-free launch wait for each other, so launches on two streams have to fit the device together: at width 896
+    one takes 218 compute units, and a small model's 13 have room beside it.  The same steps as one after the other."""
+    import paper_2505_15380_amd as ssd
+    large = si.model_shape("half_b_draft")
+    large.update(vocab=300, n_embed=300)
+    small = dict(n_layers=4, d_model=64, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=41, n_embed=43, dtype="bf16", qkv_bias=1,
+                 rope_base=1.0e4, rms_eps=1e-6)
+    runs = []
+    for shape in (large, small):
+        model, kv = _target(shape, [70], 64, extra=400)
+        x = torch.from_numpy(np.random.default_rng(7).integers(0, shape["vocab"], (1, K)).astype(np.int32)).cuda() if K else None
+        pd = torch.full((1, K, shape["vocab"]), 1.0 / shape["vocab"], device="cuda") if K else None
+        runs.append((model, kv, x, pd, torch.cuda.Stream(), kv.state(0)["pending"][0]))
+    cfg = ssd.sample_config(beta=0.3, seed=3)
+    got = []
+    for beside in (False, True):
+        for _, kv, _, _, stream, pending in runs:
+            with torch.cuda.stream(stream):
+                ssd.ssd_kv_rollback(kv, 0, 70, pending)
+        torch.cuda.synchronize()
+        outs = []
+        for step in range(20):
+            for model, kv, x, pd, stream, _ in runs:
+                with torch.cuda.stream(stream):
+                    outs.append(ssd.ssd_verify(model, kv, 1, x, pd, K, cfg, step, want_logits=True)["logits"])
+                    assert kv.last_forward_path() in (3, 4)
+                if not beside:
+                    torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        got.append(outs)
+    assert all(torch.equal(a, b) for a, b in zip(*got))
