@@ -273,6 +273,9 @@ int ssd_trace_barriers(ssd_kv* kv, int enable, void* stream, unsigned long long*
  * with eight k-tiles in flight; row tiles, column slots, k-slices of a workgroup}.  ssd_attention_plan: prompt_positions = cached positions
  * after a prompt's launch, 0 for any other launch; plan = {row tiles, key groups of a workgroup; 64-key chunks of a part}. */
 int ssd_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4]);
+/* {column block, row block, k-slice} of each workgroup of such a launch, {-1, -1, -1} of one that has none, up to `cap` workgroups; workgroup w runs
+ * on XCD w % 8.  Returns the number of workgroups. */
+int ssd_gemm_blocks(int kind, int rows, int n, int k, int cus, int* blocks, int cap);
 int ssd_attention_plan(int head_dim, int n_q_heads, int n_kv_heads, int n_seqs, int rows, int prompt_positions, int cus, int plan[3]);
 
 const char* ssd_strerror(int code);

@@ -8,20 +8,20 @@
 namespace ssd {
 
 // How the output is cut up: blocks of row tiles x blocks of column tiles (x k-slices where the output is k-split
-// partials).  Consecutive workgroup indices go to the eight XCDs in turn, and each XCD's L2 fetches what its workgroups read: the XCDs of a
+// partials).  Consecutive workgroup indices go to the eight XCDs in turn, and each XCD's L2 fetches what its workgroups read: either the XCDs of a
 // slice form a grid of row groups x column groups, each XCD a contiguous rectangle of blocks, so that activations are fetched by as many XCDs as
-// there are column groups, and weights by as many as there are row groups (the host takes the grid of the least bytes).
+// there are column groups, and weights by as many as there are row groups; or each XCD takes a contiguous run of the order (slice, column
+// block, row block).  The host takes the placement of the least bytes (place_tiles).
 struct TilePlan {
   int n_colb, n_rowb, n_slices, slice_kt;     // slice_kt: k-tiles per workgroup
   int per_xcd;                                // workgroups of an XCD
-  int rows_xcd, cols_xcd;                     // blocks of an XCD's rectangle; rows_xcd = 0: each XCD takes a contiguous run of the order
-                                              // (slice, column block, row block)
+  int rows_xcd, cols_xcd;                     // blocks of an XCD's rectangle; rows_xcd = 0: runs
   int lg_per, lg_colg;                        // logarithms of a slice's XCDs and of its column groups
-  uint32_t rows_inv;                          // 2^20 / rows_xcd + 1
+  uint32_t rows_inv;                          // 2^20 / rows_xcd + 1: i / rows_xcd = i * rows_inv >> 20 for i < 4096 and rows_xcd <= 256
 };
-// (Three integer divisions here took 0.1 us of every launch.)
-__device__ __forceinline__ bool tile_block(const TilePlan& p, int& colb, int& rowb, int& slice) {
-  const int x = (int)(blockIdx.x & 7), i = (int)(blockIdx.x >> 3);
+// The block of a workgroup; false where it has none.  (Three integer divisions here took 0.1 us of every launch.)
+__host__ __device__ __forceinline__ bool tile_block(const TilePlan& p, int workgroup, int& colb, int& rowb, int& slice) {
+  const int x = workgroup & 7, i = workgroup >> 3;
   if (p.rows_xcd) {
     const int y = x & ((1 << p.lg_per) - 1), c = (int)(((uint32_t)i * p.rows_inv) >> 20);
     slice = x >> p.lg_per;
@@ -268,7 +268,7 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
   static_assert(UA >= NBUF - 1 && UA % 2 == 0 && (EPI == EPI_PARTIAL || EPI == EPI_RESID || TN % 2 == 0), "the first waits rely on it");
   __shared__ u32x4 stage[NBUF][TN][64];
   int colb, rowb, slice;
-  if (!tile_block(p, colb, rowb, slice)) return;
+  if (!tile_block(p, (int)blockIdx.x, colb, rowb, slice)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int KT = g.K >> 5, ntiles = (g.N + 15) >> 4, last_mt = (g.M - 1) >> 4;
   const int kb = slice * p.slice_kt, nk = min(KT, kb + p.slice_kt) - kb;
@@ -405,7 +405,7 @@ __global__ void __launch_bounds__(WR * WC * 64) k_gemm_block(GemmArgs g, TilePla
   static_assert(EPI != EPI_RESID && RT % WR == 0 && CT % WC == 0 && (EPI == EPI_PARTIAL || TN % 2 == 0), "");
   extern __shared__ u32x4 lds[];                           // [NBUF][F][64]
   int colb, rowb, slice;
-  if (!tile_block(p, colb, rowb, slice)) return;
+  if (!tile_block(p, (int)blockIdx.x, colb, rowb, slice)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave / WC, wc = wave - wr * WC;
   const int KT = g.K >> 5, ntiles = (g.N + 15) >> 4, last_mt = (g.M - 1) >> 4;
   const int kb = slice * p.slice_kt, nk = min(KT, kb + p.slice_kt) - kb, hd = g.kv.hd;
@@ -507,7 +507,7 @@ __global__ void __launch_bounds__(W * 64, 1) k_gemm_kwave(GemmArgs g, TilePlan p
   __shared__ f32x4 red[W][RPR * TN][64];
   __shared__ float inv_rms[TM][16];
   int colb, rowb, slice;
-  if (!tile_block(p, colb, rowb, slice)) return;
+  if (!tile_block(p, (int)blockIdx.x, colb, rowb, slice)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int KT = g.K >> 5, ntiles = (g.N + 15) >> 4, last_mt = (g.M - 1) >> 4;
   const int kb = slice * p.slice_kt, ke = min(KT, kb + p.slice_kt);

@@ -595,17 +595,32 @@ static TilePlan gemm_plan(const GemmArgs& g, int rows, int cols, int slices) {
   p.per_xcd = cdiv(p.n_colb * p.n_rowb * p.n_slices, 8);
   p.rows_xcd = p.cols_xcd = p.lg_per = p.lg_colg = 0;
   p.rows_inv = 0;
-  if (8 % p.n_slices == 0 && p.per_xcd < 4096) {           // the XCDs' grid of the least bytes among those that give no XCD more workgroups than it has to take
-    const double a = (double)g.M * 4, w = (double)n_wt * 16 * 2;      // bytes per k of the activations (hi + lo) and of the weights
-    double best = 0;
-    p.lg_per = __builtin_ctz(8 / p.n_slices);
-    for (int lc = p.lg_per; lc >= 0; --lc) {
-      const int ng = 1 << (p.lg_per - lc), r = cdiv(p.n_rowb, ng), c = cdiv(p.n_colb, 1 << lc);
-      const double bytes = a * (1 << lc) + w * ng;
-      if (r * c <= p.per_xcd && (!p.rows_xcd || bytes < best)) { best = bytes; p.rows_xcd = r; p.cols_xcd = c; p.lg_colg = lc; p.rows_inv = (1u << 20) / r + 1; }
-    }
-  }
   return p;
+}
+// The XCDs' shares of a plan (runs so far): the placement for which their L2s fetch the least, of the runs and of the grids that give no XCD more
+// workgroups than the runs do.  (Against the runs because such a grid can fetch twice as much: gate / up of 512 rows of the 0.5B shape, 61 x 4 blocks of
+// 10 x 8 tiles, 74 MB in four row groups, the only ones that fit, and 34 in runs.  us a launch in a prompt, that grid -> runs: 200 rows 18.8 -> 17.3, 256
+// 19.3 -> 17.9, 448 to 512 1.0 to 2.9 less, 832 and 896 0.4 and 0.7; 1024 rows of this shape and of the 1.5B shape, where the matrix cores are what
+// counts, equal.  Grids that give an XCD up to an eighth more workgroups than a run fetch less still, and were from 1.8 us faster to 0.9 slower.)
+static void place_tiles(TilePlan& p, int rt, int ct) {
+  const long row = rt * 64, col = ct * 32;                 // bytes per k of a block's activations (hi + lo) and of its weights
+  const int per_slice = p.n_colb * p.n_rowb, run = p.per_xcd;
+  if (8 % p.n_slices) return;
+  long best = 0;
+  for (int x = 0; x < 8; ++x)
+    for (int o = x * run, end = std::min(o + run, per_slice * p.n_slices), next; o < end; o = next) {
+      next = std::min(end, (o / per_slice + 1) * per_slice);
+      const int first = o % per_slice, last = (next - 1) % per_slice, cols = last / p.n_rowb - first / p.n_rowb + 1;
+      best += cols * col + std::min(p.n_rowb, cols == 1 ? last - first + 1 : cols == 2 ? p.n_rowb - first % p.n_rowb + last % p.n_rowb + 1 : p.n_rowb) * row;
+    }
+  p.lg_per = __builtin_ctz(8 / p.n_slices);
+  for (int lc = p.lg_per; lc >= 0; --lc) {
+    const int r = cdiv(p.n_rowb, 1 << (p.lg_per - lc)), c = cdiv(p.n_colb, 1 << lc);
+    const long bytes = p.n_slices * (cdiv(p.n_colb, c) * (p.n_rowb * row) + cdiv(p.n_rowb, r) * (p.n_colb * col));
+    if (r * c > run || run > 4096 || r > 256 || bytes > best || (p.rows_xcd && bytes == best)) continue;      // (4096, 256: TilePlan's rows_inv)
+    best = bytes;
+    p.rows_xcd = r; p.cols_xcd = c; p.lg_colg = lc; p.rows_inv = (1u << 20) / r + 1;
+  }
 }
 static int plan_wgs(const TilePlan& p) { return p.n_colb * p.n_rowb * p.n_slices; }
 
@@ -751,7 +766,7 @@ static int launch_gemm_tile(const GemmArgs& g, const GemmPick& c, hipStream_t st
 // (Sizes outside the fit: gate / up and k-split outputs of up to 64 rows, QKV and output projection up to 512, and the output projection as long
 // as tiles of 4 x 4 fill one round.)
 template <int EPI>
-static GemmPick pick_gemm(const GemmArgs& g, int cus, int max_slices) {
+static GemmPick pick_gemm_cut(const GemmArgs& g, int cus, int max_slices) {
   const int KT = g.K / 32, MT = cdiv(g.M, 16);
   constexpr bool whole_k = EPI == EPI_QKV || EPI == EPI_RESID;
   if (KT >= 8 && (max_slices == 1 || g.N % 64 == 0)) {
@@ -773,6 +788,12 @@ static GemmPick pick_gemm(const GemmArgs& g, int cus, int max_slices) {
   if (!c.rt)                                             // more than one round whatever the tile: the largest usable one
     for (const auto& t : shapes)
       if (usable(t)) { c.rt = t[0]; c.ct = t[1]; c.p = gemm_plan<EPI>(g, c.rt, c.ct, 1); }
+  return c;
+}
+template <int EPI>
+static GemmPick pick_gemm(const GemmArgs& g, int cus, int max_slices) {
+  GemmPick c = pick_gemm_cut<EPI>(g, cus, max_slices);
+  place_tiles(c.p, c.rt, c.ct);
   return c;
 }
 // Returns the number of k-slices (1 unless `max_slices` allows more: outputs that are k-split partials); EPI_RESID: of the pieces of a
@@ -1630,12 +1651,11 @@ extern "C" int ssd_trace_barriers(ssd_kv* kv, int enable, void* stream, unsigned
 }
 
 // ------------------------------------------------------------------------------------------------ launch plans (host only)
-extern "C" int ssd_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4]) {
-  if (!plan || rows < 1 || rows > MAX_ROWS || n < 1 || k < 32 || k % 32 || cus < 1) return fail(SSD_EINVAL, "bad GEMM size");
+static int gemm_pick_of(int kind, int rows, int n, int k, int cus, GemmPick& c) {
+  if (rows < 1 || rows > MAX_ROWS || n < 1 || k < 32 || k % 32 || cus < 1) return fail(SSD_EINVAL, "bad GEMM size");
   GemmArgs g;
   memset(&g, 0, sizeof g);
   g.M = rows; g.N = n; g.K = k;
-  GemmPick c;
   switch (kind) {
     case PROF_QKV: c = pick_gemm<EPI_QKV>(g, cus, 1); break;
     case PROF_O: c = pick_gemm<EPI_RESID>(g, cus, 1); break;
@@ -1644,8 +1664,26 @@ extern "C" int ssd_gemm_plan(int kind, int rows, int n, int k, int cus, int plan
     case PROF_HEAD: c = pick_gemm<EPI_PARTIAL>(g, cus, 1); break;
     default: return fail(SSD_EINVAL, "no GEMM of kind %d", kind);
   }
+  return SSD_OK;
+}
+
+extern "C" int ssd_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4]) {
+  GemmPick c;
+  if (!plan) return fail(SSD_EINVAL, "bad GEMM size");
+  if (int rc = gemm_pick_of(kind, rows, n, k, cus, c)) return rc;
   plan[0] = c.kernel; plan[1] = c.rt; plan[2] = c.ct; plan[3] = c.p.n_slices;
   return SSD_OK;
+}
+
+extern "C" int ssd_gemm_blocks(int kind, int rows, int n, int k, int cus, int* blocks, int cap) {
+  GemmPick c;
+  if (cap > 0 && !blocks) return fail(SSD_EINVAL, "no room for the blocks");
+  if (int rc = gemm_pick_of(kind, rows, n, k, cus, c)) return rc;
+  for (int w = 0; w < std::min(cap, 8 * c.p.per_xcd); ++w) {
+    int* b = blocks + 3 * (size_t)w;
+    if (!tile_block(c.p, w, b[0], b[1], b[2])) b[0] = b[1] = b[2] = -1;
+  }
+  return 8 * c.p.per_xcd;
 }
 
 extern "C" int ssd_attention_plan(int head_dim, int n_q_heads, int n_kv_heads, int n_seqs, int rows, int prompt_positions, int cus, int plan[3]) {

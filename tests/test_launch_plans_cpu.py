@@ -52,6 +52,38 @@ def test_every_gemm_size_has_a_plan(lib):
     assert lib.ssd_gemm_plan(QKV, 1025, 32, 32, 256, plan) == -1
 
 
+@pytest.mark.parametrize("kind", [QKV, O, GATE_UP, DOWN, HEAD])
+def test_placement_of_blocks_on_the_xcds(lib, kind):
+    """Every block of the output goes to exactly one workgroup, and what the XCDs' caches fetch (a row block's activations, four bytes an input,
+    by every XCD that has a block of those rows; a column block's weights, two bytes) is never more than where each XCD takes a contiguous run of
+    the order (slice, column block, row block), nor are its workgroups."""
+    plan, blocks = (C.c_int * 4)(), (C.c_int * (3 * 65536))()
+
+    def fetched(of_xcd, rt, ct):
+        return sum(64 * rt * len({(s, r) for _, r, s in b}) + 32 * ct * len({(s, c) for c, _, s in b}) for b in of_xcd)
+
+    for rows in (1, 24, 65, 97, 200, 369, 477, 512, 600, 960, 1024):
+        for n, k in ((896, 896), (1152, 896), (2048, 1536), (4864, 896), (8960, 1536), (896, 4864), (1536, 8960), (6564, 896), (352, 64), (96, 32)):
+            for cus in (256, 64, 1):
+                assert lib.ssd_gemm_plan(kind, rows, n, k, cus, plan) == 0
+                _, rt, ct, slices = plan
+                wgs = lib.ssd_gemm_blocks(kind, rows, n, k, cus, blocks, 65536)
+                assert 0 < wgs <= 65536 and wgs % 8 == 0
+                of_xcd = [[], [], [], [], [], [], [], []]
+                for w in range(wgs):
+                    if blocks[3 * w] >= 0:
+                        of_xcd[w % 8].append(tuple(blocks[3 * w:3 * w + 3]))
+                tiles = -(-n // 16) * (2 if kind == GATE_UP else 1)
+                n_col, n_row = -(-tiles // ct), -(-rows // (16 * rt))
+                want = [(c, r, s) for s in range(slices) for c in range(n_col) for r in range(n_row)]
+                assert sorted(b for x in of_xcd for b in x) == sorted(want)
+                run = -(-len(want) // 8)
+                assert fetched(of_xcd, rt, ct) <= fetched([want[x * run:(x + 1) * run] for x in range(8)], rt, ct), (rows, n, k, cus, tuple(plan))
+                assert max(map(len, of_xcd)) <= run
+    assert lib.ssd_gemm_blocks(1, 16, 32, 32, 256, blocks, 1) == -1 and lib.ssd_gemm_blocks(QKV, 16, 32, 32, 256, None, 1) == -1
+    assert lib.ssd_gemm_blocks(QKV, 16, 32, 32, 256, None, 0) > 0
+
+
 @pytest.mark.parametrize("hd,nq,nkv,seqs,rows,positions,want", [
     # test_prompt_attention_where_later_scores_exceed_the_first
     (64, 10, 2, 1, 1024, 1024, (4, 2, 16)), (64, 10, 2, 1, 1024, 3072, (4, 4, 48)), (64, 4, 2, 1, 1024, 1024, (2, 4, 8)),
