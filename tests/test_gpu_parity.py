@@ -328,11 +328,20 @@ def test_qkv_projection_of_more_than_512_rows(nq, nkv, hd, rows):
     (256, 7680, 4, 1, 257, {"gate_up": (1, 8, 16)}),
     (768, 128, 40, 2, 385, {"qkv": (2, 4, 6)}),
     (1536, 3648, 4, 1, 129, {"down": (2, 8, 6)}),
-    (512, 64, 40, 2, 577, {"qkv": (1, 4, 8)})])
+    (512, 64, 40, 2, 577, {"qkv": (1, 4, 8)}),
+    (896, 4864, 4, 1, 1009, {"gate_up": (2, 16, 10), "down": (2, 8, 7)}),
+    (288, 8768, 4, 1, 385, {"gate_up": (2, 16, 10)}),
+    (320, 8768, 4, 1, 385, {"gate_up": (2, 16, 10), "down": (1, 4, 6)}),
+    (352, 8768, 4, 1, 385, {"gate_up": (2, 16, 10)}),
+    (2048, 2656, 4, 1, 257, {"down": (2, 8, 7)}),
+    (1856, 2944, 4, 1, 385, {"down": (2, 8, 8)}),
+    (256, 1824, 4, 1, 17, {"down": (3, 2, 2)}),
+    (1088, 1824, 4, 1, 17, {"down": (3, 4, 4)})])
 def test_projections_at_the_tiles_of_the_fit(d, ffn, nq, nkv, rows, tiles):
     """The tiles that widths of whole 64 columns and at least eight k-tiles take, each with a ragged last block of rows and, where the
-    width allows, of columns; k ranges that leave every number of k-tiles behind the loop.  (8 x 12 and 16 x 10 of gate / up and 8 x 7, 8 x 8
-    and 8 x 12 of down need full-size models: test_gpu_fullsize.py.)"""
+    width allows, of columns; k ranges that leave every number of k-tiles behind the loop.  The large tiles (16 x 10 of gate / up, 8 x 7 and
+    8 x 8 of down, in four k-slices) go round their loop twice and more; the last two sizes leave the last of eight slices one k-tile.
+    (8 x 12 of gate / up and 8 x 12 of down need full-size models: the batch of the 1.5B shape in test_gpu_fullsize.py.)"""
     import ctypes
     import paper_2505_15380_amd as ssd
     size = {"qkv": (0, (nq + 2 * nkv) * 64, d), "o": (2, d, nq * 64), "gate_up": (3, ffn, d), "down": (4, d, ffn)}
