@@ -434,6 +434,36 @@ def test_sums_of_down_projection_partials(d, ffn):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n_prefix", [12, 1540])
+def test_handed_over_words_whose_value_is_zero(n_prefix):
+    """Every kind of value that one workgroup hands another as a word which is not zero, being zero: embedding rows, products with a norm's gain
+    and sums of squares (every other token's embedding is zero, every fifth gain), queries of a whole head, halves of the new keys and values,
+    residual columns behind the output and the down projection; in launches of 1 to 16 rows on one cache, which use both sets of the words, with
+    attention in one part and in two."""
+    from tests.parity import Pair, loud_weights, verify_parity_step
+    shape = dict(n_layers=2, d_model=96, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=41, n_embed=43, dtype="bf16",
+                 qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
+    w = loud_weights(shape, 97)
+    w["embed"][::2] = 0.0
+    w["final_norm"][::5] = 0.0
+    zero = np.r_[0:64, 128:144, 160:176, 192:224]            # of q head 0, of the keys (both dims of a rotated pair), of the values
+    for l in range(2):
+        w[f"l{l}.ln1"][::5] = w[f"l{l}.ln2"][::5] = 0.0
+        w[f"l{l}.wqkv"][zero] = 0.0
+        w[f"l{l}.bqkv"][zero] = 0.0
+        w[f"l{l}.wo"][::3] = 0.0
+        w[f"l{l}.wdown"][::3] = 0.0
+    pair = Pair(None, 0, n_prefix + 96, max_rows=16, shape=shape, weights=w, store="bf16")
+    rng = np.random.default_rng(98)
+    pair.prefill(0, rng.integers(0, 43, n_prefix))
+    for s, K in enumerate((0, 1, 4, 7, 8, 15, 0, 8)):
+        verify_parity_step(pair, dict(beta=0.3, seed=99), K, s, rng, 2.0 ** -4, 2.0 ** -4)
+        assert pair.kv.last_forward_path() in (3, 4), "the barrier-free persistent kernel did not run"
+        pair.check_rows(0, 2.0 ** -7)
+    pair.check_free_stack()
+
+
+@pytest.mark.gpu
 def test_barrier_and_barrier_free_kernels_agree(monkeypatch):
     """Same model, prefix and drafts through both persistent kernels: logits agree to rounding (they share the
     arithmetic definitions but not every summation order), decisions given equal probabilities are covered above."""
