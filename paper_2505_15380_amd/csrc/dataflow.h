@@ -423,8 +423,8 @@ constexpr int DF_PACK_ROWS = 8;
 // operands: units arrive well before their operands do, so the weights' HBM latency is hidden by that wait.
 // Returns true if the workgroup has to leave (timeout somewhere in the grid).
 template <int EPI, int SB>
-__device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag, const DPhase& ph, uint32_t* lds,
-                                              const int* srow, int* sdead, int slot) {
+__device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const DPhase& ph, uint32_t* lds, const int* srow, int* sdead,
+                                              int slot) {
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -436,7 +436,7 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const uint32_t tag
   float (*red)[2][256] = (float (*)[2][256])((float*)(lds + DF_AW + DF_SQ_WORDS) + usel * 2048);
   const int M = a.rows.M;
   const int KT = ph.K >> 5, ntiles = (ph.N + 15) >> 4;
-  const int arow = lane & 15, g = lane >> 4;
+  const int g = lane >> 4;
   const int row = ut >> 4, col = ut & 15;
   const int rounds = (ph.items + NU - 1) / NU;
   for (int rd = 0; rd < rounds; ++rd) {
@@ -610,7 +610,7 @@ __device__ __forceinline__ void df_prefetch_down(const DArgs& a, const void* wdo
 }
 
 template <int SB, typename CLEAR>
-__device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag, const DPhase& ph, const void* wdown, const float* part, CLEAR clear,
+__device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const DPhase& ph, const void* wdown, const float* part, CLEAR clear,
                                              uint32_t* lds, uint32_t* sact, int* sdead, int slot) {
   constexpr int C = df_sum_cols<SB>();
   int tid = threadIdx.x;
@@ -623,7 +623,7 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
   float (*red)[2][256] = (float (*)[2][256])((float*)(lds + DF_AW + DF_SQ_WORDS) + usel * 2048);
   const int M = a.rows.M;
   const int KT = ph.K >> 5, ntiles_d = a.d >> 4, KTd = a.ffn >> 5;
-  const int arow = lane & 15, g = lane >> 4, c16 = lane & 15;
+  const int g = lane >> 4, c16 = lane & 15;
   const int row = ut >> 4, col = ut & 15;
   const int rounds = (ph.items + NU - 1) / NU;
   for (int rd = 0; rd < rounds; ++rd) {
@@ -690,7 +690,7 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const uint32_t tag,
     // ---- down projection of the workgroup's 32 columns: wave takes output tiles wave, wave + 8, ...
     if ((rd * NU + blockIdx.x * 2) < ph.items) {
       u32x4 xh = u32x4{0u, 0u, 0u, 0u}, xl = xh;
-      if (arow < M) frag_from_lds(sact + arow * 36 + g * 8, xh, xl);
+      if (c16 < M) frag_from_lds(sact + c16 * 36 + g * 8, xh, xl);
       const bf16x8 ah = __builtin_bit_cast(bf16x8, xh), al = __builtin_bit_cast(bf16x8, xl);
       // Computed transposed: a lane holds four consecutive columns of row c16.  They go out by way of LDS, row by row: a wave's seven tiles of a
       // row with one store, 128 contiguous bytes per tile.  (Straight from the registers, two stores per tile of which most lanes are masked, this
@@ -776,7 +776,7 @@ __device__ __forceinline__ float df_sum_blocks(float s) {
   return s + dpp_f<0x4E>(s);                               // quad_perm: lane ^ 2
 }
 template <int C>
-__device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const uint32_t tag, int layer, const float* part, const uint32_t* h_in,
+__device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const float* part, const uint32_t* h_in,
                                                 uint32_t* h_out, uint32_t* hg_out, uint32_t* sq_out, const float* gain_next, int shift,
                                                 uint32_t* lds, int* sdead, int slot) {
   constexpr int TB = DfPartials<C>::TB, CS = C < 32 ? C : 32;        // columns of a sum of squares
@@ -1532,7 +1532,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     if (g_q) {
       const DArgs& a = df_args();
       const DPhase cur = make_qkv(a, l);
-      if (df_gemm_phase<PE_QKV, SB>(a, tag, cur, lds, srow, &sdead, s0)) return;
+      if (df_gemm_phase<PE_QKV, SB>(a, cur, lds, srow, &sdead, s0)) return;
     }
     if (g_a) {
       const DArgs& a = df_args();
@@ -1541,7 +1541,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     if (g_o) {
       const DArgs& a = df_args();
       const DPhase cur = make_o(a, l);
-      if (df_gemm_phase<PE_RESID, SB>(a, tag, cur, lds, srow, &sdead, s0 + 4)) return;
+      if (df_gemm_phase<PE_RESID, SB>(a, cur, lds, srow, &sdead, s0 + 4)) return;
     }
     auto clear = [&]() {
       const DArgs& a = df_args();
@@ -1553,7 +1553,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
     } else {
       const DArgs& a = df_args();
       const DPhase cur = make_swiglu(a, l);
-      if (df_mlp_phase<SB>(a, tag, cur, layer_ptrs(a, l).wdown, a.part + (size_t)(l & 1) * a.st_part, clear, lds, sact, &sdead, s0 + 6)) return;
+      if (df_mlp_phase<SB>(a, cur, layer_ptrs(a, l).wdown, a.part + (size_t)(l & 1) * a.st_part, clear, lds, sact, &sdead, s0 + 6)) return;
     }
     if (g_q && g_r && l + 1 < L) {
       const DArgs& a = df_args();
@@ -1563,14 +1563,14 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
       const DArgs& a = df_args();
       const size_t hi = (size_t)(2 * l + 1);
       const float* gain_next = l + 1 < L ? layer_ptrs(a, l + 1).ln1 : a.final_norm;
-      if (df_reduce_phase<df_sum_cols<SB>()>(a, tag, l, a.part + (size_t)(l & 1) * a.st_part, a.h + set + hi * a.st_h, a.h + set + (hi + 1) * a.st_h,
+      if (df_reduce_phase<df_sum_cols<SB>()>(a, a.part + (size_t)(l & 1) * a.st_part, a.h + set + hi * a.st_h, a.h + set + (hi + 1) * a.st_h,
                           a.hg + set + (hi + 1) * a.st_h, a.sq + set + (hi + 1) * a.st_sq, gain_next, s_red, lds, &sdead, s0 + 8)) return;
     }
   }
   if (a.with_head && g_l) {
     const DArgs& a = df_args();
     const DPhase cur = make_head(a);
-    if (df_gemm_phase<PE_LOGITS, SB>(a, tag, cur, lds, srow, &sdead, 2 + L * 10)) return;
+    if (df_gemm_phase<PE_LOGITS, SB>(a, cur, lds, srow, &sdead, 2 + L * 10)) return;
   }
   if (g_r) {
     const DArgs& a = df_args();
