@@ -1015,8 +1015,8 @@ __device__ __forceinline__ void df_reserve_blocks(const DArgs& a, const int tag_
 
 // ------------------------------------------------------------------------------------------------ attention
 // Item = (sequence, kv head, part of the keys, tile of 16 query rows) on a workgroup; the query rows of a sequence are its R
-// rows times the G query heads of the group, row index qr = j * G + head-in-group.  Wave w walks chunks w, w + 8, w + 16 (of 64
-// keys) of its part with a running (max, sum, weighted values) per row and the eight waves meet once in LDS.  Scores are kept
+// rows times the G query heads of the group, row index qr = j * G + head-in-group.  Wave w takes chunks w, w + 8, w + 16 (of 64
+// keys) of its part: all their scores, one maximum and one sum per row, the weighted values; the eight waves meet once in LDS.  Scores are kept
 // in the base-2 domain (scale * log2 e folded in), so that the exponentials are single instructions.
 //
 // How a row's keys are cut follows from its position alone, so that it has the same bits alone, in a verification, in a captured
@@ -1025,7 +1025,7 @@ __device__ __forceinline__ void df_reserve_blocks(const DArgs& a, const int tag_
 // end of df_attn_phase).  Merging costs a hand-over and about 2.5 us per layer, a third round of chunks 1.2: hence one part as far
 // as three rounds reach, and two rounds beyond.  The host only provides the workgroups, from its bound of the lengths: those
 // without keys have nothing to do.  Where rows of one sequence lie on both sides of the line, part 0 walks its third round too,
-// masked for the rows beyond (their maximum, sum and values keep their bits: factors of 1, terms of 0).
+// masked for the rows beyond (their maximum, sum and values keep their bits: scores of -inf, terms of 0).
 constexpr int DF_ONE_CHUNKS = 24, DF_ONE_PART = 64 * DF_ONE_CHUNKS, DF_PART_CHUNKS = 16;
 __host__ __device__ constexpr int df_parts(int positions) {     // parts of a row that attends to this many positions
   return positions <= DF_ONE_PART ? 1 : (positions + 64 * DF_PART_CHUNKS - 1) / (64 * DF_PART_CHUNKS);

@@ -258,9 +258,9 @@ __device__ __forceinline__ void sched_interleave() {
 // that all waves need go from memory to LDS with direct loads (16 bytes per lane, a fragment per instruction, no
 // registers), NBUF k-tiles ahead, and from there into registers one k-tile ahead, beside the matrix instructions.  One barrier per k-tile: it is
 // passed when every wave has read k-tile k, whose buffer the next request then overwrites, and every wave's share of k-tile k + 1 has arrived.
-// What bounds it with many rows is power: gate / up of 1024 rows of the 0.5B shape (16 x 10) 35 us; a k-tile takes 1450 cycles where the matrix
-// instructions need 1280, but at 1.6 GHz instead of 2.4 (the same instructions on registers alone sustain 2.1 GHz, with the reads from LDS 2.0;
-// 32 x 32 x 16 instructions 1.8).  3 us of it are launch and first operands, 4 the epilogue.  With few rows it is latency.  Ahead of the waits, the order
+// What bounds it with many rows, by clock stamps: gate / up of 1024 rows of the 0.5B shape (16 x 10) 33.6 us, of which the loop is 20.8.  A k-tile takes 1460 cycles
+// where its matrix instructions need 1280, at 1.96 GHz; the same instructions from registers alone settle at 2.06 GHz, with the reads from LDS at
+// 1.94 (28 k-tiles of them by themselves run at 2.27).  3.5 us are first operands, 3.3 the epilogue, 5 the launch and the drain.  With few rows it is latency.  Ahead of the waits, the order
 // and the reads above, in a forward: 35.8 -> 34.5 us; 8 x 7 of down 21.7 (k_gemm_block) -> 20.8; output projection 10.6 (k_gemm_kwave) -> 10.0.
 template <int EPI, int TM, int TN, int W, int NBUF, int UA, int MINB>
 __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan p) {

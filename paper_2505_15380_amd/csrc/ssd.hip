@@ -641,7 +641,7 @@ struct LdsOptIn {
 // layers' launches in prompts of 24 to 1024 rows of both model shapes (29 sizes each): of a launch, per k-tile, and per k-tile for each of a compute
 // unit's workgroups.  Partial outputs cost their write at 4.2 TB/s and their read at 5.  The shape that is picked is 0.4 % (gate / up, output
 // projection) to 1.4 % (QKV) slower on average than the fastest of 19 to 25 shapes at each size, up to 12 % where two are close; those that
-// are left out were nowhere needed for that.  (Other widths follow the same figures; none was measured.  A kernel launched again and again by
+// are left out were nowhere needed for that.  (Other widths of whole 64 columns follow the same figures; none of those was measured.  A kernel launched again and again by
 // itself is up to 2 us faster than between the others, and not equally so: figures from such runs picked shapes that were slower in a forward.)
 enum GemmKernel { KERNEL_KWAVE, KERNEL_BLOCK, KERNEL_TILE, KERNEL_TILE_DEEP };      // (deep: eight k-tiles in flight instead of four)
 struct GemmShape { int rt, ct, w; GemmKernel kernel; float launch, per_kt, per_wg; };       // row tiles x column slots, waves
@@ -667,8 +667,8 @@ static auto gemm_shapes() {
                                      {4, 4, 4, D, 4.94f, 0.f, 0.144f}, {4, 6, 4, D, 4.59f, 0.221f, 0.f}}};
 }
 // Sizes whose k range is shorter than eight k-tiles, and k-split outputs of a width that is no multiple of 64, keep the shapes that they had
-// before: no such size was in the fit, no configuration has one, and the tests of ragged tiles pin these.  (Outside the fit the new shapes are
-// mostly the faster ones too, by 0 to 30 % at 23 sizes that the tests use: what a user of such a width could still gain.)
+// before: no such size was in the fit, no configuration has one, and the tests of ragged tiles hold each of them to its shape here.  (This costs a user of such
+// a width time: at 23 of the tests' sizes the shapes above were mostly the faster ones, by 0 to 30 %.)
 template <int EPI>
 static auto gemm_shapes_ragged() {
   constexpr GemmKernel B = KERNEL_BLOCK, T = KERNEL_TILE;

@@ -119,7 +119,7 @@ def test_rollback_beyond_the_device_length_is_refused():
 
 
 def test_launch_numbering_restarts_before_its_limit():
-    """The hand-over words of the barrier-free kernel are tagged with the launch number (< 2^25); the host clears the
+    """The attention's partial results and the new keys' blocks of the barrier-free kernel are tagged with the launch number (< 2^25); the host clears the
     workspace and restarts the numbering before the limit, and verification stays in lockstep with the oracle."""
     import paper_2505_15380_amd as ssd
     from tests.parity import verify_parity_step

@@ -397,9 +397,9 @@ def test_mini_bf16_attention_without_parts(n_prefix, K, monkeypatch):
 @pytest.mark.parametrize("flight,K", [("2", 0), ("2", 7), ("4", 3), ("4", 7), ("10", 7), ("16", 0), ("18", 0), ("2", 12),
                                       ("", 1), ("", 3)])
 def test_mini_bf16_operand_staging_flights(flight, K, monkeypatch):
-    """The barrier-free kernel is instantiated per number of tagged words a thread keeps in flight while it stages GEMM
-    operands (chosen per launch from the row count): every size, 2 and 4 also with rows that need several flights, more
-    than the 8 rows up to which a size can be asked for, and the launch's own choice."""
+    """The barrier-free kernel is instantiated per number of rows that it keeps in flight while it stages GEMM operands (2, 4, 6, 8, 10 for
+    SSD_DF_FLIGHT=2, 4, 10, 16, 18; chosen per launch from the row count): every instantiation, those of 2 and 4 rows also with rows that
+    need several flights, more than the 8 rows up to which one can be asked for, and the launch's own choice."""
     from tests.parity import run_verify_parity
     if flight:
         monkeypatch.setenv("SSD_DF_FLIGHT", flight)
