@@ -989,7 +989,8 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   ProfScope ps(PROF_PERSISTENT, st);
   kv->last_whole = kv->attn_whole && max_len + 16 <= DF_ONE_PART;      // (reported only)
   // The smallest instantiation whose flight of an operand staging holds the rows, where its sum tasks (of 8, 32, 32, 64, 64 columns) go well: those of
-  // two rows in one round (a second one takes 2 us, tasks of 32 columns 1.1), those of 10 on the workgroups with MLP items; 2 also needs room for its sums of squares.
+  // two rows in one round (a second one takes 2 us, tasks of 32 columns 1.1; with 224 tasks on 226 workgroups, beyond 1536 positions at width 896, they are
+  // 1.5 us a layer slower than those of 32 columns all the same), those of 10 on the workgroups with MLP items; 2 also needs room for its sums of squares.
   int sb = M <= 2 && M * (c.d_model / 8) <= std::min(PBLOCK, G) ? 2 : M <= 4 ? 4 : M <= 6 && M * npairs <= g_mlp ? 10 : M <= 8 ? 16 : 18;
   if (kv->df_sb && M <= DF_PACK_ROWS) sb = kv->df_sb;
   if (sb == 2 && M * (c.d_model / 8) > DF_SQ_WORDS) sb = 10;
