@@ -20,10 +20,10 @@
  *     return; outputs are valid after the stream is synchronised.  Calls on one handle must be issued on
  *     one stream (or be externally ordered).
  *     Forwards of at most 16 rows with bf16 storage (ssd_kv_last_forward_path 2 to 4) are one launch whose workgroups, one to a
- *     compute unit, wait for each other.  Two such launches of different handles may overlap on two streams only if the device
- *     has the compute units for both (of 256, a model of width 896 takes 218 to 256, 152 with path 2): else each
- *     may hold units that the other one waits for until their bounded waits give up, which both report as SSD_EHIP.  Issue the forwards
- *     of models that large on one stream, or order the streams.
+ *     compute unit, wait for each other.  Two such launches of different handles on two streams of a process overlap if the device
+ *     has the compute units for both (of 256, a model of width 896 takes 218 to 256, 152 with path 2), else the later one is ordered
+ *     behind the other stream.  Graphs that a caller captures around these calls, and other processes on the same device, are not seen: there
+ *     each launch may hold units that the other one waits for until their bounded waits give up, which both report as SSD_EHIP; order them.
  *   - Return value: SSD_OK (0) or a negative error code; ssd_last_error() gives a message for the last
  *     failure on the calling thread.  Arguments are validated on the host before anything is launched;
  *     nothing throws or aborts across this boundary.

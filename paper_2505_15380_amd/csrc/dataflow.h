@@ -56,7 +56,6 @@
 namespace ssd {
 
 typedef unsigned long long u64;
-constexpr int DF_AW = 21504;              // LDS words of the operand staging area (84 KB)
 constexpr int DF_ATT_ROWS = 256;          // query rows of a sequence (rows x heads of a group): at most 16 tiles of 16
 constexpr int DF_NPF = 5;                 // attention parts merged per flight
 constexpr long DF_SPIN_LIMIT = 1L << 18;
@@ -65,12 +64,37 @@ constexpr int DF_SQ_WORDS = 1024;
 constexpr int DF_RED_WORDS = 2 * 2048;
 constexpr int DF_QS = 68;                 // words from one row to the next of the queries and of the merge buffers in LDS: rows 64
                                           // words apart would put a fragment's 16 rows into the same banks
-constexpr int DF_ATT_V = 16 * DF_QS + 512 + 512 + 8 * 16 * DF_QS + 256;           // Q | new K | new V | merge O | merge m,l |
-constexpr int DF_ATT_WORDS = DF_ATT_V + 8 * 2048;                                 // values of a chunk per wave
-constexpr int DF_DN = 7;                  // down-projection output tiles a wave keeps prefetched
-constexpr int DF_TR = DF_AW + DF_SQ_WORDS + DF_RED_WORDS;                         // the MLP's partials on their way out: per wave [8 rows][DF_DN tiles][16]
-constexpr int DF_LDS_WORDS = DF_TR + 8 * 8 * DF_DN * 16;
-static_assert(DF_ATT_WORDS <= DF_LDS_WORDS && DF_LDS_WORDS <= 39 * 1024, "");
+// The two forms of the kernel: head size 64 (k_forward_dataflow), and 128 for wider models (k_forward_wide).
+struct DfNarrow {
+  static constexpr bool WIDE = false;
+  static constexpr int HD = 64, HDL = 6, NH = 1;   // head size, its logarithm, and in how many pieces of 64 dims the attention's output is taken
+  static constexpr int PF = PF_K;         // k-tiles of weights a wave of a unit keeps requested
+  static constexpr int XB = PF_K;         // k-tiles whose operands it reads from LDS at once
+  static constexpr int AW = 21504;        // LDS words of the operand staging area (84 KB)
+  static constexpr int QW = DF_QS;        // words from one row of the queries to the next in LDS
+  static constexpr int DN = 7;            // down-projection output tiles a wave keeps prefetched
+  static constexpr int ACT_PITCH = 36;    // words from one row of a workgroup's SwiGLU output to the next
+  static constexpr int TR = AW + DF_SQ_WORDS + DF_RED_WORDS;                        // the MLP's partials on their way out: per wave [8 rows][DN tiles][16]
+  static constexpr int KN = 16 * QW, VN = KN + 512, MO = VN + 512, MO_WAVE = 16 * DF_QS, ML = MO + 8 * MO_WAVE, V2 = ML + 256;   // Q | new K | new V | merge O | merge m,l |
+  static constexpr int ATT_WORDS = V2 + 8 * 2048;                                   // values of a chunk per wave
+  static constexpr int LDS_WORDS = TR + 8 * 8 * DN * 16;
+};
+// Head size 128.  28 layers of width 1536 behind 1024 positions, against one launch per operator, seven a layer: one row 1316 -> 676 us, five 1345 -> 770, eight
+// 1372 -> 876, thirteen 1408 -> 1140.  Bound by the weights, 94 MB a layer: the registers of the MLP's 140 workgroups hold 50 of them, the rest streams
+// at 4.8 TB/s when the MLP's operands are there.  Every wave has 12 k-tiles of width 1536 in flight (96 registers) and 12 tiles of the down projection (48).
+// The MLP's partials go out over the staged operands, which nothing reads any more, and a wave's share of attention over the values that it has read.
+struct DfWide {
+  static constexpr bool WIDE = true;
+  static constexpr int HD = 128, HDL = 7, NH = 2, PF = 12, XB = 2, AW = 16 * 1540, QW = 132, DN = 12, ACT_PITCH = 68, TR = 0;
+  static constexpr int MAX_K = 4 * 32 * PF;                // inputs of a projection: a wave keeps all of its k-tiles requested
+  static constexpr int KN = 16 * QW, VN = KN + 1024, ML = VN + 512, V2 = ML + 256, MO = V2, MO_WAVE = 4096;                     // Q | new K | new V (64 dims) | merge m,l |
+  static constexpr int ATT_WORDS = V2 + 8 * 4096;                                                                               // values of two chunks per wave, then merge O
+  static constexpr int LDS_WORDS = ATT_WORDS;
+};
+static_assert(DfNarrow::ATT_WORDS <= DfNarrow::LDS_WORDS && DfNarrow::LDS_WORDS <= 39 * 1024, "");
+static_assert(DfWide::ATT_WORDS <= DfWide::LDS_WORDS && 8 * 8 * DfWide::DN * 16 <= DfWide::AW && DfWide::AW + DF_SQ_WORDS + DF_RED_WORDS <= DfWide::LDS_WORDS && DfWide::LDS_WORDS <= 39 * 1024, "");
+template <int PF>
+struct DfPre { u32x4 b0[PF], b1[PF]; };   // weight fragments of a wave's first PF k-tiles, two tiles
 
 // Which single word a wave watches after a failed first flight (see df_wait_hint): the phases with many consumers (QKV, attention, MLP)
 // watch a word of their OWN operands, the output projection one of the preceding phase's.  (The MLP watching a word of the phase before: one row
@@ -95,12 +119,12 @@ struct DArgs {
   uint32_t* h;            // [2L+1][PR][d]      fp32: residual stream entering layer l at 2l, after attention at 2l+1
   uint32_t* hg;           // [2L+1][PR][d]      operand: h times the gain of the RMSNorm that consumes it
   uint32_t* sq;           // [2L+1][PR][d/8]    fp32: sums of squares of h over 32 columns (after the MLP: over df_sq_cols columns)
-  uint32_t* q;            // [L][PR][nq*64]     operand: rotated queries
-  uint32_t* kvn;          // [L][PR][2][nkv*64] bf16 (| 1 << 16): this launch's keys (rotated) and values
-  uint32_t* attn;         // [L][PR][nq*64]     operand: attention output
+  uint32_t* q;            // [L][PR][nq*HD]     operand: rotated queries (HD: head size)
+  uint32_t* kvn;          // [L][PR][2][nkv*HD] bf16 (| 1 << 16): this launch's keys (rotated) and values
+  uint32_t* attn;         // [L][PR][nq*HD]     operand: attention output
   size_t st_set;          // words from one set to the other
   u64* state;             // the last launch: its number, then (rows << 1 | set)
-  u64* att_p;             // [L][PR][nq][NP][16][6] fp32: per part and 4-dim chunk: 4 weighted values, max, sum
+  u64* att_p;             // [L][PR][nq][NP][HD/4][6] fp32: per part and 4-dim chunk: 4 weighted values, max, sum
   float* part;            // [2][row][d/C][ffn/32][C]: down-projection partials of one 32-column slice of the SwiGLU output each (buffer =
                           // layer parity; C = df_sum_cols, 8 take the room of 16).  What a sum task reads is contiguous: with a
                           // row per workgroup, 112 KB apart, its pieces and all workgroups' stores fell on few memory channels
@@ -113,6 +137,11 @@ struct DArgs {
   int small_stride;       // 2: a small-phase item has a workgroup to itself; 1: two items per workgroup
   uint32_t* bar;          // [64] error flag (sticky until the host reads it); [0], [32] belong to the kernel with grid barriers
   unsigned long long* trace;
+  // the wide form
+  int o_stride;           // small_stride of the output projection's items
+  int mlp_tiles;          // k-tiles of the down projection (32 columns of the SwiGLU output) that an MLP workgroup takes
+  int n_sum;              // partials of an output of the down projection
+  int recip_d, recip_q;   // 2^16 / pieces of 512 words in a row of d or nq * HD words, rounded up
 };
 
 // Tagged words.
@@ -212,6 +241,9 @@ template <int SB>
 constexpr int df_sum_cols() { return SB == 2 ? 8 : SB <= 10 ? 32 : 64; }
 template <int SB>
 constexpr int df_sq_cols() { return SB == 2 ? 8 : 32; }
+// Wide form: loads of four words a thread has in flight, of 512-word pieces dealt out to four quarters of a workgroup: 1, 4, 8 and 16 rows of 1536.
+template <int SB>
+constexpr int df_flight() { return SB == 2 ? 1 : SB <= 10 ? 3 : SB == 16 ? 6 : 12; }
 
 // ------------------------------------------------------------------------------------------------ GEMM phases
 struct DPhase {
@@ -328,6 +360,87 @@ __device__ __forceinline__ bool stage_operand(const DArgs& a, const uint32_t* A,
   return ok;
 }
 
+// The same for the wide form, whose rows are longer than half a workgroup takes at once: the words are dealt out as pieces of 512, and each
+// quarter of the workgroup takes every fourth of them, so that all rows of a launch are in one flight (five rows of width 1536: 15 pieces, four loads a
+// thread).  A piece's place is scalar arithmetic, as above.
+template <int FL, bool RES>
+__device__ __forceinline__ bool stage_operand_wide(const DArgs& a, const uint32_t* A, int K, const uint32_t* sq, int nsq, uint32_t* As, float* sqs, int tid,
+                                                   const uint32_t* x0, const uint32_t* x1, float& xo0, float& xo1, const uint32_t* hint) {
+  const int M = a.rows.M, nS = sq ? M * nsq : 0, per_row = (K + 511) >> 9, pieces = M * per_row, recip = K == a.d ? a.recip_d : a.recip_q;
+  const df_rsrc rs = df_make_rsrc(a.tw);
+  const uint32_t a_off = (uint32_t)(A - a.tw) * 4u;
+  const int quarter = __builtin_amdgcn_readfirstlane(tid >> 7), c = (tid & 127) * 4;
+  uint32_t* err = a.bar + 64;
+  bool ok = true;
+  auto give_up = [&](long& spins) -> bool {
+    if (spins == 0 && hint) df_wait_hint(hint, err);
+    if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, AG) != 0)) {
+      __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, AG);
+      ok = false;
+      return true;
+    }
+    __builtin_amdgcn_s_sleep(1);
+    return false;
+  };
+  uint32_t w = 1u, h0 = 1u, h1 = 1u;
+  if (!RES && tid < nS) w = ld_val(sq + tid);
+  if (RES && x0) {
+    h0 = ld_val(x0);
+    h1 = ld_val(x1);
+  }
+  for (int p0 = quarter; p0 < pieces; p0 += 4 * FL) {
+    auto row = [&](int u) { return (p0 + 4 * u) * recip >> 16; };      // (exact: fewer than 2^8 pieces)
+    auto col = [&](int u) { return (p0 + 4 * u - row(u) * per_row) * 512; };
+    uint32_t at = (uint32_t)c * 4u;
+    auto request = [&](int u) -> u32x4 {
+      return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)at, (int)(a_off + (uint32_t)(row(u) * K + col(u)) * 4u), 16 /* sc1 */);
+    };
+    u32x4 v[FL];
+#pragma unroll
+    for (int u = 0; u < FL; ++u) v[u] = p0 + 4 * u < pieces && col(u) + c < K ? request(u) : u32x4{1u, 1u, 1u, 1u};
+    for (long spins = 0;;) {
+      bool late = RES ? min(h0, h1) == 0u : w == 0u;
+#pragma unroll
+      for (int u = 0; u < FL; ++u) late = late || df_any_zero(v[u]);
+      if (!late || give_up(spins)) break;
+      asm volatile("" : "+v"(at) : : "memory");            // (the words may have changed)
+#pragma unroll
+      for (int u = 0; u < FL; ++u)
+        if (df_any_zero(v[u])) v[u] = request(u);
+      if (!RES && w == 0u) w = ld_val(sq + tid);
+      if (RES && h0 == 0u) h0 = ld_val(x0);
+      if (RES && h1 == 0u) h1 = ld_val(x1);
+    }
+    df_loads_done();
+#pragma unroll
+    for (int u = 0; u < FL; ++u)
+      if (p0 + 4 * u < pieces && col(u) + c < K) {
+        uint32_t* to = As + row(u) * (K + 4) + col(u) + c - ((c & 4) >> 1);
+        *(uint2*)to = make_uint2(__builtin_amdgcn_perm(v[u][1], v[u][0], 0x05040100u), __builtin_amdgcn_perm(v[u][3], v[u][2], 0x05040100u));
+        *(uint2*)(to + 4) = make_uint2(__builtin_amdgcn_perm(v[u][1], v[u][0], 0x07060302u), __builtin_amdgcn_perm(v[u][3], v[u][2], 0x07060302u));
+      }
+  }
+  if (!RES) {
+    if (tid < nS) sqs[tid] = __uint_as_float(w);
+    for (int i = PBLOCK + tid; i < nS; i += PBLOCK) {      // (more than 512 sums)
+      w = ld_val(sq + i);
+      for (long spins = 0; w == 0u && !give_up(spins);) w = ld_val(sq + i);
+      sqs[i] = __uint_as_float(w);
+    }
+  }
+  if (RES) {
+    xo0 = __uint_as_float(h0);
+    xo1 = __uint_as_float(h1);
+  }
+  return ok;
+}
+template <int SB, class S, bool RES>
+__device__ __forceinline__ bool df_stage(const DArgs& a, const uint32_t* A, int K, const uint32_t* sq, int nsq, uint32_t* As, float* sqs, int tid,
+                                         const uint32_t* x0, const uint32_t* x1, float& xo0, float& xo1, const uint32_t* hint) {
+  if constexpr (S::WIDE) return stage_operand_wide<df_flight<SB>(), RES>(a, A, K, sq, nsq, As, sqs, tid, x0, x1, xo0, xo1, hint);
+  else return stage_operand<SB, RES>(a, A, K, sq, nsq, As, sqs, tid, x0, x1, xo0, xo1, hint);
+}
+
 // hi / lo fragments (8 consecutive k each) of a lane from 8 staged payload words
 __device__ __forceinline__ void split_words(const u32x4 w0, const u32x4 w1, u32x4& hi, u32x4& lo) {
   hi = u32x4{__builtin_amdgcn_perm(w0[1], w0[0], 0x05040100u), __builtin_amdgcn_perm(w0[3], w0[2], 0x05040100u),
@@ -362,20 +475,13 @@ __device__ __forceinline__ int df_item_of_unit(int unit, int shift, int NU, int 
 // end.  Up to 8 rows (PACK) one instruction takes both: rows 0 .. 7 of its operand are the hi halves, 8 .. 15 the lo halves, and
 // the sums meet across the wave's halves (df_meet: what does not need them comes in between); only rows 0 .. 7 of the result mean anything then.  Half the matrix and half the
 // unpacking instructions: gate / up of one row 1.0 -> 0.7 us of a layer, QKV 1.6 -> 1.2.
-template <bool PACK>
-__device__ __forceinline__ void df_products(const uint32_t* As, int K, int M, int kb, int ke, int lane, const WPre& wl, const u32x4* w0,
+template <bool PACK, class S>
+__device__ __forceinline__ void df_products(const uint32_t* As, int K, int M, int kb, int ke, int lane, const DfPre<S::PF>& wl, const u32x4* w0,
                                             const u32x4* w1, f32x4& acc0, f32x4& acc1) {
   // (lanes of rows that are not there take the last one: what they yield is never looked at)
   const uint32_t* p = As + min(PACK ? lane & 7 : lane & 15, M - 1) * (K + 4) + (lane >> 4) * 8 + (PACK ? (lane & 8) >> 1 : 0);
   f32x4 lo0 = f32x4{0, 0, 0, 0}, lo1 = f32x4{0, 0, 0, 0};
-  // all operand fragments first (their LDS latencies overlap), then the products
-  u32x4 x[PF_K], y[PF_K];                                  // hi and lo halves (PACK: the lane's one of them)
-#pragma unroll
-  for (int u = 0; u < PF_K; ++u) {
-    const int kt = min(kb + u, ke - 1);
-    x[u] = *(const u32x4*)(p + kt * 32);
-    if (!PACK) y[u] = *(const u32x4*)(p + kt * 32 + 4);
-  }
+  constexpr int XB = S::XB;
 #define DF_MULTIPLY(X, Y, B0, B1)                                                                                            \
   {                                                                                                                          \
     const bf16x8 bv0 = __builtin_bit_cast(bf16x8, B0), bv1 = __builtin_bit_cast(bf16x8, B1), fx = __builtin_bit_cast(bf16x8, X); \
@@ -388,9 +494,21 @@ __device__ __forceinline__ void df_products(const uint32_t* As, int K, int M, in
     acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx, bv1, acc1, 0, 0, 0);                                                  \
   }
 #pragma unroll
-  for (int u = 0; u < PF_K; ++u)
-    if (kb + u < ke) DF_MULTIPLY(x[u], y[u], wl.b0[u], wl.b1[u])
-  for (int kt = kb + PF_K; kt < ke; ++kt) {                // waves with more than PF_K k-tiles
+  for (int u0 = 0; u0 < S::PF; u0 += XB) {
+    // all operand fragments first (their LDS latencies overlap), then the products; in the wide form some at a time, there are no registers for all
+    u32x4 x[XB], y[XB];                                    // hi and lo halves (PACK: the lane's one of them)
+#pragma unroll
+    for (int u = 0; u < XB; ++u) {
+      const int kt = min(kb + u0 + u, ke - 1);
+      x[u] = *(const u32x4*)(p + kt * 32);
+      if (!PACK) y[u] = *(const u32x4*)(p + kt * 32 + 4);
+    }
+#pragma unroll
+    for (int u = 0; u < XB; ++u)
+      if (kb + u0 + u < ke) DF_MULTIPLY(x[u], y[u], wl.b0[u0 + u], wl.b1[u0 + u])
+    if (S::WIDE) __builtin_amdgcn_sched_barrier(0);        // (or the reads of all of them are put first)
+  }
+  for (int kt = S::WIDE ? ke : kb + S::PF; kt < ke; ++kt) {          // waves with more than PF k-tiles (wide: none have)
     const u32x4 xk = *(const u32x4*)(p + kt * 32), yk = PACK ? xk : *(const u32x4*)(p + kt * 32 + 4);
     const u32x4 b0 = __builtin_nontemporal_load(w0 + (size_t)kt * 64), b1 = __builtin_nontemporal_load(w1 + (size_t)kt * 64);
     DF_MULTIPLY(xk, yk, b0, b1)
@@ -418,11 +536,22 @@ template <int SB>
 constexpr bool df_pack() { return SB <= 16; }
 constexpr int DF_PACK_ROWS = 8;
 
+// Column tiles of an item: of QKV the tiles of 16 columns that a rotation pairs, of the others two consecutive ones.
+template <int EPI, class S, typename PH>
+__device__ __forceinline__ bool df_gemm_item(const PH& ph, int item, int& t0, int& t1, int& split) {
+  if (!S::WIDE || EPI != PE_QKV) return gemm_item<EPI>(ph, item, t0, t1, split);
+  t0 = 0; t1 = 0; split = 0;
+  if (item >= ph.items) return false;
+  t0 = (item >> 2) * 8 + (item & 3);
+  t1 = t0 + 4;
+  return true;
+}
+
 // One GEMM phase (QKV, output projection, head); the caller skips it for a workgroup none of whose units has an
 // item.  The weight fragments of the unit's item are requested at entry, into registers, before the wait for the
 // operands: units arrive well before their operands do, so the weights' HBM latency is hidden by that wait.
 // Returns true if the workgroup has to leave (timeout somewhere in the grid).
-template <int EPI, int SB>
+template <int EPI, int SB, class S>
 __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const DPhase& ph, uint32_t* lds, const int* srow, int* sdead,
                                               int slot) {
   int tid = threadIdx.x;
@@ -432,8 +561,8 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const DPhase& ph, 
   const int unit = blockIdx.x * 2 + usel, NU = gridDim.x * 2;
   const int uitem = df_item_of_unit(unit, ph.shift, NU, ph.stride);
   uint32_t* As = lds;
-  float* sqs = (float*)(lds + DF_AW);
-  float (*red)[2][256] = (float (*)[2][256])((float*)(lds + DF_AW + DF_SQ_WORDS) + usel * 2048);
+  float* sqs = (float*)(lds + S::AW);
+  float (*red)[2][256] = (float (*)[2][256])((float*)(lds + S::AW + DF_SQ_WORDS) + usel * 2048);
   const int M = a.rows.M;
   const int KT = ph.K >> 5, ntiles = (ph.N + 15) >> 4;
   const int g = lane >> 4;
@@ -442,17 +571,17 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const DPhase& ph, 
   for (int rd = 0; rd < rounds; ++rd) {
     const int item = rd * NU + uitem;
     int t0, t1, split, kb = 0, ke = 0;
-    const bool valid = gemm_item<EPI>(ph, item, t0, t1, split);
+    const bool valid = df_gemm_item<EPI, S>(ph, item, t0, t1, split);
     if (valid) wave_krange(ph, 0, uw, kb, ke);
     const bool has1 = t1 < ntiles;
     const bool live = valid && row < M;
     const int n0 = t0 * 16 + col, n1 = t1 * 16 + col;
     const u32x4* w0 = (const u32x4*)ph.W0 + (size_t)t0 * KT * 64 + lane;
     const u32x4* w1 = (const u32x4*)ph.W1 + (size_t)(has1 ? t1 : t0) * KT * 64 + lane;
-    WPre wl;
+    DfPre<S::PF> wl;
     if (valid) {
 #pragma unroll
-      for (int u = 0; u < PF_K; ++u) {
+      for (int u = 0; u < S::PF; ++u) {
         const int kt = (kb + u < ke) ? kb + u : kb;
         wl.b0[u] = __builtin_nontemporal_load(w0 + (size_t)kt * 64);
         wl.b1[u] = __builtin_nontemporal_load(w1 + (size_t)kt * 64);
@@ -463,9 +592,9 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const DPhase& ph, 
     float2 cs = float2{1.f, 0.f};
     int pos = 0, active = 0, rblk = -1;
     if (EPI == PE_QKV && live) {
-      if (ph.bias) { bias0 = ph.bias[n0]; bias1 = ph.bias[n0 + 32]; }
+      if (ph.bias) { bias0 = ph.bias[n0]; bias1 = ph.bias[n0 + S::HD / 2]; }
       pos = srow[row]; active = srow[16 + row]; rblk = srow[32 + row];
-      cs = a.rope[(size_t)pos * 32 + (n0 & 63)];
+      cs = a.rope[(size_t)pos * (S::HD / 2) + (n0 & (S::HD - 1))];
     }
     if (EPI == PE_RESID && live) { gn0 = ph.gain_next[n0]; gn1 = ph.gain_next[n1]; }
     // ---- operands (both units of the workgroup consume the same rows); the unit that finishes residual rows takes
@@ -474,7 +603,7 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const DPhase& ph, 
     const uint32_t *hx0 = res ? ph.h_in + (size_t)row * ph.N + n0 : nullptr, *hx1 = res ? ph.h_in + (size_t)row * ph.N + n1 : nullptr;
     float hv0 = 0.f, hv1 = 0.f;
     bool ok = true;
-    if (rd == 0) ok = stage_operand<SB, EPI == PE_RESID>(a, ph.A, ph.K, ph.sq, ph.K / df_sq_cols<SB>(), As, sqs, tid, hx0, hx1, hv0, hv1, ph.hint);
+    if (rd == 0) ok = df_stage<SB, S, EPI == PE_RESID>(a, ph.A, ph.K, ph.sq, ph.K / df_sq_cols<SB>(), As, sqs, tid, hx0, hx1, hv0, hv1, ph.hint);
     if (!ok) *sdead = 1;
     __syncthreads();
     df_loads_done();
@@ -482,7 +611,7 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const DPhase& ph, 
     if (rd == 0) DF_STAMP(slot);
     // ---- products
     f32x4 acc0 = f32x4{0, 0, 0, 0}, acc1 = f32x4{0, 0, 0, 0};
-    if (valid) df_products<df_pack<SB>()>(As, ph.K, M, kb, ke, lane, wl, w0, w1, acc0, acc1);
+    if (valid) df_products<df_pack<SB>(), S>(As, ph.K, M, kb, ke, lane, wl, w0, w1, acc0, acc1);
     float inv = 1.0f;                                      // (while the matrix cores work)
     if (ph.sq) {
       float sq = 0.f;
@@ -510,28 +639,28 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const DPhase& ph, 
     if (ph.sq) { v0 *= inv; v1 *= inv; }
     if (EPI == PE_QKV) {
       if (live) {
-        const int head = n0 >> 6, dd = n0 & 63;                      // dd < 32
+        const int head = n0 >> S::HDL, dd = n0 & (S::HD - 1);          // dd < HD / 2
         v0 += bias0; v1 += bias1;
         if (head < a.nq + a.nkv) {
           const float r0 = v0 * cs.x - v1 * cs.y, r1 = v1 * cs.x + v0 * cs.y;
           v0 = r0; v1 = r1;
         }
         if (head < a.nq) {
-          uint32_t* qo = ph.out + (size_t)row * (a.nq * 64) + head * 64 + dd;
+          uint32_t* qo = ph.out + (size_t)row * (a.nq * S::HD) + head * S::HD + dd;
           st_val(qo, operand_word(v0));
-          st_val(qo + 32, operand_word(v1));
+          st_val(qo + S::HD / 2, operand_word(v1));
         } else {
           const int which = head < a.nq + a.nkv ? 0 : 1;
           const int kvh = head - a.nq - which * a.nkv;
           const bf16_t b0 = f_to_bf16(v0), b1 = f_to_bf16(v1);
-          uint32_t* ko = ph.kvn + ((size_t)row * 2 + which) * (a.nkv * 64) + kvh * 64 + dd;
+          uint32_t* ko = ph.kvn + ((size_t)row * 2 + which) * (a.nkv * S::HD) + kvh * S::HD + dd;
           st_val(ko, b0 | 0x10000u);
-          st_val(ko + 32, b1 | 0x10000u);
+          st_val(ko + S::HD / 2, b1 | 0x10000u);
           if (active && rblk >= 0) {
             bf16_t* base = (bf16_t*)a.kv.pool + kv_offset(a.kv, ph.layer, which, rblk, kvh, 0);
             const int tok = pos & 15;
-            if (which == 0) { st_ag(base + tok * 64 + dd, b0); st_ag(base + tok * 64 + dd + 32, b1); }
-            else { st_ag(base + dd * 16 + tok, b0); st_ag(base + (dd + 32) * 16 + tok, b1); }
+            if (which == 0) { st_ag(base + tok * S::HD + dd, b0); st_ag(base + tok * S::HD + dd + S::HD / 2, b1); }
+            else { st_ag(base + dd * 16 + tok, b0); st_ag(base + (dd + S::HD / 2) * 16 + tok, b1); }
           }
         }
       }
@@ -566,13 +695,14 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const DPhase& ph, 
 // Brings the weights of the unit's QKV item into the chip's cache, a word of each 128-byte line: for a workgroup that sums partials just before (16
 // rows), with nothing to do until they come.  It requests the item's weights when its sum is out, and from memory they would arrive later
 // than the operands (0.6 us a layer).
+template <class S>
 __device__ __forceinline__ void df_touch_weights(const DArgs& a, const DPhase& ph) {
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int NU = gridDim.x * 2, KT = ph.K >> 5, ntiles = (ph.N + 15) >> 4;
   int t0, t1, split;
-  if (!gemm_item<PE_QKV>(ph, df_item_of_unit(blockIdx.x * 2 + (wave >> 2), ph.shift, NU, ph.stride), t0, t1, split)) return;
+  if (!df_gemm_item<PE_QKV, S>(ph, df_item_of_unit(blockIdx.x * 2 + (wave >> 2), ph.shift, NU, ph.stride), t0, t1, split)) return;
   const uint32_t* w0 = (const uint32_t*)ph.W0 + (size_t)t0 * KT * 256;
   const uint32_t* w1 = (const uint32_t*)ph.W0 + (size_t)(t1 < ntiles ? t1 : t0) * KT * 256;
   uint32_t x = 0u;
@@ -583,10 +713,11 @@ __device__ __forceinline__ void df_touch_weights(const DArgs& a, const DPhase& p
 // ------------------------------------------------------------------------------------------------ fused MLP
 // Gate/up + SwiGLU + down projection inside one workgroup: its two units produce 32 consecutive columns of the
 // SwiGLU output, which is exactly one k-tile of the down projection; the workgroup multiplies it with that k-tile of
-// every output tile (8 waves x DF_DN tiles) and publishes a partial of the whole row.  The SwiGLU output never
+// every output tile (8 waves x DN tiles) and publishes a partial of the whole row.  The SwiGLU output never
 // leaves the workgroup, and one dependency per layer disappears; the price is ffn/32 partials per output.
 constexpr int df_part_pitch(int C) { return C == 8 ? 64 : 4 * C; }     // bytes from one partial of C columns to the next
-struct WDown { u32x4 b[DF_DN]; };
+template <int DN>
+struct WDown { u32x4 b[DN]; };
 
 // (a zero would be a partial that is not there)
 __device__ __forceinline__ void df_put_partial(df_rsrc r, uint32_t at, const f32x4 x) {
@@ -596,31 +727,32 @@ __device__ __forceinline__ void df_put_partial(df_rsrc r, uint32_t at, const f32
   __builtin_amdgcn_raw_buffer_store_b128(b, r, (int)at, 0, 16 /* sc1 */);
 }
 
-// Fragments (n-tile wave + 8 i, k-tile kt2) of the down projection for i < DF_DN; exactly DF_DN loads.
-__device__ __forceinline__ void df_prefetch_down(const DArgs& a, const void* wdown, int kt2, WDown& wd) {
+// Fragments (n-tile wave + 8 i, k-tile kt2) of the down projection for i < DN; exactly DN loads.
+template <int DN>
+__device__ __forceinline__ void df_prefetch_down(const DArgs& a, const void* wdown, int kt2, WDown<DN>& wd) {
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ntiles = a.d >> 4, KTd = a.ffn >> 5;
 #pragma unroll
-  for (int i = 0; i < DF_DN; ++i) {
-    const int nt = min(wave + 8 * i, ntiles - 1);          // (a wave may have fewer tiles than DF_DN, below 128 columns none)
+  for (int i = 0; i < DN; ++i) {
+    const int nt = min(wave + 8 * i, ntiles - 1);          // (a wave may have fewer tiles than DN, below 128 columns none)
     wd.b[i] = __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + lane);
   }
 }
 
-template <int SB, typename CLEAR>
+template <int SB, class S, typename CLEAR>
 __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const DPhase& ph, const void* wdown, const float* part, CLEAR clear,
                                              uint32_t* lds, uint32_t* sact, int* sdead, int slot) {
-  constexpr int C = df_sum_cols<SB>();
+  constexpr int C = df_sum_cols<SB>(), DN = S::DN;
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int usel = wave >> 2, uw = wave & 3, ut = tid & 255;
   const int unit = blockIdx.x * 2 + usel, NU = a.g_mlp * 2;
   uint32_t* As = lds;
-  float* sqs = (float*)(lds + DF_AW);
-  float (*red)[2][256] = (float (*)[2][256])((float*)(lds + DF_AW + DF_SQ_WORDS) + usel * 2048);
+  float* sqs = (float*)(lds + S::AW);
+  float (*red)[2][256] = (float (*)[2][256])((float*)(lds + S::AW + DF_SQ_WORDS) + usel * 2048);
   const int M = a.rows.M;
   const int KT = ph.K >> 5, ntiles_d = a.d >> 4, KTd = a.ffn >> 5;
   const int g = lane >> 4, c16 = lane & 15;
@@ -636,13 +768,13 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const DPhase& ph, c
     const int n0 = item * 16 + col;
     // the weights of the unit's item and the workgroup's down-projection tiles: requested at entry, they arrive
     // while the workgroup waits for its operands
-    WPre pre;
-    WDown wd;
+    DfPre<S::PF> pre;
+    WDown<DN> wd;
     if (valid) {
       const u32x4* w0 = (const u32x4*)ph.W0 + (size_t)item * KT * 64 + lane;
       const u32x4* w1 = (const u32x4*)ph.W1 + (size_t)item * KT * 64 + lane;
 #pragma unroll
-      for (int u = 0; u < PF_K; ++u) {
+      for (int u = 0; u < S::PF; ++u) {
         const int kt = (kb + u < ke) ? kb + u : kb;
         pre.b0[u] = __builtin_nontemporal_load(w0 + (size_t)kt * 64);
         pre.b1[u] = __builtin_nontemporal_load(w1 + (size_t)kt * 64);
@@ -655,7 +787,7 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const DPhase& ph, c
     }
     float dummy0, dummy1;
     bool ok = true;
-    if (rd == 0) ok = stage_operand<SB, false>(a, ph.A, ph.K, ph.sq, KT, As, sqs, tid, nullptr, nullptr, dummy0, dummy1, ph.hint);
+    if (rd == 0) ok = df_stage<SB, S, false>(a, ph.A, ph.K, ph.sq, KT, As, sqs, tid, nullptr, nullptr, dummy0, dummy1, ph.hint);
     if (!ok) *sdead = 1;
     __syncthreads();
     df_loads_done();
@@ -663,7 +795,7 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const DPhase& ph, c
     if (rd == 0) DF_STAMP(slot);
     f32x4 acc0 = f32x4{0, 0, 0, 0}, acc1 = f32x4{0, 0, 0, 0};
     if (valid)
-      df_products<df_pack<SB>()>(As, ph.K, M, kb, ke, lane, pre, (const u32x4*)ph.W0 + (size_t)item * KT * 64 + lane,
+      df_products<df_pack<SB>(), S>(As, ph.K, M, kb, ke, lane, pre, (const u32x4*)ph.W0 + (size_t)item * KT * 64 + lane,
                                  (const u32x4*)ph.W1 + (size_t)item * KT * 64 + lane, acc0, acc1);
     float sq = 0.f;                                        // (while the matrix cores work)
     if (row < M)
@@ -695,14 +827,14 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const DPhase& ph, c
       // Computed transposed: a lane holds four consecutive columns of row c16.  They go out by way of LDS, row by row: a wave's seven tiles of a
       // row with one store, 128 contiguous bytes per tile.  (Straight from the registers, two stores per tile of which most lanes are masked, this
       // section took 0.8 us with one row, 0.5 so; with nine rows the sums' operands are there 0.8 us earlier.)
-      f32x4 acc[DF_DN];
+      f32x4 acc[DN];
 #pragma unroll
-      for (int i = 0; i < DF_DN; ++i)
+      for (int i = 0; i < DN; ++i)
         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd.b[i]), al, f32x4{0, 0, 0, 0}, 0, 0, 0);
 #pragma unroll
-      for (int i = 0; i < DF_DN; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd.b[i]), ah, acc[i], 0, 0, 0);
+      for (int i = 0; i < DN; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd.b[i]), ah, acc[i], 0, 0, 0);
       const int nW = a.ffn >> 5;
-      float* tr = (float*)(lds + DF_TR) + wave * (8 * DF_DN * 16);
+      float* tr = (float*)(lds + S::TR) + wave * (8 * DN * 16);
       const df_rsrc rp = df_make_rsrc(part);
       const uint32_t row_bytes = (uint32_t)(ceil_div(a.d, C) * nW * df_part_pitch(C));
       auto place = [&](int nt, int q) {                              // of columns 4 q .. 4 q + 3 of a tile
@@ -711,18 +843,18 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const DPhase& ph, c
       };
       // half a wave stores a row: this lane's row of two, tile, and four columns of it
       const int half = lane >> 5, ti = (lane & 31) >> 2, nt_out = wave + 8 * ti;
-      const bool stores = ti < DF_DN && nt_out < ntiles_d;
+      const bool stores = ti < DN && nt_out < ntiles_d;
       uint32_t at = place(nt_out, lane & 3) + (uint32_t)half * row_bytes;
       for (int r0 = 0; r0 < M; r0 += 8) {
         if ((c16 & 8) == r0 && c16 < M)
 #pragma unroll
-          for (int i = 0; i < DF_DN; ++i) *(f32x4*)(tr + ((c16 & 7) * DF_DN + i) * 16 + 4 * g) = acc[i];
-        const float* from = tr + (half * DF_DN + ti) * 16 + 4 * (lane & 3);
+          for (int i = 0; i < DN; ++i) *(f32x4*)(tr + ((c16 & 7) * DN + i) * 16 + 4 * g) = acc[i];
+        const float* from = tr + (half * DN + ti) * 16 + 4 * (lane & 3);
         const int re = min(M, r0 + 8);
-        for (int r = r0; r < re; r += 2, from += 2 * DF_DN * 16, at += 2 * row_bytes)
+        for (int r = r0; r < re; r += 2, from += 2 * DN * 16, at += 2 * row_bytes)
           if (stores && r + half < re) df_put_partial(rp, at, *(const f32x4*)from);
       }
-      for (int nt = wave + 8 * DF_DN; nt < ntiles_d; nt += 8) {      // wider models: the remaining tiles, not prefetched
+      for (int nt = wave + 8 * DN; nt < ntiles_d; nt += 8) {      // wider models: the remaining tiles, not prefetched
         const bf16x8 bv = __builtin_bit_cast(bf16x8, __builtin_nontemporal_load((const u32x4*)wdown + ((size_t)nt * KTd + kt2) * 64 + lane));
         f32x4 x = f32x4{0, 0, 0, 0};
         x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, al, x, 0, 0, 0);
@@ -733,6 +865,126 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const DPhase& ph, c
     if (rd == 0) DF_STAMP(slot + 1);
     __syncthreads();
   }
+  return false;
+}
+
+// The same for the wide form: a workgroup takes `mlp_tiles` (one or two) consecutive k-tiles of the down projection: half the partials (140 of width
+// 1536), and with 280 k-tiles no second round on some of 256 workgroups.  The down projection's weights of both and the first one's gate / up are
+// requested at entry; the second one's gate / up when the registers of the first are free.
+template <int SB, class S, typename CLEAR>
+__device__ __forceinline__ bool df_mlp_wide(const DArgs& a, const DPhase& ph, const void* wdown, const float* part, CLEAR clear,
+                                            uint32_t* lds, uint32_t* sact, int* sdead, int slot) {
+  constexpr int C = df_sum_cols<SB>(), DN = S::DN, AP = S::ACT_PITCH, D1 = SB <= 16 ? 8 : 0, D2 = SB <= 16 ? DN : 8;       // tiles of the second k-tile that registers hold beside the first and its products, and beside the second's
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int usel = wave >> 2, uw = wave & 3, ut = tid & 255;
+  uint32_t* As = lds;
+  float* sqs = (float*)(lds + S::AW);
+  float (*red)[2][256] = (float (*)[2][256])((float*)(lds + S::AW + DF_SQ_WORDS) + usel * 2048);
+  const int M = a.rows.M;
+  const int KT = ph.K >> 5, ntiles_d = a.d >> 4, KTd = a.ffn >> 5;
+  const int g = lane >> 4, c16 = lane & 15;
+  const int row = ut >> 4, col = ut & 15;
+  const int kt0 = blockIdx.x * a.mlp_tiles;
+  const bool two = a.mlp_tiles == 2 && kt0 + 1 < KTd;
+  int kb, ke;
+  wave_krange(ph, 0, uw, kb, ke);
+  DfPre<S::PF> pre;
+  WDown<DN> wd[2];
+  const df_rsrc r0 = df_make_rsrc(ph.W0), r1 = df_make_rsrc(ph.W1), rd = df_make_rsrc(wdown);
+  auto request = [&](int t) {                              // (through descriptors: one register of addresses)
+    const uint32_t at = (uint32_t)((2 * (kt0 + t) + usel) * KT) << 10;
+#pragma unroll
+    for (int u = 0; u < S::PF; ++u) {
+      const uint32_t o = at + ((uint32_t)((kb + u < ke) ? kb + u : kb) << 10);
+      pre.b0[u] = __builtin_amdgcn_raw_buffer_load_b128(r0, lane * 16, (int)o, 2 /* nt */);
+      pre.b1[u] = __builtin_amdgcn_raw_buffer_load_b128(r1, lane * 16, (int)o, 2);
+    }
+  };
+  auto request_down = [&](int t, int i0, int i1) {         // (a wave may have fewer tiles than DN)
+#pragma unroll
+    for (int i = 0; i < DN; ++i)
+      if (i >= i0 && i < i1) wd[t].b[i] = __builtin_amdgcn_raw_buffer_load_b128(rd, lane * 16, (int)((uint32_t)(min(wave + 8 * i, ntiles_d - 1) * KTd + kt0 + t) << 10), 2);
+  };
+  request(0);
+  request_down(0, 0, DN);
+  if (two) request_down(1, 0, D1);
+  df_loads_done();
+  clear();
+  float dummy0, dummy1;
+  const bool ok = df_stage<SB, S, false>(a, ph.A, ph.K, ph.sq, KT, As, sqs, tid, nullptr, nullptr, dummy0, dummy1, ph.hint);
+  if (!ok) *sdead = 1;
+  __syncthreads();
+  df_loads_done();
+  if (*sdead) return true;
+  DF_STAMP(slot);
+  float sq = 0.f;
+  if (row < M)
+    for (int p = col; p < KT; p += 16) sq += sqs[row * KT + p];
+  const float inv = 1.0f / sqrtf(row16_sum(sq) / (float)ph.K + a.eps);
+  auto swiglu = [&](int t) {
+    f32x4 acc0 = f32x4{0, 0, 0, 0}, acc1 = f32x4{0, 0, 0, 0};
+    df_products<df_pack<SB>(), S>(As, ph.K, M, kb, ke, lane, pre, (const u32x4*)ph.W0 + (size_t)(2 * (kt0 + t) + usel) * KT * 64 + lane,
+                                  (const u32x4*)ph.W1 + (size_t)(2 * (kt0 + t) + usel) * KT * 64 + lane, acc0, acc1);
+    if (t == 0 && two) {
+      request(1);
+      request_down(1, D1, D2);
+    }
+    if (t == 1) request_down(1, D2, DN);
+    df_meet<df_pack<SB>()>(acc0, acc1);
+    const int obase = (g * 4) * 16 + (lane & 15);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      red[uw][0][obase + r * 16] = acc0[r];
+      red[uw][1][obase + r * 16] = acc1[r];
+    }
+    __syncthreads();
+    float v0 = (red[0][0][ut] + red[1][0][ut]) + (red[2][0][ut] + red[3][0][ut]);
+    float v1 = (red[0][1][ut] + red[1][1][ut]) + (red[2][1][ut] + red[3][1][ut]);
+    v0 *= inv;
+    v1 *= inv;
+    sact[row * AP + t * 32 + usel * 16 + col] = split_payload(row < M ? v0 / (1.0f + expf(-v0)) * v1 : 0.f);     // [16 rows][32 columns of each k-tile]
+    __syncthreads();
+  };
+  f32x4 acc[DN];
+  auto down = [&](int t) {
+    u32x4 xh = u32x4{0u, 0u, 0u, 0u}, xl = xh;
+    if (c16 < M) frag_from_lds(sact + c16 * AP + t * 32 + g * 8, xh, xl);
+    const bf16x8 ah = __builtin_bit_cast(bf16x8, xh), al = __builtin_bit_cast(bf16x8, xl);
+#pragma unroll
+    for (int i = 0; i < DN; ++i)
+      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd[t].b[i]), al, t == 0 ? f32x4{0, 0, 0, 0} : acc[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < DN; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd[t].b[i]), ah, acc[i], 0, 0, 0);
+  };
+  swiglu(0);
+  if (two) swiglu(1);
+  down(0);
+  if (two) down(1);
+  // partials out by way of LDS, row by row, as above: a row's tiles of a wave in 64 lanes, 16 tiles at most
+  const int nW = a.n_sum;
+  float* tr = (float*)(lds + S::TR) + wave * (8 * DN * 16);
+  const df_rsrc rp = df_make_rsrc(part);
+  const uint32_t row_bytes = (uint32_t)(ceil_div(a.d, C) * nW * df_part_pitch(C));
+  auto place = [&](int nt, int q) {                                  // of columns 4 q .. 4 q + 3 of a tile
+    const int n = nt * 16 + 4 * q;
+    return (uint32_t)((n / C * nW + (int)blockIdx.x) * df_part_pitch(C) + n % C * 4);
+  };
+  const int ti = lane >> 2, nt_out = wave + 8 * ti;
+  const bool stores = ti < DN && nt_out < ntiles_d;
+  uint32_t at = place(nt_out, lane & 3);
+  for (int r0 = 0; r0 < M; r0 += 8) {
+    if ((c16 & 8) == r0 && c16 < M)
+#pragma unroll
+      for (int i = 0; i < DN; ++i) *(f32x4*)(tr + ((c16 & 7) * DN + i) * 16 + 4 * g) = acc[i];
+    const float* from = tr + ti * 16 + 4 * (lane & 3);
+    const int re = min(M, r0 + 8);
+    for (int r = r0; r < re; ++r, from += DN * 16, at += row_bytes)
+      if (stores) df_put_partial(rp, at, *(const f32x4*)from);
+  }
+  DF_STAMP(slot + 1);
+  __syncthreads();
   return false;
 }
 
@@ -750,6 +1002,9 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const DPhase& ph, c
 // order in LDS.  So it is with the squares: a tree over columns whose nodes over 8 or 32 are published.
 constexpr int DF_RBLOCKS = 64;
 constexpr int DF_RW = 3;                  // partials of a block in flight
+// Partials of an output: one per MLP workgroup's share of the SwiGLU output.
+template <class S>
+__device__ __forceinline__ int df_partials(const DArgs& a) { return S::WIDE ? a.n_sum : a.ffn >> 5; }
 // A thread's partials in a task: four columns of one block, or of two consecutive ones.  The lanes that share a column and eight
 // consecutive blocks differ in lane bits that the cheap lane exchanges reach in the order of the tree (df_sum_blocks).
 template <int C>
@@ -775,7 +1030,7 @@ __device__ __forceinline__ float df_sum_blocks(float s) {
   s += dpp_f<0x124>(s);                                    // row_ror:4: that of lane ^ 4 or ^ 12, which are the same now
   return s + dpp_f<0x4E>(s);                               // quad_perm: lane ^ 2
 }
-template <int C>
+template <int C, class S>
 __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const float* part, const uint32_t* h_in,
                                                 uint32_t* h_out, uint32_t* hg_out, uint32_t* sq_out, const float* gain_next, int shift,
                                                 uint32_t* lds, int* sdead, int slot) {
@@ -783,9 +1038,9 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const float* par
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int NW = gridDim.x;
-  const int d = a.d, np = ceil_div(d, C), nW = a.ffn >> 5, tasks = a.rows.M * np;
+  const int d = a.d, np = ceil_div(d, C), nW = df_partials<S>(a), tasks = a.rows.M * np;
   const int first = df_item_of_unit(blockIdx.x, shift >> 1, NW);       // a task has the whole workgroup
-  float* rs = (float*)(lds + DF_AW + DF_SQ_WORDS);                     // [8 groups of blocks][C]
+  float* rs = (float*)(lds + S::AW + DF_SQ_WORDS);                     // [8 groups of blocks][C]
   const DfPartials<C> pt(tid, nW);
   const int bs = (nW + DF_RBLOCKS - 1) / DF_RBLOCKS;
   const df_rsrc rp = df_make_rsrc(part);
@@ -875,11 +1130,11 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const float* par
 
 // The partials that this workgroup has read in a layer become zeros again, in the next layer, when it has nothing better to do: behind its own QKV,
 // attention and output items, or when its MLP item's weights have come (right behind the sums these stores delayed the next operands).
-template <int C>
+template <int C, class S>
 __device__ __forceinline__ void df_clear_partials(const DArgs& a, const float* part, int shift) {
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
-  const int NW = gridDim.x, nW = a.ffn >> 5, tasks = a.rows.M * ceil_div(a.d, C);
+  const int NW = gridDim.x, nW = df_partials<S>(a), tasks = a.rows.M * ceil_div(a.d, C);
   const DfPartials<C> pt(tid, nW);
   const df_rsrc rp = df_make_rsrc(part);
   for (int task = df_item_of_unit(blockIdx.x, shift >> 1, NW); task < tasks; task += NW) {
@@ -890,6 +1145,7 @@ __device__ __forceinline__ void df_clear_partials(const DArgs& a, const float* p
 }
 
 // The words of a layer that the launch before left in its set become zeros: by the workgroups with MLP items, while they wait.
+template <class S>
 __device__ __forceinline__ void df_clear_layer(const DArgs& a, const size_t set, int rows, int l) {
   if (rows == 0) return;
   int tid = threadIdx.x;
@@ -907,9 +1163,9 @@ __device__ __forceinline__ void df_clear_layer(const DArgs& a, const size_t set,
     zero(a.hg + set + (size_t)hi * a.st_h, rows * a.d);
     zero(a.sq + set + (size_t)hi * a.st_sq, rows * (a.d >> 3));
   }
-  zero(a.q + set + (size_t)l * a.st_q, rows * a.nq * 64);
-  zero(a.attn + set + (size_t)l * a.st_q, rows * a.nq * 64);
-  zero(a.kvn + set + (size_t)l * a.st_kvn, rows * a.nkv * 128);
+  zero(a.q + set + (size_t)l * a.st_q, rows * a.nq * S::HD);
+  zero(a.attn + set + (size_t)l * a.st_q, rows * a.nq * S::HD);
+  zero(a.kvn + set + (size_t)l * a.st_kvn, rows * a.nkv * 2 * S::HD);
 }
 
 // ------------------------------------------------------------------------------------------------ phase 0
@@ -1031,7 +1287,7 @@ __host__ __device__ constexpr int df_parts(int positions) {     // parts of a ro
   return positions <= DF_ONE_PART ? 1 : (positions + 64 * DF_PART_CHUNKS - 1) / (64 * DF_PART_CHUNKS);
 }
 struct DAttItem {
-  int valid, b, kvh, part, rt, len, nact, off, pos_last;
+  int valid, b, kvh, part, rt, half, len, nact, off, pos_last;
   int c0, nch, nparts_b;                                 // first chunk and chunks of the part, parts of the sequence
 };
 
@@ -1040,13 +1296,16 @@ struct DAttItem {
 // whose positions are at or beyond the cached length may be reserved concurrently by this launch: whatever id is read
 // for it is only checked to be inside the pool, since each of its positions is either a row of this launch (taken from
 // the side buffer, never from the pool) or masked.
+template <class S>
 __device__ __forceinline__ DAttItem df_att_item(const DArgs& a, int item, int ntile, int* sblk) {
   DAttItem it;
-  it.valid = item < a.n_seqs * a.nkv * a.n_parts * ntile;
-  it.b = 0; it.kvh = 0; it.part = 0; it.rt = 0;
+  it.valid = item < a.n_seqs * a.nkv * a.n_parts * ntile * S::NH;
+  it.b = 0; it.kvh = 0; it.part = 0; it.rt = 0; it.half = 0;
   if (it.valid) {
-    it.rt = item % ntile;
-    int t = item / ntile;
+    if (S::NH > 1) it.half = item % S::NH;
+    const int u = item / S::NH;
+    it.rt = u % ntile;
+    int t = u / ntile;
     it.b = t % a.n_seqs;
     t /= a.n_seqs;
     it.kvh = t % a.nkv;
@@ -1081,49 +1340,57 @@ __device__ __forceinline__ DAttItem df_att_item(const DArgs& a, int item, int nt
 // its eight k, so the values come as 8 bytes (four tokens of a dim) from each of the two.  Nothing goes through LDS.
 // (With query rows as rows of the tiles a lane had four rows' statistics, each a chain of 16-lane reductions, and the weights
 // took a way through LDS: the attention of one row and 1024 keys took 5.5 us of a layer, 3.7 now.)
-struct DfK { u32x4 f[4][2]; };                           // [block][dims 0-31 / 32-63]
+// Head size 128: the keys of a chunk take 64 registers, its values as many.  An item is half of the output's dims: its workgroup works out all scores, and
+// weights 64 dims of the values.  Two chunks' keys are in registers, and the first one's values, the other two chunks' in LDS; the third
+// chunk's keys are brought into the chip's cache and take the first one's registers when its scores are there.
+template <class S>
+struct DfK { u32x4 f[4][S::HD / 32]; };                  // [block][32 dims]
 struct DfV { u32x4 f[2][4]; };                           // [pair of blocks][16 dims]
 
 // Positions at or beyond the sequence's cached length hold whatever an earlier launch left there; they are patched or
 // masked later, never used.
-__device__ __forceinline__ void df_load_k(const DArgs& a, int layer, const int (&boff)[4], int lane, DfK& k) {
-  const bf16_t* kp = (const bf16_t*)a.kv.pool + (size_t)(2 * layer) * ((size_t)a.kv.n_blocks * a.kv.nkv * 1024);
-  const int g = lane >> 4, c16 = lane & 15;
+template <class S>
+__device__ __forceinline__ const bf16_t* df_plane(const DArgs& a, int plane) { return (const bf16_t*)a.kv.pool + (size_t)plane * ((size_t)a.kv.n_blocks * a.kv.nkv * (16 * S::HD)); }
+template <class S>
+__device__ __forceinline__ void df_load_k(const DArgs& a, int layer, const int (&boff)[4], int lane, DfK<S>& k) {
+  const df_rsrc r = df_make_rsrc(df_plane<S>(a, 2 * layer));           // (through a descriptor: one register of addresses)
+  const int at = (lane & 15) * (2 * S::HD) + (lane >> 4) * 16;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    k.f[t][0] = *(const u32x4*)(kp + boff[t] + c16 * 64 + g * 8);
-    k.f[t][1] = *(const u32x4*)(kp + boff[t] + c16 * 64 + g * 8 + 32);
-  }
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int ks = 0; ks < S::HD / 32; ++ks) k.f[t][ks] = __builtin_amdgcn_raw_buffer_load_b128(r, at + 64 * ks, (int)(2u * (uint32_t)boff[t]), 0);
 }
+// (boff: of the values, with the item's half of the dims)
+template <class S>
 __device__ __forceinline__ void df_load_v(const DArgs& a, int layer, const int (&boff)[4], int lane, DfV& v) {
-  const bf16_t* vp = (const bf16_t*)a.kv.pool + (size_t)(2 * layer + 1) * ((size_t)a.kv.n_blocks * a.kv.nkv * 1024);
-  const int g = lane >> 4, c16 = lane & 15;
+  const df_rsrc r = df_make_rsrc(df_plane<S>(a, 2 * layer + 1));
+  const int at = (lane & 15) * 32 + (lane >> 4) * 8;
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) {
-      const uint2 x = *(const uint2*)(vp + boff[2 * ks] + dt * 256 + c16 * 16 + g * 4);
-      const uint2 y = *(const uint2*)(vp + boff[2 * ks + 1] + dt * 256 + c16 * 16 + g * 4);
-      v.f[ks][dt] = u32x4{x.x, x.y, y.x, y.y};
+      const auto x = __builtin_amdgcn_raw_buffer_load_b64(r, at + dt * 512, (int)(2u * (uint32_t)boff[2 * ks]), 0), y = __builtin_amdgcn_raw_buffer_load_b64(r, at + dt * 512, (int)(2u * (uint32_t)boff[2 * ks + 1]), 0);
+      v.f[ks][dt] = u32x4{x[0], x[1], y[0], y[1]};
     }
 }
 
 // Positions written by this launch: their keys and values come from the side buffer, at the pool's fragment slots.
-__device__ __forceinline__ void df_patch_k(DfK& k, int kbase, int len, int nact, const bf16_t* Kn, int lane) {
+template <class S>
+__device__ __forceinline__ void df_patch_k(DfK<S>& k, int kbase, int len, int nact, const bf16_t* Kn, int lane) {
   const int g = lane >> 4, c16 = lane & 15;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     const int jn = kbase + 16 * t + c16 - len;
-    if ((unsigned)jn < (unsigned)nact) {
-      k.f[t][0] = *(const u32x4*)(Kn + jn * 64 + g * 8);
-      k.f[t][1] = *(const u32x4*)(Kn + jn * 64 + 32 + g * 8);
-    }
+    if ((unsigned)jn < (unsigned)nact)
+#pragma unroll
+      for (int ks = 0; ks < S::HD / 32; ++ks) k.f[t][ks] = *(const u32x4*)(Kn + jn * S::HD + 32 * ks + g * 8);
   }
 }
 // Values of a chunk by way of LDS: its four blocks as they are in the pool, [block][dim][token] (2 KB each, one wave's direct
 // loads; the wave waits for them itself).
+template <class S>
 __device__ __forceinline__ void df_v_to_lds(const DArgs& a, int layer, const int (&boff)[4], int lane, uint32_t* v2) {
-  const df_rsrc r = df_make_rsrc((const u64*)((const bf16_t*)a.kv.pool + (size_t)(2 * layer + 1) * ((size_t)a.kv.n_blocks * a.kv.nkv * 1024)));
+  const df_rsrc r = df_make_rsrc(df_plane<S>(a, 2 * layer + 1));
 #pragma unroll
   for (int i = 0; i < 8; ++i) load_to_lds(r, v2 + i * 256, (int)(2u * (uint32_t)boff[i >> 1] + (uint32_t)(lane * 16 + (i & 1) * 1024)), 0);      // (32 bits: a plane has fewer than 2^31 elements)
 }
@@ -1150,8 +1417,15 @@ __device__ __forceinline__ float df_exp2(float x) { return __builtin_amdgcn_exp2
 // The lane's query row: maximum (base-2 domain), sum (the same in all lane groups) and weighted values, dims 16 dt + 4 g + r.
 struct DfRow { float m, l; f32x4 o[4]; };
 
+// The lane's query row: in registers, or (wide) where it is in LDS, of every eight dims the hi halves, then the lo halves.
+template <class S>
+struct DfQ { u32x4 hi[2], lo[2]; };
+template <>
+struct DfQ<DfWide> { const uint32_t* at; };
+
 // Scores of one chunk's keys.  qpos: position of the lane's query row (-1: none).
-__device__ __forceinline__ void df_scores(const DfK& k, const u32x4 (&qh)[2], const u32x4 (&ql)[2], int kbase, int qpos, bool masked, int lane, f32x4 (&s)[4]) {
+template <class S>
+__device__ __forceinline__ void df_scores(const DfK<S>& k, const DfQ<S>& q, int kbase, int qpos, bool masked, int lane, f32x4 (&s)[4]) {
   const int g = lane >> 4;
 #pragma unroll
   for (int t = 0; t < 4; ++t) s[t] = f32x4{0, 0, 0, 0};
@@ -1159,7 +1433,20 @@ __device__ __forceinline__ void df_scores(const DfK& k, const u32x4 (&qh)[2], co
 #pragma unroll
     for (int t = 0; t < 4; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k.f[t][ks]), __builtin_bit_cast(bf16x8, q), s[t], 0, 0, 0);
   };
-  product(0, ql[0]); product(1, ql[1]); product(0, qh[0]); product(1, qh[1]);
+  if constexpr (S::WIDE) {
+#pragma unroll
+    for (int ks = 0; ks < S::HD / 32; ++ks) {
+      const u32x4 lo = *(const u32x4*)(q.at + ks * 32 + 4), hi = *(const u32x4*)(q.at + ks * 32);
+      product(ks, lo);
+      product(ks, hi);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) product(ks, q.lo[ks]);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) product(ks, q.hi[ks]);
+  }
   if (masked) {                                            // (wave-uniform: only chunks that reach the new positions)
     const int last = qpos - kbase - 4 * g;
 #pragma unroll
@@ -1201,14 +1488,16 @@ __device__ __forceinline__ void df_values(const DfV& v, const f32x4 (&s)[4], DfR
 }
 
 // A wave's rows into the merge buffers [wave][row][dim], [wave][row][max, sum]
+template <class S>
 __device__ __forceinline__ void df_put_row(const DfRow& r, float* MO, float* ML, int wave, int lane) {
   const int g = lane >> 4, c16 = lane & 15;
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt) *(f32x4*)(MO + (wave * 16 + c16) * DF_QS + 16 * dt + 4 * g) = r.o[dt];
+  for (int dt = 0; dt < 4; ++dt) *(f32x4*)(MO + wave * S::MO_WAVE + c16 * DF_QS + 16 * dt + 4 * g) = r.o[dt];
   if (g == 0) { ML[(wave * 16 + c16) * 2] = r.m; ML[(wave * 16 + c16) * 2 + 1] = r.l; }
 }
 
 // Merge of the waves' (ascending) share of a row: maximum, sum and the two dims d0, d0 + 1.
+template <class S>
 __device__ __forceinline__ void df_merge_row(const float* MO, const float* ML, int row, int d0, float& mx, float& l, float (&o)[2]) {
   mx = -INFINITY; l = 0.f; o[0] = o[1] = 0.f;
 #pragma unroll
@@ -1218,13 +1507,13 @@ __device__ __forceinline__ void df_merge_row(const float* MO, const float* ML, i
   for (int w = 0; w < 8; ++w) {
     const float e = df_exp2(ML[(w * 16 + row) * 2] - base);
     l = fmaf(ML[(w * 16 + row) * 2 + 1], e, l);
-    const float2 x = *(const float2*)(MO + (w * 16 + row) * DF_QS + d0);
+    const float2 x = *(const float2*)(MO + w * S::MO_WAVE + row * DF_QS + d0);
     o[0] = fmaf(x.x, e, o[0]);
     o[1] = fmaf(x.y, e, o[1]);
   }
 }
 
-template <int SB>
+template <int SB, class S>
 __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag, const size_t set, int layer, const DAttItem& it, uint32_t* lds, const int* sblk,
                                               const int* srow, int* sdead, int slot) {
   int tid = threadIdx.x;
@@ -1235,28 +1524,45 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   // chunk go to LDS: the third, for which there are no registers (requested when the first keys' registers were free they held
   // the wave up for 1.2 us), or the one with new positions, which is the wave's last and is patched there (by element in
   // registers that took 1.5 us).
-  DfK kf[3];
+  const int half = S::NH == 1 ? 0 : it.half;
+  constexpr int HD = S::HD, NKF = S::WIDE ? 2 : 3;
+  DfK<S> kf[NKF];
   DfV vf[3];
-  uint32_t* v2 = lds + DF_ATT_V + wave * 2048;
+  auto v2 = [&](int j) { return lds + S::V2 + (S::WIDE ? wave * 4096 + (j == 2 ? 2048 : 0) : wave * 2048); };
   auto fresh = [&](int j) { return 64 * (it.c0 + wave + 8 * j) + 64 > it.len; };     // the chunk reaches new positions
-  auto request = [&](int j) {
-    int boff[4];
+  auto by_lds = [&](int j) { return j >= (S::WIDE ? 1 : 2) || fresh(j); };
+  auto blocks = [&](int j, int (&boff)[4]) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) boff[t] = (sblk[(wave + 8 * j) * 4 + t] * a.kv.nkv + it.kvh) * 1024;
-    df_load_k(a, layer, boff, lane, kf[j]);
-    if (j == 2 || fresh(j)) df_v_to_lds(a, layer, boff, lane, v2);
-    else df_load_v(a, layer, boff, lane, vf[j]);
+    for (int t = 0; t < 4; ++t) boff[t] = (__builtin_amdgcn_readfirstlane(sblk[(wave + 8 * j) * 4 + t]) * a.kv.nkv + it.kvh) * (16 * HD);
+  };
+  uint32_t touched = 0u;
+  auto request = [&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    int boff[4];
+    blocks(j, boff);
+    if constexpr (j < NKF) {
+      df_load_k<S>(a, layer, boff, lane, kf[j]);
+    } else {                                               // its registers are not free yet: a word of each 128-byte line
+      const uint32_t* p = (const uint32_t*)df_plane<S>(a, 2 * layer);
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (lane < HD / 4) touched |= p[(boff[t] >> 1) + lane * 32];
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) boff[t] += half * 1024;
+    if (by_lds(j)) df_v_to_lds<S>(a, layer, boff, lane, v2(j));
+    else df_load_v<S>(a, layer, boff, lane, vf[j]);
   };
   const bool live0 = it.valid && wave < it.nch, live1 = it.valid && wave + 8 < it.nch, live2 = it.valid && wave + 16 < it.nch;
-  if (live0) request(0);
-  if (live1) request(1);
-  if (live2) request(2);
-  uint32_t* Qs = lds;                                  // [16 rows][64] operand words
-  bf16_t* Kn = (bf16_t*)(lds + 16 * DF_QS);            // [16][64] new keys
-  bf16_t* Vn = (bf16_t*)(lds + 16 * DF_QS + 512);      // [16][64] new values
-  float* MO = (float*)(lds + 16 * DF_QS + 1024);       // [8 waves][16][64]
-  float* ML = MO + 8 * 16 * DF_QS;                     // [8 waves][16][2]
-  const int R = a.rows.R, G = a.nq / a.nkv, nqd = a.nq * 64, RG = R * G;
+  if (live0) request(std::integral_constant<int, 0>());
+  if (live1) request(std::integral_constant<int, 1>());
+  if (live2) request(std::integral_constant<int, 2>());
+  uint32_t* Qs = lds;                                  // [16 rows][HD] operand words
+  bf16_t* Kn = (bf16_t*)(lds + S::KN);                 // [16][HD] new keys
+  bf16_t* Vn = (bf16_t*)(lds + S::VN);                 // [16][64] new values
+  float* MO = (float*)(lds + S::MO);                   // [8 waves][16][64]
+  float* ML = (float*)(lds + S::ML);                   // [8 waves][16][2]
+  const int R = a.rows.R, G = a.nq / a.nkv, nqd = a.nq * HD, RG = R * G;
   const int r0 = 16 * it.rt, nrt = min(16, RG - r0);                         // first query row and rows of this tile
   const bool unew = (it.c0 + it.nch) * 64 > it.len;                          // the part reaches this launch's positions
   const uint32_t* q = a.q + set + (size_t)layer * a.st_q;
@@ -1273,8 +1579,12 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   bool bad = false;
   // ---- the queries of the tile's rows and this launch's keys / values of the kv head
   if (it.valid) {
-    constexpr int NB = SB == 2 ? 1 : 2;                  // requests of four words that a thread keeps in flight: one flight for 4 / all 16 new rows
-    const int nQ = nrt * 64, total = nQ + (unew ? it.nact * 128 : 0);        // <= 1024 + 2048 words
+    constexpr int NB = SB == 2 ? 1 : S::WIDE && SB == 18 ? 3 : 2;            // requests of four words that a thread keeps in flight: one flight for 4 / all 16 new rows
+    const int nQ = nrt * HD, total = nQ + (unew ? it.nact * (HD + 64) : 0);  // <= 16 HD + 16 (HD + 64) words; of the values the item's 64 dims
+    auto new_word = [&](int i, int& jn, int& which, int& dd) {               // word i of the new rows: a row's keys, then its values
+      if (HD == 64) { jn = i >> 7; which = (i >> 6) & 1; dd = i & 63; }
+      else { jn = i / (HD + 64); dd = i - jn * (HD + 64); which = dd >= HD; dd -= which ? HD : 0; }
+    };
     const df_rsrc rs = df_make_rsrc(a.tw);
     const uint32_t q_off = (uint32_t)(q - a.tw), n_off = (uint32_t)(kvn - a.tw);
     for (int base = 0; base < total; base += 4 * NB * PBLOCK) {
@@ -1282,34 +1592,45 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
       auto off = [&](uint32_t t, int u) -> uint32_t {
         const int idx = base + 4 * (u * PBLOCK + (int)t);
         if (idx < nQ) {
-          const int r = r0 + (idx >> 6), dd = idx & 63, j = r / G, gq = r - j * G;
-          return 4u * (q_off + (uint32_t)((it.b * R + j) * nqd + (it.kvh * G + gq) * 64 + dd));
+          const int r = r0 + (idx >> S::HDL), dd = idx & (HD - 1), j = r / G, gq = r - j * G;
+          return 4u * (q_off + (uint32_t)((it.b * R + j) * nqd + (it.kvh * G + gq) * HD + dd));
         }
-        const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
-        return idx < total ? 4u * (n_off + (uint32_t)((((it.b * R + it.off + jn) * 2 + which) * a.nkv + it.kvh) * 64 + dd)) : 0xFFFFFFFFu;
+        int jn, which, dd;
+        new_word(idx - nQ, jn, which, dd);
+        return idx < total ? 4u * (n_off + (uint32_t)((((it.b * R + it.off + jn) * 2 + which) * a.nkv + it.kvh) * HD + (which ? half * 64 + dd : dd))) : 0xFFFFFFFFu;
       };
-      bad = !poll_quads<NB>(rs, (uint32_t)tid, off, v, a.bar + 64, q + (size_t)it.b * R * nqd + it.kvh * G * 64) || bad;
+      bad = !poll_quads<NB>(rs, (uint32_t)tid, off, v, a.bar + 64, q + (size_t)it.b * R * nqd + it.kvh * G * HD) || bad;
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
         const int idx = base + 4 * (u * PBLOCK + tid);
-        if (idx < nQ) *(u32x4*)(Qs + (idx >> 6) * DF_QS + (idx & 63)) = v[u];
+        if (S::WIDE && idx < nQ) {
+          uint32_t* to = Qs + (idx >> S::HDL) * S::QW + (idx & (HD - 1)) - ((idx & 4) >> 1);
+          *(uint2*)to = make_uint2(__builtin_amdgcn_perm(v[u][1], v[u][0], 0x05040100u), __builtin_amdgcn_perm(v[u][3], v[u][2], 0x05040100u));
+          *(uint2*)(to + 4) = make_uint2(__builtin_amdgcn_perm(v[u][1], v[u][0], 0x07060302u), __builtin_amdgcn_perm(v[u][3], v[u][2], 0x07060302u));
+        } else if (idx < nQ) *(u32x4*)(Qs + (idx >> S::HDL) * S::QW + (idx & (HD - 1))) = v[u];
         else if (idx < total) {
-          const int i2 = idx - nQ, jn = i2 >> 7, which = (i2 >> 6) & 1, dd = i2 & 63;
-          *(uint2*)((which ? Vn : Kn) + jn * 64 + dd) = make_uint2(__builtin_amdgcn_perm(v[u][1], v[u][0], 0x05040100u), __builtin_amdgcn_perm(v[u][3], v[u][2], 0x05040100u));
+          int jn, which, dd;
+          new_word(idx - nQ, jn, which, dd);
+          *(uint2*)((which ? Vn + jn * 64 : Kn + jn * HD) + dd) = make_uint2(__builtin_amdgcn_perm(v[u][1], v[u][0], 0x05040100u), __builtin_amdgcn_perm(v[u][3], v[u][2], 0x05040100u));
         }
       }
     }
-    for (int idx = nQ + tid; idx < 1024; idx += PBLOCK) Qs[(idx >> 6) * DF_QS + (idx & 63)] = 0u;       // padding rows of the tile
+    for (int idx = nQ + tid; idx < 16 * HD; idx += PBLOCK) Qs[(idx >> S::HDL) * S::QW + (idx & (HD - 1))] = 0u;       // padding rows of the tile
   }
   if (bad) *sdead = 1;
   __syncthreads();
   if (*sdead) return true;
   DF_STAMP(slot);
   DfRow rs = {-INFINITY, 0.f, {f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}}};
+  if (S::WIDE) asm volatile("" ::"v"(touched));
   if (live0) {
-    u32x4 qh[2], ql[2];
+    DfQ<S> qf;
+    if constexpr (S::WIDE) {
+      qf.at = Qs + c16 * S::QW + g * 8;
+    } else {
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) frag_from_lds(Qs + c16 * DF_QS + ks * 32 + g * 8, qh[ks], ql[ks]);
+      for (int ks = 0; ks < 2; ++ks) frag_from_lds(Qs + c16 * S::QW + ks * 32 + g * 8, qf.hi[ks], qf.lo[ks]);
+    }
     // All scores first, one maximum and one sum over the wave's chunks, then the values: a chain of reductions across lanes once, not once per chunk.
     // (The third round is not for rows in several parts.)
     f32x4 sc[3][4];
@@ -1317,11 +1638,17 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
     auto scores = [&](auto jc) {
       constexpr int j = decltype(jc)::value;
       const int kbase = 64 * (it.c0 + wave + 8 * j);
-      if (fresh(j)) df_patch_k(kf[j], kbase, it.len, it.nact, Kn, lane);
-      df_scores(kf[j], qh, ql, kbase, j < 2 || qpos < DF_ONE_PART ? qpos : -1, fresh(j) || (j == 2 && it.nparts_b > 1), lane, sc[j]);
+      DfK<S>& k = kf[j % NKF];
+      if (fresh(j)) df_patch_k<S>(k, kbase, it.len, it.nact, Kn, lane);
+      df_scores<S>(k, qf, kbase, j < 2 || qpos < DF_ONE_PART ? qpos : -1, fresh(j) || (j == 2 && it.nparts_b > 1), lane, sc[j]);
       mx = fmaxf(mx, df_max16(sc[j]));
     };
     scores(std::integral_constant<int, 0>());
+    if (S::WIDE && live2) {
+      int boff[4];
+      blocks(2, boff);
+      df_load_k<S>(a, layer, boff, lane, kf[0]);
+    }
     if (live1) scores(std::integral_constant<int, 1>());
     if (live2) scores(std::integral_constant<int, 2>());
     rs.m = max_over_groups(mx) * sc2;
@@ -1329,7 +1656,7 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
     auto values = [&](auto jc) {
       constexpr int j = decltype(jc)::value;
       rs.l += df_weights(sc[j], sc2, base);
-      if (j == 2 || fresh(j)) df_v_from_lds(v2, 64 * (it.c0 + wave + 8 * j), it.len, it.nact, Vn, lane, vf[j]);
+      if (by_lds(j)) df_v_from_lds(v2(j), 64 * (it.c0 + wave + 8 * j), it.len, it.nact, Vn, lane, vf[j]);
       df_values(vf[j], sc[j], rs);
     };
     values(std::integral_constant<int, 0>());
@@ -1339,18 +1666,18 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
   }
   DF_STAMP2(3);
   // ---- the eight waves meet (fixed order: wave 0 .. 7); a single part's rows go out as operand words
-  df_put_row(rs, MO, ML, wave, lane);
+  df_put_row<S>(rs, MO, ML, wave, lane);
   __syncthreads();
   df_loads_done();
   DF_STAMP2(4);
   if (it.valid && row < nrt) {
     if (it.part < np_row) {
       float mx, l, o[2];
-      df_merge_row(MO, ML, row, d0, mx, l, o);
+      df_merge_row<S>(MO, ML, row, d0, mx, l, o);
       if (np_row == 1) {
-        st_val2(attn + (size_t)out_m * nqd + out_head * 64 + d0, operand_word(o[0] / l), operand_word(o[1] / l));
+        st_val2(attn + (size_t)out_m * nqd + out_head * HD + half * 64 + d0, operand_word(o[0] / l), operand_word(o[1] / l));
       } else {
-        u64* pp = att_p + ((((size_t)out_m * a.nq + out_head) * a.NP + it.part) * 16 + (d0 >> 2)) * 6;
+        u64* pp = att_p + (((((size_t)out_m * a.nq + out_head) * a.NP + it.part) * S::NH + half) * 16 + (d0 >> 2)) * 6;
         st_words2(pp + (d0 & 2), __float_as_uint(o[0]), __float_as_uint(o[1]), tag);
         if (!(d0 & 2)) st_words2(pp + 4, __float_as_uint(mx), __float_as_uint(l), tag);
       }
@@ -1366,12 +1693,12 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
       const int np = df_parts(rowpos[j] + 1);
       if (np > 1) {
         const df_rsrc rs = df_make_rsrc(att_p);
-        const uint32_t p_off = 8u * (uint32_t)(((m * a.nq + head) * a.NP) * 96 + (d0 >> 2) * 6);
+        const uint32_t p_off = 8u * (uint32_t)(((m * a.nq + head) * a.NP * S::NH + half) * 96 + (d0 >> 2) * 6);
         float mx = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;
         for (int p0 = 0; p0 < np; p0 += DF_NPF) {
           u32x4 v[DF_NPF * 2];                               // per part: the two values; maximum and sum
           auto off = [&](uint32_t at, int i) -> uint32_t {
-            return i / 2 < np - p0 ? at + (uint32_t)((p0 + i / 2) * 768 + (i % 2 ? 32 : (d0 & 2) * 8)) : 0xFFFFFFFFu;
+            return i / 2 < np - p0 ? at + (uint32_t)((p0 + i / 2) * (768 * S::NH) + (i % 2 ? 32 : (d0 & 2) * 8)) : 0xFFFFFFFFu;
           };
           bad = !poll_pairs<DF_NPF * 2>(rs, p_off, off, tag, v, a.bar + 64) || bad;
           float gm = mx;
@@ -1394,7 +1721,7 @@ __device__ __forceinline__ bool df_attn_phase(const DArgs& a, const uint32_t tag
               o1 = fmaf(__uint_as_float(v[2 * p][2]), e, o1);
             }
         }
-        st_val2(attn + (size_t)m * nqd + head * 64 + d0, operand_word(o0 / l), operand_word(o1 / l));
+        st_val2(attn + (size_t)m * nqd + head * HD + half * 64 + d0, operand_word(o0 / l), operand_word(o1 / l));
       }
     }
   }
@@ -1419,166 +1746,13 @@ __device__ __forceinline__ const DArgs& df_args() {
 // flight costs a round trip, so the host picks the smallest SB whose single flight holds the launch's rows.
 template <int SB>
 __global__ void __launch_bounds__(PBLOCK) k_forward_dataflow(DArgs) {
-  const DArgs& a = df_args();
-  __shared__ __attribute__((aligned(16))) uint32_t lds[DF_LDS_WORDS];
-  __shared__ int srow[3 * 16];
-  __shared__ uint32_t sact[16 * 36];
-  __shared__ int sdead;
-  if (threadIdx.x == 0) sdead = 0;
-  // this launch's number (the kernel that follows a forward on the stream advances the word; nothing in this launch
-  // does).  Requested first, looked at after the other start-up loads have been requested.
-  const int tag_v = ld_state(a.kv.ctl + 3);
-  const u64 state_v = ld_word(a.state);
-  uint32_t tag = 0u;
-  size_t set = 0;                                          // where this launch's set of words begins
-  const int nqkv = (a.nq + 2 * a.nkv) * 64, nqd = a.nq * 64, L = a.n_layers, np = a.d >> 5;
-  const int NU = gridDim.x * 2;
-  // items of every phase kind, and the unit that takes item 0 (the kinds with few items go to different workgroups)
-  const int n_qkv = (a.nq + 2 * a.nkv) * 2, ntile = (a.rows.R * (a.nq / a.nkv) + 15) >> 4,
-            n_att = a.n_seqs * a.nkv * a.n_parts * ntile, n_o = np, n_gu = a.ffn >> 4,
-            n_lg = (((a.vocab + 15) >> 4) + 1) >> 1;
-  const int st = a.small_stride;
-  const int st_lg = 2 * n_lg <= NU ? 2 : 1;               // the head's items: a workgroup each where there are enough (a CU's intake bounds an item's weight stream)
-  // (sums go to the first workgroups, which have MLP items; their own stores' acknowledgement comes just before there is something to sum)
-  const int s_att = NU - 2 * n_att, s_qkv = (s_att - st * n_qkv + NU) % NU, s_o = (s_qkv - st * n_o + NU) % NU, s_red = 0;
-  auto make_qkv = [&](const DArgs& a, int l) {
-    const PLayer Y = layer_ptrs(a, l);
-    DPhase x = DPhase{};
-    x.layer = l; x.A = a.hg + set + (size_t)(2 * l) * a.st_h; x.sq = a.sq + set + (size_t)(2 * l) * a.st_sq;
-    x.W0 = Y.wqkv; x.W1 = Y.wqkv; x.N = nqkv; x.K = a.d; x.gs = 1; x.items = n_qkv; x.shift = s_qkv; x.stride = st;
-    x.bias = Y.bqkv; x.out = a.q + set + (size_t)l * a.st_q; x.kvn = a.kvn + set + (size_t)l * a.st_kvn;
-    x.hint = x.A;
-    return x;
-  };
-  auto make_o = [&](const DArgs& a, int l) {
-    const PLayer Y = layer_ptrs(a, l);
-    DPhase x = DPhase{};
-    x.layer = l;
-    x.A = a.attn + set + (size_t)l * a.st_q;
-    x.W0 = Y.wo; x.W1 = Y.wo; x.N = a.d; x.K = nqd; x.gs = 1; x.items = n_o; x.shift = s_o; x.stride = st;
-    const size_t hi = (size_t)(2 * l);
-    x.h_in = a.h + set + hi * a.st_h; x.h_out = a.h + set + (hi + 1) * a.st_h; x.hg_out = a.hg + set + (hi + 1) * a.st_h;
-    x.sq_out = a.sq + set + (hi + 1) * a.st_sq;
-    x.gain_next = Y.ln2;
-    x.hint = a.q + set + (size_t)l * a.st_q;
-    return x;
-  };
-  auto make_swiglu = [&](const DArgs& a, int l) {
-    const PLayer Y = layer_ptrs(a, l);
-    DPhase x = DPhase{};
-    x.layer = l; x.A = a.hg + set + (size_t)(2 * l + 1) * a.st_h; x.sq = a.sq + set + (size_t)(2 * l + 1) * a.st_sq;
-    x.W0 = Y.wgate; x.W1 = Y.wup; x.N = a.ffn; x.K = a.d; x.gs = 1; x.items = n_gu; x.shift = 0; x.stride = 1;
-    x.hint = a.hg + set + (size_t)(2 * l + 1) * a.st_h;
-    return x;
-  };
-  auto make_head = [&](const DArgs& a) {
-    DPhase x = DPhase{};
-    x.A = a.hg + set + (size_t)(2 * L) * a.st_h; x.sq = a.sq + set + (size_t)(2 * L) * a.st_sq;
-    x.W0 = a.head; x.W1 = a.head; x.N = a.vocab; x.K = a.d; x.gs = 1; x.items = n_lg; x.shift = 0; x.stride = st_lg; x.logits = a.logits;
-    return x;
-  };
-  // which phase kinds this workgroup has a round-0 item in
-  auto has = [&](int u, int shift, int items, int stride = 1) { return df_item_of_unit(u, shift, NU, stride) < items; };
-  const int n_red = a.rows.M * ceil_div(a.d, df_sum_cols<SB>());
-  const int u0 = blockIdx.x * 2, u1 = u0 + 1;
-  const bool g_q = has(u0, s_qkv, n_qkv, st) || has(u1, s_qkv, n_qkv, st) || st * n_qkv > NU,
-             g_a = has(u0, s_att, n_att, 2),                  // (an attention item has the workgroup)
-             g_o = has(u0, s_o, n_o, st) || has(u1, s_o, n_o, st), g_g = (int)blockIdx.x < a.g_mlp,
-             g_r = df_item_of_unit((int)blockIdx.x, s_red >> 1, (int)gridDim.x) < n_red || n_red > (int)gridDim.x, g_l = has(u0, 0, n_lg, st_lg) || has(u1, 0, n_lg, st_lg) || st_lg * n_lg > NU;
-
-  DF_STAMP(1);
-  df_reserve_blocks(a, tag_v);
-  // What the launch needs of the cache state (none of it changes during the launch): the waves' attention items, and
-  // per row its position and whether it is active.
-  __shared__ int sblk[DF_ONE_CHUNKS * 4];
-  const DAttItem ait = df_att_item(a, df_item_of_unit(u0, s_att, NU, 2), ntile, sblk);
-  if ((g_q || g_a) && threadIdx.x < a.rows.M) {           // the QKV epilogue and the attention masks use them
-    const int m = threadIdx.x, brel = m / a.rows.R, j = m - brel * a.rows.R, seq = a.rows.seq0 + brel;
-    const int len = ld_state(a.kv.len + seq);
-    const int npend = a.pcap ? ld_state(a.kv.n_pend + seq) : 0;
-    const int off = a.pcap - npend;
-    srow[m] = j < off ? len : len + (j - off);
-    srow[16 + m] = j < off ? 0 : 1;
-  }
-  tag = (uint32_t)__builtin_amdgcn_readfirstlane(tag_v);
-  if (!df_tag_ok(tag)) {                                   // numbering exhausted: do nothing; the host must clear the workspace
-    if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_fetch_or(a.bar + 64, DEV_ERR_TAGS, __ATOMIC_RELAXED, AG);
-    return;
-  }
-  // The set of words: the other one than the last launch's.  (The state may already be this launch's: then the launch has gone all its way
-  // but for workgroups without an item in the layers, such as this one.)
-  const uint32_t last_tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)state_v), last = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(state_v >> 32));
-  const uint32_t which = last_tag == tag ? last & 1u : ~last & 1u;
-  const int old_rows = last_tag == tag ? 0 : (int)(last >> 1);
-  set = which * a.st_set;
-  df_embed_phase<df_sq_cols<SB>()>(a, set);
-  if (g_q && threadIdx.x < a.rows.M) {                    // the QKV epilogue appends keys and values: block of each row's position
-    u64 w = ld_word(a.rowblk + threadIdx.x);
-    for (long spins = 0; (uint32_t)(w >> 32) != tag; w = ld_word(a.rowblk + threadIdx.x)) {
-      if (++spins > DF_SPIN_LIMIT || ((spins & 63) == 0 && __hip_atomic_load(a.bar + 64, __ATOMIC_RELAXED, AG) != 0)) {
-        __hip_atomic_store(a.bar + 64, 1u, __ATOMIC_RELAXED, AG);
-        w = 0xFFFFFFFFull;                                 // no block: the row is not appended, every later wait sees the flag
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-    srow[32 + threadIdx.x] = (int)(uint32_t)w;
-  }
-  __syncthreads();
-  df_loads_done();
-  DF_STAMP(0);
-  for (int l = 0; l < L; ++l) {
-    const int s0 = 2 + l * 10;
-    if (g_q) {
-      const DArgs& a = df_args();
-      const DPhase cur = make_qkv(a, l);
-      if (df_gemm_phase<PE_QKV, SB>(a, cur, lds, srow, &sdead, s0)) return;
-    }
-    if (g_a) {
-      const DArgs& a = df_args();
-      if (df_attn_phase<SB>(a, tag, set, l, ait, lds, sblk, srow, &sdead, s0 + 2)) return;
-    }
-    if (g_o) {
-      const DArgs& a = df_args();
-      const DPhase cur = make_o(a, l);
-      if (df_gemm_phase<PE_RESID, SB>(a, cur, lds, srow, &sdead, s0 + 4)) return;
-    }
-    auto clear = [&]() {
-      const DArgs& a = df_args();
-      if (g_r && l > 0) df_clear_partials<df_sum_cols<SB>()>(a, a.part + (size_t)((l - 1) & 1) * a.st_part, s_red);
-      if (g_g) df_clear_layer(a, (which ^ 1u) * a.st_set, old_rows, l);
-    };
-    if (!g_g) {
-      clear();
-    } else {
-      const DArgs& a = df_args();
-      const DPhase cur = make_swiglu(a, l);
-      if (df_mlp_phase<SB>(a, cur, layer_ptrs(a, l).wdown, a.part + (size_t)(l & 1) * a.st_part, clear, lds, sact, &sdead, s0 + 6)) return;
-    }
-    if (g_q && g_r && l + 1 < L) {
-      const DArgs& a = df_args();
-      df_touch_weights(a, make_qkv(a, l + 1));
-    }
-    if (g_r) {
-      const DArgs& a = df_args();
-      const size_t hi = (size_t)(2 * l + 1);
-      const float* gain_next = l + 1 < L ? layer_ptrs(a, l + 1).ln1 : a.final_norm;
-      if (df_reduce_phase<df_sum_cols<SB>()>(a, a.part + (size_t)(l & 1) * a.st_part, a.h + set + hi * a.st_h, a.h + set + (hi + 1) * a.st_h,
-                          a.hg + set + (hi + 1) * a.st_h, a.sq + set + (hi + 1) * a.st_sq, gain_next, s_red, lds, &sdead, s0 + 8)) return;
-    }
-  }
-  if (a.with_head && g_l) {
-    const DArgs& a = df_args();
-    const DPhase cur = make_head(a);
-    if (df_gemm_phase<PE_LOGITS, SB>(a, cur, lds, srow, &sdead, 2 + L * 10)) return;
-  }
-  if (g_r) {
-    const DArgs& a = df_args();
-    df_clear_partials<df_sum_cols<SB>()>(a, a.part + (size_t)((L - 1) & 1) * a.st_part, s_red);
-  }
-  // (workgroup 0 sums partials of every MLP item: those have all begun long ago)
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    __hip_atomic_store(a.state, (u64)tag | (u64)((uint32_t)a.rows.M << 1 | which) << 32, __ATOMIC_RELAXED, AG);
+  using S = DfNarrow;
+#include "dataflow_body.h"
+}
+template <int SB>
+__global__ void __launch_bounds__(PBLOCK) k_forward_wide(DArgs) {
+  using S = DfWide;
+#include "dataflow_body.h"
 }
 
 }  // namespace ssd

@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
 #include <type_traits>
@@ -313,13 +314,17 @@ struct ssd_kv {
   u64 *t_base = nullptr, *t_att_p, *t_part, *t_rowblk;
   uint32_t *t_h, *t_hg, *t_sq, *t_q, *t_kvn, *t_attn;
   size_t t_words = 0, t_attp_at = 0;     // words of it; words ahead of the attention's partials (GEMM operands are among them)
+  int t_rows = 0, t_NP = 0;        // rows and attention parts that it has room for
   bool dataflow = false;
+  bool wide = false;               // head size 128: the same forward in its wide form, else one launch per operator
+  int mlp_tiles = 1;               // wide: k-tiles of the down projection that an MLP workgroup takes
   bool attn_whole = false;   // ssd_kv_last_forward_path tells launches whose attention is one part (4) from others (3) on this cache
   bool attn_mfma = true;     // per-operator path: matrix-core attention where it applies (SSD_ATTN=valu: the scalar kernel)
   int32_t* ticket_alt = nullptr;   // ssd_verify_noalloc: the commit's arrival counter in the library's static scratch
   bool capturing = false;          // a cycle is being captured on this cache: no synchronisation, no fallback kernels
   int last_path = 0;               // 1 per-operator launches, 2 barrier kernel, 3 barrier-free kernel, 4 the same with attention without parts
   bool last_whole = false;
+  int last_wgs = 0;                // workgroups of the last barrier-free forward
   int df_sb = 0;             // SSD_DF_FLIGHT=2|4|10|16|18: instantiation of the barrier-free forward up to 8 rows (0: chosen per launch)
   // host
   int32_t* mirror_host;
@@ -367,18 +372,20 @@ static size_t kv_layout(const ssd_model* m, int max_seqs, int max_rows, int n_bl
   float* p_att_ml = cv.take<float>((size_t)L * PR * c.n_q_heads * NP * 2);
   int32_t* tickets = cv.take<int32_t>(std::max(c.d_model / 32 + 1, Mmax * c.n_kv_heads));
   uint32_t* bar = cv.take<uint32_t>(128);
-  unsigned long long* trace = cv.take<unsigned long long>(p_ok ? 256 * 512 : 0);
   // words of the barrier-free forward: one block, zeroed at creation.  Two sets of 32-bit words, the attention's partials (words of 64 bits
   // from here on), the MLP's
-  const size_t TR = PR;
+  const bool wide_ok = c.dtype == SSD_DTYPE_BF16 && c.head_dim == 128;
+  const size_t TR = wide_ok ? std::min(Mmax, 16) : PR;
+  const int HD = wide_ok ? 128 : 64, TNP = wide_ok ? df_parts(m->max_positions + 1) : NP;
+  unsigned long long* trace = cv.take<unsigned long long>(TR ? 256 * 512 : 0);
   const size_t w_h = (size_t)(2 * L + 1) * TR * c.d_model, w_sq = (size_t)(2 * L + 1) * TR * (c.d_model / 8);
-  const size_t w_q = (size_t)L * TR * nqd, w_kvn = (size_t)L * TR * 2 * c.n_kv_heads * 64;
-  const size_t w_attp = (size_t)L * TR * c.n_q_heads * NP * 96;
+  const size_t w_q = (size_t)L * TR * nqd, w_kvn = (size_t)L * TR * 2 * c.n_kv_heads * HD;
+  const size_t w_attp = (size_t)L * TR * c.n_q_heads * TNP * (HD / 64 * 96);
   const size_t w_part = (size_t)2 * (c.d_ffn / 32) * TR * c.d_model;     // (two buffers of fp32, at most twice the rows apart: df_part_pitch)
   const size_t t_words = w_h * 2 + w_sq + w_q * 2 + w_kvn + w_attp + w_part + 32;
   u64* t_base = cv.take<u64>(t_words);
   if (kv) {
-    kv->t_base = t_base; kv->t_words = t_words;
+    kv->t_base = t_base; kv->t_words = t_words; kv->t_rows = (int)TR; kv->t_NP = TNP;
     uint32_t* t = (uint32_t*)t_base;
     kv->t_h = t; t += w_h; kv->t_hg = t; t += w_h; kv->t_sq = t; t += w_sq; kv->t_q = t; t += w_q; kv->t_attn = t; t += w_q; kv->t_kvn = t;
     kv->t_attp_at = w_h * 2 + w_sq + w_q * 2 + w_kvn;      // (words of 64 bits ahead; 32-bit words of a set)
@@ -467,13 +474,24 @@ extern "C" int ssd_kv_create(const ssd_model* m, int max_seqs, int max_rows, int
       kv->cus = cus;
     }
   }
+  // Its wide form: head size 128, rows that a wave's share of the down projection and the staging area hold, and compute units for the MLP's items beside
+  // QKV's and the output projection's, two to a workgroup, and some for attention.  An MLP workgroup takes as few k-tiles as that leaves room for.
+  bool wide = false;
+  if (e == hipSuccess && m->c.dtype == SSD_DTYPE_BF16 && m->c.head_dim == 128 && block_tokens == 16 && m->layer_stride && m->c.d_model <= DfWide::MAX_K && m->c.n_q_heads * 128 <= DfWide::MAX_K &&
+      m->c.n_q_heads / m->c.n_kv_heads <= 16 && (size_t)n_blocks * m->c.n_kv_heads * 2048 < ((size_t)1 << 31)) {
+    const int room = kv->cus - cdiv(m->n_qkv() / 32 + m->c.d_model / 32, 2) - 16;
+    wide = room > 0 && cdiv(m->c.d_ffn / 32, room) <= 2 && (size_t)m->c.d_ffn * m->c.d_model * 2 < ((size_t)1 << 32) - 32;
+    if (wide) kv->mlp_tiles = cdiv(m->c.d_ffn / 32, room);
+  }
   // The barrier-free forward additionally needs its word offsets to fit 32 bits; its words start as zeros.
   kv->dataflow = false;
-  if (e == hipSuccess && kv->persistent_wgs > 0 && kv->t_words > 0 && kv->t_words < ((size_t)1 << 32) && kv->t_attp_at < ((size_t)1 << 28) &&
-      (size_t)kv->p_rows * m->c.n_q_heads * kv->NP * 96 < ((size_t)1 << 28)) {      // (pairs of words are addressed by 32 bits of bytes: ahead of the parts, and in a layer's parts)
+  if (e == hipSuccess && (kv->persistent_wgs > 0 || wide) && kv->t_words > 0 && kv->t_words < ((size_t)1 << 32) && kv->t_attp_at < ((size_t)1 << 28) &&
+      (size_t)kv->t_rows * m->c.n_q_heads * kv->t_NP * (wide ? 192 : 96) < ((size_t)1 << 28)) {      // (pairs of words are addressed by 32 bits of bytes: ahead of the parts, and in a layer's parts)
     e = hipMemsetAsync(kv->t_base, 0, kv->t_words * sizeof(u64), (hipStream_t)stream);
     const char* env = getenv("SSD_FORWARD");
-    kv->dataflow = !(env && strcmp(env, "barrier") == 0);
+    const bool on = !(env && strcmp(env, "barrier") == 0);
+    kv->dataflow = on && !wide;                            // (what a captured cycle needs of both its caches)
+    kv->wide = on && wide;
   }
   {
     const char* env = getenv("SSD_ATTN");
@@ -905,6 +923,53 @@ static int launch_attn(AttnArgs a, int nchunks, int plan_chunks, bool prompt, in
   return SSD_OK;
 }
 
+// Launches whose workgroups wait for each other hold compute units while they do: two of them, half on the device each, would wait until
+// their bounded waits give up.  So such a launch is ordered behind those of other streams that it may not fit beside.  A stream's
+// launches are ordered among themselves; what is kept per stream is the largest of them, until another stream has waited for it.  A program with one
+// stream pays a look at its own entry.  Held until the launch is enqueued, so that no other thread's comes in between.  (A stream that is being
+// captured can neither wait for another one nor be waited for: its graphs are the caller's to order.)
+struct ResidentStream { int device; hipStream_t st; int wgs; };
+static std::mutex g_resident_mutex;
+static std::vector<ResidentStream> g_resident;
+constexpr size_t MAX_RESIDENT_STREAMS = 32;
+
+static bool being_captured(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+struct ResidentLaunch {
+  std::unique_lock<std::mutex> lock;
+  ResidentLaunch(hipStream_t st, int wgs, int cus) : lock(g_resident_mutex) {
+    int device = -1;
+    if (hipGetDevice(&device) != hipSuccess || being_captured(st)) return;
+    int others = 0;
+    ResidentStream* own = nullptr;
+    for (auto& r : g_resident) {
+      if (r.st == st && r.device == device) own = &r;
+      else if (r.device == device) others += r.wgs;
+    }
+    if (own && own->wgs >= wgs && others + wgs <= cus) return;
+    if (others + wgs > cus || g_resident.size() >= MAX_RESIDENT_STREAMS) {
+      for (size_t i = 0; i < g_resident.size();) {
+        const ResidentStream r = g_resident[i];
+        if (r.device != device || r.st == st) { ++i; continue; }
+        hipEvent_t ev;
+        if (!being_captured(r.st) && hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) {
+          if (hipEventRecord(ev, r.st) != hipSuccess || hipStreamWaitEvent(st, ev, 0) != hipSuccess) (void)hipGetLastError();      // (a stream that is gone has nothing to wait for)
+          (void)hipEventDestroy(ev);
+        }
+        g_resident.erase(g_resident.begin() + i);
+      }
+    }
+    for (auto& r : g_resident)
+      if (r.st == st && r.device == device) { r.wgs = std::max(r.wgs, wgs); return; }
+    if (g_resident.size() < MAX_RESIDENT_STREAMS) g_resident.push_back({device, st, wgs});
+  }
+};
+
 // The same forward as one persistent kernel (see persistent.h).
 static int forward_persistent(const ssd_model* m, ssd_kv* kv, Rows rows, int B, int pcap, const int32_t* dev_tokens,
                               int tok_stride, bool with_head, hipStream_t st) {
@@ -935,6 +1000,7 @@ static int forward_persistent(const ssd_model* m, ssd_kv* kv, Rows rows, int B, 
   a.gs_o = (c.n_q_heads * c.head_dim) / 32 <= 4 * PF_K ? 1 : splits(c.n_q_heads * c.head_dim);   // <= PF_K k-tiles per wave: all prefetched
   a.gs_d = splits(c.d_ffn);
   kv->bar_epoch += (with_head ? 1u : 0u) + 5u * (uint32_t)c.n_layers;  // barriers this launch executes
+  const ResidentLaunch order(st, G, kv->cus);
   ProfScope ps(PROF_PERSISTENT, st);
   hipLaunchKernelGGL(k_forward_persistent, dim3(G), dim3(PBLOCK), 0, st, a);
   LAUNCH_CHECK();
@@ -942,7 +1008,7 @@ static int forward_persistent(const ssd_model* m, ssd_kv* kv, Rows rows, int B, 
 }
 
 // The same forward without grid barriers between phases (see dataflow.h).  Returns -1 when the launch does not
-// fit that kernel's limits, so that the caller takes the barrier kernel instead.
+// fit that kernel's limits, so that the caller takes another one instead.
 static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, int pcap, const int32_t* dev_tokens,
                             int tok_stride, bool with_head, hipStream_t st) {
   const ssd_model_config& c = m->c;
@@ -955,17 +1021,23 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   const int n_parts = df_parts(max_len + rows.R);
   // Workgroups [0, g_mlp) take the MLP items (two 16-column items each); the phases with few items (QKV, attention,
   // output projection) get workgroups of their own after them, as far as the device has compute units.
-  const int g_mlp = std::min(kv->persistent_wgs, cdiv(c.d_ffn / 16, 2));
-  const int n_att = B * c.n_kv_heads * cdiv(rows.R * grp, 16) * n_parts, n_other = (c.n_q_heads + 2 * c.n_kv_heads) * 2 + npairs;
+  const bool wide = kv->wide;
+  const int g_mlp = wide ? cdiv(c.d_ffn / 32, kv->mlp_tiles) : std::min(kv->persistent_wgs, cdiv(c.d_ffn / 16, 2));
+  const int n_att = B * c.n_kv_heads * cdiv(rows.R * grp, 16) * n_parts * (wide ? DfWide::NH : DfNarrow::NH), n_qkv = m->n_qkv() / 32, n_other = n_qkv + npairs;
   // with compute units to spare every item of the other small phases gets a workgroup of its own, as attention's always do (its
   // waves then do not share their SIMDs with a second item), else two items share one
   const int small_stride = g_mlp + n_att + n_other <= kv->cus ? 2 : 1;
+  const int o_stride = wide && g_mlp + n_att + cdiv(n_qkv, 2) + npairs <= kv->cus ? 2 : small_stride;
   // (No more workgroups than items: those of a launch wait for each other, and a smaller model's launch on another stream may be in what is left.)
-  const int G = std::min(kv->cus, g_mlp + n_att + cdiv(small_stride * n_other, 2));
+  const int G = std::min(kv->cus, g_mlp + n_att + (wide ? cdiv(small_stride * n_qkv, 2) + cdiv(o_stride * npairs, 2) : cdiv(small_stride * n_other, 2)));
   // limits: one round of attention (its workgroups wait for each other's parts), query rows of an item, LDS staging capacity
-  const bool fits = M <= 16 && rows.R * grp <= DF_ATT_ROWS && n_att <= G && n_parts <= kv->NP &&
-                    M * (c.d_model + 4) <= DF_AW && M * (nqd + 4) <= DF_AW && M * (c.d_model / 32) <= DF_SQ_WORDS &&
-                    c.n_layers <= 128 && 2 + 10 * c.n_layers + 2 <= 512;
+  const bool fits = M <= 16 && rows.R * grp <= DF_ATT_ROWS && n_att <= G && n_parts <= kv->t_NP &&
+                    M * (std::max(c.d_model, nqd) + 4) <= (wide ? DfWide::AW : DfNarrow::AW) && M * (c.d_model / 32) <= DF_SQ_WORDS &&
+                    c.n_layers <= 128 && 2 + 10 * c.n_layers + 2 <= 512 &&
+                    // (wide, more than 12 rows of several sequences: their items of attention share workgroups with the MLP's at long
+                    // prefixes; 28 layers of width 1536, 4096 positions, 5 sequences of 3 rows 1665 us, one launch per operator 1538;
+                    // 4 of 3 rows 1511 against 1609)
+                    (!wide || M <= 12 || B * cdiv(rows.R * grp, 16) <= 6);
   if (!fits) return -1;
   DArgs a;
   memset(&a, 0, sizeof a);
@@ -976,16 +1048,20 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   a.layer_stride = m->layer_stride;
   a.kv = kv->v; a.rows = rows; a.pcap = pcap; a.n_seqs = B; a.tok_stride = tok_stride; a.with_head = with_head ? 1 : 0;
   a.tokens = dev_tokens;
-  const size_t PR = kv->p_rows;
+  const size_t PR = kv->t_rows;
   a.tw = (uint32_t*)kv->t_base; a.st_set = kv->t_attp_at; a.state = kv->t_rowblk + 16; a.h = kv->t_h; a.hg = kv->t_hg; a.sq = kv->t_sq; a.q = kv->t_q; a.kvn = kv->t_kvn; a.attn = kv->t_attn;
   a.att_p = kv->t_att_p; a.logits = kv->logits;
-  a.st_h = PR * c.d_model; a.st_sq = PR * (c.d_model / 8); a.st_q = PR * nqd; a.st_kvn = PR * 2 * c.n_kv_heads * 64;
-  a.st_att_p = PR * c.n_q_heads * kv->NP * 96;
+  a.st_h = PR * c.d_model; a.st_sq = PR * (c.d_model / 8); a.st_q = PR * nqd; a.st_kvn = PR * 2 * c.n_kv_heads * c.head_dim;
+  a.st_att_p = PR * c.n_q_heads * kv->t_NP * (c.head_dim / 64 * 96);
   a.rowblk = kv->t_rowblk;
   a.part = (float*)kv->t_part; a.st_part = (size_t)2 * (c.d_ffn / 32) * PR * c.d_model;
-  a.NP = kv->NP; a.n_parts = n_parts; a.g_mlp = g_mlp; a.small_stride = small_stride;
+  a.NP = kv->t_NP; a.n_parts = n_parts; a.g_mlp = g_mlp; a.small_stride = small_stride;
+  a.o_stride = o_stride; a.mlp_tiles = kv->mlp_tiles; a.n_sum = g_mlp;
+  a.recip_d = cdiv(65536, cdiv(c.d_model, 512)); a.recip_q = cdiv(65536, cdiv(nqd, 512));
   a.bar = kv->bar;
   a.trace = kv->trace_on ? kv->trace : nullptr;
+  kv->last_wgs = G;
+  const ResidentLaunch order(st, G, kv->cus);
   ProfScope ps(PROF_PERSISTENT, st);
   kv->last_whole = kv->attn_whole && max_len + 16 <= DF_ONE_PART;      // (reported only)
   // The smallest instantiation whose flight of an operand staging holds the rows, where its sum tasks (of 8, 32, 32, 64, 64 columns) go well: those of
@@ -994,6 +1070,16 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   int sb = M <= 2 && M * (c.d_model / 8) <= std::min(PBLOCK, G) ? 2 : M <= 4 ? 4 : M <= 6 && M * npairs <= g_mlp ? 10 : M <= 8 ? 16 : 18;
   if (kv->df_sb && M <= DF_PACK_ROWS) sb = kv->df_sb;
   if (sb == 2 && M * (c.d_model / 8) > DF_SQ_WORDS) sb = 10;
+  if (wide) {
+    // One row: sums of 8 columns; up to four: of 32; more: of 64, which are one round of workgroups up to 9 rows of width 1536.
+    sb = kv->df_sb && M <= DF_PACK_ROWS ? (kv->df_sb == 10 ? 16 : kv->df_sb) : M == 1 ? 2 : M <= 4 ? 4 : M <= 8 ? 16 : 18;
+    if (sb == 2 && M * (c.d_model / 8) > DF_SQ_WORDS) sb = 4;
+#define DF_LAUNCH(S) hipLaunchKernelGGL((k_forward_wide<S>), dim3(G), dim3(PBLOCK), 0, st, a)
+    if (sb == 2) DF_LAUNCH(2); else if (sb == 4) DF_LAUNCH(4); else if (sb == 16) DF_LAUNCH(16); else DF_LAUNCH(18);
+#undef DF_LAUNCH
+    LAUNCH_CHECK();
+    return SSD_OK;
+  }
 #define DF_LAUNCH(S) hipLaunchKernelGGL((k_forward_dataflow<S>), dim3(G), dim3(PBLOCK), 0, st, a)
   if (sb == 2) DF_LAUNCH(2); else if (sb == 4) DF_LAUNCH(4); else if (sb == 10) DF_LAUNCH(10); else if (sb == 16) DF_LAUNCH(16); else DF_LAUNCH(18);
 #undef DF_LAUNCH
@@ -1027,6 +1113,10 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     if (kv->capturing) return fail(SSD_ENOSUP, "this launch does not fit the barrier-free forward kernel: it cannot be captured");
     kv->last_path = 2;
     return forward_persistent(m, kv, rows, B, pcap, dev_tokens, tok_stride, with_head, st);
+  }
+  if (kv->wide && M <= kv->t_rows) {
+    const int rc = forward_dataflow(m, kv, rows, B, pcap, dev_tokens, tok_stride, with_head, st);
+    if (rc >= 0) { kv->last_path = kv->last_whole ? 4 : 3; return rc; }
   }
   kv->last_path = 1;
 
@@ -1494,6 +1584,7 @@ struct ssd_cycle {
   hipGraphExec_t exec = nullptr;
   int cap_len_t = -1, cap_len_d = -1;     // the captured launch shapes hold while every length bound stays at or below these
   int captures = 0;
+  int wgs = 0;                            // workgroups of its largest forward
 };
 
 static void cycle_drop(ssd_cycle* c) {
@@ -1555,6 +1646,7 @@ static int cycle_capture(ssd_cycle* c, hipStream_t st) {
                        c->kv->v.ctl + 4);
     if (hipGetLastError() != hipSuccess) rc = fail(SSD_EHIP, "k_kv_follow launch failed");
   }
+  c->wgs = std::max(c->kv->last_wgs, c->kv_d->last_wgs);
   hipGraph_t g = nullptr;
   e = hipStreamEndCapture(st, &g);
   restore();
@@ -1610,7 +1702,10 @@ extern "C" int ssd_cycle_launch(ssd_cycle* c, void* stream) {
     fits = bt <= c->kv->v.n_blocks && bd <= c->kv_d->v.n_blocks;
   }
   if (!fits && (rc = cycle_capture(c, st))) return rc;
-  HIP_TRY(hipGraphLaunch(c->exec, st));
+  {
+    const ResidentLaunch order(st, c->wgs, c->kv->cus);
+    HIP_TRY(hipGraphLaunch(c->exec, st));
+  }
   c->kv->launch_no += 1;
   c->kv_d->launch_no += (uint32_t)K;
   c->kv->last_path = 3;
@@ -1639,7 +1734,7 @@ extern "C" int ssd_trace_barriers(ssd_kv* kv, int enable, void* stream, unsigned
 #else
   if (out) {
     HIP_TRY(hipStreamSynchronize((hipStream_t)stream));
-    const int G = kv->persistent_wgs > 0 ? (kv->dataflow ? std::min(kv->cus, 256) : kv->persistent_wgs) : 0, S = 2 * (1 + 5 * kv->m->c.n_layers);
+    const int G = kv->dataflow || kv->wide ? std::min(kv->cus, 256) : kv->persistent_wgs, S = 2 * (1 + 5 * kv->m->c.n_layers);
     if (G <= 0 || S > 512) return fail(SSD_ENOSUP, "no persistent kernel trace for this cache");
     if (cap < G * 512) return fail(SSD_ENOMEM, "cap %d < %d samples", cap, G * 512);
     HIP_TRY(hipMemcpy(out, kv->trace, sizeof(unsigned long long) * 512 * G, hipMemcpyDeviceToHost));

@@ -1,0 +1,117 @@
+"""GPU tests of the barrier-free forward's wide form (head size 128): against the oracle at the edges of its tiles, phases and row counts, the bits of its
+rows, and two such launches on two streams."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+WIDE = dict(n_layers=2, d_model=1536, n_q_heads=12, n_kv_heads=2, head_dim=128, d_ffn=8960, vocab=300, n_embed=300, dtype="bf16", qkv_bias=1,
+            rope_base=1.0e6, rms_eps=1e-6)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_15380_amd as pkg
+    pkg.load_library()
+
+
+def _shape(name):
+    if name == "mini128":
+        return si.model_shape("mini128_bf16")
+    s = dict(WIDE)
+    if name == "odd":            # one kv head, width of 3 x 32 (a last sum task of half a width), 301 k-tiles of the down projection: the last workgroup has one
+        s.update(d_model=96, n_q_heads=3, n_kv_heads=1, d_ffn=32 * 301)
+    if name == "one_layer":
+        s.update(n_layers=1)
+    return s
+
+
+@pytest.mark.parametrize("name,lens,K", [
+    ("mini128", [40], 0), ("mini128", [63], 1), ("mini128", [1010], 4), ("mini128", [1530], 7), ("mini128", [2040], 12),
+    ("mini128", [5, 130], 5), ("mini128", [1535, 20, 300], 3), ("odd", [33], 2), ("odd", [150], 8), ("odd", [70], 15), ("odd", [1100], 3),
+    ("one_layer", [20], 0), ("one_layer", [50], 7), ("one_layer", [18], 12)])
+def test_wide_forward_against_the_oracle(name, lens, K):
+    """Two verifications each, and the cached keys and values after each.  Rows 1 to 16 (sums of 8, 32 and 64 columns, both halves of an operand in one
+    instruction or in two), new rows within a chunk, across chunks and across the end of the only part.  With the cache's format in the oracle
+    what is left are fp32 sums and keys that round the other way, as in test_mini_bf16_parity_with_matched_cache_format, whose bounds these are."""
+    from tests.parity import Pair, verify_parity_step
+    shape = _shape(name)
+    steps = 2
+    pair = Pair(None, 881, max(lens) + steps * (K + 1) + 20, max_seqs=len(lens), max_rows=256, shape=shape, store="bf16")
+    for b, n in enumerate(lens):
+        pair.prefill(b, np.random.default_rng(90 + b).integers(0, shape["n_embed"], n + 1))
+    rng = np.random.default_rng(12)
+    for s in range(steps):
+        verify_parity_step(pair, dict(beta=0.2, temperature=1.0, top_k=0, greedy=False, seed=77), K, s, rng, 4e-3, 4e-3, seqs=range(len(lens)))
+        assert pair.kv.last_forward_path() == 3
+        for b in range(len(lens)):
+            pair.check_state(b, 1.6e-2)
+        pair.check_free_stack()
+
+
+@pytest.mark.parametrize("name,K,rows", [("mini128", 7, 8), ("mini128", 12, 13), ("odd", 15, 16), ("one_layer", 5, 6)])
+def test_wide_rows_of_a_prompt_with_loud_weights(name, K, rows):
+    """A prompt in launches of `rows` rows, on weights with which a lost piece of a tile counts: each cached row within one step of bf16 of the oracle's."""
+    from tests.parity import Pair, loud_weights
+    shape = dict(_shape(name), n_layers=2)
+    if name == "one_layer":
+        shape.update(d_ffn=32 * 185)                       # more k-tiles than workgroups: 93 workgroups, the last with one
+    pair = Pair(None, 0, 96, max_rows=rows, shape=shape, weights=loud_weights(shape, 31), store="bf16")
+    pair.prefill(0, np.random.default_rng(32).integers(0, shape["n_embed"], 3 * rows + 2))
+    assert pair.kv.last_forward_path() == 3
+    pair.check_rows(0, 2.0 ** -7)
+
+
+@pytest.mark.parametrize("name,K,cached", [("mini128", 7, 60), ("mini128", 7, 1514), ("mini128", 7, 1530), ("mini128", 12, 1535), ("mini128", 4, 2046),
+                                           ("one_layer", 4, 100), ("odd", 12, 1020)])
+def test_wide_rows_verified_together_have_the_bits_of_rows_decoded_alone(name, K, cached):
+    from tests.test_gpu_row_bits import _target, _verify_logits
+    import paper_2505_15380_amd as ssd
+    shape = _shape(name)
+    model, kv = _target(shape, [cached], 256)
+    x = torch.from_numpy(np.random.default_rng(7).integers(0, shape["vocab"], (1, K)).astype(np.int32)).cuda()
+    pending = kv.state(0)["pending"][0]
+    together, path = _verify_logits(model, kv, 1, x)
+    assert path == 3
+    for i, tok in enumerate([pending] + x[0].tolist()):
+        ssd.ssd_kv_rollback(kv, 0, cached + i, tok)
+        alone, path = _verify_logits(model, kv, 1, x[:, :0])
+        assert path == 3
+        assert torch.equal(alone[0, 0], together[0, i]), f"row {i}: differs by {float((alone[0, 0] - together[0, i]).abs().max())}"
+
+
+@pytest.mark.parametrize("other", ["wide", "narrow"])
+def test_launches_that_do_not_fit_the_device_together_are_ordered(other):
+    """Two models on two streams, issued in turn without a wait in between; 204 and more workgroups each.  The same steps as one after the other."""
+    from tests.test_gpu_row_bits import _target
+    import paper_2505_15380_amd as ssd
+    second = _shape("one_layer") if other == "wide" else dict(si.model_shape("half_b_draft"), vocab=300, n_embed=300)
+    K, runs = 4, []
+    for shape in (_shape("wide"), second):
+        model, kv = _target(shape, [70], 64, extra=400)
+        x = torch.from_numpy(np.random.default_rng(7).integers(0, shape["vocab"], (1, K)).astype(np.int32)).cuda()
+        pd = torch.full((1, K, shape["vocab"]), 1.0 / shape["vocab"], device="cuda")
+        runs.append((model, kv, x, pd, torch.cuda.Stream(), kv.state(0)["pending"][0]))
+    cfg = ssd.sample_config(beta=0.3, seed=3)
+    got = []
+    for beside in (False, True):
+        for _, kv, _, _, stream, pending in runs:
+            with torch.cuda.stream(stream):
+                ssd.ssd_kv_rollback(kv, 0, 70, pending)
+        torch.cuda.synchronize()
+        outs = []
+        for step in range(12):
+            for model, kv, x, pd, stream, _ in runs:
+                with torch.cuda.stream(stream):
+                    outs.append(ssd.ssd_verify(model, kv, 1, x, pd, K, cfg, step, want_logits=True)["logits"])
+                    assert kv.last_forward_path() in (3, 4)
+                if not beside:
+                    torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        got.append(outs)
+    assert all(torch.equal(a, b) for a, b in zip(*got))
