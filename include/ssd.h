@@ -19,9 +19,9 @@
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls enqueue work and
  *     return; outputs are valid after the stream is synchronised.  Calls on one handle must be issued on
  *     one stream (or be externally ordered).
- *     Forwards of at most 16 rows with bf16 storage (ssd_kv_last_forward_path 2 to 4) are one launch whose workgroups, one to a
+ *     Forwards of few rows (ssd_kv_last_forward_path 2 to 5) are one launch whose workgroups, one to a
  *     compute unit, wait for each other.  Two such launches of different handles on two streams of a process overlap if the device
- *     has the compute units for both (of 256, a model of width 896 takes 218 to 256, 152 with path 2), else the later one is ordered
+ *     has the compute units for both (of 256, a model of width 896 takes 218 to 256, 152 with path 2, one of width 128 in fp32 13 to 100), else the later one is ordered
  *     behind the other stream.  Graphs that a caller captures around these calls, and other processes on the same device, are not seen: there
  *     each launch may hold units that the other one waits for until their bounded waits give up, which both report as SSD_EHIP; order them.
  *   - Return value: SSD_OK (0) or a negative error code; ssd_last_error() gives a message for the last
@@ -253,13 +253,15 @@ int ssd_profile_begin(int kind);
 int ssd_profile_end(double* total_ms, int* launches);
 
 /* Which kernels ran the last decoder forward on `kv` (host bookkeeping, no synchronisation):
- * 0 none yet, 1 one launch per operator (fp32 storage, more than 16 rows, head_dim other than 64),
+ * 0 none yet, 1 one launch per operator (more than 16 rows, wider shapes than 3 and 5 take, fp32 beyond 5),
  * 2 one persistent kernel with grid barriers between phases, 3 one persistent kernel whose phases are ordered by
- * the data themselves (the default for bf16 storage and at most 16 rows; the environment variable
- * SSD_FORWARD=barrier, read at ssd_kv_create, selects 2 instead; 2 is also what runs when a launch exceeds the
- * limits of 3), 4 the same kernel where no part of a prefix can meet another one's: at most 1520 cached positions, by the
+ * the data themselves (the default for bf16 storage and at most 16 rows; head_dim 128: d_model and n_q_heads*128 up to 1536, and of
+ * more than 12 rows of several sequences only few; the environment variable SSD_FORWARD=barrier, read at ssd_kv_create, selects 2 instead, 1 with
+ * head_dim 128 or fp32; 2, or 1, is also what runs when a launch exceeds the limits of 3), 4 the same kernel where no part of a prefix can meet another one's: at most 1520 cached positions, by the
  * host's bound of the lengths, on a cache created with pending_cap 2 (SSD_ATTN_WHOLE=1: on every cache, 0: on none).  The
- * kernel is the same and so are the results: a row attends in one part up to 1536 positions and in parts of 1024 beyond. */
+ * kernel is the same and so are the results: a row attends in one part up to 1536 positions and in parts of 1024 beyond; 5 the same
+ * idea for fp32 storage, with the bits of 1: head_dim 32, d_model and n_q_heads*32 up to 256, d_ffn up to 512, at most 64 rows of 16 sequences (16 rows
+ * each) that hold up to 1024 positions. */
 int ssd_kv_last_forward_path(const ssd_kv* kv);
 
 /* Phase trace of the persistent forward kernels, recorded only by builds with -DSSD_TRACE (otherwise SSD_ENOSUP

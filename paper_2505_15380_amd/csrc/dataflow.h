@@ -1208,7 +1208,7 @@ __device__ __forceinline__ void df_embed_phase(const DArgs& a, const size_t set)
   }
 }
 
-// Block reservation for the rows of this launch: lane b of the first wave of workgroup 0 takes sequence b (at most
+// Block reservation for the rows of this launch, by one workgroup: lane b of its first wave takes sequence b (at most
 // 16 sequences).  Two memory round trips for all of them: the state words, then the ids (free-stack entries for new
 // blocks, table entries for blocks already owned).  Sequences take from the free stack in ascending order, top first,
 // as a serial walk over the sequences would.  Nothing waits for the table itself: the block that holds a row's new
@@ -1217,8 +1217,9 @@ __device__ __forceinline__ void df_embed_phase(const DArgs& a, const size_t set)
 // grid barrier.
 __device__ __forceinline__ bool df_tag_ok(uint32_t tag) { return tag != 0u && tag < TAG_LIMIT; }
 
-__device__ __forceinline__ void df_reserve_blocks(const DArgs& a, const int tag_v) {
-  if (blockIdx.x != 0 || threadIdx.x >= 64) return;
+template <typename AR>
+__device__ __forceinline__ void df_reserve_blocks(const AR& a, const int tag_v, const bool mine) {
+  if (!mine || threadIdx.x >= 64) return;
   const int b = threadIdx.x, R = a.rows.R;
   const bool on = b < a.n_seqs;
   const int s = a.rows.seq0 + (on ? b : 0);

@@ -68,7 +68,7 @@
              g_r = df_item_of_unit((int)blockIdx.x, s_red >> 1, (int)gridDim.x) < n_red || n_red > (int)gridDim.x, g_l = has(u0, 0, n_lg, st_lg) || has(u1, 0, n_lg, st_lg) || st_lg * n_lg > NU;
 
   DF_STAMP(1);
-  df_reserve_blocks(a, tag_v);
+  df_reserve_blocks(a, tag_v, blockIdx.x == 0);
   // What the launch needs of the cache state (none of it changes during the launch): the waves' attention items, and
   // per row its position and whether it is active.
   __shared__ int sblk[DF_ONE_CHUNKS * 4];

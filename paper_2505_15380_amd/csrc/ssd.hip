@@ -23,6 +23,7 @@
 #include "gemm_tile.h"
 #include "persistent.h"
 #include "dataflow.h"
+#include "small.h"
 #include "sample.h"
 
 using namespace ssd;
@@ -316,13 +317,14 @@ struct ssd_kv {
   size_t t_words = 0, t_attp_at = 0;     // words of it; words ahead of the attention's partials (GEMM operands are among them)
   int t_rows = 0, t_NP = 0;        // rows and attention parts that it has room for
   bool dataflow = false;
+  bool small = false;              // fp32: a few rows as one launch, else one per operator
   bool wide = false;               // head size 128: the same forward in its wide form, else one launch per operator
   int mlp_tiles = 1;               // wide: k-tiles of the down projection that an MLP workgroup takes
   bool attn_whole = false;   // ssd_kv_last_forward_path tells launches whose attention is one part (4) from others (3) on this cache
   bool attn_mfma = true;     // per-operator path: matrix-core attention where it applies (SSD_ATTN=valu: the scalar kernel)
   int32_t* ticket_alt = nullptr;   // ssd_verify_noalloc: the commit's arrival counter in the library's static scratch
   bool capturing = false;          // a cycle is being captured on this cache: no synchronisation, no fallback kernels
-  int last_path = 0;               // 1 per-operator launches, 2 barrier kernel, 3 barrier-free kernel, 4 the same with attention without parts
+  int last_path = 0;               // 1 per-operator launches, 2 barrier kernel, 3 barrier-free kernel, 4 the same with attention without parts, 5 fp32 in one launch
   bool last_whole = false;
   int last_wgs = 0;                // workgroups of the last barrier-free forward
   int df_sb = 0;             // SSD_DF_FLIGHT=2|4|10|16|18: instantiation of the barrier-free forward up to 8 rows (0: chosen per launch)
@@ -330,6 +332,12 @@ struct ssd_kv {
   int32_t* mirror_host;
   std::vector<int> len_ub, npend_ub;
 };
+
+// Shapes whose fp32 forward of a few rows is one launch (small.h).  (With head size 64 two chunks of keys and values do not fit the registers.)
+static bool small_shape(const ssd_model_config& c) {
+  return c.dtype == SSD_DTYPE_FP32 && c.head_dim == SF_HD && c.d_model <= SF_MAX_D && c.n_q_heads * SF_HD <= SF_MAX_D && c.d_ffn <= SF_MAX_FFN &&
+         c.n_q_heads / c.n_kv_heads <= SF_MAX_GROUP;
+}
 
 static size_t kv_layout(const ssd_model* m, int max_seqs, int max_rows, int n_blocks, int mbps, void* base, ssd_kv* kv) {
   const ssd_model_config& c = m->c;
@@ -374,15 +382,17 @@ static size_t kv_layout(const ssd_model* m, int max_seqs, int max_rows, int n_bl
   uint32_t* bar = cv.take<uint32_t>(128);
   // words of the barrier-free forward: one block, zeroed at creation.  Two sets of 32-bit words, the attention's partials (words of 64 bits
   // from here on), the MLP's
+  const bool small_ok = small_shape(c);
   const bool wide_ok = c.dtype == SSD_DTYPE_BF16 && c.head_dim == 128;
-  const size_t TR = wide_ok ? std::min(Mmax, 16) : PR;
+  const size_t TR = wide_ok ? std::min(Mmax, 16) : PR, SR = small_ok ? std::min(Mmax, SF_MAX_ROWS) : 0;
+  const size_t s_set = (size_t)L * SR * (nqd + 2 * c.d_model + c.d_ffn);      // (32-bit words; two sets)
   const int HD = wide_ok ? 128 : 64, TNP = wide_ok ? df_parts(m->max_positions + 1) : NP;
   unsigned long long* trace = cv.take<unsigned long long>(TR ? 256 * 512 : 0);
   const size_t w_h = (size_t)(2 * L + 1) * TR * c.d_model, w_sq = (size_t)(2 * L + 1) * TR * (c.d_model / 8);
   const size_t w_q = (size_t)L * TR * nqd, w_kvn = (size_t)L * TR * 2 * c.n_kv_heads * HD;
   const size_t w_attp = (size_t)L * TR * c.n_q_heads * TNP * (HD / 64 * 96);
   const size_t w_part = (size_t)2 * (c.d_ffn / 32) * TR * c.d_model;     // (two buffers of fp32, at most twice the rows apart: df_part_pitch)
-  const size_t t_words = w_h * 2 + w_sq + w_q * 2 + w_kvn + w_attp + w_part + 32;
+  const size_t t_words = small_ok ? s_set + SF_MAX_ROWS + 16 : w_h * 2 + w_sq + w_q * 2 + w_kvn + w_attp + w_part + 32;
   u64* t_base = cv.take<u64>(t_words);
   if (kv) {
     kv->t_base = t_base; kv->t_words = t_words; kv->t_rows = (int)TR; kv->t_NP = TNP;
@@ -392,6 +402,7 @@ static size_t kv_layout(const ssd_model* m, int max_seqs, int max_rows, int n_bl
     kv->t_att_p = t_base + kv->t_attp_at;
     kv->t_part = kv->t_att_p + w_attp;
     kv->t_rowblk = kv->t_part + w_part;
+    if (small_ok) { kv->t_rows = (int)SR; kv->t_attp_at = s_set; kv->t_rowblk = t_base + s_set; }
 
     kv->trace = trace;
     kv->p_h = p_h; kv->p_hg = p_hg; kv->p_sumsq = p_sumsq; kv->p_q = p_q; kv->p_attn = p_attn; kv->p_act = p_act; kv->p_part = p_part; kv->p_att_o = p_att_o;
@@ -483,14 +494,17 @@ extern "C" int ssd_kv_create(const ssd_model* m, int max_seqs, int max_rows, int
     wide = room > 0 && cdiv(m->c.d_ffn / 32, room) <= 2 && (size_t)m->c.d_ffn * m->c.d_model * 2 < ((size_t)1 << 32) - 32;
     if (wide) kv->mlp_tiles = cdiv(m->c.d_ffn / 32, room);
   }
+  const bool small = e == hipSuccess && small_shape(m->c) && block_tokens == 16 && m->layer_stride && kv->t_words < ((size_t)1 << 28) &&
+                     (size_t)n_blocks * m->c.n_kv_heads * (64 * SF_HD) < ((size_t)1 << 31);      // (words, and a plane of the pool, are addressed by 32 bits of bytes)
   // The barrier-free forward additionally needs its word offsets to fit 32 bits; its words start as zeros.
   kv->dataflow = false;
-  if (e == hipSuccess && (kv->persistent_wgs > 0 || wide) && kv->t_words > 0 && kv->t_words < ((size_t)1 << 32) && kv->t_attp_at < ((size_t)1 << 28) &&
+  if (e == hipSuccess && (kv->persistent_wgs > 0 || wide || small) && kv->t_words > 0 && kv->t_words < ((size_t)1 << 32) && kv->t_attp_at < ((size_t)1 << 28) &&
       (size_t)kv->t_rows * m->c.n_q_heads * kv->t_NP * (wide ? 192 : 96) < ((size_t)1 << 28)) {      // (pairs of words are addressed by 32 bits of bytes: ahead of the parts, and in a layer's parts)
     e = hipMemsetAsync(kv->t_base, 0, kv->t_words * sizeof(u64), (hipStream_t)stream);
     const char* env = getenv("SSD_FORWARD");
     const bool on = !(env && strcmp(env, "barrier") == 0);
-    kv->dataflow = on && !wide;                            // (what a captured cycle needs of both its caches)
+    kv->dataflow = on && !wide && !small;                  // (what a captured cycle needs of both its caches)
+    kv->small = on && small;
     kv->wide = on && wide;
   }
   {
@@ -1087,6 +1101,37 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   return SSD_OK;
 }
 
+// The fp32 forward of a few rows as one launch (see small.h): up to 16 rows a sequence and 64 in all, of up to 16 sequences that attend in one part, with a compute
+// unit for every item.  Returns -1 where that is not so; the launches per operator give the same bits.
+static int forward_small(const ssd_model* m, ssd_kv* kv, Rows rows, int B, int pcap, const int32_t* dev_tokens, int tok_stride, bool with_head,
+                         hipStream_t st) {
+  const ssd_model_config& c = m->c;
+  const int M = rows.M, T = cdiv(M, 16), grp = c.n_q_heads / c.n_kv_heads;
+  int max_len = 0;
+  for (int s = rows.seq0; s < rows.seq0 + B; ++s) max_len = std::max(max_len, kv->len_ub[s]);
+  SArgs a;
+  memset(&a, 0, sizeof a);
+  a.first_gu = B * c.n_kv_heads * cdiv(rows.R * grp, 16);
+  a.first_down = a.first_gu + c.d_ffn / 32 * T;
+  a.first_end = a.first_down + c.d_model / 32 * T;
+  const int G = a.first_end + 1;
+  a.tiles = cdiv(rows.R * grp, 16);
+  a.recip_tiles = cdiv(65536, a.tiles); a.recip_seqs = cdiv(65536, B); a.recip_T = cdiv(65536, T); a.recip_R = cdiv(65536, rows.R); a.recip_G = cdiv(65536, grp);
+  if (M > kv->t_rows || rows.R > 16 || B > 16 || max_len + rows.R > att_f32_part<SF_HD>() * ATT_CHUNK || G > kv->cus) return -1;
+  a.n_layers = c.n_layers; a.d = c.d_model; a.nq = c.n_q_heads; a.nkv = c.n_kv_heads; a.ffn = c.d_ffn; a.vocab = c.vocab; a.n_embed = c.n_embed;
+  a.eps = c.rms_eps; a.scale = 1.0f / sqrtf((float)c.head_dim);
+  a.embed = (const float*)m->embed; a.final_norm = m->final_norm; a.head = (const float*)m->head; a.rope = m->rope;
+  a.layer0 = m->host_layers[0]; a.layer_stride = m->layer_stride;
+  a.kv = kv->v; a.rows = rows; a.pcap = pcap; a.n_seqs = B; a.tok_stride = tok_stride; a.with_head = with_head ? 1 : 0; a.tokens = dev_tokens;
+  a.tw = (uint32_t*)kv->t_base; a.st_set = kv->t_attp_at; a.cap = kv->t_rows; a.rowblk = kv->t_rowblk; a.state = kv->t_rowblk + SF_MAX_ROWS;
+  a.logits = kv->logits; a.bar = kv->bar;
+  const ResidentLaunch order(st, G, kv->cus);
+  ProfScope ps(PROF_PERSISTENT, st);
+  hipLaunchKernelGGL(k_forward_f32, dim3(G), dim3(PBLOCK), 0, st, a);
+  LAUNCH_CHECK();
+  return SSD_OK;
+}
+
 // One decoder forward for sequences [seq0, seq0+B), R rows each.  pcap = pending slots at the head of each
 // sequence's rows (0: all rows take explicit tokens).  Leaves logits [B*R][vocab] in the workspace when
 // with_head.  The caller has checked room.
@@ -1119,6 +1164,10 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     if (rc >= 0) { kv->last_path = kv->last_whole ? 4 : 3; return rc; }
   }
   kv->last_path = 1;
+  if (kv->small) {
+    const int rc = forward_small(m, kv, rows, B, pcap, dev_tokens, tok_stride, with_head, st);
+    if (rc >= 0) { kv->last_path = 5; return rc; }
+  }
 
   EmbedArgs e;
   e.kv = kv->v; e.rows = rows; e.pcap = pcap; e.n_seqs = B; e.tokens = dev_tokens; e.tok_stride = tok_stride;
