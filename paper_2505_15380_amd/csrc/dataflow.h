@@ -78,10 +78,11 @@ struct DfNarrow {
   static constexpr int KN = 16 * QW, VN = KN + 512, MO = VN + 512, MO_WAVE = 16 * DF_QS, ML = MO + 8 * MO_WAVE, V2 = ML + 256;   // Q | new K | new V | merge O | merge m,l |
   static constexpr int ATT_WORDS = V2 + 8 * 2048;                                   // values of a chunk per wave
   static constexpr int LDS_WORDS = TR + 8 * 8 * DN * 16;
+  static constexpr int AW8 = AW, RS = AW + DF_SQ_WORDS;
 };
-// Head size 128.  28 layers of width 1536 behind 1024 positions, against one launch per operator, seven a layer: one row 1316 -> 676 us, five 1345 -> 770, eight
-// 1372 -> 876, thirteen 1408 -> 1140.  Bound by the weights, 94 MB a layer: the registers of the MLP's 140 workgroups hold 50 of them, the rest streams
-// at 4.8 TB/s when the MLP's operands are there.  Every wave has 12 k-tiles of width 1536 in flight (96 registers) and 12 tiles of the down projection (48).
+// Head size 128.  28 layers of width 1536 behind 1024 positions, against one launch per operator, seven a layer: one row 1316 -> 636 us, five 1349 -> 743, eight
+// 1376 -> 840, thirteen 1408 -> 1146.  Bound by the weights, 94 MB a layer: the registers and LDS of the MLP's 140 workgroups hold 70 of them while they wait, the
+// rest streams when their operands are there.  Every wave has 12 k-tiles of width 1536 in flight (96 registers) and 12 tiles of the down projection (48).
 // The MLP's partials go out over the staged operands, which nothing reads any more, and a wave's share of attention over the values that it has read.
 struct DfWide {
   static constexpr bool WIDE = true;
@@ -89,10 +90,19 @@ struct DfWide {
   static constexpr int MAX_K = 4 * 32 * PF;                // inputs of a projection: a wave keeps all of its k-tiles requested
   static constexpr int KN = 16 * QW, VN = KN + 1024, ML = VN + 512, V2 = ML + 256, MO = V2, MO_WAVE = 4096;                     // Q | new K | new V (64 dims) | merge m,l |
   static constexpr int ATT_WORDS = V2 + 8 * 4096;                                                                               // values of two chunks per wave, then merge O
-  static constexpr int LDS_WORDS = ATT_WORDS;
+  static constexpr int LDS_WORDS = 37952;
+  static constexpr int AW8 = 8 * 1540, RS = AW8 + DF_SQ_WORDS;           // operands of up to 8 rows; where sum tasks meet
 };
 static_assert(DfNarrow::ATT_WORDS <= DfNarrow::LDS_WORDS && DfNarrow::LDS_WORDS <= 39 * 1024, "");
-static_assert(DfWide::ATT_WORDS <= DfWide::LDS_WORDS && 8 * 8 * DfWide::DN * 16 <= DfWide::AW && DfWide::AW + DF_SQ_WORDS + DF_RED_WORDS <= DfWide::LDS_WORDS && DfWide::LDS_WORDS <= 39 * 1024, "");
+// The staging area of an instantiation, and how many of a wave's tiles of the down projection the wide form has in LDS behind it and what it is followed by.
+template <int SB, class S>
+constexpr int df_aw() { return SB <= 16 ? S::AW8 : S::AW; }
+template <int SB, class S>
+constexpr int df_wl() { return df_aw<SB, S>() + DF_SQ_WORDS + DF_RED_WORDS; }
+template <int SB>
+constexpr int df_lds_tiles() { return SB <= 16 ? 10 : 0; }
+static_assert(DfWide::ATT_WORDS <= DfWide::LDS_WORDS && 8 * 8 * DfWide::DN * 16 <= DfWide::AW8 && DfWide::LDS_WORDS <= 39 * 1024 &&
+              df_wl<16, DfWide>() + df_lds_tiles<16>() * 2048 <= DfWide::LDS_WORDS && df_wl<18, DfWide>() + df_lds_tiles<18>() * 2048 <= DfWide::LDS_WORDS, "");
 template <int PF>
 struct DfPre { u32x4 b0[PF], b1[PF]; };   // weight fragments of a wave's first PF k-tiles, two tiles
 
@@ -241,9 +251,9 @@ template <int SB>
 constexpr int df_sum_cols() { return SB == 2 ? 8 : SB <= 10 ? 32 : 64; }
 template <int SB>
 constexpr int df_sq_cols() { return SB == 2 ? 8 : 32; }
-// Wide form: loads of four words a thread has in flight, of 512-word pieces dealt out to four quarters of a workgroup: 1, 4, 8 and 16 rows of 1536.
+// Wide form (SB = 4, 16, 18): loads of four words a thread has in flight, of 512-word pieces dealt out to four quarters of a workgroup: 2, 8 and 16 rows of 1536.
 template <int SB>
-constexpr int df_flight() { return SB == 2 ? 1 : SB <= 10 ? 3 : SB == 16 ? 6 : 12; }
+constexpr int df_flight() { return SB == 4 ? 2 : SB == 16 ? 6 : 12; }
 
 // ------------------------------------------------------------------------------------------------ GEMM phases
 struct DPhase {
@@ -561,8 +571,8 @@ __device__ __forceinline__ bool df_gemm_phase(const DArgs& a, const DPhase& ph, 
   const int unit = blockIdx.x * 2 + usel, NU = gridDim.x * 2;
   const int uitem = df_item_of_unit(unit, ph.shift, NU, ph.stride);
   uint32_t* As = lds;
-  float* sqs = (float*)(lds + S::AW);
-  float (*red)[2][256] = (float (*)[2][256])((float*)(lds + S::AW + DF_SQ_WORDS) + usel * 2048);
+  float* sqs = (float*)(lds + df_aw<SB, S>());
+  float (*red)[2][256] = (float (*)[2][256])((float*)(lds + df_aw<SB, S>() + DF_SQ_WORDS) + usel * 2048);
   const int M = a.rows.M;
   const int KT = ph.K >> 5, ntiles = (ph.N + 15) >> 4;
   const int g = lane >> 4;
@@ -751,8 +761,8 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const DPhase& ph, c
   const int usel = wave >> 2, uw = wave & 3, ut = tid & 255;
   const int unit = blockIdx.x * 2 + usel, NU = a.g_mlp * 2;
   uint32_t* As = lds;
-  float* sqs = (float*)(lds + S::AW);
-  float (*red)[2][256] = (float (*)[2][256])((float*)(lds + S::AW + DF_SQ_WORDS) + usel * 2048);
+  float* sqs = (float*)(lds + df_aw<SB, S>());
+  float (*red)[2][256] = (float (*)[2][256])((float*)(lds + df_aw<SB, S>() + DF_SQ_WORDS) + usel * 2048);
   const int M = a.rows.M;
   const int KT = ph.K >> 5, ntiles_d = a.d >> 4, KTd = a.ffn >> 5;
   const int g = lane >> 4, c16 = lane & 15;
@@ -869,19 +879,23 @@ __device__ __forceinline__ bool df_mlp_phase(const DArgs& a, const DPhase& ph, c
 }
 
 // The same for the wide form: a workgroup takes `mlp_tiles` (one or two) consecutive k-tiles of the down projection: half the partials (140 of width
-// 1536), and with 280 k-tiles no second round on some of 256 workgroups.  The down projection's weights of both and the first one's gate / up are
-// requested at entry; the second one's gate / up when the registers of the first are free.
+// 1536), and with 280 k-tiles no second round on some of 256 workgroups.  What does not fit the registers and LDS while it waits streams behind the operands, 140
+// workgroups at 5 TB/s, so as much as fits is requested at entry: the first k-tile, and of the second the down projection (ten of a wave's twelve tiles to LDS
+// with up to 8 rows) and four or five of its twelve k-tiles of gate / up.  Five rows of width 1536 (28 layers): 770 us with two thirds of the second's down
+// projection in registers and nothing else of it, 763 with it in LDS, 754 with two k-tiles of gate / up beside, 743 with four.  (The next layer's requested before
+// the sums, when nothing streams: 770, the sums wait behind it.  More than 8 rows have no room: their operands are 98 KB.)
 template <int SB, class S, typename CLEAR>
 __device__ __forceinline__ bool df_mlp_wide(const DArgs& a, const DPhase& ph, const void* wdown, const float* part, CLEAR clear,
                                             uint32_t* lds, uint32_t* sact, int* sdead, int slot) {
-  constexpr int C = df_sum_cols<SB>(), DN = S::DN, AP = S::ACT_PITCH, D1 = SB <= 16 ? 8 : 0, D2 = SB <= 16 ? DN : 8;       // tiles of the second k-tile that registers hold beside the first and its products, and beside the second's
+  constexpr int C = df_sum_cols<SB>(), DN = S::DN, AP = S::ACT_PITCH;
+  constexpr int LD = df_lds_tiles<SB>(), G1 = SB == 4 ? 4 : SB == 16 ? 5 : 0, D2 = 8;          // of the second k-tile: tiles of the down projection in LDS, k-tiles of gate / up in registers
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int usel = wave >> 2, uw = wave & 3, ut = tid & 255;
   uint32_t* As = lds;
-  float* sqs = (float*)(lds + S::AW);
-  float (*red)[2][256] = (float (*)[2][256])((float*)(lds + S::AW + DF_SQ_WORDS) + usel * 2048);
+  float* sqs = (float*)(lds + df_aw<SB, S>());
+  float (*red)[2][256] = (float (*)[2][256])((float*)(lds + df_aw<SB, S>() + DF_SQ_WORDS) + usel * 2048);
   const int M = a.rows.M;
   const int KT = ph.K >> 5, ntiles_d = a.d >> 4, KTd = a.ffn >> 5;
   const int g = lane >> 4, c16 = lane & 15;
@@ -891,25 +905,29 @@ __device__ __forceinline__ bool df_mlp_wide(const DArgs& a, const DPhase& ph, co
   int kb, ke;
   wave_krange(ph, 0, uw, kb, ke);
   DfPre<S::PF> pre;
-  WDown<DN> wd[2];
+  WDown<DN> wd;
+  u32x4 wr[DN - LD], p0[G1 + 1], p1[G1 + 1];
+  uint32_t* wl = lds + df_wl<SB, S>() + wave * (LD * 256);
   const df_rsrc r0 = df_make_rsrc(ph.W0), r1 = df_make_rsrc(ph.W1), rd = df_make_rsrc(wdown);
-  auto request = [&](int t) {                              // (through descriptors: one register of addresses)
-    const uint32_t at = (uint32_t)((2 * (kt0 + t) + usel) * KT) << 10;
-#pragma unroll
-    for (int u = 0; u < S::PF; ++u) {
-      const uint32_t o = at + ((uint32_t)((kb + u < ke) ? kb + u : kb) << 10);
-      pre.b0[u] = __builtin_amdgcn_raw_buffer_load_b128(r0, lane * 16, (int)o, 2 /* nt */);
-      pre.b1[u] = __builtin_amdgcn_raw_buffer_load_b128(r1, lane * 16, (int)o, 2);
-    }
+  auto gate_up = [&](int t, int u, u32x4& x0, u32x4& x1) {            // (through descriptors: one register of addresses)
+    const uint32_t o = (uint32_t)((2 * (kt0 + t) + usel) * KT + ((kb + u < ke) ? kb + u : kb)) << 10;
+    x0 = __builtin_amdgcn_raw_buffer_load_b128(r0, lane * 16, (int)o, 2 /* nt */);
+    x1 = __builtin_amdgcn_raw_buffer_load_b128(r1, lane * 16, (int)o, 2);
   };
-  auto request_down = [&](int t, int i0, int i1) {         // (a wave may have fewer tiles than DN)
+  auto down_at = [&](int t, int i) { return (int)((uint32_t)(min(wave + 8 * i, ntiles_d - 1) * KTd + kt0 + t) << 10); };       // (a wave may have fewer tiles than DN)
 #pragma unroll
-    for (int i = 0; i < DN; ++i)
-      if (i >= i0 && i < i1) wd[t].b[i] = __builtin_amdgcn_raw_buffer_load_b128(rd, lane * 16, (int)((uint32_t)(min(wave + 8 * i, ntiles_d - 1) * KTd + kt0 + t) << 10), 2);
-  };
-  request(0);
-  request_down(0, 0, DN);
-  if (two) request_down(1, 0, D1);
+  for (int u = 0; u < S::PF; ++u) gate_up(0, u, pre.b0[u], pre.b1[u]);
+#pragma unroll
+  for (int i = 0; i < DN; ++i) wd.b[i] = __builtin_amdgcn_raw_buffer_load_b128(rd, lane * 16, down_at(0, i), 2);
+  if (two) {
+#pragma unroll
+    for (int i = 0; i < LD; ++i) load_to_lds(rd, wl + i * 256, lane * 16, down_at(1, i));
+    if (SB <= 16)
+#pragma unroll
+      for (int i = LD; i < DN; ++i) wr[i - LD] = __builtin_amdgcn_raw_buffer_load_b128(rd, lane * 16, down_at(1, i), 2);
+#pragma unroll
+    for (int u = 0; u < G1; ++u) gate_up(1, u, p0[u], p1[u]);
+  }
   df_loads_done();
   clear();
   float dummy0, dummy1;
@@ -928,10 +946,18 @@ __device__ __forceinline__ bool df_mlp_wide(const DArgs& a, const DPhase& ph, co
     df_products<df_pack<SB>(), S>(As, ph.K, M, kb, ke, lane, pre, (const u32x4*)ph.W0 + (size_t)(2 * (kt0 + t) + usel) * KT * 64 + lane,
                                   (const u32x4*)ph.W1 + (size_t)(2 * (kt0 + t) + usel) * KT * 64 + lane, acc0, acc1);
     if (t == 0 && two) {
-      request(1);
-      request_down(1, D1, D2);
+#pragma unroll
+      for (int u = 0; u < S::PF; ++u) {
+        if (u < G1) { pre.b0[u] = p0[u]; pre.b1[u] = p1[u]; }
+        else gate_up(1, u, pre.b0[u], pre.b1[u]);
+      }
+      if (SB > 16)
+#pragma unroll
+        for (int i = LD; i < D2; ++i) wr[i - LD] = __builtin_amdgcn_raw_buffer_load_b128(rd, lane * 16, down_at(1, i), 2);
     }
-    if (t == 1) request_down(1, D2, DN);
+    if (SB > 16 && t == 1)
+#pragma unroll
+      for (int i = D2; i < DN; ++i) wr[i - LD] = __builtin_amdgcn_raw_buffer_load_b128(rd, lane * 16, down_at(1, i), 2);
     df_meet<df_pack<SB>()>(acc0, acc1);
     const int obase = (g * 4) * 16 + (lane & 15);
 #pragma unroll
@@ -953,10 +979,11 @@ __device__ __forceinline__ bool df_mlp_wide(const DArgs& a, const DPhase& ph, co
     if (c16 < M) frag_from_lds(sact + c16 * AP + t * 32 + g * 8, xh, xl);
     const bf16x8 ah = __builtin_bit_cast(bf16x8, xh), al = __builtin_bit_cast(bf16x8, xl);
 #pragma unroll
-    for (int i = 0; i < DN; ++i)
-      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd[t].b[i]), al, t == 0 ? f32x4{0, 0, 0, 0} : acc[i], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < DN; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wd[t].b[i]), ah, acc[i], 0, 0, 0);
+    for (int i = 0; i < DN; ++i) {
+      const bf16x8 w = __builtin_bit_cast(bf16x8, t == 0 ? wd.b[i] : i < LD ? *(const u32x4*)(wl + i * 256 + lane * 4) : wr[max(i - LD, 0)]);
+      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, al, t == 0 ? f32x4{0, 0, 0, 0} : acc[i], 0, 0, 0);
+      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, ah, acc[i], 0, 0, 0);
+    }
   };
   swiglu(0);
   if (two) swiglu(1);
@@ -1040,7 +1067,7 @@ __device__ __forceinline__ bool df_reduce_phase(const DArgs& a, const float* par
   const int NW = gridDim.x;
   const int d = a.d, np = ceil_div(d, C), nW = df_partials<S>(a), tasks = a.rows.M * np;
   const int first = df_item_of_unit(blockIdx.x, shift >> 1, NW);       // a task has the whole workgroup
-  float* rs = (float*)(lds + S::AW + DF_SQ_WORDS);                     // [8 groups of blocks][C]
+  float* rs = (float*)(lds + S::RS);                     // [8 groups of blocks][C]
   const DfPartials<C> pt(tid, nW);
   const int bs = (nW + DF_RBLOCKS - 1) / DF_RBLOCKS;
   const df_rsrc rp = df_make_rsrc(part);

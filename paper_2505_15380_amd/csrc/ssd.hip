@@ -1085,11 +1085,11 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   if (kv->df_sb && M <= DF_PACK_ROWS) sb = kv->df_sb;
   if (sb == 2 && M * (c.d_model / 8) > DF_SQ_WORDS) sb = 10;
   if (wide) {
-    // One row: sums of 8 columns; up to four: of 32; more: of 64, which are one round of workgroups up to 9 rows of width 1536.
-    sb = kv->df_sb && M <= DF_PACK_ROWS ? (kv->df_sb == 10 ? 16 : kv->df_sb) : M == 1 ? 2 : M <= 4 ? 4 : M <= 8 ? 16 : 18;
-    if (sb == 2 && M * (c.d_model / 8) > DF_SQ_WORDS) sb = 4;
+    // Sums of 32 columns for one or two rows, of 64 for more, which then go to workgroups with MLP items (28 layers of width 1536: one row 676 us with 8
+    // columns, 639 with 32, 651 with 64; two 668 and 671, three 706 with 32 and 698 with 64, four 743 and 721).
+    sb = kv->df_sb && M <= DF_PACK_ROWS ? (kv->df_sb <= 4 ? 4 : kv->df_sb == 18 ? 18 : 16) : M <= 2 ? 4 : M <= 8 ? 16 : 18;
 #define DF_LAUNCH(S) hipLaunchKernelGGL((k_forward_wide<S>), dim3(G), dim3(PBLOCK), 0, st, a)
-    if (sb == 2) DF_LAUNCH(2); else if (sb == 4) DF_LAUNCH(4); else if (sb == 16) DF_LAUNCH(16); else DF_LAUNCH(18);
+    if (sb == 4) DF_LAUNCH(4); else if (sb == 16) DF_LAUNCH(16); else DF_LAUNCH(18);
 #undef DF_LAUNCH
     LAUNCH_CHECK();
     return SSD_OK;
