@@ -107,7 +107,9 @@ int    ssd_model_destroy(ssd_model* m);
  * Pool layout (dtype elements): keys [layer][0][block][kv_head][token_in_block][head_dim], stored after the
  * rotary embedding; values [layer][1][block][kv_head][head_dim][token_in_block] (token-minor, the order the
  * matrix-core attention reads them in).  The pool must hold finite values (e.g. zeros) when handed over.  `max_rows` bounds the rows of one forward per sequence (K+1 for verify, the
- * chunk of a prefill); max_seqs*max_rows <= 1024.  `pending_cap` is 1 for a target cache and 2 for a draft
+ * chunk of a prefill); max_seqs*max_rows <= 1024.  A bf16 cache with max_seqs 1 and max_rows 1024, the most, takes a prompt in launches of up to
+ * 4096 rows where the model's attention of so many rows needs no merge (head_dim 64 or 128, 16-token blocks, more than 8 query heads on 256
+ * compute units); ssd_kv_workspace_bytes counts the room, as far as max_positions has use for it.  `pending_cap` is 1 for a target cache and 2 for a draft
  * cache (a draft may owe two tokens after a fully accepted cycle).  Blocks are handed out lowest id first;
  * see ssd_kv_state for the exact bookkeeping.  dev_ws must hold ssd_kv_workspace_bytes(). */
 size_t ssd_kv_pool_bytes(const ssd_model* m, int n_blocks, int block_tokens);
@@ -283,6 +285,9 @@ int ssd_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4]);
 /* {column block, row block, k-slice} of each workgroup of such a launch, {-1, -1, -1} of one that has none, up to `cap` workgroups; workgroup w runs
  * on XCD w % 8.  Returns the number of workgroups. */
 int ssd_gemm_blocks(int kind, int rows, int n, int k, int cus, int* blocks, int cap);
+/* Both for a prompt's launches, which have up to 4096 rows where ssd_kv_create says so (kind 0, 2, 3, 4): plan, and the blocks of up to `cap`
+ * workgroups; returns their number. */
+int ssd_prompt_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4], int* blocks, int cap);
 int ssd_attention_plan(int head_dim, int n_q_heads, int n_kv_heads, int n_seqs, int rows, int prompt_positions, int cus, int plan[3]);
 
 const char* ssd_strerror(int code);

@@ -317,7 +317,8 @@ __global__ void __launch_bounds__(WQ * WK * 64, WQ * WK / 4) k_attn_mfma(AttnArg
   constexpr int NB = 8 / WQ;                               // blocks that a wave loads of a chunk: half of a key group's waves keys, half values
   static_assert(WQ == 2 || WQ == 4, "");
   extern __shared__ u32x4 kvs[];                           // [key group][keys, values][buffer][block][KS][64]
-  const int part = blockIdx.x % a.nparts, tgroup = blockIdx.x / a.nparts, kvh = blockIdx.y, brel = blockIdx.z;
+  // (the last rows, which reach the most keys, first: a long prompt's launch has more workgroups than fit, and the short ones fill its end)
+  const int part = blockIdx.x % a.nparts, tgroup = (gridDim.x - 1 - blockIdx.x) / a.nparts, kvh = blockIdx.y, brel = blockIdx.z;
   const int seq = a.rows.seq0 + brel;
   const int R = a.rows.R, nkv = a.kv.nkv, G = a.nq / nkv, RG = R * G, m_first = brel * R;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);

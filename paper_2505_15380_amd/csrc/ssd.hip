@@ -289,11 +289,13 @@ extern "C" int ssd_model_destroy(ssd_model* m) {
 // ------------------------------------------------------------------------------------------------ kv
 constexpr int MAX_SPLITS = 16;   // capacity of the k-split partial buffer
 constexpr int MAX_ROWS = 1024;
+constexpr int MAX_PROMPT_ROWS = 4096;
 
 struct ssd_kv {
   const ssd_model* m;
   KvView v;
   int max_seqs, max_rows, NC;
+  int prompt_rows;                 // rows that the per-operator buffers have room for (at least max_seqs * max_rows)
   // workspace
   Rows rows;
   float *h, *q, *o_part, *ml_part, *part, *logits, *probs;
@@ -339,10 +341,17 @@ static bool small_shape(const ssd_model_config& c) {
          c.n_q_heads / c.n_kv_heads <= SF_MAX_GROUP;
 }
 
+// Rows of the per-operator buffers.  A cache for one sequence's prompts in the largest launches (max_seqs 1, max_rows 1024) takes launches of up to
+// 4096 rows where attention needs no partials for them (prompt_chunk): 136 MB more for the 0.5B shape and 4096 positions.
+static int prompt_capacity(const ssd_model* m, int max_seqs, int max_rows) {
+  if (max_seqs != 1 || max_rows != MAX_ROWS || m->c.dtype != SSD_DTYPE_BF16 || m->c.head_dim == 32) return max_seqs * max_rows;
+  return std::min(std::max(m->max_positions, MAX_ROWS), MAX_PROMPT_ROWS);
+}
+
 static size_t kv_layout(const ssd_model* m, int max_seqs, int max_rows, int n_blocks, int mbps, void* base, ssd_kv* kv) {
   const ssd_model_config& c = m->c;
   Carver cv(base);
-  const int Mmax = max_seqs * max_rows;
+  const int Mmax = max_seqs * max_rows, Wmax = prompt_capacity(m, max_seqs, max_rows);
   const int NC = cdiv(m->max_positions, ATT_CHUNK);
   const int nqd = c.n_q_heads * c.head_dim;
   int32_t* len = cv.take<int32_t>(max_seqs);
@@ -352,13 +361,13 @@ static size_t kv_layout(const ssd_model* m, int max_seqs, int max_rows, int n_bl
   int32_t* table = cv.take<int32_t>((size_t)max_seqs * mbps);
   int32_t* free_stack = cv.take<int32_t>(n_blocks);
   int32_t* ctl = cv.take<int32_t>(8);
-  int32_t* rpos = cv.take<int32_t>(Mmax);
-  int32_t* ract = cv.take<int32_t>(Mmax);
+  int32_t* rpos = cv.take<int32_t>(Wmax);
+  int32_t* ract = cv.take<int32_t>(Wmax);
   int32_t* scratch_i = cv.take<int32_t>(2 * max_seqs);
-  const int Mpad = cdiv(Mmax, 16) * 16;                    // operand buffers also serve as split rows: whole row tiles
-  float* h = cv.take<float>((size_t)Mmax * c.d_model);
+  const int Mpad = cdiv(Wmax, 16) * 16;                    // operand buffers also serve as split rows: whole row tiles
+  float* h = cv.take<float>((size_t)Wmax * c.d_model);
   void* xn = cv.take<float>((size_t)Mpad * c.d_model);
-  float* q = cv.take<float>((size_t)Mmax * nqd);
+  float* q = cv.take<float>((size_t)Wmax * nqd);
   float* o_part = cv.take<float>((size_t)Mmax * c.n_q_heads * NC * c.head_dim);
   float* ml_part = cv.take<float>((size_t)Mmax * c.n_q_heads * NC * 2);
   void* attn = cv.take<float>((size_t)Mpad * nqd);
@@ -414,6 +423,7 @@ static size_t kv_layout(const ssd_model* m, int max_seqs, int max_rows, int n_bl
     kv->h = h; kv->xn = xn; kv->q = q; kv->o_part = o_part; kv->ml_part = ml_part; kv->attn = attn; kv->part = part;
     kv->act = act; kv->logits = logits; kv->probs = probs;
     kv->NC = NC;
+    kv->prompt_rows = Wmax;
   }
   return cv.size();
 }
@@ -698,6 +708,27 @@ static auto gemm_shapes() {
                                      {2, 4, 2, D, 4.31f, 0.004f, 0.103f}, {3, 2, 3, D, 2.85f, 0.f, 0.117f}, {4, 3, 4, D, 3.67f, 0.f, 0.157f},
                                      {4, 4, 4, D, 4.94f, 0.f, 0.144f}, {4, 6, 4, D, 4.59f, 0.221f, 0.f}}};
 }
+// Launches of more than 1024 rows, which only prompts have: a compute unit then has several workgroups whatever the tile, so the tiles are those of four
+// waves that leave room for a second workgroup, whose matrix instructions hide the first one's operands and epilogue (gate / up, down), and wider
+// ones than a single round wants (QKV, output projection).  Figures as above, fitted to 1100 to 4096 rows of the 0.5B shape and 1100 to 3000 of the
+// 1.5B shape (14 sizes, 9 to 25 shapes each): the shape picked is 0.4 to 0.7 us a launch slower on average than the fastest, 3 at most.  us a layer against
+// what the figures above pick, at 4096 rows of width 896 and at 3000 of 1536: gate / up -11.4 and -6.8, down 0.5 and -13.4, QKV -6.0 and -7.6, output projection
+// -10.3 and -7.4.  (At 65 to 1024 rows these shapes are within 1 us of those picked above, mostly slower.)
+template <int EPI>
+static auto gemm_shapes_prompt() {
+  constexpr GemmKernel B = KERNEL_BLOCK, T = KERNEL_TILE, D = KERNEL_TILE_DEEP;
+  if constexpr (EPI == EPI_SWIGLU)
+    return std::array<GemmShape, 3>{{{8, 10, 4, T, 13.82f, 0.f, 0.265f}, {8, 12, 4, T, 6.78f, 0.055f, 0.325f}, {12, 8, 4, T, 0.f, 0.542f, 0.266f}}};
+  else if constexpr (EPI == EPI_PARTIAL)
+    return std::array<GemmShape, 5>{{{8, 7, 8, T, 7.06f, 0.f, 0.259f}, {8, 8, 8, T, 8.74f, 0.f, 0.264f}, {8, 10, 4, T, 2.09f, 0.105f, 0.306f},
+                                     {8, 12, 4, T, 3.85f, 0.105f, 0.326f}, {12, 8, 4, T, 3.27f, 0.095f, 0.351f}}};
+  else if constexpr (EPI == EPI_QKV)
+    return std::array<GemmShape, 6>{{{4, 6, 4, T, 3.27f, 0.001f, 0.218f}, {4, 8, 8, B, 4.68f, 0.f, 0.228f}, {8, 6, 8, T, 5.44f, 0.142f, 0.192f},
+                                     {8, 8, 8, T, 5.95f, 0.016f, 0.323f}, {8, 10, 8, T, 5.66f, 0.214f, 0.227f}, {16, 8, 8, T, 6.9f, 0.f, 0.605f}}};
+  else
+    return std::array<GemmShape, 5>{{{4, 4, 4, D, 3.49f, 0.007f, 0.212f}, {4, 6, 4, D, 6.01f, 0.f, 0.215f}, {4, 8, 4, T, 1.62f, 0.244f, 0.139f},
+                                     {8, 6, 8, T, 8.9f, 0.089f, 0.184f}, {8, 7, 8, T, 4.99f, 0.24f, 0.139f}}};
+}
 // Sizes whose k range is shorter than eight k-tiles, and k-split outputs of a width that is no multiple of 64, keep the shapes that they had
 // before: no such size was in the fit, no configuration has one, and the tests of ragged tiles hold each of them to its shape here.  (This costs a user of such
 // a width time: at 23 of the tests' sizes the shapes above were mostly the faster ones, by 0 to 30 %.)
@@ -768,25 +799,28 @@ static int launch_gemm_tile(const GemmArgs& g, const GemmPick& c, hipStream_t st
   }
 #define TILE(RT, CT, W) TILE_OF(KERNEL_TILE, RT, CT, W, 4, 4, RT == 16 ? 1 : 2)
 #define TILE_DEEP(RT, CT, W) TILE_OF(KERNEL_TILE_DEEP, RT, CT, W, 8, 8, 1)
+#define TILE_PAIR(RT, CT, W) TILE_OF(KERNEL_TILE, RT, CT, W, 3, 2, 2)       // (two k-tiles of activations in flight: more do not fit the registers beside a second workgroup's)
   if constexpr (EPI == EPI_QKV) {
     BLOCK(4, 4, 4, 1, 5); BLOCK(4, 8, 4, 2, 5);
-    TILE(4, 4, 4) TILE(4, 6, 4) TILE_DEEP(3, 2, 3)
+    TILE(4, 4, 4) TILE(4, 6, 4) TILE_DEEP(3, 2, 3) TILE(8, 6, 8) TILE(8, 8, 8) TILE(8, 10, 8) TILE(16, 8, 8)
   } else if constexpr (EPI == EPI_SWIGLU) {
     BLOCK(2, 8, 2, 2, 5); BLOCK(4, 6, 4, 1, 5); BLOCK(4, 8, 4, 2, 5); BLOCK(4, 10, 4, 1, 5); BLOCK(5, 6, 5, 1, 5); BLOCK(7, 6, 7, 1, 5); BLOCK(8, 16, 4, 2, 4);
     TILE(4, 8, 4) TILE(4, 10, 4) TILE(8, 8, 8) TILE(8, 10, 8) TILE(16, 10, 8)
-    TILE_OF(KERNEL_TILE, 8, 12, 4, 3, 2, 2)                // (two k-tiles of activations in flight: more do not fit the registers)
+    TILE_PAIR(8, 10, 4) TILE_PAIR(8, 12, 4) TILE_PAIR(12, 8, 4)
   } else if constexpr (EPI == EPI_PARTIAL) {
     BLOCK(4, 4, 4, 1, 5); BLOCK(4, 6, 4, 2, 5); BLOCK(4, 8, 4, 2, 5); BLOCK(8, 7, 8, 1, 4); BLOCK(8, 12, 4, 2, 4);
     TILE(8, 6, 8) TILE(8, 7, 8) TILE(8, 8, 8) TILE(16, 6, 8) TILE(16, 8, 8)
+    TILE_PAIR(8, 10, 4) TILE_PAIR(8, 12, 4) TILE_PAIR(12, 8, 4)
     TILE_DEEP(2, 2, 2) TILE_DEEP(4, 3, 4) TILE_DEEP(4, 4, 4)
   } else if constexpr (EPI == EPI_RESID) {
-    TILE(4, 4, 4) TILE(4, 6, 4) TILE(4, 8, 4)
+    TILE(4, 4, 4) TILE(4, 6, 4) TILE(4, 8, 4) TILE(8, 6, 8) TILE(8, 7, 8)
     TILE_DEEP(2, 2, 2) TILE_DEEP(2, 3, 2) TILE_DEEP(2, 4, 2) TILE_DEEP(3, 2, 3) TILE_DEEP(4, 3, 4) TILE_DEEP(4, 4, 4) TILE_DEEP(4, 6, 4) TILE_DEEP(4, 8, 4)
   }
 #undef BLOCK
 #undef TILE_OF
 #undef TILE
 #undef TILE_DEEP
+#undef TILE_PAIR
   return fail(SSD_EHIP, "no GEMM kernel of %d x %d tiles and %d waves", c.rt, c.ct, c.w);
 }
 
@@ -801,6 +835,7 @@ template <int EPI>
 static GemmPick pick_gemm_cut(const GemmArgs& g, int cus, int max_slices) {
   const int KT = g.K / 32, MT = cdiv(g.M, 16);
   constexpr bool whole_k = EPI == EPI_QKV || EPI == EPI_RESID;
+  if (g.M > MAX_ROWS) return pick_gemm_shape<EPI>(g, cus, max_slices, gemm_shapes_prompt<EPI>());
   if (KT >= 8 && (max_slices == 1 || g.N % 64 == 0)) {
     if (MT > (EPI == EPI_SWIGLU ? 4 : 1)) return pick_gemm_shape<EPI>(g, cus, max_slices, gemm_shapes<EPI>());
   } else if (MT > (whole_k ? 32 : 4) && !(EPI == EPI_RESID && plan_wgs(gemm_plan<EPI>(g, 4, 4, 1)) <= cus)) {
@@ -828,6 +863,8 @@ static GemmPick pick_gemm(const GemmArgs& g, int cus, int max_slices) {
   place_tiles(c.p, c.rt, c.ct);
   return c;
 }
+// Slices of k-split outputs of `rows` rows in the buffer of partials, which has room for MAX_SPLITS of `capacity` rows.
+static int partial_slices(int capacity, int rows) { return std::min(MAX_SPLITS, std::max(1, MAX_SPLITS * capacity / rows)); }
 // Returns the number of k-slices (1 unless `max_slices` allows more: outputs that are k-split partials); EPI_RESID: of the pieces of a
 // row's sum of squares.
 template <int EPI>
@@ -1188,6 +1225,7 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
   const void* const normed = bf16 ? (const void*)kv->xn : kv->h;           // fp32: the GEMM normalises its operand itself
   const size_t part_stride = (size_t)M * d;
   const int pairs_d = cdiv(d, 32);
+  const int max_slices = partial_slices(kv->max_seqs * kv->max_rows, M);
   // The output projection is not k-split: its epilogue adds the residual and prepares the norm before gate / up, and no add + norm
   // kernel runs between them (1024 rows: 10.8 us of width 896 and 21.4 of 1536, where two k-slices and the add + norm kernel took 9.8 + 7.6
   // and 16.2 + 12).
@@ -1257,7 +1295,7 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     g.out = kv->part; g.out_split_stride = part_stride; g.ldo = d;
     {
       ProfScope ps(PROF_DOWN, st);
-      if constexpr (bf16) { n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, MAX_SPLITS, st); rc = std::min(0, n_part); }
+      if constexpr (bf16) { n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, max_slices, st); rc = std::min(0, n_part); }
       else { g.h = kv->h; rc = launch_gemm_f32<EPI_RESID>(g, pairs_d, st); }
     }
     if (rc) return rc;
@@ -1293,6 +1331,18 @@ static int check_sample(const ssd_sample_config* s) {
 }
 
 // ------------------------------------------------------------------------------------------------ prefill
+// Rows of a prompt's launches: the caller's max_rows, or what the buffers hold where that is more and a launch of more than 1024 rows attends in one part
+// whatever its rows (its tiles alone are for more than half of the device: pick_attn_mfma), since the buffers of attention's partials have room for
+// max_rows.  Every launch of a layer costs 5 to 10 us beside its loop, and one
+// of 1024 rows fills the device once, mostly not evenly: 4096 positions of the 0.5B shape took 10.62 ms in four launches and take 7.88 in one (8.85 with the
+// tiles of 1024 rows), 1501 of the 1.5B shape 9.55 ms and 8.41.
+static int prompt_chunk(const ssd_kv* kv) {
+  const ssd_model_config& c = kv->m->c;
+  const int tiles = cdiv(MAX_ROWS * (c.n_q_heads / c.n_kv_heads), 16);
+  const bool one_part = kv->attn_mfma && kv->v.bt == 16 && cdiv(tiles, 4) * c.n_kv_heads > kv->cus / 2;
+  return one_part ? std::max(kv->max_rows, kv->prompt_rows) : kv->max_rows;
+}
+
 extern "C" int ssd_prefill(ssd_model* m, ssd_kv* kv, int seq, const int32_t* dev_tokens, int n, void* stream) {
   int rc = check_pair(m, kv);
   if (rc) return rc;
@@ -1305,7 +1355,7 @@ extern "C" int ssd_prefill(ssd_model* m, ssd_kv* kv, int seq, const int32_t* dev
   kv->len_ub[seq] = 0;
   kv->npend_ub[seq] = 0;
   if ((rc = kv_check_room(kv, seq, 1, n - 1, st))) return rc;
-  const int chunk = std::min(kv->max_rows, MAX_ROWS);
+  const int chunk = prompt_chunk(kv);
   for (int i = 0; i < n - 1; i += chunk) {
     const int R = std::min(chunk, n - 1 - i);
     if ((rc = forward_any(m, kv, seq, 1, R, 0, dev_tokens + i, 0, false, st))) return rc;
@@ -1796,8 +1846,8 @@ extern "C" int ssd_trace_barriers(ssd_kv* kv, int enable, void* stream, unsigned
 }
 
 // ------------------------------------------------------------------------------------------------ launch plans (host only)
-static int gemm_pick_of(int kind, int rows, int n, int k, int cus, GemmPick& c) {
-  if (rows < 1 || rows > MAX_ROWS || n < 1 || k < 32 || k % 32 || cus < 1) return fail(SSD_EINVAL, "bad GEMM size");
+static int gemm_pick_of(int kind, int rows, int n, int k, int cus, GemmPick& c, int max_rows = MAX_ROWS) {
+  if (rows < 1 || rows > max_rows || n < 1 || k < 32 || k % 32 || cus < 1) return fail(SSD_EINVAL, "bad GEMM size");
   GemmArgs g;
   memset(&g, 0, sizeof g);
   g.M = rows; g.N = n; g.K = k;
@@ -1805,11 +1855,19 @@ static int gemm_pick_of(int kind, int rows, int n, int k, int cus, GemmPick& c) 
     case PROF_QKV: c = pick_gemm<EPI_QKV>(g, cus, 1); break;
     case PROF_O: c = pick_gemm<EPI_RESID>(g, cus, 1); break;
     case PROF_GATEUP: c = pick_gemm<EPI_SWIGLU>(g, cus, 1); break;
-    case PROF_DOWN: c = pick_gemm<EPI_PARTIAL>(g, cus, MAX_SPLITS); break;
+    case PROF_DOWN: c = pick_gemm<EPI_PARTIAL>(g, cus, partial_slices(MAX_ROWS, std::max(rows, MAX_ROWS))); break;
     case PROF_HEAD: c = pick_gemm<EPI_PARTIAL>(g, cus, 1); break;
     default: return fail(SSD_EINVAL, "no GEMM of kind %d", kind);
   }
   return SSD_OK;
+}
+
+static int gemm_blocks_of(const GemmPick& c, int* blocks, int cap) {
+  for (int w = 0; w < std::min(cap, 8 * c.p.per_xcd); ++w) {
+    int* b = blocks + 3 * (size_t)w;
+    if (!tile_block(c.p, w, b[0], b[1], b[2])) b[0] = b[1] = b[2] = -1;
+  }
+  return 8 * c.p.per_xcd;
 }
 
 extern "C" int ssd_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4]) {
@@ -1824,11 +1882,15 @@ extern "C" int ssd_gemm_blocks(int kind, int rows, int n, int k, int cus, int* b
   GemmPick c;
   if (cap > 0 && !blocks) return fail(SSD_EINVAL, "no room for the blocks");
   if (int rc = gemm_pick_of(kind, rows, n, k, cus, c)) return rc;
-  for (int w = 0; w < std::min(cap, 8 * c.p.per_xcd); ++w) {
-    int* b = blocks + 3 * (size_t)w;
-    if (!tile_block(c.p, w, b[0], b[1], b[2])) b[0] = b[1] = b[2] = -1;
-  }
-  return 8 * c.p.per_xcd;
+  return gemm_blocks_of(c, blocks, cap);
+}
+
+extern "C" int ssd_prompt_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4], int* blocks, int cap) {
+  GemmPick c;
+  if (!plan || kind == PROF_HEAD || (cap > 0 && !blocks)) return fail(SSD_EINVAL, "bad GEMM size");
+  if (int rc = gemm_pick_of(kind, rows, n, k, cus, c, MAX_PROMPT_ROWS)) return rc;
+  plan[0] = c.kernel; plan[1] = c.rt; plan[2] = c.ct; plan[3] = c.p.n_slices;
+  return gemm_blocks_of(c, blocks, cap);
 }
 
 extern "C" int ssd_attention_plan(int head_dim, int n_q_heads, int n_kv_heads, int n_seqs, int rows, int prompt_positions, int cus, int plan[3]) {

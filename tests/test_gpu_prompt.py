@@ -1,0 +1,80 @@
+"""Prompts in launches of more than 1024 rows: every tile that such launches pick, and which launches there are."""
+import ctypes as C
+
+import pytest
+
+from tests.test_gpu_parity import check_prompt
+
+QKV, O, GATE_UP, DOWN = 0, 2, 3, 4
+BLOCK, TILE, TILE_DEEP = 1, 2, 3
+# (query heads, kv heads, head size, width, ffn, rows): the tiles of QKV, output projection, gate / up and down
+SIZES = [((9, 1, 64, 32, 96, 1025), ((TILE, 4, 6), (TILE_DEEP, 4, 4), (TILE, 12, 8), (TILE, 8, 10))),
+         ((9, 1, 64, 1056, 96, 1025), ((TILE, 4, 6), (TILE, 4, 8), (TILE, 8, 12), (TILE, 8, 10))),
+         ((12, 12, 64, 2080, 96, 1025), ((TILE, 8, 6), (TILE, 8, 7), (TILE, 8, 10), (TILE, 8, 10))),
+         ((14, 2, 64, 672, 96, 1537), ((BLOCK, 4, 8), (TILE_DEEP, 4, 6), (TILE, 8, 12), (TILE, 8, 10))),
+         ((9, 1, 64, 32, 4896, 2049), ((TILE, 4, 6), (TILE_DEEP, 4, 4), (TILE, 12, 8), (TILE, 8, 7))),
+         ((24, 8, 64, 2080, 1056, 1153), ((TILE, 8, 8), (TILE, 8, 6), (TILE, 8, 10), (TILE, 12, 8))),
+         ((40, 8, 64, 544, 4896, 1153), ((TILE, 8, 10), (TILE_DEEP, 4, 4), (TILE, 8, 12), (TILE, 8, 12))),
+         ((12, 12, 64, 672, 96, 3073), ((TILE, 16, 8), (TILE, 8, 7), (TILE, 8, 12), (TILE, 8, 10))),
+         ((9, 1, 64, 1600, 4896, 1025), ((TILE, 4, 6), (TILE, 4, 8), (TILE, 8, 12), (TILE, 8, 8))),
+         ((12, 2, 128, 96, 96, 1501), ((TILE, 4, 6), (TILE_DEEP, 4, 4), (TILE, 12, 8), (TILE, 8, 10)))]
+
+
+def _shape(nq, nkv, hd, d, ffn):
+    return dict(n_layers=2, d_model=d, n_q_heads=nq, n_kv_heads=nkv, head_dim=hd, d_ffn=ffn, vocab=41, n_embed=43, dtype="bf16",
+                qkv_bias=1, rope_base=1.0e4, rms_eps=1e-6)
+
+
+def _gemms(nq, nkv, hd, d, ffn):
+    return (QKV, (nq + 2 * nkv) * hd, d), (O, d, nq * hd), (GATE_UP, ffn, d), (DOWN, d, ffn)
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2505_15380_amd as pkg
+    return pkg.load_library()
+
+
+@pytest.mark.parametrize("size,tiles", SIZES)
+def test_sizes_reach_the_tiles_they_name(lib, size, tiles):
+    plan = (C.c_int * 4)()
+    for (kind, n, k), want in zip(_gemms(*size[:5]), tiles):
+        assert lib.ssd_prompt_gemm_plan(kind, size[5], n, k, 256, plan, None, 0) > 0
+        assert tuple(plan[:3]) == want, kind
+
+
+def test_blocks_of_a_prompts_launch_cover_the_output_once(lib):
+    plan, blocks = (C.c_int * 4)(), (C.c_int * (3 * 65536))()
+    for rows in (1, 1024, 1025, 1501, 2500, 4095, 4096):
+        for n, k in ((896, 896), (1152, 896), (2048, 1536), (4864, 896), (8960, 1536), (896, 4864), (1536, 8960), (352, 64), (96, 32)):
+            for kind in (QKV, O, GATE_UP, DOWN):
+                for cus in (256, 64):
+                    wgs = lib.ssd_prompt_gemm_plan(kind, rows, n, k, cus, plan, blocks, 65536)
+                    assert 0 < wgs <= 65536
+                    _, rt, ct, slices = plan
+                    assert slices * rows <= 16 * max(1024, rows) and slices <= 8
+                    got = sorted(tuple(blocks[3 * w:3 * w + 3]) for w in range(wgs) if blocks[3 * w] >= 0)
+                    tiles = -(-n // 16) * (2 if kind == GATE_UP else 1)
+                    assert got == sorted((c, r, s) for s in range(slices) for c in range(-(-tiles // ct)) for r in range(-(-rows // (16 * rt))))
+    assert lib.ssd_prompt_gemm_plan(QKV, 4097, 32, 32, 256, plan, None, 0) == -1 and lib.ssd_prompt_gemm_plan(5, 16, 32, 32, 256, plan, None, 0) == -1
+    assert lib.ssd_prompt_gemm_plan(QKV, 16, 32, 32, 256, None, None, 0) == -1 and lib.ssd_prompt_gemm_plan(QKV, 16, 32, 32, 256, plan, None, 1) == -1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("size", [s for s, _ in SIZES])
+def test_each_tile_against_the_oracle(size):
+    """Last row tiles of one row and ragged ones, ragged last column blocks, k ranges of one k-tile and of more than the buffers hold, k-slices."""
+    check_prompt(_shape(*size[:5]), size[5], 85 + size[5] % 7)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nq,rows,launches", [(9, 4096, 1), (9, 4181, 2), (8, 1057, 2)])
+def test_which_launches_a_prompt_takes(nq, rows, launches):
+    """Up to 4096 rows a launch; the rest attends to the cached ones.  Eight query heads would need partials: 1024 rows a launch."""
+    import paper_2505_15380_amd as ssd
+    ssd.ssd_profile_begin("qkv")
+    try:
+        check_prompt(_shape(nq, 1, 64, 64, 96), rows, 21)
+    finally:
+        _, count = ssd.ssd_profile_end()
+    assert count == 2 * launches             # (two layers)
