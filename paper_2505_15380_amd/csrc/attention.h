@@ -299,8 +299,8 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
 // a wave has 80 a chunk, half of them for the split of P, and 16 exponentials.  With few keys per workgroup it is the chain of
 // dependent latencies, and the code itself, fetched cold by every launch.
 // So there are two loops.  Eight waves (4 tiles x 2 key groups, or 2 x 4: the launch's choice) take short parts: one copy of the code,
-// the reference is the running maximum.  4 x 4 takes prompts whose parts have more than 16 chunks (and head size 64: 128 KB of LDS):
-// sixteen waves to overlap matrix and vector instructions, and the reference, the maximum of the row's first chunk, moves only to a score that exceeds it by ATT_LAZY, so that
+// the reference is the running maximum.  The other (LAZY) takes prompts whose parts have more than 16 chunks, with head size 64 on sixteen waves of a compute
+// unit (4 x 4, 8 x 2 or two workgroups of 4 x 2: pick_attn_mfma) to overlap matrix and vector instructions, and the reference, the maximum of the row's first chunk, moves only to a score that exceeds it by ATT_LAZY, so that
 // the usual chunk asks each lane for its own largest score and no more (some row of sixteen has a new maximum in most chunks: a
 // maximum across lanes and 40 instructions of scaling).  The heaviest key then weighs anything up to 2^8 instead of 1, which the
 // truncating split holds exactly; the split of later chunks rounds hi to nearest in return (error against 64 bits 0.85 times the other
@@ -310,12 +310,11 @@ __global__ void __launch_bounds__(att_f32_waves<HD>() * WAVE) k_attn_f32(AttnArg
 constexpr float ATT_LAZY = 8.0f;                         // weights may reach 2^8 before the reference moves (fp32 sums and the hi + lo split of
                                                          // a weight are as exact at any scale)
 
-template <int HD, int WQ, int WK>
-__global__ void __launch_bounds__(WQ * WK * 64, WQ * WK / 4) k_attn_mfma(AttnArgs a) {
+template <int HD, int WQ, int WK, bool LAZY>
+__global__ void __launch_bounds__(WQ * WK * 64, LAZY && HD == 64 ? 4 : WQ * WK / 4) k_attn_mfma(AttnArgs a) {
   constexpr int KS = HD / 32, DT = HD / 16;
-  constexpr bool LAZY = WQ * WK == 16;
   constexpr int NB = 8 / WQ;                               // blocks that a wave loads of a chunk: half of a key group's waves keys, half values
-  static_assert(WQ == 2 || WQ == 4, "");
+  static_assert(WQ == 2 || WQ == 4 || WQ == 8, "");
   extern __shared__ u32x4 kvs[];                           // [key group][keys, values][buffer][block][KS][64]
   // (the last rows, which reach the most keys, first: a long prompt's launch has more workgroups than fit, and the short ones fill its end)
   const int part = blockIdx.x % a.nparts, tgroup = (gridDim.x - 1 - blockIdx.x) / a.nparts, kvh = blockIdx.y, brel = blockIdx.z;

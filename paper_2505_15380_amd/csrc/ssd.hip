@@ -895,17 +895,17 @@ static int launch_gemm(const GemmArgs& g, int cus, int max_slices, hipStream_t s
 // launch on every batch measured (16 x 7 rows at 256 to 4096 positions 2521 us a cycle either way, 64 x 8 at 128 to 1024 3536,
 // 8 x 9 of the 1.5B shape 3850); 48, 32 and 16 were up to 2, 5 and 8 % slower.
 constexpr int ATT_PLAN_CHUNKS = 64;
-template <int HD, int WQ, int WK>
+template <int HD, int WQ, int WK, bool LAZY>
 static int launch_attn_mfma_parts(const AttnArgs& a, int n_tg, int nkv, int B, hipStream_t st) {
   constexpr int LDS = WK * 2 * 2 * HD * 128;              // two buffers of 64 keys and 64 values per key group
   static LdsOptIn lds;
-  if (hipError_t e = lds.ask((const void*)k_attn_mfma<HD, WQ, WK>, LDS); e != hipSuccess)
+  if (hipError_t e = lds.ask((const void*)k_attn_mfma<HD, WQ, WK, LAZY>, LDS); e != hipSuccess)
     return fail(SSD_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
-  hipLaunchKernelGGL((k_attn_mfma<HD, WQ, WK>), dim3(a.nparts * n_tg, nkv, B), dim3(WQ * WK * 64), LDS, st, a);
+  hipLaunchKernelGGL((k_attn_mfma<HD, WQ, WK, LAZY>), dim3(a.nparts * n_tg, nkv, B), dim3(WQ * WK * 64), LDS, st, a);
   LAUNCH_CHECK();
   return SSD_OK;
 }
-struct AttnPick { int wq, wk, n_tg, part_chunks; };        // row tiles x key groups of a workgroup, groups of tiles, chunks of a part
+struct AttnPick { int wq, wk, n_tg, part_chunks; bool lazy; };        // row tiles x key groups of a workgroup, groups of tiles, chunks of a part; the loop whose reference rarely moves
 static AttnPick pick_attn_mfma(int hd, int rows, int group, int plan_chunks, bool prompt, int nkv, int B, int cus) {
   const int tiles = cdiv(rows * group, 16);
   // Two tiles x four key groups (head size 64) where workgroups of four tiles would be for a quarter to half of the device: a chain
@@ -918,12 +918,17 @@ static AttnPick pick_attn_mfma(int hd, int rows, int group, int plan_chunks, boo
   // 14.9 and 14.6, 832 (13) 16.6 and 15.9, 1024 (16) 18.3 and 17.1.
   const int four = B * nkv * cdiv(tiles, 4);
   const bool narrow = hd == 64 && four <= cus / 2 && four >= cus / 4;
-  AttnPick c{narrow ? 2 : 4, narrow ? 4 : 2, 0, 0};
+  AttnPick c{narrow ? 2 : 4, narrow ? 4 : 2, 0, 0, false};
   c.n_tg = cdiv(tiles, c.wq);
   const int want = std::min(std::max(1, cus / (c.n_tg * nkv * B)), cdiv(plan_chunks, c.wk));
   c.part_chunks = cdiv(cdiv(plan_chunks, want), c.wk) * c.wk;
-  if (hd == 64 && !narrow && prompt && c.part_chunks > 16) {
-    c.wk = 4;
+  // With more workgroups than compute units 4 x 2 instead, two on a compute unit, whose ends and beginnings overlap, and from three times as many 8 x 2, which reads
+  // the keys half as often (one launch for the whole prompt, 1100 / 1501 / 2500 / 4096 rows: 4 x 4 19.0 / 25.3 / 45.6 / 89, 4 x 2 18.8 / 24.7 / 44.8 / 78, 8 x 2
+  // 24.9 / 30.2 / 44.6 / 73 to 78).  Head size 128 has the room for 4 x 2 alone (1100 and 1501 rows of the 1.5B shape 29.1 -> 27.2 and 36.2 -> 33.1).
+  if (!narrow && prompt && c.part_chunks > 16) {
+    c.lazy = true;
+    if (hd == 64 && four <= cus) c.wk = 4;
+    if (hd == 64 && four > 3 * cus) { c.wq = 8; c.n_tg = cdiv(tiles, c.wq); }
     c.part_chunks = cdiv(c.part_chunks, c.wk) * c.wk;      // (a part is whole rounds of the key groups: they would walk into the next one)
   }
   return c;
@@ -935,9 +940,11 @@ static int launch_attn_mfma(AttnArgs a, int nchunks, int plan_chunks, bool promp
   a.nparts = cdiv(nchunks, c.part_chunks);
   int rc;
   if constexpr (HD == 64)
-    rc = c.wq == 2 ? launch_attn_mfma_parts<HD, 2, 4>(a, c.n_tg, nkv, B, st)
-         : c.wk == 4 ? launch_attn_mfma_parts<HD, 4, 4>(a, c.n_tg, nkv, B, st) : launch_attn_mfma_parts<HD, 4, 2>(a, c.n_tg, nkv, B, st);
-  else rc = launch_attn_mfma_parts<HD, 4, 2>(a, c.n_tg, nkv, B, st);
+    rc = c.wq == 2 ? launch_attn_mfma_parts<HD, 2, 4, false>(a, c.n_tg, nkv, B, st)
+         : c.wq == 8 ? launch_attn_mfma_parts<HD, 8, 2, true>(a, c.n_tg, nkv, B, st)
+         : c.wk == 4 ? launch_attn_mfma_parts<HD, 4, 4, true>(a, c.n_tg, nkv, B, st)
+         : c.lazy ? launch_attn_mfma_parts<HD, 4, 2, true>(a, c.n_tg, nkv, B, st) : launch_attn_mfma_parts<HD, 4, 2, false>(a, c.n_tg, nkv, B, st);
+  else rc = c.lazy ? launch_attn_mfma_parts<HD, 4, 2, true>(a, c.n_tg, nkv, B, st) : launch_attn_mfma_parts<HD, 4, 2, false>(a, c.n_tg, nkv, B, st);
   if (rc) return rc;
   if (a.nparts > 1) {
     hipLaunchKernelGGL((k_attn_combine_parts<HD>), dim3(cdiv(M * a.nq, BLOCK / (HD / 4))), dim3(BLOCK), 0, st, a);
