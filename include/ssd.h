@@ -286,7 +286,7 @@ int ssd_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4]);
  * on XCD w % 8.  Returns the number of workgroups. */
 int ssd_gemm_blocks(int kind, int rows, int n, int k, int cus, int* blocks, int cap);
 /* Both for a prompt's launches, which have up to 4096 rows where ssd_kv_create says so (kind 0, 2, 3, 4): plan, and the blocks of up to `cap`
- * workgroups; returns their number. */
+ * workgroups; returns their number.  A down projection that adds the residual itself has 0 k-slices. */
 int ssd_prompt_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4], int* blocks, int cap);
 int ssd_attention_plan(int head_dim, int n_q_heads, int n_kv_heads, int n_seqs, int rows, int prompt_positions, int cus, int plan[3]);
 

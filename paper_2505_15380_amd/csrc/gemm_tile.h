@@ -195,6 +195,7 @@ __device__ __forceinline__ float tile_epilogue(const GemmArgs& g, int t0, int t1
   } else {
     const int hd = g.kv.hd, half = hd >> 1, nq = g.nq, nkv = g.kv.nkv;
     const int n0 = t0 * 16 + col, head = n0 >> __builtin_ctz(hd), d = n0 & (hd - 1);
+    v0 *= inv; v1 *= inv;                                  // (1 unless the operand is still to be normalised)
     if (g.bias) {
       const f32x4 b0 = *(const f32x4*)(g.bias + n0), b1 = *(const f32x4*)(g.bias + n0 + half);
 #pragma unroll
@@ -310,7 +311,7 @@ __global__ void __launch_bounds__(W * 64, MINB) k_gemm_tile(GemmArgs g, TilePlan
   RowDest rd[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) rd[i] = EPI == EPI_QKV ? row_dest(g, ((rowb * W + wave) * TM + i) * 16 + (lane & 15)) : RowDest{0, -1};
-  const bool scaled = EPI == EPI_SWIGLU && g.rms_d > 0;
+  const bool scaled = (EPI == EPI_SWIGLU || EPI == EPI_QKV) && g.rms_d > 0;
   RowSums rs[TM];
   if (scaled)
 #pragma unroll
@@ -439,7 +440,7 @@ __global__ void __launch_bounds__(WR * WC * 64) k_gemm_block(GemmArgs g, TilePla
   RowDest rd[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) rd[i] = EPI == EPI_QKV ? row_dest(g, row_of(i)) : RowDest{0, -1};
-  const bool scaled = EPI == EPI_SWIGLU && g.rms_d > 0;
+  const bool scaled = (EPI == EPI_SWIGLU || EPI == EPI_QKV) && g.rms_d > 0;
   RowSums rs[TM];
   if (scaled)
 #pragma unroll

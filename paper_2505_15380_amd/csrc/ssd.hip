@@ -644,9 +644,11 @@ static TilePlan gemm_plan(const GemmArgs& g, int rows, int cols, int slices) {
 // 10 x 8 tiles, 74 MB in four row groups, the only ones that fit, and 34 in runs.  us a launch in a prompt, that grid -> runs: 200 rows 18.8 -> 17.3, 256
 // 19.3 -> 17.9, 448 to 512 1.0 to 2.9 less, 832 and 896 0.4 and 0.7; 1024 rows of this shape and of the 1.5B shape, where the matrix cores are what
 // counts, equal.  Grids that give an XCD up to an eighth more workgroups than a run fetch less still, and were from 1.8 us faster to 0.9 slower.)
-static void place_tiles(TilePlan& p, int rt, int ct) {
+// `xcd_cus` > 0 (a prompt's launches of more than 1024 rows, whose activations are far larger than the L2s): any grid that takes no more rounds of an XCD's compute
+// units than the runs do.
+static void place_tiles(TilePlan& p, int rt, int ct, int xcd_cus) {
   const long row = rt * 64, col = ct * 32;                 // bytes per k of a block's activations (hi + lo) and of its weights
-  const int per_slice = p.n_colb * p.n_rowb, run = p.per_xcd;
+  const int per_slice = p.n_colb * p.n_rowb, run = p.per_xcd, most = xcd_cus > 0 ? cdiv(run, xcd_cus) * xcd_cus : run;
   if (8 % p.n_slices) return;
   long best = 0;
   for (int x = 0; x < 8; ++x)
@@ -659,9 +661,10 @@ static void place_tiles(TilePlan& p, int rt, int ct) {
   for (int lc = p.lg_per; lc >= 0; --lc) {
     const int r = cdiv(p.n_rowb, 1 << (p.lg_per - lc)), c = cdiv(p.n_colb, 1 << lc);
     const long bytes = p.n_slices * (cdiv(p.n_colb, c) * (p.n_rowb * row) + cdiv(p.n_rowb, r) * (p.n_colb * col));
-    if (r * c > run || run > 4096 || r > 256 || bytes > best || (p.rows_xcd && bytes == best)) continue;      // (4096, 256: TilePlan's rows_inv)
+    if (r * c > most || most > 4096 || r > 256 || bytes > best || (p.rows_xcd && bytes == best)) continue;      // (4096, 256: TilePlan's rows_inv)
     best = bytes;
     p.rows_xcd = r; p.cols_xcd = c; p.lg_colg = lc; p.rows_inv = (1u << 20) / r + 1;
+    p.per_xcd = std::max(run, r * c);
   }
 }
 static int plan_wgs(const TilePlan& p) { return p.n_colb * p.n_rowb * p.n_slices; }
@@ -759,6 +762,7 @@ struct GemmPick {
   GemmKernel kernel;
   int rt, ct, w;                                           // row tiles x column slots of a workgroup; its waves (k_gemm_tile)
   TilePlan p;
+  double us = 0;                                           // the estimate, where the pick is by estimate
 };
 template <int EPI, typename SHAPES>
 static GemmPick pick_gemm_shape(const GemmArgs& g, int cus, int max_slices, const SHAPES& shapes) {
@@ -772,7 +776,7 @@ static GemmPick pick_gemm_shape(const GemmArgs& g, int cus, int max_slices, cons
       const double us = s.launch + q.slice_kt * (s.per_kt + s.per_wg * cdiv(plan_wgs(q), cus)) + (EPI == EPI_PARTIAL ? (double)q.n_slices * g.M * g.N * 4 * 0.44e-6 : 0.0);
       if (!c.w || us < best_us) { c = s; best_us = us; p = q; }
     }
-  return {c.kernel, c.rt, c.ct, c.w, p};
+  return {c.kernel, c.rt, c.ct, c.w, p, best_us};
 }
 template <int EPI>
 static GemmPick pick_gemm_ragged(const GemmArgs& g, int cus, int max_slices) {
@@ -860,11 +864,18 @@ static GemmPick pick_gemm_cut(const GemmArgs& g, int cus, int max_slices) {
 template <int EPI>
 static GemmPick pick_gemm(const GemmArgs& g, int cus, int max_slices) {
   GemmPick c = pick_gemm_cut<EPI>(g, cus, max_slices);
-  place_tiles(c.p, c.rt, c.ct);
+  place_tiles(c.p, c.rt, c.ct, g.M > MAX_ROWS ? cus / 8 : 0);
   return c;
 }
 // Slices of k-split outputs of `rows` rows in the buffer of partials, which has room for MAX_SPLITS of `capacity` rows.
 static int partial_slices(int capacity, int rows) { return std::min(MAX_SPLITS, std::max(1, MAX_SPLITS * capacity / rows)); }
+// Does a prompt's down projection add the residual and leave the sums of squares itself, as the output projection does, so that no add + norm kernel runs ahead of the
+// next layer's QKV projection, which then divides by the r.m.s.?  For that it cannot be k-split.  Where the estimates say so, with what the add + norm kernel takes.
+// Prompts of 4096, 3400 and 3000 positions of width 896 -4.9, -1.8 and -3.4 %, of 2500 -0.3; by hand where the estimate says no, 2048 +7.4, 1501 of width 1536 +2.1.
+static bool down_adds_residual(const GemmArgs& g, int cus, int max_slices) {
+  if (g.M <= MAX_ROWS) return false;
+  return pick_gemm<EPI_RESID>(g, cus, 1).us < pick_gemm<EPI_PARTIAL>(g, cus, max_slices).us + 3.0 + 4.2e-6 * g.M * g.N;
+}
 // Returns the number of k-slices (1 unless `max_slices` allows more: outputs that are k-split partials); EPI_RESID: of the pieces of a
 // row's sum of squares.
 template <int EPI>
@@ -1243,14 +1254,15 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     LAUNCH_CHECK();
     return SSD_OK;
   };
-  int n_part = 0, pieces = 0;
+  int n_part = 0, pieces = 0, down_pieces = 0;             // (down_pieces: of the sums of squares that the down projection left, 0 where it left partials)
   int rc;
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW& L = m->layers[l];
-    if (l > 0 && (rc = add_norm(n_part, L.ln1))) return rc;      // (the first layer's: in k_embed)
+    if (l > 0 && !down_pieces && (rc = add_norm(n_part, L.ln1))) return rc;      // (the first layer's: in k_embed)
     GemmArgs g = g0;                                       // QKV + bias + rotary + cache write
     g.A = normed; g.W0 = L.wqkv; g.W1 = L.wqkv; g.N = nqkv; g.K = d;
     g.bias = L.bqkv; g.q = kv->q; g.layer = l;
+    if (down_pieces) { g.sumsq = kv->part; g.rms_d = d; g.sum_pieces = down_pieces; }
     {
       ProfScope ps(PROF_QKV, st);
       if constexpr (bf16) rc = std::min(0, launch_gemm<EPI_QKV>(g, kv->cus, 1, st));
@@ -1302,7 +1314,16 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     g.out = kv->part; g.out_split_stride = part_stride; g.ldo = d;
     {
       ProfScope ps(PROF_DOWN, st);
-      if constexpr (bf16) { n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, max_slices, st); rc = std::min(0, n_part); }
+      if constexpr (bf16) {
+        down_pieces = 0;
+        if (!with_head && down_adds_residual(g, kv->cus, max_slices)) {
+          g.gain = l + 1 < c.n_layers ? m->layers[l + 1].ln1 : m->final_norm; g.hg = kv->xn; g.h = kv->h; g.sumsq = kv->part; g.sum_pieces = 1;
+          rc = down_pieces = launch_gemm<EPI_RESID>(g, kv->cus, 1, st);
+        } else {
+          rc = n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, max_slices, st);
+        }
+        rc = std::min(0, rc);
+      }
       else { g.h = kv->h; rc = launch_gemm_f32<EPI_RESID>(g, pairs_d, st); }
     }
     if (rc) return rc;
@@ -1862,7 +1883,11 @@ static int gemm_pick_of(int kind, int rows, int n, int k, int cus, GemmPick& c, 
     case PROF_QKV: c = pick_gemm<EPI_QKV>(g, cus, 1); break;
     case PROF_O: c = pick_gemm<EPI_RESID>(g, cus, 1); break;
     case PROF_GATEUP: c = pick_gemm<EPI_SWIGLU>(g, cus, 1); break;
-    case PROF_DOWN: c = pick_gemm<EPI_PARTIAL>(g, cus, partial_slices(MAX_ROWS, std::max(rows, MAX_ROWS))); break;
+    case PROF_DOWN: {
+      const int slices = partial_slices(MAX_ROWS, std::max(rows, MAX_ROWS));
+      c = down_adds_residual(g, cus, slices) ? pick_gemm<EPI_RESID>(g, cus, 1) : pick_gemm<EPI_PARTIAL>(g, cus, slices);
+      break;
+    }
     case PROF_HEAD: c = pick_gemm<EPI_PARTIAL>(g, cus, 1); break;
     default: return fail(SSD_EINVAL, "no GEMM of kind %d", kind);
   }
@@ -1896,7 +1921,11 @@ extern "C" int ssd_prompt_gemm_plan(int kind, int rows, int n, int k, int cus, i
   GemmPick c;
   if (!plan || kind == PROF_HEAD || (cap > 0 && !blocks)) return fail(SSD_EINVAL, "bad GEMM size");
   if (int rc = gemm_pick_of(kind, rows, n, k, cus, c, MAX_PROMPT_ROWS)) return rc;
-  plan[0] = c.kernel; plan[1] = c.rt; plan[2] = c.ct; plan[3] = c.p.n_slices;
+  GemmArgs g;
+  memset(&g, 0, sizeof g);
+  g.M = rows; g.N = n; g.K = k;
+  plan[0] = c.kernel; plan[1] = c.rt; plan[2] = c.ct;
+  plan[3] = kind == PROF_DOWN && down_adds_residual(g, cus, partial_slices(MAX_ROWS, std::max(rows, MAX_ROWS))) ? 0 : c.p.n_slices;
   return gemm_blocks_of(c, blocks, cap);
 }
 

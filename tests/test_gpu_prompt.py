@@ -11,17 +11,20 @@ from tests.test_gpu_parity import check_prompt
 
 QKV, O, GATE_UP, DOWN = 0, 2, 3, 4
 BLOCK, TILE, TILE_DEEP = 1, 2, 3
-# (query heads, kv heads, head size, width, ffn, rows): the tiles of QKV, output projection, gate / up and down
-SIZES = [((9, 1, 64, 32, 96, 1025), ((TILE, 4, 6), (TILE_DEEP, 4, 4), (TILE, 12, 8), (TILE, 8, 10))),
-         ((9, 1, 64, 1056, 96, 1025), ((TILE, 4, 6), (TILE, 4, 8), (TILE, 8, 12), (TILE, 8, 10))),
-         ((12, 12, 64, 2080, 96, 1025), ((TILE, 8, 6), (TILE, 8, 7), (TILE, 8, 10), (TILE, 8, 10))),
-         ((14, 2, 64, 672, 96, 1537), ((BLOCK, 4, 8), (TILE_DEEP, 4, 6), (TILE, 8, 12), (TILE, 8, 10))),
-         ((9, 1, 64, 32, 4896, 2049), ((TILE, 4, 6), (TILE_DEEP, 4, 4), (TILE, 12, 8), (TILE, 8, 7))),
-         ((24, 8, 64, 2080, 1056, 1153), ((TILE, 8, 8), (TILE, 8, 6), (TILE, 8, 10), (TILE, 12, 8))),
-         ((40, 8, 64, 544, 4896, 1153), ((TILE, 8, 10), (TILE_DEEP, 4, 4), (TILE, 8, 12), (TILE, 8, 12))),
-         ((12, 12, 64, 672, 96, 3073), ((TILE, 16, 8), (TILE, 8, 7), (TILE, 8, 12), (TILE, 8, 10))),
-         ((9, 1, 64, 1600, 4896, 1025), ((TILE, 4, 6), (TILE, 4, 8), (TILE, 8, 12), (TILE, 8, 8))),
-         ((12, 2, 128, 96, 96, 1501), ((TILE, 4, 6), (TILE_DEEP, 4, 4), (TILE, 12, 8), (TILE, 8, 10)))]
+# (query heads, kv heads, head size, width, ffn, rows): the tiles of QKV, output projection, gate / up and down; does down add the residual itself?
+SIZES = [((9, 1, 64, 1056, 96, 1025), ((TILE, 4, 6), (TILE, 4, 8), (TILE, 8, 12), (TILE, 4, 8)), True),
+         ((9, 1, 64, 32, 608, 1025), ((TILE, 4, 6), (TILE_DEEP, 4, 4), (TILE, 12, 8), (TILE_DEEP, 4, 4)), True),
+         ((9, 1, 64, 32, 1056, 1025), ((TILE, 4, 6), (TILE_DEEP, 4, 4), (TILE, 12, 8), (TILE, 8, 10)), False),
+         ((12, 12, 64, 2080, 96, 1025), ((TILE, 8, 6), (TILE, 8, 7), (TILE, 8, 10), (TILE, 4, 8)), True),
+         ((14, 2, 64, 672, 1056, 1537), ((BLOCK, 4, 8), (TILE_DEEP, 4, 6), (TILE, 8, 12), (TILE_DEEP, 4, 6)), True),
+         ((9, 1, 64, 32, 4896, 2049), ((TILE, 4, 6), (TILE_DEEP, 4, 4), (TILE, 12, 8), (TILE, 8, 7)), False),
+         ((24, 8, 64, 2080, 1056, 1153), ((TILE, 8, 8), (TILE, 8, 6), (TILE, 8, 10), (TILE, 8, 7)), True),
+         ((40, 8, 64, 544, 4896, 1153), ((TILE, 8, 10), (TILE_DEEP, 4, 4), (TILE, 8, 12), (TILE, 8, 12)), False),
+         ((9, 1, 64, 544, 4896, 1025), ((TILE, 4, 6), (TILE_DEEP, 4, 4), (TILE, 12, 8), (TILE, 12, 8)), False),
+         ((12, 12, 64, 672, 96, 3073), ((TILE, 16, 8), (TILE, 8, 7), (TILE, 8, 12), (TILE, 4, 8)), True),
+         ((9, 1, 64, 1600, 4896, 1025), ((TILE, 4, 6), (TILE, 4, 8), (TILE, 8, 12), (TILE, 8, 8)), False),
+         ((9, 1, 64, 1600, 4896, 1153), ((TILE, 4, 6), (TILE, 4, 8), (TILE, 8, 12), (TILE, 8, 6)), True),
+         ((12, 2, 128, 96, 96, 1501), ((TILE, 4, 6), (TILE_DEEP, 4, 4), (TILE, 12, 8), (TILE, 4, 8)), True)]
 
 
 def _shape(nq, nkv, hd, d, ffn):
@@ -39,12 +42,13 @@ def lib():
     return pkg.load_library()
 
 
-@pytest.mark.parametrize("size,tiles", SIZES)
-def test_sizes_reach_the_tiles_they_name(lib, size, tiles):
+@pytest.mark.parametrize("size,tiles,unsplit", SIZES)
+def test_sizes_reach_the_tiles_they_name(lib, size, tiles, unsplit):
     plan = (C.c_int * 4)()
     for (kind, n, k), want in zip(_gemms(*size[:5]), tiles):
         assert lib.ssd_prompt_gemm_plan(kind, size[5], n, k, 256, plan, None, 0) > 0
         assert tuple(plan[:3]) == want, kind
+    assert (plan[3] == 0) == unsplit
 
 
 def test_blocks_of_a_prompts_launch_cover_the_output_once(lib):
@@ -56,6 +60,7 @@ def test_blocks_of_a_prompts_launch_cover_the_output_once(lib):
                     wgs = lib.ssd_prompt_gemm_plan(kind, rows, n, k, cus, plan, blocks, 65536)
                     assert 0 < wgs <= 65536
                     _, rt, ct, slices = plan
+                    slices = slices or 1
                     assert slices * rows <= 16 * max(1024, rows) and slices <= 8
                     got = sorted(tuple(blocks[3 * w:3 * w + 3]) for w in range(wgs) if blocks[3 * w] >= 0)
                     tiles = -(-n // 16) * (2 if kind == GATE_UP else 1)
@@ -65,9 +70,10 @@ def test_blocks_of_a_prompts_launch_cover_the_output_once(lib):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("size", [s for s, _ in SIZES])
+@pytest.mark.parametrize("size", [s[0] for s in SIZES])
 def test_each_tile_against_the_oracle(size):
-    """Last row tiles of one row and ragged ones, ragged last column blocks, k ranges of one k-tile and of more than the buffers hold, k-slices."""
+    """Last row tiles of one row and ragged ones, ragged last column blocks, k ranges of one k-tile and of more than the buffers hold, k-slices; sums of squares that
+    the down projection leaves to the next layer."""
     check_prompt(_shape(*size[:5]), size[5], 85 + size[5] % 7)
 
 
