@@ -1269,6 +1269,7 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
       else { g.gain = L.ln1; rc = launch_gemm_f32<EPI_QKV>(g, (nq + 2 * nkv) * (hd / 32), st); }
     }
     if (rc) return rc;
+    if (!with_head && l + 1 == c.n_layers) return SSD_OK;  // a prompt is its keys and values: nothing reads what comes behind the last layer's
 
     AttnArgs a;
     a.q = kv->q; a.kv = kv->v; a.rows = rows; a.layer = l; a.nq = nq; a.scale = 1.0f / sqrtf((float)hd);
@@ -1317,7 +1318,7 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
       if constexpr (bf16) {
         down_pieces = 0;
         if (!with_head && down_adds_residual(g, kv->cus, max_slices)) {
-          g.gain = l + 1 < c.n_layers ? m->layers[l + 1].ln1 : m->final_norm; g.hg = kv->xn; g.h = kv->h; g.sumsq = kv->part; g.sum_pieces = 1;
+          g.gain = m->layers[l + 1].ln1; g.hg = kv->xn; g.h = kv->h; g.sumsq = kv->part; g.sum_pieces = 1;
           rc = down_pieces = launch_gemm<EPI_RESID>(g, kv->cus, 1, st);
         } else {
           rc = n_part = launch_gemm<EPI_PARTIAL>(g, kv->cus, max_slices, st);
@@ -1328,7 +1329,6 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     }
     if (rc) return rc;
   }
-  if (!with_head) return SSD_OK;
   if ((rc = add_norm(n_part, m->final_norm))) return rc;
   GemmArgs g = g0;
   g.A = normed; g.W0 = m->head; g.W1 = m->head; g.N = c.vocab; g.K = d;
