@@ -2,7 +2,7 @@
 
     python -m paper_2505_15380_amd.bench_prefill [--workload half_b_k4] [--tokens 4096] [--rows 1024] [--iters 3]
 
-Prefills `--tokens` positions of the workload's target shape in launches of up to `--rows` rows (every operator its
+Prefills `--tokens` positions of the workload's target shape in launches of up to `--rows` rows, 1024 meaning up to 4096 (every operator its
 own launch: more rows than the persistent kernels take) and prints one JSON line: the whole prefill's time, tokens/s,
 the time per operator kind from the library's own event pairs, and the GEMM rate those imply.  This is the command the
 prefill's rocprofv3 summary under profiles/ was taken with; `bench.py` stays the headline benchmark."""
@@ -56,10 +56,11 @@ def measure(args, weights=None):
         t, cnt = ssd.ssd_profile_end()
         per_kind[kind] = {"us_per_launch": round(t / cnt * 1e3, 1), "launches": cnt}
     d, hd, nq, nkv, ffn, L = (shape[k] for k in ("d_model", "head_dim", "n_q_heads", "n_kv_heads", "d_ffn", "n_layers"))
-    gemm_flops = 2 * (n - 1) * L * (d * (nq + 2 * nkv) * hd + nq * hd * d + 3 * d * ffn)
+    # (a prompt is its keys and values: the last layer ends with its QKV projection)
+    gemm_flops = 2 * (n - 1) * (L * d * (nq + 2 * nkv) * hd + (L - 1) * (nq * hd * d + 3 * d * ffn))
     gemm_s = sum(per_kind[k]["us_per_launch"] * per_kind[k]["launches"] for k in ("qkv", "o", "gate_up", "down")) * 1e-6
     return {
-        "workload": args.workload, "tokens": n - 1, "rows_per_launch": args.rows, "forward_path": kv.last_forward_path(),
+        "workload": args.workload, "tokens": n - 1, "rows_per_launch": -(-(n - 1) * L // per_kind["qkv"]["launches"]), "forward_path": kv.last_forward_path(),
         "prefill_ms": round(ms, 2), "tokens_per_s": round((n - 1) / (ms * 1e-3), 1), "per_operator": per_kind,
         "gemm_flops": gemm_flops, "gemm_TFLOPs_between_events": round(gemm_flops / gemm_s / 1e12, 1),
         "gemm_frac_of_bf16_mfma_peak": round(gemm_flops / gemm_s / 2.5e15, 4),

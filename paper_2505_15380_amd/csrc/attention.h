@@ -25,6 +25,7 @@ struct AttnArgs {
   void* out;            // [M][nq*hd] (combine)
   int split_kt;         // > 0: `out` is written as split rows (common.h) with this many k-tiles per row (nq*hd / 32)
   int nparts, part_keys;      // k_attn_mfma, k_attn_f32: grid.x = nparts x (groups of) row tiles; keys per part, a multiple of 64
+  int n_tg;                   // k_attn_mfma: groups of row tiles
   int nchunks;                // k_attn_f32: chunks of the longest sequence
 };
 
@@ -316,8 +317,8 @@ __global__ void __launch_bounds__(WQ * WK * 64, LAZY && HD == 64 ? 4 : WQ * WK /
   constexpr int NB = 8 / WQ;                               // blocks that a wave loads of a chunk: half of a key group's waves keys, half values
   static_assert(WQ == 2 || WQ == 4 || WQ == 8, "");
   extern __shared__ u32x4 kvs[];                           // [key group][keys, values][buffer][block][KS][64]
-  // (the last rows, which reach the most keys, first: a long prompt's launch has more workgroups than fit, and the short ones fill its end)
-  const int part = blockIdx.x % a.nparts, tgroup = (gridDim.x - 1 - blockIdx.x) / a.nparts, kvh = blockIdx.y, brel = blockIdx.z;
+  // (LAZY: the last rows, which reach the most keys, first: a long prompt's launch has more workgroups than fit, and the short ones fill its end)
+  const int part = blockIdx.x % a.nparts, tgroup = LAZY ? a.n_tg - 1 - blockIdx.x / a.nparts : blockIdx.x / a.nparts, kvh = blockIdx.y, brel = blockIdx.z;
   const int seq = a.rows.seq0 + brel;
   const int R = a.rows.R, nkv = a.kv.nkv, G = a.nq / nkv, RG = R * G, m_first = brel * R;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);

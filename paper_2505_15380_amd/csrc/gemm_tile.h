@@ -1,5 +1,5 @@
-// GEMMs of the decoder with bf16 storage where it runs one launch per operator (more than 16 rows, or a head size other than
-// 64), Y[M,N] = X[M,Kd] . W[N,Kd]^T on MFMA 16x16x32 bf16 tiles, on operands that are already in fragment order: weights as packed tiles (gemm.h), activations as split rows (common.h: hi and lo bf16
+// GEMMs of the decoder with bf16 storage where it runs one launch per operator (more than 16 rows, or head size
+// 32), Y[M,N] = X[M,Kd] . W[N,Kd]^T on MFMA 16x16x32 bf16 tiles, on operands that are already in fragment order: weights as packed tiles (gemm.h), activations as split rows (common.h: hi and lo bf16
 // halves, 1 KB per fragment).  The weight fragment is the matrix core's first operand, so that an accumulator register
 // group holds four consecutive output features of one row: lane l has row l % 16, features 4 (l / 16) .. + 3 of a tile.
 #pragma once

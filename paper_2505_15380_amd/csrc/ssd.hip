@@ -949,6 +949,7 @@ static int launch_attn_mfma(AttnArgs a, int nchunks, int plan_chunks, bool promp
   const AttnPick c = pick_attn_mfma(HD, a.rows.R, a.nq / nkv, plan_chunks, prompt, nkv, B, cus);
   a.part_keys = c.part_chunks * 64;
   a.nparts = cdiv(nchunks, c.part_chunks);
+  a.n_tg = c.n_tg;
   int rc;
   if constexpr (HD == 64)
     rc = c.wq == 2 ? launch_attn_mfma_parts<HD, 2, 4, false>(a, c.n_tg, nkv, B, st)
