@@ -995,13 +995,15 @@ static int launch_attn(AttnArgs a, int nchunks, int plan_chunks, bool prompt, in
 
 // Launches whose workgroups wait for each other hold compute units while they do: two of them, half on the device each, would wait until
 // their bounded waits give up.  So such a launch is ordered behind those of other streams that it may not fit beside.  A stream's
-// launches are ordered among themselves; what is kept per stream is the largest of them, until another stream has waited for it.  A program with one
+// launches are ordered among themselves; what is kept per stream is the most that its launches, and those of other streams that they were ordered
+// behind and that may still run, take together; it goes over to a stream that waits for it.  The sum over the streams never exceeds the device.  A program with one
 // stream pays a look at its own entry.  Held until the launch is enqueued, so that no other thread's comes in between.  (A stream that is being
 // captured can neither wait for another one nor be waited for: its graphs are the caller's to order.)
 struct ResidentStream { int device; hipStream_t st; int wgs; };
 static std::mutex g_resident_mutex;
-static std::vector<ResidentStream> g_resident;
-constexpr size_t MAX_RESIDENT_STREAMS = 32;
+constexpr int MAX_RESIDENT_STREAMS = 32;
+static ResidentStream g_resident[MAX_RESIDENT_STREAMS];
+static int g_residents = 0;
 
 static bool being_captured(hipStream_t st) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -1015,28 +1017,32 @@ struct ResidentLaunch {
   ResidentLaunch(hipStream_t st, int wgs, int cus) : lock(g_resident_mutex) {
     int device = -1;
     if (hipGetDevice(&device) != hipSuccess || being_captured(st)) return;
-    int others = 0;
+    int others = 0, ahead = 0;                             // workgroups on other streams; with this stream's, where it waits for them: they may all still run
     ResidentStream* own = nullptr;
-    for (auto& r : g_resident) {
+    for (int i = 0; i < g_residents; ++i) {
+      ResidentStream& r = g_resident[i];
       if (r.st == st && r.device == device) own = &r;
       else if (r.device == device) others += r.wgs;
     }
-    if (own && own->wgs >= wgs && others + wgs <= cus) return;
-    if (others + wgs > cus || g_resident.size() >= MAX_RESIDENT_STREAMS) {
-      for (size_t i = 0; i < g_resident.size();) {
+    if (own && own->wgs >= wgs) return;                    // (it fits: the sum does)
+    if (others + wgs > cus || (!own && g_residents >= MAX_RESIDENT_STREAMS)) {
+      ahead = others + (own ? own->wgs : 0);
+      int kept = 0;
+      for (int i = 0; i < g_residents; ++i) {
         const ResidentStream r = g_resident[i];
-        if (r.device != device || r.st == st) { ++i; continue; }
+        if (r.device != device || r.st == st) { g_resident[kept++] = r; continue; }
         hipEvent_t ev;
         if (!being_captured(r.st) && hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) {
           if (hipEventRecord(ev, r.st) != hipSuccess || hipStreamWaitEvent(st, ev, 0) != hipSuccess) (void)hipGetLastError();      // (a stream that is gone has nothing to wait for)
           (void)hipEventDestroy(ev);
         }
-        g_resident.erase(g_resident.begin() + i);
       }
+      g_residents = kept;
     }
-    for (auto& r : g_resident)
-      if (r.st == st && r.device == device) { r.wgs = std::max(r.wgs, wgs); return; }
-    if (g_resident.size() < MAX_RESIDENT_STREAMS) g_resident.push_back({device, st, wgs});
+    wgs = std::max(wgs, ahead);
+    for (int i = 0; i < g_residents; ++i)
+      if (g_resident[i].st == st && g_resident[i].device == device) { g_resident[i].wgs = std::max(g_resident[i].wgs, wgs); return; }
+    if (g_residents < MAX_RESIDENT_STREAMS) g_resident[g_residents++] = {device, st, wgs};
   }
 };
 
