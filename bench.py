@@ -221,7 +221,7 @@ def main():
                         "flops": r["gemm_flops"] + r["attention_flops"], "frac_mfma_bf16_peak": r["frac_of_bf16_mfma_peak"],
                         "per_operator_us": {k: v["us_per_verify"] for k, v in r["per_operator"].items()}}
             torch.cuda.empty_cache()
-        # ---- and the prompt prefill that precedes the cycles: 4096 tokens, 1024 rows per launch ------------------
+        # ---- and the prompt prefill that precedes the cycles: 4096 tokens, one launch per operator and layer ------------------
         from paper_2505_15380_amd import bench_prefill
         r = bench_prefill.measure(argparse.Namespace(workload="half_b_k4", tokens=4096, rows=1024, iters=3), weights=tw)
         rec["prefill"] = {k: r[k] for k in ("tokens", "rows_per_launch", "prefill_ms", "tokens_per_s", "forward_path",
