@@ -453,7 +453,7 @@ __device__ __forceinline__ void sf_gate_up(const SArgs& a, uint32_t* set, const 
     const int g16 = min(2 * item + half, (a.ffn >> 4) - 1);
     sf_weights(Y.wgate, Y.wup, a.ffn, a.d, g16, g16, kb, ke, lane, wg);
     sf_gain(Y.ln2, kb, ke, lane, gn);
-    // the residual rows (long there: the attention that this waits for depends on all of them)
+    // the residual rows (long there once a word of attention is: it depends on the whole row)
     uint32_t ra[2], rb[2];
     auto residual = [&](int rd, uint32_t (&r)[2]) {
       const int n0 = 32 * min(2 * rd + half_t, pairs - 1) + col;
@@ -465,7 +465,14 @@ __device__ __forceinline__ void sf_gate_up(const SArgs& a, uint32_t* set, const 
     if (!res) { residual(0, ra); residual(1, rb); }
     const uint32_t* first_res = res && m < M ? res + 32 * min(half_t, pairs - 1) + col : nullptr;
     if (!sf_poll(lw.attn, m_lane, nqd, kbo, keo, lane, A, first_res, first_res ? first_res + 16 : nullptr, h0, h1, err)) s.dead = 1;
-    if (res) { ra[0] = __float_as_uint(h0); ra[1] = __float_as_uint(h1); residual(1, rb); }
+    if (res) {
+      ra[0] = __float_as_uint(h0); ra[1] = __float_as_uint(h1);
+      residual(1, rb);
+      // (a wave without a step of the output projection, one query head, has seen no attention: it awaits these words themselves)
+      if (kbo == keo)
+        for (long spins = 0; min(rb[0], rb[1]) == 0u; residual(1, rb))
+          if (sf_give_up(spins, err)) { s.dead = 1; break; }
+    }
     auto round = [&](int rd, const SfWeights& w, const uint32_t (&r)[2]) {
       const int p = 2 * rd + half_t, n0 = 32 * p + col;
       float ss;
