@@ -433,6 +433,7 @@ __device__ __forceinline__ void sf_gate_up(const SArgs& a, uint32_t* set, const 
   int nw, kb, ke, kbo, keo;
   sf_steps(nqd, wave & 3, nw, kbo, keo);                   // (nw = 4 for both)
   sf_steps(a.d, wave & 3, nw, kb, ke);
+  const int kbp = kbo < keo ? kbo : 0, kep = kbo < keo ? keo : 1;      // a wave without a step awaits attention all the same: it reads what that depends on
   const int m_lane = min(m0 + li, M - 1);
   const float* er = a.embed + (size_t)mine.token(a) * a.d;
   const f32x4 none[4] = {};
@@ -464,15 +465,8 @@ __device__ __forceinline__ void sf_gate_up(const SArgs& a, uint32_t* set, const 
     };
     if (!res) { residual(0, ra); residual(1, rb); }
     const uint32_t* first_res = res && m < M ? res + 32 * min(half_t, pairs - 1) + col : nullptr;
-    if (!sf_poll(lw.attn, m_lane, nqd, kbo, keo, lane, A, first_res, first_res ? first_res + 16 : nullptr, h0, h1, err)) s.dead = 1;
-    if (res) {
-      ra[0] = __float_as_uint(h0); ra[1] = __float_as_uint(h1);
-      residual(1, rb);
-      // (a wave without a step of the output projection, one query head, has seen no attention: it awaits these words themselves)
-      if (kbo == keo)
-        for (long spins = 0; min(rb[0], rb[1]) == 0u; residual(1, rb))
-          if (sf_give_up(spins, err)) { s.dead = 1; break; }
-    }
+    if (!sf_poll(lw.attn, m_lane, nqd, kbp, kep, lane, A, first_res, first_res ? first_res + 16 : nullptr, h0, h1, err)) s.dead = 1;
+    if (res) { ra[0] = __float_as_uint(h0); ra[1] = __float_as_uint(h1); residual(1, rb); }
     auto round = [&](int rd, const SfWeights& w, const uint32_t (&r)[2]) {
       const int p = 2 * rd + half_t, n0 = 32 * p + col;
       float ss;
