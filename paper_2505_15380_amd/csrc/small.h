@@ -38,7 +38,7 @@ struct SArgs {
   uint32_t* tw;                 // two sets of words
   size_t st_set;                // words of a set: per layer [cap][attention | h after attention | SwiGLU | h after the MLP]
   int cap;                      // rows that the workspace has room for
-  u64* state;
+  u64* state;                   // the last launch that has gone through its layers: its number, then (rows of the one before it << 16 | rows << 1 | set)
   u64* rowblk;                  // [SF_MAX_ROWS]
   float* logits;
   uint32_t* bar;
@@ -594,7 +594,9 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_f32(SArgs a) {
   }
   const uint32_t last_tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)state_v), last = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(state_v >> 32));
   const uint32_t which = last_tag == tag ? last & 1u : ~last & 1u;
-  const int old_rows = last_tag == tag ? 0 : (int)(last >> 1);
+  // (The state may already be this launch's: with several row tiles its last layer does not depend on the workgroups of the others, and one that begins
+  // only now still has its share of the launch before to zero.)
+  const int old_rows = (int)(last_tag == tag ? last >> 16 : (last & 0xFFFFu) >> 1);
   uint32_t* set = a.tw + which * a.st_set;
   __syncthreads();
   if (att) {
@@ -617,8 +619,7 @@ __global__ void __launch_bounds__(PBLOCK) k_forward_f32(SArgs a) {
   } else {
     const int i = wg - a.first_down, item = sf_div(i, a.recip_T);
     sf_down(a, set, item, (i - item * T) * 16, s);
-    // (every workgroup has long begun: the last layer depends on all of them)
-    if (wg == a.first_down && tid == 0) __hip_atomic_store(a.state, (u64)tag | (u64)((uint32_t)M << 1 | which) << 32, __ATOMIC_RELAXED, AG);
+    if (wg == a.first_down && tid == 0) __hip_atomic_store(a.state, (u64)tag | (u64)((uint32_t)old_rows << 16 | (uint32_t)M << 1 | which) << 32, __ATOMIC_RELAXED, AG);
   }
 }
 

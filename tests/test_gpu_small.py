@@ -77,3 +77,29 @@ def test_one_launch_has_the_bits_of_the_launches_per_operator(name, lens, K, pca
     assert a[1][-1] == path and set(b[1]) == {1}
     assert all(torch.equal(x, y) for x, y in zip(a[0], b[0]))
     assert a[2:] == b[2:]
+
+
+def test_launches_of_changing_rows_leave_no_words_behind(monkeypatch):
+    """Launches of one to four row tiles in turn, over a workspace of two sets of words: each zeroes what the one before left, also with fewer
+    row tiles than that had.  Bits of the launches per operator after each."""
+    import paper_2505_15380_amd as ssd
+    shape = si.model_shape("tiny")
+    w = ssd.upload_weights(shape, si.make_weights(shape, 150))
+    V, got = shape["vocab"], []
+    for mode in ("", "barrier"):
+        if mode:
+            monkeypatch.setenv("SSD_FORWARD", mode)
+        model = ssd.Model(shape, w, 400)
+        kv = ssd.KVCache(model, 4, 64, 4 * 25, 16)
+        for b in range(4):
+            toks = np.random.default_rng(1000 + b).integers(0, V, 30 + 9 * b).astype(np.int32)
+            ssd.ssd_prefill(model, kv, b, torch.from_numpy(toks).cuda())
+        rng, outs = np.random.default_rng(3), []
+        for s, (B, K) in enumerate([(4, 15), (1, 0), (4, 11), (2, 15), (3, 4), (4, 15), (4, 15), (1, 7), (1, 7), (4, 12)]):
+            x = torch.from_numpy(rng.integers(0, V, (B, K)).astype(np.int32)).cuda() if K else None
+            pd = torch.full((B, K, V), 1.0 / V, device="cuda") if K else None
+            o = ssd.ssd_verify(model, kv, B, x, pd, K, ssd.sample_config(beta=0.3, seed=3), s, want_logits=True)
+            assert kv.last_forward_path() == (1 if mode else 5)
+            outs += [o["logits"].clone(), o["next_token"].clone(), kv.pool.clone()]
+        got.append(outs)
+    assert all(torch.equal(a, b) for a, b in zip(*got))
