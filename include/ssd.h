@@ -262,7 +262,7 @@ int ssd_profile_end(double* total_ms, int* launches);
  * head_dim 128 or fp32; 2, or 1, is also what runs when a launch exceeds the limits of 3), 4 the same kernel where no part of a prefix can meet another one's: at most 1520 cached positions, by the
  * host's bound of the lengths, on a cache created with pending_cap 2 (SSD_ATTN_WHOLE=1: on every cache, 0: on none).  The
  * kernel is the same and so are the results: a row attends in one part up to 1536 positions and in parts of 1024 beyond; 5 the same
- * idea for fp32 storage, with the bits of 1: head_dim 32, d_model and n_q_heads*32 up to 256, d_ffn up to 512, at most 64 rows of 16 sequences (16 rows
+ * idea for fp32 storage, with the bits of 1: head_dim 32, d_model and n_q_heads*32 up to 256 (of wide models with many heads to a kv head only those for which it is the faster one), d_ffn up to 512, at most 64 rows of 16 sequences (16 rows
  * each) that hold up to 1024 positions. */
 int ssd_kv_last_forward_path(const ssd_kv* kv);
 

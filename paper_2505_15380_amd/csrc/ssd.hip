@@ -336,9 +336,15 @@ struct ssd_kv {
 };
 
 // Shapes whose fp32 forward of a few rows is one launch (small.h).  (With head size 64 two chunks of keys and values do not fit the registers.)
+// A workgroup of a kv head computes the projections of its G query heads, its key and its value two at a time, and every workgroup of gate / up the whole
+// output projection, where the launches per operator have a workgroup for each: with wide rows and many heads the chain of those is the shorter one.  The line is a fit to
+// 4 widths x 13 groupings x 2 ffn sizes x 3 launches (1 to 64 rows), time per operator over time in one launch: width 256, 8 heads over 8 / 4 / 2 / 1 kv heads
+// 1.01 / 1.02 / 0.93 / 0.80, 6 over 2 1.00, 6 over 1 0.91, 4 over 1 1.03; width 192, 8 over 2 / 1 1.08 / 0.94, 6 over 1 1.02; width 128, 8 over 1 1.12; the
+// two configurations 1.35 and 1.6.
 static bool small_shape(const ssd_model_config& c) {
+  const int group = c.n_q_heads / c.n_kv_heads;
   return c.dtype == SSD_DTYPE_FP32 && c.head_dim == SF_HD && c.d_model <= SF_MAX_D && c.n_q_heads * SF_HD <= SF_MAX_D && c.d_ffn <= SF_MAX_FFN &&
-         c.n_q_heads / c.n_kv_heads <= SF_MAX_GROUP;
+         group <= SF_MAX_GROUP && c.d_model * (c.n_q_heads + 3 * (cdiv(group + 2, 2) - 2)) <= 9 * 256;
 }
 
 // Rows of the per-operator buffers.  A cache for one sequence's prompts in the largest launches (max_seqs 1, max_rows 1024) takes launches of up to

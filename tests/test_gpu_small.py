@@ -21,7 +21,10 @@ SHAPES = {
     "narrowest": dict(n_layers=1, d_model=32, n_q_heads=1, n_kv_heads=1, d_ffn=32, vocab=17, n_embed=17),              # waves without a step
     "one_head": dict(n_layers=3, d_model=224, n_q_heads=1, n_kv_heads=1, d_ffn=96, vocab=65, n_embed=65),                # waves without a step, four rounds of residual columns
     "grouped": dict(n_layers=3, d_model=192, n_q_heads=6, n_kv_heads=2, d_ffn=320, vocab=777, n_embed=800, qkv_bias=1),  # five waves for the down projection
-    "widest": dict(n_layers=2, d_model=256, n_q_heads=8, n_kv_heads=1, d_ffn=512, vocab=513, n_embed=513, qkv_bias=1),   # ten heads to a workgroup
+    "widest": dict(n_layers=2, d_model=256, n_q_heads=8, n_kv_heads=8, d_ffn=512, vocab=513, n_embed=513, qkv_bias=1),
+    "ten_heads": dict(n_layers=2, d_model=128, n_q_heads=8, n_kv_heads=1, d_ffn=512, vocab=513, n_embed=513, qkv_bias=1),  # to a workgroup of attention
+    "group_of_3": dict(n_layers=2, d_model=256, n_q_heads=6, n_kv_heads=2, d_ffn=512, vocab=513, n_embed=513, qkv_bias=1),
+    "group_of_4": dict(n_layers=2, d_model=256, n_q_heads=8, n_kv_heads=2, d_ffn=512, vocab=513, n_embed=513, qkv_bias=1),  # faster per operator
 }
 
 
@@ -60,7 +63,8 @@ def _run(shape, w, lens, K, pcap, steps):
     ("tiny", [20] * 17, 0, 1, 1),            # 17 sequences
     ("one_head", [40], 15, 1, 5), ("one_head", [33, 5, 70], 10, 1, 5), ("one_head", [21], 8, 1, 5),
     ("narrowest", [1], 2, 1, 5), ("narrowest", [90, 14], 0, 2, 5), ("grouped", [31], 4, 1, 5), ("grouped", [100, 5, 300], 5, 1, 5),
-    ("grouped", [17, 15, 16], 0, 2, 5), ("widest", [129], 8, 1, 5), ("widest", [12] * 3, 15, 1, 5)])
+    ("grouped", [17, 15, 16], 0, 2, 5), ("widest", [129], 8, 1, 5), ("widest", [12] * 3, 15, 1, 5),
+    ("ten_heads", [129], 8, 1, 5), ("ten_heads", [12] * 3, 15, 1, 5), ("group_of_3", [12] * 3, 15, 1, 5), ("group_of_4", [40], 4, 1, 1)])
 def test_one_launch_has_the_bits_of_the_launches_per_operator(name, lens, K, pcap, path, monkeypatch):
     """Logits, draws, the cache's pool, lengths, tables and free blocks after four steps; `path`: of the last of them."""
     import paper_2505_15380_amd as ssd
