@@ -1112,14 +1112,19 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   const int o_stride = wide && g_mlp + n_att + cdiv(n_qkv, 2) + npairs <= kv->cus ? 2 : small_stride;
   // (No more workgroups than items: those of a launch wait for each other, and a smaller model's launch on another stream may be in what is left.)
   const int G = std::min(kv->cus, g_mlp + n_att + (wide ? cdiv(small_stride * n_qkv, 2) + cdiv(o_stride * npairs, 2) : cdiv(small_stride * n_other, 2)));
+  // Wide, more than 12 rows of several sequences: the launches per operator where items of the small phases share workgroups with the MLP's, which with two k-tiles each
+  // have no room for the second one's weights while they wait, and the prefixes are not long enough to make up for it (beyond 3072 positions the launches per
+  // operator have that many more parts to merge).  With more than six tiles of attention, also of one sequence, they run whatever the prefix.  28 layers of width 1536, us in one launch and per
+  // operator: 2 sequences of 8 rows behind 1200 / 2060 / 2600 / 3100 / 4096 positions 1235 / 1510 / 1534 / 1546 / 1603 and 1409 / 1460 / 1485 / 1520 / 1583; 3 of 5
+  // 1234 / 1505 / 1521 / 1507 / 1536 and 1390 / 1441 / 1470 / 1529 / 1615; 5 of 3 behind 4096 1665 and 1538.  (12 rows: 2 of 6 1173 / 1420 / 1448 / 1440 / 1447 and
+  // 1390 / 1437 / 1464 / 1497 / 1553, 4 of 3 1478 and 1710 behind 4096.)
+  const bool shared = g_mlp + n_att + cdiv(n_other, 2) > kv->cus;
+  const bool wide_batch = B * cdiv(rows.R * grp, 16) <= 6 && !(B > 1 && shared && kv->mlp_tiles == 2 && n_parts <= 3);
   // limits: one round of attention (its workgroups wait for each other's parts), query rows of an item, LDS staging capacity
   const bool fits = M <= 16 && rows.R * grp <= DF_ATT_ROWS && n_att <= G && n_parts <= kv->t_NP &&
                     M * (std::max(c.d_model, nqd) + 4) <= (wide ? DfWide::AW : DfNarrow::AW) && M * (c.d_model / 32) <= DF_SQ_WORDS &&
                     c.n_layers <= 128 && 2 + 10 * c.n_layers + 2 <= 512 &&
-                    // (wide, more than 12 rows of several sequences: their items of attention share workgroups with the MLP's at long
-                    // prefixes; 28 layers of width 1536, 4096 positions, 5 sequences of 3 rows 1665 us, one launch per operator 1538;
-                    // 4 of 3 rows 1511 against 1609)
-                    (!wide || M <= 12 || B * cdiv(rows.R * grp, 16) <= 6);
+                    (!wide || M <= 12 || wide_batch);
   if (!fits) return -1;
   DArgs a;
   memset(&a, 0, sizeof a);

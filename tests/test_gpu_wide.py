@@ -116,3 +116,14 @@ def test_launches_that_do_not_fit_the_device_together_are_ordered(other):
         torch.cuda.synchronize()
         got.append(outs)
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("lens,K,path", [([2040, 2060], 7, 1), ([1500, 700], 7, 3), ([3090, 20], 7, 3), ([2060], 15, 3), ([2060, 2060, 30], 4, 1),
+                                         ([2060, 2060], 5, 3), ([30] * 5, 2, 1)])
+def test_which_batches_of_wide_rows_are_one_launch(lens, K, path):
+    """More than 12 rows of several sequences whose phases share workgroups, up to 3072 positions, and more than six tiles: one launch per operator."""
+    from tests.test_gpu_row_bits import _target, _verify_logits
+    shape = _shape("one_layer")
+    model, kv = _target(shape, lens, 128)
+    x = torch.from_numpy(np.random.default_rng(7).integers(0, shape["vocab"], (len(lens), K)).astype(np.int32)).cuda()
+    assert _verify_logits(model, kv, len(lens), x)[1] == path
