@@ -22,6 +22,7 @@
 #include "gemm.h"
 #include "gemm_tile.h"
 #include "persistent.h"
+#include "resident.h"
 #include "dataflow.h"
 #include "small.h"
 #include "sample.h"
@@ -999,17 +1000,11 @@ static int launch_attn(AttnArgs a, int nchunks, int plan_chunks, bool prompt, in
   return SSD_OK;
 }
 
-// Launches whose workgroups wait for each other hold compute units while they do: two of them, half on the device each, would wait until
-// their bounded waits give up.  So such a launch is ordered behind those of other streams that it may not fit beside.  A stream's
-// launches are ordered among themselves; what is kept per stream is the most that its launches, and those of other streams that they were ordered
-// behind and that may still run, take together; it goes over to a stream that waits for it.  The sum over the streams never exceeds the device.  A program with one
-// stream pays a look at its own entry.  Held until the launch is enqueued, so that no other thread's comes in between.  (A stream that is being
-// captured can neither wait for another one nor be waited for: its graphs are the caller's to order.)
-struct ResidentStream { int device; hipStream_t st; int wgs; };
+// Launches whose workgroups wait for each other, of all streams (resident.h).  A program with one stream pays a look at its own entry.  Held until the launch is
+// enqueued, so that no other thread's comes in between.  (A stream that is being captured can neither wait for another one nor be waited for: its graphs are
+// the caller's to order.)
 static std::mutex g_resident_mutex;
-constexpr int MAX_RESIDENT_STREAMS = 32;
-static ResidentStream g_resident[MAX_RESIDENT_STREAMS];
-static int g_residents = 0;
+static ResidentTable g_resident;
 
 static bool being_captured(hipStream_t st) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -1023,32 +1018,13 @@ struct ResidentLaunch {
   ResidentLaunch(hipStream_t st, int wgs, int cus) : lock(g_resident_mutex) {
     int device = -1;
     if (hipGetDevice(&device) != hipSuccess || being_captured(st)) return;
-    int others = 0, ahead = 0;                             // workgroups on other streams; with this stream's, where it waits for them: they may all still run
-    ResidentStream* own = nullptr;
-    for (int i = 0; i < g_residents; ++i) {
-      ResidentStream& r = g_resident[i];
-      if (r.st == st && r.device == device) own = &r;
-      else if (r.device == device) others += r.wgs;
-    }
-    if (own && own->wgs >= wgs) return;                    // (it fits: the sum does)
-    if (others + wgs > cus || (!own && g_residents >= MAX_RESIDENT_STREAMS)) {
-      ahead = others + (own ? own->wgs : 0);
-      int kept = 0;
-      for (int i = 0; i < g_residents; ++i) {
-        const ResidentStream r = g_resident[i];
-        if (r.device != device || r.st == st) { g_resident[kept++] = r; continue; }
-        hipEvent_t ev;
-        if (!being_captured(r.st) && hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) {
-          if (hipEventRecord(ev, r.st) != hipSuccess || hipStreamWaitEvent(st, ev, 0) != hipSuccess) (void)hipGetLastError();      // (a stream that is gone has nothing to wait for)
-          (void)hipEventDestroy(ev);
-        }
-      }
-      g_residents = kept;
-    }
-    wgs = std::max(wgs, ahead);
-    for (int i = 0; i < g_residents; ++i)
-      if (g_resident[i].st == st && g_resident[i].device == device) { g_resident[i].wgs = std::max(g_resident[i].wgs, wgs); return; }
-    if (g_residents < MAX_RESIDENT_STREAMS) g_resident[g_residents++] = {device, st, wgs};
+    g_resident.admit(device, st, wgs, cus, [&](const ResidentTable::Entry& x) {
+      const hipStream_t other = (hipStream_t)x.stream;
+      hipEvent_t ev;
+      if (being_captured(other) || hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return;
+      if (hipEventRecord(ev, other) != hipSuccess || hipStreamWaitEvent(st, ev, 0) != hipSuccess) (void)hipGetLastError();      // (a stream that is gone has nothing to wait for)
+      (void)hipEventDestroy(ev);
+    });
   }
 };
 
@@ -1954,5 +1930,17 @@ extern "C" int ssd_attention_plan(int head_dim, int n_q_heads, int n_kv_heads, i
   const AttnPick c = pick_attn_mfma(head_dim, rows, n_q_heads / n_kv_heads, prompt_positions ? cdiv(prompt_positions, ATT_CHUNK) : ATT_PLAN_CHUNKS,
                                     prompt_positions > 0, n_kv_heads, n_seqs, cus);
   plan[0] = c.wq; plan[1] = c.wk; plan[2] = c.part_chunks;
+  return SSD_OK;
+}
+
+extern "C" int ssd_resident_order(const int* launches, int n, int cus, int* behind) {
+  if (!launches || !behind || n < 0 || cus < 1) return fail(SSD_EINVAL, "bad launches");
+  ResidentTable t;
+  for (int i = 0; i < n; ++i) {
+    const int stream = launches[2 * i], wgs = launches[2 * i + 1];
+    if (stream < 0 || wgs < 1 || wgs > cus) return fail(SSD_EINVAL, "bad launch %d", i);
+    behind[i] = 0;
+    t.admit(0, (const void*)(size_t)(stream + 16), wgs, cus, [&](const ResidentTable::Entry&) { ++behind[i]; });
+  }
   return SSD_OK;
 }
