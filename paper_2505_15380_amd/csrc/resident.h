@@ -13,13 +13,16 @@ namespace ssd {
 
 struct ResidentTable {
   static constexpr int CAP = 32, XCDS = 8;
-  struct Entry { int device; const void* stream; int share; };
+  // stream: its handle, or an odd number for a thread's own one (hipStreamPerThread, which names another stream in each thread).  done: event behind the last
+  // launch of a stream that other threads cannot name.
+  struct Entry { int device; const void* stream; int share; void* done; };
   Entry e[CAP];
   int n = 0;
 
-  // A launch of `wgs` workgroups on `stream`; wait_for(entry) orders it behind what that entry's stream has been given.
+  // A launch of `wgs` workgroups on `stream`; wait_for(entry) orders it behind what that entry's stream has been given.  Returns the stream's entry, until the
+  // next call (null: the table is full of other devices' streams).
   template <typename WAIT>
-  void admit(int device, const void* stream, int wgs, int cus, WAIT wait_for) {
+  Entry* admit(int device, const void* stream, int wgs, int cus, WAIT wait_for) {
     int share = (wgs + XCDS - 1) / XCDS, others = 0;
     const int room = (cus + XCDS - 1) / XCDS;
     Entry* own = nullptr;
@@ -28,7 +31,7 @@ struct ResidentTable {
       if (e[i].stream == stream) own = &e[i];
       else others += e[i].share;
     }
-    if (own && own->share >= share) return;                // (it fits: the sum does)
+    if (own && own->share >= share) return own;                // (it fits: the sum does)
     if (others + share > room || (!own && n >= CAP)) {
       share = std::max(share, others + (own ? own->share : 0));      // (they may all still run)
       int kept = 0;
@@ -40,8 +43,10 @@ struct ResidentTable {
       n = kept;
     }
     for (int i = 0; i < n; ++i)
-      if (e[i].stream == stream && e[i].device == device) { e[i].share = std::max(e[i].share, share); return; }
-    if (n < CAP) e[n++] = {device, stream, share};
+      if (e[i].stream == stream && e[i].device == device) { e[i].share = std::max(e[i].share, share); return &e[i]; }
+    if (n >= CAP) return nullptr;
+    e[n] = {device, stream, share, nullptr};
+    return &e[n++];
   }
 };
 

@@ -1013,18 +1013,36 @@ static bool being_captured(hipStream_t st) {
   return true;
 }
 
+// What a stream is in the table: hipStreamPerThread is another stream in each thread (and a thread that has ended is none), hipStreamLegacy the default one.
+static const void* resident_key(hipStream_t st) {
+  static std::atomic<size_t> threads{0};
+  thread_local const size_t thread = threads++;
+  return st == hipStreamPerThread ? (const void*)(2 * thread + 1) : st == hipStreamLegacy ? nullptr : (const void*)st;
+}
+
 struct ResidentLaunch {
   std::unique_lock<std::mutex> lock;
-  ResidentLaunch(hipStream_t st, int wgs, int cus) : lock(g_resident_mutex) {
+  hipStream_t st;
+  hipEvent_t done = nullptr;
+  ResidentLaunch(hipStream_t stream, int wgs, int cus) : lock(g_resident_mutex), st(stream) {
     int device = -1;
     if (hipGetDevice(&device) != hipSuccess || being_captured(st)) return;
-    g_resident.admit(device, st, wgs, cus, [&](const ResidentTable::Entry& x) {
-      const hipStream_t other = (hipStream_t)x.stream;
-      hipEvent_t ev;
-      if (being_captured(other) || hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return;
-      if (hipEventRecord(ev, other) != hipSuccess || hipStreamWaitEvent(st, ev, 0) != hipSuccess) (void)hipGetLastError();      // (a stream that is gone has nothing to wait for)
+    ResidentTable::Entry* own = g_resident.admit(device, resident_key(st), wgs, cus, [&](const ResidentTable::Entry& x) {
+      hipEvent_t ev = (hipEvent_t)x.done;
+      if (!ev) {
+        const hipStream_t other = (hipStream_t)x.stream;
+        if (being_captured(other) || hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return;
+        if (hipEventRecord(ev, other) != hipSuccess) (void)hipGetLastError();      // (a stream that is gone has nothing to wait for)
+      }
+      if (hipStreamWaitEvent(st, ev, 0) != hipSuccess) (void)hipGetLastError();
       (void)hipEventDestroy(ev);
     });
+    if (st != hipStreamPerThread || !own) return;
+    if (!own->done && hipEventCreateWithFlags(&done, hipEventDisableTiming) == hipSuccess) own->done = done;
+    done = (hipEvent_t)own->done;
+  }
+  ~ResidentLaunch() {
+    if (done && hipEventRecord(done, st) != hipSuccess) (void)hipGetLastError();
   }
 };
 

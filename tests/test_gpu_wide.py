@@ -118,6 +118,53 @@ def test_launches_that_do_not_fit_the_device_together_are_ordered(other):
     assert all(torch.equal(a, b) for a, b in zip(*got))
 
 
+def test_launches_of_threads_on_their_own_streams_are_ordered(monkeypatch):
+    """hipStreamPerThread is one handle for a stream of each thread: two threads that issue launches of 204 and 218 workgroups on it at once.
+    The same steps as one after the other."""
+    import threading
+    import paper_2505_15380_amd as ssd
+    from paper_2505_15380_amd import binding
+    from tests.test_gpu_row_bits import _target
+    K, runs = 4, []
+    for shape in (_shape("one_layer"), dict(si.model_shape("half_b_draft"), vocab=300, n_embed=300)):
+        model, kv = _target(shape, [70], 64, extra=400)
+        x = torch.from_numpy(np.random.default_rng(7).integers(0, shape["vocab"], (1, K)).astype(np.int32)).cuda()
+        pd = torch.full((1, K, shape["vocab"]), 1.0 / shape["vocab"], device="cuda")
+        outs = [dict(n_accepted=torch.zeros(1, dtype=torch.int32, device="cuda"), next_token=torch.zeros(1, dtype=torch.int32, device="cuda"), probs=None,
+                     logits=torch.zeros(1, K + 1, shape["vocab"], device="cuda")) for _ in range(40)]
+        runs.append((model, kv, x, pd, outs, kv.state(0)["pending"][0]))
+    cfg, got, errors = ssd.sample_config(beta=0.3, seed=3), [], []
+
+    def steps(run):
+        try:
+            model, kv, x, pd, outs, pending = run
+            for s in range(40):
+                if s % 20 == 0:
+                    ssd.ssd_kv_rollback(kv, 0, 70, pending)
+                ssd.ssd_verify(model, kv, 1, x, pd, K, cfg, s, out=outs[s])
+        except Exception as e:                               # (raised again in the test's own thread)
+            errors.append(e)
+
+    for beside in (False, True):
+        torch.cuda.synchronize()
+        if beside:
+            monkeypatch.setattr(binding, "_stream", lambda: 2)
+            threads = [threading.Thread(target=steps, args=(r,)) for r in runs]
+            for t in threads:
+                t.start()
+            for t in threads:
+                t.join()
+            monkeypatch.undo()
+        else:
+            for r in runs:
+                steps(r)
+        torch.cuda.synchronize()
+        assert not errors, errors
+        assert all(r[1].last_forward_path() in (3, 4) for r in runs)
+        got.append([o["logits"].clone() for r in runs for o in r[4]])
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 @pytest.mark.parametrize("lens,K,path", [([2040, 2060], 7, 1), ([1500, 700], 7, 3), ([3090, 20], 7, 3), ([2060], 15, 3), ([2060, 2060, 30], 4, 1),
                                          ([2060, 2060], 5, 3), ([30] * 5, 2, 1)])
 def test_which_batches_of_wide_rows_are_one_launch(lens, K, path):
