@@ -21,9 +21,10 @@
  *     one stream (or be externally ordered).
  *     Forwards of few rows (ssd_kv_last_forward_path 2 to 5) are one launch whose workgroups, one to a
  *     compute unit, wait for each other.  Two such launches of different handles on two streams of a process overlap if every XCD of the
- *     device has the compute units for its eighth of both (32 of 256; a model of width 896 takes 28 to 32 of them, 19 with path 2, one of width 128 in fp32 2 to 13), else the
- *     later one is ordered behind the other stream (ssd_resident_order).  Graphs that a caller captures around these calls, and other processes on the same device, are not seen: there
- *     each launch may hold units that the other one waits for until their bounded waits give up, which both report as SSD_EHIP; order them.
+ *     device has the compute units for its eighth of both (32 of 256; a model of width 896 takes 28 to 32 of them, 19 with path 2, one of width 128 in fp32 2 to 13), else the later
+ *     call waits on the host until those that it does not fit beside are over (ssd_resident_fits).  After a second of that, with whatever else their streams have before them, it runs
+ *     as one launch per operator (path 1), a captured cycle call by call.  Graphs that a caller captures around these calls, and other processes on the same device, are not
+ *     seen: there each launch may hold units that the other one waits for until their bounded waits give up, which both report as SSD_EHIP; order them.
  *   - Return value: SSD_OK (0) or a negative error code; ssd_last_error() gives a message for the last
  *     failure on the calling thread.  Arguments are validated on the host before anything is launched;
  *     nothing throws or aborts across this boundary.
@@ -288,9 +289,9 @@ int ssd_gemm_blocks(int kind, int rows, int n, int k, int cus, int* blocks, int 
 /* Both for a prompt's launches, which have up to 4096 rows where ssd_kv_create says so (kind 0, 2, 3, 4): plan, and the blocks of up to `cap`
  * workgroups; returns their number.  A down projection that adds the residual itself has 0 k-slices. */
 int ssd_prompt_gemm_plan(int kind, int rows, int n, int k, int cus, int plan[4], int* blocks, int cap);
-/* n launches whose workgroups wait for each other, {stream (any number), workgroups} each, on a device of `cus` compute units: behind[i] = number of other
- * streams that launch i is ordered behind, 0 where it may run beside whatever they still run. */
-int ssd_resident_order(const int* launches, int n, int cus, int* behind);
+/* May a launch of `wgs` workgroups that wait for each other on `stream` (any number) run beside n such launches, {stream, workgroups} each, on a device of `cus` compute
+ * units?  1 or 0. */
+int ssd_resident_fits(const int* running, int n, int stream, int wgs, int cus);
 int ssd_attention_plan(int head_dim, int n_q_heads, int n_kv_heads, int n_seqs, int rows, int prompt_positions, int cus, int plan[3]);
 
 const char* ssd_strerror(int code);

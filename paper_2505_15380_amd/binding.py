@@ -12,7 +12,7 @@ EXPORTED_SYMBOLS = [
     "ssd_kv_rollback", "ssd_kv_follow", "ssd_verify_from_probs", "ssd_warp_probs", "ssd_kv_state",
     "ssd_kv_free_stack", "ssd_profile_begin", "ssd_profile_end", "ssd_kv_last_forward_path", "ssd_trace_barriers", "ssd_strerror", "ssd_last_error",
     "ssd_verify_noalloc", "ssd_kv_clear_error", "ssd_kv_test_hook", "ssd_cycle_create", "ssd_cycle_launch", "ssd_cycle_captures", "ssd_cycle_destroy",
-    "ssd_gemm_plan", "ssd_gemm_blocks", "ssd_prompt_gemm_plan", "ssd_attention_plan", "ssd_resident_order",
+    "ssd_gemm_plan", "ssd_gemm_blocks", "ssd_prompt_gemm_plan", "ssd_attention_plan", "ssd_resident_fits",
 ]
 
 
@@ -89,7 +89,7 @@ def load_library():
         "ssd_prompt_gemm_plan": (i32, [i32, i32, i32, i32, i32, C.POINTER(C.c_int), C.POINTER(C.c_int), i32]),
         "ssd_gemm_blocks": (i32, [i32, i32, i32, i32, i32, C.POINTER(C.c_int), i32]),
         "ssd_attention_plan": (i32, [i32, i32, i32, i32, i32, i32, i32, C.POINTER(C.c_int)]),
-        "ssd_resident_order": (i32, [C.POINTER(C.c_int), i32, i32, C.POINTER(C.c_int)]),
+        "ssd_resident_fits": (i32, [C.POINTER(C.c_int), i32, i32, i32, i32]),
         "ssd_strerror": (C.c_char_p, [i32]),
         "ssd_last_error": (C.c_char_p, []),
     }

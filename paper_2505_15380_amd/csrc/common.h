@@ -72,12 +72,16 @@ struct KvView {
   int32_t* ctl;        // [0] free_top  [1] state error bits (KV_ERR_*)  [2] arrival counter of the accept kernel
                        // [3] number of the next forward launch on this cache (the tag of its hand-over words)
                        // [4],[5] cycle counter of a captured cycle (low, high word of the random counter's step)
+                       // [6] captured cycles that have been replayed (a draft's cache)
   uint32_t* err;       // sticky error word of the persistent forward kernels: DEV_ERR_* bits
-  int32_t* mirror;     // host-mapped copy: [max_seqs][2] = (len, n_pend), then [2*max_seqs] = ctl[1], [2*max_seqs+1] = *err
+  int32_t* mirror;     // host-mapped copy: [max_seqs][2] = (len, n_pend), then [2*max_seqs] = ctl[1], [2*max_seqs+1] = *err and the MIRROR_* words
   void* pool;
   int n_blocks, bt, mbps, max_seqs, pcap;
   int n_layers, nkv, hd;
 };
+
+// Words of the mirror behind the sequences' that say which launches are over: the number of the last forward that was given one, captured cycles.
+constexpr int MIRROR_FORWARD = 2, MIRROR_CYCLE = 3, MIRROR_WORDS = 4;
 
 constexpr int KV_ERR_POOL = 1;        // the device allocator ran out of blocks
 constexpr int KV_ERR_ROLLBACK = 4;    // a rollback asked for more positions than the sequence holds (refused)
@@ -331,10 +335,14 @@ __device__ inline void kv_publish(const KvView& kv, int seq) {
   kv_publish_seq(kv, seq);
   kv_publish_flags(kv);
 }
-// After a forward: the next launch on this cache gets the next number (one thread, the kernel that follows the forward).
-__device__ inline void kv_bump_launch(const KvView& kv) {
+// After a forward: the next launch on this cache gets the next number (one thread, the kernel that follows the forward), and the host learns that this one is over.
+__device__ inline void kv_publish_forward(const KvView& kv, uint32_t publish) {
+  if (publish) kv.mirror[2 * kv.max_seqs + MIRROR_FORWARD] = (int32_t)publish;
+}
+__device__ inline void kv_bump_launch(const KvView& kv, uint32_t publish) {
   const uint32_t t = (uint32_t)kv.ctl[3] + 1u;
   kv.ctl[3] = (int32_t)t;
+  kv_publish_forward(kv, publish);
 }
 
 // Rows of one forward: row m belongs to sequence seq0 + m / R at offset j = m % R.

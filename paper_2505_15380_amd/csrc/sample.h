@@ -395,6 +395,7 @@ struct AcceptArgs {
                          // that a captured graph of a cycle draws fresh uniforms at every replay
   int bump_step;         // the committing thread advances that counter (the last sampling kernel of a cycle without drafts)
   int bump_launch;       // this kernel follows a forward on a.kv: the committing thread advances the cache's launch number
+  uint32_t publish;      // and leaves this in the mirror, where it is not 0
   int slot_base;         // r_i uses slot slot_base + i - 1, the emitted token slot_base + K
   int B, K, V;
   float beta;
@@ -546,7 +547,7 @@ __device__ __forceinline__ void accept_seq(const AcceptArgs a, const int b, cons
   if (a.kv.len == nullptr) return;
   if (solo) {                                              // kv_truncate + kv_publish on the values read at the start
     if (tid == 0) {
-      if (a.bump_launch && b == 0) a.kv.ctl[3] = st_launch + 1;
+      if (a.bump_launch && b == 0) { a.kv.ctl[3] = st_launch + 1; kv_publish_forward(a.kv, a.publish); }
       if (a.bump_step && a.step_dev) {
         const uint64_t nx = step - a.step + 1;
         ((int32_t*)a.step_dev)[0] = (int32_t)(uint32_t)nx;
@@ -587,7 +588,7 @@ __device__ __forceinline__ void accept_seq(const AcceptArgs a, const int b, cons
   const bool failed = *a.kv.err != 0;                      // the forward did not finish: commit nothing
   if (tid == 0) {
     *a.ticket = 0;
-    if (a.bump_launch) kv_bump_launch(a.kv);
+    if (a.bump_launch) kv_bump_launch(a.kv, a.publish);
     if (a.bump_step && a.step_dev) {
       const uint64_t nx = step - a.step + 1;
       ((int32_t*)a.step_dev)[0] = (int32_t)(uint32_t)nx;
@@ -633,12 +634,12 @@ __global__ void __launch_bounds__(SBLOCK) k_warp_accept(WarpArgs w, AcceptArgs a
 // the commit of a prefill chunk.  after_forward: the kernel follows a forward on this cache (advances its launch number;
 // commits nothing if that forward did not finish).
 __global__ void __launch_bounds__(BLOCK) k_kv_set(KvView kv, int seq, int new_len, int add_len, int set_pending, int pending_value,
-                                                  const int32_t* pending_ptr, int after_forward) {
+                                                  const int32_t* pending_ptr, int after_forward, uint32_t publish) {
   const int tid = threadIdx.x, len = kv.len[seq], own = kv.owned[seq], top = kv.ctl[0];
   const bool failed = *kv.err != 0, refused = new_len > len;
   const int target = new_len >= 0 ? new_len : len + add_len, keep = ceil_div(target, kv.bt);
   __syncthreads();                                         // every thread has read the state
-  if (tid == 0 && after_forward) kv_bump_launch(kv);
+  if (tid == 0 && after_forward) kv_bump_launch(kv, publish);
   if (failed || refused) {
     if (tid == 0) {
       if (!failed) kv.ctl[1] |= KV_ERR_ROLLBACK;
@@ -663,9 +664,10 @@ __global__ void __launch_bounds__(BLOCK) k_kv_set(KvView kv, int seq, int new_le
 
 // Draft cache after a verification of K drafts (see ssd_kv_follow): one workgroup, one thread per sequence.
 __global__ void k_kv_follow(KvView kv, int n_seqs, int K, const int32_t* n_acc, const int32_t* next_tok,
-                            const int32_t* x, int32_t* step_dev) {
+                            const int32_t* x, int32_t* step_dev, int replayed) {
   __shared__ int w16[16];
   const int s = threadIdx.x;
+  if (replayed && s == 0) kv.mirror[2 * kv.max_seqs + MIRROR_CYCLE] = ++kv.ctl[6];
   if (step_dev && s == 0) {                                // last kernel of a captured cycle: the next replay is the next step
     const uint64_t nx = ((uint64_t)(uint32_t)step_dev[0] | ((uint64_t)(uint32_t)step_dev[1] << 32)) + 1;
     step_dev[0] = (int32_t)(uint32_t)nx;
@@ -696,7 +698,7 @@ __global__ void k_kv_init(KvView kv) {
   }
   if (i < kv.max_seqs * kv.mbps) kv.table[i] = -1;
   if (i == 0) {
-    kv.ctl[0] = kv.n_blocks; kv.ctl[1] = 0; kv.ctl[2] = 0; kv.ctl[3] = 1; kv.ctl[4] = 0; kv.ctl[5] = 0;
+    kv.ctl[0] = kv.n_blocks; kv.ctl[1] = 0; kv.ctl[2] = 0; kv.ctl[3] = 1; kv.ctl[4] = 0; kv.ctl[5] = 0; kv.ctl[6] = 0;
     kv.mirror[2 * kv.max_seqs] = 0; kv.mirror[2 * kv.max_seqs + 1] = 0;
   }
 }

@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <array>
 #include <atomic>
+#include <chrono>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -14,6 +15,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -326,6 +328,10 @@ struct ssd_kv {
   bool attn_whole = false;   // ssd_kv_last_forward_path tells launches whose attention is one part (4) from others (3) on this cache
   bool attn_mfma = true;     // per-operator path: matrix-core attention where it applies (SSD_ATTN=valu: the scalar kernel)
   int32_t* ticket_alt = nullptr;   // ssd_verify_noalloc: the commit's arrival counter in the library's static scratch
+  // what of its launches other streams' may have to be kept from (resident.h); under g_resident_mutex but for the words that device code leaves in the mirror
+  struct { ssd_kv* next = nullptr; bool listed = false, slow = false; int device = -1, wgs = 0; const void* stream = nullptr; uint32_t forward = 0, cycle = 0; } run;
+  uint32_t forwards = 0, cycles = 0;      // such launches given a number so far: forwards by themselves, captured cycles (on the draft's cache)
+  uint32_t publish = 0;            // the number that the kernel behind this forward leaves in the mirror, 0: none
   bool capturing = false;          // a cycle is being captured on this cache: no synchronisation, no fallback kernels
   int last_path = 0;               // 1 per-operator launches, 2 barrier kernel, 3 barrier-free kernel, 4 the same with attention without parts, 5 fp32 in one launch
   bool last_whole = false;
@@ -335,6 +341,88 @@ struct ssd_kv {
   int32_t* mirror_host;
   std::vector<int> len_ub, npend_ub;
 };
+
+// Launches whose workgroups wait for each other, of all caches (resident.h).  One that does not fit beside what other streams still run is held back here, on the host,
+// until they are over, which the kernels behind them leave in the caches' mirrors.  Nothing is asked of the other streams themselves, which may be being captured, be
+// another thread's (hipStreamPerThread) or be gone: HIP (7.2) ends the process when it is asked about a stream that was destroyed, refuses to wait for an event of one that is
+// being captured, and breaks off every capture when the device is waited for.  And a program with one stream pays nothing, where an event behind each launch
+// takes 1.0 to 1.4 us of its stream's time (of 22 for the smallest forward).  us for a step of each of two streams in turn, with events and stream waits -> held back here:
+// two 0.5B targets 669 -> 659 (one after the other 647), two drafts 166 -> 156 (144), a 0.5B target and the smallest one, which fit, 393 -> 323.  A launch that has been held back for RESIDENT_WAIT_MS, behind whatever else these streams
+// have before theirs, is not admitted, nor are others while that lasts: the caller takes launches that do not wait.
+// The mutex is held until the launch is enqueued, so that no other thread's comes in between.  (A launch on a stream that is being captured is not looked at: its
+// graphs are the caller's to order.)
+static std::mutex g_resident_mutex;
+static ssd_kv* g_resident = nullptr;                       // caches that have had such a launch
+constexpr int RESIDENT_WAIT_MS = 1000;
+
+// What tells streams apart: hipStreamPerThread is another one in each thread, hipStreamLegacy the default one.  (A handle that is used again after its stream was destroyed
+// does no harm: hipStreamDestroy waits for the stream's work.)
+static const void* resident_key(hipStream_t st) {
+  static std::atomic<size_t> threads{0};
+  thread_local const size_t thread = threads++;
+  return st == hipStreamPerThread ? (const void*)(2 * thread + 1) : st == hipStreamLegacy ? nullptr : (const void*)st;
+}
+
+static bool resident_running(const ssd_kv* kv) {
+  const volatile int32_t* w = kv->mirror_host + 2 * kv->max_seqs;
+  return (int32_t)((uint32_t)w[MIRROR_FORWARD] - kv->run.forward) < 0 || (int32_t)((uint32_t)w[MIRROR_CYCLE] - kv->run.cycle) < 0;
+}
+
+struct ResidentLaunch {
+  std::unique_lock<std::mutex> lock;
+  bool admitted = true;                                    // false: launches that do not wait must do
+  ResidentLaunch(ssd_kv* kv, hipStream_t st, int wgs, bool cycle = false) : lock(g_resident_mutex) {
+    int device = -1;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipGetDevice(&device) != hipSuccess) return;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) { (void)hipGetLastError(); return; }      // (the default stream beside a capture: the launch will say so)
+    if (cs != hipStreamCaptureStatusNone) return;
+    const void* key = resident_key(st);
+    std::chrono::steady_clock::time_point until{};
+    while (!fits(kv, device, key, wgs)) {
+      bool slow = false;
+      for (ssd_kv* o = g_resident; o; o = o->run.next) slow = slow || (o->run.slow && other(o, kv, device, key));
+      const auto now = std::chrono::steady_clock::now();
+      if (until.time_since_epoch().count() == 0) until = now + std::chrono::milliseconds(RESIDENT_WAIT_MS);
+      if (slow || now >= until) {
+        for (ssd_kv* o = g_resident; o; o = o->run.next)
+          if (other(o, kv, device, key)) o->run.slow = true;
+        admitted = false;
+        return;
+      }
+      std::this_thread::yield();
+    }
+    auto& run = kv->run;
+    if (!run.listed) { run.listed = true; run.next = g_resident; g_resident = kv; }
+    run.wgs = resident_running(kv) ? std::max(run.wgs, wgs) : wgs;      // (its earlier ones too, whatever stream they are on: the caller orders a cache's calls)
+    run.slow = false;
+    run.device = device;
+    run.stream = key;
+    if (cycle) { run.cycle = ++kv->cycles; return; }
+    if (++kv->forwards == 0) ++kv->forwards;
+    run.forward = kv->publish = kv->forwards;
+  }
+  // Does `o` run something that a launch on `kv` has to mind?
+  static bool other(const ssd_kv* o, const ssd_kv* kv, int device, const void* key) {
+    return o != kv && o->run.device == device && o->run.stream != key && resident_running(o);
+  }
+  static bool fits(const ssd_kv* kv, int device, const void* key, int wgs) {
+    Resident running[64];
+    int n = 0;
+    for (const ssd_kv* o = g_resident; o; o = o->run.next) {
+      if (!other(o, kv, device, key)) continue;
+      if (n == 64) return false;
+      running[n++] = {o->run.stream, o->run.wgs};
+    }
+    return n == 0 || resident_fits(running, n, key, wgs, kv->cus);
+  }
+};
+
+static void resident_forget(ssd_kv* kv) {
+  std::lock_guard<std::mutex> lock(g_resident_mutex);
+  for (ssd_kv** p = &g_resident; *p; p = &(*p)->run.next)
+    if (*p == kv) { *p = kv->run.next; return; }
+}
 
 // Shapes whose fp32 forward of a few rows is one launch (small.h).  (With head size 64 two chunks of keys and values do not fit the registers.)
 // A workgroup of a kv head computes the projections of its G query heads, its key and its value two at a time, and every workgroup of gate / up the whole
@@ -470,9 +558,9 @@ extern "C" int ssd_kv_create(const ssd_model* m, int max_seqs, int max_rows, int
   v.n_blocks = n_blocks; v.bt = block_tokens; v.mbps = mbps; v.max_seqs = max_seqs; v.pcap = pending_cap;
   v.n_layers = m->c.n_layers; v.nkv = m->c.n_kv_heads; v.hd = m->c.head_dim;
   v.err = kv->bar + 64;
-  hipError_t e = hipHostMalloc((void**)&kv->mirror_host, (2 * max_seqs + 2) * sizeof(int32_t), hipHostMallocMapped);
+  hipError_t e = hipHostMalloc((void**)&kv->mirror_host, (2 * max_seqs + MIRROR_WORDS) * sizeof(int32_t), hipHostMallocMapped);
   if (e != hipSuccess) { delete kv; return fail(SSD_EHIP, "hipHostMalloc: %s", hipGetErrorString(e)); }
-  memset(kv->mirror_host, 0, (2 * max_seqs + 2) * sizeof(int32_t));
+  memset(kv->mirror_host, 0, (2 * max_seqs + MIRROR_WORDS) * sizeof(int32_t));
   e = hipHostGetDevicePointer((void**)&v.mirror, kv->mirror_host, 0);
   if (e != hipSuccess) { (void)hipHostFree(kv->mirror_host); delete kv; return fail(SSD_EHIP, "hipHostGetDevicePointer: %s", hipGetErrorString(e)); }
   kv->len_ub.assign(max_seqs, 0);
@@ -540,6 +628,7 @@ extern "C" int ssd_kv_create(const ssd_model* m, int max_seqs, int max_rows, int
 
 extern "C" int ssd_kv_destroy(ssd_kv* kv) {
   if (!kv) return SSD_OK;
+  resident_forget(kv);
   if (kv->mirror_host) (void)hipHostFree(kv->mirror_host);
   delete kv;
   return SSD_OK;
@@ -1000,53 +1089,7 @@ static int launch_attn(AttnArgs a, int nchunks, int plan_chunks, bool prompt, in
   return SSD_OK;
 }
 
-// Launches whose workgroups wait for each other, of all streams (resident.h).  A program with one stream pays a look at its own entry.  Held until the launch is
-// enqueued, so that no other thread's comes in between.  (A stream that is being captured can neither wait for another one nor be waited for: its graphs are
-// the caller's to order.)
-static std::mutex g_resident_mutex;
-static ResidentTable g_resident;
-
-static bool being_captured(hipStream_t st) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();
-  return true;
-}
-
-// What a stream is in the table: hipStreamPerThread is another stream in each thread (and a thread that has ended is none), hipStreamLegacy the default one.
-static const void* resident_key(hipStream_t st) {
-  static std::atomic<size_t> threads{0};
-  thread_local const size_t thread = threads++;
-  return st == hipStreamPerThread ? (const void*)(2 * thread + 1) : st == hipStreamLegacy ? nullptr : (const void*)st;
-}
-
-struct ResidentLaunch {
-  std::unique_lock<std::mutex> lock;
-  hipStream_t st;
-  hipEvent_t done = nullptr;
-  ResidentLaunch(hipStream_t stream, int wgs, int cus) : lock(g_resident_mutex), st(stream) {
-    int device = -1;
-    if (hipGetDevice(&device) != hipSuccess || being_captured(st)) return;
-    ResidentTable::Entry* own = g_resident.admit(device, resident_key(st), wgs, cus, [&](const ResidentTable::Entry& x) {
-      hipEvent_t ev = (hipEvent_t)x.done;
-      if (!ev) {
-        const hipStream_t other = (hipStream_t)x.stream;
-        if (being_captured(other) || hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return;
-        if (hipEventRecord(ev, other) != hipSuccess) (void)hipGetLastError();      // (a stream that is gone has nothing to wait for)
-      }
-      if (hipStreamWaitEvent(st, ev, 0) != hipSuccess) (void)hipGetLastError();
-      (void)hipEventDestroy(ev);
-    });
-    if (st != hipStreamPerThread || !own) return;
-    if (!own->done && hipEventCreateWithFlags(&done, hipEventDisableTiming) == hipSuccess) own->done = done;
-    done = (hipEvent_t)own->done;
-  }
-  ~ResidentLaunch() {
-    if (done && hipEventRecord(done, st) != hipSuccess) (void)hipGetLastError();
-  }
-};
-
-// The same forward as one persistent kernel (see persistent.h).
+// The same forward as one persistent kernel (see persistent.h).  Returns -1 when it is not admitted beside what other streams run.
 static int forward_persistent(const ssd_model* m, ssd_kv* kv, Rows rows, int B, int pcap, const int32_t* dev_tokens,
                               int tok_stride, bool with_head, hipStream_t st) {
   const ssd_model_config& c = m->c;
@@ -1075,8 +1118,9 @@ static int forward_persistent(const ssd_model* m, ssd_kv* kv, Rows rows, int B, 
   auto splits = [&](int K) { return std::max(1, std::min(std::min(NU / npairs, (K / 32) / 4), P_MAX_SPLITS)); };
   a.gs_o = (c.n_q_heads * c.head_dim) / 32 <= 4 * PF_K ? 1 : splits(c.n_q_heads * c.head_dim);   // <= PF_K k-tiles per wave: all prefetched
   a.gs_d = splits(c.d_ffn);
+  const ResidentLaunch order(kv, st, G);
+  if (!order.admitted) return -1;
   kv->bar_epoch += (with_head ? 1u : 0u) + 5u * (uint32_t)c.n_layers;  // barriers this launch executes
-  const ResidentLaunch order(st, G, kv->cus);
   ProfScope ps(PROF_PERSISTENT, st);
   hipLaunchKernelGGL(k_forward_persistent, dim3(G), dim3(PBLOCK), 0, st, a);
   LAUNCH_CHECK();
@@ -1084,7 +1128,7 @@ static int forward_persistent(const ssd_model* m, ssd_kv* kv, Rows rows, int B, 
 }
 
 // The same forward without grid barriers between phases (see dataflow.h).  Returns -1 when the launch does not
-// fit that kernel's limits, so that the caller takes another one instead.
+// fit that kernel's limits or is not admitted beside what other streams run, so that the caller takes another one instead.
 static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, int pcap, const int32_t* dev_tokens,
                             int tok_stride, bool with_head, hipStream_t st) {
   const ssd_model_config& c = m->c;
@@ -1142,7 +1186,8 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   a.bar = kv->bar;
   a.trace = kv->trace_on ? kv->trace : nullptr;
   kv->last_wgs = G;
-  const ResidentLaunch order(st, G, kv->cus);
+  const ResidentLaunch order(kv, st, G);
+  if (!order.admitted) return -1;
   ProfScope ps(PROF_PERSISTENT, st);
   kv->last_whole = kv->attn_whole && max_len + 16 <= DF_ONE_PART;      // (reported only)
   // The smallest instantiation whose flight of an operand staging holds the rows, where its sum tasks (of 8, 32, 32, 64, 64 columns) go well: those of
@@ -1169,7 +1214,7 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
 }
 
 // The fp32 forward of a few rows as one launch (see small.h): up to 16 rows a sequence and 64 in all, of up to 16 sequences that attend in one part, with a compute
-// unit for every item.  Returns -1 where that is not so; the launches per operator give the same bits.
+// unit for every item.  Returns -1 where that is not so, or where it is not admitted beside what other streams run; the launches per operator give the same bits.
 static int forward_small(const ssd_model* m, ssd_kv* kv, Rows rows, int B, int pcap, const int32_t* dev_tokens, int tok_stride, bool with_head,
                          hipStream_t st) {
   const ssd_model_config& c = m->c;
@@ -1192,7 +1237,8 @@ static int forward_small(const ssd_model* m, ssd_kv* kv, Rows rows, int B, int p
   a.kv = kv->v; a.rows = rows; a.pcap = pcap; a.n_seqs = B; a.tok_stride = tok_stride; a.with_head = with_head ? 1 : 0; a.tokens = dev_tokens;
   a.tw = (uint32_t*)kv->t_base; a.st_set = kv->t_attp_at; a.cap = kv->t_rows; a.rowblk = kv->t_rowblk; a.state = kv->t_rowblk + SF_MAX_ROWS;
   a.logits = kv->logits; a.bar = kv->bar;
-  const ResidentLaunch order(st, G, kv->cus);
+  const ResidentLaunch order(kv, st, G);
+  if (!order.admitted) return -1;
   ProfScope ps(PROF_PERSISTENT, st);
   hipLaunchKernelGGL(k_forward_f32, dim3(G), dim3(PBLOCK), 0, st, a);
   LAUNCH_CHECK();
@@ -1214,6 +1260,7 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
     const int rc = kv_launch_guard(kv, st, 1);
     if (rc) return rc;
     ++kv->launch_no;
+    kv->publish = 0;
   }
   if (kv->capturing && !(kv->persistent_wgs > 0 && M <= kv->p_rows && kv->dataflow))
     return fail(SSD_ENOSUP, "this launch does not fit the barrier-free forward kernel: it cannot be captured");
@@ -1223,8 +1270,8 @@ static int forward(const ssd_model* m, ssd_kv* kv, int seq0, int B, int R, int p
       if (rc >= 0) { kv->last_path = kv->last_whole ? 4 : 3; return rc; }
     }
     if (kv->capturing) return fail(SSD_ENOSUP, "this launch does not fit the barrier-free forward kernel: it cannot be captured");
-    kv->last_path = 2;
-    return forward_persistent(m, kv, rows, B, pcap, dev_tokens, tok_stride, with_head, st);
+    const int rc = forward_persistent(m, kv, rows, B, pcap, dev_tokens, tok_stride, with_head, st);
+    if (rc != -1) { kv->last_path = 2; return rc; }
   }
   if (kv->wide && M <= kv->t_rows) {
     const int rc = forward_dataflow(m, kv, rows, B, pcap, dev_tokens, tok_stride, with_head, st);
@@ -1390,7 +1437,7 @@ extern "C" int ssd_prefill(ssd_model* m, ssd_kv* kv, int seq, const int32_t* dev
   if (seq < 0 || seq >= kv->max_seqs) return fail(SSD_EINVAL, "sequence %d out of range", seq);
   if ((rc = kv_check_flags(kv))) return rc;
   hipStream_t st = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, 0, 0, 0, 0, (const int32_t*)nullptr, 0);
+  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, 0, 0, 0, 0, (const int32_t*)nullptr, 0, 0u);
   LAUNCH_CHECK();
   kv->len_ub[seq] = 0;
   kv->npend_ub[seq] = 0;
@@ -1399,11 +1446,11 @@ extern "C" int ssd_prefill(ssd_model* m, ssd_kv* kv, int seq, const int32_t* dev
   for (int i = 0; i < n - 1; i += chunk) {
     const int R = std::min(chunk, n - 1 - i);
     if ((rc = forward_any(m, kv, seq, 1, R, 0, dev_tokens + i, 0, false, st))) return rc;
-    hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, -1, R, 0, 0, (const int32_t*)nullptr, 1);
+    hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, -1, R, 0, 0, (const int32_t*)nullptr, 1, kv->publish);
     LAUNCH_CHECK();
     kv->len_ub[seq] += R;
   }
-  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, -1, 0, 1, 0, dev_tokens + (n - 1), 0);
+  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, -1, 0, 1, 0, dev_tokens + (n - 1), 0, 0u);
   LAUNCH_CHECK();
   kv->npend_ub[seq] = 1;
   return SSD_OK;
@@ -1456,7 +1503,7 @@ static int step(ssd_model* m, ssd_kv* kv, int B, int K, const int32_t* dev_x, co
     LAUNCH_CHECK();
   }
   a.pd = dev_pd; a.x = dev_x; a.uniforms = nullptr; a.seed = cfg->seed; a.step = step_ctr;
-  a.step_dev = step_dev; a.bump_step = bump_step ? 1 : 0; a.bump_launch = 1;
+  a.step_dev = step_dev; a.bump_step = bump_step ? 1 : 0; a.bump_launch = 1; a.publish = kv->publish;
   a.B = B; a.K = K; a.V = V; a.beta = cfg->beta;
   a.n_acc = dev_n; a.next_tok = dev_next; a.tok_stride = next_stride; a.flags = nullptr;
   a.kv = kv->v; a.seq0 = 0;
@@ -1593,7 +1640,7 @@ extern "C" int ssd_kv_rollback(ssd_kv* kv, int seq, int new_len, int pending_tok
     if (new_len < 0 || new_len > kv->len_ub[seq])
       return fail(SSD_EINVAL, "rollback to %d but sequence %d holds %d positions", new_len, seq, kv->len_ub[seq]);
   }
-  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, new_len, 0, 1, pending_token, (const int32_t*)nullptr, 0);
+  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, new_len, 0, 1, pending_token, (const int32_t*)nullptr, 0, 0u);
   LAUNCH_CHECK();
   kv->len_ub[seq] = new_len;
   kv->npend_ub[seq] = 1;
@@ -1610,7 +1657,7 @@ extern "C" int ssd_kv_follow(ssd_kv* kv_d, int n_seqs, int K, const int32_t* dev
     if (rc) return rc;
   }
   hipLaunchKernelGGL(k_kv_follow, dim3(1), dim3(cdiv(n_seqs, 64) * 64), 0, (hipStream_t)stream, kv_d->v, n_seqs, K, dev_n_accepted,
-                     dev_next_token, dev_draft_tokens, (int32_t*)nullptr);
+                     dev_next_token, dev_draft_tokens, (int32_t*)nullptr, 0);
   LAUNCH_CHECK();
   for (int s = 0; s < n_seqs; ++s) kv_d->npend_ub[s] = 2;       // the length can only have shrunk
   return SSD_OK;
@@ -1742,12 +1789,38 @@ static void cycle_advance_bounds(ssd_cycle* c) {
   }
 }
 
+// The calls of one cycle, which leave the bounds as the eager calls do (a capture keeps the ones it is made for).
+static int cycle_steps(ssd_cycle* c, hipStream_t st) {
+  const int K = c->K, V = c->target->c.vocab;
+  const bool capture = c->kv->capturing;
+  const int32_t* step_dev = c->kv->v.ctl + 4;
+  ssd_sample_config dc = c->dcfg;
+  dc.beta = 0.0f;
+  int rc = SSD_OK;
+  for (int i = 0; i < K && !rc; ++i) {
+    rc = step(c->draft, c->kv_d, c->n_seqs, 0, nullptr, nullptr, &dc, 0, SSD_DRAFT_SLOT0 + i, nullptr, c->x + i, K,
+              c->pd + (size_t)i * V, (size_t)K * V, true, nullptr, st, step_dev, false, i == 0);
+    if (rc) return rc;
+    for (int s = 0; s < c->n_seqs; ++s) {
+      if (!capture) c->kv_d->len_ub[s] += c->kv_d->npend_ub[s];
+      c->kv_d->npend_ub[s] = 1;                            // after a draft step exactly one token is pending
+    }
+  }
+  if ((rc = step(c->target, c->kv, c->n_seqs, K, c->x, c->pd, &c->cfg, 0, 0, c->n_acc, c->next, 1, nullptr, 0, false,
+                 nullptr, st, step_dev, false, true))) return rc;
+  hipLaunchKernelGGL(k_kv_follow, dim3(1), dim3(cdiv(c->n_seqs, 64) * 64), 0, st, c->kv_d->v, c->n_seqs, K, c->n_acc, c->next, c->x,
+                     c->kv->v.ctl + 4, capture ? 1 : 0);
+  if (hipGetLastError() != hipSuccess) return fail(SSD_EHIP, "k_kv_follow launch failed");
+  for (int s = 0; s < c->n_seqs && !capture; ++s) { c->kv->len_ub[s] += K + 1; c->kv->npend_ub[s] = 1; c->kv_d->npend_ub[s] = 2; }
+  return SSD_OK;
+}
+
 static int cycle_capture(ssd_cycle* c, hipStream_t st) {
   cycle_drop(c);
   int rc;
   // exact lengths, room for the replays this capture will serve, numbering that cannot run out inside them
   if ((rc = kv_refresh(c->kv, st)) || (rc = kv_refresh(c->kv_d, st))) return rc;
-  const int K = c->K, V = c->target->c.vocab;
+  const int K = c->K;
   int max_t = 0, max_d = 0;
   for (int s = 0; s < c->n_seqs; ++s) { max_t = std::max(max_t, c->kv->len_ub[s]); max_d = std::max(max_d, c->kv_d->len_ub[s]); }
   // launch shapes (attention parts, workgroups) are those of a prefix up to 256 positions longer than today's
@@ -1769,22 +1842,7 @@ static int cycle_capture(ssd_cycle* c, hipStream_t st) {
                          c->kv->launch_no = ln_t; c->kv_d->launch_no = ln_d; c->kv->capturing = c->kv_d->capturing = false; };
   hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) { restore(); return fail(SSD_EHIP, "hipStreamBeginCapture: %s", hipGetErrorString(e)); }
-  const int32_t* step_dev = c->kv->v.ctl + 4;
-  ssd_sample_config dc = c->dcfg;
-  dc.beta = 0.0f;
-  rc = SSD_OK;
-  for (int i = 0; i < K && !rc; ++i) {
-    rc = step(c->draft, c->kv_d, c->n_seqs, 0, nullptr, nullptr, &dc, 0, SSD_DRAFT_SLOT0 + i, nullptr, c->x + i, K,
-              c->pd + (size_t)i * V, (size_t)K * V, true, nullptr, st, step_dev, false, i == 0);
-    for (int s = 0; s < c->n_seqs; ++s) c->kv_d->npend_ub[s] = 1;        // after a draft step exactly one token is pending
-  }
-  if (!rc) rc = step(c->target, c->kv, c->n_seqs, K, c->x, c->pd, &c->cfg, 0, 0, c->n_acc, c->next, 1, nullptr, 0, false,
-                     nullptr, st, step_dev, false, true);
-  if (!rc) {
-    hipLaunchKernelGGL(k_kv_follow, dim3(1), dim3(cdiv(c->n_seqs, 64) * 64), 0, st, c->kv_d->v, c->n_seqs, K, c->n_acc, c->next, c->x,
-                       c->kv->v.ctl + 4);
-    if (hipGetLastError() != hipSuccess) rc = fail(SSD_EHIP, "k_kv_follow launch failed");
-  }
+  rc = cycle_steps(c, st);
   c->wgs = std::max(c->kv->last_wgs, c->kv_d->last_wgs);
   hipGraph_t g = nullptr;
   e = hipStreamEndCapture(st, &g);
@@ -1841,10 +1899,17 @@ extern "C" int ssd_cycle_launch(ssd_cycle* c, void* stream) {
     fits = bt <= c->kv->v.n_blocks && bd <= c->kv_d->v.n_blocks;
   }
   if (!fits && (rc = cycle_capture(c, st))) return rc;
+  bool admitted;
   {
-    const ResidentLaunch order(st, c->wgs, c->kv->cus);
-    HIP_TRY(hipGraphLaunch(c->exec, st));
+    const uint32_t cycles = c->kv_d->cycles;
+    const ResidentLaunch order(c->kv_d, st, c->wgs, true);
+    admitted = order.admitted;
+    if (const hipError_t e = admitted ? hipGraphLaunch(c->exec, st) : hipSuccess; e != hipSuccess) {
+      c->kv_d->run.cycle = c->kv_d->cycles = cycles;       // (nothing of it will say that it is over)
+      return fail(SSD_EHIP, "hipGraphLaunch: %s", hipGetErrorString(e));
+    }
   }
+  if (!admitted) return cycle_steps(c, st);                // (call by call: those of its forwards that are not admitted either run one launch per operator)
   c->kv->launch_no += 1;
   c->kv_d->launch_no += (uint32_t)K;
   c->kv->last_path = 3;
@@ -1951,14 +2016,13 @@ extern "C" int ssd_attention_plan(int head_dim, int n_q_heads, int n_kv_heads, i
   return SSD_OK;
 }
 
-extern "C" int ssd_resident_order(const int* launches, int n, int cus, int* behind) {
-  if (!launches || !behind || n < 0 || cus < 1) return fail(SSD_EINVAL, "bad launches");
-  ResidentTable t;
+extern "C" int ssd_resident_fits(const int* running, int n, int stream, int wgs, int cus) {
+  constexpr int MOST = 64;
+  Resident r[MOST];
+  if (n < 0 || n > MOST || (n && !running) || cus < 1 || wgs < 1 || wgs > cus) return fail(SSD_EINVAL, "bad launches");
   for (int i = 0; i < n; ++i) {
-    const int stream = launches[2 * i], wgs = launches[2 * i + 1];
-    if (stream < 0 || wgs < 1 || wgs > cus) return fail(SSD_EINVAL, "bad launch %d", i);
-    behind[i] = 0;
-    t.admit(0, (const void*)(size_t)(stream + 16), wgs, cus, [&](const ResidentTable::Entry&) { ++behind[i]; });
+    if (running[2 * i + 1] < 1 || running[2 * i + 1] > cus) return fail(SSD_EINVAL, "bad launch %d", i);
+    r[i] = {(const void*)(size_t)running[2 * i], running[2 * i + 1]};
   }
-  return SSD_OK;
+  return resident_fits(r, n, (const void*)(size_t)stream, wgs, cus) ? 1 : 0;
 }

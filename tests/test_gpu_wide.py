@@ -174,3 +174,103 @@ def test_which_batches_of_wide_rows_are_one_launch(lens, K, path):
     model, kv = _target(shape, lens, 128)
     x = torch.from_numpy(np.random.default_rng(7).integers(0, shape["vocab"], (len(lens), K)).astype(np.int32)).cuda()
     assert _verify_logits(model, kv, len(lens), x)[1] == path
+
+
+@pytest.mark.parametrize("busy", [False, True])
+def test_launches_beside_a_stream_that_is_being_captured(busy):
+    """What a stream was given before its capture may still run: a launch of another stream that does not fit beside it waits for it on the host, and, where
+    that takes more than a second (`busy`), runs per operator, a captured cycle call by call.  Logits within the rounding of cached keys, decisions the same."""
+    import ctypes as C
+    import paper_2505_15380_amd as ssd
+    from tests.test_gpu_cycle import make_session
+    from tests.test_gpu_row_bits import _target
+    hip = ssd.load_library()                                 # (the runtime that the library is linked with)
+    K, a, b = 4, torch.cuda.Stream(), torch.cuda.Stream()
+    cfg = ssd.sample_config(beta=0.3, seed=3)
+
+    def verify(shape, model, kv):
+        x = torch.from_numpy(np.random.default_rng(7).integers(0, shape["vocab"], (1, K)).astype(np.int32)).cuda()
+        pd = torch.full((1, K, shape["vocab"]), 1.0 / shape["vocab"], device="cuda")
+        return lambda: ssd.ssd_verify(model, kv, 1, x, pd, K, cfg, 0, want_logits=True)["logits"]
+
+    shapes = [_shape("one_layer"), dict(si.model_shape("half_b_draft"), vocab=300, n_embed=300), si.model_shape("tiny")]
+    targets = [_target(s, [70], 64) for s in shapes]
+    calls = [verify(s, *t) for s, t in zip(shapes, targets)]
+    one, _ = make_session("mini", 3, beta=0.3, steps=8, n_prefix=60)
+    two, _ = make_session("mini", 3, beta=0.3, steps=8, n_prefix=60)
+    pending = [kv.state(0)["pending"][0] for _, kv in targets]
+    m = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    out = torch.empty_like(m)
+    torch.mm(m, m, out=out)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(b):
+        g = one.graph_cycle()
+        g.launch()
+        two.cycle(0)
+        ref = [f() for f in calls[1:]]
+        for (_, kv), p in zip(targets[1:], pending[1:]):
+            ssd.ssd_kv_rollback(kv, 0, 70, p)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(a):
+        if busy:                                             # 3 to 4 seconds of products of at least 1 ms each at the card's peak, measured first
+            start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(20):
+                torch.mm(m, m, out=out)
+            stop.record()
+            a.synchronize()
+            for _ in range(min(5000, int(3500 / (start.elapsed_time(stop) / 20)))):
+                torch.mm(m, m, out=out)
+        calls[0]()
+        assert targets[0][1].last_forward_path() == 3
+    graph, held = C.c_void_p(), []
+    assert hip.hipStreamBeginCapture(C.c_void_p(a.cuda_stream), 1) == 0      # (thread-local)
+    try:
+        with torch.cuda.stream(b):
+            got = [f() for f in calls[1:]]
+            held.append(targets[1][1].last_forward_path())
+            for c in (1, 2):
+                g.launch()
+                held.append(one.kv.last_forward_path())
+    finally:
+        assert hip.hipStreamEndCapture(C.c_void_p(a.cuda_stream), C.byref(graph)) == 0      # (nothing broke it off)
+    if graph.value:
+        assert hip.hipGraphDestroy(graph) == 0
+    assert held == [1 if busy else 3] * 3
+    torch.cuda.synchronize()
+    with torch.cuda.stream(b):
+        for c in (1, 2):
+            two.cycle(c)
+        g.launch()
+        two.cycle(3)
+        assert one.kv.last_forward_path() == 3
+        ssd.ssd_kv_rollback(targets[1][1], 0, 70, pending[1])
+        again = calls[1]()
+        assert targets[1][1].last_forward_path() == 3
+        torch.cuda.synchronize()
+        assert torch.equal(one.x, two.x) and int(one.n_acc[0]) == int(two.n_acc[0]) and int(one.next[0]) == int(two.next[0])
+        assert one.kv.state(0) == two.kv.state(0) and one.kv_d.state(0) == two.kv_d.state(0)
+        # path 1 against path 3: cached keys and values of bf16 that round the other way
+        assert float((one.pd - two.pd).norm()) <= 1e-2 * float(two.pd.norm())
+    assert torch.equal(again, ref[0]) and torch.equal(got[1], ref[1])        # (fp32: the same bits either way)
+    assert float((got[0] - ref[0]).norm()) <= 1e-2 * float(ref[0].norm())
+
+
+def test_a_stream_that_was_destroyed_is_not_asked(monkeypatch):
+    """Its handle may be anything by then: launches that would not have fitted beside its last ones go on as ever."""
+    import ctypes as C
+    import paper_2505_15380_amd as ssd
+    from paper_2505_15380_amd import binding
+    from tests.test_gpu_row_bits import _target, _verify_logits
+    hip = ssd.load_library()
+    x = torch.zeros(1, 0, dtype=torch.int32, device="cuda")
+    for shape in (_shape("one_layer"), dict(si.model_shape("half_b_draft"), vocab=300, n_embed=300)):
+        model, kv = _target(shape, [70], 64)
+        torch.cuda.synchronize()
+        st = C.c_void_p()
+        assert hip.hipStreamCreate(C.byref(st)) == 0
+        with monkeypatch.context() as m:
+            m.setattr(binding, "_stream", lambda: st.value)
+            assert _verify_logits(model, kv, 1, x)[1] == 3
+        assert hip.hipStreamDestroy(st) == 0
+        assert _verify_logits(model, kv, 1, x)[1] == 3

@@ -116,41 +116,23 @@ def test_parts_of_attention_are_whole_rounds_of_the_key_groups(lib):
     assert lib.ssd_attention_plan(32, 2, 1, 1, 1, 0, 256, plan) == -1 and lib.ssd_attention_plan(64, 3, 2, 1, 1, 0, 256, plan) == -1
 
 
-def _order(lib, launches, cus=256):
-    flat, behind = (C.c_int * (2 * len(launches)))(*[v for x in launches for v in x]), (C.c_int * len(launches))()
-    assert lib.ssd_resident_order(flat, len(launches), cus, behind) == 0
-    return list(behind)
+def _fits(lib, running, stream, wgs, cus=256):
+    return lib.ssd_resident_fits((C.c_int * (2 * len(running) or 1))(*[v for x in running for v in x]), len(running), stream, wgs, cus)
 
 
-@pytest.mark.parametrize("a,b,ordered", [
-    (216, 37, False), (218, 32, False), (128, 128, False), (13, 100, False),                # 27 + 5, 28 + 4, 16 + 16, 2 + 13 of an XCD's 32 units
-    (218, 37, True), (218, 38, True), (222, 34, True), (228, 28, True), (204, 52, True),    # at most 256 together, but 33 on some XCD
-    (218, 33, True), (129, 128, True), (256, 1, True)])
-def test_launches_are_ordered_where_an_xcds_share_does_not_fit(lib, a, b, ordered):
-    assert _order(lib, [(0, a), (1, b)]) == [0, int(ordered)]
-    assert _order(lib, [(0, b), (1, a)]) == [0, int(ordered)]
+@pytest.mark.parametrize("a,b,fits", [
+    (216, 37, 1), (218, 32, 1), (128, 128, 1), (13, 100, 1),                               # 27 + 5, 28 + 4, 16 + 16, 2 + 13 of an XCD's 32 units
+    (218, 37, 0), (218, 38, 0), (222, 34, 0), (228, 28, 0), (204, 52, 0),                  # at most 256 together, but 33 on some XCD
+    (218, 33, 0), (129, 128, 0), (256, 1, 0)])
+def test_launches_run_side_by_side_where_every_xcds_share_fits(lib, a, b, fits):
+    assert _fits(lib, [(0, a)], 1, b) == _fits(lib, [(0, b)], 1, a) == fits
+    assert _fits(lib, [(0, a)], 0, b) == 1                   # (a stream's launches are ordered among themselves)
 
 
-def test_shares_of_launches_that_may_run_side_by_side_fit_every_xcd(lib):
-    """Random launches on five streams against a model that keeps, per launch, what it was ordered behind: any set of launches that nothing orders
-    among themselves, one per stream, has at most 32 workgroups on an XCD."""
-    import itertools
-    import random
-    rng = random.Random(5)
-    for trial in range(200):
-        launches = [(rng.randrange(5), rng.choice([1, 13, 25, 37, 64, 100, 152, 218, 256, rng.randint(1, 256)])) for _ in range(12)]
-        behind = _order(lib, launches)
-        before = []                                          # launches that are over when launch i begins
-        last = {}
-        for i, (s, _) in enumerate(launches):
-            done = set()
-            for t, j in last.items():
-                if t == s or behind[i]:
-                    done |= {j} | before[j]
-            before.append(done)
-            last[s] = i
-        for combo in itertools.chain.from_iterable(itertools.combinations(range(12), r) for r in (2, 3, 4)):
-            if all(i not in before[j] for i in combo for j in combo if i < j):
-                assert sum(-(-launches[i][1] // 8) for i in combo) <= 32, (launches, behind, combo)
-    assert lib.ssd_resident_order(None, 1, 256, (C.c_int * 1)()) == -1 and _order(lib, []) == []
-    assert lib.ssd_resident_order((C.c_int * 2)(0, 257), 1, 256, (C.c_int * 1)()) == -1
+def test_a_stream_counts_with_its_largest_launch(lib):
+    assert _fits(lib, [], 0, 256) == 1
+    assert _fits(lib, [(0, 100), (0, 218), (0, 13)], 1, 32) == 1 and _fits(lib, [(0, 13), (0, 218)], 1, 33) == 0
+    assert _fits(lib, [(0, 100), (2, 100), (0, 90), (1, 256)], 1, 48) == 1 and _fits(lib, [(0, 100), (2, 100), (0, 90)], 1, 49) == 0
+    assert _fits(lib, [(s, 1) for s in range(31)], 31, 8) == 1 and _fits(lib, [(s, 1) for s in range(32)], 32, 1) == 0
+    assert _fits(lib, [(0, 32)], 1, 32, 64) == 1 and _fits(lib, [(0, 33)], 1, 32, 64) == 0
+    assert _fits(lib, [], 0, 257) == -1 and _fits(lib, [(0, 0)], 1, 1) == -1 and lib.ssd_resident_fits(None, 1, 0, 1, 256) == -1
