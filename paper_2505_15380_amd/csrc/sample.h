@@ -394,8 +394,7 @@ struct AcceptArgs {
   const int32_t* step_dev;  // when set: two words (low, high) of a device-resident cycle counter that is added to `step`, so
                          // that a captured graph of a cycle draws fresh uniforms at every replay
   int bump_step;         // the committing thread advances that counter (the last sampling kernel of a cycle without drafts)
-  int bump_launch;       // this kernel follows a forward on a.kv: the committing thread advances the cache's launch number
-  uint32_t publish;      // and leaves this in the mirror, where it is not 0
+  uint32_t launch;       // not 0: this kernel follows a forward on a.kv, the committing thread advances the cache's launch number (kv_publish_forward)
   int slot_base;         // r_i uses slot slot_base + i - 1, the emitted token slot_base + K
   int B, K, V;
   float beta;
@@ -547,7 +546,7 @@ __device__ __forceinline__ void accept_seq(const AcceptArgs a, const int b, cons
   if (a.kv.len == nullptr) return;
   if (solo) {                                              // kv_truncate + kv_publish on the values read at the start
     if (tid == 0) {
-      if (a.bump_launch && b == 0) { a.kv.ctl[3] = st_launch + 1; kv_publish_forward(a.kv, a.publish); }
+      if (a.launch && b == 0) { a.kv.ctl[3] = st_launch + 1; kv_publish_forward(a.kv, a.launch); }
       if (a.bump_step && a.step_dev) {
         const uint64_t nx = step - a.step + 1;
         ((int32_t*)a.step_dev)[0] = (int32_t)(uint32_t)nx;
@@ -588,7 +587,7 @@ __device__ __forceinline__ void accept_seq(const AcceptArgs a, const int b, cons
   const bool failed = *a.kv.err != 0;                      // the forward did not finish: commit nothing
   if (tid == 0) {
     *a.ticket = 0;
-    if (a.bump_launch) kv_bump_launch(a.kv, a.publish);
+    if (a.launch) kv_bump_launch(a.kv, a.launch);
     if (a.bump_step && a.step_dev) {
       const uint64_t nx = step - a.step + 1;
       ((int32_t*)a.step_dev)[0] = (int32_t)(uint32_t)nx;
@@ -631,15 +630,15 @@ __global__ void __launch_bounds__(SBLOCK) k_warp_accept(WarpArgs w, AcceptArgs a
 // ------------------------------------------------------------------------------------------ small state kernels
 // Truncate one sequence and (optionally) set its pending token from a value or from device memory.  new_len >= 0 is a
 // rollback: a target beyond the cached length is refused (the state stays, KV_ERR_ROLLBACK is raised).  add_len is
-// the commit of a prefill chunk.  after_forward: the kernel follows a forward on this cache (advances its launch number;
+// the commit of a prefill chunk.  after_forward (kv_publish_forward's `launch`): the kernel follows a forward on this cache (advances its launch number;
 // commits nothing if that forward did not finish).
 __global__ void __launch_bounds__(BLOCK) k_kv_set(KvView kv, int seq, int new_len, int add_len, int set_pending, int pending_value,
-                                                  const int32_t* pending_ptr, int after_forward, uint32_t publish) {
+                                                  const int32_t* pending_ptr, uint32_t after_forward) {
   const int tid = threadIdx.x, len = kv.len[seq], own = kv.owned[seq], top = kv.ctl[0];
   const bool failed = *kv.err != 0, refused = new_len > len;
   const int target = new_len >= 0 ? new_len : len + add_len, keep = ceil_div(target, kv.bt);
   __syncthreads();                                         // every thread has read the state
-  if (tid == 0 && after_forward) kv_bump_launch(kv, publish);
+  if (tid == 0 && after_forward) kv_bump_launch(kv, after_forward);
   if (failed || refused) {
     if (tid == 0) {
       if (!failed) kv.ctl[1] |= KV_ERR_ROLLBACK;
@@ -667,11 +666,15 @@ __global__ void k_kv_follow(KvView kv, int n_seqs, int K, const int32_t* n_acc, 
                             const int32_t* x, int32_t* step_dev, int replayed) {
   __shared__ int w16[16];
   const int s = threadIdx.x;
-  if (replayed && s == 0) kv.mirror[2 * kv.max_seqs + MIRROR_CYCLE] = ++kv.ctl[6];
   if (step_dev && s == 0) {                                // last kernel of a captured cycle: the next replay is the next step
+    const int32_t cycles = kv.ctl[6] + 1;
     const uint64_t nx = ((uint64_t)(uint32_t)step_dev[0] | ((uint64_t)(uint32_t)step_dev[1] << 32)) + 1;
     step_dev[0] = (int32_t)(uint32_t)nx;
     step_dev[1] = (int32_t)(uint32_t)(nx >> 32);
+    if (replayed) {
+      kv.ctl[6] = cycles;
+      kv.mirror[2 * kv.max_seqs + MIRROR_CYCLE] = cycles;
+    }
   }
   if (*kv.err) {
     if (s == 0) kv_publish_flags(kv);

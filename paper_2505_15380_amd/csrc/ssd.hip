@@ -365,7 +365,7 @@ static const void* resident_key(hipStream_t st) {
 
 static bool resident_running(const ssd_kv* kv) {
   const volatile int32_t* w = kv->mirror_host + 2 * kv->max_seqs;
-  return (int32_t)((uint32_t)w[MIRROR_FORWARD] - kv->run.forward) < 0 || (int32_t)((uint32_t)w[MIRROR_CYCLE] - kv->run.cycle) < 0;
+  return (((uint32_t)w[MIRROR_FORWARD] - kv->run.forward) & 0x40000000u) != 0 || (int32_t)((uint32_t)w[MIRROR_CYCLE] - kv->run.cycle) < 0;
 }
 
 struct ResidentLaunch {
@@ -399,7 +399,8 @@ struct ResidentLaunch {
     run.device = device;
     run.stream = key;
     if (cycle) { run.cycle = ++kv->cycles; return; }
-    if (++kv->forwards == 0) ++kv->forwards;
+    kv->forwards = (kv->forwards + 1) & 0x7FFFFFFFu;       // (31 bits reach the kernels)
+    if (kv->forwards == 0) kv->forwards = 1;
     run.forward = kv->publish = kv->forwards;
   }
   // Does `o` run something that a launch on `kv` has to mind?
@@ -1437,7 +1438,7 @@ extern "C" int ssd_prefill(ssd_model* m, ssd_kv* kv, int seq, const int32_t* dev
   if (seq < 0 || seq >= kv->max_seqs) return fail(SSD_EINVAL, "sequence %d out of range", seq);
   if ((rc = kv_check_flags(kv))) return rc;
   hipStream_t st = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, 0, 0, 0, 0, (const int32_t*)nullptr, 0, 0u);
+  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, 0, 0, 0, 0, (const int32_t*)nullptr, 0u);
   LAUNCH_CHECK();
   kv->len_ub[seq] = 0;
   kv->npend_ub[seq] = 0;
@@ -1446,11 +1447,11 @@ extern "C" int ssd_prefill(ssd_model* m, ssd_kv* kv, int seq, const int32_t* dev
   for (int i = 0; i < n - 1; i += chunk) {
     const int R = std::min(chunk, n - 1 - i);
     if ((rc = forward_any(m, kv, seq, 1, R, 0, dev_tokens + i, 0, false, st))) return rc;
-    hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, -1, R, 0, 0, (const int32_t*)nullptr, 1, kv->publish);
+    hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, -1, R, 0, 0, (const int32_t*)nullptr, 2 * kv->publish + 1);
     LAUNCH_CHECK();
     kv->len_ub[seq] += R;
   }
-  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, -1, 0, 1, 0, dev_tokens + (n - 1), 0, 0u);
+  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, -1, 0, 1, 0, dev_tokens + (n - 1), 0u);
   LAUNCH_CHECK();
   kv->npend_ub[seq] = 1;
   return SSD_OK;
@@ -1503,7 +1504,7 @@ static int step(ssd_model* m, ssd_kv* kv, int B, int K, const int32_t* dev_x, co
     LAUNCH_CHECK();
   }
   a.pd = dev_pd; a.x = dev_x; a.uniforms = nullptr; a.seed = cfg->seed; a.step = step_ctr;
-  a.step_dev = step_dev; a.bump_step = bump_step ? 1 : 0; a.bump_launch = 1; a.publish = kv->publish;
+  a.step_dev = step_dev; a.bump_step = bump_step ? 1 : 0; a.launch = 2 * kv->publish + 1;
   a.B = B; a.K = K; a.V = V; a.beta = cfg->beta;
   a.n_acc = dev_n; a.next_tok = dev_next; a.tok_stride = next_stride; a.flags = nullptr;
   a.kv = kv->v; a.seq0 = 0;
@@ -1640,7 +1641,7 @@ extern "C" int ssd_kv_rollback(ssd_kv* kv, int seq, int new_len, int pending_tok
     if (new_len < 0 || new_len > kv->len_ub[seq])
       return fail(SSD_EINVAL, "rollback to %d but sequence %d holds %d positions", new_len, seq, kv->len_ub[seq]);
   }
-  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, new_len, 0, 1, pending_token, (const int32_t*)nullptr, 0, 0u);
+  hipLaunchKernelGGL(k_kv_set, dim3(1), dim3(BLOCK), 0, st, kv->v, seq, new_len, 0, 1, pending_token, (const int32_t*)nullptr, 0u);
   LAUNCH_CHECK();
   kv->len_ub[seq] = new_len;
   kv->npend_ub[seq] = 1;
