@@ -335,7 +335,7 @@ struct ssd_kv {
   bool capturing = false;          // a cycle is being captured on this cache: no synchronisation, no fallback kernels
   int last_path = 0;               // 1 per-operator launches, 2 barrier kernel, 3 barrier-free kernel, 4 the same with attention without parts, 5 fp32 in one launch
   bool last_whole = false;
-  int last_wgs = 0;                // workgroups of the last barrier-free forward
+  int last_wgs = 0;                // workgroups of the last barrier-free forward; of the largest one of a cycle that is being captured
   int df_sb = 0;             // SSD_DF_FLIGHT=2|4|10|16|18: instantiation of the barrier-free forward up to 8 rows (0: chosen per launch)
   // host
   int32_t* mirror_host;
@@ -1186,7 +1186,7 @@ static int forward_dataflow(const ssd_model* m, ssd_kv* kv, Rows rows, int B, in
   a.recip_d = cdiv(65536, cdiv(c.d_model, 512)); a.recip_q = cdiv(65536, cdiv(nqd, 512));
   a.bar = kv->bar;
   a.trace = kv->trace_on ? kv->trace : nullptr;
-  kv->last_wgs = G;
+  kv->last_wgs = kv->capturing ? std::max(kv->last_wgs, G) : G;
   const ResidentLaunch order(kv, st, G);
   if (!order.admitted) return -1;
   ProfScope ps(PROF_PERSISTENT, st);
@@ -1839,6 +1839,7 @@ static int cycle_capture(ssd_cycle* c, hipStream_t st) {
     c->kv->npend_ub[s] = 1; c->kv_d->npend_ub[s] = 2;      // the first draft step of a cycle may owe two tokens
   }
   c->kv->capturing = c->kv_d->capturing = true;
+  c->kv->last_wgs = c->kv_d->last_wgs = 0;
   auto restore = [&]() { c->kv->len_ub = lt; c->kv_d->len_ub = ld; c->kv->npend_ub = nt; c->kv_d->npend_ub = nd;
                          c->kv->launch_no = ln_t; c->kv_d->launch_no = ln_d; c->kv->capturing = c->kv_d->capturing = false; };
   hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
