@@ -107,8 +107,8 @@ int    ssd_model_destroy(ssd_model* m);
 /* ---- KV cache + sequence state ----------------------------------------------------------------------
  * Pool layout (dtype elements): keys [layer][0][block][kv_head][token_in_block][head_dim], stored after the
  * rotary embedding; values [layer][1][block][kv_head][head_dim][token_in_block] (token-minor, the order the
- * matrix-core attention reads them in).  The pool must hold finite values (e.g. zeros) when handed over.  `max_rows` bounds the rows of one forward per sequence (K+1 for verify, the
- * chunk of a prefill); max_seqs*max_rows <= 1024.  A bf16 cache with max_seqs 1 and max_rows 1024, the most, takes a prompt in launches of up to
+ * matrix-core attention reads them in).  The pool must hold finite values (e.g. zeros) when handed over.  max_seqs*max_rows <= 1024 bounds the rows of one forward: `max_rows` per sequence of a
+ * verification (K+1), all of them of a prompt, which takes launches of up to max_seqs*max_rows rows.  A bf16 cache with max_seqs 1 and max_rows 1024, the most, takes a prompt in launches of up to
  * 4096 rows where the model's attention of so many rows needs no merge (head_dim 64 or 128, 16-token blocks, more than 8 query heads on 256
  * compute units); ssd_kv_workspace_bytes counts the room, as far as max_positions has use for it.  `pending_cap` is 1 for a target cache and 2 for a draft
  * cache (a draft may owe two tokens after a fully accepted cycle).  Blocks are handed out lowest id first;

@@ -1419,16 +1419,17 @@ static int check_sample(const ssd_sample_config* s) {
 }
 
 // ------------------------------------------------------------------------------------------------ prefill
-// Rows of a prompt's launches: the caller's max_rows, or what the buffers hold where that is more and a launch of more than 1024 rows attends in one part
-// whatever its rows (its tiles alone are for more than half of the device: pick_attn_mfma), since the buffers of attention's partials have room for
-// max_rows.  Every launch of a layer costs 5 to 10 us beside its loop, and one
+// Rows of a prompt's launches: as many as the buffers have room for, max_seqs * max_rows; where that is 1024 for one sequence up to prompt_rows, if a launch of more than 1024
+// rows attends in one part whatever its rows (its tiles alone are for more than half of the device: pick_attn_mfma), since the buffers of attention's partials have
+// room for 1024.  Every launch of a layer costs 5 to 10 us beside its loop, and one
 // of 1024 rows fills the device once, mostly not evenly: 4096 positions of the 0.5B shape took 10.62 ms in four launches and take 7.88 in one (8.85 with the
-// tiles of 1024 rows), 1501 of the 1.5B shape 9.55 ms and 8.41.
+// tiles of 1024 rows), 1501 of the 1.5B shape 9.55 ms and 8.41.  8 layers of the 0.5B shape, 300 and 1000 positions into a cache of 16 sequences of 64 rows: 1509 and 4997 us in
+// launches of 64 rows, 382 and 699 as one.
 static int prompt_chunk(const ssd_kv* kv) {
   const ssd_model_config& c = kv->m->c;
   const int tiles = cdiv(MAX_ROWS * (c.n_q_heads / c.n_kv_heads), 16);
   const bool one_part = kv->attn_mfma && kv->v.bt == 16 && cdiv(tiles, 4) * c.n_kv_heads > kv->cus / 2;
-  return one_part ? std::max(kv->max_rows, kv->prompt_rows) : kv->max_rows;
+  return one_part ? kv->prompt_rows : kv->max_seqs * kv->max_rows;
 }
 
 extern "C" int ssd_prefill(ssd_model* m, ssd_kv* kv, int seq, const int32_t* dev_tokens, int n, void* stream) {

@@ -8,7 +8,7 @@ from . import binding as B
 class SSDSession:
     def __init__(self, target_shape, target_w, draft_shape, draft_w, n_seqs, K, max_positions, cfg, dcfg,
                  block_tokens=16, n_blocks=None, max_rows=None, device="cuda"):
-        if max_rows is None:                     # rows per sequence and launch: prefill chunks (the library takes 1024 rows in all; with 1024 a prompt takes up to 4096)
+        if max_rows is None:                     # rows per sequence of a verification; a prompt's launches have n_seqs * max_rows (the library takes 1024 in all; for one sequence a prompt takes up to 4096)
             max_rows = max(K + 1, 1024 // n_seqs)
         self.K, self.n_seqs = K, n_seqs
         self.cfg, self.dcfg = cfg, dcfg

@@ -91,6 +91,46 @@ def test_which_launches_a_prompt_takes(nq, rows, launches):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("nq,nkv,hd,seqs,rows,positions,launches", [(2, 1, 64, 4, 16, 150, 3), (9, 1, 64, 4, 16, 128, 2), (4, 2, 128, 16, 64, 1030, 2),
+                                                                     (9, 9, 64, 3, 300, 905, 2), (2, 2, 32, 16, 2, 70, 3), (12, 12, 64, 8, 128, 1025, 2)])
+def test_prompts_into_caches_of_several_sequences(nq, nkv, hd, seqs, rows, positions, launches):
+    """A prompt takes launches of max_seqs * max_rows rows, as many as the buffers have room for, whatever the heads: also of a sequence that is not the first,
+    over a cache that others have blocks in.  Against the oracle with the cache's format, as check_prompt."""
+    import paper_2505_15380_amd as ssd
+    from tests.parity import Pair, loud_weights
+    shape = _shape(nq, nkv, hd, 64, 96)
+    pair = Pair(None, 0, positions + 16, max_seqs=seqs, max_rows=rows, n_blocks=2 * (positions // 16 + 2), shape=shape, weights=loud_weights(shape, 23), store="bf16")
+    pair.prefill(0, np.random.default_rng(24).integers(0, 43, 40))
+    ssd.ssd_profile_begin("qkv")
+    try:
+        pair.prefill(seqs - 1, np.random.default_rng(25).integers(0, 43, positions + 1))
+    finally:
+        _, count = ssd.ssd_profile_end()
+    # (a last launch of at most 16 rows that is one for all operators has no projections of its own)
+    assert count in (2 * launches, 2 * (launches - 1)) and (count == 2 * launches or (positions - 1) % (seqs * rows) < 16)
+    for seq in (0, seqs - 1):
+        pair.check_rows(seq, 2.0 ** -7)
+        pair.check_state(seq, 2.0 ** -4)
+    pair.check_free_stack()
+
+
+@pytest.mark.gpu
+def test_fp32_prompts_have_the_same_bits_in_any_launches():
+    import paper_2505_15380_amd as ssd
+    shape = si.model_shape("tiny")
+    w = ssd.upload_weights(shape, si.make_weights(shape, 150))
+    toks = torch.from_numpy(np.random.default_rng(26).integers(0, shape["vocab"], 301).astype(np.int32)).cuda()
+    got = []
+    for seqs, rows in ((1, 300), (1, 16), (2, 9), (16, 64), (64, 1)):
+        model = ssd.Model(shape, w, 320)
+        kv = ssd.KVCache(model, seqs, rows, 20, 16)
+        ssd.ssd_prefill(model, kv, 0, toks)
+        torch.cuda.synchronize()
+        got.append([kv.gather(0, l, 300) for l in range(shape["n_layers"])])
+    assert all(np.array_equal(a[l][i], got[0][l][i]) for a in got for l in range(shape["n_layers"]) for i in (0, 1))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("nq,nkv,hd,rows,positions", [(16, 1, 64, 1024, 3301), (14, 2, 64, 1024, 1501), (12, 2, 128, 1024, 1501), (12, 2, 128, 500, 1499)])
 def test_prompt_attention_where_later_scores_exceed_the_first(nq, nkv, hd, rows, positions):
     """Scores of spread 10, so that the weights' reference moves after a row's first chunk, in the forms of long prompts: eight tiles by two key groups (831
