@@ -371,10 +371,10 @@ def test_prefill_in_large_chunks_then_verify(shape_name, max_rows, n_tokens):
         pair.check_state(0, 2e-2, layers=[shape["n_layers"] - 1])
 
 
-@pytest.mark.parametrize("nq,nkv,rows,positions", [(10, 2, 1024, 3099), (4, 2, 1024, 3099), (7, 1, 560, 4480)])
+@pytest.mark.parametrize("nq,nkv,rows,positions", [(10, 2, 1023, 3099), (4, 2, 1024, 3099), (7, 1, 560, 4480)])
 def test_prompt_attention_where_later_scores_exceed_the_first(nq, nkv, rows, positions):
     """A prompt in launches of `rows` whose scores have a spread of 10, so that the weights' reference of many
-    rows moves after their first chunk.  Ten query heads over two kv heads: one part per launch, of 16 chunks by two key groups, then of 32 and
+    rows moves after their first chunk.  Ten query heads over two kv heads (launches of 1023 rows: of 1024 it would be one launch): one part per launch, of 16 chunks by two key groups, then of 32 and
     48 by four with the reference that rarely moves; four heads: two tiles by four key groups, two parts of 8, 16 and 24 chunks; seven heads over
     one kv head: the last launch's 70 chunks in parts of 20, by four key groups (18, a quarter, would not be whole rounds of the groups).
     Keys and values of the second layer follow from the attention of the first: against the oracle with the cache's format.  Where a key rounds the other way on one side (one element in 4000: fp32

@@ -53,18 +53,20 @@ def test_sizes_reach_the_tiles_they_name(lib, size, tiles, unsplit):
 
 def test_blocks_of_a_prompts_launch_cover_the_output_once(lib):
     plan, blocks = (C.c_int * 4)(), (C.c_int * (3 * 65536))()
-    for rows in (1, 1024, 1025, 1501, 2500, 4095, 4096):
-        for n, k in ((896, 896), (1152, 896), (2048, 1536), (4864, 896), (8960, 1536), (896, 4864), (1536, 8960), (352, 64), (96, 32)):
+    for rows in (1, 1024, 1025, 1501, 2048, 2049, 2500, 4095, 4096):
+        for n, k in ((896, 896), (1152, 896), (2048, 1536), (4864, 896), (8960, 1536), (896, 4864), (1536, 8960), (352, 64), (96, 32), (96, 8960), (352, 8960)):
             for kind in (QKV, O, GATE_UP, DOWN):
                 for cus in (256, 64):
                     wgs = lib.ssd_prompt_gemm_plan(kind, rows, n, k, cus, plan, blocks, 65536)
                     assert 0 < wgs <= 65536
                     _, rt, ct, slices = plan
                     slices = slices or 1
-                    assert slices * rows <= 16 * max(1024, rows) and slices <= 8
+                    assert slices * rows <= 16 * 1024 and slices <= 8      # (the partials' room)
                     got = sorted(tuple(blocks[3 * w:3 * w + 3]) for w in range(wgs) if blocks[3 * w] >= 0)
                     tiles = -(-n // 16) * (2 if kind == GATE_UP else 1)
                     assert got == sorted((c, r, s) for s in range(slices) for c in range(-(-tiles // ct)) for r in range(-(-rows // (16 * rt))))
+    for rows, slices in ((1025, 8), (2048, 8), (2049, 4), (4096, 4)):     # sizes that would rather have eight where eight do not fit
+        assert lib.ssd_prompt_gemm_plan(DOWN, rows, 96, 8960, 256, plan, None, 0) > 0 and plan[3] == slices
     assert lib.ssd_prompt_gemm_plan(QKV, 4097, 32, 32, 256, plan, None, 0) == -1 and lib.ssd_prompt_gemm_plan(5, 16, 32, 32, 256, plan, None, 0) == -1
     assert lib.ssd_prompt_gemm_plan(QKV, 16, 32, 32, 256, None, None, 0) == -1 and lib.ssd_prompt_gemm_plan(QKV, 16, 32, 32, 256, plan, None, 1) == -1
 

@@ -34,10 +34,10 @@ def _shape(name):
 @pytest.mark.parametrize("name,lens,K", [
     ("mini128", [40], 0), ("mini128", [63], 1), ("mini128", [1010], 4), ("mini128", [1530], 7), ("mini128", [2040], 12),
     ("mini128", [5, 130], 5), ("mini128", [1535, 20, 300], 3), ("odd", [33], 2), ("odd", [150], 8), ("odd", [70], 15), ("odd", [1100], 3),
-    ("one_layer", [20], 0), ("one_layer", [50], 7), ("one_layer", [18], 12)])
+    ("one_layer", [20], 0), ("one_layer", [50], 7), ("one_layer", [18], 12), ("one_layer", [45], 15), ("mini128", [5116], 7)])
 def test_wide_forward_against_the_oracle(name, lens, K):
     """Two verifications each, and the cached keys and values after each.  Rows 1 to 16 (sums of 8, 32 and 64 columns, both halves of an operand in one
-    instruction or in two), new rows within a chunk, across chunks and across the end of the only part.  With the cache's format in the oracle
+    instruction or in two), new rows within a chunk, across chunks, across the end of the only part and into a sixth part (five are merged in one flight).  With the cache's format in the oracle
     what is left are fp32 sums and keys that round the other way, as in test_mini_bf16_parity_with_matched_cache_format, whose bounds these are."""
     from tests.parity import Pair, verify_parity_step
     shape = _shape(name)
@@ -54,7 +54,7 @@ def test_wide_forward_against_the_oracle(name, lens, K):
         pair.check_free_stack()
 
 
-@pytest.mark.parametrize("name,K,rows", [("mini128", 7, 8), ("mini128", 12, 13), ("odd", 15, 16), ("one_layer", 5, 6)])
+@pytest.mark.parametrize("name,K,rows", [("mini128", 7, 8), ("mini128", 12, 13), ("odd", 15, 16), ("one_layer", 5, 6), ("one_layer", 15, 16)])
 def test_wide_rows_of_a_prompt_with_loud_weights(name, K, rows):
     """A prompt in launches of `rows` rows, on weights with which a lost piece of a tile counts: each cached row within one step of bf16 of the oracle's."""
     from tests.parity import Pair, loud_weights
@@ -68,7 +68,7 @@ def test_wide_rows_of_a_prompt_with_loud_weights(name, K, rows):
 
 
 @pytest.mark.parametrize("name,K,cached", [("mini128", 7, 60), ("mini128", 7, 1514), ("mini128", 7, 1530), ("mini128", 12, 1535), ("mini128", 4, 2046),
-                                           ("one_layer", 4, 100), ("odd", 12, 1020)])
+                                           ("one_layer", 4, 100), ("one_layer", 15, 120), ("odd", 12, 1020), ("mini128", 7, 5116), ("mini128", 15, 6140)])
 def test_wide_rows_verified_together_have_the_bits_of_rows_decoded_alone(name, K, cached):
     from tests.test_gpu_row_bits import _target, _verify_logits
     import paper_2505_15380_amd as ssd

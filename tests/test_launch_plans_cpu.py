@@ -86,7 +86,7 @@ def test_placement_of_blocks_on_the_xcds(lib, kind):
 
 @pytest.mark.parametrize("hd,nq,nkv,seqs,rows,positions,want", [
     # test_prompt_attention_where_later_scores_exceed_the_first
-    (64, 10, 2, 1, 1024, 1024, (4, 2, 16)), (64, 10, 2, 1, 1024, 3072, (4, 4, 48)), (64, 4, 2, 1, 1024, 1024, (2, 4, 8)),
+    (64, 10, 2, 1, 1023, 1023, (4, 2, 16)), (64, 10, 2, 1, 1023, 2046, (4, 4, 32)), (64, 10, 2, 1, 1023, 3069, (4, 4, 48)), (64, 4, 2, 1, 1024, 1024, (2, 4, 8)),
     (64, 4, 2, 1, 1024, 3072, (2, 4, 24)), (64, 7, 1, 1, 560, 3920, (4, 2, 16)), (64, 7, 1, 1, 560, 4480, (4, 4, 20)),
     # batches
     (64, 14, 2, 16, 7, 0, (4, 2, 8)), (64, 14, 2, 64, 8, 0, (2, 4, 64)), (128, 12, 2, 8, 9, 0, (4, 2, 4))])
