@@ -1,9 +1,9 @@
 """Latency of a prompt prefill (the decoder forward over the prefix that fills the cache before the first SSD cycle).
 
-    python -m paper_2505_15380_amd.bench_prefill [--workload half_b_k4] [--tokens 4096] [--rows 1024] [--iters 3]
+    python -m paper_2505_15380_amd.bench_prefill [--workload half_b_k4] [--tokens 4096] [--rows 1024] [--seqs 1] [--iters 3]
 
-Prefills `--tokens` positions of the workload's target shape in launches of up to `--rows` rows, 1024 meaning up to 4096 (every operator its
-own launch: more rows than the persistent kernels take) and prints one JSON line: the whole prefill's time, tokens/s,
+Prefills `--tokens` positions of the workload's target shape into a cache of `--seqs` sequences and `--rows` rows, in launches of as many rows as that
+has room for, 1024 for one sequence meaning up to 4096 (every operator its own launch: more rows than the persistent kernels take) and prints one JSON line: the whole prefill's time, tokens/s,
 the time per operator kind from the library's own event pairs, and the GEMM rate those imply.  This is the command the
 prefill's rocprofv3 summary under profiles/ was taken with; `bench.py` stays the headline benchmark."""
 import argparse
@@ -20,12 +20,13 @@ def main():
     ap.add_argument("--workload", default="half_b_k4")
     ap.add_argument("--tokens", type=int, default=4096)
     ap.add_argument("--rows", type=int, default=1024)
+    ap.add_argument("--seqs", type=int, default=1)
     ap.add_argument("--iters", type=int, default=3)
     print(json.dumps(measure(ap.parse_args())))
 
 
 def measure(args, weights=None):
-    """The record of one prefill (args: workload, tokens, rows, iters).  `weights`: the target's tensors when the caller has
+    """The record of one prefill (args: workload, tokens, rows, iters and, where it is not 1, seqs).  `weights`: the target's tensors when the caller has
     them already."""
     import torch
     import paper_2505_15380_amd as ssd
@@ -38,7 +39,7 @@ def measure(args, weights=None):
     toks = torch.from_numpy(si.make_prefix(shape, n // 4, n - n // 4, wl["seeds"]["prefix"])).cuda()
     bt = 16
     model = ssd.Model(shape, ssd.upload_weights(shape, w), n + 64)
-    kv = ssd.KVCache(model, 1, args.rows, (n + 64) // bt + 2, bt, (n + 64) // bt + 1, 1)
+    kv = ssd.KVCache(model, getattr(args, "seqs", 1), args.rows, (n + 64) // bt + 2, bt, (n + 64) // bt + 1, 1)
     ssd.ssd_prefill(model, kv, 0, toks)                   # warm-up; a prefill of a sequence starts it over
     torch.cuda.synchronize()
     stream = torch.cuda.current_stream()

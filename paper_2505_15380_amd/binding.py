@@ -219,8 +219,8 @@ class KVCache:
                     n_owned=own.value, table=list(table)[:own.value])
 
     def last_forward_path(self):
-        """1 one launch per operator, 2 persistent kernel with grid barriers, 3 barrier-free persistent kernel,
-        4 the same with the attention of a short prefix done without parts."""
+        """1 one launch per operator, 2 persistent kernel with grid barriers, 3 barrier-free persistent kernel (head size 64 or 128),
+        4 the same with the attention of a short prefix done without parts, 5 the fp32 forward of few rows as one launch."""
         return load_library().ssd_kv_last_forward_path(self.handle)
 
     def clear_error(self):

@@ -482,7 +482,7 @@ def test_captured_cycle_replays_like_the_eager_cycle(workload, K, cycles):
     (shapes are captured 256 positions ahead).  The eager cycle is the one the lockstep tests hold against the oracle."""
     import paper_2505_15380_amd as ssd
     side = torch.cuda.Stream()                             # HIP cannot capture the default stream
-    if cycles == 0:                                        # fp32 storage runs one launch per operator: no capture
+    if cycles == 0:                                        # only the bf16 barrier-free forward of head size 64 is captured
         sess, _ = make_session(workload, K, beta=0.2, steps=4)
         torch.cuda.synchronize()
         with pytest.raises(ssd.SSDError) as e:
