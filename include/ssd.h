@@ -23,8 +23,9 @@
  *     compute unit, wait for each other.  Two such launches of different handles on two streams of a process overlap if every XCD of the
  *     device has the compute units for its eighth of both (32 of 256; a model of width 896 takes 28 to 32 of them, 19 with path 2, one of width 128 in fp32 2 to 13), else the later
  *     call waits on the host until those that it does not fit beside are over (ssd_resident_fits).  After a second of that, with whatever else their streams have before them, it runs
- *     as one launch per operator (path 1), a captured cycle call by call.  Graphs that a caller captures around these calls, and other processes on the same device, are not
- *     seen: there each launch may hold units that the other one waits for until their bounded waits give up, which both report as SSD_EHIP; order them.
+ *     as one launch per operator (path 1), a captured cycle call by call.  Calls that a caller captures in graphs of its own run as one launch per
+ *     operator too with head_dim 128 or fp32 storage, so that such graphs can be replayed on any streams; with bf16 and head_dim 64 they wait, and neither replays nor other
+ *     processes on the same device are seen: there each launch may hold units that the other one waits for until their bounded waits give up, which both report as SSD_EHIP; order them.
  *   - Return value: SSD_OK (0) or a negative error code; ssd_last_error() gives a message for the last
  *     failure on the calling thread.  Arguments are validated on the host before anything is launched;
  *     nothing throws or aborts across this boundary.

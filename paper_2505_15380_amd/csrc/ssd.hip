@@ -349,8 +349,8 @@ struct ssd_kv {
 // takes 1.0 to 1.4 us of its stream's time (of 22 for the smallest forward).  us for a step of each of two streams in turn, with events and stream waits -> held back here:
 // two 0.5B targets 669 -> 659 (one after the other 647), two drafts 166 -> 156 (144), a 0.5B target and the smallest one, which fit, 393 -> 323.  A launch that has been held back for RESIDENT_WAIT_MS, behind whatever else these streams
 // have before theirs, is not admitted, nor are others while that lasts: the caller takes launches that do not wait.
-// The mutex is held until the launch is enqueued, so that no other thread's comes in between.  (A launch on a stream that is being captured is not looked at: its
-// graphs are the caller's to order.)
+// The mutex is held until the launch is enqueued, so that no other thread's comes in between.  Where a caller captures the calls, replays are not seen: there head size
+// 128 and fp32, whose launches per operator can be replayed on any streams at once and any number of times, keep those; with head size 64 the graphs are the caller's to order.
 static std::mutex g_resident_mutex;
 static ssd_kv* g_resident = nullptr;                       // caches that have had such a launch
 constexpr int RESIDENT_WAIT_MS = 1000;
@@ -376,7 +376,10 @@ struct ResidentLaunch {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipGetDevice(&device) != hipSuccess) return;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) { (void)hipGetLastError(); return; }      // (the default stream beside a capture: the launch will say so)
-    if (cs != hipStreamCaptureStatusNone) return;
+    if (cs != hipStreamCaptureStatusNone) {                // replays in a caller's graph are not seen: only the forms that have always been captured there
+      admitted = kv->capturing || !(kv->wide || kv->small);
+      return;
+    }
     const void* key = resident_key(st);
     std::chrono::steady_clock::time_point until{};
     while (!fits(kv, device, key, wgs)) {

@@ -274,3 +274,51 @@ def test_a_stream_that_was_destroyed_is_not_asked(monkeypatch):
             assert _verify_logits(model, kv, 1, x)[1] == 3
         assert hip.hipStreamDestroy(st) == 0
         assert _verify_logits(model, kv, 1, x)[1] == 3
+
+
+@pytest.mark.parametrize("name", ["mini128", "one_layer", "tiny"])
+def test_calls_in_a_callers_graph_run_per_operator(name, monkeypatch):
+    """A graph that the caller captures may be replayed beside others, which the library does not see: head size 128 and fp32 have no launches there that wait. Several
+    replays, with eager calls and waits in between, against the launches per operator of a second cache."""
+    import paper_2505_15380_amd as ssd
+    from tests.test_gpu_row_bits import _target
+    shape = si.model_shape("tiny") if name == "tiny" else _shape(name)
+    K, V, caches = 3, shape["vocab"], []
+    x = torch.from_numpy(np.random.default_rng(7).integers(0, V, (1, K)).astype(np.int32)).cuda()
+    pd = torch.full((1, K, V), 1.0 / V, device="cuda")
+    cfg = ssd.sample_config(beta=0.3, seed=3)
+    for mode in ("", "barrier"):
+        if mode:
+            monkeypatch.setenv("SSD_FORWARD", mode)
+        model, kv = _target(shape, [70], 32, extra=200)
+        out = dict(n_accepted=torch.zeros(1, dtype=torch.int32, device="cuda"), next_token=torch.zeros(1, dtype=torch.int32, device="cuda"), probs=None,
+                   logits=torch.zeros(1, K + 1, V, device="cuda"))
+        caches.append((model, kv, out))
+    (model, kv, out), (model1, kv1, out1) = caches
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        ssd.ssd_verify(model, kv, 1, x, pd, K, cfg, 0, out=out)
+        assert kv.last_forward_path() == (5 if name == "tiny" else 3)
+    ssd.ssd_verify(model1, kv1, 1, x, pd, K, cfg, 0, out=out1)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        ssd.ssd_verify(model, kv, 1, x, pd, K, cfg, 1, out=out)
+    assert kv.last_forward_path() == 1
+    for replay in range(5):
+        with torch.cuda.stream(side):
+            graph.replay()
+        ssd.ssd_verify(model1, kv1, 1, x, pd, K, cfg, 1, out=out1)
+        torch.cuda.synchronize()
+        assert int(out["next_token"][0]) == int(out1["next_token"][0]) and kv.state(0)["len"] == kv1.state(0)["len"], replay
+        if name == "tiny":
+            assert torch.equal(out["logits"], out1["logits"]), replay
+        else:
+            assert float((out["logits"] - out1["logits"]).norm()) <= 1e-2 * float(out1["logits"].norm()), replay
+        if replay == 2:                                      # eager work on the captured cache between replays
+            with torch.cuda.stream(side):
+                ssd.ssd_verify(model, kv, 1, x, pd, K, cfg, 9, out=out)
+            assert kv.last_forward_path() == (5 if name == "tiny" else 3)
+            ssd.ssd_verify(model1, kv1, 1, x, pd, K, cfg, 9, out=out1)
+            torch.cuda.synchronize()
