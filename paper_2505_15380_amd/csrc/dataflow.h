@@ -398,7 +398,8 @@ __device__ __forceinline__ bool stage_operand_wide(const DArgs& a, const uint32_
     h0 = ld_val(x0);
     h1 = ld_val(x1);
   }
-  for (int p0 = quarter; p0 < pieces; p0 += 4 * FL) {
+  int p0 = quarter;
+  do {                                                     // (a quarter without a piece, one or two in all, still awaits its threads' residual words)
     auto row = [&](int u) { return (p0 + 4 * u) * recip >> 16; };      // (exact: fewer than 2^8 pieces)
     auto col = [&](int u) { return (p0 + 4 * u - row(u) * per_row) * 512; };
     uint32_t at = (uint32_t)c * 4u;
@@ -429,7 +430,8 @@ __device__ __forceinline__ bool stage_operand_wide(const DArgs& a, const uint32_
         *(uint2*)to = make_uint2(__builtin_amdgcn_perm(v[u][1], v[u][0], 0x05040100u), __builtin_amdgcn_perm(v[u][3], v[u][2], 0x05040100u));
         *(uint2*)(to + 4) = make_uint2(__builtin_amdgcn_perm(v[u][1], v[u][0], 0x07060302u), __builtin_amdgcn_perm(v[u][3], v[u][2], 0x07060302u));
       }
-  }
+    p0 += 4 * FL;
+  } while (p0 < pieces);
   if (!RES) {
     if (tid < nS) sqs[tid] = __uint_as_float(w);
     for (int i = PBLOCK + tid; i < nS; i += PBLOCK) {      // (more than 512 sums)

@@ -28,13 +28,18 @@ def _shape(name):
         s.update(d_model=96, n_q_heads=3, n_kv_heads=1, d_ffn=32 * 301)
     if name == "one_layer":
         s.update(n_layers=1)
+    if name == "eight_heads":    # items of the output projection two to a workgroup, and one row's operands two pieces of 512 words: half of the threads have none
+        s.update(n_layers=3, n_q_heads=8, d_ffn=32 * 192)
+    if name == "four_heads":     # the same with two rows
+        s.update(n_layers=3, n_q_heads=4, d_ffn=32 * 200)
     return s
 
 
 @pytest.mark.parametrize("name,lens,K", [
     ("mini128", [40], 0), ("mini128", [63], 1), ("mini128", [1010], 4), ("mini128", [1530], 7), ("mini128", [2040], 12),
     ("mini128", [5, 130], 5), ("mini128", [1535, 20, 300], 3), ("odd", [33], 2), ("odd", [150], 8), ("odd", [70], 15), ("odd", [1100], 3),
-    ("one_layer", [20], 0), ("one_layer", [50], 7), ("one_layer", [18], 12), ("one_layer", [45], 15), ("mini128", [5116], 7)])
+    ("one_layer", [20], 0), ("one_layer", [50], 7), ("one_layer", [18], 12), ("one_layer", [45], 15), ("mini128", [5116], 7),
+    ("eight_heads", [40], 0), ("eight_heads", [40], 2), ("four_heads", [40], 1), ("four_heads", [30], 0)])
 def test_wide_forward_against_the_oracle(name, lens, K):
     """Two verifications each, and the cached keys and values after each.  Rows 1 to 16 (sums of 8, 32 and 64 columns, both halves of an operand in one
     instruction or in two), new rows within a chunk, across chunks, across the end of the only part and into a sixth part (five are merged in one flight).  With the cache's format in the oracle
@@ -68,7 +73,8 @@ def test_wide_rows_of_a_prompt_with_loud_weights(name, K, rows):
 
 
 @pytest.mark.parametrize("name,K,cached", [("mini128", 7, 60), ("mini128", 7, 1514), ("mini128", 7, 1530), ("mini128", 12, 1535), ("mini128", 4, 2046),
-                                           ("one_layer", 4, 100), ("one_layer", 15, 120), ("odd", 12, 1020), ("mini128", 7, 5116), ("mini128", 15, 6140)])
+                                           ("one_layer", 4, 100), ("one_layer", 15, 120), ("odd", 12, 1020), ("mini128", 7, 5116), ("mini128", 15, 6140),
+                                           ("eight_heads", 7, 60), ("four_heads", 3, 60)])
 def test_wide_rows_verified_together_have_the_bits_of_rows_decoded_alone(name, K, cached):
     from tests.test_gpu_row_bits import _target, _verify_logits
     import paper_2505_15380_amd as ssd
